@@ -17,8 +17,8 @@
  * code on failure (nothing is thrown, nothing aborts) and ctcbs_step may return the
  * positive CTCBS_DONE.  All device work is enqueued on the stream given at creation; the
  * only host synchronisations are inside ctcbs_create (end), ctcbs_finalize,
- * ctcbs_poll/ctcbs_peek/ctcbs_stats/ctcbs_profile_read; the optional periodic look of
- * ctcbs_step only waits for work enqueued two intervals earlier.
+ * ctcbs_poll/ctcbs_peek/ctcbs_stats/ctcbs_profile_read; with poll_every > 0 ctcbs_step also
+ * waits, without draining the stream, until the device is within a few steps of the host.
  * A handle is not thread-safe.
  */
 #ifndef CTCBS_H
@@ -84,10 +84,11 @@ typedef struct {
   float end_d;          /* log-domain D_end of Eq. (4) (paper: -10)                        */
   int32_t end_c;        /* C of Algorithm 3 (paper: 2)                                     */
   int32_t eos_run;      /* frames of the CTCBS_END_EOS_RUN rule (10)                       */
-  int32_t poll_every;   /* > 0: every that many steps ctcbs_step looks, without draining the
-                           stream, at the count of finished utterances the device has
-                           published (it may lag by up to two such intervals) and keeps the
-                           host from running further ahead than that; 0: never             */
+  int32_t poll_every;   /* > 0: every that many steps ctcbs_step reports, without draining the
+                           stream, the count of finished utterances the device has
+                           published (it may lag by up to two such intervals), and it keeps the
+                           host from running further ahead than that (or than five steps, if
+                           that is less); 0: never                                         */
   int32_t win_union;    /* 0: every hypothesis has its own window (the two equations for s_ij, e_ij);
                            1: one window for the whole batch, s^l = min_ij s_ij, e^l = max_ij
                            e_ij (last two equations of Sec. 3.2.3), cut at each T_i          */

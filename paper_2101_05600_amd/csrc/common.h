@@ -85,8 +85,8 @@ struct Params {
   double lambda, beta;
   // posteriors, token-major: xT[(u*V + k)*Tp + t] = log p^c(z_t = k), t = 1..T_u; 0 elsewhere
   float* xT;
-  const int32_t* lens;       // [U]
-  const int32_t* lmax;       // [U] step cap per utterance
+  int32_t* lens;             // [U]
+  int32_t* lmax;             // [U] step cap per utterance
   // Cumulative blank log-posterior per utterance, fp64: Bcum[u*Tp + t] = sum_{v<=t} max(x_v(blank),
   // BLANK_FLOOR), Bcum[u*Tp] = 0.  Forward variables are stored with B_t taken out: for a hypothesis
   // g with offset off'(g), gamma_t(g) = stored_t + B_t + off'(g).  On the path that stays in blank the
@@ -129,7 +129,7 @@ struct Params {
   int32_t* n_finished;       // [1]
   int32_t* err;              // [1] bits set by the kernels' own consistency checks (0: none failed)
   int32_t* union_win;        // [2][2] per step parity: (min tau, max of min(tau~ + M2, T)) over live hypotheses
-  int32_t* host_finished;    // [1] host-resident copy (device-mapped pinned memory), one step behind
+  unsigned long long* host_progress;   // [1] in pinned host memory, see publish_progress
   // back-pointer trie, level l holds the hypotheses of length l: [l_cap+1][U][Wb]
   int32_t* trie_parent;
   int32_t* trie_token;
@@ -179,6 +179,12 @@ enum { ERR_CAND_ID = 1, ERR_WINDOW = 2, ERR_LIST_ENTRY = 4, ERR_TOKEN = 8, ERR_T
 __device__ __forceinline__ int checked(const Params& p, int v, int lo, int hi, int bit) {
   if (v < lo || v > hi) { atomicOr(p.err, bit); v = v < lo ? lo : hi; }
   return v;
+}
+
+// For the host's non-blocking look: the step that has begun and the count of utterances finished before it, in one
+// 64-bit store to pinned host memory (uncached: it needs no fence to arrive).
+__device__ __forceinline__ void publish_progress(const Params& p, int l) {
+  *(volatile unsigned long long*)p.host_progress = ((unsigned long long)(unsigned)l << 32) | (unsigned)*p.n_finished;
 }
 
 __device__ __forceinline__ float canon0(float v) { return v < LOG0_CLASS ? LOG0F : v; }

@@ -4,11 +4,13 @@
 
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <chrono>
 #include <map>
 #include <mutex>
 #include <new>
 #include <stdlib.h>
 #include <string.h>
+#include <thread>
 #include <vector>
 
 #include "common.h"
@@ -39,8 +41,6 @@ struct ctcbs {
   int32_t cur;         // buffer holding the current beam
   int32_t l_cap;       // largest step cap over the batch
   int32_t l_cap_alloc; // step cap of an utterance of t_max frames: what the buffers are sized for
-  int32_t *d_lens, *d_lmax;
-  int32_t union_init[4];
   int32_t known_finished;
   size_t score_smem_bytes;
   int score_block, score_lpc, select_block;
@@ -48,16 +48,17 @@ struct ctcbs {
   bool score_wide;
   int dense_nit, dense_nch;   // all-candidates score kernel: float4 per lane and column (0: not used), chunks per utterance
   size_t dense_smem_bytes;
-  // result staging
-  int32_t *d_tokens, *d_frames, *d_ntok, *d_flags;
-  float* d_score;
+  // Pinned, device-mapped host memory, one allocation: the progress word that the score kernel refreshes every
+  // step (upper half: the step that has begun, lower half: utterances finished before it), the batch set-up that
+  // the ingest kernels read (lengths, step caps, first batch-wide window), and the results that k_finalize writes.
+  // Kernels access it directly: a transfer between pageable memory and the device costs 20-30 us here, and a
+  // decode needed three on the way in and six on the way out.
+  void* h_pin;
+  unsigned long long* h_flag;
+  int32_t* h_setup;
+  const int32_t* d_setup;
+  Results h_res, d_res;        // host and device addresses of the result arrays
   int32_t res_cap;
-  // non-blocking progress: pinned, device-mapped word the score kernel refreshes every step, and
-  // two events that keep the host at most two poll intervals ahead of the device
-  int32_t* h_flag;
-  hipEvent_t throttle[2];
-  bool throttle_made, throttle_armed[2];
-  int32_t throttle_k;
   // optional per-kernel timing
   bool profiling;
   std::vector<hipEvent_t> events;   // 3 per recorded step: before score, after score, after select
@@ -79,11 +80,7 @@ static int dev_alloc(ctcbs* h, T** out, size_t n) {
 static void free_all(ctcbs* h) {
   for (void* q : h->allocs) (void)hipFree(q);
   h->allocs.clear();
-  if (h->h_flag) { (void)hipHostFree(h->h_flag); h->h_flag = nullptr; }
-  if (h->throttle_made) {
-    (void)hipEventDestroy(h->throttle[0]); (void)hipEventDestroy(h->throttle[1]);
-    h->throttle_made = false;
-  }
+  if (h->h_pin) { (void)hipHostFree(h->h_pin); h->h_pin = nullptr; }
 }
 
 static int step_cap(const ctcbs_config_t* c, int T) {
@@ -146,38 +143,32 @@ static int ingest(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens) {
     if (lmax[u] > l_cap) l_cap = lmax[u];
   }
   hipStream_t st = h->stream;
-  HIPCHK(hipStreamSynchronize(st));              // the staging vectors below are reused
+  // (nothing still reads the set-up words: the previous ingest ended with a synchronisation)
   h->lens.swap(lens); h->lmax.swap(lmax); h->l_cap = l_cap;
-  const size_t UW = (size_t)U * p.Wb;
-  HIPCHK(hipMemcpyAsync(h->d_lens, h->lens.data(), sizeof(int32_t) * U, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(h->d_lmax, h->lmax.data(), sizeof(int32_t) * U, hipMemcpyHostToDevice, st));
-  {
-    // step 1: every hypothesis is empty, tau = tau~ = 0
-    int e_max = 0;
-    for (int u = 0; u < U; ++u) { int e = c.win_m2 < h->lens[u] ? c.win_m2 : h->lens[u]; if (e > e_max) e_max = e; }
-    h->union_init[0] = 0x7fffffff; h->union_init[1] = -1; h->union_init[2] = 0; h->union_init[3] = e_max;
-    HIPCHK(hipMemcpyAsync(p.union_win, h->union_init, sizeof(h->union_init), hipMemcpyHostToDevice, st));
+  int e_max = 0;                                 // step 1: every hypothesis is empty, tau = tau~ = 0
+  for (int u = 0; u < U; ++u) {
+    const int e = c.win_m2 < h->lens[u] ? c.win_m2 : h->lens[u];
+    if (e > e_max) e_max = e;
+    h->h_setup[4 + u] = h->lens[u];
+    h->h_setup[4 + U + u] = h->lmax[u];
   }
-  HIPCHK(hipMemsetAsync(p.grp_n, 0, sizeof(int32_t) * UW, st));
-  HIPCHK(hipMemsetAsync(p.stopped, 0, sizeof(int32_t) * UW, st));
-  HIPCHK(hipMemsetAsync(p.err, 0, sizeof(int32_t), st));
+  h->h_setup[0] = 0x7fffffff; h->h_setup[1] = -1; h->h_setup[2] = 0; h->h_setup[3] = e_max;
+  hipLaunchKernelGGL(k_setup, dim3((U + 255) / 256), dim3(256), 0, st, p, h->d_setup, n_empty);
+  HIPCHK(hipGetLastError());
   {
     const int nvt = (p.V + 255) / 256, ntt = (c.t_max + 5 + 31) / 32;   // stored indices 0 .. t_max + 4
     const int n_tiles = nvt * ntt, per_xcd = (n_tiles + 7) / 8;
-    const dim3 tg(8 * per_xcd, U);
+    const dim3 tg(8 + 8 * per_xcd, U);           // (the first eight columns: the empty-prefix state, see k_ingest)
     if (p.V % 4 == 0 && ((uintptr_t)d_ctc_logp & 15) == 0)
-      hipLaunchKernelGGL(k_transpose<true>, tg, dim3(256), 0, st, p, d_ctc_logp, nvt, n_tiles, per_xcd);
+      hipLaunchKernelGGL(k_ingest<true>, tg, dim3(256), 0, st, p, d_ctc_logp, nvt, n_tiles, per_xcd);
     else
-      hipLaunchKernelGGL(k_transpose<false>, tg, dim3(256), 0, st, p, d_ctc_logp, nvt, n_tiles, per_xcd);
+      hipLaunchKernelGGL(k_ingest<false>, tg, dim3(256), 0, st, p, d_ctc_logp, nvt, n_tiles, per_xcd);
   }
-  HIPCHK(hipGetLastError());
-  hipLaunchKernelGGL(k_init_state, dim3(U), dim3(64), 0, st, p, n_empty);
   HIPCHK(hipGetLastError());
   h->step = 0; h->cur = 0; h->known_finished = n_empty;
   h->profiling = false; h->ev_used = 0;
-  h->throttle_k = 0; h->throttle_armed[0] = h->throttle_armed[1] = false;
-  *h->h_flag = n_empty;
   HIPCHK(hipStreamSynchronize(st));
+  *h->h_flag = (unsigned)n_empty;                // (after the wait: steps of the batch before may have been under way)
   return CTCBS_OK;
 }
 
@@ -207,12 +198,10 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
 
   const size_t UW = (size_t)U * Wb;
   int rc;
-  int32_t*& d_lens = h->d_lens; int32_t*& d_lmax = h->d_lmax;
 #define A(ptr, n) if ((rc = dev_alloc(h, &(ptr), (n))) != CTCBS_OK) return rc
   A(p.xT, (size_t)U * V * p.Tp);
   A(p.Bcum, (size_t)U * p.Tp);
-  A(d_lens, (size_t)U); A(d_lmax, (size_t)U);
-  p.lens = d_lens; p.lmax = d_lmax;
+  A(p.lens, (size_t)U); A(p.lmax, (size_t)U);
   for (int b = 0; b < 2; ++b) {
     A(p.gn[b], UW * p.Tp); A(p.gb[b], UW * p.Tp);
     A(p.rec[b], UW);
@@ -237,22 +226,31 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   A(p.trace, UW * 16);
 #endif
   h->res_cap = h->l_cap_alloc;
-  A(h->d_tokens, (size_t)U * h->res_cap); A(h->d_frames, (size_t)U * h->res_cap);
-  A(h->d_ntok, (size_t)U); A(h->d_flags, (size_t)U); A(h->d_score, (size_t)U);
 #undef A
 
   {
+    const size_t n_setup = 4 + (size_t)2 * U, n_res = (size_t)U * h->res_cap;
+    const size_t o_setup = 64, o_res = o_setup + ((n_setup * 4 + 63) & ~(size_t)63);
+    const size_t bytes = o_res + ((size_t)U * 4 + n_res * 2) * 4;
     void* hp = nullptr;
-    hipError_t e = hipHostMalloc(&hp, 64, hipHostMallocMapped);
+    hipError_t e = hipHostMalloc(&hp, bytes, hipHostMallocMapped);
     if (e != hipSuccess) { g_last_hip = (int)e; (void)hipGetLastError(); return CTCBS_ENOMEM; }
-    h->h_flag = (int32_t*)hp;
-    *h->h_flag = 0;
+    h->h_pin = hp;
     void* dp = nullptr;
     HIPCHK(hipHostGetDevicePointer(&dp, hp, 0));
-    p.host_finished = (int32_t*)dp;
-    HIPCHK(hipEventCreateWithFlags(&h->throttle[0], hipEventDisableTiming));
-    HIPCHK(hipEventCreateWithFlags(&h->throttle[1], hipEventDisableTiming));
-    h->throttle_made = true;
+    h->h_flag = (unsigned long long*)hp;
+    *h->h_flag = 0;
+    p.host_progress = (unsigned long long*)dp;
+    h->h_setup = (int32_t*)((char*)hp + o_setup);
+    h->d_setup = (const int32_t*)((char*)dp + o_setup);
+    auto results = [&](void* base) {
+      Results r;
+      r.ntok = (int32_t*)((char*)base + o_res); r.flags = r.ntok + U; r.err = r.flags + U;
+      r.score = (float*)(r.err + U);
+      r.tokens = (int32_t*)(r.score + U); r.frames = r.tokens + n_res;
+      return r;
+    };
+    h->h_res = results(hp); h->d_res = results(dp);
   }
   // launch shapes of the per-step kernels
   h->score_block = 256;
@@ -307,7 +305,7 @@ extern "C" int ctcbs_create(const ctcbs_config_t* cfg, const float* d_ctc_logp, 
   if (rc != CTCBS_OK) return rc;
   ctcbs* h = new (std::nothrow) ctcbs();
   if (!h) return CTCBS_ENOMEM;
-  h->h_flag = nullptr; h->throttle_made = false;
+  h->h_pin = nullptr;
   h->cfg = *cfg;
   h->stream = (hipStream_t)cfg->stream;
   if (hipGetDevice(&h->device) != hipSuccess) { g_last_hip = (int)hipGetLastError(); delete h; return CTCBS_EHIP; }
@@ -364,6 +362,37 @@ static hipError_t launch_dense(ctcbs* h, const Params& p, const float* att, int 
   hipLaunchKernelGGL((k_score_dense<1024, NIT>), dim3(p.U * h->dense_nch), dim3(1024), h->dense_smem_bytes,
                      h->stream, p, att, l, h->cur, h->dense_nch);
   return hipGetLastError();
+}
+
+// Looks at the progress word after step l has been enqueued, without draining the stream, and keeps the host
+// from running more than a few steps ahead of the device: far enough that the device always has work queued
+// (a step's launches take the host less time than the device needs to run them), and no further, because every
+// step that is already queued when the last utterance finishes still runs, for nothing (a dead step takes about
+// 6 us; with a look every eight steps and two intervals of lead, up to sixteen of them ended every decode).
+#define CTCBS_STEPS_AHEAD 5
+static int follow_progress(ctcbs* h, int l) {
+  const int ahead = 2 * h->cfg.poll_every < CTCBS_STEPS_AHEAD ? 2 * h->cfg.poll_every : CTCBS_STEPS_AHEAD;
+  unsigned long long v = *(volatile unsigned long long*)h->h_flag;
+  if ((int)(v >> 32) + ahead < l) {
+    // (the wait ends: the stream's work ends, or hipStreamQuery reports why it does not)
+    std::chrono::steady_clock::time_point asked = std::chrono::steady_clock::now();
+    for (long spins = 1;; ++spins) {
+      v = *(volatile unsigned long long*)h->h_flag;
+      if ((int)(v >> 32) + ahead >= l) break;
+      if ((spins & 63) != 0) continue;
+      const auto now = std::chrono::steady_clock::now();
+      if (now - asked < std::chrono::milliseconds(1)) {
+        if (spins > (1 << 14)) std::this_thread::yield();
+        continue;
+      }
+      asked = now;
+      const hipError_t e = hipStreamQuery(h->stream);
+      if (e == hipSuccess) { v = *(volatile unsigned long long*)h->h_flag; break; }   // everything enqueued has run
+      if (e != hipErrorNotReady) { g_last_hip = (int)e; return CTCBS_EHIP; }
+    }
+  }
+  h->known_finished = (int32_t)(uint32_t)v;
+  return CTCBS_OK;
 }
 
 // One step with the kernels working on `p`: the handle's own parameter block, or a copy of it whose
@@ -435,15 +464,10 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   h->cur ^= 1;
   h->p_step = p;                           // where this step's intermediate arrays lie (ctcbs_peek)
   int polled = -1;
-  if (h->cfg.poll_every > 0 && (l % h->cfg.poll_every) == 0) {
-    // wait (normally not at all) for the interval before the last one, then look at the count the
-    // device has published; the device keeps at least one interval of queued work meanwhile
-    const int k = h->throttle_k++;
-    if (h->throttle_armed[(k + 1) & 1]) HIPCHK(hipEventSynchronize(h->throttle[(k + 1) & 1]));
-    HIPCHK(hipEventRecord(h->throttle[k & 1], h->stream));
-    h->throttle_armed[k & 1] = true;
-    polled = *(volatile int32_t*)h->h_flag;
-    h->known_finished = polled;
+  if (h->cfg.poll_every > 0) {
+    const int rc = follow_progress(h, l);
+    if (rc != CTCBS_OK) return rc;
+    if (l % h->cfg.poll_every == 0) polled = h->known_finished;
   }
   if (out) {
     out->step = l; out->n_finished = polled;
@@ -543,26 +567,21 @@ extern "C" int ctcbs_finalize(ctcbs_t* h, int32_t* h_tokens, int32_t cap, int32_
   const size_t fin_lds = (size_t)(h->l_cap_alloc + 1) * h->p.Wb + (size_t)h->l_cap_alloc + 1;
   const int use_lds = fin_lds <= 60 * 1024;
   hipLaunchKernelGGL((k_finalize<256>), dim3(U), dim3(256), use_lds ? fin_lds : 0, h->stream, h->p, h->cur,
-                     h->step, rc_cap, use_lds, h->d_tokens, h->d_frames, h->d_ntok, h->d_score, h->d_flags);
+                     h->step, rc_cap, use_lds, h_frames != nullptr ? 1 : 0, h->d_res);
   HIPCHK(hipGetLastError());
-  std::vector<int32_t> tok((size_t)U * rc_cap), frm((size_t)U * rc_cap), nt(U), fl(U);
-  HIPCHK(hipMemcpyAsync(tok.data(), h->d_tokens, tok.size() * 4, hipMemcpyDeviceToHost, h->stream));
-  HIPCHK(hipMemcpyAsync(frm.data(), h->d_frames, frm.size() * 4, hipMemcpyDeviceToHost, h->stream));
-  HIPCHK(hipMemcpyAsync(nt.data(), h->d_ntok, (size_t)U * 4, hipMemcpyDeviceToHost, h->stream));
-  HIPCHK(hipMemcpyAsync(fl.data(), h->d_flags, (size_t)U * 4, hipMemcpyDeviceToHost, h->stream));
-  HIPCHK(hipMemcpyAsync(h_score, h->d_score, (size_t)U * 4, hipMemcpyDeviceToHost, h->stream));
-  int32_t err = 0;
-  HIPCHK(hipMemcpyAsync(&err, h->p.err, sizeof err, hipMemcpyDeviceToHost, h->stream));
   HIPCHK(hipStreamSynchronize(h->stream));
+  const Results& r = h->h_res;
+  int32_t err = 0;
+  for (int u = 0; u < U; ++u) err |= r.err[u];
   if (err != 0) return CTCBS_ESTATE;     // a kernel's consistency check failed during this decode: no result
   for (int u = 0; u < U; ++u) {
-    if (nt[u] < 0 || nt[u] > cap) return CTCBS_ECAP;
-    h_ntok[u] = nt[u];
-    for (int k = 0; k < nt[u]; ++k) {
-      h_tokens[(size_t)u * cap + k] = tok[(size_t)u * rc_cap + k];
-      if (h_frames) h_frames[(size_t)u * cap + k] = frm[(size_t)u * rc_cap + k];
-    }
-    if (h_flags) h_flags[u] = fl[u];
+    const int n = r.ntok[u];
+    h_score[u] = r.score[u];
+    if (n < 0 || n > cap) return CTCBS_ECAP;
+    h_ntok[u] = n;
+    memcpy(h_tokens + (size_t)u * cap, r.tokens + (size_t)u * rc_cap, (size_t)n * 4);
+    if (h_frames) memcpy(h_frames + (size_t)u * cap, r.frames + (size_t)u * rc_cap, (size_t)n * 4);
+    if (h_flags) h_flags[u] = r.flags[u];
   }
   return CTCBS_OK;
 }

@@ -2,6 +2,101 @@
 #pragma once
 #include "common.h"
 
+// What the host sets up for a batch -- lengths, step caps, the first batch-wide window -- from pinned host memory
+// into device memory, and the batch-wide counters.  set[0..3]: the window words, set[4..]: lengths, then step caps.
+__global__ __launch_bounds__(256) void k_setup(Params p, const int32_t* set, int n_empty) {
+  const int u = blockIdx.x * 256 + threadIdx.x;
+  if (u < p.U) { p.lens[u] = set[4 + u]; p.lmax[u] = set[4 + p.U + u]; }
+  if (u < 4) p.union_win[u] = set[u];
+  if (u == 0) { *p.n_finished = n_empty; *p.err = 0; }
+}
+
+// Per-frame reference and empty-prefix state, one work-group per utterance.  z_0 = blank (first alignment rule of
+// Sec. 2.1), so the blank variable of the empty hypothesis at frame t is the running sum of the blank
+// log-posteriors and the label variable is log0.  That running sum (fp64, each term floored at
+// BLANK_FLOOR) is also the reference B_t every stored forward variable is taken relative to: the
+// empty hypothesis's stored blank variable is therefore 0 at every frame (minus whatever the
+// floor cut off: log0 from the first frame on whose blank probability is zero).
+// The blank column is read from the caller's posteriors, not from xT: it then depends on nothing that the
+// transposition writes and runs beside it (in a launch of its own, one wave per utterance: 13 us at cfg2, 23 us at
+// 1500 frames, after the transposition).  The frames of a round of 2048 are all requested before the first is used.
+// An utterance of no frames is an unused slot of the batch: it counts as finished from the start (counted by the
+// host), holds no hypothesis and takes part in nothing.
+__device__ __forceinline__ void init_state(const Params& p, const float* __restrict__ x, int u) {
+  __shared__ double s_v[2][4], s_c[2][4];                // per wave: totals of the pass
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int T = p.lens[u];
+  const size_t hyp0 = (size_t)u * p.Wb;
+  float* gn = p.gn[0] + hyp0 * p.Tp;
+  float* gb = p.gb[0] + hyp0 * p.Tp;
+  double* Bu = p.Bcum + (size_t)u * p.Tp;
+  const float* xb = x + (size_t)u * p.t_max * p.V + p.blank_id;   // row t - 1 holds frame t
+  double carry = 0.0, carry_cut = 0.0;
+  if (tid == 0) { gn[0] = LOG0F; gb[0] = 0.0f; Bu[0] = 0.0; }
+  constexpr int R = 8;
+  for (int base = 1; base <= T; base += 256 * R) {
+    float x0[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const int t = base + 256 * k + tid;
+      x0[k] = t <= T ? fmaxf(xb[(size_t)(t - 1) * p.V], LOG0F) : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      if (base + 256 * k > T) break;                     // (uniform)
+      const int t = base + 256 * k + tid;
+      double v = (double)fmaxf(x0[k], BLANK_FLOOR);      // floored term of B_t
+      double c = (double)x0[k] - v;                      // what the floor cut off (0 or negative)
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const double n = __shfl_up(v, o), nc = __shfl_up(c, o);
+        if (lane >= o) { v += n; c += nc; }
+      }
+      if (lane == 63) { s_v[k & 1][w] = v; s_c[k & 1][w] = c; }
+      lds_barrier();                                     // (two buffers: the next pass writes the other one)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const double a = s_v[k & 1][i], b = s_c[k & 1][i];
+        if (i < w) { v += a; c += b; }
+      }
+      v += carry; c += carry_cut;
+      if (t <= T) { Bu[t] = v; gb[t] = fmaxf((float)c, LOG0F); gn[t] = LOG0F; }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { carry += s_v[k & 1][i]; carry_cut += s_c[k & 1][i]; }
+    }
+  }
+  for (int t = T + 1 + tid; t < p.Tp; t += 256) Bu[t] = carry;   // (never weighted: keeps reads defined)
+  if (tid < p.Wb) {
+    const size_t h = hyp0 + tid;
+    const bool first = tid == 0 && T > 0;
+    HypRec r;
+    r.live = first; r.last = -1; r.rs = 0; r.re = T; r.tau = 0; r.tau_end = 0; r.ref = 0; r.pad = 0;
+    r.off = 0.0; r.att = 0.0; r.joint = 0.0; r.bref = 0.0;
+    p.rec[0][h] = r;
+    // the other buffer: dead until the first selection fills it, but never left holding what the
+    // allocation happened to contain (a kernel may load a dead slot's record before it looks at its flag)
+    r.live = 0;
+    p.rec[1][h] = r;
+    p.grp_n[h] = 0; p.stopped[h] = 0;
+    p.out_live[h] = first; p.out_parent[h] = 0; p.out_token[h] = -1; p.out_score[h] = 0.0f;
+    p.out_tau[h] = 0; p.out_tau_end[h] = 0; p.out_eos_added[h] = 0; p.out_stopped[h] = 0;
+    p.trie_parent[h] = 0; p.trie_token[h] = -1; p.trie_tau[h] = 0;   // level 0: the empty hypothesis
+  }
+  if (tid == 64) {
+    UttInfo ui;
+    ui.T = T; ui.lmax = p.lmax[u]; ui.BT = carry;          // (B_T: the running sum after the last frame; 0 for T = 0)
+    p.uinfo[u] = ui;
+    UttState s;
+    s.best_score = LOG0D; s.fb_score = LOG0D;
+    for (int i = 0; i < MAX_END_M; ++i) { s.ring_score[i] = LOG0D; s.ring_tag[i] = -1; }
+    s.n_ended = 0; s.best_step = 0; s.best_slot = 0; s.cnt_tau_T = 0; s.finished_step = T > 0 ? 0 : -1; s.pad = 0;
+    p.utt[u] = s;
+    p.finished[u] = T > 0 ? 0 : 1;
+    p.cells[u] = 0ull;
+    p.groups[u] = 0ull;
+  }
+}
+
 // CTC log-posteriors [U][t_max][V] (frame-major, as an encoder emits them) -> token-major
 // xT[u][k][t], t = 1..T_u, so that one candidate's frames are contiguous.  A work-group moves a
 // tile of 256 tokens x 32 stored frames through LDS: 1 KB contiguous per frame on the way in
@@ -16,13 +111,20 @@
 // fetched into one L2 instead of two, and each XCD streams through its own region of memory.
 // Which eighth an XCD takes rotates with the utterance, so that short utterances (whose last
 // eighths are empty) do not leave the same XCDs idle.
+// Grid: (8 + 8 * per_xcd, U).  The first column of work-groups sets up the utterances' initial state instead
+// (seven idle columns beside it keep the tiles' order over the XCDs).
 template <bool VEC>
-__global__ __launch_bounds__(256) void k_transpose(Params p, const float* __restrict__ x, int nvt, int n_tiles,
+__global__ __launch_bounds__(256) void k_ingest(Params p, const float* __restrict__ x, int nvt, int n_tiles,
                                                    int per_xcd) {
   __shared__ __attribute__((aligned(16))) float tile[32][260];
   const int u = blockIdx.y;
+  const int bx = (int)blockIdx.x - 8;
+  if (bx < 0) {
+    if (bx == -8) init_state(p, x, u);
+    return;
+  }
   const int T = p.lens[u];
-  const int g = (((int)blockIdx.x - u) & 7) * per_xcd + (blockIdx.x >> 3);
+  const int g = ((bx - u) & 7) * per_xcd + (bx >> 3);
   if (g >= n_tiles) return;
   const int jt = g / nvt, vt = g - jt * nvt;
   const int d0 = jt * 32;                                // first stored frame index of the tile
@@ -74,69 +176,5 @@ __global__ __launch_bounds__(256) void k_transpose(Params p, const float* __rest
       o.w = (d + 3 <= T) ? tile[t4 + 3][vs] : 0.0f;
       *(float4*)(dst + (size_t)(v0 + vl) * p.Tp + d) = o;
     }
-  }
-}
-
-// Per-frame reference and empty-prefix state.  z_0 = blank (first alignment rule of Sec. 2.1), so
-// the blank variable of the empty hypothesis at frame t is the running sum of the blank
-// log-posteriors and the label variable is log0.  That running sum (fp64, each term floored at
-// BLANK_FLOOR) is also the reference B_t every stored forward variable is taken relative to: the
-// empty hypothesis's stored blank variable is therefore 0 at every frame (minus whatever the
-// floor cut off: log0 from the first frame on whose blank probability is zero).
-// One wave per utterance.  An utterance of no frames is an unused slot of the batch: it counts as
-// finished from the start (n_empty of them, counted by the host), holds no hypothesis and takes
-// part in nothing.
-__global__ __launch_bounds__(64) void k_init_state(Params p, int n_empty) {
-  const int u = blockIdx.x, lane = threadIdx.x;
-  const int T = p.lens[u];
-  const size_t hyp0 = (size_t)u * p.Wb;
-  float* gn = p.gn[0] + hyp0 * p.Tp;
-  float* gb = p.gb[0] + hyp0 * p.Tp;
-  double* Bu = p.Bcum + (size_t)u * p.Tp;
-  const float* xb = p.xT + ((size_t)u * p.V + p.blank_id) * p.Tp;
-  double carry = 0.0, carry_cut = 0.0;
-  if (lane == 0) { gn[0] = LOG0F; gb[0] = 0.0f; Bu[0] = 0.0; }
-  for (int base = 1; base <= T; base += 64) {
-    int t = base + lane;
-    const float x0 = (t <= T) ? xb[t] : 0.0f;
-    double v = (double)fmaxf(x0, BLANK_FLOOR);           // floored term of B_t
-    double c = (double)x0 - v;                            // what the floor cut off (0 or negative)
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      double n = __shfl_up(v, o), nc = __shfl_up(c, o);
-      if (lane >= o) { v += n; c += nc; }
-    }
-    v += carry; c += carry_cut;
-    if (t <= T) { Bu[t] = v; gb[t] = fmaxf((float)c, LOG0F); gn[t] = LOG0F; }
-    carry = __shfl(v, 63); carry_cut = __shfl(c, 63);
-  }
-  for (int t = T + 1 + lane; t < p.Tp; t += 64) Bu[t] = carry;   // (never weighted: keeps reads defined)
-  for (int j = lane; j < p.Wb; j += 64) {
-    size_t h = hyp0 + j;
-    HypRec r;
-    r.live = (j == 0 && T > 0); r.last = -1; r.rs = 0; r.re = T; r.tau = 0; r.tau_end = 0; r.ref = 0; r.pad = 0;
-    r.off = 0.0; r.att = 0.0; r.joint = 0.0; r.bref = 0.0;
-    p.rec[0][h] = r;
-    // the other buffer: dead until the first selection fills it, but never left holding what the
-    // allocation happened to contain (a kernel may load a dead slot's record before it looks at its flag)
-    r.live = 0;
-    p.rec[1][h] = r;
-    p.out_live[h] = (j == 0 && T > 0); p.out_parent[h] = 0; p.out_token[h] = -1; p.out_score[h] = 0.0f;
-    p.out_tau[h] = 0; p.out_tau_end[h] = 0; p.out_eos_added[h] = 0; p.out_stopped[h] = 0;
-    p.trie_parent[h] = 0; p.trie_token[h] = -1; p.trie_tau[h] = 0;   // level 0: the empty hypothesis
-  }
-  if (lane == 0) {
-    UttInfo ui;
-    ui.T = T; ui.lmax = p.lmax[u]; ui.BT = carry;          // (B_T: the running sum after the last frame; 0 for T = 0)
-    p.uinfo[u] = ui;
-    UttState s;
-    s.best_score = LOG0D; s.fb_score = LOG0D;
-    for (int i = 0; i < MAX_END_M; ++i) { s.ring_score[i] = LOG0D; s.ring_tag[i] = -1; }
-    s.n_ended = 0; s.best_step = 0; s.best_slot = 0; s.cnt_tau_T = 0; s.finished_step = T > 0 ? 0 : -1; s.pad = 0;
-    p.utt[u] = s;
-    p.finished[u] = T > 0 ? 0 : 1;
-    p.cells[u] = 0ull;
-    p.groups[u] = 0ull;
-    if (u == 0) *p.n_finished = n_empty;
   }
 }

@@ -326,11 +326,8 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
   const int tau = rec.tau, tau_end = rec.tau_end;
   const int rs = rec.rs, re = rec.re, last = rec.last;
   const double off = rec.off, acum = rec.att;
-  // publish the count of finished utterances (as of the previous step) where the host can
-  // read it without synchronising: one writer, plain store to device-mapped pinned memory
-  if (grp == 0 && tid == 0) {
-    *(volatile int32_t*)p.host_finished = *p.n_finished;
-    __threadfence_system();
+  if (grp == 0 && tid == BLOCK - 1) {                      // (not in wave 0, which finishes last)
+    publish_progress(p, l);
     // batch-union window: clear the slot the select kernel of this step will fill for the next one
     p.union_win[2 * ((l + 1) & 1)] = 0x7fffffff;
     p.union_win[2 * ((l + 1) & 1) + 1] = -1;

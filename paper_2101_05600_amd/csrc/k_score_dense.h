@@ -32,11 +32,7 @@ __global__ __launch_bounds__(BLOCK) void k_score_dense(Params p, const float* __
   const int u = blockIdx.x / nch, chunk = blockIdx.x - u * nch;
   const size_t h0 = (size_t)u * Wb;
 
-  if (blockIdx.x == 0 && tid == 0) {
-    // the count of finished utterances (as of the previous step) for the host's non-blocking look
-    *(volatile int32_t*)p.host_finished = *p.n_finished;
-    __threadfence_system();
-  }
+  if (blockIdx.x == 0 && tid == BLOCK - 1) publish_progress(p, l);
   const int T = p.lens[u];
   const bool fin = p.finished[u] != 0;
   const double* Bu = p.Bcum + (size_t)u * Tp;
