@@ -59,8 +59,8 @@ enum {
 /*
  * Search configuration (Algorithm 2's inputs plus the constants of Sec. 3.2).
  * Limits: 1 <= beam <= 32; 3 <= vocab; 1 <= t_max <= 6140; end_m <= 8; eos_run <= 32.
- * (With 0 < cand_k < vocab-2 the fast candidate selection needs vocab to be a multiple of 4
- * and at most 6144; other vocabularies take a slower, equivalent path.)
+ * (With 0 < cand_k < vocab-2 the fast candidate selection needs a vocab of at most 16384;
+ * larger ones take a slower, equivalent path.)
  */
 typedef struct {
   int32_t n_utt;        /* U                                                               */
@@ -151,9 +151,8 @@ int ctcbs_reset(ctcbs_t* h, const float* d_ctc_logp, const int32_t* h_lens);
  * fp32, [U][Wb][V], the whole buffer valid device memory); rows of dead slots and finished
  * utterances may be fetched but their contents are never looked at (garbage and NaN are fine).
  * At the first step only slot 0 of each utterance is live.  The buffer must stay valid until
- * the step's work has run on the stream.  Rows that start on 16-byte boundaries (d_att_logp
- * 16-byte aligned and V a multiple of 4) take the fast candidate selection; any other
- * alignment is accepted and takes a slower, equivalent path.  `out` may be NULL.
+ * the step's work has run on the stream.  Any alignment of the rows is accepted.  `out` may
+ * be NULL.
  * Returns CTCBS_DONE (and enqueues nothing) once the handle knows that all utterances are
  * finished: after a look or ctcbs_poll saw it, or when the step index passes every
  * utterance's cap.  Steps enqueued after the last utterance finished do nothing.
@@ -168,10 +167,10 @@ int ctcbs_step(ctcbs_t* h, const float* d_att_logp, ctcbs_step_out_t* out);
  * carry a step's intermediate values from the score kernel to the select kernel (windows, eos
  * scores, the groups' best-first lists, stop flags, work counts) lie in a fixed 4 MiB array inside
  * the library's image (one copy per GPU, held until the process ends) instead of the handle's own
- * memory.  The call allocates nothing, on the host or on the device, and enqueues no memset.
+ * memory.  The call allocates nothing, on the host or on the device, and enqueues what ctcbs_step does.
  * Limits: the device the handle was created on must be current (else CTCBS_ESTATE); at most 256
  * candidates per hypothesis and not every id a candidate, and
- * 40*U*Wb + 24*U*Wb*Wb bytes (each array rounded up to 256) within the 4 MiB (else CTCBS_EINVAL:
+ * 64*U*Wb + 24*U*Wb*Wb bytes (each array rounded up to 256) within the 4 MiB (else CTCBS_EINVAL:
  * e.g. U = 256 at beam 20 fits, U = 2048 at beam 10 does not).
  * Every call on a GPU uses that GPU's one array, whatever the handle: steps of different handles
  * (or streams) that overlap in time on one GPU race on it.  Callers that keep several batches in

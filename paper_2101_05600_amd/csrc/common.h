@@ -69,6 +69,23 @@ struct __align__(64) HypRec {
   double bref;               // B_r (copied from Bcum so that no load depends on `ref`)
 };
 
+struct ListEntry {           // one entry of a group's best-first list
+  double J;                  // joint score
+  int32_t tok;
+  float inc, att;            // prefix-score increment, this step's attention log-prob
+  int32_t pad;
+};
+
+// What the score kernel hands to the select kernel about one group, in one 64-byte line.
+struct __align__(64) GroupOut {
+  int32_t n;                 // entries of the group's best-first list
+  int32_t stopped;           // eos-run rule fired
+  int32_t win_s, win_e;      // window (empty: win_e < win_s)
+  double ctc_eos, joint_eos; // eos scores
+  long long cells;           // prefix-score terms
+  int32_t pad[6];
+};
+
 struct UttInfo {             // per utterance, constant over a decode
   int32_t T, lmax;           // frames, step cap
   double BT;                 // B_T
@@ -101,26 +118,14 @@ struct Params {
   HypRec* rec[2];
   int32_t keep_cand;         // 1: the per-candidate arrays below are filled every step (ctcbs_peek; large K needs them)
   // per-step scratch between the score and the select kernel
-  int32_t* win_s;            // [U][Wb]
-  int32_t* win_e;
   int32_t* cand_id;          // [U][Wb][K]
   float* cand_inc;           // [U][Wb][K] log psi(g.c) - off(g)
   float* cand_att;           // [U][Wb][K] this step's attention log-prob of c
   float* cand_pre;           // [U][Wb][K] scratch of the eos-run rule
   double* cand_ctc;          // [U][Wb][K] log psi(g.c)
   double* cand_joint;        // [U][Wb][K]
-  int32_t* grp_n;            // [U][Wb] entries of the group's sorted list
-  // the group's best-first list, [U][Wb][Wb]: joint score, candidate index, token,
-  // prefix-score increment, this step's attention log-prob
-  double* grp_J;
-  int32_t* grp_ci;
-  int32_t* grp_tok;
-  float* grp_inc;
-  float* grp_att;
-  double* ctc_eos;           // [U][Wb]
-  double* joint_eos;         // [U][Wb]
-  int32_t* stopped;          // [U][Wb] eos-run rule fired
-  long long* grp_cells;      // [U][Wb]
+  GroupOut* grp;             // [U][Wb]
+  ListEntry* grp_list;       // [U][Wb][Wb] the group's best-first list
   // utterance state
   UttState* utt;             // [U]
   uint8_t* finished;         // [U]
@@ -144,6 +149,62 @@ struct Params {
   uint8_t* out_eos_added;
   uint8_t* out_stopped;
   unsigned long long* trace; // [max(U*Wb, U)][16] per-block phase time stamps (tuning builds only)
+};
+
+// Kernel arguments that a work-group needs early, kept in one block of few 64-byte lines: left to itself the compiler
+// fetches arguments one by one where they are first used, and in a kernel of a few microseconds every first touch
+// of a line is a trip to memory in a chain of them.  PIN makes a value be in scalar registers from here on, so that
+// loads written above it are issued together and waited for once.
+#if defined(__AMDGCN__)
+#define PIN4(a, b, c, d) __asm__ volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d))
+#else
+#define PIN4(a, b, c, d) do { } while (0)
+#endif
+
+// arguments of the score kernel behind the preloaded ones
+struct ScoreArgs {
+  const float* xT;
+  const double* Bcum;
+  const float *gn, *gb;      // of the current buffer
+  ListEntry* grp_list;
+  GroupOut* grp;
+  double lambda, beta;
+  int32_t Tp, K, blank_id, eos_id, win_m1, win_m2, end_flags, eos_run;
+  int32_t wp_max, off_f, off_small;   // LDS layout: floats per f array, byte offsets
+  int32_t mode, U;           // mode: SC_* bits
+  int32_t pad;
+  int32_t* err;
+  // not needed early
+  int32_t* union_win;
+  const int32_t* n_finished;
+  unsigned long long* host_progress;
+  int32_t* cand_id;
+  float *cand_inc, *cand_att, *cand_pre;
+  double *cand_ctc, *cand_joint;
+  unsigned long long* trace;
+};
+enum { SC_RESTRICTED = 1, SC_LOGITS = 2, SC_UNION = 4, SC_KEEP = 8 };
+
+// arguments of the select kernels behind the preloaded ones
+struct SelectArgs {
+  const float* xT;
+  const double* Bcum;
+  const float *gn, *gb;      // of the current buffer
+  float *gn_new, *gb_new;    // of the other one
+  HypRec* rec_new;
+  int32_t* trie;             // back-pointers of this level: parent, token, tau, each trie_stride apart
+  int32_t* out;              // step outputs, each UW apart: parent, token, score (float), tau, tau_end
+  uint8_t* out8;             // live, eos_added, stopped, each UW apart
+  uint32_t trie_stride;
+  int32_t U, V, Tp, blank_id, end_flags, end_m, end_c;
+  float end_d;
+  int32_t win_union, win_m2;
+  int32_t* err;
+  uint8_t* finished;
+  int32_t* n_finished;
+  unsigned long long *cells, *groups;
+  int32_t* union_win;
+  unsigned long long* trace;
 };
 
 // natural logarithm of a normal positive number: the hardware's log2 times ln 2 (about 1.5 ulp; the
@@ -176,14 +237,16 @@ __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_wave_barrier
 // indices): a value outside its range is clamped into it, so that no access leaves its array, and
 // the step's error bit is set; ctcbs_finalize then reports CTCBS_ESTATE instead of a result.
 enum { ERR_CAND_ID = 1, ERR_WINDOW = 2, ERR_LIST_ENTRY = 4, ERR_TOKEN = 8, ERR_TIME_INDEX = 16, ERR_BACKTRACK = 32 };
-__device__ __forceinline__ int checked(const Params& p, int v, int lo, int hi, int bit) {
+template <class P>
+__device__ __forceinline__ int checked(const P& p, int v, int lo, int hi, int bit) {
   if (v < lo || v > hi) { atomicOr(p.err, bit); v = v < lo ? lo : hi; }
   return v;
 }
 
 // For the host's non-blocking look: the step that has begun and the count of utterances finished before it, in one
 // 64-bit store to pinned host memory (uncached: it needs no fence to arrive).
-__device__ __forceinline__ void publish_progress(const Params& p, int l) {
+template <class P>
+__device__ __forceinline__ void publish_progress(const P& p, int l) {
   *(volatile unsigned long long*)p.host_progress = ((unsigned long long)(unsigned)l << 32) | (unsigned)*p.n_finished;
 }
 
@@ -227,6 +290,9 @@ __device__ __forceinline__ float row16_sum(float v) {
 __device__ __forceinline__ float lane_f(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
+// a value that all lanes of the wave hold alike, into a scalar register: the compiler cannot know it of what comes
+// from LDS or from a wave's number, and without it loops and choices on such values run on vector registers with lane masks
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 // inclusive prefix sum over the 64 lanes
 __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t x, int /*lane*/) {
   int v = (int)x;

@@ -32,7 +32,7 @@ struct ctcbs {
   ctcbs_config_t cfg;
   Params p;
   Params p_step;       // the parameter block of the last step enqueued
-  ScoreSmem sm;
+  int32_t off_f, off_small, wp_max;   // the score kernel's LDS layout
   hipStream_t stream;
   int device;          // the device the handle lives on (current at creation)
   std::vector<void*> allocs;
@@ -45,7 +45,8 @@ struct ctcbs {
   size_t score_smem_bytes;
   int score_block, score_lpc, select_block;
   bool select_fpl2;            // the select kernels' form with the two-frames-per-lane recurrence only
-  bool score_wide;
+  bool score_wide, score_bigk;
+  int score_nv4;               // granules of an attention row per lane
   int dense_nit, dense_nch;   // all-candidates score kernel: float4 per lane and column (0: not used), chunks per utterance
   size_t dense_smem_bytes;
   // Pinned, device-mapped host memory, one allocation: the progress word that the score kernel refreshes every
@@ -196,7 +197,9 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   h->l_cap = h->l_cap_alloc;
   p.l_cap = h->l_cap_alloc;
 
-  const size_t UW = (size_t)U * Wb;
+  // (the score kernel's grid is whole eights of utterances: what it reads first has entries for the last of them)
+  const size_t U8 = ((size_t)U + 7) & ~(size_t)7;
+  const size_t UW = (size_t)U * Wb, UW8 = U8 * Wb;
   int rc;
 #define A(ptr, n) if ((rc = dev_alloc(h, &(ptr), (n))) != CTCBS_OK) return rc
   A(p.xT, (size_t)U * V * p.Tp);
@@ -204,24 +207,24 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   A(p.lens, (size_t)U); A(p.lmax, (size_t)U);
   for (int b = 0; b < 2; ++b) {
     A(p.gn[b], UW * p.Tp); A(p.gb[b], UW * p.Tp);
-    A(p.rec[b], UW);
+    A(p.rec[b], UW8);
   }
-  A(p.uinfo, (size_t)U);
-  A(p.win_s, UW); A(p.win_e, UW);
+  A(p.uinfo, U8);
   {
     const size_t nc = p.keep_cand ? UW * K : 1;            // (not kept: never touched)
     A(p.cand_id, nc); A(p.cand_inc, nc); A(p.cand_att, nc); A(p.cand_pre, nc);
     A(p.cand_ctc, nc); A(p.cand_joint, nc);
   }
-  A(p.grp_n, UW); A(p.grp_J, UW * Wb); A(p.grp_ci, UW * Wb); A(p.grp_tok, UW * Wb);
-  A(p.grp_inc, UW * Wb); A(p.grp_att, UW * Wb);
-  A(p.ctc_eos, UW); A(p.joint_eos, UW); A(p.stopped, UW); A(p.grp_cells, UW);
-  A(p.utt, (size_t)U); A(p.finished, (size_t)((U + 3) & ~3));   /* read as whole words by the score kernel */ A(p.cells, (size_t)U); A(p.groups, (size_t)U);
+  A(p.grp, UW); A(p.grp_list, UW * Wb);
+  A(p.utt, (size_t)U); A(p.finished, U8);   /* read as whole words by the score kernel */ A(p.cells, (size_t)U); A(p.groups, (size_t)U);
   A(p.n_finished, (size_t)1); A(p.union_win, (size_t)4); A(p.err, (size_t)1);
   const size_t trie_n = (size_t)(h->l_cap_alloc + 1) * UW;
-  A(p.trie_parent, trie_n); A(p.trie_token, trie_n); A(p.trie_tau, trie_n);
-  A(p.out_parent, UW); A(p.out_token, UW); A(p.out_score, UW); A(p.out_live, UW);
-  A(p.out_tau, UW); A(p.out_tau_end, UW); A(p.out_eos_added, UW); A(p.out_stopped, UW);
+  A(p.trie_parent, trie_n * 3); p.trie_token = p.trie_parent + trie_n; p.trie_tau = p.trie_token + trie_n;
+  A(p.out_parent, UW * 5); p.out_token = p.out_parent + UW; p.out_score = (float*)(p.out_token + UW);
+  p.out_tau = p.out_parent + 3 * UW; p.out_tau_end = p.out_tau + UW;
+  A(p.out_live, UW * 3); p.out_eos_added = p.out_live + UW; p.out_stopped = p.out_eos_added + UW;
+  if (UW8 > UW)                                  // utterances that do not exist: their records stay dead
+    for (int b = 0; b < 2; ++b) HIPCHK(hipMemsetAsync(p.rec[b] + UW, 0, (UW8 - UW) * sizeof(HypRec), h->stream));
 #ifdef CTCBS_TRACE
   A(p.trace, UW * 16);
 #endif
@@ -262,15 +265,19 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   h->score_lpc = (windowed || short_whole) ? 16 : 64;
   // windows beyond 128 frames (16 lanes x 2 float4): four float4 per lane in flight, two candidates at a time
   h->score_wide = short_whole || (windowed && (c.win_m1 + c.win_m2 + 1 + 3) > 128);
-  ScoreSmem& sm = h->sm;
-  size_t off = 0;
-  sm.off_work = (int32_t)off;
-  off += restricted ? (size_t)PIVOT_CAP * 12 : 0;       // short list (key, id, flag); also holds the radix histogram
-  sm.off_f = (int32_t)off;
-  off += (size_t)2 * p.Tp * 4;                   // Tp is a multiple of 4: both arrays 16-byte aligned
-  sm.off_small = (int32_t)off;
-  if (K <= h->score_block) off += (size_t)K * 32 + 8;
-  sm.wp_max = p.Tp;
+  // LDS of the score kernel: the short list (or the radix histogram), the f terms, the per-candidate arrays
+  size_t off = restricted ? (size_t)PIVOT_CAP * 8 : 0;
+  h->off_f = (int32_t)off;
+  // the f terms, padded to whole rounds of the column loads (4 * LPC * IT frames)
+  const int round_frames = 4 * h->score_lpc * (h->score_lpc == 64 || h->score_wide ? 4 : 2);
+  h->wp_max = (p.Tp + round_frames - 1) / round_frames * round_frames;
+  off += (size_t)2 * h->wp_max * 4;
+  h->off_small = (int32_t)off;
+  h->score_bigk = K > 64 || V > 65536;
+  const size_t small = (size_t)(h->score_bigk ? (K <= h->score_block ? K : 0) : 64) * 32 + 8;
+  const size_t gran = restricted ? (size_t)4 * ShortList::GCAP * 20 : 0;     // (the short list's granules, before those)
+  off += small > gran ? small : gran;
+  h->score_nv4 = V <= 3072 ? 3 : (V <= 5120 ? 5 : (V <= 10240 ? 10 : 16));
   h->score_smem_bytes = off;
   // all-candidates kernel: needs the f terms of all beam slots in LDS and a column window in registers
   h->dense_nit = 0; h->dense_nch = 1; h->dense_smem_bytes = (size_t)Wb * p.Tp * 4;
@@ -334,25 +341,44 @@ static hipError_t allow_lds(const void* kernel, size_t bytes) {
   }
 }
 
-template <int BLOCK, int LPC, int CB, int IT, bool BIGK>
+template <int BLOCK, int LPC, int CB, int IT, int NV4, bool BIGK>
 static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, int l) {
-  hipError_t ea = allow_lds((const void*)k_score<BLOCK, LPC, CB, IT, BIGK>, h->score_smem_bytes);
+  hipError_t ea = allow_lds((const void*)k_score<BLOCK, LPC, CB, IT, NV4, BIGK>, h->score_smem_bytes);
   if (ea != hipSuccess) return ea;
-  // attention rows that do not start on 16-byte boundaries cannot be loaded as float4: the candidate
-  // selection then reads them element by element (slower, equivalent)
-  const int flags = (((uintptr_t)att & 15) == 0 && p.V % 4 == 0) ? 1 : 0;
-  hipLaunchKernelGGL((k_score<BLOCK, LPC, CB, IT, BIGK>), dim3(p.Wb, p.U), dim3(BLOCK), h->score_smem_bytes,
+  const int in_regs = p.restricted && p.V >= 8 && p.V <= 4 * NV4 * BLOCK ? 1 : 0;
+  const int sh = p.U >= 8 ? 3 : 0;
+  const int flags = in_regs | sh << 4;
+  const dim3 grid(1u << sh, (unsigned)p.Wb, (unsigned)(p.U + (1 << sh) - 1) >> sh);
+  ScoreArgs a;
+  a.xT = p.xT; a.Bcum = p.Bcum; a.gn = p.gn[h->cur]; a.gb = p.gb[h->cur]; a.grp_list = p.grp_list; a.grp = p.grp;
+  a.lambda = p.lambda; a.beta = p.beta;
+  a.Tp = p.Tp; a.K = p.K; a.blank_id = p.blank_id; a.eos_id = p.eos_id; a.win_m1 = p.win_m1; a.win_m2 = p.win_m2;
+  a.end_flags = p.end_flags; a.eos_run = p.eos_run; a.wp_max = h->wp_max; a.off_f = h->off_f; a.off_small = h->off_small;
+  a.mode = (p.restricted ? SC_RESTRICTED : 0) | (p.att_logits ? SC_LOGITS : 0) | (p.win_union ? SC_UNION : 0) |
+           (p.keep_cand ? SC_KEEP : 0);
+  a.U = p.U; a.pad = 0; a.err = p.err; a.union_win = p.union_win; a.n_finished = p.n_finished; a.host_progress = p.host_progress;
+  a.cand_id = p.cand_id; a.cand_inc = p.cand_inc; a.cand_att = p.cand_att; a.cand_pre = p.cand_pre; a.cand_ctc = p.cand_ctc;
+  a.cand_joint = p.cand_joint; a.trace = p.trace;
+  hipLaunchKernelGGL((k_score<BLOCK, LPC, CB, IT, NV4, BIGK>), grid, dim3(BLOCK), h->score_smem_bytes,
                      h->stream, (const HypRec*)p.rec[h->cur], (const UttInfo*)p.uinfo, (const uint32_t*)p.finished,
-                     att, (int)p.Wb, (int)p.V, flags, l, p, h->sm, h->cur);
+                     att, (int)p.Wb, (int)p.V, flags, l, a);
   return hipGetLastError();
 }
 
-// the kernel's form with the paths for many candidates only where they can be taken (see k_score)
+// the kernel's form: registers for the row as the vocabulary needs them (up to 3072, 5120, 10240, 16384 ids; larger
+// ones never hold it), and the paths for many candidates only where they can be taken (see k_score)
 template <int BLOCK, int LPC, int CB, int IT>
 static hipError_t launch_score(ctcbs* h, const Params& p, const float* att, int l) {
-  const bool one_wave_ranks = p.K <= BLOCK && p.K <= 64 && p.V <= 65536;
-  if (!one_wave_ranks) return launch_score_as<BLOCK, LPC, CB, IT, true>(h, p, att, l);
-  return launch_score_as<BLOCK, LPC, CB, IT, false>(h, p, att, l);
+  if (h->score_bigk) {
+    if (h->score_nv4 <= 5) return launch_score_as<BLOCK, LPC, CB, IT, 5, true>(h, p, att, l);
+    return launch_score_as<BLOCK, LPC, CB, IT, 16, true>(h, p, att, l);
+  }
+  switch (h->score_nv4) {
+    case 3: return launch_score_as<BLOCK, LPC, CB, IT, 3, false>(h, p, att, l);
+    case 5: return launch_score_as<BLOCK, LPC, CB, IT, 5, false>(h, p, att, l);
+    case 10: return launch_score_as<BLOCK, LPC, CB, IT, 10, false>(h, p, att, l);
+    default: return launch_score_as<BLOCK, LPC, CB, IT, 16, false>(h, p, att, l);
+  }
 }
 
 template <int NIT>
@@ -438,26 +464,33 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   // window needs the utterance's hypotheses in one place.
   const bool split = !p.win_union && p.U * p.Wb <= 2048;
   const size_t split_lds = (size_t)28 * p.Wb * p.Wb + 64;
+  SelectArgs a;
+  const int nxt = h->cur ^ 1;
+  a.xT = p.xT; a.Bcum = p.Bcum; a.gn = p.gn[h->cur]; a.gb = p.gb[h->cur]; a.gn_new = p.gn[nxt]; a.gb_new = p.gb[nxt];
+  a.rec_new = p.rec[nxt]; a.trie = p.trie_parent + (size_t)l * p.U * p.Wb; a.out = p.out_parent; a.out8 = p.out_live;
+  a.trie_stride = (uint32_t)(p.trie_token - p.trie_parent);
+  a.U = p.U; a.V = p.V; a.Tp = p.Tp; a.blank_id = p.blank_id; a.end_flags = p.end_flags; a.end_m = p.end_m; a.end_c = p.end_c;
+  a.end_d = p.end_d; a.win_union = p.win_union; a.win_m2 = p.win_m2; a.err = p.err; a.finished = p.finished;
+  a.n_finished = p.n_finished; a.cells = p.cells; a.groups = p.groups; a.union_win = p.union_win; a.trace = p.trace;
+#define CTCBS_SELECT(K, G, BS, LDS, L)                                                                       \
+  hipLaunchKernelGGL(K, G, dim3(BS), LDS, h->stream, (const HypRec*)p.rec[h->cur], p.utt, (const GroupOut*)p.grp, \
+                     (const ListEntry*)p.grp_list, (const UttInfo*)p.uinfo, (int)p.Wb, L, a)
   if (split) {
-    if (h->select_fpl2)
-      hipLaunchKernelGGL((k_select_split<256, 2>), dim3(p.U * p.Wb), dim3(256), split_lds, h->stream,
-                         (const HypRec*)p.rec[h->cur], p.utt, (const int32_t*)p.grp_n, (const double*)p.grp_J,
-                         (const int32_t*)p.grp_tok, (const float*)p.grp_inc, (const float*)p.grp_att, (int)p.Wb, l, p, h->cur);
-    else
-      hipLaunchKernelGGL((k_select_split<256, 8>), dim3(p.U * p.Wb), dim3(256), split_lds, h->stream,
-                         (const HypRec*)p.rec[h->cur], p.utt, (const int32_t*)p.grp_n, (const double*)p.grp_J,
-                         (const int32_t*)p.grp_tok, (const float*)p.grp_inc, (const float*)p.grp_att, (int)p.Wb, l, p, h->cur);
+    const int sh = p.U >= 8 ? 3 : 0;
+    const dim3 grid(1u << sh, (unsigned)p.Wb, (unsigned)(p.U + (1 << sh) - 1) >> sh);
+    if (h->select_fpl2) CTCBS_SELECT((k_select_split<256, 2>), grid, 256, split_lds, l | sh << 28);
+    else CTCBS_SELECT((k_select_split<256, 8>), grid, 256, split_lds, l | sh << 28);
   } else {
     const int NE = p.Wb * p.Wb;
-    const size_t sel_lds = (size_t)16 * ((NE + 9) & ~1) + (size_t)32 * NE;
-#define CTCBS_SELECT(BS, F) hipLaunchKernelGGL((k_select<BS, F>), dim3(p.U), dim3(BS), sel_lds, h->stream, p, l, h->cur)
+    const size_t sel_lds = (size_t)16 * ((NE + 9) & ~1) + (size_t)28 * NE;
+    const dim3 grid(p.U);
     switch (h->select_block) {
-      case 256: if (h->select_fpl2) CTCBS_SELECT(256, 2); else CTCBS_SELECT(256, 8); break;
-      case 512: if (h->select_fpl2) CTCBS_SELECT(512, 2); else CTCBS_SELECT(512, 8); break;
-      default: if (h->select_fpl2) CTCBS_SELECT(1024, 2); else CTCBS_SELECT(1024, 8); break;
+      case 256: if (h->select_fpl2) CTCBS_SELECT((k_select<256, 2>), grid, 256, sel_lds, l); else CTCBS_SELECT((k_select<256, 8>), grid, 256, sel_lds, l); break;
+      case 512: if (h->select_fpl2) CTCBS_SELECT((k_select<512, 2>), grid, 512, sel_lds, l); else CTCBS_SELECT((k_select<512, 8>), grid, 512, sel_lds, l); break;
+      default: if (h->select_fpl2) CTCBS_SELECT((k_select<1024, 2>), grid, 1024, sel_lds, l); else CTCBS_SELECT((k_select<1024, 8>), grid, 1024, sel_lds, l); break;
     }
-#undef CTCBS_SELECT
   }
+#undef CTCBS_SELECT
   HIPCHK(hipGetLastError());
   if (ev) HIPCHK(hipEventRecord(ev[2], h->stream));
   h->step = l;
@@ -498,13 +531,7 @@ static unsigned char* g_scratch_ptr[CTCBS_MAX_DEVICES];     // device address of
 static size_t static_scratch_need(const Params& p) {
   const size_t UW = (size_t)p.U * p.Wb, L = UW * p.Wb;
   auto r = [](size_t n) { return (n + 255) & ~(size_t)255; };
-  return r(UW * 4) * 4 /* win_s, win_e, grp_n, stopped */ + r(UW * 8) * 3 /* ctc_eos, joint_eos, grp_cells */ +
-         r(L * 8) /* grp_J */ + r(L * 4) * 4 /* grp_ci, grp_tok, grp_inc, grp_att */;
-}
-
-__global__ void k_clear_words(int32_t* a, int32_t* b, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) { a[i] = 0; b[i] = 0; }
+  return r(UW * sizeof(GroupOut)) + r(L * sizeof(ListEntry));
 }
 
 extern "C" int ctcbs_step_static(ctcbs_t* h, const float* d_att_logp, ctcbs_step_out_t* out) {
@@ -532,16 +559,10 @@ extern "C" int ctcbs_step_static(ctcbs_t* h, const float* d_att_logp, ctcbs_step
   const size_t UW = (size_t)p.U * p.Wb, L = UW * p.Wb;
   size_t off = 0;
   auto take = [&](size_t bytes) { unsigned char* q = base + off; off += (bytes + 255) & ~(size_t)255; return q; };
-  p.win_s = (int32_t*)take(UW * 4); p.win_e = (int32_t*)take(UW * 4);
-  p.grp_n = (int32_t*)take(UW * 4); p.stopped = (int32_t*)take(UW * 4);
-  p.ctc_eos = (double*)take(UW * 8); p.joint_eos = (double*)take(UW * 8); p.grp_cells = (long long*)take(UW * 8);
-  p.grp_J = (double*)take(L * 8);
-  p.grp_ci = (int32_t*)take(L * 4); p.grp_tok = (int32_t*)take(L * 4);
-  p.grp_inc = (float*)take(L * 4); p.grp_att = (float*)take(L * 4);
-  // the array keeps what the last call on this GPU (of any handle) left: list lengths and stop flags start
-  // from zero (a fill kernel, not a memset node: the call may be under graph capture)
-  hipLaunchKernelGGL(k_clear_words, dim3((unsigned)((UW + 255) / 256)), dim3(256), 0, h->stream, p.grp_n, p.stopped, (int)UW);
-  HIPCHK(hipGetLastError());
+  // (the array keeps what the last call on this GPU, of any handle, left: the score kernel writes every group's
+  // line, and the select kernel reads no list entry past a line's count)
+  p.grp = (GroupOut*)take(UW * sizeof(GroupOut));
+  p.grp_list = (ListEntry*)take(L * sizeof(ListEntry));
   return step_impl(h, p, d_att_logp, out);
 }
 
@@ -647,10 +668,8 @@ extern "C" int ctcbs_peek(ctcbs_t* h, int32_t what, void* h_dst, size_t bytes, s
     case CTCBS_PEEK_CAND_ID: src = p.cand_id; sz = UW * p.K * 4; break;
     case CTCBS_PEEK_CAND_CTC: src = p.cand_ctc; sz = UW * p.K * 8; break;
     case CTCBS_PEEK_CAND_JOINT: src = p.cand_joint; sz = UW * p.K * 8; break;
-    case CTCBS_PEEK_WIN_S: src = p.win_s; sz = UW * 4; break;
-    case CTCBS_PEEK_WIN_E: src = p.win_e; sz = UW * 4; break;
-    case CTCBS_PEEK_CTC_EOS: src = p.ctc_eos; sz = UW * 8; break;
-    case CTCBS_PEEK_JOINT_EOS: src = p.joint_eos; sz = UW * 8; break;
+    case CTCBS_PEEK_WIN_S: case CTCBS_PEEK_WIN_E: sz = UW * 4; break;
+    case CTCBS_PEEK_CTC_EOS: case CTCBS_PEEK_JOINT_EOS: sz = UW * 8; break;
     case CTCBS_PEEK_N_CAND:
       if (need) *need = 4;
       if (h_dst && bytes >= 4) memcpy(h_dst, &k, 4);
@@ -658,7 +677,20 @@ extern "C" int ctcbs_peek(ctcbs_t* h, int32_t what, void* h_dst, size_t bytes, s
     default: return CTCBS_EINVAL;
   }
   if (need) *need = sz;
-  if (h_dst && bytes) {
+  if (h_dst && bytes && !src) {                            // a field of the groups' lines
+    std::vector<GroupOut> g(UW);
+    HIPCHK(hipMemcpyAsync(g.data(), p.grp, UW * sizeof(GroupOut), hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
+    for (size_t i = 0; i < UW; ++i) {
+      const size_t w = sz / UW;
+      if ((i + 1) * w > bytes) break;
+      char* d = (char*)h_dst + i * w;
+      if (what == CTCBS_PEEK_WIN_S) memcpy(d, &g[i].win_s, w);
+      else if (what == CTCBS_PEEK_WIN_E) memcpy(d, &g[i].win_e, w);
+      else if (what == CTCBS_PEEK_CTC_EOS) memcpy(d, &g[i].ctc_eos, w);
+      else memcpy(d, &g[i].joint_eos, w);
+    }
+  } else if (h_dst && bytes) {
     HIPCHK(hipMemcpyAsync(h_dst, src, bytes < sz ? bytes : sz, hipMemcpyDeviceToHost, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
   }

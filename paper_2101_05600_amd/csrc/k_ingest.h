@@ -77,7 +77,7 @@ __device__ __forceinline__ void init_state(const Params& p, const float* __restr
     // allocation happened to contain (a kernel may load a dead slot's record before it looks at its flag)
     r.live = 0;
     p.rec[1][h] = r;
-    p.grp_n[h] = 0; p.stopped[h] = 0;
+    p.grp[h] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
     p.out_live[h] = first; p.out_parent[h] = 0; p.out_token[h] = -1; p.out_score[h] = 0.0f;
     p.out_tau[h] = 0; p.out_tau_end[h] = 0; p.out_eos_added[h] = 0; p.out_stopped[h] = 0;
     p.trie_parent[h] = 0; p.trie_token[h] = -1; p.trie_tau[h] = 0;   // level 0: the empty hypothesis

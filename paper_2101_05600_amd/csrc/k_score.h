@@ -1,142 +1,179 @@
 // Score kernel: one work-group per (utterance, beam slot) hypothesis g.
 //   1. candidate pre-selection: the K ids with the largest attention log-prob, ties to the
 //      smaller id.  The row never goes through LDS: every lane keeps its float4 loads in
-//      registers.  Fast path: a
-//      pivot L that is provably not above
-//      the K-th largest value (every wave contributes the ceil(K/#waves)-th largest of its
-//      lanes' maxima, found by bisection on the upper key bits), then an exact ranking of the
-//      few values >= L.  Rows that do not fit the registers, or with so many values >= L that
-//      the short list overflows (heavy ties), take a radix select that re-reads the row.
+//      registers.  A pivot that is provably not above the K-th largest value (every wave contributes
+//      a value that its share of K of its lanes' maxima reach, found by bisection with ballots), then
+//      a short list of the few values that reach it (about 1.4 K), then the K largest of these: up to
+//      64 entries are ranked by every wave for itself, one per lane; more, or equal values at the
+//      K-th place, by the work-group.  Rows that do not fit the registers, or with so many values at the
+//      pivot that the short list overflows (heavy ties), take a radix select that re-reads the row.
 //   2. window [s, e] from g's time indices (the two equations after Eq. (5));
 //   3. prefix score of every extension g.c: log-sum over t in [s, e] of
 //      f_t + log p^c(z_t = c), f_t = blank variable of g at t-1 if c repeats g's last label,
 //      else phi_{t-1}(g)  (Eq. (3) / Eq. (5)); frames run along lanes (16 or 64 lanes per
 //      candidate, float4 per lane), all of a lane's column loads are issued before the first
-//      is consumed, streaming log-sum-exp with one exp per term;
+//      is consumed; the terms are formed in units of log 2 by one fused multiply-add each, their
+//      maximum per lane is taken, then one exp2 per term;
 //   4. eos score phi_T(g), joint scores (Eq. (1)), the eos-run test, and the group's
 //      best-first list of at most Wb candidates for the per-utterance selection.
-// The candidate list of a group is in no particular (but reproducible) order; wherever
+// The candidate list of a group is in no particular order and no result depends on it; wherever
 // equal scores must be ordered the token id decides.
 #pragma once
 #include "common.h"
 
 #define PIVOT_CAP 512     // entries of the short list (all waves together)
-#define PIVOT_NV4 6       // float4 loads per lane held in registers (rows of up to 6144 ids)
 #define RADIX_BITS 10
-
-struct ScoreSmem {
-  // byte offsets into dynamic LDS, computed on the host
-  int32_t off_work;   // union: uint32 hist[1 << RADIX_BITS] | short list of the pivot selection
-  int32_t off_f;      // float F[wp_max], Fb[wp_max]
-  int32_t off_small;  // per-candidate arrays of the group (K <= block size), see k_score
-  int32_t wp_max;     // floats available per F array
-};
 
 __device__ __forceinline__ float key_to_att(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
 // ---- candidate selection -----------------------------------------------------------------
-// Pivot path on the lane's register-resident row values (v[k] = ids 4 * (tid + k * BLOCK) ..+3;
-// excluded ids and ids past the row's end hold -inf).  Comparisons run on the floats
-// themselves; only each lane's maximum and the few collected values are turned into
-// order-preserving keys.  Short-list entries are 64-bit: key in the upper word, ~id in the
-// lower, so that one integer comparison orders by (value descending, id ascending).
-// Returns false (uniformly) if the short list would overflow or, with NaNs in the row, would
-// hold fewer than K values.  Writes the K ids (and their attention values) best first.
-// s_ent: PIVOT_CAP + 4 entries; s_w: 2 * (BLOCK / 64) words.
-template <int BLOCK>
-__device__ __forceinline__ bool select_pivot(const float4 (&v)[PIVOT_NV4], int K, int blank_id, int eos_id,
-                                             unsigned long long* s_ent, uint32_t* s_w, bool use_lds,
-                                             int32_t* out_lds, float* out_att_lds, int32_t* out_g,
-                                             unsigned long long* tr) {
-  constexpr int NW = BLOCK / 64;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const float ninf = -__builtin_huge_valf();
-  float fmx = ninf;
-#pragma unroll
-  for (int k = 0; k < PIVOT_NV4; ++k)
-    fmx = fmaxf(fmx, fmaxf(fmaxf(v[k].x, v[k].y), fmaxf(v[k].z, v[k].w)));
-  const uint32_t lmax = att_key(fmx, -1, -2, -2);
-  TRACE_MARK_AT(tr, 6);
-  // r-th largest lane maximum of this wave, by bisection on the upper 16 key bits (sign,
-  // exponent, 7 mantissa bits): stopping early only lowers the pivot, which stays valid
-  const int r = (K + NW - 1) / NW;
-  uint32_t thr = 0;
-#pragma unroll 4
-  for (int bit = 31; bit >= 16; --bit) {
-    const uint32_t trial = thr | (1u << bit);
-    if (__popcll(__ballot(lmax >= trial)) >= r) thr = trial;
+// An attention row in the registers of a work-group: 16-byte granules of it (granule g = ids head + 4 g ..
+// + 3, g = tid + k * BLOCK), and the at most six ids before the first and after the last whole granule of
+// a row that does not start or end on a 16-byte boundary (ex, of id ex_id, in the first lanes).  Ids past the
+// row's end, blank and eos hold -inf.
+template <int NV4>
+struct RowRegs {
+  float4 v[NV4];
+  float ex;
+  int ex_id, head, n_ex;
+};
+
+// The short list: wave w's entries at s_ent[w * WCAP ..], each region padded with zeros to a multiple of four.
+// Entries are 64-bit: order-preserving key in the upper word, ~id in the lower, so that one
+// integer comparison orders by (value descending, id ascending).
+struct ShortList {
+  static constexpr int WCAP = PIVOT_CAP / 4;
+  static constexpr int GCAP = 64;                          // granules per wave
+  int n, n0, n1, n2, n3;     // entries: all, of each wave
+  __device__ __forceinline__ int at(int e) const {         // where entry e lies
+    return e + (e >= n0 ? WCAP - n0 : 0) + (e >= n0 + n1 ? WCAP - n1 : 0) + (e >= n0 + n1 + n2 ? WCAP - n2 : 0);
   }
-  TRACE_MARK_AT(tr, 7);
-  if (lane == 0) s_w[w] = thr;
-  lds_barrier();
-  uint32_t Lk = s_w[0];
+  __device__ __forceinline__ int of(int w) const { return w == 0 ? n0 : (w == 1 ? n1 : (w == 2 ? n2 : n3)); }
+};
+
+// A wave's pivot: a value that at least r of its lanes' maxima reach, r the wave's share of K by the lanes that
+// hold part of the row (have of all): the smallest of the waves' pivots is then reached by at least K values.
+// Bisection on the distance below the wave's largest value, in sixteenths up to 32 -- nine steps of compare, count,
+// choose at 53 cycles each (on the upper half of the float's bits it would take sixteen; a way out of the loop when the
+// answer is exact costs 44 cycles a step, more than it saves).  A lane counts as reaching M - (d + 1) / 16 if floor(16 (M -
+// its maximum)) <= d; subtraction is monotone and M - that is exact enough for its maximum to be >= the pivot then.
+// Where the r-th value lies further down, or is not finite: bisection on the float's upper 16 bits.
+__device__ __forceinline__ float wave_pivot(float fmx, int K, int have, int all) {
+  const float ninf = -__builtin_huge_valf();
+  const int r = all == 256 ? (K + 3) >> 2 : (K * have + all - 1) / max(all, 1);
+  float M = row16_max(fmx);
+  M = fmaxf(fmaxf(lane_f(M, 0), lane_f(M, 16)), fmaxf(lane_f(M, 32), lane_f(M, 48)));
+  // (a lane without a value, a NaN: past the end of the scale)
+  const float d16 = (M - fmx) * 16.0f;
+  const int q = d16 < 511.0f ? (int)d16 : 511;
+  int lim = 511;                                           // smallest d found so that r lanes have q <= d
 #pragma unroll
-  for (int i = 1; i < NW; ++i) Lk = min(Lk, s_w[i]);
-  // at least NW * r >= K values are >= L (as a float: -inf if no wave had r finite maxima)
-  const float L = Lk <= att_key(ninf, -1, -2, -2) ? ninf : key_to_att(Lk);
-  // hits are rare (about 1.4 K of the whole row).  Every lane notes its own in a bit mask (bit
-  // 4k+j = component j of v[k]); a wave scan of the counts and the waves' totals give each lane the
-  // place of its first hit in the short list
-  uint32_t mask = 0;
+  for (int bit = 256; bit > 0; bit >>= 1) {
+    const int c = __popcll(__ballot(q <= lim - bit));
+    lim = c >= r ? lim - bit : lim;
+  }
+  float L = M - (float)(lim + 1) * 0.0625f;
+  if (lim >= 511) {                                        // (uniform, rare)
+    const uint32_t key = att_key(fmx, -1, -2, -2);
+    uint32_t thr = 0;
+#pragma unroll 1
+    for (int bit = 31; bit >= 16; --bit) {
+      const uint32_t trial = thr | (1u << bit);
+      if (__popcll(__ballot(key >= trial)) >= r) thr = trial;
+    }
+    L = thr <= att_key(ninf, -1, -2, -2) ? ninf : key_to_att(thr);
+  }
+  return r > 0 ? L : -ninf;
+}
+
+// This wave's part of the short list.  Its granules whose maximum reaches L are packed into LDS (one ballot per
+// register; hits are rare: 1 % of a row), then their values are looked at with a lane each.  Returns how many
+// values reach L; a region that would overflow stores no more (WCAP + 1 is returned if granules overflowed).
+template <int BLOCK, int NV4>
+__device__ __forceinline__ int collect_hits(const RowRegs<NV4>& r, const float (&m4)[NV4], float L, int blank_id, int eos_id,
+                                            float4* gran, int32_t* gid, unsigned long long* ent) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  int ngr = 0;                                             // (scalar, like n below: counts of ballots)
+  auto pack = [&](bool hit, float4 v, int id) {
+    const unsigned long long b = __ballot(hit);
+    if (hit) {
+      const int pos = ngr + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u));
+      gran[min(pos, ShortList::GCAP - 1)] = v; gid[min(pos, ShortList::GCAP - 1)] = id;
+    }
+    ngr += __popcll(b);
+  };
 #pragma unroll
-  for (int k = 0; k < PIVOT_NV4; ++k)
-    mask |= ((uint32_t)(v[k].x >= L) << (4 * k)) | ((uint32_t)(v[k].y >= L) << (4 * k + 1)) |
-            ((uint32_t)(v[k].z >= L) << (4 * k + 2)) | ((uint32_t)(v[k].w >= L) << (4 * k + 3));
-  const int cnt = __popc(mask);
-  const int inc = (int)wave_incl_scan_u32((uint32_t)cnt, lane);
-  if (lane == 63) s_w[NW + w] = (uint32_t)inc;
-  lds_barrier();
-  int base = 0, total = 0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) { const int c = (int)s_w[NW + i]; base += i < w ? c : 0; total += c; }
-  if (total > PIVOT_CAP || total < K) return false;
-  TRACE_MARK_AT(tr, 14);
-  const bool linf = (L == ninf);                           // then excluded ids (held as -inf) are hits too
-  int pos = base + inc - cnt;
-  // per float4 slot, one hit per trip (most lanes have none, hardly any more than one)
-#pragma unroll
-  for (int k = 0; k < PIVOT_NV4; ++k) {
-    uint32_t m4 = (mask >> (4 * k)) & 15u;
-    while (m4 != 0u) {
-      const int j = __ffs((int)m4) - 1;
-      m4 &= m4 - 1u;
-      const float val = j == 0 ? v[k].x : (j == 1 ? v[k].y : (j == 2 ? v[k].z : v[k].w));
-      const int id = 4 * (tid + k * BLOCK) + j;
+  for (int k = 0; k < NV4; ++k) pack(m4[k] >= L, r.v[k], r.head + 4 * (tid + k * BLOCK));
+  if (r.n_ex > 0) {                                        // (uniform)
+    const float ninf = -__builtin_huge_valf();
+    pack(tid < r.n_ex && r.ex >= L, make_float4(r.ex, ninf, ninf, ninf), r.ex_id);
+  }
+  wave_lds_fence();
+  const bool linf = (L == -__builtin_huge_valf());         // then excluded ids (held as -inf) are hits too
+  int n = 0;
+  const int nv = 4 * min(ngr, ShortList::GCAP);
+  for (int i0 = 0; i0 < nv; i0 += 64) {
+    const int i = i0 + lane;
+    const float val = i < nv ? ((const float*)gran)[i] : 0.0f;
+    const int id = i < nv ? gid[i >> 2] + (i & 3) : 0;
+    const bool hit = i < nv && val >= L;
+    const unsigned long long b = __ballot(hit);
+    if (hit) {
+      const int pos = n + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u));
       const uint32_t u = __float_as_uint(val);
       uint32_t key = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
       if (linf && (id == blank_id || id == eos_id)) key = 0u;   // below a genuine -inf
-      s_ent[pos++] = ((unsigned long long)key << 32) | (uint32_t)~id;
+      if (pos < ShortList::WCAP) ent[pos] = ((unsigned long long)key << 32) | (uint32_t)~id;
     }
+    n += __popcll(b);
   }
-  const int n = total;
-  const int n4 = (n + 3) >> 2;
-  if (tid < 4 && n + tid < 4 * n4) s_ent[n + tid] = 0ull;    // pad to a multiple of four
-  lds_barrier();
-  TRACE_MARK_AT(tr, 15);
-  // exact rank: four lanes per entry, each comparing against a quarter of the list (two entries
-  // per read), partial ranks summed inside the quad; the rank is the output slot
-  const int part = tid & 3;
-  const ulonglong2* s_ent2 = (const ulonglong2*)s_ent;
-  for (int e = tid >> 2; e < ((n + BLOCK / 4 - 1) / (BLOCK / 4)) * (BLOCK / 4); e += BLOCK / 4) {
-    const unsigned long long me = e < n ? s_ent[e] : ~0ull;
-    int rank = 0;
-    for (int o4 = part; o4 < n4; o4 += 4) {
-      const ulonglong2 a = s_ent2[2 * o4], b = s_ent2[2 * o4 + 1];
-      rank += (int)(a.x > me) + (int)(a.y > me) + (int)(b.x > me) + (int)(b.y > me);
-    }
-    rank += dpp_i<0xB1, 0xf>(0, rank);                     // quad_perm [1,0,3,2]
-    rank += dpp_i<0x4E, 0xf>(0, rank);                     // quad_perm [2,3,0,1]
-    if (part == 0 && e < n && rank < K) {
-      const int mid = (int)~(uint32_t)me;
-      // (small K: the ids stay in LDS; the global copy is written with the scores at the end, so that
-      // no store is pending when the candidates' columns are fetched)
-      if (use_lds) { out_lds[rank] = mid; out_att_lds[rank] = key_to_att((uint32_t)(me >> 32)); }
-      else out_g[rank] = mid;
-    }
+  if (lane < 3 && n + lane < ((n + 3) & ~3) && n + lane < ShortList::WCAP) ent[n + lane] = 0ull;
+  return ngr > ShortList::GCAP ? ShortList::WCAP + 1 : n;
+}
+
+// The K largest of a short list of at most 64 entries, by every wave for itself and without a barrier: each lane holds
+// an entry, the entries are broadcast one after the other (readlane) and every lane counts those above its own.  (A
+// bisection with ballots until exactly K entries are left takes twice as long.)  ids: this wave's copy of their ids, best
+// first; s_av: their values, by the first wave.  False (in all waves alike) if equal values straddle the K-th place.
+__device__ __forceinline__ bool take_k(const unsigned long long* s_ent, const ShortList& sl, int K, int32_t* ids, float* s_av) {
+  const int lane = threadIdx.x & 63;
+  const unsigned long long me = s_ent[sl.at(min(lane, sl.n - 1))];
+  const int key = lane < sl.n ? (int)((uint32_t)(me >> 32) ^ 0x80000000u) : (int)0x80000000;   // (as a signed number)
+  int rank = 0;
+#pragma unroll
+  for (int e = 0; e < 64; e += 16) {                       // (lanes past the last entry hold the smallest number)
+    if (e >= sl.n) break;                                  // (constant lane numbers: three instructions an entry)
+#pragma unroll
+    for (int k = 0; k < 16; ++k) rank += (int)(__builtin_amdgcn_readlane(key, e + k) > key);
+  }
+  const bool take = lane < sl.n && rank < K;
+  if (__popcll(__ballot(take)) != K) return false;         // (equal values have equal ranks)
+  const int pos = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(__ballot(take) >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)__ballot(take), 0u));
+  if (take) {
+    ids[pos] = (int)~(uint32_t)me;
+    if (threadIdx.x < 64) s_av[pos] = key_to_att((uint32_t)(me >> 32));
   }
   return true;
+}
+
+// How many entries of the short list exceed `me`, the quad's lanes together.
+__device__ __forceinline__ int list_rank_quad(const unsigned long long* s_ent, const ShortList& sl, unsigned long long me,
+                                              int part) {
+  int rank = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const ulonglong2* e2 = (const ulonglong2*)(s_ent + w * ShortList::WCAP);
+    const int q = (sl.of(w) + 3) >> 2;
+    for (int i = part; i < q; i += 4) {
+      const ulonglong2 a = e2[2 * i], b = e2[2 * i + 1];
+      rank += ((int)(a.x > me) + (int)(a.y > me)) + ((int)(b.x > me) + (int)(b.y > me));
+    }
+  }
+  rank += dpp_i<0xB1, 0xf>(0, rank);                       // quad_perm [1,0,3,2]
+  rank += dpp_i<0x4E, 0xf>(0, rank);                       // quad_perm [2,3,0,1]
+  return rank;
 }
 
 // Radix select on the order-preserving keys (10 + 10 + 10 + 2 bits) straight from the row in
@@ -210,24 +247,52 @@ __device__ __forceinline__ void select_radix(const float* __restrict__ arow, int
   }
 }
 
-// ---- streaming log-sum-exp pieces -----------------------------------------------------------
+// ---- log-sum-exp pieces -----------------------------------------------------------------------
+// In units of log 2: m the largest term of the lane so far, s the sum of 2^(term - m).
+#define L2E 1.4426950408889634f
+#define LN2 0.6931471805599453f
 struct Lse { float m, s; };
 
-__device__ __forceinline__ void lse_add4(Lse& a, const float4 x, const float4 f) {
-  const float v0 = f.x + x.x, v1 = f.y + x.y, v2 = f.z + x.z, v3 = f.w + x.w;
-  const float mn = fmaxf(a.m, fmaxf(fmaxf(v0, v1), fmaxf(v2, v3)));
-  a.s = a.s * __expf(a.m - mn) + (__expf(v0 - mn) + __expf(v1 - mn)) + (__expf(v2 - mn) + __expf(v3 - mn));
-  a.m = mn;
+// N float4 of a column against the (scaled) f terms: one fused multiply-add, one subtraction, one exp2 and one
+// addition per term, and the maximum.
+template <int N>
+__device__ __forceinline__ Lse lse_block(const float4 (&x)[N], const float4 (&f)[N]) {
+  float t[4 * N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    t[4 * i] = fmaf(x[i].x, L2E, f[i].x); t[4 * i + 1] = fmaf(x[i].y, L2E, f[i].y);
+    t[4 * i + 2] = fmaf(x[i].z, L2E, f[i].z); t[4 * i + 3] = fmaf(x[i].w, L2E, f[i].w);
+  }
+  Lse r;
+  r.m = t[0];
+#pragma unroll
+  for (int i = 1; i < 4 * N; ++i) r.m = fmaxf(r.m, t[i]);
+  float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 4 * N; i += 2) {
+    s0 += __builtin_amdgcn_exp2f(t[i] - r.m);
+    s1 += __builtin_amdgcn_exp2f(t[i + 1] - r.m);
+  }
+  r.s = s0 + s1;
+  return r;
+}
+__device__ __forceinline__ Lse lse_join(Lse a, Lse b) {
+  Lse r;
+  r.m = fmaxf(a.m, b.m);
+  r.s = a.s * __builtin_amdgcn_exp2f(a.m - r.m) + b.s * __builtin_amdgcn_exp2f(b.m - r.m);
+  return r;
 }
 
+// all lanes of a candidate together; natural logarithm
 template <int LPC>
 __device__ __forceinline__ float lse_finish(Lse a) {
   static_assert(LPC == 16 || LPC == 64, "a candidate's lanes are one DPP row or one wave");
   float M = row16_max(a.m);
   if (LPC == 64) M = fmaxf(fmaxf(lane_f(M, 0), lane_f(M, 16)), fmaxf(lane_f(M, 32), lane_f(M, 48)));
-  float s = row16_sum(a.s * __expf(a.m - M));
+  float s = row16_sum(a.s * __builtin_amdgcn_exp2f(a.m - M));
   if (LPC == 64) s = (lane_f(s, 0) + lane_f(s, 16)) + (lane_f(s, 32) + lane_f(s, 48));
-  return (M < LOG0_CLASS) ? LOG0F : M + fast_logf(s);    // (s >= 1: the largest term contributes 1)
+  const float r = (M + __builtin_amdgcn_logf(s)) * LN2;    // (s >= 1: the largest term contributes 1)
+  return (M < LOG0_CLASS) ? LOG0F : r;
 }
 
 // Block-wide maximum / sum (logits mode: log-sum-exp of a whole attention row).  The per-lane
@@ -270,34 +335,41 @@ __device__ __forceinline__ unsigned long long joint_key(double J, int tok, bool 
   return (k & ~0xFFFFull) | (unsigned long long)(0xFFFF - tok);
 }
 
-// Grid: (Wb, U).  flags bit 0: the attention rows start on 16-byte boundaries.
+// Grid: (1 << sh, Wb, ceil(U / (1 << sh))), sh = bits 4-7 of flags: utterance z * 2^sh + x, beam slot y.  With sh = 3 the
+// work-groups of an utterance share an XCD (work-groups go round-robin over the eight), and with it the L2 in
+// which a column that several beam slots score is fetched once.
+// flags bit 0: the whole row can be held in registers (NV4 * BLOCK granules).
 // The arguments in front of the parameter block are what the first loads of a work-group need (the records
-// of the current buffer = p.rec[cur], p.uinfo, p.finished as words, the attention rows, p.Wb, p.V): as plain
+// of the current buffer = p.rec[cur], p.uinfo, p.finished as words, the attention rows, Wb, p.V): as plain
 // leading arguments they are handed to the wave in registers when it starts (kernel-argument preload),
 // so that the record's load does not have to wait for a load of the argument block first.
-// BIGK: more candidates per hypothesis than one wave ranks (K > 64, or ids beyond 65535).  Only that form of the
+// NV4: granules of the row per lane.  BIGK: more candidates per hypothesis than one wave ranks (K > 64, or ids
+// beyond 65535).  Only that form of the
 // kernel carries the paths for it: candidate arrays in global memory when K exceeds the work-group, the exact
 // ranking by the whole work-group, the eos-run rule's work-group-wide path (a second sum beside the first in
-// the column pass, the test across all waves).  They cost registers that the common form does without (69
-// against 77-89, i.e. seven work-groups per compute unit against five or six).
-template <int BLOCK, int LPC, int CB, int IT, bool BIGK>
-__global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const HypRec* __restrict__ rec_now,
+// the column pass, the test across all waves).  They cost registers that the common form does without.
+template <int BLOCK, int LPC, int CB, int IT, int NV4, bool BIGK>
+__global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 && CB * IT <= 6 ? 7 : 5))) void k_score(const HypRec* __restrict__ rec_now,
                                                  const UttInfo* __restrict__ uinfo, const uint32_t* __restrict__ fin_words,
                                                  const float* __restrict__ att, int Wb, int V, int flags, int l,
-                                                 Params p, ScoreSmem sm, int cur) {
+                                                 ScoreArgs p) {
   extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ __align__(16) float s_thr[BLOCK / 64];        // the waves' pivots
+  __shared__ int s_cnt[BLOCK / 64];                        // short list: entries per wave
+  __shared__ int32_t s_wid[BIGK ? 1 : BLOCK];              // the K candidates, each wave's own copy
   __shared__ uint32_t s_scan[BLOCK / 64 + 1];
-  __shared__ uint32_t s_w[2 * (BLOCK / 64)];
   __shared__ uint32_t s_sel[2];
   __shared__ float s_e2w[(BLOCK / 64) * MAX_EOS_RUN + 1];
   __shared__ int s_nvalid;
-  __shared__ __align__(8) float s_red[4 * (BLOCK / 64)];   // BLOCK/64 floats, then BLOCK/64 doubles
+  __shared__ __align__(8) float s_red[4 * (BLOCK / 64)];   // per wave: floats (a row's maxima), then doubles (its sums)
+  __shared__ float s_lse;                                  // raw scores in: the row's log-sum-exp
   __shared__ double s_eos[2];                              // eos scores, computed early, written at the end
   __shared__ float s_e2f[2 * MAX_EOS_RUN];                 // eos-run rule: f terms of the last R frames (both kinds)
 
-  const int tid = threadIdx.x;
-  const int u = blockIdx.y;
-  const int grp = u * Wb + blockIdx.x;
+  const int tid = threadIdx.x, w = uni(tid >> 6);
+  const int sh = (flags >> 4) & 15;
+  const int u = (int)((blockIdx.z << sh) + blockIdx.x);
+  const int grp = u * Wb + (int)blockIdx.y;
   // first round of loads, g's record and the utterance's constants: one 64-byte line and one 16-byte entry
   // through the scalar path (uniform addresses, nothing in this kernel writes them)
   const HypRec rec = rec_now[grp];
@@ -306,22 +378,34 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
   // can take the scalar path, a byte load cannot)
   const uint32_t fin_word = fin_words[u >> 2];
   TRACE_DECL;
-  const int K = p.K;
-  const bool smallk = !BIGK || (K <= BLOCK);
-
   // ---------------- the attention row -----------------------------------------------------------
   // As soon as the record says that the slot holds a hypothesis its row is fetched, all loads in
-  // flight together (a dead slot fetches nothing).
+  // flight together (a dead slot fetches nothing).  Whole 16-byte granules by the lanes in turn; what a row that
+  // is not aligned has before and after them by the first lanes.
   const float* arow = att + (size_t)grp * V;
-  const bool in_regs = p.restricted && (V & 3) == 0 && (V >> 2) <= PIVOT_NV4 * BLOCK && (flags & 1);
-  float4 arow_r[PIVOT_NV4];
-  const int dead = (int)((fin_word >> (8 * (u & 3))) & 0xffu) | (rec.live == 0);
-  if (in_regs && !dead) {
-    const float4* a4 = (const float4*)arow;
-    const int nv4 = V >> 2;
+  const bool in_regs = (flags & 1) != 0;
+  RowRegs<NV4> row;
+  row.head = (int)((0u - (unsigned)((uintptr_t)arow >> 2)) & 3u);
+  const int ng = (V - row.head) >> 2;                      // whole granules
+  const int tail = V - row.head - 4 * ng;
+  row.n_ex = row.head + tail;
+  row.ex_id = tid < row.head ? tid : row.head + 4 * ng + (tid - row.head);
+  row.ex = -__builtin_huge_valf();
+  auto fetch_row = [&]() {
+    const float4* a4 = (const float4*)(arow + row.head);
 #pragma unroll
-    for (int k = 0; k < PIVOT_NV4; ++k) arow_r[k] = a4[min(tid + k * BLOCK, nv4 - 1)];
-  }
+    for (int k = 0; k < NV4; ++k) row.v[k] = a4[min(tid + k * BLOCK, ng - 1)];
+    if (tid < row.n_ex) row.ex = arow[row.ex_id];
+  };
+  PIN4(rec.live, rec.off, ui.BT, fin_word);
+  PIN4(p.xT, p.Bcum, p.gn, p.gb);
+  PIN4(p.grp_list, p.grp, p.lambda, p.beta);
+  PIN4(p.Tp, p.K, p.win_m1, p.eos_run);
+  PIN4(p.wp_max, p.off_f, p.mode, p.err);
+  const int dead = (int)((fin_word >> (8 * (u & 3))) & 0xffu) | (rec.live == 0);
+  if (in_regs && !dead) fetch_row();
+  const int K = p.K;
+  const bool smallk = !BIGK || (K <= BLOCK);
   const int T = ui.T;
   const int tau = rec.tau, tau_end = rec.tau_end;
   const int rs = rec.rs, re = rec.re, last = rec.last;
@@ -333,58 +417,49 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
     p.union_win[2 * ((l + 1) & 1) + 1] = -1;
   }
   if (dead) {
-    if (tid == 0) {
-      p.grp_n[grp] = 0; p.win_s[grp] = 0; p.win_e[grp] = -1; p.stopped[grp] = 0;
-      p.ctc_eos[grp] = LOG0D; p.joint_eos[grp] = LOG0D; p.grp_cells[grp] = 0;
-    }
+    // (the grid is whole eights of utterances; those past the last are dead here too)
+    if (tid == 0 && u < p.U) p.grp[grp] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
     return;
   }
 
   TRACE_MARK(0);
-  uint32_t* s_work = (uint32_t*)(smem + sm.off_work);
-  float* s_F = (float*)(smem + sm.off_f);
-  float* s_Fb = s_F + sm.wp_max;
+  uint32_t* s_work = (uint32_t*)(smem);
+  // (the radix histogram, or) the short list, and the granules that hold its values
+  unsigned long long* s_ent = (unsigned long long*)s_work;
+  float4* s_gran = (float4*)(smem + p.off_small);         // (the arrays of that place are only used when these are done with)
+  int32_t* s_gid = (int32_t*)(s_gran + 4 * ShortList::GCAP);
+  float* s_F = (float*)(smem + p.off_f);                  // f terms, in units of log 2
+  float* s_Fb = s_F + p.wp_max;
   // per-candidate arrays of the group (K <= BLOCK): sort key and joint score (8 bytes each), then
   // id, prefix-score increment, attention value, eos-run scratch (4 bytes each)
-  const int Ks = smallk ? K : 0;
-  unsigned long long* s_key = (unsigned long long*)(smem + sm.off_small);
+  const int Ks = BIGK ? (smallk ? K : 0) : 64;
+  unsigned long long* s_key = (unsigned long long*)(smem + p.off_small);
   double* s_J = (double*)(s_key + Ks);                     // joint score as computed (NaN kept)
   int32_t* s_cid = (int32_t*)(s_J + Ks);                   // only touched when smallk
   float* s_inc = (float*)(s_cid + Ks);
   float* s_av = s_inc + Ks;
-  float* s_pre = s_av + Ks;                                // eos-run rule: prefix score without the last R frames
+  float* s_pre = s_av + Ks;                                // BIGK: prefix score without the last R frames
   int32_t* g_cid = p.cand_id + (size_t)grp * K;
 
-  // logits mode: the row holds unnormalised scores; log_softmax is folded in here (the order of
+  // raw scores in: the row holds unnormalised scores; log_softmax is folded in here (the order of
   // the ids is the same, only the values the scores use are shifted by the row's log-sum-exp)
+  const bool logits = (p.mode & SC_LOGITS) != 0;
   float row_lse = 0.0f;
-  if (p.att_logits) {
-    float* s_redf = s_red;
-    double* s_redd = (double*)(s_red + 2 * (BLOCK / 64));
+  float x_blank = 0.0f;
+  const float x_eos = arow[p.eos_id];
+  if (logits) x_blank = arow[p.blank_id];
+  if (logits && !in_regs) {
     float m = -3.0e38f, sum = 0.0f;
-    if (in_regs) {
-      const int nv4 = V >> 2;
-#pragma unroll
-      for (int k = 0; k < PIVOT_NV4; ++k)
-        if (tid + k * BLOCK < nv4)
-          m = fmaxf(m, fmaxf(fmaxf(arow_r[k].x, arow_r[k].y), fmaxf(arow_r[k].z, arow_r[k].w)));
-      const float M = block_max_f<BLOCK>(m, s_redf);
-#pragma unroll
-      for (int k = 0; k < PIVOT_NV4; ++k)
-        if (tid + k * BLOCK < nv4)
-          sum += (__expf(arow_r[k].x - M) + __expf(arow_r[k].y - M)) + (__expf(arow_r[k].z - M) + __expf(arow_r[k].w - M));
-      row_lse = (float)((double)M + log(block_sum_d<BLOCK>(sum, s_redd)));
-    } else {
-      for (int i = tid; i < V; i += BLOCK) m = fmaxf(m, arow[i]);
-      const float M = block_max_f<BLOCK>(m, s_redf);
-      for (int i = tid; i < V; i += BLOCK) sum += __expf(arow[i] - M);
-      row_lse = (float)((double)M + log(block_sum_d<BLOCK>(sum, s_redd)));
-    }
+    for (int i = tid; i < V; i += BLOCK) m = fmaxf(m, arow[i]);
+    const float M = block_max_f<BLOCK>(m, s_red);
+    for (int i = tid; i < V; i += BLOCK) sum += __expf(arow[i] - M);
+    row_lse = (float)((double)M + log(block_sum_d<BLOCK>(sum, (double*)(s_red + BLOCK / 64))));
+    if (tid == 0) s_lse = row_lse;                         // (read after further barriers)
   }
 
   // ---------------- window (needs only g's record) ----------------------------------------
   int s = l > 1 ? l : 1, e = T;
-  if (p.win_union) {            // s^l = min_ij s_ij, e^l = max_ij e_ij (last two equations of Sec. 3.2.3)
+  if (p.mode & SC_UNION) {            // s^l = min_ij s_ij, e^l = max_ij e_ij (last two equations of Sec. 3.2.3)
     if (p.win_m1 >= 0) s = max(s, p.union_win[2 * (l & 1)] - p.win_m1);
     if (p.win_m2 >= 0) e = min(e, p.union_win[2 * (l & 1) + 1]);
   } else {
@@ -396,9 +471,8 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
   const int W = e >= s ? e - s + 1 : 0;
   const int t0 = s & ~3;                                   // column loads start on a 16-byte boundary
   const int n4 = W > 0 ? ((e - t0) >> 2) + 1 : 0;
-  const int Wp = n4 * 4;
-  const float* gn = p.gn[cur] + (size_t)grp * p.Tp;
-  const float* gb = p.gb[cur] + (size_t)grp * p.Tp;
+  const float* gn = p.gn + (size_t)grp * p.Tp;
+  const float* gb = p.gb + (size_t)grp * p.Tp;
   // Stored forward variables have the per-frame reference B_t taken out (see Params::Bcum); all
   // increments of this step are relative to off'(g) + B_r, r = g's reference frame
   const double* Bu = p.Bcum + (size_t)u * p.Tp;
@@ -406,84 +480,157 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
   const double offr = off + Bref;
   const double BT = ui.BT - Bref;                          // B_T - B_r
 
-  // eos inputs (thread 0), fetched now so that nothing waits for them later
-  float eos_n = LOG0F, eos_b = LOG0F, eos_a = 0.0f;
-  if (tid == 0) {
-    if (rs <= T && re >= T) { eos_n = gn[T]; eos_b = gb[T]; }
-    eos_a = arow[p.eos_id];               // (logits mode: shifted by the row's log-sum-exp below)
-  }
+  // What the f terms, the eos score and the eos-run rule need of g's state is requested here, behind the row, and
+  // used after the candidate selection: nothing waits for it before.
+  auto in_range = [&](int t) { return t >= s && t <= e && t - 1 >= rs && t - 1 <= re; };   // frame t has an f term
+  const int pr0 = min(max(t0 + tid - 1, 0), T);
+  const float f0_n = gn[pr0], f0_b = gb[pr0];
+  const double f0_B = Bu[pr0];
+  float eos_n = LOG0F, eos_b = LOG0F;
+  if (tid == 0 && rs <= T && re >= T) { eos_n = gn[T]; eos_b = gb[T]; }
 
   TRACE_MARK(1);
-  // ---------------- stage the f terms of the window in LDS ---------------------------------
-  // gamma_{t-1}(g) - off' - B_r = stored_{t-1} + (B_{t-1} - B_r); far from r the second part is
-  // large and coarse in fp32, and the term is then negligible by that same factor
-  auto f_terms = [&](int t, float& f, float& fb) {
-    f = LOG0F; fb = LOG0F;
-    if (t >= s && t <= e) {
-      const int pr = t - 1;
-      if (pr >= rs && pr <= re) {
-        const float bt = (float)(Bu[pr] - Bref);
-        const float n = gn[pr]; fb = gb[pr]; f = canon0(lae(n, fb) + bt); fb = canon0(fb + bt);
-      }
-    }
-  };
   const int R = p.eos_run;
   const bool e2 = (p.end_flags & 4) && R > 0 && T >= R && W > 0 && e == T && re == T &&
                   max(s, rs) <= T - R + 1;
-  const bool wave_rank = !BIGK || (smallk && K <= 64 && V <= 65536);  // the group's list is ranked by one wave on 64-bit keys
+  constexpr bool wave_rank = !BIGK;                        // the group's list is ranked by one wave on 64-bit keys
   // eos-run rule with few candidates: the f terms of the last R frames are kept apart (and left out of the
   // window's arrays), so that the sums below stop at frame T - R; the first wave completes them at the end
   const bool e2w = e2 && wave_rank;
   const bool e2g = BIGK && e2 && !wave_rank;               // the rule by the whole work-group (many candidates)
-  for (int i = tid; i < Wp; i += BLOCK) {
-    float f, fb;
-    f_terms(t0 + i, f, fb);
-    const int k = t0 + i - (T - R + 1);
-    if (e2w && k >= 0 && k < R) { s_e2f[k] = f; s_e2f[MAX_EOS_RUN + k] = fb; f = LOG0F; fb = LOG0F; }
-    s_F[i] = f; s_Fb[i] = fb;
-  }
+  // the arrays hold whole rounds of LPC * IT float4 (log0 past the window's end), so that the sums need no bounds
+  const int n4r = max(1, (n4 + LPC * IT - 1) / (LPC * IT)) * (LPC * IT);
   const double lam = p.lambda, jbase = (1.0 - lam) * acum + p.beta * (double)l;
-  // eos-run rule: E_t = phi_t(g) of frame t = T-R+1+tid, fetched now so that the test at the end does not wait for it
-  float e2_Et = LOG0F;
-  if (e2 && tid < R) {
-    const int t = T - R + 1 + tid;
-    e2_Et = canon0(lae(gn[t], gb[t]) + (float)(Bu[t] - Bref));
-  }
-  if (tid == 0) {
-    // eos: phi_T(g) = off' + B_T + stored
-    const float ce = (rs <= T && re >= T) ? canon0(lae(eos_n, eos_b)) : LOG0F;
-    const bool v = ce > LOG0_CLASS;
-    const double ctc = v ? offr + BT + (double)ce : LOG0D;
-    s_eos[0] = ctc;
-    s_eos[1] = v ? lam * ctc + (1.0 - lam) * (double)(eos_a - row_lse) + jbase : LOG0D;
-  }
+  // eos-run rule: E_t = phi_t(g) of frame t = T-R+1+tid
+  float e2_Et = LOG0F, e2_n = LOG0F, e2_b = LOG0F;
+  double e2_B = 0.0;
+  if (e2 && tid < R) { const int t = T - R + 1 + tid; e2_n = gn[t]; e2_b = gb[t]; e2_B = Bu[t]; }
+  // The f terms of the window into LDS:
+  // gamma_{t-1}(g) - off' - B_r = stored_{t-1} + (B_{t-1} - B_r); far from r the second part is
+  // large and coarse in fp32, and the term is then negligible by that same factor
+  auto stage_state = [&]() {
+    float n = f0_n, b = f0_b;
+    double B = f0_B;
+    for (int i = tid; i < 4 * n4r; i += BLOCK) {
+      const int t = t0 + i;
+      if (i >= BLOCK) { const int pr = min(max(t - 1, 0), T); n = gn[pr]; b = gb[pr]; B = Bu[pr]; }
+      float f = LOG0F, fb = LOG0F;
+      if (in_range(t)) {
+        const float bt = (float)(B - Bref);
+        f = canon0(lae(n, b) + bt); fb = canon0(b + bt);
+      }
+      const int k = t - (T - R + 1);
+      if (e2w && k >= 0 && k < R) { s_e2f[k] = f; s_e2f[MAX_EOS_RUN + k] = fb; f = LOG0F; fb = LOG0F; }
+      s_F[i] = f * L2E; s_Fb[i] = fb * L2E;
+    }
+    if (e2 && tid < R) e2_Et = canon0(lae(e2_n, e2_b) + (float)(e2_B - Bref));
+    if (tid == 0) {
+      // eos: phi_T(g) = off' + B_T + stored  (raw scores: the joint score still lacks the row's log-sum-exp)
+      const float ce = (rs <= T && re >= T) ? canon0(lae(eos_n, eos_b)) : LOG0F;
+      const bool v = ce > LOG0_CLASS;
+      const double ctc = v ? offr + BT + (double)ce : LOG0D;
+      s_eos[0] = ctc;
+      s_eos[1] = v ? lam * ctc + (1.0 - lam) * (double)x_eos + jbase : LOG0D;
+    }
+  };
   TRACE_MARK(2);
 
   // ---------------- 1. candidates -----------------------------------------------------------
-  if (p.restricted) {
+  // direct: the K ids lie in s_wid (a copy per wave) and s_av, else in s_cid / s_av (or, K > BLOCK, in global memory)
+  bool direct = false;
+  if (p.mode & SC_RESTRICTED) {
     bool ok = false;
     if (in_regs) {
       // ids past the row's end, blank and eos never compete: hold them as -inf
-      const int nv4 = V >> 2;
       const float ninf = -__builtin_huge_valf();
+      const int gb4 = p.blank_id - row.head, ge4 = p.eos_id - row.head;   // (negative: among the first lanes' ids)
 #pragma unroll
-      for (int k = 0; k < PIVOT_NV4; ++k) {
-        const int i4 = tid + k * BLOCK;
-        if (i4 >= nv4) arow_r[k] = make_float4(ninf, ninf, ninf, ninf);
-        if (i4 == (p.blank_id >> 2) || i4 == (p.eos_id >> 2)) {
-          const int jb = i4 == (p.blank_id >> 2) ? (p.blank_id & 3) : -1;
-          const int je = i4 == (p.eos_id >> 2) ? (p.eos_id & 3) : -1;
-          if (jb == 0 || je == 0) arow_r[k].x = ninf;
-          if (jb == 1 || je == 1) arow_r[k].y = ninf;
-          if (jb == 2 || je == 2) arow_r[k].z = ninf;
-          if (jb == 3 || je == 3) arow_r[k].w = ninf;
+      for (int k = 0; k < NV4; ++k) {
+        if ((k + 1) * BLOCK > ng && tid + k * BLOCK >= ng) row.v[k] = make_float4(ninf, ninf, ninf, ninf);
+        auto drop = [&](int g) {                           // (uniform test first: one register of NV4, one lane)
+          if (g >= 4 * k * BLOCK && g < 4 * (k + 1) * BLOCK && (g >> 2) - k * BLOCK == tid) {
+            if ((g & 3) == 0) row.v[k].x = ninf;
+            if ((g & 3) == 1) row.v[k].y = ninf;
+            if ((g & 3) == 2) row.v[k].z = ninf;
+            if ((g & 3) == 3) row.v[k].w = ninf;
+          }
+        };
+        drop(gb4); drop(ge4);
+      }
+      if (tid < row.n_ex && (row.ex_id == p.blank_id || row.ex_id == p.eos_id)) row.ex = ninf;
+      float m4[NV4], fmx = row.ex;                         // the granules' maxima, the lane's
+#pragma unroll
+      for (int k = 0; k < NV4; ++k) {
+        m4[k] = fmaxf(fmaxf(row.v[k].x, row.v[k].y), fmaxf(row.v[k].z, row.v[k].w));
+        fmx = fmaxf(fmx, m4[k]);
+      }
+      TRACE_MARK(6);
+      const float thr = wave_pivot(fmx, K, min(max(ng - 64 * w, 0), 64), ng < BLOCK ? ng : BLOCK);
+      if ((tid & 63) == 0) s_thr[w] = thr;
+      if (logits) {                                        // (the row's maximum, ids that do not compete left out)
+        float m = row16_max(fmx);
+        m = fmaxf(fmaxf(lane_f(m, 0), lane_f(m, 16)), fmaxf(lane_f(m, 32), lane_f(m, 48)));
+        if ((tid & 63) == 0) s_red[w] = m;
+      }
+      lds_barrier();
+      TRACE_MARK(7);
+      // at least K values are >= L (-inf if there are not K lanes with finite maxima)
+      const float L = fminf(fminf(s_thr[0], s_thr[1]), fminf(s_thr[2], s_thr[3]));
+      const int nh = collect_hits<BLOCK, NV4>(row, m4, L, p.blank_id, p.eos_id, s_gran + w * ShortList::GCAP,
+                                              s_gid + w * ShortList::GCAP, s_ent + w * ShortList::WCAP);
+      if ((tid & 63) == 0) s_cnt[w] = nh;
+      TRACE_MARK(14);
+      float M = 0.0f;
+      if (logits) {
+        M = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
+        M = fmaxf(fmaxf(M, -3.0e38f), fmaxf(x_blank, x_eos));
+        float sum = __expf(row.ex - M);
+#pragma unroll
+        for (int k = 0; k < NV4; ++k)
+          sum += (__expf(row.v[k].x - M) + __expf(row.v[k].y - M)) + (__expf(row.v[k].z - M) + __expf(row.v[k].w - M));
+        if (tid == 0) sum += __expf(x_blank - M) + __expf(x_eos - M);
+        sum = row16_sum(sum);
+        const double ws = ((double)lane_f(sum, 0) + (double)lane_f(sum, 16)) +
+                          ((double)lane_f(sum, 32) + (double)lane_f(sum, 48));
+        if ((tid & 63) == 0) ((double*)(s_red + BLOCK / 64))[w] = ws;
+      }
+      stage_state();
+      lds_barrier();
+      TRACE_MARK(15);
+      ShortList sl;
+      sl.n0 = uni(s_cnt[0]); sl.n1 = uni(s_cnt[1]); sl.n2 = uni(s_cnt[2]); sl.n3 = uni(s_cnt[3]);
+      sl.n = (sl.n0 + sl.n1) + (sl.n2 + sl.n3);
+      // (NaNs in the row: fewer than K values may have been found)
+      ok = sl.n >= K && max(max(sl.n0, sl.n1), max(sl.n2, sl.n3)) <= ShortList::WCAP;
+      if (logits && (BIGK || w == 2)) {                    // (by one wave, beside the columns' loads)
+        const double* sd = (const double*)(s_red + BLOCK / 64);
+        row_lse = (float)((double)M + log((sd[0] + sd[1]) + (sd[2] + sd[3])));
+        if (tid == 128) s_lse = row_lse;
+      }
+      if (!BIGK && ok && sl.n <= 64) {
+        direct = take_k(s_ent, sl, K, s_wid + 64 * w, s_av);
+        wave_lds_fence();
+      }
+      if (ok && !direct) {
+        // exact rank, four lanes per entry; the rank is the candidate's place
+        for (int e0 = 0; e0 < sl.n; e0 += BLOCK / 4) {
+          const int en = e0 + (tid >> 2);
+          const unsigned long long me = en < sl.n ? s_ent[sl.at(en)] : ~0ull;
+          const int rank = list_rank_quad(s_ent, sl, me, tid & 3);
+          if ((tid & 3) == 0 && en < sl.n && rank < K) {
+            const int mid = (int)~(uint32_t)me;
+            // (small K: the ids stay in LDS; the global copy is written with the scores at the end, so that
+            // no store is pending when the candidates' columns are fetched)
+            if (smallk) { s_cid[rank] = mid; s_av[rank] = key_to_att((uint32_t)(me >> 32)); }
+            else g_cid[rank] = mid;
+          }
         }
       }
-      ok = select_pivot<BLOCK>(arow_r, K, p.blank_id, p.eos_id, (unsigned long long*)s_work,
-                               s_w, smallk, s_cid, s_av, g_cid, TRACE_ARG);
     }
+    if (!in_regs) stage_state();
     if (!ok) select_radix<BLOCK>(arow, V, K, p.blank_id, p.eos_id, s_work, s_scan, s_sel, smallk, s_cid, s_av, g_cid);
   } else {
+    stage_state();
     const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
     for (int i = tid; i < K; i += BLOCK) {
       const int id = full_v_id(i, lo_ex, hi_ex);
@@ -492,7 +639,11 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
     }
   }
   // candidates and f terms visible to the whole block (large K: the ids are read back from global memory)
-  if (smallk) lds_barrier(); else __syncthreads();
+  if (!direct) { if (smallk) lds_barrier(); else __syncthreads(); }
+  auto cand_id = [&](int c) -> int {
+    if (direct) return s_wid[64 * w + c];
+    return smallk ? s_cid[c] : checked(p, g_cid[c], 0, V - 1, ERR_CAND_ID);
+  };
   TRACE_MARK(3);
 
   // ---------------- 3. prefix scores ----------------------------------------------------
@@ -503,13 +654,14 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
   float* g_catt = p.cand_att + (size_t)grp * K;
   double* g_ctc = p.cand_ctc + (size_t)grp * K;
   double* g_joint = p.cand_joint + (size_t)grp * K;
-  for (int c0 = sg; c0 < K; c0 += NSG * CB) {
+  for (int cb = 0; cb < K; cb += NSG * CB) {              // (uniform: every chain takes part in every round)
+    const int c0 = cb + sg;
     float4 x[CB][IT];
     int ids[CB];
 #pragma unroll
     for (int b = 0; b < CB; ++b) {
       const int c = c0 + b * NSG;
-      ids[b] = (c < K) ? checked(p, smallk ? s_cid[c] : g_cid[c], 0, V - 1, ERR_CAND_ID) : -1;
+      ids[b] = (c < K) ? cand_id(c) : -1;
       const float4* col = (const float4*)(xu + (size_t)(ids[b] < 0 ? 0 : ids[b]) * p.Tp + t0);
 #pragma unroll
       for (int it = 0; it < IT; ++it)                        // unconditional (clamped) loads: all in flight together
@@ -521,45 +673,43 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
       if (ids[b] < 0) continue;                            // uniform over the LPC lanes of a chain
       const int id = ids[b];
       const float4* col = (const float4*)(xu + (size_t)id * p.Tp + t0);
-      const float4* f4 = (const float4*)(s_F + ((id == last) ? sm.wp_max : 0));   // Fb follows F
+      const float4* f4 = (const float4*)(s_F + ((id == last) ? p.wp_max : 0));   // Fb follows F
       float inc = LOG0F, pre = LOG0F;
-      {
-        Lse a; a.m = LOG0F; a.s = 0.0f;
-        if (!e2g) {
+      if (!e2g) {
+        float4 f[IT];
 #pragma unroll
-          for (int it = 0; it < IT; ++it) {
-            const int i = q + it * LPC;
-            if (i < n4) lse_add4(a, x[b][it], f4[i]);
-          }
-          for (int i = q + IT * LPC; i < n4; i += LPC) lse_add4(a, col[i], f4[i]);
-        } else {
-          // the sum in two parts: frames up to T - R (needed on its own below) and the last R frames,
-          // which only the few lanes at the window's end hold
-          Lse aq; aq.m = LOG0F; aq.s = 0.0f;
-          const int tc = T - R;
-          auto split = [&](const float4 xv, const float4 fv, int tb) {
-            float4 fc;
-            fc.x = tb <= tc ? fv.x : LOG0F; fc.y = tb + 1 <= tc ? fv.y : LOG0F;
-            fc.z = tb + 2 <= tc ? fv.z : LOG0F; fc.w = tb + 3 <= tc ? fv.w : LOG0F;
-            lse_add4(a, xv, fc);
-            if (tb + 3 > tc) {
-              fc.x = tb > tc ? fv.x : LOG0F; fc.y = tb + 1 > tc ? fv.y : LOG0F;
-              fc.z = tb + 2 > tc ? fv.z : LOG0F; fc.w = tb + 3 > tc ? fv.w : LOG0F;
-              lse_add4(aq, xv, fc);
-            }
-          };
+        for (int it = 0; it < IT; ++it) f[it] = f4[q + it * LPC];
+        Lse a = lse_block<IT>(x[b], f);
+        for (int i0 = LPC * IT; i0 < n4; i0 += LPC * IT) {   // (windows beyond one round of loads)
+          float4 y[IT];
 #pragma unroll
-          for (int it = 0; it < IT; ++it) {
-            const int i = q + it * LPC;
-            if (i < n4) split(x[b][it], f4[i], t0 + 4 * i);
-          }
-          for (int i = q + IT * LPC; i < n4; i += LPC) split(col[i], f4[i], t0 + 4 * i);
-          pre = lse_finish<LPC>(a);
-          const float mn = fmaxf(a.m, aq.m);                // whole window: both parts
-          a.s = a.s * __expf(a.m - mn) + aq.s * __expf(aq.m - mn);
-          a.m = mn;
+          for (int it = 0; it < IT; ++it) { y[it] = col[min(i0 + q + it * LPC, n4 - 1)]; f[it] = f4[i0 + q + it * LPC]; }
+          a = lse_join(a, lse_block<IT>(y, f));
         }
-        inc = (W > 0) ? lse_finish<LPC>(a) : LOG0F;
+        inc = lse_finish<LPC>(a);
+      } else {
+        // the sum in two parts: frames up to T - R (needed on its own below) and the last R frames
+        Lse a, aq;
+        a.m = aq.m = LOG0F; a.s = aq.s = 0.0f;
+        const int tc = T - R;
+        for (int i0 = 0; i0 < n4; i0 += LPC * IT) {
+#pragma unroll
+          for (int it = 0; it < IT; ++it) {
+            const int i = i0 + q + it * LPC;
+            const int tb = t0 + 4 * i;
+            float4 xv[1], fv[1];
+            const float4 f = f4[i];
+            xv[0] = i0 == 0 ? x[b][it] : col[min(i, n4 - 1)];
+            fv[0].x = tb <= tc ? f.x : LOG0F; fv[0].y = tb + 1 <= tc ? f.y : LOG0F;
+            fv[0].z = tb + 2 <= tc ? f.z : LOG0F; fv[0].w = tb + 3 <= tc ? f.w : LOG0F;
+            a = lse_join(a, lse_block<1>(xv, fv));
+            fv[0].x = tb > tc ? f.x : LOG0F; fv[0].y = tb + 1 > tc ? f.y : LOG0F;
+            fv[0].z = tb + 2 > tc ? f.z : LOG0F; fv[0].w = tb + 3 > tc ? f.w : LOG0F;
+            aq = lse_join(aq, lse_block<1>(xv, fv));
+          }
+        }
+        pre = lse_finish<LPC>(a);
+        inc = lse_finish<LPC>(lse_join(a, aq));
       }
       if (q == 0 && wave_rank) {
         // (joint scores and sort keys: one lane per candidate at the end, not one pass per chain here)
@@ -617,7 +767,7 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
       for (int c = tid; c < K; c += BLOCK) {
         const int id = smallk ? s_cid[c] : g_cid[c];
         const float* colf = xu + (size_t)id * p.Tp;
-        const float* ff = s_F + ((id == last) ? sm.wp_max : 0);
+        const float* ff = s_F + ((id == last) ? p.wp_max : 0);
         float xv[E2C];
 #pragma unroll
         for (int k = 0; k < E2C; ++k) xv[k] = colf[min(T - R + 1 + k0 + k, T)];   // all loads in flight
@@ -625,7 +775,7 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
 #pragma unroll
         for (int k = 0; k < E2C; ++k) {
           if (k0 + k < R) {
-            acc = lae(acc, ff[T - R + 1 + k0 + k - t0] + xv[k]);
+            acc = lae(acc, fmaf(ff[T - R + 1 + k0 + k - t0], LN2, xv[k]));
             xmax[k] = fmaxf(xmax[k], canon0(acc));
           }
         }
@@ -656,39 +806,40 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
     }                                                      // maybe
     lds_barrier();                                         // s_nvalid is reset below
   }
-  auto group_outputs = [&]() {
-    p.stopped[grp] = fire;
-    p.ctc_eos[grp] = s_eos[0]; p.joint_eos[grp] = s_eos[1];
-    p.win_s[grp] = s; p.win_e[grp] = e;
-    p.grp_cells[grp] = (long long)K * (long long)W;
+  auto group_outputs = [&](int n) {
+    const double je = s_eos[1];
+    p.grp[grp] = GroupOut{n, fire, s, e, s_eos[0],
+                          logits && je > (double)LOG0_CLASS ? je - (1.0 - lam) * (double)row_lse : je,
+                          (long long)K * (long long)W, {0, 0, 0, 0, 0, 0}};
   };
-  if (!wave_rank && tid == 0) group_outputs();
+  if (!smallk && tid == 0) group_outputs(0);               // (the list builder counts)
 
   if (smallk) {
     if (wave_rank) {
-      // one lane of the first wave per candidate from here on
+      // one lane of the first wave per entry from here on
       constexpr int E2W = 16;                              // eos-run rule: frames per round of loads
       constexpr bool E2_EARLY = (CB * IT <= 6);            // (the forms with more column loads in flight have no registers to spare)
       float xv0[E2_EARLY ? E2W : 1];
       if (E2_EARLY && e2 && tid < 64) {                    // the candidate's posteriors of the last R frames: on
-        const float* colf = xu + (size_t)s_cid[tid < K ? tid : 0] * p.Tp;   // their way while the other waves finish
+        const float* colf = xu + (size_t)cand_id(tid < K ? tid : 0) * p.Tp;   // their way while the other waves finish
 #pragma unroll
         for (int k = 0; k < E2W; ++k) xv0[k] = colf[min(T - R + 1 + k, T)];
       }
       lds_barrier();                                       // prefix scores complete; the other waves are done
       if (tid >= 64) return;
+      const bool has = tid < K;
+      const int id = cand_id(has ? tid : 0);
+      if (logits) row_lse = s_lse;
       if (e2) {
         // eos-run rule by one wave.  The sums so far stop at frame T - R; walking through the last R frames
         // completes them and gives, on the way, X_t = best running prefix score of the extensions at frame
         // t, to be held against E_t (in lane t - (T-R+1) since the start of the kernel).
-        const bool has = tid < K;
         auto wave_max = [](float v) {
           v = row16_max(v);
           return fmaxf(fmaxf(lane_f(v, 0), lane_f(v, 16)), fmaxf(lane_f(v, 32), lane_f(v, 48)));
         };
-        const int e2id = s_cid[has ? tid : 0];
-        const float* colf = xu + (size_t)e2id * p.Tp;
-        const float* ff = s_e2f + ((e2id == last) ? MAX_EOS_RUN : 0);
+        const float* colf = xu + (size_t)id * p.Tp;
+        const float* ff = s_e2f + ((id == last) ? MAX_EOS_RUN : 0);
         float acc = has ? s_inc[tid] : LOG0F;
         fire = 1;
         for (int k0 = 0; k0 < R; k0 += E2W) {
@@ -714,38 +865,31 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
         if (has) s_inc[tid] = canon0(acc);                 // the whole window's sum
         wave_lds_fence();
       }
-      if (tid == 0) group_outputs();
-      // rank by (joint desc, token asc) on 64-bit keys
-      unsigned long long me = 0ull;
-      if (tid < K) {                                       // joint score (Eq. (1)) and sort key of candidate `tid`
-        const float inc = s_inc[tid], av = s_av[tid] - row_lse;
-        const bool valid = inc > LOG0_CLASS;
-        const double ctc = valid ? offr + (double)inc : LOG0D;
-        const double J = valid ? lam * ctc + (1.0 - lam) * (double)av + jbase : LOG0D;
-        me = joint_key(J, s_cid[tid] & 0xFFFF, valid && J == J);
-        s_J[tid] = J; s_av[tid] = av; s_key[tid] = me;
-      }
-      wave_lds_fence();                                    // keys: written by their lanes, read by all below
+      // rank by (joint desc, token asc) on 64-bit keys; joint score (Eq. (1)) and sort key of entry `tid`
+      const float inc = has ? s_inc[tid] : LOG0F;
+      const float av = s_av[has ? tid : 0] - row_lse;
+      const bool valid = inc > LOG0_CLASS;
+      const double ctc = valid ? offr + (double)inc : LOG0D;
+      const double J = valid ? lam * ctc + (1.0 - lam) * (double)av + jbase : LOG0D;
+      const unsigned long long me = has ? joint_key(J, id & 0xFFFF, valid && J == J) : 0ull;
+      const int me_lo = (int)(uint32_t)me, me_hi = (int)(uint32_t)(me >> 32);
       int rank = 0;
-      const ulonglong2* k2 = (const ulonglong2*)s_key;
-      int c = 0;
-      for (; c + 8 <= K; c += 8) {                         // four reads in flight at a time
-        const ulonglong2 o0 = k2[c >> 1], o1 = k2[(c >> 1) + 1], o2 = k2[(c >> 1) + 2], o3 = k2[(c >> 1) + 3];
-        rank += ((int)(o0.x > me) + (int)(o0.y > me)) + ((int)(o1.x > me) + (int)(o1.y > me)) +
-                ((int)(o2.x > me) + (int)(o2.y > me)) + ((int)(o3.x > me) + (int)(o3.y > me));
+#pragma unroll
+      for (int c = 0; c < 64; c += 16) {                   // (lanes past the last entry hold zeros)
+        if (c >= K) break;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          const unsigned long long o = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane(me_hi, c + k) << 32) |
+                                       (uint32_t)__builtin_amdgcn_readlane(me_lo, c + k);
+          rank += (int)(o > me);
+        }
       }
-      for (; c + 1 < K; c += 2) {
-        const ulonglong2 o = k2[c >> 1];
-        rank += (int)(o.x > me) + (int)(o.y > me);
-      }
-      if (K & 1) rank += (int)(s_key[K - 1] > me);
       const int nv = __popcll(__ballot(me != 0ull));
-      if (!fire && me != 0ull && rank < p.Wb) {
-        const size_t o = (size_t)grp * p.Wb + rank;
-        p.grp_J[o] = s_J[tid]; p.grp_ci[o] = tid; p.grp_tok[o] = s_cid[tid];
-        p.grp_inc[o] = s_inc[tid]; p.grp_att[o] = s_av[tid];
+      if (!fire && me != 0ull && rank < Wb) p.grp_list[(size_t)grp * Wb + rank] = ListEntry{J, id, inc, av, 0};
+      if (tid == 0) group_outputs(fire ? 0 : min(nv, Wb));
+      if ((p.mode & SC_KEEP) && has) {
+        g_cid[tid] = id; g_inc[tid] = inc; g_catt[tid] = av; g_ctc[tid] = ctc; g_joint[tid] = J;
       }
-      if (tid == 0) p.grp_n[grp] = fire ? 0 : min(nv, p.Wb);
     } else {
       // rank by (joint desc, token asc), exact comparison: four lanes per candidate
       if (tid == 0) s_nvalid = 0;
@@ -765,24 +909,20 @@ __global__ __launch_bounds__(BLOCK, (CB * IT > 8 ? 4 : 5)) void k_score(const Hy
           rank += dpp_i<0xB1, 0xf>(0, rank);               // quad_perm [1,0,3,2]
           rank += dpp_i<0x4E, 0xf>(0, rank);               // quad_perm [2,3,0,1]
           if (part == 0 && mv) {
-            if (rank < p.Wb) {
-              const size_t o = (size_t)grp * p.Wb + rank;
-              p.grp_J[o] = me; p.grp_ci[o] = ee; p.grp_tok[o] = s_cid[ee];
-              p.grp_inc[o] = s_inc[ee]; p.grp_att[o] = s_av[ee];
-            }
+            if (rank < Wb) p.grp_list[(size_t)grp * Wb + rank] = ListEntry{me, s_cid[ee], s_inc[ee], s_av[ee], 0};
             atomicAdd(&s_nvalid, 1);
           }
         }
       }
       lds_barrier();
-      if (tid == 0) p.grp_n[grp] = fire ? 0 : min(s_nvalid, p.Wb);
-    }
-    if (p.keep_cand) {
-      for (int c = tid; c < K; c += BLOCK) {
-        const float inc = s_inc[c];
-        g_cid[c] = s_cid[c]; g_inc[c] = inc; g_catt[c] = s_av[c];
-        g_ctc[c] = inc > LOG0_CLASS ? offr + (double)inc : LOG0D;
-        g_joint[c] = s_J[c];
+      if (tid == 0) group_outputs(fire ? 0 : min(s_nvalid, Wb));
+      if (p.mode & SC_KEEP) {
+        for (int c = tid; c < K; c += BLOCK) {
+          const float inc = s_inc[c];
+          g_cid[c] = s_cid[c]; g_inc[c] = inc; g_catt[c] = s_av[c];
+          g_ctc[c] = inc > LOG0_CLASS ? offr + (double)inc : LOG0D;
+          g_joint[c] = s_J[c];
+        }
       }
     }
   }
@@ -798,8 +938,8 @@ __global__ __launch_bounds__(BLOCK) void k_group_top(Params p, int cur) {
   __shared__ int s_pick[MAX_BEAM];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int grp = blockIdx.x, u = grp / p.Wb, K = p.K;
-  if (p.finished[u] || !p.rec[cur][grp].live) return;      // k_score already wrote grp_n = 0
-  if (p.stopped[grp]) { if (tid == 0) p.grp_n[grp] = 0; return; }
+  if (p.finished[u] || !p.rec[cur][grp].live) return;      // k_score already wrote a count of 0
+  if (p.grp[grp].stopped) { if (tid == 0) p.grp[grp].n = 0; return; }
   const double* J = p.cand_joint + (size_t)grp * K;
   const int32_t* ids = p.cand_id + (size_t)grp * K;       // equal scores: smaller token id first
   int n = 0;
@@ -826,15 +966,15 @@ __global__ __launch_bounds__(BLOCK) void k_group_top(Params p, int cur) {
       s_pick[r] = (bi == 0x7fffffff) ? -1 : bi;
       if (bi != 0x7fffffff) {
         const size_t o = (size_t)grp * p.Wb + r;
-        p.grp_J[o] = bv; p.grp_ci[o] = bi; p.grp_tok[o] = p.cand_id[(size_t)grp * K + bi];
-        p.grp_inc[o] = p.cand_inc[(size_t)grp * K + bi]; p.grp_att[o] = p.cand_att[(size_t)grp * K + bi];
+        const size_t g = (size_t)grp * K + bi;
+        p.grp_list[o] = ListEntry{bv, p.cand_id[g], p.cand_inc[g], p.cand_att[g], 0};
       }
     }
     __syncthreads();
     if (s_pick[r] < 0) break;
     ++n;
   }
-  if (tid == 0) p.grp_n[grp] = n;
+  if (tid == 0) p.grp[grp].n = n;
 }
 
 // The same list for candidate sets of up to BLOCK * EPT ids, from registers: every thread loads
@@ -848,8 +988,8 @@ __global__ __launch_bounds__(BLOCK) void k_group_top_regs(Params p, int cur) {
   __shared__ unsigned long long s_k[2][NW];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int grp = blockIdx.x, u = grp / p.Wb, K = p.K;
-  if (p.finished[u] || !p.rec[cur][grp].live) return;      // the score kernel already wrote grp_n = 0
-  if (p.stopped[grp]) { if (tid == 0) p.grp_n[grp] = 0; return; }
+  if (p.finished[u] || !p.rec[cur][grp].live) return;      // the score kernel already wrote a count of 0
+  if (p.grp[grp].stopped) { if (tid == 0) p.grp[grp].n = 0; return; }
   const double* J = p.cand_joint + (size_t)grp * K;
   unsigned long long key[EPT];
 #pragma unroll
@@ -885,10 +1025,9 @@ __global__ __launch_bounds__(BLOCK) void k_group_top_regs(Params p, int cur) {
       if (key[k] == best) key[k] = 0ull;                    // only its owner holds this key
     if (tid == 0) {
       const size_t o = (size_t)grp * p.Wb + r, g = (size_t)grp * K + c;
-      p.grp_J[o] = J[c]; p.grp_ci[o] = c; p.grp_tok[o] = p.cand_id[g];
-      p.grp_inc[o] = p.cand_inc[g]; p.grp_att[o] = p.cand_att[g];
+      p.grp_list[o] = ListEntry{J[c], p.cand_id[g], p.cand_inc[g], p.cand_att[g], 0};
     }
     ++n;
   }
-  if (tid == 0) p.grp_n[grp] = n;
+  if (tid == 0) p.grp[grp].n = n;
 }

@@ -55,8 +55,7 @@ __global__ __launch_bounds__(BLOCK) void k_score_dense(Params p, const float* __
     q_jbase[tid] = (1.0 - p.lambda) * r.att + p.beta * (double)l;
     if (live && e >= s) { atomicMin(&s_lo, s); atomicMax(&s_hi, e); }
     if (chunk == 0 && !live) {
-      p.grp_n[h] = 0; p.win_s[h] = 0; p.win_e[h] = -1; p.stopped[h] = 0;
-      p.ctc_eos[h] = LOG0D; p.joint_eos[h] = LOG0D; p.grp_cells[h] = 0;
+      p.grp[h] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
     }
   }
   __syncthreads();
@@ -92,18 +91,16 @@ __global__ __launch_bounds__(BLOCK) void k_score_dense(Params p, const float* __
     const float ce = has ? canon0(lae(gn[T], gb[T])) : LOG0F;
     const bool v = ce > LOG0_CLASS;
     const double ctc = v ? q_offr[j] + (Bu[T] - Bu[q_ref[j]]) + (double)ce : LOG0D;
-    p.ctc_eos[h] = ctc;
-    p.joint_eos[h] = v ? p.lambda * ctc + (1.0 - p.lambda) * (double)att[h * V + p.eos_id] + q_jbase[j] : LOG0D;
-    p.win_s[h] = q_s[j]; p.win_e[h] = q_e[j]; p.stopped[h] = 0;
     const int W = q_e[j] >= q_s[j] ? q_e[j] - q_s[j] + 1 : 0;
-    p.grp_cells[h] = (long long)K * (long long)W;
+    p.grp[h] = GroupOut{0, 0, q_s[j], q_e[j], ctc,
+                        v ? p.lambda * ctc + (1.0 - p.lambda) * (double)att[h * V + p.eos_id] + q_jbase[j] : LOG0D,
+                        (long long)K * (long long)W, {0, 0, 0, 0, 0, 0}};
   }
   __syncthreads();
   // ---- per slot: the largest f term M_j; the terms are then held as (f - M_j) * log2(e), so that
   // a product term is 2^(x * log2(e) + held) <= 1: one fused multiply-add, one exp2, one add per
   // term, no running maximum.  (A sum that underflows -- every term more than ~85 nats below
   // M_j -- is redone the careful way, see below.)
-  constexpr float L2E = 1.4426950408889634f, LN2 = 0.6931471805599453f;
   for (int j = w; j < Wb; j += NW) {
     if (!q_live[j]) continue;
     float* Fj = s_F + (size_t)j * Tp;
@@ -157,14 +154,13 @@ __global__ __launch_bounds__(BLOCK) void k_score_dense(Params p, const float* __
           for (int it = 0; it < NIT; ++it) {
             const int i = lane + it * 64;
             if (i < n4) {
-              const float4 f2 = F4[i];
-              float4 f;
-              f.x = canon0(fmaf(f2.x, LN2, mref)); f.y = canon0(fmaf(f2.y, LN2, mref));
-              f.z = canon0(fmaf(f2.z, LN2, mref)); f.w = canon0(fmaf(f2.w, LN2, mref));
-              lse_add4(a, x[it], f);
+              float4 f[1], xv[1];
+              f[0] = F4[i]; xv[0] = x[it];
+              a = lse_join(a, lse_block<1>(xv, f));
             }
           }
           inc = lse_finish<64>(a);
+          inc = inc > LOG0_CLASS ? inc + mref : LOG0F;
         }
       }
       mine = (lane == j) ? inc : mine;
@@ -195,10 +191,9 @@ __global__ __launch_bounds__(BLOCK) void k_score_dense(Params p, const float* __
       for (int t = s + lane; t <= e; t += 64) {
         const int pr = t - 1;
         if (pr < rs || pr > re) continue;
-        const float v = canon0(gb[pr] + (float)(Bu[pr] - Bref)) + colf[t];
-        const float mn = fmaxf(a.m, v);
-        a.s = a.s * __expf(a.m - mn) + __expf(v - mn);
-        a.m = mn;
+        Lse v;
+        v.m = (canon0(gb[pr] + (float)(Bu[pr] - Bref)) + colf[t]) * L2E; v.s = 1.0f;
+        a = lse_join(a, v);
       }
       const float inc = lse_finish<64>(a);
       if (lane == 0) {

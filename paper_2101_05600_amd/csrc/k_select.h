@@ -80,19 +80,19 @@ struct SurvivorIn {
 };
 // FPL consecutive frames per lane, 64 * FPL frames per pass.
 template <int FPL>
-__device__ __forceinline__ void wave_survivor_fpl(const Params& p, int u, int n, int cur, const SurvivorIn& in,
+__device__ __forceinline__ void wave_survivor_fpl(const SelectArgs& p, int Wb, int u, int n, const SurvivorIn& in,
                                                   int& arg_n, int& arg_b, float& delta_out, double& bref_out) {
   const int lane = threadIdx.x & 63;
-  const size_t h0 = (size_t)u * p.Wb;
-  const size_t hp = h0 + checked(p, in.par, 0, p.Wb - 1, ERR_LIST_ENTRY);
+  const size_t h0 = (size_t)u * Wb;
+  const size_t hp = h0 + checked(p, in.par, 0, Wb - 1, ERR_LIST_ENTRY);
   const float* xu = p.xT + (size_t)u * p.V * p.Tp;
   const float* x0 = xu + (size_t)p.blank_id * p.Tp;
   const float* xc = xu + (size_t)checked(p, in.tok, 0, p.V - 1, ERR_TOKEN) * p.Tp;
   const double* Bu = p.Bcum + (size_t)u * p.Tp;
-  const float* pgn = p.gn[cur] + hp * p.Tp;
-  const float* pgb = p.gb[cur] + hp * p.Tp;
-  float* cgn = p.gn[cur ^ 1] + (h0 + n) * p.Tp;
-  float* cgb = p.gb[cur ^ 1] + (h0 + n) * p.Tp;
+  const float* pgn = p.gn + hp * p.Tp;
+  const float* pgb = p.gb + hp * p.Tp;
+  float* cgn = p.gn_new + (h0 + n) * p.Tp;
+  float* cgb = p.gb_new + (h0 + n) * p.Tp;
   const int T = in.T;
   const int s = checked(p, in.s, 1, T, ERR_WINDOW), en = checked(p, in.en, s, T, ERR_WINDOW), rs = in.rs, re = in.re;
   const double Bnew = Bu[checked(p, in.ptau, 0, T, ERR_TIME_INDEX)];   // the child's reference frame is the parent's tau
@@ -177,12 +177,12 @@ __device__ __forceinline__ void wave_survivor_fpl(const Params& p, int u, int n,
 // host asks for that when the window margins keep windows within 128 frames but for rare exceptions: the
 // forms with more frames per lane are what sets the kernel's register count (97 against 58).
 template <int FPLMAX>
-__device__ __forceinline__ void wave_survivor(const Params& p, int u, int n, int cur, const SurvivorIn& in,
+__device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u, int n, const SurvivorIn& in,
                                               int& arg_n, int& arg_b, float& delta_out, double& bref_out) {
   const int W = in.en - in.s + 1;
-  if (FPLMAX == 2 || W <= 128) wave_survivor_fpl<2>(p, u, n, cur, in, arg_n, arg_b, delta_out, bref_out);
-  else if (W <= 256) wave_survivor_fpl<4>(p, u, n, cur, in, arg_n, arg_b, delta_out, bref_out);
-  else wave_survivor_fpl<8>(p, u, n, cur, in, arg_n, arg_b, delta_out, bref_out);
+  if (FPLMAX == 2 || W <= 128) wave_survivor_fpl<2>(p, Wb, u, n, in, arg_n, arg_b, delta_out, bref_out);
+  else if (W <= 256) wave_survivor_fpl<4>(p, Wb, u, n, in, arg_n, arg_b, delta_out, bref_out);
+  else wave_survivor_fpl<8>(p, Wb, u, n, in, arg_n, arg_b, delta_out, bref_out);
 }
 
 // How many of the keys s_k2[0 .. 2 * quads) (four per quad, zero padding at the end) exceed `me`,
@@ -243,13 +243,12 @@ __device__ __forceinline__ int pack_contenders(const unsigned long long* s_key, 
 // prefix-score terms of this step.  st_* / ring_*: the utterance's state as loaded by lane 0
 // (scalars) and lanes m < M (ring entries).  Writes the state back, the two per-old-slot
 // outputs and the work counters; returns whether the utterance finishes at this step.
-__device__ __forceinline__ bool wave_ended_set(const Params& p, int u, int l, int T, int lmax_u, bool has_best,
+__device__ __forceinline__ bool wave_ended_set(const SelectArgs& p, int Wb, int u, UttState* us, int l, int T, int lmax_u, bool has_best,
                                                double best, int n_new, bool mine, double je_in, int stp_in,
                                                int tau_j, long long cells_j, double st_best, int st_n,
                                                int st_cnt, double ring_sc, int ring_tag) {
-  const int lane = threadIdx.x & 63, Wb = p.Wb;
-  const size_t h0 = (size_t)u * Wb;
-  UttState* us = p.utt + u;
+  const int lane = threadIdx.x & 63;
+  const size_t h0 = (size_t)u * Wb, UW = (size_t)p.U * Wb;
   const bool forced = (l >= lmax_u);
   const double je = mine ? je_in : LOG0D;
   const int stp = mine ? stp_in : 0;
@@ -268,7 +267,7 @@ __device__ __forceinline__ bool wave_ended_set(const Params& p, int u, int l, in
     const double ov = __shfl_xor(bje, o); const int oj = __shfl_xor(bj, o);
     if (ov > bje || (ov == bje && oj < bj)) { bje = ov; bj = oj; }
   }
-  if (lane < Wb) { p.out_eos_added[h0 + lane] = (uint8_t)added; p.out_stopped[h0 + lane] = (uint8_t)stp; }
+  if (lane < Wb) { p.out8[UW + h0 + lane] = (uint8_t)added; p.out8[2 * UW + h0 + lane] = (uint8_t)stp; }
   const int n_before = __shfl(st_n, 0);
   const int n_ended = n_before + n_add;
   const int cnt = __shfl(st_cnt, 0) + n_tauT;
@@ -303,19 +302,20 @@ __device__ __forceinline__ bool wave_ended_set(const Params& p, int u, int l, in
   return fin;
 }
 
-// Dynamic LDS: 16 * ((Wb * Wb + 9) & ~1) + 32 * Wb * Wb bytes (the list entries and the packed contenders).
+// Dynamic LDS: 16 * ((Wb * Wb + 9) & ~1) + 28 * Wb * Wb bytes (the list entries and the packed contenders).
 template <int BLOCK, int FPLMAX>
-__global__ __launch_bounds__(BLOCK) void k_select(Params p, int l, int cur) {
+__global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
+                                                  const GroupOut* __restrict__ grp, const ListEntry* __restrict__ grp_list,
+                                                  const UttInfo* __restrict__ uinfo, int Wb, int l, SelectArgs p) {
   constexpr int NW = BLOCK / 64;
   extern __shared__ __align__(16) unsigned char sel_smem[];
-  const int NE_ = p.Wb * p.Wb;
+  const int NE_ = Wb * Wb;
   const int NK_ = (NE_ + 9) & ~1;                                     // NE + 8 keys, an even count: both key arrays on 16-byte boundaries
   unsigned long long* s_key = (unsigned long long*)sel_smem;          // [NE + 8]
   unsigned long long* s_ck = s_key + NK_;                             // [NE + 8] keys of the entries that can reach the new beam
   double* s_J = (double*)(s_ck + NK_);                                // [NE]
   int* s_par = (int*)(s_J + NE_);                                     // [NE] each
-  int* s_ci = s_par + NE_;
-  int* s_tok = s_ci + NE_;
+  int* s_tok = s_par + NE_;
   int* s_cidx = s_tok + NE_;
   float* s_inc = (float*)(s_cidx + NE_);
   float* s_att = s_inc + NE_;
@@ -333,27 +333,27 @@ __global__ __launch_bounds__(BLOCK) void k_select(Params p, int l, int cur) {
   __shared__ double s_bref[MAX_BEAM];                      // B at each new hypothesis's reference frame
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int u = blockIdx.x, Wb = p.Wb;
+  const int u = blockIdx.x;
   if (p.finished[u]) return;               // outputs of a finished utterance were settled when it finished
-  const int nxt = cur ^ 1;
   const size_t h0 = (size_t)u * Wb;
-  TRACE_POINT(p, u, 8);
+  TRACE_POINT(p, (size_t)u * Wb, 8);
 
   // ---- first round of loads: everything that depends on nothing --------------------------------
   if (tid < Wb) {
     const size_t h = h0 + tid;
-    const HypRec r = p.rec[cur][h];
-    o_live[tid] = r.live; o_n[tid] = p.grp_n[h]; o_stp[tid] = p.stopped[h];
+    const HypRec r = rec_now[h];
+    const GroupOut g = grp[h];
+    o_live[tid] = r.live; o_n[tid] = g.n; o_stp[tid] = g.stopped;
     o_tau[tid] = r.tau; o_tau_end[tid] = r.tau_end;
     o_rs[tid] = r.rs; o_re[tid] = r.re; o_last[tid] = r.last;
-    o_ws[tid] = p.win_s[h]; o_we[tid] = p.win_e[h]; o_ref[tid] = r.ref;
-    o_cells[tid] = p.grp_cells[h];
-    o_je[tid] = p.joint_eos[h]; o_hatt[tid] = r.att; o_off[tid] = r.off;
+    o_ws[tid] = g.win_s; o_we[tid] = g.win_e; o_ref[tid] = r.ref;
+    o_cells[tid] = g.cells;
+    o_je[tid] = g.joint_eos; o_hatt[tid] = r.att; o_off[tid] = r.off;
   }
-  const int T = p.lens[u];
-  const int lmax_u = p.lmax[u];
+  const int T = uinfo[u].T;
+  const int lmax_u = uinfo[u].lmax;
   // utterance state, wave 0: lane 0 the scalars, lanes m < M the ring entries
-  UttState* us = p.utt + u;
+  UttState* us = utt + u;
   double st_best = LOG0D, ring_sc = LOG0D;
   int st_n = 0, st_cnt = 0, ring_tag = -1;
   if (w == 0) {
@@ -372,10 +372,10 @@ __global__ __launch_bounds__(BLOCK) void k_select(Params p, int l, int cur) {
     if (i < NE) {
       const int j = i / Wb, r = i - j * Wb;
       const size_t o = h0 * Wb + i;
-      const int nj = p.grp_n[h0 + j];
-      const double Jv = p.grp_J[o];
-      s_par[i] = j; s_ci[i] = p.grp_ci[o]; s_tok[i] = p.grp_tok[o];
-      s_inc[i] = p.grp_inc[o]; s_att[i] = p.grp_att[o];
+      const int nj = grp[h0 + j].n;
+      const ListEntry le = grp_list[o];
+      const double Jv = le.J;
+      s_par[i] = j; s_tok[i] = le.tok; s_inc[i] = le.inc; s_att[i] = le.att;
       s_J[i] = Jv;
       const unsigned long long bb = (unsigned long long)__double_as_longlong(Jv);
       const unsigned long long k = (bb >> 63) ? ~bb : (bb | 0x8000000000000000ull);
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(BLOCK) void k_select(Params p, int l, int cur) {
   if (tid < 2) s_cnt[tid] = 0;
   if (tid == 2) s_min = ~0ull;
   lds_barrier();
-  TRACE_POINT(p, u, 9);
+  TRACE_POINT(p, (size_t)u * Wb, 9);
   int ne = 0;
 #pragma unroll 8
   for (int j = 0; j < Wb; ++j) ne += o_n[j];
@@ -411,7 +411,7 @@ __global__ __launch_bounds__(BLOCK) void k_select(Params p, int l, int cur) {
   }
   lds_barrier();
 
-  TRACE_POINT(p, u, 10);
+  TRACE_POINT(p, (size_t)u * Wb, 10);
   // ---- ended set, end detection: wave 0, lane j = old slot j ---------------------------------
   const int n_new = min(ne, Wb);
   if (w == 0) {
@@ -419,17 +419,18 @@ __global__ __launch_bounds__(BLOCK) void k_select(Params p, int l, int cur) {
     const double best = has_best ? s_J[checked(p, s_sel[0], 0, NE - 1, ERR_LIST_ENTRY)] : LOG0D;
     const int j = lane < Wb ? lane : 0;
     const bool mine = lane < Wb && o_live[j];
-    const bool fin = wave_ended_set(p, u, l, T, lmax_u, has_best, best, n_new, mine, o_je[j], o_stp[j], o_tau[j],
+    const bool fin = wave_ended_set(p, Wb, u, us, l, T, lmax_u, has_best, best, n_new, mine, o_je[j], o_stp[j], o_tau[j],
                                     o_cells[j], st_best, st_n, st_cnt, ring_sc, ring_tag);
     if (lane == 0) s_fin = fin ? 1 : 0;
   }
-  TRACE_POINT(p, u, 11);
+  TRACE_POINT(p, (size_t)u * Wb, 11);
 
-  TRACE_POINT(p, u, 12);
+  TRACE_POINT(p, (size_t)u * Wb, 12);
   // ---- forward variables of the new hypotheses --------------------------------------------
   // (wave 0 is busy with the ended set above; the other waves take the survivors at once.  A
   // finished utterance's new state is computed too but never used: its slots are marked dead.)
-  const size_t trie_l = ((size_t)l * p.U + u) * Wb;
+  const size_t UW = (size_t)p.U * Wb;
+  float* out_score = (float*)(p.out + 2 * UW);
   for (int n = w - 1; n >= 0 && n < n_new; n += NW - 1) {
     const int e = checked(p, s_sel[n], 0, NE - 1, ERR_LIST_ENTRY), par = s_par[e];
     SurvivorIn in;
@@ -439,10 +440,10 @@ __global__ __launch_bounds__(BLOCK) void k_select(Params p, int l, int cur) {
     int arg_n, arg_b;
     float delta;
     double bref;
-    wave_survivor<FPLMAX>(p, u, n, cur, in, arg_n, arg_b, delta, bref);
+    wave_survivor<FPLMAX>(p, Wb, u, n, in, arg_n, arg_b, delta, bref);
     if (lane == 0) {
-      p.out_tau[h0 + n] = arg_n; p.out_tau_end[h0 + n] = arg_b;
-      p.trie_tau[trie_l + n] = arg_n;
+      p.out[3 * UW + h0 + n] = arg_n; p.out[4 * UW + h0 + n] = arg_b;
+      p.trie[(size_t)2 * p.trie_stride + h0 + n] = arg_n;
       s_ntau[n] = arg_n; s_ntau_end[n] = arg_b; s_delta[n] = delta; s_bref[n] = bref;
     }
   }
@@ -453,9 +454,9 @@ __global__ __launch_bounds__(BLOCK) void k_select(Params p, int l, int cur) {
     const size_t h = h0 + n;
     if (n < n_new) {
       const int e = checked(p, s_sel[n], 0, NE - 1, ERR_LIST_ENTRY), par = s_par[e], tok = s_tok[e];
-      p.out_parent[h] = par; p.out_token[h] = tok; p.out_score[h] = (float)s_J[e];
-      p.out_live[h] = fin ? 0 : 1;
-      p.trie_parent[trie_l + n] = par; p.trie_token[trie_l + n] = tok;
+      p.out[h] = par; p.out[UW + h] = tok; out_score[h] = (float)s_J[e];
+      p.out8[h] = fin ? 0 : 1;
+      p.trie[h] = par; p.trie[p.trie_stride + h] = tok;
       HypRec r;
       r.live = fin ? 0 : 1; r.last = tok; r.rs = o_ws[par]; r.re = o_we[par];
       r.tau = s_ntau[n]; r.tau_end = s_ntau_end[n]; r.ref = o_tau[par]; r.pad = 0;
@@ -463,20 +464,20 @@ __global__ __launch_bounds__(BLOCK) void k_select(Params p, int l, int cur) {
       r.att = o_hatt[par] + (double)s_att[e];
       r.joint = s_J[e];
       r.bref = s_bref[n];
-      p.rec[nxt][h] = r;
+      p.rec_new[h] = r;
       if (p.win_union && !fin) {                 // this hypothesis's share of the next step's window
         atomicMin(&p.union_win[2 * ((l + 1) & 1)], s_ntau[n]);
         atomicMax(&p.union_win[2 * ((l + 1) & 1) + 1], min(s_ntau_end[n] + p.win_m2, T));
       }
     } else {
-      p.out_parent[h] = -1; p.out_token[h] = -1; p.out_score[h] = LOG0F; p.out_live[h] = 0;
-      p.out_tau[h] = 0; p.out_tau_end[h] = 0;
-      p.trie_parent[trie_l + n] = -1; p.trie_token[trie_l + n] = -1; p.trie_tau[trie_l + n] = 0;
-      p.rec[nxt][h].live = 0;
+      p.out[h] = -1; p.out[UW + h] = -1; out_score[h] = LOG0F; p.out8[h] = 0;
+      p.out[3 * UW + h] = 0; p.out[4 * UW + h] = 0;
+      p.trie[h] = -1; p.trie[p.trie_stride + h] = -1; p.trie[(size_t)2 * p.trie_stride + h] = 0;
+      p.rec_new[h].live = 0;
     }
   }
 
-  TRACE_POINT(p, u, 13);
+  TRACE_POINT(p, (size_t)u * Wb, 13);
 }
 
 // Split form of the select kernel: one work-group per (utterance, new beam slot n), used
@@ -492,14 +493,13 @@ __global__ __launch_bounds__(BLOCK) void k_select(Params p, int l, int cur) {
 // is taken from the step number at which the utterance finished (0 or the current step both
 // mean no).
 // Dynamic LDS: 28 * Wb * Wb + 64 bytes (the list entries).
-// The arguments in front of the parameter block are what the first round of loads needs (p.rec[cur], p.utt,
-// p.grp_n and the list arrays, p.Wb): plain leading arguments reach the wave in registers when it starts
-// (kernel-argument preload), so that those loads do not wait for a load of the argument block first.
+// The arguments in front of the block are what the first round of loads needs: plain leading arguments reach the wave
+// in registers when it starts (kernel-argument preload), so that those loads do not wait for a load of the arguments.
+// Grid: (1 << sh, Wb, ceil(U / (1 << sh))), sh = l >> 28: utterance z * 2^sh + x, new slot y (as in k_score).
 template <int BLOCK, int FPLMAX>
 __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
-                                                        const int32_t* __restrict__ grp_n, const double* __restrict__ grp_J,
-                                                        const int32_t* __restrict__ grp_tok, const float* __restrict__ grp_inc,
-                                                        const float* __restrict__ grp_att, int Wb, int l, Params p, int cur) {
+                                                        const GroupOut* __restrict__ grp, const ListEntry* __restrict__ grp_list,
+                                                        const UttInfo* __restrict__ uinfo, int Wb, int l_sh, SelectArgs p) {
   static_assert(BLOCK >= 128, "wave 0 and wave 1 have different jobs");
   extern __shared__ __align__(16) unsigned char split_smem[];
   const int NE = Wb * Wb;
@@ -515,27 +515,29 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
   __shared__ int s_pick[2];                // entry ranked n, entry ranked 0
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int u = blockIdx.x / Wb, n = blockIdx.x - u * Wb;
+  const int l = l_sh & 0xfffffff, sh = l_sh >> 28;
+  const int u = (int)((blockIdx.z << sh) + blockIdx.x), n = (int)blockIdx.y;
+  if (u >= p.U) return;                    // (the grid is whole eights of utterances)
   UttState* us = utt + u;
   const int fs = us->finished_step;        // (tested after the first round of loads is on its way)
-  const int nxt = cur ^ 1;
   const size_t h0 = (size_t)u * Wb;
   const bool lead = (n == 0);
-  if (lead) TRACE_POINT(p, u, 8);
+  if (lead) TRACE_POINT(p, (size_t)u * Wb, 8);
 
   // ---- first round of loads: everything that depends on nothing --------------------------------
   if (tid < Wb) {
     const size_t h = h0 + tid;
     const HypRec r = rec_now[h];
-    o_live[tid] = r.live; o_n[tid] = grp_n[h]; o_stp[tid] = p.stopped[h];
+    const GroupOut g = grp[h];
+    o_live[tid] = r.live; o_n[tid] = g.n; o_stp[tid] = g.stopped;
     o_tau[tid] = r.tau; o_tau_end[tid] = r.tau_end;
     o_rs[tid] = r.rs; o_re[tid] = r.re; o_last[tid] = r.last;
-    o_ws[tid] = p.win_s[h]; o_we[tid] = p.win_e[h]; o_ref[tid] = r.ref;
-    o_cells[tid] = p.grp_cells[h];
-    o_je[tid] = p.joint_eos[h]; o_hatt[tid] = r.att; o_off[tid] = r.off;
+    o_ws[tid] = g.win_s; o_we[tid] = g.win_e; o_ref[tid] = r.ref;
+    o_cells[tid] = g.cells;
+    o_je[tid] = g.joint_eos; o_hatt[tid] = r.att; o_off[tid] = r.off;
   }
-  const int T = p.lens[u];
-  const int lmax_u = p.lmax[u];
+  const int T = uinfo[u].T;
+  const int lmax_u = uinfo[u].lmax;
   double st_best = LOG0D, ring_sc = LOG0D;
   int st_n = 0, st_cnt = 0, ring_tag = -1;
   if (lead && w == 1) {
@@ -553,9 +555,10 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
     if (i < NE) {
       const int j = i / Wb, r = i - j * Wb;
       const size_t o = h0 * Wb + i;
-      const int nj = grp_n[h0 + j];
-      const double Jv = grp_J[o];
-      s_tok[i] = grp_tok[o]; s_inc[i] = grp_inc[o]; s_att[i] = grp_att[o];
+      const int nj = grp[h0 + j].n;
+      const ListEntry le = grp_list[o];
+      const double Jv = le.J;
+      s_tok[i] = le.tok; s_inc[i] = le.inc; s_att[i] = le.att;
       s_J[i] = Jv;
       const unsigned long long b = (unsigned long long)__double_as_longlong(Jv);
       const unsigned long long k = (b >> 63) ? ~b : (b | 0x8000000000000000ull);
@@ -566,7 +569,7 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
   if (tid < 2) s_pick[tid] = -1;
   if (fs != 0 && fs < l) return;           // outputs of a finished utterance were settled when it finished
   lds_barrier();
-  if (lead) TRACE_POINT(p, u, 9);
+  if (lead) TRACE_POINT(p, (size_t)u * Wb, 9);
 
   // ---- rank (total order: joint desc, parent slot asc, token asc = position asc) -------------
   // L lanes per entry, each comparing against every L-th pair of the list
@@ -594,9 +597,10 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
     }
   }
   lds_barrier();
-  if (lead) TRACE_POINT(p, u, 10);
+  if (lead) TRACE_POINT(p, (size_t)u * Wb, 10);
 
-  const size_t trie_l = ((size_t)l * p.U + u) * Wb;
+  const size_t UW = (size_t)p.U * Wb;
+  float* out_score = (float*)(p.out + 2 * UW);
   if (w == 0) {
     // ---- new hypothesis n: forward variables, record, outputs, back-pointer -----------------
     const size_t h = h0 + n;
@@ -609,14 +613,14 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
       int arg_n, arg_b;
       float delta;
       double bref;
-      wave_survivor<FPLMAX>(p, u, n, cur, in, arg_n, arg_b, delta, bref);
+      wave_survivor<FPLMAX>(p, Wb, u, n, in, arg_n, arg_b, delta, bref);
       if (lane == 0) {
-        p.out_tau[h] = arg_n; p.out_tau_end[h] = arg_b;
-        p.trie_tau[trie_l + n] = arg_n;
-        p.out_parent[h] = par; p.out_token[h] = in.tok; p.out_score[h] = (float)s_J[e];
-        p.trie_parent[trie_l + n] = par; p.trie_token[trie_l + n] = in.tok;
+        p.out[3 * UW + h] = arg_n; p.out[4 * UW + h] = arg_b;
+        p.trie[(size_t)2 * p.trie_stride + h] = arg_n;
+        p.out[h] = par; p.out[UW + h] = in.tok; out_score[h] = (float)s_J[e];
+        p.trie[h] = par; p.trie[p.trie_stride + h] = in.tok;
         // (the record's live flag belongs to the utterance's lead work-group, see below)
-        HypRec* r = p.rec[nxt] + h;
+        HypRec* r = p.rec_new + h;
         r->last = in.tok; r->rs = in.s; r->re = in.en; r->tau = arg_n; r->tau_end = arg_b; r->ref = in.ptau;
         r->off = o_off[par] + (double)delta;
         r->att = o_hatt[par] + (double)s_att[e];
@@ -624,9 +628,9 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
         r->bref = bref;
       }
     } else if (lane == 0) {
-      p.out_parent[h] = -1; p.out_token[h] = -1; p.out_score[h] = LOG0F;
-      p.out_tau[h] = 0; p.out_tau_end[h] = 0;
-      p.trie_parent[trie_l + n] = -1; p.trie_token[trie_l + n] = -1; p.trie_tau[trie_l + n] = 0;
+      p.out[h] = -1; p.out[UW + h] = -1; out_score[h] = LOG0F;
+      p.out[3 * UW + h] = 0; p.out[4 * UW + h] = 0;
+      p.trie[h] = -1; p.trie[p.trie_stride + h] = -1; p.trie[(size_t)2 * p.trie_stride + h] = 0;
     }
   } else if (lead && w == 1) {
     // ---- the utterance as a whole: ended set, end detection, live flags ----------------------
@@ -634,13 +638,13 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
     const double best = has_best ? s_J[checked(p, s_pick[1], 0, NE - 1, ERR_LIST_ENTRY)] : LOG0D;
     const int j = lane < Wb ? lane : 0;
     const bool mine = lane < Wb && o_live[j];
-    const bool fin = wave_ended_set(p, u, l, T, lmax_u, has_best, best, n_new, mine, o_je[j], o_stp[j], o_tau[j],
+    const bool fin = wave_ended_set(p, Wb, u, us, l, T, lmax_u, has_best, best, n_new, mine, o_je[j], o_stp[j], o_tau[j],
                                     o_cells[j], st_best, st_n, st_cnt, ring_sc, ring_tag);
     if (lane < Wb) {
       const int lv = (lane < n_new && !fin) ? 1 : 0;
-      p.out_live[h0 + lane] = (uint8_t)lv;
-      p.rec[nxt][h0 + lane].live = lv;
+      p.out8[h0 + lane] = (uint8_t)lv;
+      p.rec_new[h0 + lane].live = lv;
     }
   }
-  if (lead) TRACE_POINT(p, u, 13);
+  if (lead) TRACE_POINT(p, (size_t)u * Wb, 13);
 }
