@@ -91,6 +91,8 @@ struct UttInfo {             // per utterance, constant over a decode
   double BT;                 // B_T
 };
 
+struct DenseSlot;            // (k_dense.h)
+
 struct Params {
   // sizes and configuration
   int32_t U, V, Wb, K, Tp, t_max, blank_id, eos_id;
@@ -116,6 +118,8 @@ struct Params {
   float* gn[2];
   float* gb[2];
   HypRec* rec[2];
+  float* dense_F;            // [U][Wb][Tp] every id a candidate: exp of the f terms (k_dense.h)
+  DenseSlot* dense_slot;     // [U][Wb]
   int32_t keep_cand;         // 1: the per-candidate arrays below are filled every step (ctcbs_peek; large K needs them)
   // per-step scratch between the score and the select kernel
   int32_t* cand_id;          // [U][Wb][K]

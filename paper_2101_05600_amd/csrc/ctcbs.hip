@@ -17,7 +17,7 @@
 #include "k_finalize.h"
 #include "k_ingest.h"
 #include "k_score.h"
-#include "k_score_dense.h"
+#include "k_dense.h"
 #include "k_select.h"
 
 static thread_local int g_last_hip = 0;
@@ -47,8 +47,7 @@ struct ctcbs {
   bool select_fpl2;            // the select kernels' form with the two-frames-per-lane recurrence only
   bool score_wide, score_bigk;
   int score_nv4;               // granules of an attention row per lane
-  int dense_nit, dense_nch;   // all-candidates score kernel: float4 per lane and column (0: not used), chunks per utterance
-  size_t dense_smem_bytes;
+  bool dense;                  // every id a candidate: the kernels of k_dense.h
   // Pinned, device-mapped host memory, one allocation: the progress word that the score kernel refreshes every
   // step (upper half: the step that has begun, lower half: utterances finished before it), the batch set-up that
   // the ingest kernels read (lengths, step caps, first batch-wide window), and the results that k_finalize writes.
@@ -190,7 +189,11 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   p.att_logits = c.att_is_logits ? 1 : 0;
   p.win_union = c.win_union ? 1 : 0;
   // large candidate sets go through the per-candidate arrays in global memory whatever the caller asked for
-  p.keep_cand = (c.keep_candidates || K > 256 || !restricted) ? 1 : 0;
+  p.keep_cand = (c.keep_candidates || K > 256) ? 1 : 0;
+  // every id a candidate (not: few ids, the eos-run rule, raw decoder scores, the batch-wide window): the kernels of
+  // k_dense.h; up to 64 ids k_score ranks the list itself and a step is two launches instead of four
+  h->dense = !restricted && K > 64 && !(c.end_flags & CTCBS_END_EOS_RUN) && !c.att_is_logits && !c.win_union;
+  if (h->dense && K <= 8192) p.keep_cand = c.keep_candidates ? 1 : 0;   // (the list builder for more ids reads those arrays)
 
   // capacity for any batch of lengths <= t_max (the step cap grows with the length)
   h->l_cap_alloc = step_cap(&c, c.t_max);
@@ -212,8 +215,10 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   A(p.uinfo, U8);
   {
     const size_t nc = p.keep_cand ? UW * K : 1;            // (not kept: never touched)
-    A(p.cand_id, nc); A(p.cand_inc, nc); A(p.cand_att, nc); A(p.cand_pre, nc);
-    A(p.cand_ctc, nc); A(p.cand_joint, nc);
+    const size_t nd = h->dense ? UW * K : nc;
+    A(p.cand_id, nc); A(p.cand_inc, nd); A(p.cand_att, nc); A(p.cand_pre, nc);
+    A(p.cand_ctc, nc); A(p.cand_joint, nd);
+    A(p.dense_F, h->dense ? UW * p.Tp : 1); A(p.dense_slot, h->dense ? UW : 1);
   }
   A(p.grp, UW); A(p.grp_list, UW * Wb);
   A(p.utt, (size_t)U); A(p.finished, U8);   /* read as whole words by the score kernel */ A(p.cells, (size_t)U); A(p.groups, (size_t)U);
@@ -279,16 +284,6 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   off += small > gran ? small : gran;
   h->score_nv4 = V <= 3072 ? 3 : (V <= 5120 ? 5 : (V <= 10240 ? 10 : 16));
   h->score_smem_bytes = off;
-  // all-candidates kernel: needs the f terms of all beam slots in LDS and a column window in registers
-  h->dense_nit = 0; h->dense_nch = 1; h->dense_smem_bytes = (size_t)Wb * p.Tp * 4;
-  if (!restricted && !(c.end_flags & CTCBS_END_EOS_RUN) && !c.att_is_logits && !c.win_union &&
-      h->dense_smem_bytes <= 150 * 1024 && p.Tp <= 2048) {
-    h->dense_nit = p.Tp <= 256 ? 1 : (p.Tp <= 512 ? 2 : (p.Tp <= 1024 ? 4 : (p.Tp <= 1536 ? 6 : 8)));
-    // enough work-groups to cover the chip, but at least a few dozen candidates each
-    int nch = (256 + U - 1) / U;
-    const int most = K / 32 > 1 ? K / 32 : 1;
-    h->dense_nch = nch < 1 ? 1 : (nch > most ? most : nch);
-  }
   if (off > 160 * 1024) return CTCBS_EINVAL;
   // per-hypothesis windows whose margins keep them within 128 frames (but for a hypothesis whose two time
   // indices lie far apart): the select kernels then carry the two-frames-per-lane recurrence only
@@ -381,12 +376,34 @@ static hipError_t launch_score(ctcbs* h, const Params& p, const float* att, int 
   }
 }
 
-template <int NIT>
+// Every id a candidate.  64 candidates per work-group where that gives every compute unit a few work-groups (each reads
+// the slots' F once: a third of what it reads of the posteriors), 16 otherwise.
+template <int NT>
+static hipError_t launch_dense_scores(ctcbs* h, const Params& p, const float* att, int l) {
+  const dim3 grid((unsigned)(p.K + 16 * NT - 1) / (16 * NT), (unsigned)p.U);
+#define CTCBS_DENSE(MT)                                                                                            \
+  hipLaunchKernelGGL((k_dense_scores<NT, MT>), grid, dim3(256), 0, h->stream, (const float*)p.xT, (const float*)p.dense_F, \
+                     (const DenseSlot*)p.dense_slot, att, (int)p.Wb, (int)p.Tp, (int)p.V, (int)p.K, p, l, h->cur)
+  if (p.Wb <= 16) CTCBS_DENSE(1); else CTCBS_DENSE(2);
+#undef CTCBS_DENSE
+  return hipGetLastError();
+}
 static hipError_t launch_dense(ctcbs* h, const Params& p, const float* att, int l) {
-  hipError_t ea = allow_lds((const void*)k_score_dense<1024, NIT>, h->dense_smem_bytes);
-  if (ea != hipSuccess) return ea;
-  hipLaunchKernelGGL((k_score_dense<1024, NIT>), dim3(p.U * h->dense_nch), dim3(1024), h->dense_smem_bytes,
-                     h->stream, p, att, l, h->cur, h->dense_nch);
+  hipLaunchKernelGGL((k_dense_prep<256>), dim3(p.Wb, p.U), dim3(256), (size_t)p.Tp * 4, h->stream, p, att, l, h->cur);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if ((long long)p.U * ((p.K + 63) / 64) >= 512) return launch_dense_scores<4>(h, p, att, l);
+  return launch_dense_scores<1>(h, p, att, l);
+}
+
+// the groups' lists from joint scores in global memory
+static hipError_t launch_lists(ctcbs* h, const Params& p, const float* att) {
+  const dim3 grid(p.Wb, p.U);
+#define CTCBS_LIST(E, D) hipLaunchKernelGGL((k_list_top<E, D>), grid, dim3(256), 0, h->stream, p, att, h->cur)
+  if (p.K > 8192) hipLaunchKernelGGL((k_group_top<256>), dim3(p.U * p.Wb), dim3(256), 0, h->stream, p, h->cur);
+  else if (h->dense) { if (p.K <= 1024) CTCBS_LIST(4, true); else if (p.K <= 5120) CTCBS_LIST(20, true); else CTCBS_LIST(32, true); }
+  else { if (p.K <= 1024) CTCBS_LIST(4, false); else if (p.K <= 5120) CTCBS_LIST(20, false); else CTCBS_LIST(32, false); }
+#undef CTCBS_LIST
   return hipGetLastError();
 }
 
@@ -437,26 +454,14 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   // memory, 16 lanes x 4 float4 wider windows and whole utterances of up to 512 frames; whole-utterance
   // windows beyond that use whole waves, 4 float4 (1024 frames) in flight (see create_impl)
   hipError_t e;
-  switch (h->dense_nit) {                 // every id a candidate: one work-group serves all beam slots
-    case 1: e = launch_dense<1>(h, p, d_att_logp, l); break;
-    case 2: e = launch_dense<2>(h, p, d_att_logp, l); break;
-    case 4: e = launch_dense<4>(h, p, d_att_logp, l); break;
-    case 6: e = launch_dense<6>(h, p, d_att_logp, l); break;
-    case 8: e = launch_dense<8>(h, p, d_att_logp, l); break;
-    default:
-      e = (h->score_lpc == 16) ? (h->score_wide ? launch_score<256, 16, 2, 4>(h, p, d_att_logp, l)
-                                                : launch_score<256, 16, 3, 2>(h, p, d_att_logp, l))
-                               : launch_score<256, 64, 2, 4>(h, p, d_att_logp, l);
-  }
+  if (h->dense) e = launch_dense(h, p, d_att_logp, l);
+  else
+    e = (h->score_lpc == 16) ? (h->score_wide ? launch_score<256, 16, 2, 4>(h, p, d_att_logp, l)
+                                              : launch_score<256, 16, 3, 2>(h, p, d_att_logp, l))
+                             : launch_score<256, 64, 2, 4>(h, p, d_att_logp, l);
   HIPCHK(e);
   if (ev) HIPCHK(hipEventRecord(ev[1], h->stream));       // (the list builder below counts as selection)
-  if (h->dense_nit || p.K > h->score_block) {
-    if (p.K <= 1024 * 8)
-      hipLaunchKernelGGL((k_group_top_regs<1024, 8>), dim3(p.U * p.Wb), dim3(1024), 0, h->stream, p, h->cur);
-    else
-      hipLaunchKernelGGL((k_group_top<256>), dim3(p.U * p.Wb), dim3(256), 0, h->stream, p, h->cur);
-    HIPCHK(hipGetLastError());
-  }
+  if (h->dense || p.K > h->score_block) HIPCHK(launch_lists(h, p, d_att_logp));
   // Small batches leave most compute units idle in the one-work-group-per-utterance form: there the
   // split form (one work-group per new beam slot, each ranking the utterance's lists itself) is
   // faster (measured: U=64 and U=128 at beam 10).  Large batches fill the chip either way and the
@@ -538,7 +543,7 @@ extern "C" int ctcbs_step_static(ctcbs_t* h, const float* d_att_logp, ctcbs_step
   if (!h || !d_att_logp) return CTCBS_EINVAL;
   // candidate sets that go through arrays in global memory (more than 256 candidates per hypothesis, or
   // every id a candidate) would need those arrays here too: not offered
-  if (h->dense_nit || h->p.K > h->score_block) return CTCBS_EINVAL;
+  if (h->dense || h->p.K > h->score_block) return CTCBS_EINVAL;
   if (static_scratch_need(h->p) > CTCBS_STATIC_SCRATCH_BYTES) return CTCBS_EINVAL;
   int dev = -1;
   HIPCHK(hipGetDevice(&dev));

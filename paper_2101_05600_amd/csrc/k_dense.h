@@ -1,0 +1,247 @@
+// Scoring when every id but blank and eos is a candidate (the paper's Eq. (3) as it stands, no pre-selection).
+// The sum over frames of exp(f_t(g) + x_t(c)) is a product of two matrices -- exp(f_t(g)), beam slots by frames, and
+// exp(x_t(c)) = p^c(z_t = c), frames by candidates -- so that one exp2 per (candidate, frame) serves all beam slots of an
+// utterance and the rest is fp32 MFMA.  What is left is the time it takes to read the posteriors once.
+//   k_dense_prep   per (utterance, slot): window, F_t = exp(f_t - M) over it (M the largest f term; 0 outside), eos
+//                  scores, and the one candidate the product does not fit: the repeat of the slot's last label (blank
+//                  variable only, third alignment rule of Sec. 2.1);
+//   k_dense_scores per (utterance, chunk of candidates): the product, then joint scores (Eq. (1));
+//   k_list_top     per (utterance, slot): the group's best-first list.
+// Range: a product below 2^-126 (87 nats under M) counts as nothing; a sum of such products -- below 1e-30 -- is redone
+// frame by frame in the log domain.
+// Not handled here (the host then launches k_score): top-K candidates, up to 64 ids, the eos-run rule, raw
+// decoder scores, the batch-wide window.
+#pragma once
+#include "common.h"
+#include "k_score.h"
+
+struct __align__(64) DenseSlot {
+  int32_t live, last, s, e;  // window
+  float mref, inc_rep;       // M; increment of the candidate that repeats the last label
+  int32_t rs, re, ref;
+  int32_t pad;
+  double offr, jbase;        // off' + B_r; joint score without this step's terms
+};
+
+typedef float f32x4 __attribute__((__vector_size__(16)));
+
+// f term of frame t (log domain): gamma_{t-1}(g) relative to off' + B_r; only where t - 1 lies in the stored range
+__device__ __forceinline__ float dense_f(const float* gn, const float* gb, const double* Bu, double Bref, int t) {
+  return canon0(lae(gn[t - 1], gb[t - 1]) + (float)(Bu[t - 1] - Bref));
+}
+
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __restrict__ att, int l, int cur) {
+  extern __shared__ __align__(16) unsigned char dense_smem[];
+  float* dense_f_lds = (float*)dense_smem;                     // [Tp]
+  __shared__ float s_red[BLOCK / 64], s_rs[BLOCK / 64];
+  const int tid = threadIdx.x, w = uni(tid >> 6);
+  const int Wb = p.Wb, Tp = p.Tp, u = blockIdx.y, j = blockIdx.x;
+  const size_t h = (size_t)u * Wb + j;
+  const HypRec r = p.rec[cur][h];
+  const UttInfo ui = p.uinfo[u];
+  if (h == 0 && tid == BLOCK - 1) publish_progress(p, l);
+  const int T = ui.T;
+  DenseSlot* slot = p.dense_slot + h;
+  if (p.finished[u] || !r.live) {
+    if (tid == 0) {
+      p.grp[h] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
+      slot->live = 0; slot->s = 0x7fffffff; slot->e = -1;
+    }
+    return;
+  }
+  int s = l > 1 ? l : 1, e = T;
+  if (p.win_m1 >= 0) s = max(s, r.tau - p.win_m1);
+  if (p.win_m2 >= 0) e = min(e, r.tau_end + p.win_m2);
+  s = checked(p, s, 1, T + 1, ERR_WINDOW);
+  e = checked(p, e, -1, T, ERR_WINDOW);
+  const float* gn = p.gn[cur] + h * Tp;
+  const float* gb = p.gb[cur] + h * Tp;
+  const double* Bu = p.Bcum + (size_t)u * Tp;
+  const double Bref = r.bref;
+  const int lo = max(s, r.rs + 1), hi = min(e, r.re + 1);      // frames that have an f term
+  const bool rep_ok = r.last >= 0 && r.last != p.blank_id && r.last != p.eos_id && r.last < p.V;
+  const float* xr = p.xT + ((size_t)u * p.V + (rep_ok ? r.last : 0)) * Tp;
+  float m = LOG0F;
+  Lse a;                                                       // the repeated label's sum
+  a.m = LOG0F; a.s = 0.0f;
+  for (int t = lo + tid; t <= hi; t += BLOCK) {
+    const float n = gn[t - 1], b = gb[t - 1], bt = (float)(Bu[t - 1] - Bref);
+    const float f = canon0(lae(n, b) + bt);
+    dense_f_lds[t] = f;
+    m = fmaxf(m, f);
+    Lse v;
+    v.m = (canon0(b + bt) + xr[t]) * L2E; v.s = 1.0f;
+    a = lse_join(a, v);
+  }
+  m = row16_max(m);
+  m = fmaxf(fmaxf(lane_f(m, 0), lane_f(m, 16)), fmaxf(lane_f(m, 32), lane_f(m, 48)));
+  float am = row16_max(a.m);
+  am = fmaxf(fmaxf(lane_f(am, 0), lane_f(am, 16)), fmaxf(lane_f(am, 32), lane_f(am, 48)));
+  float as = row16_sum(a.s * __builtin_amdgcn_exp2f(a.m - am));
+  as = (lane_f(as, 0) + lane_f(as, 16)) + (lane_f(as, 32) + lane_f(as, 48));
+  __shared__ float s_am[BLOCK / 64];
+  if ((tid & 63) == 0) { s_red[w] = m; s_am[w] = am; s_rs[w] = as; }
+  lds_barrier();
+  float M = s_red[0];
+#pragma unroll
+  for (int i = 1; i < BLOCK / 64; ++i) M = fmaxf(M, s_red[i]);
+  const bool some = M > LOG0_CLASS;                            // else: no term at all, every increment is log0
+  float* F = p.dense_F + h * Tp;
+  for (int t = tid; t < Tp; t += BLOCK) {
+    float v = 0.0f;
+    if (some && t >= lo && t <= hi) v = __builtin_amdgcn_exp2f((dense_f_lds[t] - M) * L2E);
+    F[t] = v;
+  }
+  if (tid == 0) {
+    Lse c;
+    c.m = s_am[0]; c.s = s_rs[0];
+#pragma unroll
+    for (int i = 1; i < BLOCK / 64; ++i) { Lse d; d.m = s_am[i]; d.s = s_rs[i]; c = lse_join(c, d); }
+    DenseSlot q;
+    q.live = 1; q.last = rep_ok ? r.last : -1; q.s = s; q.e = e;
+    q.mref = M; q.inc_rep = c.m < LOG0_CLASS ? LOG0F : (c.m + __builtin_amdgcn_logf(c.s)) * LN2;
+    q.rs = r.rs; q.re = r.re; q.ref = r.ref; q.pad = 0;
+    q.offr = r.off + Bref;
+    q.jbase = (1.0 - p.lambda) * r.att + p.beta * (double)l;
+    *slot = q;
+    const bool has = r.rs <= T && r.re >= T;
+    const float ce = has ? canon0(lae(gn[T], gb[T])) : LOG0F;
+    const bool v = ce > LOG0_CLASS;
+    const double ctc = v ? q.offr + (ui.BT - Bref) + (double)ce : LOG0D;
+    const int W = e >= s ? e - s + 1 : 0;
+    p.grp[h] = GroupOut{0, 0, s, e, ctc, v ? p.lambda * ctc + (1.0 - p.lambda) * (double)att[h * p.V + p.eos_id] + q.jbase : LOG0D,
+                        (long long)p.K * (long long)W, {0, 0, 0, 0, 0, 0}};
+  }
+}
+
+// Grid: (chunks of 16 * NT candidates, U), four waves that share the frames of the window: each sums a quarter of
+// them for all the work-group's candidates and slots (no operand is shared between waves, so none goes through LDS),
+// and their sums meet in LDS at the end.  MFMA 16x16x4: lane (n, q) = (lane & 15, lane >> 4) holds four consecutive
+// frames of candidate n (of slot n): its float4 serves four products whose frame index runs over the four q.
+// Bound: the posteriors, once (4 V T bytes per utterance; 16 utterances of 1500 frames, 5000 ids: 480 MB).  MFMA:
+// 32 cycles for 16 x 16 x 4, two slot tiles beyond 16 slots: half the time the bytes take.
+template <int NT, int MT>
+__global__ __launch_bounds__(256, 4) void k_dense_scores(const float* __restrict__ xT, const float* __restrict__ F,
+                                                         const DenseSlot* __restrict__ slots, const float* __restrict__ att,
+                                                         int Wb, int Tp, int V, int K, Params p, int l, int cur) {
+  constexpr int NC = 16 * NT;
+  __shared__ float s_acc[4][16 * MT][NC + 1];
+  __shared__ int s_last[MAX_BEAM], s_live[MAX_BEAM];
+  __shared__ float s_m[MAX_BEAM], s_rep[MAX_BEAM];
+  __shared__ double s_offr[MAX_BEAM], s_jb[MAX_BEAM];
+  const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6), n = lane & 15, q = lane >> 4;
+  const int u = blockIdx.y, c0 = (int)blockIdx.x * NC;
+  const size_t h0 = (size_t)u * Wb;
+  if (p.finished[u]) return;
+  const int T = p.uinfo[u].T;
+  int smin = l > 1 ? l : 1, emax = T;
+  {
+    DenseSlot d;
+    d.live = 0; d.s = 0x7fffffff; d.e = -1;
+    if (lane < Wb) d = slots[h0 + lane];
+    if (tid < Wb) { s_last[tid] = d.last; s_live[tid] = d.live; s_m[tid] = d.mref; s_rep[tid] = d.inc_rep; s_offr[tid] = d.offr; s_jb[tid] = d.jbase; }
+    if (p.win_m1 >= 0 || p.win_m2 >= 0) {                      // the slots' windows together
+      int a = d.live ? d.s : 0x7fffffff, b = d.live ? d.e : -1;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) { a = min(a, __shfl_xor(a, o)); b = max(b, __shfl_xor(b, o)); }
+      smin = uni(min(max(a, 1), T)); emax = uni(min(b, T));
+    }
+  }
+  const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
+  const float* xu = xT + (size_t)u * V * Tp;
+  const int b0 = smin >> 4, nb = emax >= smin ? (emax >> 4) - b0 + 1 : 0;      // 16-frame blocks (rows of xT are whole multiples)
+  const int bw = b0 + ((nb * w) >> 2), ew = b0 + ((nb * (w + 1)) >> 2);
+  const float* bp[NT];
+  const float* ap[MT];
+#pragma unroll
+  for (int k = 0; k < NT; ++k) bp[k] = xu + (size_t)full_v_id(min(c0 + 16 * k + n, K - 1), lo_ex, hi_ex) * Tp + 4 * q;
+#pragma unroll
+  for (int k = 0; k < MT; ++k) ap[k] = F + (h0 + min(16 * k + n, Wb - 1)) * Tp + 4 * q;
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int k = 0; k < NT; ++k) acc[i][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  float4 x[NT], f[MT];
+  auto fetch = [&](int b, float4 (&xx)[NT], float4 (&ff)[MT]) {
+#pragma unroll
+    for (int k = 0; k < NT; ++k) xx[k] = *(const float4*)(bp[k] + 16 * b);
+#pragma unroll
+    for (int k = 0; k < MT; ++k) ff[k] = *(const float4*)(ap[k] + 16 * b);
+  };
+  if (bw < ew) fetch(bw, x, f);
+  for (int b = bw; b < ew; ++b) {
+    float4 xn[NT], fn[MT];
+    fetch(min(b + 1, ew - 1), xn, fn);                         // the next block's loads fly during this block's products
+    float ex[NT][4], fa[MT][4];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      ex[k][0] = __builtin_amdgcn_exp2f(x[k].x * L2E); ex[k][1] = __builtin_amdgcn_exp2f(x[k].y * L2E);
+      ex[k][2] = __builtin_amdgcn_exp2f(x[k].z * L2E); ex[k][3] = __builtin_amdgcn_exp2f(x[k].w * L2E);
+    }
+#pragma unroll
+    for (int k = 0; k < MT; ++k) { fa[k][0] = f[k].x; fa[k][1] = f[k].y; fa[k][2] = f[k].z; fa[k][3] = f[k].w; }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int k = 0; k < NT; ++k)
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[i][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][c], ex[k][c], acc[i][k], 0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < NT; ++k) x[k] = xn[k];
+#pragma unroll
+    for (int k = 0; k < MT; ++k) f[k] = fn[k];
+  }
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int k = 0; k < NT; ++k)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s_acc[w][16 * i + 4 * q + r][16 * k + n] = acc[i][k][r];
+  lds_barrier();
+  // ---- scores: lane = candidate, the slots dealt to 256 / NC groups of lanes ----
+  const double lam = p.lambda;
+  const int cc = tid & (NC - 1), c = c0 + cc;
+  const int id = full_v_id(min(c, K - 1), lo_ex, hi_ex);
+  for (int j0 = 0; j0 < Wb; j0 += 256 / NC) {
+    const int j = j0 + tid / NC, js = min(j, Wb - 1);
+    const bool mine = j < Wb && c < K && s_live[js];
+    const float av = mine ? att[(h0 + j) * V + id] : 0.0f;
+    const float sum = (s_acc[0][js][cc] + s_acc[1][js][cc]) + (s_acc[2][js][cc] + s_acc[3][js][cc]);
+    float inc = s_m[js] + __builtin_amdgcn_logf(sum) * LN2;
+    const bool rep = id == s_last[js];
+    if (rep) inc = s_rep[js];
+    const bool redo = mine && !rep && !(sum > 1.0e-30f);
+    unsigned long long todo = __ballot(redo);
+    while (todo != 0ull) {                                     // (uniform) every product far below M, or none finite
+      const int who = __ffsll((long long)todo) - 1;
+      todo &= todo - 1ull;
+      const int jr = __builtin_amdgcn_readlane(js, who), idr = __builtin_amdgcn_readlane(id, who);
+      const size_t h = h0 + jr;
+      const DenseSlot d = slots[h];
+      const float* gn = p.gn[cur] + h * Tp;
+      const float* gb = p.gb[cur] + h * Tp;
+      const double* Bu = p.Bcum + (size_t)u * Tp;
+      const double Bref = Bu[checked(p, d.ref, 0, T, ERR_TIME_INDEX)];
+      const float* col = xu + (size_t)idr * Tp;
+      Lse a;
+      a.m = LOG0F; a.s = 0.0f;
+      for (int t = max(d.s, d.rs + 1) + lane; t <= min(d.e, d.re + 1); t += 64) {
+        Lse v;
+        v.m = (dense_f(gn, gb, Bu, Bref, t) + col[t]) * L2E; v.s = 1.0f;
+        a = lse_join(a, v);
+      }
+      const float r = lse_finish<64>(a);
+      if (lane == who) inc = r;
+    }
+    if (mine) {
+      const size_t o = (h0 + j) * (size_t)K + c;
+      const bool valid = inc > LOG0_CLASS;
+      const double ctc = valid ? s_offr[js] + (double)inc : LOG0D;
+      const double J = valid ? lam * ctc + (1.0 - lam) * (double)av + s_jb[js] : LOG0D;
+      p.cand_inc[o] = valid ? inc : LOG0F; p.cand_joint[o] = J;
+      if (p.keep_cand) { p.cand_id[o] = id; p.cand_att[o] = av; p.cand_ctc[o] = ctc; }
+    }
+  }
+}

@@ -929,7 +929,8 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 && CB * IT
   TRACE_MARK(5);
   TRACE_FLUSH(p, grp);
 }
-// Group list for large candidate sets (K > block size): Wb rounds of a block-wide argmax
+
+// The list for more than 8192 candidates with arrays of their own (see k_list_top for the usual form): Wb rounds of a block-wide argmax
 // over the joint scores in global memory.  One work-group per (utterance, beam slot).
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_group_top(Params p, int cur) {
@@ -977,34 +978,94 @@ __global__ __launch_bounds__(BLOCK) void k_group_top(Params p, int cur) {
   if (tid == 0) p.grp[grp].n = n;
 }
 
-// The same list for candidate sets of up to BLOCK * EPT ids, from registers: every thread loads
-// its share of the joint scores once, as 64-bit keys (order-preserving image of the score whose
-// 13 lowest mantissa bits carry 8191 - candidate index: larger score first, then the smaller
-// index = the smaller token id; scores equal to within 2^-39 relative count as equal); each of
-// the Wb rounds is then a block-wide maximum of keys and the owner retires the winner.
-template <int BLOCK, int EPT>
-__global__ __launch_bounds__(BLOCK) void k_group_top_regs(Params p, int cur) {
-  constexpr int NW = BLOCK / 64;
+// Group list for candidate sets whose joint scores lie in global memory (K > block size, or every id a candidate): one
+// work-group per (utterance, beam slot).  Every lane holds its share of the scores as 64-bit keys (order-preserving
+// image of the score whose 13 lowest mantissa bits carry 8191 - candidate index: larger score first, then the smaller
+// index = the smaller token id; scores equal to within 2^-39 relative count as equal).  The upper halves give a pivot that
+// at least Wb of the keys reach (as for the candidates, see wave_pivot), the few that do are packed into LDS and ranked.
+// More than CAP of them (scores equal in the upper half, that is to 2^-20 relative): Wb rounds of a block-wide maximum.
+// (68 us at 4998 candidates, beam 20, with the rounds alone: a round costs 2 us.)
+// DENSE: ids follow from the candidate's index and attention values are fetched from the row.
+template <int EPT, bool DENSE>
+__global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restrict__ att, int cur) {
+  constexpr int BLOCK = 256, NW = BLOCK / 64, CAP = 512;
   __shared__ unsigned long long s_k[2][NW];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int grp = blockIdx.x, u = grp / p.Wb, K = p.K;
+  __shared__ __align__(16) unsigned long long s_ent[CAP + 4];
+  __shared__ uint32_t s_thr[NW];
+  __shared__ int s_n;
+  const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6);
+  const int grp = (int)(blockIdx.y * gridDim.x + blockIdx.x), u = blockIdx.y, K = p.K, Wb = p.Wb;
   if (p.finished[u] || !p.rec[cur][grp].live) return;      // the score kernel already wrote a count of 0
   if (p.grp[grp].stopped) { if (tid == 0) p.grp[grp].n = 0; return; }
   const double* J = p.cand_joint + (size_t)grp * K;
   unsigned long long key[EPT];
+  uint32_t kmax = 0u;
 #pragma unroll
   for (int k = 0; k < EPT; ++k) {
     const int c = tid + k * BLOCK;
-    const double v = c < K ? J[c] : LOG0D;
+    const double v = J[min(c, K - 1)];
     unsigned long long kk = 0ull;                           // not a competitor
-    if (v > (double)LOG0_CLASS) {                           // (false for NaN)
+    if (c < K && v > (double)LOG0_CLASS) {                  // (false for NaN)
       const unsigned long long b = (unsigned long long)__double_as_longlong(v);
       kk = (((b >> 63) ? ~b : (b | 0x8000000000000000ull)) & ~0x1FFFull) | (unsigned long long)(0x1FFF - c);
     }
     key[k] = kk;
+    kmax = max(kmax, (uint32_t)(kk >> 32));
   }
-  int n = 0;
-  for (int r = 0; r < p.Wb; ++r) {
+  auto emit = [&](unsigned long long k, int r) {
+    const int c = 0x1FFF - (int)(k & 0x1FFFull);
+    const size_t g = (size_t)grp * K + c;
+    int id;
+    float av;
+    if (DENSE) {
+      id = full_v_id(c, min(p.blank_id, p.eos_id), max(p.blank_id, p.eos_id));
+      av = att[(size_t)grp * p.V + id];
+    } else { id = checked(p, p.cand_id[g], 0, p.V - 1, ERR_CAND_ID); av = p.cand_att[g]; }
+    p.grp_list[(size_t)grp * Wb + r] = ListEntry{J[c], id, p.cand_inc[g], av, 0};
+  };
+  // pivot on the upper halves: every wave's share of Wb
+  const int have = min(max(K - 64 * w, 0), 64), all = K < BLOCK ? K : BLOCK;
+  const int r = (Wb * have + all - 1) / all;
+  uint32_t thr = 0u;
+#pragma unroll
+  for (int bit = 31; bit >= 10; --bit) {
+    const uint32_t t = thr | (1u << bit);
+    if (__popcll(__ballot(kmax >= t)) >= r) thr = t;
+  }
+  if (lane == 0) s_thr[w] = r > 0 ? thr : 0xffffffffu;
+  if (tid == 0) s_n = 0;
+  lds_barrier();
+  const uint32_t L = max(min(min(s_thr[0], s_thr[1]), min(s_thr[2], s_thr[3])), 1u);
+#pragma unroll
+  for (int k = 0; k < EPT; ++k)
+    if ((uint32_t)(key[k] >> 32) >= L) {
+      const int pos = atomicAdd(&s_n, 1);
+      if (pos < CAP) s_ent[pos] = key[k];
+    }
+  lds_barrier();
+  const int n = uni(s_n);
+  if (n <= CAP) {
+    if (tid < 4) s_ent[n + tid] = 0ull;
+    lds_barrier();
+    const ulonglong2* e2 = (const ulonglong2*)s_ent;
+    const int q = (n + 3) >> 2;
+    for (int e0 = 0; e0 < n; e0 += BLOCK / 4) {
+      const int e = e0 + (tid >> 2);
+      const unsigned long long me = e < n ? s_ent[e] : ~0ull;
+      int rank = 0;
+      for (int i = tid & 3; i < q; i += 4) {
+        const ulonglong2 a = e2[2 * i], b = e2[2 * i + 1];
+        rank += ((int)(a.x > me) + (int)(a.y > me)) + ((int)(b.x > me) + (int)(b.y > me));
+      }
+      rank += dpp_i<0xB1, 0xf>(0, rank);                   // quad_perm [1,0,3,2]
+      rank += dpp_i<0x4E, 0xf>(0, rank);                   // quad_perm [2,3,0,1]
+      if ((tid & 3) == 0 && e < n && rank < Wb) emit(me, rank);
+    }
+    if (tid == 0) p.grp[grp].n = min(n, Wb);
+    return;
+  }
+  int found = 0;
+  for (int rd = 0; rd < Wb; ++rd) {
     unsigned long long best = key[0];
 #pragma unroll
     for (int k = 1; k < EPT; ++k) best = key[k] > best ? key[k] : best;
@@ -1013,21 +1074,17 @@ __global__ __launch_bounds__(BLOCK) void k_group_top_regs(Params p, int cur) {
       const unsigned long long ob = __shfl_xor(best, o);
       best = ob > best ? ob : best;
     }
-    if (lane == 0) s_k[r & 1][w] = best;
+    if (lane == 0) s_k[rd & 1][w] = best;
     lds_barrier();                                          // (two buffers: one barrier per round is enough)
-    best = s_k[r & 1][0];
+    best = s_k[rd & 1][0];
 #pragma unroll
-    for (int i = 1; i < NW; ++i) best = s_k[r & 1][i] > best ? s_k[r & 1][i] : best;
+    for (int i = 1; i < NW; ++i) best = s_k[rd & 1][i] > best ? s_k[rd & 1][i] : best;
     if (best == 0ull) break;                                // uniform: no finite candidate left
-    const int c = 0x1FFF - (int)(best & 0x1FFFull);
 #pragma unroll
     for (int k = 0; k < EPT; ++k)
       if (key[k] == best) key[k] = 0ull;                    // only its owner holds this key
-    if (tid == 0) {
-      const size_t o = (size_t)grp * p.Wb + r, g = (size_t)grp * K + c;
-      p.grp_list[o] = ListEntry{J[c], p.cand_id[g], p.cand_inc[g], p.cand_att[g], 0};
-    }
-    ++n;
+    if (tid == 0) emit(best, rd);
+    ++found;
   }
-  if (tid == 0) p.grp[grp].n = n;
+  if (tid == 0) p.grp[grp].n = found;
 }

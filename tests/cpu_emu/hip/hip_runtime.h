@@ -278,6 +278,16 @@ inline unsigned __builtin_amdgcn_mbcnt_hi(unsigned m, unsigned add) {
   const unsigned below = l <= 32 ? 0u : ((1u << (l - 32)) - 1u);
   return (unsigned)__builtin_popcount(m & below) + add;
 }
+// 16x16x4 fp32 matrix product: lane l holds A[l & 15][l >> 4], B[l >> 4][l & 15] and rows 4 (l >> 4) .. + 3 of column l & 15
+typedef float emu_f32x4 __attribute__((__vector_size__(16)));
+inline emu_f32x4 __builtin_amdgcn_mfma_f32_16x16x4f32(float a, float b, emu_f32x4 c, int, int, int) {
+  const int l = emu::self().lane;
+  for (int k = 0; k < 4; ++k) {
+    const float bk = emu::from_lane(b, (l & 15) + 16 * k);
+    for (int r = 0; r < 4; ++r) c[r] += emu::from_lane(a, 4 * (l >> 4) + r + 16 * k) * bk;
+  }
+  return c;
+}
 // DPP controls of GFX9 (all lanes active, bank mask 0xf): quad_perm, row_shl/shr/ror, wave_shr:1,
 // row_mirror, row_bcast15, row_bcast31; a lane without a source, or in a row that the row mask
 // leaves out, keeps `old`
@@ -324,6 +334,7 @@ inline double min(double a, double b) { return fmin(a, b); }
 inline double max(double a, double b) { return fmax(a, b); }
 inline int __popc(unsigned v) { return __builtin_popcount(v); }
 inline int __popcll(unsigned long long v) { return __builtin_popcountll(v); }
+inline int __ffsll(long long v) { return __builtin_ffsll(v); }
 inline int __ffs(int v) { return __builtin_ffs(v); }
 inline int __float_as_int(float f) { int i; memcpy(&i, &f, 4); return i; }
 inline unsigned __float_as_uint(float f) { unsigned i; memcpy(&i, &f, 4); return i; }
