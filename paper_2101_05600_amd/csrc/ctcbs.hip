@@ -192,8 +192,8 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   p.keep_cand = (c.keep_candidates || K > 256) ? 1 : 0;
   // every id a candidate (not: few ids, the eos-run rule, raw decoder scores, the batch-wide window): the kernels of
   // k_dense.h; up to 64 ids k_score ranks the list itself and a step is two launches instead of four
-  h->dense = !restricted && K > 64 && !(c.end_flags & CTCBS_END_EOS_RUN) && !c.att_is_logits && !c.win_union;
-  if (h->dense && K <= 8192) p.keep_cand = c.keep_candidates ? 1 : 0;   // (the list builder for more ids reads those arrays)
+  h->dense = !restricted && K > 64 && K <= 16384 && !(c.end_flags & CTCBS_END_EOS_RUN) && !c.att_is_logits && !c.win_union;
+  if (h->dense) p.keep_cand = c.keep_candidates ? 1 : 0;
 
   // capacity for any batch of lengths <= t_max (the step cap grows with the length)
   h->l_cap_alloc = step_cap(&c, c.t_max);
@@ -379,11 +379,11 @@ static hipError_t launch_score(ctcbs* h, const Params& p, const float* att, int 
 // Every id a candidate.  64 candidates per work-group where that gives every compute unit a few work-groups (each reads
 // the slots' F once: a third of what it reads of the posteriors), 16 otherwise.
 template <int NT>
-static hipError_t launch_dense_scores(ctcbs* h, const Params& p, const float* att, int l) {
+static hipError_t launch_dense_scores(ctcbs* h, const Params& p, int l) {
   const dim3 grid((unsigned)(p.K + 16 * NT - 1) / (16 * NT), (unsigned)p.U);
 #define CTCBS_DENSE(MT)                                                                                            \
   hipLaunchKernelGGL((k_dense_scores<NT, MT>), grid, dim3(256), 0, h->stream, (const float*)p.xT, (const float*)p.dense_F, \
-                     (const DenseSlot*)p.dense_slot, att, (int)p.Wb, (int)p.Tp, (int)p.V, (int)p.K, p, l, h->cur)
+                     (const DenseSlot*)p.dense_slot, (int)p.Wb, (int)p.Tp, (int)p.V, (int)p.K, p, l, h->cur)
   if (p.Wb <= 16) CTCBS_DENSE(1); else CTCBS_DENSE(2);
 #undef CTCBS_DENSE
   return hipGetLastError();
@@ -392,15 +392,16 @@ static hipError_t launch_dense(ctcbs* h, const Params& p, const float* att, int 
   hipLaunchKernelGGL((k_dense_prep<256>), dim3(p.Wb, p.U), dim3(256), (size_t)p.Tp * 4, h->stream, p, att, l, h->cur);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if ((long long)p.U * ((p.K + 63) / 64) >= 512) return launch_dense_scores<4>(h, p, att, l);
-  return launch_dense_scores<1>(h, p, att, l);
+  if ((long long)p.U * ((p.K + 63) / 64) >= 512) return launch_dense_scores<4>(h, p, l);
+  return launch_dense_scores<1>(h, p, l);
 }
 
 // the groups' lists from joint scores in global memory
 static hipError_t launch_lists(ctcbs* h, const Params& p, const float* att) {
   const dim3 grid(p.Wb, p.U);
 #define CTCBS_LIST(E, D) hipLaunchKernelGGL((k_list_top<E, D>), grid, dim3(256), 0, h->stream, p, att, h->cur)
-  if (p.K > 8192) hipLaunchKernelGGL((k_group_top<256>), dim3(p.U * p.Wb), dim3(256), 0, h->stream, p, h->cur);
+  if (p.K > 8192 && h->dense) CTCBS_LIST(64, true);
+  else if (p.K > 8192) hipLaunchKernelGGL((k_group_top<256>), dim3(p.U * p.Wb), dim3(256), 0, h->stream, p, h->cur);
   else if (h->dense) { if (p.K <= 1024) CTCBS_LIST(4, true); else if (p.K <= 5120) CTCBS_LIST(20, true); else CTCBS_LIST(32, true); }
   else { if (p.K <= 1024) CTCBS_LIST(4, false); else if (p.K <= 5120) CTCBS_LIST(20, false); else CTCBS_LIST(32, false); }
 #undef CTCBS_LIST

@@ -5,8 +5,8 @@
 //   k_dense_prep   per (utterance, slot): window, F_t = exp(f_t - M) over it (M the largest f term; 0 outside), eos
 //                  scores, and the one candidate the product does not fit: the repeat of the slot's last label (blank
 //                  variable only, third alignment rule of Sec. 2.1);
-//   k_dense_scores per (utterance, chunk of candidates): the product, then joint scores (Eq. (1));
-//   k_list_top     per (utterance, slot): the group's best-first list.
+//   k_dense_scores per (utterance, chunk of candidates): the product, i.e. the prefix-score increments;
+//   k_list_top     per (utterance, slot): joint scores (Eq. (1)) and the group's best-first list.
 // Range: a product below 2^-126 (87 nats under M) counts as nothing; a sum of such products -- below 1e-30 -- is redone
 // frame by frame in the log domain.
 // Not handled here (the host then launches k_score): top-K candidates, up to 64 ids, the eos-run rule, raw
@@ -14,14 +14,6 @@
 #pragma once
 #include "common.h"
 #include "k_score.h"
-
-struct __align__(64) DenseSlot {
-  int32_t live, last, s, e;  // window
-  float mref, inc_rep;       // M; increment of the candidate that repeats the last label
-  int32_t rs, re, ref;
-  int32_t pad;
-  double offr, jbase;        // off' + B_r; joint score without this step's terms
-};
 
 typedef float f32x4 __attribute__((__vector_size__(16)));
 
@@ -115,21 +107,20 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
   }
 }
 
-// Grid: (chunks of 16 * NT candidates, U), four waves that share the frames of the window: each sums a quarter of
-// them for all the work-group's candidates and slots (no operand is shared between waves, so none goes through LDS),
+// Grid: (chunks of 16 * NT candidates, U), four waves that share the frames of the window: each takes every fourth
+// block of 16 frames (together they walk along the columns) for all the work-group's candidates and slots (no operand is shared between waves, so none goes through LDS),
 // and their sums meet in LDS at the end.  MFMA 16x16x4: lane (n, q) = (lane & 15, lane >> 4) holds four consecutive
 // frames of candidate n (of slot n): its float4 serves four products whose frame index runs over the four q.
 // Bound: the posteriors, once (4 V T bytes per utterance; 16 utterances of 1500 frames, 5000 ids: 480 MB).  MFMA:
 // 32 cycles for 16 x 16 x 4, two slot tiles beyond 16 slots: half the time the bytes take.
 template <int NT, int MT>
-__global__ __launch_bounds__(256, 4) void k_dense_scores(const float* __restrict__ xT, const float* __restrict__ F,
-                                                         const DenseSlot* __restrict__ slots, const float* __restrict__ att,
+__global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict__ xT, const float* __restrict__ F,
+                                                         const DenseSlot* __restrict__ slots,
                                                          int Wb, int Tp, int V, int K, Params p, int l, int cur) {
   constexpr int NC = 16 * NT;
   __shared__ float s_acc[4][16 * MT][NC + 1];
   __shared__ int s_last[MAX_BEAM], s_live[MAX_BEAM];
   __shared__ float s_m[MAX_BEAM], s_rep[MAX_BEAM];
-  __shared__ double s_offr[MAX_BEAM], s_jb[MAX_BEAM];
   const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6), n = lane & 15, q = lane >> 4;
   const int u = blockIdx.y, c0 = (int)blockIdx.x * NC;
   const size_t h0 = (size_t)u * Wb;
@@ -140,7 +131,7 @@ __global__ __launch_bounds__(256, 4) void k_dense_scores(const float* __restrict
     DenseSlot d;
     d.live = 0; d.s = 0x7fffffff; d.e = -1;
     if (lane < Wb) d = slots[h0 + lane];
-    if (tid < Wb) { s_last[tid] = d.last; s_live[tid] = d.live; s_m[tid] = d.mref; s_rep[tid] = d.inc_rep; s_offr[tid] = d.offr; s_jb[tid] = d.jbase; }
+    if (tid < Wb) { s_last[tid] = d.last; s_live[tid] = d.live; s_m[tid] = d.mref; s_rep[tid] = d.inc_rep; }
     if (p.win_m1 >= 0 || p.win_m2 >= 0) {                      // the slots' windows together
       int a = d.live ? d.s : 0x7fffffff, b = d.live ? d.e : -1;
 #pragma unroll
@@ -150,8 +141,8 @@ __global__ __launch_bounds__(256, 4) void k_dense_scores(const float* __restrict
   }
   const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
   const float* xu = xT + (size_t)u * V * Tp;
-  const int b0 = smin >> 4, nb = emax >= smin ? (emax >> 4) - b0 + 1 : 0;      // 16-frame blocks (rows of xT are whole multiples)
-  const int bw = b0 + ((nb * w) >> 2), ew = b0 + ((nb * (w + 1)) >> 2);
+  const int b0 = smin >> 5, nb = emax >= smin ? (emax >> 5) - b0 + 1 : 0;      // blocks of 32 frames: whole lines of xT
+  const int bw = b0 + w, ew = b0 + nb;
   const float* bp[NT];
   const float* ap[MT];
 #pragma unroll
@@ -163,35 +154,41 @@ __global__ __launch_bounds__(256, 4) void k_dense_scores(const float* __restrict
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int k = 0; k < NT; ++k) acc[i][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  float4 x[NT], f[MT];
-  auto fetch = [&](int b, float4 (&xx)[NT], float4 (&ff)[MT]) {
+  float4 x[2][NT], f[2][MT];
+  auto fetch = [&](int b, float4 (&xx)[2][NT], float4 (&ff)[2][MT]) {
 #pragma unroll
-    for (int k = 0; k < NT; ++k) xx[k] = *(const float4*)(bp[k] + 16 * b);
+    for (int k = 0; k < NT; ++k) { xx[0][k] = *(const float4*)(bp[k] + 32 * b); xx[1][k] = *(const float4*)(bp[k] + 32 * b + 16); }
 #pragma unroll
-    for (int k = 0; k < MT; ++k) ff[k] = *(const float4*)(ap[k] + 16 * b);
+    for (int k = 0; k < MT; ++k) { ff[0][k] = *(const float4*)(ap[k] + 32 * b); ff[1][k] = *(const float4*)(ap[k] + 32 * b + 16); }
   };
   if (bw < ew) fetch(bw, x, f);
-  for (int b = bw; b < ew; ++b) {
-    float4 xn[NT], fn[MT];
-    fetch(min(b + 1, ew - 1), xn, fn);                         // the next block's loads fly during this block's products
-    float ex[NT][4], fa[MT][4];
+  for (int b = bw; b < ew; b += 4) {
+    float4 xn[2][NT], fn[2][MT];
+    fetch(min(b + 4, ew - 1), xn, fn);                         // the next block's loads fly during this block's products
 #pragma unroll
-    for (int k = 0; k < NT; ++k) {
-      ex[k][0] = __builtin_amdgcn_exp2f(x[k].x * L2E); ex[k][1] = __builtin_amdgcn_exp2f(x[k].y * L2E);
-      ex[k][2] = __builtin_amdgcn_exp2f(x[k].z * L2E); ex[k][3] = __builtin_amdgcn_exp2f(x[k].w * L2E);
+    for (int hf = 0; hf < 2; ++hf) {
+      float ex[NT][4], fa[MT][4];
+#pragma unroll
+      for (int k = 0; k < NT; ++k) {
+        ex[k][0] = __builtin_amdgcn_exp2f(x[hf][k].x * L2E); ex[k][1] = __builtin_amdgcn_exp2f(x[hf][k].y * L2E);
+        ex[k][2] = __builtin_amdgcn_exp2f(x[hf][k].z * L2E); ex[k][3] = __builtin_amdgcn_exp2f(x[hf][k].w * L2E);
+      }
+#pragma unroll
+      for (int k = 0; k < MT; ++k) { fa[k][0] = f[hf][k].x; fa[k][1] = f[hf][k].y; fa[k][2] = f[hf][k].z; fa[k][3] = f[hf][k].w; }
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int k = 0; k < NT; ++k)
+#pragma unroll
+          for (int i = 0; i < MT; ++i) acc[i][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][c], ex[k][c], acc[i][k], 0, 0, 0);
     }
 #pragma unroll
-    for (int k = 0; k < MT; ++k) { fa[k][0] = f[k].x; fa[k][1] = f[k].y; fa[k][2] = f[k].z; fa[k][3] = f[k].w; }
+    for (int g = 0; g < 2; ++g) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+      for (int k = 0; k < NT; ++k) x[g][k] = xn[g][k];
 #pragma unroll
-      for (int k = 0; k < NT; ++k)
-#pragma unroll
-        for (int i = 0; i < MT; ++i) acc[i][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][c], ex[k][c], acc[i][k], 0, 0, 0);
-#pragma unroll
-    for (int k = 0; k < NT; ++k) x[k] = xn[k];
-#pragma unroll
-    for (int k = 0; k < MT; ++k) f[k] = fn[k];
+      for (int k = 0; k < MT; ++k) f[g][k] = fn[g][k];
+    }
   }
 #pragma unroll
   for (int i = 0; i < MT; ++i)
@@ -200,14 +197,12 @@ __global__ __launch_bounds__(256, 4) void k_dense_scores(const float* __restrict
 #pragma unroll
       for (int r = 0; r < 4; ++r) s_acc[w][16 * i + 4 * q + r][16 * k + n] = acc[i][k][r];
   lds_barrier();
-  // ---- scores: lane = candidate, the slots dealt to 256 / NC groups of lanes ----
-  const double lam = p.lambda;
+  // ---- increments: lane = candidate, the slots dealt to 256 / NC groups of lanes ----
   const int cc = tid & (NC - 1), c = c0 + cc;
   const int id = full_v_id(min(c, K - 1), lo_ex, hi_ex);
   for (int j0 = 0; j0 < Wb; j0 += 256 / NC) {
     const int j = j0 + tid / NC, js = min(j, Wb - 1);
     const bool mine = j < Wb && c < K && s_live[js];
-    const float av = mine ? att[(h0 + j) * V + id] : 0.0f;
     const float sum = (s_acc[0][js][cc] + s_acc[1][js][cc]) + (s_acc[2][js][cc] + s_acc[3][js][cc]);
     float inc = s_m[js] + __builtin_amdgcn_logf(sum) * LN2;
     const bool rep = id == s_last[js];
@@ -235,13 +230,6 @@ __global__ __launch_bounds__(256, 4) void k_dense_scores(const float* __restrict
       const float r = lse_finish<64>(a);
       if (lane == who) inc = r;
     }
-    if (mine) {
-      const size_t o = (h0 + j) * (size_t)K + c;
-      const bool valid = inc > LOG0_CLASS;
-      const double ctc = valid ? s_offr[js] + (double)inc : LOG0D;
-      const double J = valid ? lam * ctc + (1.0 - lam) * (double)av + s_jb[js] : LOG0D;
-      p.cand_inc[o] = valid ? inc : LOG0F; p.cand_joint[o] = J;
-      if (p.keep_cand) { p.cand_id[o] = id; p.cand_att[o] = av; p.cand_ctc[o] = ctc; }
-    }
+    if (mine) p.cand_inc[(h0 + j) * (size_t)K + c] = canon0(inc);
   }
 }

@@ -21,6 +21,15 @@
 #pragma once
 #include "common.h"
 
+// (every id a candidate, see k_dense.h) one beam slot
+struct __align__(64) DenseSlot {
+  int32_t live, last, s, e;  // window
+  float mref, inc_rep;       // largest f term M; increment of the candidate that repeats the last label
+  int32_t rs, re, ref;
+  int32_t pad;
+  double offr, jbase;        // off' + B_r; joint score without this step's terms
+};
+
 #define PIVOT_CAP 512     // entries of the short list (all waves together)
 #define RADIX_BITS 10
 
@@ -980,15 +989,17 @@ __global__ __launch_bounds__(BLOCK) void k_group_top(Params p, int cur) {
 
 // Group list for candidate sets whose joint scores lie in global memory (K > block size, or every id a candidate): one
 // work-group per (utterance, beam slot).  Every lane holds its share of the scores as 64-bit keys (order-preserving
-// image of the score whose 13 lowest mantissa bits carry 8191 - candidate index: larger score first, then the smaller
-// index = the smaller token id; scores equal to within 2^-39 relative count as equal).  The upper halves give a pivot that
+// image of the score whose 13 lowest mantissa bits (14 beyond 8192 candidates) carry the candidate index, inverted: larger score first, then the smaller
+// index = the smaller token id; scores equal to within 2^-38 relative count as equal).  The upper halves give a pivot that
 // at least Wb of the keys reach (as for the candidates, see wave_pivot), the few that do are packed into LDS and ranked.
 // More than CAP of them (scores equal in the upper half, that is to 2^-20 relative): Wb rounds of a block-wide maximum.
 // (68 us at 4998 candidates, beam 20, with the rounds alone: a round costs 2 us.)
-// DENSE: ids follow from the candidate's index and attention values are fetched from the row.
+// DENSE: every id is a candidate (its id follows from its place) and only the increments lie in memory: the joint score
+// is formed here, next to the row of attention values.
 template <int EPT, bool DENSE>
 __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restrict__ att, int cur) {
   constexpr int BLOCK = 256, NW = BLOCK / 64, CAP = 512;
+  constexpr unsigned long long IMASK = EPT > 32 ? 0x3FFFull : 0x1FFFull;
   __shared__ unsigned long long s_k[2][NW];
   __shared__ __align__(16) unsigned long long s_ent[CAP + 4];
   __shared__ uint32_t s_thr[NW];
@@ -997,31 +1008,55 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
   const int grp = (int)(blockIdx.y * gridDim.x + blockIdx.x), u = blockIdx.y, K = p.K, Wb = p.Wb;
   if (p.finished[u] || !p.rec[cur][grp].live) return;      // the score kernel already wrote a count of 0
   if (p.grp[grp].stopped) { if (tid == 0) p.grp[grp].n = 0; return; }
-  const double* J = p.cand_joint + (size_t)grp * K;
+  const double* J = p.cand_joint + (size_t)grp * K;         // (not DENSE)
   unsigned long long key[EPT];
   uint32_t kmax = 0u;
+  const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
+  const float* arow = att + (size_t)grp * p.V;
+  const float* ginc = p.cand_inc + (size_t)grp * K;
+  double offr = 0.0, jbase = 0.0;
+  if (DENSE) { offr = p.dense_slot[grp].offr; jbase = p.dense_slot[grp].jbase; }
+  auto joint = [&](float inc, float a) {
+    return inc > LOG0_CLASS ? p.lambda * (offr + (double)inc) + (1.0 - p.lambda) * (double)a + jbase : LOG0D;
+  };
+  constexpr int CH = EPT <= 20 ? EPT : 16;                  // loads in flight
 #pragma unroll
-  for (int k = 0; k < EPT; ++k) {
-    const int c = tid + k * BLOCK;
-    const double v = J[min(c, K - 1)];
-    unsigned long long kk = 0ull;                           // not a competitor
-    if (c < K && v > (double)LOG0_CLASS) {                  // (false for NaN)
-      const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-      kk = (((b >> 63) ? ~b : (b | 0x8000000000000000ull)) & ~0x1FFFull) | (unsigned long long)(0x1FFF - c);
+  for (int k0 = 0; k0 < EPT; k0 += CH) {
+    float iv[CH], av[CH];
+    double jv[CH];
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+      const int c = min(tid + (k0 + k) * BLOCK, K - 1);
+      if (DENSE) { iv[k] = ginc[c]; av[k] = arow[full_v_id(c, lo_ex, hi_ex)]; }
+      else jv[k] = J[c];
     }
-    key[k] = kk;
-    kmax = max(kmax, (uint32_t)(kk >> 32));
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+      const int c = tid + (k0 + k) * BLOCK;
+      const double v = DENSE ? joint(iv[k], av[k]) : jv[k];
+      if (DENSE && p.keep_cand && c < K) {
+        const size_t g = (size_t)grp * K + c;
+        p.cand_id[g] = full_v_id(c, lo_ex, hi_ex); p.cand_att[g] = av[k]; p.cand_joint[g] = v;
+        p.cand_ctc[g] = iv[k] > LOG0_CLASS ? offr + (double)iv[k] : LOG0D;
+      }
+      unsigned long long kk = 0ull;                         // not a competitor
+      if (c < K && v > (double)LOG0_CLASS) {                // (false for NaN)
+        const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+        kk = (((b >> 63) ? ~b : (b | 0x8000000000000000ull)) & ~IMASK) | (IMASK - (unsigned long long)c);
+      }
+      key[k0 + k] = kk;
+      kmax = max(kmax, (uint32_t)(kk >> 32));
+    }
   }
   auto emit = [&](unsigned long long k, int r) {
-    const int c = 0x1FFF - (int)(k & 0x1FFFull);
+    const int c = min((int)(IMASK - (k & IMASK)), K - 1);
     const size_t g = (size_t)grp * K + c;
+    const float inc = ginc[c];
     int id;
-    float av;
-    if (DENSE) {
-      id = full_v_id(c, min(p.blank_id, p.eos_id), max(p.blank_id, p.eos_id));
-      av = att[(size_t)grp * p.V + id];
-    } else { id = checked(p, p.cand_id[g], 0, p.V - 1, ERR_CAND_ID); av = p.cand_att[g]; }
-    p.grp_list[(size_t)grp * Wb + r] = ListEntry{J[c], id, p.cand_inc[g], av, 0};
+    float a;
+    if (DENSE) { id = full_v_id(c, lo_ex, hi_ex); a = arow[id]; }
+    else { id = checked(p, p.cand_id[g], 0, p.V - 1, ERR_CAND_ID); a = p.cand_att[g]; }
+    p.grp_list[(size_t)grp * Wb + r] = ListEntry{DENSE ? joint(inc, a) : J[c], id, inc, a, 0};
   };
   // pivot on the upper halves: every wave's share of Wb
   const int have = min(max(K - 64 * w, 0), 64), all = K < BLOCK ? K : BLOCK;
