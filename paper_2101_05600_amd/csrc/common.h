@@ -137,7 +137,10 @@ struct Params {
   unsigned long long* groups;// [U] live (utterance, beam) groups so far
   int32_t* n_finished;       // [1]
   int32_t* err;              // [1] bits set by the kernels' own consistency checks (0: none failed)
-  int32_t* union_win;        // [2][2] per step parity: (min tau, max of min(tau~ + M2, T)) over live hypotheses
+  // batch-wide window, per step parity: (min tau, max of min(tau~ + M2, T)) over live hypotheses; [2][2] for the whole
+  // batch, or [2][U][2] per utterance (split select kernel: its work-groups do not know whether the utterance finishes)
+  int32_t* union_win;
+  int32_t union_utt;         // 1: per utterance
   unsigned long long* host_progress;   // [1] in pinned host memory, see publish_progress
   // back-pointer trie, level l holds the hypotheses of length l: [l_cap+1][U][Wb]
   int32_t* trie_parent;
@@ -158,11 +161,15 @@ struct Params {
 // Kernel arguments that a work-group needs early, kept in one block of few 64-byte lines: left to itself the compiler
 // fetches arguments one by one where they are first used, and in a kernel of a few microseconds every first touch
 // of a line is a trip to memory in a chain of them.  PIN makes a value be in scalar registers from here on, so that
-// loads written above it are issued together and waited for once.
+// loads written above it are issued together and waited for once.  LOADED does the same for vector registers: without it
+// the compiler moves a load into the branch that alone uses it, behind the arrival of the loads before, and a
+// round of loads becomes a chain of them.
 #if defined(__AMDGCN__)
 #define PIN4(a, b, c, d) __asm__ volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d))
+#define LOADED(a) __asm__ volatile("" : "+v"(a))
 #else
 #define PIN4(a, b, c, d) do { } while (0)
+#define LOADED(a) do { } while (0)
 #endif
 
 // arguments of the score kernel behind the preloaded ones
@@ -187,7 +194,7 @@ struct ScoreArgs {
   double *cand_ctc, *cand_joint;
   unsigned long long* trace;
 };
-enum { SC_RESTRICTED = 1, SC_LOGITS = 2, SC_UNION = 4, SC_KEEP = 8 };
+enum { SC_RESTRICTED = 1, SC_LOGITS = 2, SC_UNION = 4, SC_KEEP = 8, SC_UNION_UTT = 16 };
 
 // arguments of the select kernels behind the preloaded ones
 struct SelectArgs {
@@ -245,6 +252,18 @@ template <class P>
 __device__ __forceinline__ int checked(const P& p, int v, int lo, int hi, int bit) {
   if (v < lo || v > hi) { atomicOr(p.err, bit); v = v < lo ? lo : hi; }
   return v;
+}
+
+// The same for several values in a row: no branch for each (a branch costs a lone wave 40 cycles, taken or not), their
+// bits are collected and reported together.
+__device__ __forceinline__ int clamped(int v, int lo, int hi, int bit, int& bad) {
+  const int c = min(max(v, lo), hi);
+  bad |= c != v ? bit : 0;
+  return c;
+}
+template <class P>
+__device__ __forceinline__ void report(const P& p, int bad) {
+  if (bad != 0) atomicOr(p.err, bad);
 }
 
 // For the host's non-blocking look: the step that has begun and the count of utterances finished before it, in one

@@ -22,6 +22,8 @@
 
 static thread_local int g_last_hip = 0;
 
+#define CTCBS_SPLIT_GROUPS 2048   // (utterance, beam slot) groups up to which the split select kernel runs, see step_impl
+
 #define HIPCHK(expr)                                   \
   do {                                                 \
     hipError_t _e = (expr);                            \
@@ -44,7 +46,8 @@ struct ctcbs {
   int32_t known_finished;
   size_t score_smem_bytes;
   int score_block, score_lpc, select_block;
-  bool select_fpl2;            // the select kernels' form with the two-frames-per-lane recurrence only
+  int select_lps;              // select kernel: lanes per new hypothesis
+  bool select_wide;            // windows beyond 128 frames are common
   bool score_wide, score_bigk;
   int score_nv4;               // granules of an attention row per lane
   bool dense;                  // every id a candidate: the kernels of k_dense.h
@@ -188,6 +191,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   p.lambda = (double)c.ctc_weight; p.beta = (double)c.length_bonus;
   p.att_logits = c.att_is_logits ? 1 : 0;
   p.win_union = c.win_union ? 1 : 0;
+  p.union_utt = c.win_union && U * Wb <= CTCBS_SPLIT_GROUPS ? 1 : 0;
   // large candidate sets go through the per-candidate arrays in global memory whatever the caller asked for
   p.keep_cand = (c.keep_candidates || K > 256) ? 1 : 0;
   // every id a candidate (not: few ids, the eos-run rule, raw decoder scores, the batch-wide window): the kernels of
@@ -222,7 +226,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   }
   A(p.grp, UW); A(p.grp_list, UW * Wb);
   A(p.utt, (size_t)U); A(p.finished, U8);   /* read as whole words by the score kernel */ A(p.cells, (size_t)U); A(p.groups, (size_t)U);
-  A(p.n_finished, (size_t)1); A(p.union_win, (size_t)4); A(p.err, (size_t)1);
+  A(p.n_finished, (size_t)1); A(p.union_win, p.union_utt ? (size_t)4 * U : (size_t)4); A(p.err, (size_t)1);
   const size_t trie_n = (size_t)(h->l_cap_alloc + 1) * UW;
   A(p.trie_parent, trie_n * 3); p.trie_token = p.trie_parent + trie_n; p.trie_tau = p.trie_token + trie_n;
   A(p.out_parent, UW * 5); p.out_token = p.out_parent + UW; p.out_score = (float*)(p.out_token + UW);
@@ -285,16 +289,14 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   h->score_nv4 = V <= 3072 ? 3 : (V <= 5120 ? 5 : (V <= 10240 ? 10 : 16));
   h->score_smem_bytes = off;
   if (off > 160 * 1024) return CTCBS_EINVAL;
-  // per-hypothesis windows whose margins keep them within 128 frames (but for a hypothesis whose two time
-  // indices lie far apart): the select kernels then carry the two-frames-per-lane recurrence only
-  h->select_fpl2 = windowed && !c.win_union && (c.win_m1 + c.win_m2 + 1 + 3) <= 128;
-  int nw = Wb < 16 ? Wb : 16;
+  // Survivors of the select kernels: per-hypothesis windows whose margins keep them within 128 (256) frames, but for a
+  // hypothesis whose two time indices lie far apart, go 16 lanes x 8 frames (32 x 8) each, others 64 x 8.
+  const int span = c.win_m1 >= 0 && c.win_m2 >= 0 && !c.win_union ? c.win_m1 + c.win_m2 + 1 + 3 : 1 << 30;
+  h->select_lps = span <= 128 ? 16 : (span <= 256 ? 32 : 64);
+  h->select_wide = span > 128;
+  // one wave for the ended set and one round of the others for the new hypotheses, as far as a work-group goes
+  const int nw = 1 + (Wb * h->select_lps + 63) / 64;
   h->select_block = 64 * (nw <= 4 ? 4 : (nw <= 8 ? 8 : 16));
-  // One wave for the ended set plus one per new hypothesis is the shape that finishes an utterance soonest.
-  // From two utterances per compute unit on, what counts is how many utterances are resident: at beam
-  // 9..12, eight waves (survivors in two rounds) then beat sixteen (measured at beam 10: 14.9 against 18.1 us
-  // at 512 utterances, 37.9 against 55.0 at 2048; at 256 utterances 12.8 against 11.4)
-  if (h->select_block == 1024 && Wb <= 12 && U >= 512) h->select_block = 512;
 
   return ingest(h, d_ctc_logp, h_lens);
 }
@@ -350,7 +352,7 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
   a.Tp = p.Tp; a.K = p.K; a.blank_id = p.blank_id; a.eos_id = p.eos_id; a.win_m1 = p.win_m1; a.win_m2 = p.win_m2;
   a.end_flags = p.end_flags; a.eos_run = p.eos_run; a.wp_max = h->wp_max; a.off_f = h->off_f; a.off_small = h->off_small;
   a.mode = (p.restricted ? SC_RESTRICTED : 0) | (p.att_logits ? SC_LOGITS : 0) | (p.win_union ? SC_UNION : 0) |
-           (p.keep_cand ? SC_KEEP : 0);
+           (p.keep_cand ? SC_KEEP : 0) | (p.union_utt ? SC_UNION_UTT : 0);
   a.U = p.U; a.pad = 0; a.err = p.err; a.union_win = p.union_win; a.n_finished = p.n_finished; a.host_progress = p.host_progress;
   a.cand_id = p.cand_id; a.cand_inc = p.cand_inc; a.cand_att = p.cand_att; a.cand_pre = p.cand_pre; a.cand_ctc = p.cand_ctc;
   a.cand_joint = p.cand_joint; a.trace = p.trace;
@@ -466,10 +468,9 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   // Small batches leave most compute units idle in the one-work-group-per-utterance form: there the
   // split form (one work-group per new beam slot, each ranking the utterance's lists itself) is
   // faster (measured: U=64 and U=128 at beam 10).  Large batches fill the chip either way and the
-  // Wb-fold repeated ranking only costs (U=256 at beam 20: three times slower).  The batch-union
-  // window needs the utterance's hypotheses in one place.
-  const bool split = !p.win_union && p.U * p.Wb <= 2048;
-  const size_t split_lds = (size_t)28 * p.Wb * p.Wb + 64;
+  // Wb-fold repeated ranking only costs (U=256 at beam 20: three times slower).
+  const bool split = p.U * p.Wb <= CTCBS_SPLIT_GROUPS;
+  const size_t split_lds = (size_t)28 * p.Wb * p.Wb + 64 + 16 + (p.Wb > 12 ? (size_t)12 * p.Wb * p.Wb + 64 : 0);
   SelectArgs a;
   const int nxt = h->cur ^ 1;
   a.xT = p.xT; a.Bcum = p.Bcum; a.gn = p.gn[h->cur]; a.gb = p.gb[h->cur]; a.gn_new = p.gn[nxt]; a.gb_new = p.gb[nxt];
@@ -483,18 +484,25 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
                      (const ListEntry*)p.grp_list, (const UttInfo*)p.uinfo, (int)p.Wb, L, a)
   if (split) {
     const int sh = p.U >= 8 ? 3 : 0;
-    const dim3 grid(1u << sh, (unsigned)p.Wb, (unsigned)(p.U + (1 << sh) - 1) >> sh);
-    if (h->select_fpl2) CTCBS_SELECT((k_select_split<256, 2>), grid, 256, split_lds, l | sh << 28);
-    else CTCBS_SELECT((k_select_split<256, 8>), grid, 256, split_lds, l | sh << 28);
+    const dim3 grid(1u << sh, (unsigned)p.Wb + (h->select_wide ? 1 : 0), (unsigned)(p.U + (1 << sh) - 1) >> sh);
+    if (h->select_wide) CTCBS_SELECT((k_select_split<256, true>), grid, 256, split_lds, l | sh << 28);
+    else CTCBS_SELECT((k_select_split<256, false>), grid, 256, split_lds, l | sh << 28);
   } else {
     const int NE = p.Wb * p.Wb;
     const size_t sel_lds = (size_t)16 * ((NE + 9) & ~1) + (size_t)28 * NE;
     const dim3 grid(p.U);
+#define CTCBS_SELECT_LPS(BS)                                                              \
+  do {                                                                                    \
+    if (h->select_lps == 16) CTCBS_SELECT((k_select<BS, 16, 8>), grid, BS, sel_lds, l);   \
+    else if (h->select_lps == 32) CTCBS_SELECT((k_select<BS, 32, 8>), grid, BS, sel_lds, l); \
+    else CTCBS_SELECT((k_select<BS, 64, 8>), grid, BS, sel_lds, l);                       \
+  } while (0)
     switch (h->select_block) {
-      case 256: if (h->select_fpl2) CTCBS_SELECT((k_select<256, 2>), grid, 256, sel_lds, l); else CTCBS_SELECT((k_select<256, 8>), grid, 256, sel_lds, l); break;
-      case 512: if (h->select_fpl2) CTCBS_SELECT((k_select<512, 2>), grid, 512, sel_lds, l); else CTCBS_SELECT((k_select<512, 8>), grid, 512, sel_lds, l); break;
-      default: if (h->select_fpl2) CTCBS_SELECT((k_select<1024, 2>), grid, 1024, sel_lds, l); else CTCBS_SELECT((k_select<1024, 8>), grid, 1024, sel_lds, l); break;
+      case 256: CTCBS_SELECT_LPS(256); break;
+      case 512: CTCBS_SELECT_LPS(512); break;
+      default: CTCBS_SELECT_LPS(1024); break;
     }
+#undef CTCBS_SELECT_LPS
   }
 #undef CTCBS_SELECT
   HIPCHK(hipGetLastError());

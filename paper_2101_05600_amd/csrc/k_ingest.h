@@ -7,7 +7,14 @@
 __global__ __launch_bounds__(256) void k_setup(Params p, const int32_t* set, int n_empty) {
   const int u = blockIdx.x * 256 + threadIdx.x;
   if (u < p.U) { p.lens[u] = set[4 + u]; p.lmax[u] = set[4 + p.U + u]; }
-  if (u < 4) p.union_win[u] = set[u];
+  if (p.union_utt) {                                       // step 1: every hypothesis is empty, tau = tau~ = 0
+    if (u < p.U) {
+      int32_t* sh = p.union_win + 2 * ((size_t)p.U + u);   // (the first step's parity is 1)
+      const int T = set[4 + u];
+      p.union_win[2 * u] = 0x7fffffff; p.union_win[2 * u + 1] = -1;
+      sh[0] = 0; sh[1] = p.win_m2 < T ? p.win_m2 : T;
+    }
+  } else if (u < 4) p.union_win[u] = set[u];
   if (u == 0) { *p.n_finished = n_empty; *p.err = 0; }
 }
 

@@ -358,7 +358,7 @@ __device__ __forceinline__ unsigned long long joint_key(double J, int tok, bool 
 // ranking by the whole work-group, the eos-run rule's work-group-wide path (a second sum beside the first in
 // the column pass, the test across all waves).  They cost registers that the common form does without.
 template <int BLOCK, int LPC, int CB, int IT, int NV4, bool BIGK>
-__global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 && CB * IT <= 6 ? 7 : 5))) void k_score(const HypRec* __restrict__ rec_now,
+__global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT <= 6 ? 7 : 6) : 5))) void k_score(const HypRec* __restrict__ rec_now,
                                                  const UttInfo* __restrict__ uinfo, const uint32_t* __restrict__ fin_words,
                                                  const float* __restrict__ att, int Wb, int V, int flags, int l,
                                                  ScoreArgs p) {
@@ -421,9 +421,15 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 && CB * IT
   const double off = rec.off, acum = rec.att;
   if (grp == 0 && tid == BLOCK - 1) {                      // (not in wave 0, which finishes last)
     publish_progress(p, l);
-    // batch-union window: clear the slot the select kernel of this step will fill for the next one
-    p.union_win[2 * ((l + 1) & 1)] = 0x7fffffff;
-    p.union_win[2 * ((l + 1) & 1) + 1] = -1;
+    // batch-wide window: clear the slot the select kernel of this step will fill for the next one
+    if (!(p.mode & SC_UNION_UTT)) {
+      p.union_win[2 * ((l + 1) & 1)] = 0x7fffffff;
+      p.union_win[2 * ((l + 1) & 1) + 1] = -1;
+    }
+  }
+  if ((p.mode & SC_UNION_UTT) && blockIdx.y == 0 && tid == BLOCK - 1 && u < p.U) {
+    int32_t* sh_u = p.union_win + 2 * ((size_t)((l + 1) & 1) * p.U + u);
+    sh_u[0] = 0x7fffffff; sh_u[1] = -1;
   }
   if (dead) {
     // (the grid is whole eights of utterances; those past the last are dead here too)
@@ -469,14 +475,30 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 && CB * IT
   // ---------------- window (needs only g's record) ----------------------------------------
   int s = l > 1 ? l : 1, e = T;
   if (p.mode & SC_UNION) {            // s^l = min_ij s_ij, e^l = max_ij e_ij (last two equations of Sec. 3.2.3)
-    if (p.win_m1 >= 0) s = max(s, p.union_win[2 * (l & 1)] - p.win_m1);
-    if (p.win_m2 >= 0) e = min(e, p.union_win[2 * (l & 1) + 1]);
+    int lo = 0x7fffffff, hi = -1;
+    if (p.mode & SC_UNION_UTT) {                           // the unfinished utterances' shares together
+      const int32_t* shares = p.union_win + 2 * (size_t)(l & 1) * p.U;
+      for (int i = tid; i < p.U; i += BLOCK)
+        if (((fin_words[i >> 2] >> (8 * (i & 3))) & 0xffu) == 0u) { lo = min(lo, shares[2 * i]); hi = max(hi, shares[2 * i + 1]); }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) { lo = min(lo, __shfl_xor(lo, o)); hi = max(hi, __shfl_xor(hi, o)); }
+      if ((tid & 63) == 0) { s_cnt[w] = lo; s_scan[w] = (uint32_t)hi; }
+      lds_barrier();
+#pragma unroll
+      for (int i = 0; i < BLOCK / 64; ++i) { lo = min(lo, s_cnt[i]); hi = max(hi, (int)s_scan[i]); }
+      lo = uni(lo); hi = uni(hi);
+      lds_barrier();                                       // (both arrays serve the selection below)
+    } else { lo = p.union_win[2 * (l & 1)]; hi = p.union_win[2 * (l & 1) + 1]; }
+    if (p.win_m1 >= 0) s = max(s, lo - p.win_m1);
+    if (p.win_m2 >= 0) e = min(e, hi);
   } else {
     if (p.win_m1 >= 0) s = max(s, tau - p.win_m1);
     if (p.win_m2 >= 0) e = min(e, tau_end + p.win_m2);
   }
-  s = checked(p, s, 1, T + 1, ERR_WINDOW);                 // (an empty window is e < s; its loads stay inside the row)
-  e = checked(p, e, -1, T, ERR_WINDOW);
+  int bad = 0;
+  s = clamped(s, 1, T + 1, ERR_WINDOW, bad);               // (an empty window is e < s; its loads stay inside the row)
+  e = clamped(e, -1, T, ERR_WINDOW, bad);
+  report(p, bad);
   const int W = e >= s ? e - s + 1 : 0;
   const int t0 = s & ~3;                                   // column loads start on a 16-byte boundary
   const int n4 = W > 0 ? ((e - t0) >> 2) + 1 : 0;

@@ -5,8 +5,8 @@
 //   - the "p > best_score" test that moves g.<eos> into the ended set, forced ending at the
 //     step cap, the eos-run stops;
 //   - ENDDETECT: Eq. (4), then Algorithm 3's tau count;
-//   - forward variables of the new hypotheses over their parent's window (one wave each,
-//     the recurrence evaluated as two wave-level scans of affine maps in the (logaddexp, +)
+//   - forward variables of the new hypotheses over their parent's window (a part of a wave, a wave or four waves each,
+//     the recurrence evaluated as two scans of affine maps in the (logaddexp, +)
 //     semiring), their time indices tau / tau~ (first argmax from the parent's tau on);
 //   - back-pointer record and the step's outputs.
 // Everything the decisions need is fetched in one round of independent loads at the top
@@ -29,23 +29,13 @@ __device__ __forceinline__ Aff aff_stage(Aff v) {
   return aff_then(left, v);
 }
 
-// inclusive scan of affine maps over the wave: lane t ends with map_0 then ... then map_t
-__device__ __forceinline__ Aff wave_scan_aff(Aff v) {
-  v = aff_stage<0x111, 0xf>(v);
-  v = aff_stage<0x112, 0xf>(v);
-  v = aff_stage<0x114, 0xf>(v);
-  v = aff_stage<0x118, 0xf>(v);
-  v = aff_stage<0x142, 0xa>(v);
-  v = aff_stage<0x143, 0xc>(v);
-  return v;
-}
-
 struct ArgMax { float v; int t; };
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ ArgMax argmax_stage(ArgMax x) {
   const float ov = dpp_f<CTRL, ROW_MASK>(-3.0e38f, x.v);
   const int ot = dpp_i<CTRL, ROW_MASK>(0x7fffffff, x.t);
-  if (ov > x.v || (ov == x.v && ot < x.t)) { x.v = ov; x.t = ot; }
+  const bool up = ov > x.v || (ov == x.v && ot < x.t);
+  x.v = up ? ov : x.v; x.t = up ? ot : x.t;
   return x;
 }
 // largest value, earliest frame among equals; result valid in lane 63
@@ -60,10 +50,13 @@ __device__ __forceinline__ ArgMax wave_argmax(ArgMax x) {
   return x;
 }
 
-// Forward variables of one new hypothesis (parent slot `par` extended by `tok`) over the
-// parent's window, by one wave: two scans of affine maps in the (logaddexp, +) semiring (each lane
-// owns a few consecutive frames, composes their maps, the wave scans the composed maps, and the
+// Forward variables of new hypotheses (parent slot `par` extended by `tok`) over the
+// parent's window: two scans of affine maps in the (logaddexp, +) semiring (each lane
+// owns FPL consecutive frames, composes their maps, the lanes scan the composed maps, and each
 // lane then replays its own frames).
+// LPS lanes share a survivor, 64 / LPS survivors a wave: 16 lanes x 8 frames cost a wave about 1.6 times the instructions
+// of 64 lanes x 2 frames and do four survivors instead of one, which is what counts once there are more survivors than
+// idle SIMDs; NWV = 4: the four waves of a work-group share one survivor (long windows of small batches).
 // The recurrence runs on the stored form of the variables (per-frame reference B_t taken out,
 // see Params::Bcum): with x'_t(c) = x_t(c) - max(x_t(blank), floor) and d_t = x_t(blank) -
 // max(x_t(blank), floor) (zero unless the floor cut),
@@ -72,60 +65,255 @@ __device__ __forceinline__ ArgMax wave_argmax(ArgMax x) {
 // re-based by delta = inc + (B_r - B_r'), r the parent's reference frame and r' = the parent's
 // tau the child's: its values are then near zero around its own tau.  Writes the new state into
 // slot n of the other buffer and returns delta and tau / tau~ (first argmax of the true variables,
-// stored + B_t, from the parent's tau on; the parent's values if nothing is finite).
+// stored + B_t, from the parent's tau on; the parent's values if nothing is finite), these two in the survivor's last lane.
+// Lanes own frames from a multiple of four on, so that state, posteriors and B go as 16-byte accesses; what a float4
+// holds outside the window is written as log0 and never read (the stored range says so).
 struct SurvivorIn {
   int par, tok, s, en, rs, re, ptau, ptau_end, plast, pref;
   float inc;
   int T;            // frames of the utterance (bounds of every time index)
 };
-// FPL consecutive frames per lane, 64 * FPL frames per pass.
-template <int FPL>
-__device__ __forceinline__ void wave_survivor_fpl(const SelectArgs& p, int Wb, int u, int n, const SurvivorIn& in,
-                                                  int& arg_n, int& arg_b, float& delta_out, double& bref_out) {
-  const int lane = threadIdx.x & 63;
+
+// inclusive scan of affine maps over LPS lanes: lane t ends with map_0 then ... then map_t
+template <int LPS>
+__device__ __forceinline__ Aff scan_aff(Aff v) {
+  v = aff_stage<0x111, 0xf>(v);
+  v = aff_stage<0x112, 0xf>(v);
+  v = aff_stage<0x114, 0xf>(v);
+  v = aff_stage<0x118, 0xf>(v);
+  if (LPS >= 32) v = aff_stage<0x142, 0xa>(v);
+  if (LPS >= 64) v = aff_stage<0x143, 0xc>(v);
+  return v;
+}
+// largest value, earliest frame among equals; valid in the last of LPS lanes
+template <int LPS>
+__device__ __forceinline__ ArgMax lanes_argmax(ArgMax x) {
+  x = argmax_stage<0x111, 0xf>(x);
+  x = argmax_stage<0x112, 0xf>(x);
+  x = argmax_stage<0x114, 0xf>(x);
+  x = argmax_stage<0x118, 0xf>(x);
+  if (LPS >= 32) x = argmax_stage<0x142, 0xa>(x);
+  if (LPS >= 64) x = argmax_stage<0x143, 0xc>(x);
+  return x;
+}
+
+struct SurvivorLds {                                       // NWV > 1
+  Aff tot[2][4];                                           // the waves' composed maps (n, b)
+  float last_n, last_b;                                    // the values of the pass's last frame
+  ArgMax best[2][4];
+};
+
+template <int LPS, int FPL, int NWV>
+__device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int n, bool active, const SurvivorIn& in,
+                                         SurvivorLds* sx, int& arg_n, int& arg_b, float& delta_out, double& bref_out) {
+  static_assert(FPL % 4 == 0 && (NWV == 1 || LPS == 64), "float4 per lane; waves share a survivor as wholes");
+  constexpr int NQ = FPL / 4, SPAN = LPS * FPL * NWV;      // frames per pass
+  const int lane = threadIdx.x & 63, w = NWV > 1 ? uni(threadIdx.x >> 6) : 0;
+  const int li = lane & (LPS - 1), lf = (w * 64 + li) * FPL;   // lane's place, its first frame's
   const size_t h0 = (size_t)u * Wb;
-  const size_t hp = h0 + checked(p, in.par, 0, Wb - 1, ERR_LIST_ENTRY);
+  int bad = 0;
+  const size_t hp = h0 + clamped(in.par, 0, Wb - 1, ERR_LIST_ENTRY, bad);
   const float* xu = p.xT + (size_t)u * p.V * p.Tp;
-  const float* x0 = xu + (size_t)p.blank_id * p.Tp;
-  const float* xc = xu + (size_t)checked(p, in.tok, 0, p.V - 1, ERR_TOKEN) * p.Tp;
+  const float* x0p = xu + (size_t)p.blank_id * p.Tp;
+  const float* xcp = xu + (size_t)clamped(in.tok, 0, p.V - 1, ERR_TOKEN, bad) * p.Tp;
   const double* Bu = p.Bcum + (size_t)u * p.Tp;
   const float* pgn = p.gn + hp * p.Tp;
   const float* pgb = p.gb + hp * p.Tp;
   float* cgn = p.gn_new + (h0 + n) * p.Tp;
   float* cgb = p.gb_new + (h0 + n) * p.Tp;
   const int T = in.T;
-  const int s = checked(p, in.s, 1, T, ERR_WINDOW), en = checked(p, in.en, s, T, ERR_WINDOW), rs = in.rs, re = in.re;
-  const double Bnew = Bu[checked(p, in.ptau, 0, T, ERR_TIME_INDEX)];   // the child's reference frame is the parent's tau
-  const float delta = in.inc + (float)(Bu[checked(p, in.pref, 0, T, ERR_TIME_INDEX)] - Bnew);
-  delta_out = delta;
+  const int s = clamped(in.s, 1, T, ERR_WINDOW, bad), en = clamped(in.en, s, T, ERR_WINDOW, bad), rs = in.rs, re = in.re;
+  // (the child's reference frame is the parent's tau; both values are first needed after the recurrence)
+  double Bnew = Bu[clamped(in.ptau, 0, T, ERR_TIME_INDEX, bad)], Bold = Bu[clamped(in.pref, 0, T, ERR_TIME_INDEX, bad)];
+  report(p, bad);
+  const bool rep = (in.tok == in.plast);
+  const int lo = max(s, in.ptau);
+  float carry_n = LOG0F, carry_b = LOG0F;
+  ArgMax best_n, best_b;
+  best_n.v = best_b.v = LOG0F; best_n.t = best_b.t = 0;
+  for (int base = s & ~3; __ballot(base <= en) != 0ull; base += SPAN) {
+    float gn[FPL], gb[FPL], x0[FPL], xc[FPL];
+    double Bt[FPL];
+    const int t0 = base + lf;
+    const int tm = min(max(base - 1, 0), T);               // the frame before the pass
+    const float gn_m = pgn[tm], gb_m = pgb[tm];
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {                         // (clamped into the row; rows are whole multiples of four)
+      const int t4 = min(t0 + 4 * k, p.Tp - 4);
+      const float4 a = *(const float4*)(pgn + t4), b = *(const float4*)(pgb + t4), c = *(const float4*)(x0p + t4),
+                   d = *(const float4*)(xcp + t4);
+      const double2 e = *(const double2*)(Bu + t4), f = *(const double2*)(Bu + t4 + 2);
+      gn[4 * k] = a.x; gn[4 * k + 1] = a.y; gn[4 * k + 2] = a.z; gn[4 * k + 3] = a.w;
+      gb[4 * k] = b.x; gb[4 * k + 1] = b.y; gb[4 * k + 2] = b.z; gb[4 * k + 3] = b.w;
+      x0[4 * k] = c.x; x0[4 * k + 1] = c.y; x0[4 * k + 2] = c.z; x0[4 * k + 3] = c.w;
+      xc[4 * k] = d.x; xc[4 * k + 1] = d.y; xc[4 * k + 2] = d.z; xc[4 * k + 3] = d.w;
+      Bt[4 * k] = e.x; Bt[4 * k + 1] = e.y; Bt[4 * k + 2] = f.x; Bt[4 * k + 3] = f.y;
+    }
+    float tw_n = 0.0f, tw_b = 0.0f;                        // the frame before the wave's
+    if (NWV > 1) { const int tw = min(max(base + w * 64 * FPL - 1, 0), T); tw_n = pgn[tw]; tw_b = pgb[tw]; }
+#pragma unroll
+    for (int k = 0; k < FPL; ++k) { LOADED(gn[k]); LOADED(gb[k]); }
+    // the previous frame's state: the lane before holds it for the lane's first frame
+    float pn = dpp_f<0x138, 0xf>(0.0f, gn[FPL - 1]), pb = dpp_f<0x138, 0xf>(0.0f, gb[FPL - 1]);
+    if (li == 0) { pn = NWV > 1 ? tw_n : gn_m; pb = NWV > 1 ? tw_b : gb_m; }
+    Aff mn[FPL];                                           // n_t = (n_{t-1} (+) f_t) + x'_t(c)
+    float d[FPL];
+    bool v[FPL];
+#pragma unroll
+    for (int k = 0; k < FPL; ++k) {
+      const int t = t0 + k;
+      v[k] = t >= s && t <= en;
+      const float gnp = k == 0 ? pn : gn[k > 0 ? k - 1 : 0], gbp = k == 0 ? pb : gb[k > 0 ? k - 1 : 0];
+      const float x0f = fmaxf(x0[k], BLANK_FLOOR), x = xc[k] - x0f;
+      d[k] = x0[k] - x0f;
+      float f = LOG0F;
+      if (t - 1 >= rs && t - 1 <= re) f = rep ? gbp : lae(gnp, gbp);
+      mn[k].a = v[k] ? x : 0.0f; mn[k].b = v[k] ? f + x : LOG0F;
+    }
+    auto run = [&](const Aff (&mp)[FPL], float carry, int which, float& v_in, float (&out)[FPL]) {
+      Aff C = mp[0];
+#pragma unroll
+      for (int k = 1; k < FPL; ++k) C = aff_then(C, mp[k]);
+      const Aff P = scan_aff<LPS>(C);
+      Aff E;                                               // maps of all earlier lanes
+      E.a = dpp_f<0x138, 0xf>(0.0f, P.a); E.b = dpp_f<0x138, 0xf>(LOG0F, P.b);
+      if (li == 0) { E.a = 0.0f; E.b = LOG0F; }
+      if (NWV > 1) {
+        if (lane == 63) sx->tot[which][w] = P;
+        lds_barrier();
+        Aff W;                                             // maps of all earlier waves
+        W.a = 0.0f; W.b = LOG0F;
+#pragma unroll
+        for (int i = 0; i < NWV - 1; ++i) if (i < w) W = aff_then(W, sx->tot[which][i]);
+        E = aff_then(W, E);
+      }
+      v_in = lae(E.a + carry, E.b);
+      out[0] = lae(v_in + mp[0].a, mp[0].b);
+#pragma unroll
+      for (int k = 1; k < FPL; ++k) out[k] = lae(out[k - 1] + mp[k].a, mp[k].b);
+    };
+    float n_in, b_in, nv[FPL], bv[FPL];
+    run(mn, carry_n, 0, n_in, nv);
+    Aff mb[FPL];                                           // b_t = (n_{t-1} (+) b_{t-1}) + d_t
+#pragma unroll
+    for (int k = 0; k < FPL; ++k) {
+      const float nprev = k == 0 ? n_in : nv[k > 0 ? k - 1 : 0];
+      mb[k].a = v[k] ? d[k] : 0.0f; mb[k].b = v[k] ? nprev + d[k] : LOG0F;
+    }
+    run(mb, carry_b, 1, b_in, bv);
+    const float delta = in.inc + (float)(Bold - Bnew);
+    // re-base, store, and the lane's own first argmax over t >= lo of the true variables
+    // (stored + B_t; B relative to the child's reference)
+    ArgMax xn, xb;
+    xn.v = LOG0F; xn.t = t0; xb.v = LOG0F; xb.t = t0;
+    float rn[FPL], rb[FPL];
+#pragma unroll
+    for (int k = 0; k < FPL; ++k) {
+      const int t = t0 + k;
+      rn[k] = (!v[k] || nv[k] < LOG0_CLASS) ? LOG0F : nv[k] - delta;
+      rb[k] = (!v[k] || bv[k] < LOG0_CLASS) ? LOG0F : bv[k] - delta;
+      const bool ok = t >= lo;
+      const float bt = (float)(Bt[k] - Bnew);
+      const float cn = (ok && rn[k] > LOG0_CLASS) ? rn[k] + bt : LOG0F;
+      const float cb = (ok && rb[k] > LOG0_CLASS) ? rb[k] + bt : LOG0F;
+      if (cn > xn.v) { xn.v = cn; xn.t = t; }              // (strict: the earlier frame keeps a tie)
+      if (cb > xb.v) { xb.v = cb; xb.t = t; }
+    }
+    if (active) {
+#pragma unroll
+      for (int k = 0; k < NQ; ++k)
+        if (t0 + 4 * k <= en && t0 + 4 * k + 3 >= s) {
+          *(float4*)(cgn + t0 + 4 * k) = make_float4(rn[4 * k], rn[4 * k + 1], rn[4 * k + 2], rn[4 * k + 3]);
+          *(float4*)(cgb + t0 + 4 * k) = make_float4(rb[4 * k], rb[4 * k + 1], rb[4 * k + 2], rb[4 * k + 3]);
+        }
+    }
+    xn = lanes_argmax<LPS>(xn); xb = lanes_argmax<LPS>(xb);
+    if (xn.v > LOG0_CLASS && xn.v > best_n.v) best_n = xn;
+    if (xb.v > LOG0_CLASS && xb.v > best_b.v) best_b = xb;
+    if (__ballot(base + SPAN <= en) != 0ull) {             // (uniform) another pass: hand on the last frame's values
+      if (NWV > 1) {
+        if (threadIdx.x == 64 * NWV - 1) { sx->last_n = nv[FPL - 1]; sx->last_b = bv[FPL - 1]; }
+        lds_barrier();
+        carry_n = sx->last_n; carry_b = sx->last_b;
+        lds_barrier();
+      } else {
+        carry_n = __shfl(nv[FPL - 1], (lane & ~(LPS - 1)) + LPS - 1);
+        carry_b = __shfl(bv[FPL - 1], (lane & ~(LPS - 1)) + LPS - 1);
+      }
+    }
+  }
+  if (NWV > 1) {
+    if (lane == 63) { sx->best[0][w] = best_n; sx->best[1][w] = best_b; }
+    lds_barrier();
+    best_n = sx->best[0][0]; best_b = sx->best[1][0];      // (waves hold ascending frames within a pass, not across passes)
+#pragma unroll
+    for (int i = 1; i < NWV; ++i) {
+      const ArgMax a = sx->best[0][i], b = sx->best[1][i];
+      if (a.v > best_n.v || (a.v == best_n.v && a.t < best_n.t)) best_n = a;
+      if (b.v > best_b.v || (b.v == best_b.v && b.t < best_b.t)) best_b = b;
+    }
+  }
+  arg_n = best_n.v > LOG0_CLASS ? best_n.t : in.ptau;
+  arg_b = best_b.v > LOG0_CLASS ? best_b.t : in.ptau_end;
+  delta_out = in.inc + (float)(Bold - Bnew);
   bref_out = Bnew;
+}
+
+// The form of least latency for windows of up to 128 frames: one wave, two frames per lane (any start; longer windows
+// in several passes).
+__device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u, int n, const SurvivorIn& in,
+                                                  int& arg_n, int& arg_b, float& delta_out, double& bref_out) {
+  constexpr int FPL = 2;
+  const int lane = threadIdx.x & 63;
+  const size_t h0 = (size_t)u * Wb;
+  int bad = 0;
+  const size_t hp = h0 + clamped(in.par, 0, Wb - 1, ERR_LIST_ENTRY, bad);
+  const float* xu = p.xT + (size_t)u * p.V * p.Tp;
+  const float* x0 = xu + (size_t)p.blank_id * p.Tp;
+  const float* xc = xu + (size_t)clamped(in.tok, 0, p.V - 1, ERR_TOKEN, bad) * p.Tp;
+  const double* Bu = p.Bcum + (size_t)u * p.Tp;
+  const float* pgn = p.gn + hp * p.Tp;
+  const float* pgb = p.gb + hp * p.Tp;
+  float* cgn = p.gn_new + (h0 + n) * p.Tp;
+  float* cgb = p.gb_new + (h0 + n) * p.Tp;
+  const int T = in.T;
+  const int s = clamped(in.s, 1, T, ERR_WINDOW, bad), en = clamped(in.en, s, T, ERR_WINDOW, bad), rs = in.rs, re = in.re;
+  // (the child's reference frame is the parent's tau; both values are first needed after the recurrence)
+  double Bnew = Bu[clamped(in.ptau, 0, T, ERR_TIME_INDEX, bad)], Bold = Bu[clamped(in.pref, 0, T, ERR_TIME_INDEX, bad)];
+  report(p, bad);
   const bool rep = (in.tok == in.plast);
   const int lo = max(s, in.ptau);
   float carry_n = LOG0F, carry_b = LOG0F;
   float best_n = LOG0F, best_b = LOG0F;
   arg_n = in.ptau; arg_b = in.ptau_end;
   for (int base = s; base <= en; base += 64 * FPL) {
-    int t[FPL]; bool v[FPL]; float bt[FPL];
+    int t[FPL]; bool v[FPL]; double Bt[FPL];
+    float g_n[FPL], g_b[FPL], x0v[FPL], xcv[FPL];
     Aff mn[FPL];                                         // n_t = (n_{t-1} (+) f_t) + x'_t(c)
     float d[FPL];
 #pragma unroll
-    for (int k = 0; k < FPL; ++k) {
+    for (int k = 0; k < FPL; ++k) {                      // one round of loads
       t[k] = base + FPL * lane + k;
       v[k] = t[k] <= en;
       const int tc = min(t[k], en);                      // clamped: loads are unconditional
-      const float gn = pgn[max(tc - 1, 0)], gb = pgb[max(tc - 1, 0)];
-      const float x0v = x0[tc];
-      const float x = xc[tc] - fmaxf(x0v, BLANK_FLOOR);
-      d[k] = x0v - fmaxf(x0v, BLANK_FLOOR);
-      bt[k] = (float)(Bu[tc] - Bnew);
-      float f = LOG0F;
-      if (t[k] - 1 >= rs && t[k] - 1 <= re) f = rep ? gb : lae(gn, gb);
+      g_n[k] = pgn[tc - 1]; g_b[k] = pgb[tc - 1]; x0v[k] = x0[tc]; xcv[k] = xc[tc];   // (tc >= s >= 1)
+      Bt[k] = Bu[tc];
+    }
+#pragma unroll
+    for (int k = 0; k < FPL; ++k) { LOADED(g_n[k]); LOADED(g_b[k]); }
+#pragma unroll
+    for (int k = 0; k < FPL; ++k) {
+      const float gn = g_n[k], gb = g_b[k];
+      const float x = xcv[k] - fmaxf(x0v[k], BLANK_FLOOR);
+      d[k] = x0v[k] - fmaxf(x0v[k], BLANK_FLOOR);
+      float f = rep ? gb : lae(gn, gb);
+      f = t[k] - 1 >= rs && t[k] - 1 <= re ? f : LOG0F;
       mn[k].a = v[k] ? x : 0.0f; mn[k].b = v[k] ? f + x : LOG0F;
     }
     Aff C = mn[0];
 #pragma unroll
     for (int k = 1; k < FPL; ++k) C = aff_then(C, mn[k]);
-    Aff P = wave_scan_aff(C);
+    Aff P = scan_aff<64>(C);
     Aff E;                                               // maps of all earlier lanes
     E.a = dpp_f<0x138, 0xf>(0.0f, P.a); E.b = dpp_f<0x138, 0xf>(LOG0F, P.b);
     const float n_in = lae(E.a + carry_n, E.b);
@@ -142,7 +330,7 @@ __device__ __forceinline__ void wave_survivor_fpl(const SelectArgs& p, int Wb, i
     C = mb[0];
 #pragma unroll
     for (int k = 1; k < FPL; ++k) C = aff_then(C, mb[k]);
-    P = wave_scan_aff(C);
+    P = scan_aff<64>(C);
     E.a = dpp_f<0x138, 0xf>(0.0f, P.a); E.b = dpp_f<0x138, 0xf>(LOG0F, P.b);
     const float b_in = lae(E.a + carry_b, E.b);
     float bv[FPL];
@@ -150,6 +338,7 @@ __device__ __forceinline__ void wave_survivor_fpl(const SelectArgs& p, int Wb, i
 #pragma unroll
     for (int k = 1; k < FPL; ++k) bv[k] = lae(bv[k - 1] + mb[k].a, mb[k].b);
     carry_n = lane_f(nv[FPL - 1], 63); carry_b = lane_f(bv[FPL - 1], 63);
+    const float delta = in.inc + (float)(Bold - Bnew);
     // re-base, store, and the lane's own first argmax over t >= lo of the true variables
     // (stored + B_t; B relative to the child's reference)
     ArgMax xn, xb;
@@ -160,8 +349,9 @@ __device__ __forceinline__ void wave_survivor_fpl(const SelectArgs& p, int Wb, i
       const float rb = (bv[k] < LOG0_CLASS) ? LOG0F : bv[k] - delta;
       if (v[k]) { cgn[t[k]] = rn; cgb[t[k]] = rb; }
       const bool ok = v[k] && t[k] >= lo;
-      const float cn = (ok && rn > LOG0_CLASS) ? rn + bt[k] : LOG0F;
-      const float cb = (ok && rb > LOG0_CLASS) ? rb + bt[k] : LOG0F;
+      const float bt = (float)(Bt[k] - Bnew);
+      const float cn = (ok && rn > LOG0_CLASS) ? rn + bt : LOG0F;
+      const float cb = (ok && rb > LOG0_CLASS) ? rb + bt : LOG0F;
       if (cn > xn.v) { xn.v = cn; xn.t = t[k]; }           // (strict: the earlier frame keeps a tie)
       if (cb > xb.v) { xb.v = cb; xb.t = t[k]; }
     }
@@ -169,20 +359,8 @@ __device__ __forceinline__ void wave_survivor_fpl(const SelectArgs& p, int Wb, i
     if (xn.v > LOG0_CLASS && xn.v > best_n) { best_n = xn.v; arg_n = xn.t; }
     if (xb.v > LOG0_CLASS && xb.v > best_b) { best_b = xb.v; arg_b = xb.t; }
   }
-}
-
-// windows of up to 128 frames: two frames per lane, one pass; up to 256: four per lane (a pass costs
-// about 1.4 times as much and covers twice as many frames); longer ones: eight per lane.
-// FPLMAX = 2: the kernel carries the two-frames form only (wider windows take several passes of it).  The
-// host asks for that when the window margins keep windows within 128 frames but for rare exceptions: the
-// forms with more frames per lane are what sets the kernel's register count (97 against 58).
-template <int FPLMAX>
-__device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u, int n, const SurvivorIn& in,
-                                              int& arg_n, int& arg_b, float& delta_out, double& bref_out) {
-  const int W = in.en - in.s + 1;
-  if (FPLMAX == 2 || W <= 128) wave_survivor_fpl<2>(p, Wb, u, n, in, arg_n, arg_b, delta_out, bref_out);
-  else if (W <= 256) wave_survivor_fpl<4>(p, Wb, u, n, in, arg_n, arg_b, delta_out, bref_out);
-  else wave_survivor_fpl<8>(p, Wb, u, n, in, arg_n, arg_b, delta_out, bref_out);
+  delta_out = in.inc + (float)(Bold - Bnew);
+  bref_out = Bnew;
 }
 
 // How many of the keys s_k2[0 .. 2 * quads) (four per quad, zero padding at the end) exceed `me`,
@@ -265,7 +443,8 @@ __device__ __forceinline__ bool wave_ended_set(const SelectArgs& p, int Wb, int 
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     const double ov = __shfl_xor(bje, o); const int oj = __shfl_xor(bj, o);
-    if (ov > bje || (ov == bje && oj < bj)) { bje = ov; bj = oj; }
+    const bool up = ov > bje || (ov == bje && oj < bj);
+    bje = up ? ov : bje; bj = up ? oj : bj;
   }
   if (lane < Wb) { p.out8[UW + h0 + lane] = (uint8_t)added; p.out8[2 * UW + h0 + lane] = (uint8_t)stp; }
   const int n_before = __shfl(st_n, 0);
@@ -302,8 +481,9 @@ __device__ __forceinline__ bool wave_ended_set(const SelectArgs& p, int Wb, int 
   return fin;
 }
 
+// Wave 0 takes the ended set, the others 64 / LPS new hypotheses each at a time.
 // Dynamic LDS: 16 * ((Wb * Wb + 9) & ~1) + 28 * Wb * Wb bytes (the list entries and the packed contenders).
-template <int BLOCK, int FPLMAX>
+template <int BLOCK, int LPS, int FPL>
 __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
                                                   const GroupOut* __restrict__ grp, const ListEntry* __restrict__ grp_list,
                                                   const UttInfo* __restrict__ uinfo, int Wb, int l, SelectArgs p) {
@@ -431,17 +611,26 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
   // finished utterance's new state is computed too but never used: its slots are marked dead.)
   const size_t UW = (size_t)p.U * Wb;
   float* out_score = (float*)(p.out + 2 * UW);
-  for (int n = w - 1; n >= 0 && n < n_new; n += NW - 1) {
-    const int e = checked(p, s_sel[n], 0, NE - 1, ERR_LIST_ENTRY), par = s_par[e];
+  constexpr int PER = 64 / LPS;
+  const int wu = uni(w), nu = uni(n_new);
+  for (int n0 = (wu - 1) * PER; n0 >= 0 && n0 < nu; n0 += (NW - 1) * PER) {
+    const int n = n0 + lane / LPS;
+    const bool active = n < nu;
+    const int e = active ? checked(p, s_sel[n], 0, NE - 1, ERR_LIST_ENTRY) : 0, par = active ? s_par[e] : 0;
     SurvivorIn in;
-    in.par = par; in.tok = s_tok[e]; in.inc = s_inc[e]; in.T = T;
-    in.s = o_ws[par]; in.en = o_we[par]; in.rs = o_rs[par]; in.re = o_re[par];
-    in.ptau = o_tau[par]; in.ptau_end = o_tau_end[par]; in.plast = o_last[par]; in.pref = o_ref[par];
+    in.par = par; in.T = T;
+    if (active) {
+      in.tok = s_tok[e]; in.inc = s_inc[e];
+      in.s = o_ws[par]; in.en = o_we[par]; in.rs = o_rs[par]; in.re = o_re[par];
+      in.ptau = o_tau[par]; in.ptau_end = o_tau_end[par]; in.plast = o_last[par]; in.pref = o_ref[par];
+    } else {                                               // (lanes without a hypothesis go through the motions)
+      in.tok = p.blank_id; in.inc = 0.0f; in.s = in.en = 1; in.rs = in.re = in.ptau = in.ptau_end = in.plast = in.pref = 0;
+    }
     int arg_n, arg_b;
     float delta;
     double bref;
-    wave_survivor<FPLMAX>(p, Wb, u, n, in, arg_n, arg_b, delta, bref);
-    if (lane == 0) {
+    survivor<LPS, FPL, 1>(p, Wb, u, active ? n : 0, active, in, nullptr, arg_n, arg_b, delta, bref);
+    if (active && (lane & (LPS - 1)) == LPS - 1) {
       p.out[3 * UW + h0 + n] = arg_n; p.out[4 * UW + h0 + n] = arg_b;
       p.trie[(size_t)2 * p.trie_stride + h0 + n] = arg_n;
       s_ntau[n] = arg_n; s_ntau_end[n] = arg_b; s_delta[n] = delta; s_bref[n] = bref;
@@ -492,11 +681,15 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
 // the utterance state is read by slot 0's work-group alone, and "finished before this step"
 // is taken from the step number at which the utterance finished (0 or the current step both
 // mean no).
-// Dynamic LDS: 28 * Wb * Wb + 64 bytes (the list entries).
+// WIDE: windows beyond 128 frames are common (the host knows from the window margins).  All waves of a work-group then
+// share the recurrence of such a window, and what belongs to the utterance as a whole is done by a work-group of its
+// own, slot number Wb.
+// Dynamic LDS: 28 * Wb * Wb + 64 bytes (the list entries), for beams above 12 another 12 * Wb * Wb + 80 (the packed
+// contenders: with 400 entries, all against all took 7 us).
 // The arguments in front of the block are what the first round of loads needs: plain leading arguments reach the wave
 // in registers when it starts (kernel-argument preload), so that those loads do not wait for a load of the arguments.
 // Grid: (1 << sh, Wb, ceil(U / (1 << sh))), sh = l >> 28: utterance z * 2^sh + x, new slot y (as in k_score).
-template <int BLOCK, int FPLMAX>
+template <int BLOCK, bool WIDE>
 __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
                                                         const GroupOut* __restrict__ grp, const ListEntry* __restrict__ grp_list,
                                                         const UttInfo* __restrict__ uinfo, int Wb, int l_sh, SelectArgs p) {
@@ -508,8 +701,14 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
   int* s_tok = (int*)(s_J + NE);                                      // [NE]
   float* s_inc = (float*)(s_tok + NE);                                // [NE]
   float* s_att = s_inc + NE;                                          // [NE]
-  __shared__ int o_live[MAX_BEAM], o_n[MAX_BEAM], o_stp[MAX_BEAM], o_tau[MAX_BEAM], o_tau_end[MAX_BEAM];
-  __shared__ int o_rs[MAX_BEAM], o_re[MAX_BEAM], o_last[MAX_BEAM], o_ws[MAX_BEAM], o_we[MAX_BEAM], o_ref[MAX_BEAM];
+  unsigned long long* s_ck = (unsigned long long*)(split_smem + ((28 * (size_t)NE + 64 + 15) & ~(size_t)15));   // [NE + 8] (Wb > 12)
+  int* s_cidx = (int*)(s_ck + NE + 8);                                // [NE]
+  __shared__ SurvivorLds s_sx;
+  __shared__ int s_cnt[2];
+  __shared__ unsigned long long s_min;
+  const bool pack = Wb > 12;
+  __shared__ int o_live[MAX_BEAM], o_n[MAX_BEAM], o_stp[MAX_BEAM], o_tau[MAX_BEAM];
+  __shared__ int o_par[MAX_BEAM][8];       // what a survivor needs of its parent: window, range, tau, tau~, last label, reference frame
   __shared__ long long o_cells[MAX_BEAM];
   __shared__ double o_je[MAX_BEAM], o_hatt[MAX_BEAM], o_off[MAX_BEAM];
   __shared__ int s_pick[2];                // entry ranked n, entry ranked 0
@@ -521,7 +720,7 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
   UttState* us = utt + u;
   const int fs = us->finished_step;        // (tested after the first round of loads is on its way)
   const size_t h0 = (size_t)u * Wb;
-  const bool lead = (n == 0);
+  const bool lead = (n == (WIDE ? Wb : 0));
   if (lead) TRACE_POINT(p, (size_t)u * Wb, 8);
 
   // ---- first round of loads: everything that depends on nothing --------------------------------
@@ -530,9 +729,9 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
     const HypRec r = rec_now[h];
     const GroupOut g = grp[h];
     o_live[tid] = r.live; o_n[tid] = g.n; o_stp[tid] = g.stopped;
-    o_tau[tid] = r.tau; o_tau_end[tid] = r.tau_end;
-    o_rs[tid] = r.rs; o_re[tid] = r.re; o_last[tid] = r.last;
-    o_ws[tid] = g.win_s; o_we[tid] = g.win_e; o_ref[tid] = r.ref;
+    o_tau[tid] = r.tau;
+    o_par[tid][0] = g.win_s; o_par[tid][1] = g.win_e; o_par[tid][2] = r.rs; o_par[tid][3] = r.re;
+    o_par[tid][4] = r.tau; o_par[tid][5] = r.tau_end; o_par[tid][6] = r.last; o_par[tid][7] = r.ref;
     o_cells[tid] = g.cells;
     o_je[tid] = g.joint_eos; o_hatt[tid] = r.att; o_off[tid] = r.off;
   }
@@ -540,7 +739,8 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
   const int lmax_u = uinfo[u].lmax;
   double st_best = LOG0D, ring_sc = LOG0D;
   int st_n = 0, st_cnt = 0, ring_tag = -1;
-  if (lead && w == 1) {
+  const int lead_w = WIDE ? 0 : 1;        // the wave for the utterance as a whole
+  if (lead && w == lead_w) {
     if (lane == 0) { st_best = us->best_score; st_n = us->n_ended; st_cnt = us->cnt_tau_T; }
     if (lane < p.end_m) { ring_sc = us->ring_score[lane]; ring_tag = us->ring_tag[lane]; }
   }
@@ -565,8 +765,10 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
       key = r < nj ? ((k & ~1023ull) | (unsigned long long)(1023 - i)) : (unsigned long long)(1023 - i) >> 1;
     }
     s_key[i] = key;
+    if (pack) s_ck[i] = 0ull;
   }
-  if (tid < 2) s_pick[tid] = -1;
+  if (tid < 2) { s_pick[tid] = -1; s_cnt[tid] = 0; }
+  if (tid == 2) s_min = ~0ull;
   if (fs != 0 && fs < l) return;           // outputs of a finished utterance were settled when it finished
   lds_barrier();
   if (lead) TRACE_POINT(p, (size_t)u * Wb, 9);
@@ -577,9 +779,23 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
 #pragma unroll 8
   for (int j = 0; j < Wb; ++j) ne += o_n[j];
   const int n_new = min(ne, Wb);
-  // (all entries against all: packing the contenders first, as the per-utterance kernel does, costs two
-  // barriers more than it saves at these sizes -- measured)
-  {
+  if (pack) {
+    const int NC = uni(pack_contenders<BLOCK>(s_key, NE, Wb, o_n, s_ck, s_cidx, s_cnt, &s_min));
+    const int L = NC <= BLOCK / 8 ? 8 : (NC <= BLOCK / 4 ? 4 : (NC <= BLOCK / 2 ? 2 : 1));
+    const int part = tid & (L - 1), quads = (NC + 3) >> 2;   // (zeros follow the packed keys)
+    for (int e0 = 0; e0 < NC; e0 += BLOCK / L) {
+      const int e = e0 + tid / L;
+      int rank = count_greater((const ulonglong2*)s_ck, s_ck[min(e, NC)], part, L, quads);
+      if (L >= 2) rank += dpp_i<0xB1, 0xf>(0, rank);       // quad_perm [1,0,3,2]
+      if (L >= 4) rank += dpp_i<0x4E, 0xf>(0, rank);       // quad_perm [2,3,0,1]
+      if (L == 8) rank += dpp_i<0x104, 0xf>(0, rank);      // row_shl:4
+      if (part == 0 && e < NC) {
+        if (rank == n) s_pick[0] = s_cidx[e];
+        if (rank == 0) s_pick[1] = s_cidx[e];
+      }
+    }
+  } else {
+    // (all entries against all: packing the contenders first costs two barriers more than it saves at these sizes)
     const int L = NE <= 64 ? 4 : (NE <= 128 ? 2 : 1);
     const int part = tid & (L - 1);
     const int quads = (NE + 3) >> 2;                       // (the padding holds zeros)
@@ -601,20 +817,29 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
 
   const size_t UW = (size_t)p.U * Wb;
   float* out_score = (float*)(p.out + 2 * UW);
-  if (w == 0) {
+  const bool hyp = n < Wb && n < n_new;
+  const int e_n = hyp ? uni(checked(p, s_pick[0], 0, NE - 1, ERR_LIST_ENTRY)) : 0, par = e_n / Wb;
+  // (a lane each, then into scalar registers: the recurrence below then runs on scalar bases and bounds)
+  const int pv = o_par[par][lane & 7];
+  const int par_s = __builtin_amdgcn_readlane(pv, 0), par_e = __builtin_amdgcn_readlane(pv, 1);
+  const bool shared = WIDE && hyp && par_e - par_s >= 128;                   // all waves take part (uniform)
+  if (n < Wb && (w == 0 || shared)) {
     // ---- new hypothesis n: forward variables, record, outputs, back-pointer -----------------
     const size_t h = h0 + n;
-    if (n < n_new) {
-      const int e = checked(p, s_pick[0], 0, NE - 1, ERR_LIST_ENTRY), par = e / Wb;
+    if (hyp) {
+      const int e = e_n;
       SurvivorIn in;
-      in.par = par; in.tok = s_tok[e]; in.inc = s_inc[e]; in.T = T;
-      in.s = o_ws[par]; in.en = o_we[par]; in.rs = o_rs[par]; in.re = o_re[par];
-      in.ptau = o_tau[par]; in.ptau_end = o_tau_end[par]; in.plast = o_last[par]; in.pref = o_ref[par];
+      in.par = par; in.tok = uni(s_tok[e]); in.inc = s_inc[e]; in.T = T;
+      in.s = par_s; in.en = par_e;
+      in.rs = __builtin_amdgcn_readlane(pv, 2); in.re = __builtin_amdgcn_readlane(pv, 3);
+      in.ptau = __builtin_amdgcn_readlane(pv, 4); in.ptau_end = __builtin_amdgcn_readlane(pv, 5);
+      in.plast = __builtin_amdgcn_readlane(pv, 6); in.pref = __builtin_amdgcn_readlane(pv, 7);
       int arg_n, arg_b;
       float delta;
       double bref;
-      wave_survivor<FPLMAX>(p, Wb, u, n, in, arg_n, arg_b, delta, bref);
-      if (lane == 0) {
+      if (shared) survivor<64, 4, BLOCK / 64>(p, Wb, u, n, true, in, &s_sx, arg_n, arg_b, delta, bref);
+      else wave_survivor(p, Wb, u, n, in, arg_n, arg_b, delta, bref);
+      if (tid == 0) {
         p.out[3 * UW + h] = arg_n; p.out[4 * UW + h] = arg_b;
         p.trie[(size_t)2 * p.trie_stride + h] = arg_n;
         p.out[h] = par; p.out[UW + h] = in.tok; out_score[h] = (float)s_J[e];
@@ -626,13 +851,18 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
         r->att = o_hatt[par] + (double)s_att[e];
         r->joint = s_J[e];
         r->bref = bref;
+        if (p.win_union) {                       // the utterance's share of the next step's window (ignored if it finishes)
+          int32_t* sh = p.union_win + 2 * ((size_t)((l + 1) & 1) * p.U + u);
+          atomicMin(&sh[0], arg_n);
+          atomicMax(&sh[1], min(arg_b + p.win_m2, T));
+        }
       }
     } else if (lane == 0) {
       p.out[h] = -1; p.out[UW + h] = -1; out_score[h] = LOG0F;
       p.out[3 * UW + h] = 0; p.out[4 * UW + h] = 0;
       p.trie[h] = -1; p.trie[p.trie_stride + h] = -1; p.trie[(size_t)2 * p.trie_stride + h] = 0;
     }
-  } else if (lead && w == 1) {
+  } else if (lead && w == lead_w) {
     // ---- the utterance as a whole: ended set, end detection, live flags ----------------------
     const bool has_best = ne > 0;
     const double best = has_best ? s_J[checked(p, s_pick[1], 0, NE - 1, ERR_LIST_ENTRY)] : LOG0D;
