@@ -48,7 +48,8 @@ struct ctcbs {
   int score_block, score_lpc, select_block;
   int select_lps;              // select kernel: lanes per new hypothesis
   bool select_wide;            // windows beyond 128 frames are common
-  bool score_wide, score_bigk;
+  int score_it;                // float4 per lane and column in flight
+  bool score_bigk;
   int score_nv4;               // granules of an attention row per lane
   bool dense;                  // every id a candidate: the kernels of k_dense.h
   // Pinned, device-mapped host memory, one allocation: the progress word that the score kernel refreshes every
@@ -272,13 +273,14 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   // 25.1 -> 26.9 us, T in 1000..1500 34.2 -> 43.5 us: beyond 512 frames the 64-lane form stays)
   const bool short_whole = !windowed && p.Tp <= 512;
   h->score_lpc = (windowed || short_whole) ? 16 : 64;
-  // windows beyond 128 frames (16 lanes x 2 float4): four float4 per lane in flight, two candidates at a time
-  h->score_wide = short_whole || (windowed && (c.win_m1 + c.win_m2 + 1 + 3) > 128);
+  // float4 per lane in flight: windows of up to 128 frames (16 lanes x 2 float4), up to 192, wider ones.  Three fit
+  // in 72 registers, seven waves per SIMD, where four take 80 and spill; one load fewer per lane for the same frames.
+  h->score_it = h->score_lpc == 64 || short_whole ? 4 : (c.win_m1 + c.win_m2 + 1 + 3 <= 128 ? 2 : (c.win_m1 + c.win_m2 + 1 + 3 <= 192 ? 3 : 4));
   // LDS of the score kernel: the short list (or the radix histogram), the f terms, the per-candidate arrays
   size_t off = restricted ? (size_t)PIVOT_CAP * 8 : 0;
   h->off_f = (int32_t)off;
   // the f terms, padded to whole rounds of the column loads (4 * LPC * IT frames)
-  const int round_frames = 4 * h->score_lpc * (h->score_lpc == 64 || h->score_wide ? 4 : 2);
+  const int round_frames = 4 * h->score_lpc * h->score_it;
   h->wp_max = (p.Tp + round_frames - 1) / round_frames * round_frames;
   off += (size_t)2 * h->wp_max * 4;
   h->off_small = (int32_t)off;
@@ -453,15 +455,16 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
     h->ev_used += 3;
     HIPCHK(hipEventRecord(ev[0], h->stream));
   }
-  // 16 lanes x 2 float4 per candidate cover windows of up to 128 frames without a second trip to
-  // memory, 16 lanes x 4 float4 wider windows and whole utterances of up to 512 frames; whole-utterance
+  // 16 lanes x 2 (3) float4 per candidate cover windows of up to 128 (192) frames without a second trip to
+  // memory, 16 lanes x 4 float4 serve wider windows and whole utterances of up to 512 frames; whole-utterance
   // windows beyond that use whole waves, 4 float4 (1024 frames) in flight (see create_impl)
   hipError_t e;
   if (h->dense) e = launch_dense(h, p, d_att_logp, l);
   else
-    e = (h->score_lpc == 16) ? (h->score_wide ? launch_score<256, 16, 2, 4>(h, p, d_att_logp, l)
-                                              : launch_score<256, 16, 3, 2>(h, p, d_att_logp, l))
-                             : launch_score<256, 64, 2, 4>(h, p, d_att_logp, l);
+    e = h->score_lpc == 64 ? launch_score<256, 64, 2, 4>(h, p, d_att_logp, l)
+        : h->score_it == 2 ? launch_score<256, 16, 3, 2>(h, p, d_att_logp, l)
+        : h->score_it == 3 ? launch_score<256, 16, 2, 3>(h, p, d_att_logp, l)
+                           : launch_score<256, 16, 2, 4>(h, p, d_att_logp, l);
   HIPCHK(e);
   if (ev) HIPCHK(hipEventRecord(ev[1], h->stream));       // (the list builder below counts as selection)
   if (h->dense || p.K > h->score_block) HIPCHK(launch_lists(h, p, d_att_logp));

@@ -1,9 +1,9 @@
 // Score kernel: one work-group per (utterance, beam slot) hypothesis g.
 //   1. candidate pre-selection: the K ids with the largest attention log-prob, ties to the
 //      smaller id.  The row never goes through LDS: every lane keeps its float4 loads in
-//      registers.  A pivot that is provably not above the K-th largest value (every wave contributes
-//      a value that its share of K of its lanes' maxima reach, found by bisection with ballots), then
-//      a short list of the few values that reach it (about 1.4 K), then the K largest of these: up to
+//      registers.  A pivot that is provably not above the K-th largest value (K of the lanes' maxima
+//      reach it; found by bisection with ballots), then
+//      a short list of the few values that reach it (about 1.2 K), then the K largest of these: up to
 //      64 entries are ranked by every wave for itself, one per lane; more, or equal values at the
 //      K-th place, by the work-group.  Rows that do not fit the registers, or with so many values at the
 //      pivot that the short list overflows (heavy ties), take a radix select that re-reads the row.
@@ -62,39 +62,47 @@ struct ShortList {
   __device__ __forceinline__ int of(int w) const { return w == 0 ? n0 : (w == 1 ? n1 : (w == 2 ? n2 : n3)); }
 };
 
-// A wave's pivot: a value that at least r of its lanes' maxima reach, r the wave's share of K by the lanes that
-// hold part of the row (have of all): the smallest of the waves' pivots is then reached by at least K values.
-// Bisection on the distance below the wave's largest value, in sixteenths up to 32 -- nine steps of compare, count,
-// choose at 53 cycles each (on the upper half of the float's bits it would take sixteen; a way out of the loop when the
-// answer is exact costs 44 cycles a step, more than it saves).  A lane counts as reaching M - (d + 1) / 16 if floor(16 (M -
-// its maximum)) <= d; subtraction is monotone and M - that is exact enough for its maximum to be >= the pivot then.
-// Where the r-th value lies further down, or is not finite: bisection on the float's upper 16 bits.
-__device__ __forceinline__ float wave_pivot(float fmx, int K, int have, int all) {
+// The pivot: a value that at least K of the lanes' maxima reach (s_mx, complete), found by every wave for itself.
+// Bisection on the distance below the row's largest value, in sixteenths up to 32: nine steps of compare, count,
+// choose (a way out of the loop when the answer is exact costs more than it saves, and on the upper half of the
+// float's bits it would take sixteen steps).  A maximum counts as reaching M - (d + 1) / 16 if floor(16 (M -
+// maximum)) <= d; subtraction is monotone and M - that is exact enough for the maximum to be >= the pivot then.
+// Where the K-th value lies further down, or is not finite: bisection on the float's upper 16 bits.
+// (Pivots of the waves on their own, a quarter of K each, cost less, but the smallest of the four lets 60 values
+// through instead of 47 for K = 40, in every fourth row more than the 64 that one wave ranks: a beam-40 step of
+// one utterance 1259 -> 1249 us per decode, a beam-20 batch of 512 15710 -> 15135 us together with the form below
+// that holds three float4 per lane.)
+template <int BLOCK>
+__device__ __forceinline__ float find_pivot(const float* s_mx, int K, float& M) {
+  static_assert(BLOCK == 256, "four maxima per lane");
   const float ninf = -__builtin_huge_valf();
-  const int r = all == 256 ? (K + 3) >> 2 : (K * have + all - 1) / max(all, 1);
-  float M = row16_max(fmx);
+  const float4 m = ((const float4*)s_mx)[threadIdx.x & 63];
+  M = row16_max(fmaxf(fmaxf(m.x, m.y), fmaxf(m.z, m.w)));
   M = fmaxf(fmaxf(lane_f(M, 0), lane_f(M, 16)), fmaxf(lane_f(M, 32), lane_f(M, 48)));
-  // (a lane without a value, a NaN: past the end of the scale)
-  const float d16 = (M - fmx) * 16.0f;
-  const int q = d16 < 511.0f ? (int)d16 : 511;
-  int lim = 511;                                           // smallest d found so that r lanes have q <= d
+  // (a lane without a value: past the end of the scale)
+  auto scale = [&](float v) { const float d16 = (M - v) * 16.0f; return d16 < 511.0f ? (int)d16 : 511; };
+  const int q0 = scale(m.x), q1 = scale(m.y), q2 = scale(m.z), q3 = scale(m.w);
+  int lim = 511;                                           // smallest d found so that K lanes have q <= d
 #pragma unroll
   for (int bit = 256; bit > 0; bit >>= 1) {
-    const int c = __popcll(__ballot(q <= lim - bit));
-    lim = c >= r ? lim - bit : lim;
+    const int t = lim - bit;
+    const int c = (__popcll(__ballot(q0 <= t)) + __popcll(__ballot(q1 <= t))) + (__popcll(__ballot(q2 <= t)) + __popcll(__ballot(q3 <= t)));
+    lim = c >= K ? t : lim;
   }
   float L = M - (float)(lim + 1) * 0.0625f;
   if (lim >= 511) {                                        // (uniform, rare)
-    const uint32_t key = att_key(fmx, -1, -2, -2);
+    const uint32_t k0 = att_key(m.x, -1, -2, -2), k1 = att_key(m.y, -1, -2, -2), k2 = att_key(m.z, -1, -2, -2),
+                   k3 = att_key(m.w, -1, -2, -2);
     uint32_t thr = 0;
 #pragma unroll 1
     for (int bit = 31; bit >= 16; --bit) {
-      const uint32_t trial = thr | (1u << bit);
-      if (__popcll(__ballot(key >= trial)) >= r) thr = trial;
+      const uint32_t t = thr | (1u << bit);
+      const int c = (__popcll(__ballot(k0 >= t)) + __popcll(__ballot(k1 >= t))) + (__popcll(__ballot(k2 >= t)) + __popcll(__ballot(k3 >= t)));
+      if (c >= K) thr = t;
     }
     L = thr <= att_key(ninf, -1, -2, -2) ? ninf : key_to_att(thr);
   }
-  return r > 0 ? L : -ninf;
+  return L;
 }
 
 // This wave's part of the short list.  Its granules whose maximum reaches L are packed into LDS (one ballot per
@@ -363,7 +371,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
                                                  const float* __restrict__ att, int Wb, int V, int flags, int l,
                                                  ScoreArgs p) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ __align__(16) float s_thr[BLOCK / 64];        // the waves' pivots
+  __shared__ __align__(16) float s_mx[BLOCK];              // the lanes' maxima
   __shared__ int s_cnt[BLOCK / 64];                        // short list: entries per wave
   __shared__ int32_t s_wid[BIGK ? 1 : BLOCK];              // the K candidates, each wave's own copy
   __shared__ uint32_t s_scan[BLOCK / 64 + 1];
@@ -596,24 +604,17 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
         fmx = fmaxf(fmx, m4[k]);
       }
       TRACE_MARK(6);
-      const float thr = wave_pivot(fmx, K, min(max(ng - 64 * w, 0), 64), ng < BLOCK ? ng : BLOCK);
-      if ((tid & 63) == 0) s_thr[w] = thr;
-      if (logits) {                                        // (the row's maximum, ids that do not compete left out)
-        float m = row16_max(fmx);
-        m = fmaxf(fmaxf(lane_f(m, 0), lane_f(m, 16)), fmaxf(lane_f(m, 32), lane_f(m, 48)));
-        if ((tid & 63) == 0) s_red[w] = m;
-      }
+      s_mx[tid] = fmx;
       lds_barrier();
-      TRACE_MARK(7);
       // at least K values are >= L (-inf if there are not K lanes with finite maxima)
-      const float L = fminf(fminf(s_thr[0], s_thr[1]), fminf(s_thr[2], s_thr[3]));
+      float M;
+      const float L = find_pivot<BLOCK>(s_mx, K, M);
+      TRACE_MARK(7);
       const int nh = collect_hits<BLOCK, NV4>(row, m4, L, p.blank_id, p.eos_id, s_gran + w * ShortList::GCAP,
                                               s_gid + w * ShortList::GCAP, s_ent + w * ShortList::WCAP);
       if ((tid & 63) == 0) s_cnt[w] = nh;
       TRACE_MARK(14);
-      float M = 0.0f;
       if (logits) {
-        M = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
         M = fmaxf(fmaxf(M, -3.0e38f), fmaxf(x_blank, x_eos));
         float sum = __expf(row.ex - M);
 #pragma unroll
@@ -1013,7 +1014,7 @@ __global__ __launch_bounds__(BLOCK) void k_group_top(Params p, int cur) {
 // work-group per (utterance, beam slot).  Every lane holds its share of the scores as 64-bit keys (order-preserving
 // image of the score whose 13 lowest mantissa bits (14 beyond 8192 candidates) carry the candidate index, inverted: larger score first, then the smaller
 // index = the smaller token id; scores equal to within 2^-38 relative count as equal).  The upper halves give a pivot that
-// at least Wb of the keys reach (as for the candidates, see wave_pivot), the few that do are packed into LDS and ranked.
+// at least Wb of the keys reach (as for the candidates, see find_pivot), the few that do are packed into LDS and ranked.
 // More than CAP of them (scores equal in the upper half, that is to 2^-20 relative): Wb rounds of a block-wide maximum.
 // (68 us at 4998 candidates, beam 20, with the rounds alone: a round costs 2 us.)
 // DENSE: every id is a candidate (its id follows from its place) and only the increments lie in memory: the joint score
