@@ -160,7 +160,7 @@ static int ingest(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens) {
   hipLaunchKernelGGL(k_setup, dim3((U + 255) / 256), dim3(256), 0, st, p, h->d_setup, n_empty);
   HIPCHK(hipGetLastError());
   {
-    const int nvt = (p.V + 255) / 256, ntt = (c.t_max + 5 + 31) / 32;   // stored indices 0 .. t_max + 4
+    const int nvt = (p.V + INGEST_TOK - 1) / INGEST_TOK, ntt = (c.t_max + 5 + 31) / 32;   // stored indices 0 .. t_max + 4
     const int n_tiles = nvt * ntt, per_xcd = (n_tiles + 7) / 8;
     const dim3 tg(8 + 8 * per_xcd, U);           // (the first eight columns: the empty-prefix state, see k_ingest)
     if (p.V % 4 == 0 && ((uintptr_t)d_ctc_logp & 15) == 0)

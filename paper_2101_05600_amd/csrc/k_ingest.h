@@ -106,7 +106,7 @@ __device__ __forceinline__ void init_state(const Params& p, const float* __restr
 
 // CTC log-posteriors [U][t_max][V] (frame-major, as an encoder emits them) -> token-major
 // xT[u][k][t], t = 1..T_u, so that one candidate's frames are contiguous.  A work-group moves a
-// tile of 256 tokens x 32 stored frames through LDS: 1 KB contiguous per frame on the way in
+// tile of 128 tokens x 32 stored frames through LDS: 512 bytes contiguous per frame on the way in
 // (float4 per lane when rows are 16-byte aligned: VEC), whole aligned 128-byte lines per token on
 // the way out (rows of xT start on line boundaries, and the tile is cut in STORED frame indices,
 // which are one more than the 0-based input frame).  Frames at and beyond T_u are never read.
@@ -118,12 +118,21 @@ __device__ __forceinline__ void init_state(const Params& p, const float* __restr
 // fetched into one L2 instead of two, and each XCD streams through its own region of memory.
 // Which eighth an XCD takes rotates with the utterance, so that short utterances (whose last
 // eighths are empty) do not leave the same XCDs idle.
+// Bound by memory (each value read and written once).  Four float4 per lane and 17 KB per work-group keep more
+// work-groups at different points of load and store than eight and 33 KB do: 512 utterances of 250..875 frames, 5000 ids,
+// 2397 -> 2280 us, 5.1 TB/s, where a plain copy of the same form reaches 5.7.  64 tokens or 64 frames per tile
+// are not faster, nor is a bound on the registers.
 // Grid: (8 + 8 * per_xcd, U).  The first column of work-groups sets up the utterances' initial state instead
 // (seven idle columns beside it keep the tiles' order over the XCDs).
+#define INGEST_TOK 128    // tokens of a tile
+
 template <bool VEC>
 __global__ __launch_bounds__(256) void k_ingest(Params p, const float* __restrict__ x, int nvt, int n_tiles,
                                                    int per_xcd) {
-  __shared__ __attribute__((aligned(16))) float tile[32][260];
+  __shared__ __attribute__((aligned(16))) float tile[32][INGEST_TOK + 4];
+  constexpr int N4 = INGEST_TOK / 32;                      // float4 per thread: the tile's 32 frames in this many rounds
+  constexpr int LPF = INGEST_TOK / 4;                      // lanes per frame
+
   const int u = blockIdx.y;
   const int bx = (int)blockIdx.x - 8;
   if (bx < 0) {
@@ -136,14 +145,14 @@ __global__ __launch_bounds__(256) void k_ingest(Params p, const float* __restric
   const int jt = g / nvt, vt = g - jt * nvt;
   const int d0 = jt * 32;                                // first stored frame index of the tile
   if (d0 > T + 4) return;
-  const int v0 = vt * 256;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int v0 = vt * INGEST_TOK;
+  const int lane = threadIdx.x % LPF, w = threadIdx.x / LPF;   // (lane of the frame, frames of a round)
   const float* src = x + (size_t)u * p.t_max * p.V;
-  float4 r[8];
+  float4 r[N4];
   const int v = v0 + 4 * lane;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int tt = d0 - 1 + w * 8 + i;                   // 0-based input frame of stored index tt + 1
+  for (int i = 0; i < N4; ++i) {
+    const int tt = d0 - 1 + w + (256 / LPF) * i;                   // 0-based input frame of stored index tt + 1
     r[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (tt >= 0 && tt < T) {
       const float* row = src + (size_t)tt * p.V + v;
@@ -158,16 +167,16 @@ __global__ __launch_bounds__(256) void k_ingest(Params p, const float* __restric
     }
   }
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < N4; ++i) {
     float4 c;
     c.x = fmaxf(r[i].x, LOG0F); c.y = fmaxf(r[i].y, LOG0F); c.z = fmaxf(r[i].z, LOG0F); c.w = fmaxf(r[i].w, LOG0F);
-    const int t = w * 8 + i;
+    const int t = w + (256 / LPF) * i;
     *(float4*)&tile[t][(4 * lane) ^ (((t >> 3) & 3) << 2)] = c;   // (swizzle: see the reads below)
   }
   __syncthreads();
   float* dst = p.xT + (size_t)u * p.V * p.Tp;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < N4; ++i) {
     const int q = i * 256 + threadIdx.x;
     const int vl = q >> 3, t4 = (q & 7) * 4;             // eight lanes cover one token's 32 frames
     // a wave reads 8 tokens x 8 groups of 4 frames; with rows of 260 floats, frames 8 apart would
