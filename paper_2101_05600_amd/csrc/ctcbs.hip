@@ -473,7 +473,7 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   // faster (measured: U=64 and U=128 at beam 10).  Large batches fill the chip either way and the
   // Wb-fold repeated ranking only costs (U=256 at beam 20: three times slower).
   const bool split = p.U * p.Wb <= CTCBS_SPLIT_GROUPS;
-  const size_t split_lds = (size_t)28 * p.Wb * p.Wb + 64 + 16 + (p.Wb > 12 ? (size_t)12 * p.Wb * p.Wb + 64 : 0);
+  const size_t sel_lds = (size_t)36 * ((p.Wb * p.Wb + 63) & ~63) + 32;
   SelectArgs a;
   const int nxt = h->cur ^ 1;
   a.xT = p.xT; a.Bcum = p.Bcum; a.gn = p.gn[h->cur]; a.gb = p.gb[h->cur]; a.gn_new = p.gn[nxt]; a.gb_new = p.gb[nxt];
@@ -482,17 +482,16 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   a.U = p.U; a.V = p.V; a.Tp = p.Tp; a.blank_id = p.blank_id; a.end_flags = p.end_flags; a.end_m = p.end_m; a.end_c = p.end_c;
   a.end_d = p.end_d; a.win_union = p.win_union; a.win_m2 = p.win_m2; a.err = p.err; a.finished = p.finished;
   a.n_finished = p.n_finished; a.cells = p.cells; a.groups = p.groups; a.union_win = p.union_win; a.trace = p.trace;
+  const int wb_m = (65536 / p.Wb + 1) << 8 | p.Wb;         // (see k_select)
 #define CTCBS_SELECT(K, G, BS, LDS, L)                                                                       \
   hipLaunchKernelGGL(K, G, dim3(BS), LDS, h->stream, (const HypRec*)p.rec[h->cur], p.utt, (const GroupOut*)p.grp, \
-                     (const ListEntry*)p.grp_list, (const UttInfo*)p.uinfo, (int)p.Wb, L, a)
+                     (const ListEntry*)p.grp_list, (const UttInfo*)p.uinfo, wb_m, L, (int)p.U, a)
   if (split) {
     const int sh = p.U >= 8 ? 3 : 0;
-    const dim3 grid(1u << sh, (unsigned)p.Wb + (h->select_wide ? 1 : 0), (unsigned)(p.U + (1 << sh) - 1) >> sh);
-    if (h->select_wide) CTCBS_SELECT((k_select_split<256, true>), grid, 256, split_lds, l | sh << 28);
-    else CTCBS_SELECT((k_select_split<256, false>), grid, 256, split_lds, l | sh << 28);
+    const dim3 grid(1u << sh, (unsigned)p.Wb + 1, (unsigned)(p.U + (1 << sh) - 1) >> sh);
+    if (h->select_wide || p.Wb > 12) CTCBS_SELECT((k_select_split<256>), grid, 256, sel_lds, l | sh << 28);
+    else CTCBS_SELECT((k_select_split<64>), grid, 64, sel_lds, l | sh << 28);
   } else {
-    const int NE = p.Wb * p.Wb;
-    const size_t sel_lds = (size_t)16 * ((NE + 9) & ~1) + (size_t)28 * NE;
     const dim3 grid(p.U);
 #define CTCBS_SELECT_LPS(BS)                                                              \
   do {                                                                                    \

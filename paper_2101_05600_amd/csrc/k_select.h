@@ -30,23 +30,39 @@ __device__ __forceinline__ Aff aff_stage(Aff v) {
 }
 
 struct ArgMax { float v; int t; };
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ ArgMax argmax_stage(ArgMax x) {
-  const float ov = dpp_f<CTRL, ROW_MASK>(-3.0e38f, x.v);
-  const int ot = dpp_i<CTRL, ROW_MASK>(0x7fffffff, x.t);
-  const bool up = ov > x.v || (ov == x.v && ot < x.t);
-  x.v = up ? ov : x.v; x.t = up ? ot : x.t;
-  return x;
+
+// over a row of 16 lanes, result in all of them
+__device__ __forceinline__ int row16_min_i(int v) {
+  v = min(v, dpp_i<0x128, 0xf>(v, v));
+  v = min(v, dpp_i<0x124, 0xf>(v, v));
+  v = min(v, dpp_i<0x122, 0xf>(v, v));
+  v = min(v, dpp_i<0x121, 0xf>(v, v));
+  return v;
 }
-// largest value, earliest frame among equals; result valid in lane 63
-__device__ __forceinline__ ArgMax wave_argmax(ArgMax x) {
-  x = argmax_stage<0x111, 0xf>(x);
-  x = argmax_stage<0x112, 0xf>(x);
-  x = argmax_stage<0x114, 0xf>(x);
-  x = argmax_stage<0x118, 0xf>(x);
-  x = argmax_stage<0x142, 0xa>(x);
-  x = argmax_stage<0x143, 0xc>(x);
-  x.v = lane_f(x.v, 63); x.t = __builtin_amdgcn_readlane(x.t, 63);
+// largest value, earliest frame among equals, over LPS lanes; result in all of them.  The largest value first, then the
+// smallest frame among the lanes that hold it: each step of either is one instruction, which on pairs took nine (the
+// three maxima of a step together: 1.3 -> 0.6 us at a batch of 512).
+template <int LPS>
+__device__ __forceinline__ ArgMax lanes_argmax(ArgMax x) {
+  float m = row16_max(x.v);
+  if (LPS == 64) {                          // (lanes hold ascending frames: the first of them)
+    ArgMax r;
+    r.v = fmaxf(fmaxf(lane_f(m, 0), lane_f(m, 16)), fmaxf(lane_f(m, 32), lane_f(m, 48)));
+    r.t = __builtin_amdgcn_readlane(x.t, __ffsll((long long)__ballot(x.v == r.v)) - 1);
+    return r;
+  }
+  const bool hi = (threadIdx.x & 32) != 0;
+  if (LPS == 32) {
+    const float a = fmaxf(lane_f(m, 0), lane_f(m, 16)), b = fmaxf(lane_f(m, 32), lane_f(m, 48));
+    m = hi ? b : a;
+  }
+  int t = row16_min_i(x.v == m ? x.t : 0x7fffffff);
+  if (LPS == 32) {
+    const int a = min(__builtin_amdgcn_readlane(t, 0), __builtin_amdgcn_readlane(t, 16));
+    const int b = min(__builtin_amdgcn_readlane(t, 32), __builtin_amdgcn_readlane(t, 48));
+    t = hi ? b : a;
+  }
+  x.v = m; x.t = t;
   return x;
 }
 
@@ -65,7 +81,7 @@ __device__ __forceinline__ ArgMax wave_argmax(ArgMax x) {
 // re-based by delta = inc + (B_r - B_r'), r the parent's reference frame and r' = the parent's
 // tau the child's: its values are then near zero around its own tau.  Writes the new state into
 // slot n of the other buffer and returns delta and tau / tau~ (first argmax of the true variables,
-// stored + B_t, from the parent's tau on; the parent's values if nothing is finite), these two in the survivor's last lane.
+// stored + B_t, from the parent's tau on; the parent's values if nothing is finite).
 // Lanes own frames from a multiple of four on, so that state, posteriors and B go as 16-byte accesses; what a float4
 // holds outside the window is written as log0 and never read (the stored range says so).
 struct SurvivorIn {
@@ -85,18 +101,6 @@ __device__ __forceinline__ Aff scan_aff(Aff v) {
   if (LPS >= 64) v = aff_stage<0x143, 0xc>(v);
   return v;
 }
-// largest value, earliest frame among equals; valid in the last of LPS lanes
-template <int LPS>
-__device__ __forceinline__ ArgMax lanes_argmax(ArgMax x) {
-  x = argmax_stage<0x111, 0xf>(x);
-  x = argmax_stage<0x112, 0xf>(x);
-  x = argmax_stage<0x114, 0xf>(x);
-  x = argmax_stage<0x118, 0xf>(x);
-  if (LPS >= 32) x = argmax_stage<0x142, 0xa>(x);
-  if (LPS >= 64) x = argmax_stage<0x143, 0xc>(x);
-  return x;
-}
-
 struct SurvivorLds {                                       // NWV > 1
   Aff tot[2][4];                                           // the waves' composed maps (n, b)
   float last_n, last_b;                                    // the values of the pass's last frame
@@ -170,11 +174,12 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
       if (t - 1 >= rs && t - 1 <= re) f = rep ? gbp : lae(gnp, gbp);
       mn[k].a = v[k] ? x : 0.0f; mn[k].b = v[k] ? f + x : LOG0F;
     }
-    auto run = [&](const Aff (&mp)[FPL], float carry, int which, float& v_in, float (&out)[FPL]) {
-      Aff C = mp[0];
+    // (mp: the frames' maps on entry; composed from the lane's first frame on as soon as they are read, so that the
+    // lane's values then follow from v_in each for itself, not one after the other)
+    auto run = [&](Aff (&mp)[FPL], float carry, int which, float& v_in, float (&out)[FPL]) {
 #pragma unroll
-      for (int k = 1; k < FPL; ++k) C = aff_then(C, mp[k]);
-      const Aff P = scan_aff<LPS>(C);
+      for (int k = 1; k < FPL; ++k) mp[k] = aff_then(mp[k - 1], mp[k]);
+      const Aff P = scan_aff<LPS>(mp[FPL - 1]);
       Aff E;                                               // maps of all earlier lanes
       E.a = dpp_f<0x138, 0xf>(0.0f, P.a); E.b = dpp_f<0x138, 0xf>(LOG0F, P.b);
       if (li == 0) { E.a = 0.0f; E.b = LOG0F; }
@@ -188,9 +193,8 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
         E = aff_then(W, E);
       }
       v_in = lae(E.a + carry, E.b);
-      out[0] = lae(v_in + mp[0].a, mp[0].b);
 #pragma unroll
-      for (int k = 1; k < FPL; ++k) out[k] = lae(out[k - 1] + mp[k].a, mp[k].b);
+      for (int k = 0; k < FPL; ++k) out[k] = lae(v_in + mp[k].a, mp[k].b);
     };
     float n_in, b_in, nv[FPL], bv[FPL];
     run(mn, carry_n, 0, n_in, nv);
@@ -214,8 +218,8 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
       rb[k] = (!v[k] || bv[k] < LOG0_CLASS) ? LOG0F : bv[k] - delta;
       const bool ok = t >= lo;
       const float bt = (float)(Bt[k] - Bnew);
-      const float cn = (ok && rn[k] > LOG0_CLASS) ? rn[k] + bt : LOG0F;
-      const float cb = (ok && rb[k] > LOG0_CLASS) ? rb[k] + bt : LOG0F;
+      // (bt <= 0 from the child's reference frame on: what is log0 stays in its class)
+      const float cn = ok ? rn[k] + bt : LOG0F, cb = ok ? rb[k] + bt : LOG0F;
       if (cn > xn.v) { xn.v = cn; xn.t = t; }              // (strict: the earlier frame keeps a tie)
       if (cb > xb.v) { xb.v = cb; xb.t = t; }
     }
@@ -243,7 +247,7 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
     }
   }
   if (NWV > 1) {
-    if (lane == 63) { sx->best[0][w] = best_n; sx->best[1][w] = best_b; }
+    if (lane == 0) { sx->best[0][w] = best_n; sx->best[1][w] = best_b; }
     lds_barrier();
     best_n = sx->best[0][0]; best_b = sx->best[1][0];      // (waves hold ascending frames within a pass, not across passes)
 #pragma unroll
@@ -350,12 +354,11 @@ __device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u
       if (v[k]) { cgn[t[k]] = rn; cgb[t[k]] = rb; }
       const bool ok = v[k] && t[k] >= lo;
       const float bt = (float)(Bt[k] - Bnew);
-      const float cn = (ok && rn > LOG0_CLASS) ? rn + bt : LOG0F;
-      const float cb = (ok && rb > LOG0_CLASS) ? rb + bt : LOG0F;
+      const float cn = ok ? rn + bt : LOG0F, cb = ok ? rb + bt : LOG0F;   // (bt <= 0, as in `survivor`)
       if (cn > xn.v) { xn.v = cn; xn.t = t[k]; }           // (strict: the earlier frame keeps a tie)
       if (cb > xb.v) { xb.v = cb; xb.t = t[k]; }
     }
-    xn = wave_argmax(xn); xb = wave_argmax(xb);
+    xn = lanes_argmax<64>(xn); xb = lanes_argmax<64>(xb);
     if (xn.v > LOG0_CLASS && xn.v > best_n) { best_n = xn.v; arg_n = xn.t; }
     if (xb.v > LOG0_CLASS && xb.v > best_b) { best_b = xb.v; arg_b = xb.t; }
   }
@@ -363,57 +366,87 @@ __device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u
   bref_out = Bnew;
 }
 
-// How many of the keys s_k2[0 .. 2 * quads) (four per quad, zero padding at the end) exceed `me`,
-// counting every L-th quad from `part` on.  Sixteen keys are fetched before the first is compared, so
-// that the LDS round trips overlap.
-__device__ __forceinline__ int count_greater(const ulonglong2* s_k2, unsigned long long me, int part, int L,
-                                             int quads) {
-  int n = 0, q4 = part;
-  for (; q4 + 3 * L < quads; q4 += 4 * L) {
-    ulonglong2 v[8];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) { v[2 * k] = s_k2[2 * (q4 + k * L)]; v[2 * k + 1] = s_k2[2 * (q4 + k * L) + 1]; }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) n += (int)(v[k].x > me) + (int)(v[k].y > me);
-  }
-  for (; q4 < quads; q4 += L) {
-    const ulonglong2 v = s_k2[2 * q4], v2 = s_k2[2 * q4 + 1];
-    n += (int)(v.x > me) + (int)(v.y > me) + (int)(v2.x > me) + (int)(v2.y > me);
-  }
-  return n;
+// The lists' sort keys: the score as an order-preserving integer whose 10 lowest mantissa bits are replaced by the
+// entry's position i = j * Wb + r (group j's r-th best; earlier position = larger key).  One integer comparison then
+// gives a strict total order: joint score descending and, among scores equal to within 2^-42 relative (far inside the
+// tolerance to which scores are meaningful), parent slot, then token, ascending.  Entries past a list's length: 0.
+__device__ __forceinline__ unsigned long long entry_key(double J, int i, bool in) {
+  const long long b = __double_as_longlong(J);
+  const unsigned long long k = (unsigned long long)(b ^ ((b >> 63) | (long long)0x8000000000000000ull));
+  return ((k & ~1023ull) | (unsigned long long)(1023 - i)) & (in ? ~0ull : 0ull);
+}
+__device__ __forceinline__ int key_entry(unsigned long long key) { return 1023 - (int)(key & 1023ull); }
+
+__device__ __forceinline__ unsigned long long lane_u64(unsigned long long v, int lane) {
+  return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), lane) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
 
-// The lists are sorted, so few of their Wb * Wb entries can reach the new beam.  A lower bound on the
-// Wb-th largest key: the smallest of the first R entries of every non-empty list, R such that those
-// are at least Wb entries (if the lists are too short for that: no bound).  Entries below the bound
-// cannot rank among the first Wb; the others are packed into s_ck (keys) / s_cidx (their entry
-// numbers), followed by zero keys, and only they are ranked against each other: a key carries its
-// entry number, so the rank among them is the rank among all.  s_ck must hold zeros on entry,
-// s_cnt[0..1] zeros and *s_min all ones; both barriers are inside.  Returns how many were packed.
-template <int BLOCK>
-__device__ __forceinline__ int pack_contenders(const unsigned long long* s_key, int NE, int Wb, const int* o_n,
-                                               unsigned long long* s_ck, int* s_cidx, int* s_cnt,
-                                               unsigned long long* s_min) {
-  const int tid = threadIdx.x;
-  int nl = 0;
-#pragma unroll 8
-  for (int j = 0; j < Wb; ++j) nl += (o_n[j] > 0);
-  const int R = nl > 0 ? (Wb + nl - 1) / nl : 0;
-  for (int i = tid; i < NE; i += BLOCK) {
-    const int j = i / Wb, r = i - j * Wb;
-    if (r < R && r < o_n[j]) { atomicMin(s_min, s_key[i]); atomicAdd(&s_cnt[0], 1); }
+// The Wb largest of the lists' entries in order, by one wave.  The lists are sorted, so few of the Wb * Wb entries can
+// be among them: a lower bound on the Wb-th largest is the Wb-th largest of the first two of every list (compared by the
+// upper halves of their keys; no bound if there are fewer), found with one comparison per list entry on values that
+// readlane makes scalar; the entries that reach the bound, about 1.3 Wb, are packed into s_ck ([NP + 4], 16-byte
+// aligned) and ranked in the same way.  put(rank, entry, valid) is called by all lanes together.  Returns how many were
+// packed: at least Wb if there are that many entries at all.  s_key: NP entries, a multiple of 64, zeros behind the lists'.
+// One wave needs no barrier: 100 entries all against all by four waves, keys broadcast from LDS, took 1.3 us, the
+// packing of the entries above the smallest head through atomics and a ranking by the whole work-group 1.9 us (beam 10,
+// 512 utterances) and 2.6 us (beam 20).
+template <class F>
+__device__ __forceinline__ int rank_lists(const unsigned long long* s_key, unsigned long long* s_ck, int NP, int Wb, F&& put) {
+  const int lane = threadIdx.x & 63;
+  // (a lane per entry, list lane / 2; the low six bits make the values unique, below 64: no entry)
+  const bool in2 = (lane >> 1) < Wb && (lane & 1) < Wb;
+  uint32_t hi = (uint32_t)(s_key[min(lane >> 1, Wb - 1) * Wb + min(lane & 1, Wb - 1)] >> 32);
+  LOADED(hi);                                              // (no branch round the load)
+  const uint32_t k1 = in2 ? (hi & ~63u) | (uint32_t)(63 - lane) : 0u;
+  uint32_t bound = 64u;                                    // (an entry's upper half is above that)
+  if (__popcll(__ballot(k1 >= 64u)) >= Wb) {
+    int above = 0;
+#pragma unroll
+    for (int q = 0; q < 64; ++q) {
+      if ((q & 7) == 0 && q >= 2 * Wb) break;              // (uniform)
+      above += (uint32_t)__builtin_amdgcn_readlane((int)k1, q) > k1 ? 1 : 0;
+    }
+    const int at = (__ffsll((long long)__ballot(above == Wb - 1)) - 1) & 63;
+    bound = (uint32_t)__builtin_amdgcn_readlane((int)k1, at) & ~63u;
   }
-  lds_barrier();
-  const unsigned long long bound = s_cnt[0] >= Wb ? *s_min : 0ull;
-  for (int i = tid; i < NE; i += BLOCK) {
-    const unsigned long long k = s_key[i];
-    if (k > 1023ull && k >= bound) {
-      const int pos = atomicAdd(&s_cnt[1], 1);
-      s_ck[pos] = k; s_cidx[pos] = i;
+  int n = 0;
+  unsigned long long next = s_key[lane];
+  for (int i0 = 0; i0 < NP; i0 += 64) {
+    const unsigned long long key = next;
+    next = s_key[min(i0 + 64, NP - 64) + lane];
+    const unsigned long long m = __ballot((uint32_t)(key >> 32) >= bound);
+    if ((uint32_t)(key >> 32) >= bound)
+      s_ck[n + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] = key;
+    n += __popcll(m);
+  }
+  __builtin_amdgcn_wave_barrier();
+  if (n <= 64) {
+    const unsigned long long at = s_ck[lane], me = lane < n ? at : 0ull;
+    int above = 0;
+#pragma unroll
+    for (int q = 0; q < 64; ++q) {
+      if ((q & 7) == 0 && q >= n) break;                   // (uniform)
+      above += lane_u64(me, q) > me ? 1 : 0;
+    }
+    put(above, key_entry(me), lane < n);
+  } else {                                                 // (beams of about 30 and more, scores that agree in 26 bits)
+    const int quads = (n + 3) >> 2;
+    if (lane < 4) s_ck[n + lane] = 0ull;
+    __builtin_amdgcn_wave_barrier();
+    const ulonglong2* s_k2 = (const ulonglong2*)s_ck;
+    for (int e0 = 0; e0 < n; e0 += 64) {
+      const unsigned long long me = e0 + lane < n ? s_ck[e0 + lane] : 0ull;
+      int above = 0;
+#pragma unroll 4
+      for (int q = 0; q < quads; ++q) {
+        const ulonglong2 v = s_k2[2 * q], v2 = s_k2[2 * q + 1];
+        above += (int)(v.x > me) + (int)(v.y > me) + (int)(v2.x > me) + (int)(v2.y > me);
+      }
+      put(above, key_entry(me), e0 + lane < n);
     }
   }
-  lds_barrier();
-  return s_cnt[1];
+  return n;
 }
 
 // Ended set and ENDDETECT of one utterance, by one wave (lane j = old slot j).  `mine`: slot j
@@ -481,29 +514,28 @@ __device__ __forceinline__ bool wave_ended_set(const SelectArgs& p, int Wb, int 
   return fin;
 }
 
-// Wave 0 takes the ended set, the others 64 / LPS new hypotheses each at a time.
-// Dynamic LDS: 16 * ((Wb * Wb + 9) & ~1) + 28 * Wb * Wb bytes (the list entries and the packed contenders).
+// Wave 0 ranks the lists and takes the ended set, the others 64 / LPS new hypotheses each at a time.
+// Wb_m: the beam, in the bits from 8 on 65536 / Wb + 1 (a position i < 1024 is of list (i * that) >> 16).
+// Dynamic LDS: 36 * NP + 32 bytes, NP = Wb * Wb rounded up to whole waves (the list entries and the packed keys).
 template <int BLOCK, int LPS, int FPL>
 __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
                                                   const GroupOut* __restrict__ grp, const ListEntry* __restrict__ grp_list,
-                                                  const UttInfo* __restrict__ uinfo, int Wb, int l, SelectArgs p) {
+                                                  const UttInfo* __restrict__ uinfo, int Wb_m, int l, int U, SelectArgs p) {
   constexpr int NW = BLOCK / 64;
   extern __shared__ __align__(16) unsigned char sel_smem[];
-  const int NE_ = Wb * Wb;
-  const int NK_ = (NE_ + 9) & ~1;                                     // NE + 8 keys, an even count: both key arrays on 16-byte boundaries
-  unsigned long long* s_key = (unsigned long long*)sel_smem;          // [NE + 8]
-  unsigned long long* s_ck = s_key + NK_;                             // [NE + 8] keys of the entries that can reach the new beam
-  double* s_J = (double*)(s_ck + NK_);                                // [NE]
-  int* s_par = (int*)(s_J + NE_);                                     // [NE] each
-  int* s_tok = s_par + NE_;
-  int* s_cidx = s_tok + NE_;
-  float* s_inc = (float*)(s_cidx + NE_);
-  float* s_att = s_inc + NE_;
+  const int Wb = Wb_m & 255, div_m = Wb_m >> 8;
+  const int NE = Wb * Wb;
+  const int NP = (NE + 63) & ~63;
+  unsigned long long* s_key = (unsigned long long*)sel_smem;          // [NP]
+  unsigned long long* s_ck = s_key + NP;                              // [NP + 4] keys of the entries that can reach the new beam
+  double* s_J = (double*)(s_ck + NP + 4);                             // [NP]
+  int* s_tok = (int*)(s_J + NP);                                      // [NP] each
+  float* s_inc = (float*)(s_tok + NP);
+  float* s_att = s_inc + NP;
   __shared__ int s_sel[MAX_BEAM];          // entry index of the new beam's slot n
-  __shared__ int s_cnt[2];
-  __shared__ unsigned long long s_min;
+  __shared__ int s_n;                      // entries ranked
   // old slots' records
-  __shared__ int o_live[MAX_BEAM], o_n[MAX_BEAM], o_stp[MAX_BEAM], o_tau[MAX_BEAM], o_tau_end[MAX_BEAM];
+  __shared__ int o_live[MAX_BEAM], o_stp[MAX_BEAM], o_tau[MAX_BEAM], o_tau_end[MAX_BEAM];
   __shared__ int o_rs[MAX_BEAM], o_re[MAX_BEAM], o_last[MAX_BEAM], o_ws[MAX_BEAM], o_we[MAX_BEAM], o_ref[MAX_BEAM];
   __shared__ long long o_cells[MAX_BEAM];
   __shared__ double o_je[MAX_BEAM], o_hatt[MAX_BEAM], o_off[MAX_BEAM];
@@ -512,84 +544,69 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
   __shared__ float s_delta[MAX_BEAM];                      // by how much each new hypothesis was re-based
   __shared__ double s_bref[MAX_BEAM];                      // B at each new hypothesis's reference frame
 
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6);
   const int u = blockIdx.x;
-  if (p.finished[u]) return;               // outputs of a finished utterance were settled when it finished
   const size_t h0 = (size_t)u * Wb;
   TRACE_POINT(p, (size_t)u * Wb, 8);
 
   // ---- first round of loads: everything that depends on nothing --------------------------------
+  // (loads first, with indices clamped instead of branches, all of their uses behind them)
+  UttState* us = utt + u;
+  const int fs = us->finished_step;
+  const int hj = min(tid, Wb - 1);
+  const HypRec r = rec_now[h0 + hj];
+  const GroupOut g = grp[h0 + hj];
+  const UttInfo ui = uinfo[u];
+  const int T = ui.T, lmax_u = ui.lmax;
+  // utterance state, wave 0: the scalars, lanes m < M the ring entries
+  double st_best = LOG0D, ring_sc = LOG0D;
+  int st_n = 0, st_cnt = 0, ring_tag = -1;
+  if (w == 0) {
+    st_best = us->best_score; st_n = us->n_ended; st_cnt = us->cnt_tau_T;
+    ring_sc = us->ring_score[min(lane, MAX_END_M - 1)]; ring_tag = us->ring_tag[min(lane, MAX_END_M - 1)];
+  }
+  // group lists: entry i = j * Wb + r of this utterance (group j's r-th best; Wb * Wb <= 1024 entries)
+  auto load_entry = [&](int i, ListEntry& le, int& nj) {
+    const int ic = min(i, NE - 1);
+    le = grp_list[h0 * Wb + ic];
+    nj = grp[h0 + ((ic * div_m) >> 16)].n;
+  };
+  auto keep_entry = [&](int i, const ListEntry& le, int nj) {
+    s_tok[i] = le.tok; s_inc[i] = le.inc; s_att[i] = le.att;
+    s_J[i] = le.J;
+    s_key[i] = entry_key(le.J, i, (i < NE) & (i - ((i * div_m) >> 16) * Wb < nj));
+  };
+  ListEntry le;
+  int nj;
+  load_entry(tid, le, nj);
+  // (scalar loads: on their way together and waited for once, beside the vector loads)
+  PIN4(fs, T, lmax_u, p.err);
+  PIN4(p.xT, p.Bcum, p.gn, p.gb);
+  PIN4(p.gn_new, p.gb_new, p.rec_new, p.trie);
+  PIN4(p.out, p.out8, p.trie_stride, p.V);
+  PIN4(p.Tp, p.blank_id, p.end_flags, p.end_m);
+  PIN4(p.end_c, p.end_d, p.win_union, p.win_m2);
+  PIN4(p.finished, p.n_finished, p.cells, p.groups);
+  if (fs != 0 && fs < l) return;           // outputs of a finished utterance were settled when it finished
+  if (64 * w < NP) keep_entry(tid, le, nj);                // (whole waves)
+  for (int i = tid + BLOCK; i < NP; i += BLOCK) { load_entry(i, le, nj); keep_entry(i, le, nj); }
   if (tid < Wb) {
-    const size_t h = h0 + tid;
-    const HypRec r = rec_now[h];
-    const GroupOut g = grp[h];
-    o_live[tid] = r.live; o_n[tid] = g.n; o_stp[tid] = g.stopped;
+    o_live[tid] = r.live; o_stp[tid] = g.stopped;
     o_tau[tid] = r.tau; o_tau_end[tid] = r.tau_end;
     o_rs[tid] = r.rs; o_re[tid] = r.re; o_last[tid] = r.last;
     o_ws[tid] = g.win_s; o_we[tid] = g.win_e; o_ref[tid] = r.ref;
     o_cells[tid] = g.cells;
     o_je[tid] = g.joint_eos; o_hatt[tid] = r.att; o_off[tid] = r.off;
   }
-  const int T = uinfo[u].T;
-  const int lmax_u = uinfo[u].lmax;
-  // utterance state, wave 0: lane 0 the scalars, lanes m < M the ring entries
-  UttState* us = utt + u;
-  double st_best = LOG0D, ring_sc = LOG0D;
-  int st_n = 0, st_cnt = 0, ring_tag = -1;
-  if (w == 0) {
-    if (lane == 0) { st_best = us->best_score; st_n = us->n_ended; st_cnt = us->cnt_tau_T; }
-    if (lane < p.end_m) { ring_sc = us->ring_score[lane]; ring_tag = us->ring_tag[lane]; }
-  }
-  // group lists: entry i = j * Wb + r of this utterance (group j's r-th best; Wb * Wb <= 1024 entries),
-  // each with a 64-bit sort key: the score as an order-preserving integer whose 10 lowest mantissa
-  // bits are replaced by the entry's position (earlier position = larger key).  One integer comparison
-  // then gives a strict total order: joint score descending and, among scores equal to within 2^-42
-  // relative (far inside the tolerance to which scores are meaningful), parent slot, then token,
-  // ascending.  Entries past a list's length and the padding get keys below every score.
-  const int NE = Wb * Wb;
-  for (int i = tid; i < NE + 8; i += BLOCK) {
-    unsigned long long key = 0ull;
-    if (i < NE) {
-      const int j = i / Wb, r = i - j * Wb;
-      const size_t o = h0 * Wb + i;
-      const int nj = grp[h0 + j].n;
-      const ListEntry le = grp_list[o];
-      const double Jv = le.J;
-      s_par[i] = j; s_tok[i] = le.tok; s_inc[i] = le.inc; s_att[i] = le.att;
-      s_J[i] = Jv;
-      const unsigned long long bb = (unsigned long long)__double_as_longlong(Jv);
-      const unsigned long long k = (bb >> 63) ? ~bb : (bb | 0x8000000000000000ull);
-      key = r < nj ? ((k & ~1023ull) | (unsigned long long)(1023 - i)) : (unsigned long long)(1023 - i) >> 1;
-    }
-    s_key[i] = key;
-    s_ck[i] = 0ull;
-  }
   if (tid < MAX_BEAM) s_sel[tid] = -1;
-  if (tid < 2) s_cnt[tid] = 0;
-  if (tid == 2) s_min = ~0ull;
   lds_barrier();
   TRACE_POINT(p, (size_t)u * Wb, 9);
-  int ne = 0;
-#pragma unroll 8
-  for (int j = 0; j < Wb; ++j) ne += o_n[j];
-  // ---- rank the contenders: L lanes per entry, each comparing against every L-th quad of keys ----
-  {
-    const int NC = pack_contenders<BLOCK>(s_key, NE, Wb, o_n, s_ck, s_cidx, s_cnt, &s_min);
-    const int L = NC <= BLOCK / 8 ? 8 : (NC <= BLOCK / 4 ? 4 : (NC <= BLOCK / 2 ? 2 : 1));
-    const int part = tid & (L - 1);
-    const int quads = (NC + 3) >> 2;                       // (zeros follow the packed keys)
-    const ulonglong2* s_k2 = (const ulonglong2*)s_ck;
-    for (int e0 = 0; e0 < NC; e0 += BLOCK / L) {
-      const int e = e0 + tid / L;
-      const unsigned long long me = s_ck[min(e, NC)];
-      int rank = count_greater(s_k2, me, part, L, quads);
-      if (L >= 2) rank += dpp_i<0xB1, 0xf>(0, rank);       // quad_perm [1,0,3,2]
-      if (L >= 4) rank += dpp_i<0x4E, 0xf>(0, rank);       // quad_perm [2,3,0,1]
-      if (L == 8) rank += dpp_i<0x104, 0xf>(0, rank);      // row_shl:4: the first lane of the eight gets the other quad's sum
-      if (part == 0 && e < NC && rank < Wb) s_sel[rank] = s_cidx[e];
-    }
+  if (w == 0) {
+    const int n = rank_lists(s_key, s_ck, NP, Wb, [&](int rank, int e, bool valid) { if (valid && rank < Wb) s_sel[rank] = e; });
+    if (lane == 0) s_n = n;
   }
   lds_barrier();
+  const int ne = s_n;
 
   TRACE_POINT(p, (size_t)u * Wb, 10);
   // ---- ended set, end detection: wave 0, lane j = old slot j ---------------------------------
@@ -616,7 +633,7 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
   for (int n0 = (wu - 1) * PER; n0 >= 0 && n0 < nu; n0 += (NW - 1) * PER) {
     const int n = n0 + lane / LPS;
     const bool active = n < nu;
-    const int e = active ? checked(p, s_sel[n], 0, NE - 1, ERR_LIST_ENTRY) : 0, par = active ? s_par[e] : 0;
+    const int e = active ? checked(p, s_sel[n], 0, NE - 1, ERR_LIST_ENTRY) : 0, par = (e * div_m) >> 16;
     SurvivorIn in;
     in.par = par; in.T = T;
     if (active) {
@@ -642,7 +659,7 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
   for (int n = tid; n < Wb; n += BLOCK) {
     const size_t h = h0 + n;
     if (n < n_new) {
-      const int e = checked(p, s_sel[n], 0, NE - 1, ERR_LIST_ENTRY), par = s_par[e], tok = s_tok[e];
+      const int e = checked(p, s_sel[n], 0, NE - 1, ERR_LIST_ENTRY), par = (e * div_m) >> 16, tok = s_tok[e];
       p.out[h] = par; p.out[UW + h] = tok; out_score[h] = (float)s_J[e];
       p.out8[h] = fin ? 0 : 1;
       p.trie[h] = par; p.trie[p.trie_stride + h] = tok;
@@ -672,153 +689,127 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
 // Split form of the select kernel: one work-group per (utterance, new beam slot n), used
 // whenever no state is shared across utterances (per-hypothesis windows).  Every work-group of
 // an utterance ranks the utterance's Wb * Wb list entries itself (the lists are small, the
-// ranking is cheaper than a second launch), wave 0 then evaluates the forward variables of
-// new hypothesis n and writes its record; in the work-group of slot 0, wave 1 meanwhile
+// ranking is cheaper than a second launch), evaluates the forward variables of
+// new hypothesis n and writes its record; the work-group of slot number Wb meanwhile
 // updates the ended set, runs ENDDETECT and writes what belongs to the utterance as a whole
 // (finished flag, live flags of all slots, the per-old-slot outputs, work counters).  The
 // survivors of one utterance so run on Wb compute units instead of sharing one.
 // Within a launch the work-groups of an utterance only read what the others do not write:
-// the utterance state is read by slot 0's work-group alone, and "finished before this step"
+// the utterance state is read by the last slot's work-group alone, and "finished before this step"
 // is taken from the step number at which the utterance finished (0 or the current step both
 // mean no).
-// WIDE: windows beyond 128 frames are common (the host knows from the window margins).  All waves of a work-group then
-// share the recurrence of such a window, and what belongs to the utterance as a whole is done by a work-group of its
-// own, slot number Wb.
-// Dynamic LDS: 28 * Wb * Wb + 64 bytes (the list entries), for beams above 12 another 12 * Wb * Wb + 80 (the packed
-// contenders: with 400 entries, all against all took 7 us).
+// One wave does all of it (BLOCK = 64), with no barrier to wait at.  Where windows beyond 128 frames are common (the
+// host knows from the window margins), and for beams above 12, whose lists are long to load, it is four: all of them
+// load, the first one ranks, and all share the recurrence of a window of more than 128 frames.
+// Dynamic LDS: 36 * NP + 32 bytes, NP = Wb * Wb rounded up to whole waves (the list entries and the packed keys).
 // The arguments in front of the block are what the first round of loads needs: plain leading arguments reach the wave
 // in registers when it starts (kernel-argument preload), so that those loads do not wait for a load of the arguments.
 // Grid: (1 << sh, Wb, ceil(U / (1 << sh))), sh = l >> 28: utterance z * 2^sh + x, new slot y (as in k_score).
-template <int BLOCK, bool WIDE>
+template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
                                                         const GroupOut* __restrict__ grp, const ListEntry* __restrict__ grp_list,
-                                                        const UttInfo* __restrict__ uinfo, int Wb, int l_sh, SelectArgs p) {
-  static_assert(BLOCK >= 128, "wave 0 and wave 1 have different jobs");
+                                                        const UttInfo* __restrict__ uinfo, int Wb_m, int l_sh, int U, SelectArgs p) {
+  constexpr bool WIDE = BLOCK > 64;
   extern __shared__ __align__(16) unsigned char split_smem[];
+  const int Wb = Wb_m & 255, div_m = Wb_m >> 8;                       // (see k_select)
   const int NE = Wb * Wb;
-  unsigned long long* s_key = (unsigned long long*)split_smem;        // [NE + 8]
-  double* s_J = (double*)(s_key + NE + 8);                            // [NE]
-  int* s_tok = (int*)(s_J + NE);                                      // [NE]
-  float* s_inc = (float*)(s_tok + NE);                                // [NE]
-  float* s_att = s_inc + NE;                                          // [NE]
-  unsigned long long* s_ck = (unsigned long long*)(split_smem + ((28 * (size_t)NE + 64 + 15) & ~(size_t)15));   // [NE + 8] (Wb > 12)
-  int* s_cidx = (int*)(s_ck + NE + 8);                                // [NE]
+  const int NP = (NE + 63) & ~63;
+  unsigned long long* s_key = (unsigned long long*)split_smem;        // [NP]
+  unsigned long long* s_ck = s_key + NP;                              // [NP + 4]
+  double* s_J = (double*)(s_ck + NP + 4);                             // [NP]
+  int* s_tok = (int*)(s_J + NP);                                      // [NP] each
+  float* s_inc = (float*)(s_tok + NP);
+  float* s_att = s_inc + NP;
   __shared__ SurvivorLds s_sx;
-  __shared__ int s_cnt[2];
-  __shared__ unsigned long long s_min;
-  const bool pack = Wb > 12;
-  __shared__ int o_live[MAX_BEAM], o_n[MAX_BEAM], o_stp[MAX_BEAM], o_tau[MAX_BEAM];
+  __shared__ int o_live[MAX_BEAM], o_stp[MAX_BEAM], o_tau[MAX_BEAM];
   __shared__ int o_par[MAX_BEAM][8];       // what a survivor needs of its parent: window, range, tau, tau~, last label, reference frame
   __shared__ long long o_cells[MAX_BEAM];
   __shared__ double o_je[MAX_BEAM], o_hatt[MAX_BEAM], o_off[MAX_BEAM];
-  __shared__ int s_pick[2];                // entry ranked n, entry ranked 0
+  __shared__ int s_pick[3];                // entry ranked n, entry ranked 0, number of entries ranked
 
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = BLOCK == 64 ? 0 : uni(tid >> 6);
   const int l = l_sh & 0xfffffff, sh = l_sh >> 28;
   const int u = (int)((blockIdx.z << sh) + blockIdx.x), n = (int)blockIdx.y;
-  if (u >= p.U) return;                    // (the grid is whole eights of utterances)
+  if (u >= U) return;                    // (the grid is whole eights of utterances)
   UttState* us = utt + u;
   const int fs = us->finished_step;        // (tested after the first round of loads is on its way)
   const size_t h0 = (size_t)u * Wb;
-  const bool lead = (n == (WIDE ? Wb : 0));
+  const bool lead = n == Wb;
   if (lead) TRACE_POINT(p, (size_t)u * Wb, 8);
 
   // ---- first round of loads: everything that depends on nothing --------------------------------
+  // (as in k_select)
+  const int hj = min(tid, Wb - 1);
+  const HypRec r = rec_now[h0 + hj];
+  const GroupOut g = grp[h0 + hj];
+  constexpr int CH = BLOCK == 64 ? 3 : 1024 / BLOCK;       // (NE <= 144 for one wave)
+  ListEntry le[CH];
+  int nj[CH];
+#pragma unroll
+  for (int k = 0; k < CH; ++k) {
+    const int i = min(tid + k * BLOCK, NE - 1);
+    if (BLOCK == 64 || k == 0 || k * BLOCK < NE) { le[k] = grp_list[h0 * Wb + i]; nj[k] = grp[h0 + ((i * div_m) >> 16)].n; }
+  }
+  const UttInfo ui = uinfo[u];
+  const int T = ui.T, lmax_u = ui.lmax;
+  double st_best = LOG0D, ring_sc = LOG0D;
+  int st_n = 0, st_cnt = 0, ring_tag = -1;
+  if (lead && w == 0) {
+    st_best = us->best_score; st_n = us->n_ended; st_cnt = us->cnt_tau_T;
+    ring_sc = us->ring_score[min(lane, MAX_END_M - 1)]; ring_tag = us->ring_tag[min(lane, MAX_END_M - 1)];
+  }
+  // (scalar loads: on their way together and waited for once, beside the vector loads)
+  PIN4(fs, T, lmax_u, p.err);
+  PIN4(p.xT, p.Bcum, p.gn, p.gb);
+  PIN4(p.gn_new, p.gb_new, p.rec_new, p.trie);
+  PIN4(p.out, p.out8, p.trie_stride, p.V);
+  PIN4(p.Tp, p.blank_id, p.end_flags, p.end_m);
+  PIN4(p.end_c, p.end_d, p.win_union, p.win_m2);
+  PIN4(p.finished, p.n_finished, p.cells, p.groups);
+#pragma unroll
+  for (int k = 0; k < CH; ++k) {
+    const int i = tid + k * BLOCK;
+    if (k * BLOCK + 64 * w < NP) {         // (whole waves)
+      s_tok[i] = le[k].tok; s_inc[i] = le[k].inc; s_att[i] = le[k].att;
+      s_J[i] = le[k].J;
+      s_key[i] = entry_key(le[k].J, i, (i < NE) & (i - ((i * div_m) >> 16) * Wb < nj[k]));
+    }
+  }
   if (tid < Wb) {
-    const size_t h = h0 + tid;
-    const HypRec r = rec_now[h];
-    const GroupOut g = grp[h];
-    o_live[tid] = r.live; o_n[tid] = g.n; o_stp[tid] = g.stopped;
+    o_live[tid] = r.live; o_stp[tid] = g.stopped;
     o_tau[tid] = r.tau;
     o_par[tid][0] = g.win_s; o_par[tid][1] = g.win_e; o_par[tid][2] = r.rs; o_par[tid][3] = r.re;
     o_par[tid][4] = r.tau; o_par[tid][5] = r.tau_end; o_par[tid][6] = r.last; o_par[tid][7] = r.ref;
     o_cells[tid] = g.cells;
     o_je[tid] = g.joint_eos; o_hatt[tid] = r.att; o_off[tid] = r.off;
   }
-  const int T = uinfo[u].T;
-  const int lmax_u = uinfo[u].lmax;
-  double st_best = LOG0D, ring_sc = LOG0D;
-  int st_n = 0, st_cnt = 0, ring_tag = -1;
-  const int lead_w = WIDE ? 0 : 1;        // the wave for the utterance as a whole
-  if (lead && w == lead_w) {
-    if (lane == 0) { st_best = us->best_score; st_n = us->n_ended; st_cnt = us->cnt_tau_T; }
-    if (lane < p.end_m) { ring_sc = us->ring_score[lane]; ring_tag = us->ring_tag[lane]; }
-  }
-  // list entries i = j * Wb + r (group j's r-th best), each with a 64-bit sort key: the score as
-  // an order-preserving integer whose 10 lowest mantissa bits are replaced by the entry's
-  // position (earlier position = larger key).  One integer comparison then gives a strict total
-  // order: joint score descending, and among scores equal to within 2^-42 relative (far inside
-  // the tolerance to which scores are meaningful) parent slot, then token, ascending.  Entries
-  // past a list's length and the padding get keys below every score.
-  for (int i = tid; i < NE + 8; i += BLOCK) {
-    unsigned long long key = 0ull;
-    if (i < NE) {
-      const int j = i / Wb, r = i - j * Wb;
-      const size_t o = h0 * Wb + i;
-      const int nj = grp[h0 + j].n;
-      const ListEntry le = grp_list[o];
-      const double Jv = le.J;
-      s_tok[i] = le.tok; s_inc[i] = le.inc; s_att[i] = le.att;
-      s_J[i] = Jv;
-      const unsigned long long b = (unsigned long long)__double_as_longlong(Jv);
-      const unsigned long long k = (b >> 63) ? ~b : (b | 0x8000000000000000ull);
-      key = r < nj ? ((k & ~1023ull) | (unsigned long long)(1023 - i)) : (unsigned long long)(1023 - i) >> 1;
-    }
-    s_key[i] = key;
-    if (pack) s_ck[i] = 0ull;
-  }
-  if (tid < 2) { s_pick[tid] = -1; s_cnt[tid] = 0; }
-  if (tid == 2) s_min = ~0ull;
   if (fs != 0 && fs < l) return;           // outputs of a finished utterance were settled when it finished
   lds_barrier();
   if (lead) TRACE_POINT(p, (size_t)u * Wb, 9);
 
-  // ---- rank (total order: joint desc, parent slot asc, token asc = position asc) -------------
-  // L lanes per entry, each comparing against every L-th pair of the list
-  int ne = 0;
-#pragma unroll 8
-  for (int j = 0; j < Wb; ++j) ne += o_n[j];
-  const int n_new = min(ne, Wb);
-  if (pack) {
-    const int NC = uni(pack_contenders<BLOCK>(s_key, NE, Wb, o_n, s_ck, s_cidx, s_cnt, &s_min));
-    const int L = NC <= BLOCK / 8 ? 8 : (NC <= BLOCK / 4 ? 4 : (NC <= BLOCK / 2 ? 2 : 1));
-    const int part = tid & (L - 1), quads = (NC + 3) >> 2;   // (zeros follow the packed keys)
-    for (int e0 = 0; e0 < NC; e0 += BLOCK / L) {
-      const int e = e0 + tid / L;
-      int rank = count_greater((const ulonglong2*)s_ck, s_ck[min(e, NC)], part, L, quads);
-      if (L >= 2) rank += dpp_i<0xB1, 0xf>(0, rank);       // quad_perm [1,0,3,2]
-      if (L >= 4) rank += dpp_i<0x4E, 0xf>(0, rank);       // quad_perm [2,3,0,1]
-      if (L == 8) rank += dpp_i<0x104, 0xf>(0, rank);      // row_shl:4
-      if (part == 0 && e < NC) {
-        if (rank == n) s_pick[0] = s_cidx[e];
-        if (rank == 0) s_pick[1] = s_cidx[e];
-      }
-    }
-  } else {
-    // (all entries against all: packing the contenders first costs two barriers more than it saves at these sizes)
-    const int L = NE <= 64 ? 4 : (NE <= 128 ? 2 : 1);
-    const int part = tid & (L - 1);
-    const int quads = (NE + 3) >> 2;                       // (the padding holds zeros)
-    const ulonglong2* s_k2 = (const ulonglong2*)s_key;
-    for (int e0 = 0; e0 < NE; e0 += BLOCK / L) {
-      const int e = e0 + tid / L;
-      const unsigned long long me = s_key[min(e, NE)];
-      int rank = count_greater(s_k2, me, part, L, quads);
-      if (L >= 2) rank += dpp_i<0xB1, 0xf>(0, rank);       // quad_perm [1,0,3,2]
-      if (L == 4) rank += dpp_i<0x4E, 0xf>(0, rank);       // quad_perm [2,3,0,1]
-      if (part == 0 && e < NE && me > 1023ull) {
-        if (rank == n) s_pick[0] = e;
-        if (rank == 0) s_pick[1] = e;
-      }
-    }
+  int pick_n = -1, pick_0 = -1, ne = 0;                    // entry ranked n, entry ranked 0 (all scalar)
+  if (w == 0) {
+    ne = rank_lists(s_key, s_ck, NP, Wb, [&](int rank, int e, bool) {   // (ranks below ne are of entries)
+      const unsigned long long mn = __ballot(rank == n), m0 = __ballot(rank == 0);
+      const int en = __builtin_amdgcn_readlane(e, (__ffsll((long long)mn) - 1) & 63), e0 = __builtin_amdgcn_readlane(e, (__ffsll((long long)m0) - 1) & 63);
+      pick_n = mn != 0ull ? en : pick_n;
+      pick_0 = m0 != 0ull ? e0 : pick_0;
+    });
+    if (WIDE && lane == 0) { s_pick[0] = pick_n; s_pick[1] = pick_0; s_pick[2] = ne; }
   }
-  lds_barrier();
+  if (WIDE) {
+    lds_barrier();
+    pick_n = uni(s_pick[0]); pick_0 = uni(s_pick[1]); ne = uni(s_pick[2]);
+  }
+  const int n_new = min(ne, Wb);
   if (lead) TRACE_POINT(p, (size_t)u * Wb, 10);
 
   const size_t UW = (size_t)p.U * Wb;
   float* out_score = (float*)(p.out + 2 * UW);
   const bool hyp = n < Wb && n < n_new;
-  const int e_n = hyp ? uni(checked(p, s_pick[0], 0, NE - 1, ERR_LIST_ENTRY)) : 0, par = e_n / Wb;
+  int bad = 0;
+  const int e_n = clamped(hyp ? pick_n : 0, 0, NE - 1, ERR_LIST_ENTRY, bad), par = (e_n * div_m) >> 16;
+  report(p, bad);
   // (a lane each, then into scalar registers: the recurrence below then runs on scalar bases and bounds)
   const int pv = o_par[par][lane & 7];
   const int par_s = __builtin_amdgcn_readlane(pv, 0), par_e = __builtin_amdgcn_readlane(pv, 1);
@@ -837,7 +828,7 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
       int arg_n, arg_b;
       float delta;
       double bref;
-      if (shared) survivor<64, 4, BLOCK / 64>(p, Wb, u, n, true, in, &s_sx, arg_n, arg_b, delta, bref);
+      if (WIDE && shared) survivor<64, 4, BLOCK / 64>(p, Wb, u, n, true, in, &s_sx, arg_n, arg_b, delta, bref);
       else wave_survivor(p, Wb, u, n, in, arg_n, arg_b, delta, bref);
       if (tid == 0) {
         p.out[3 * UW + h] = arg_n; p.out[4 * UW + h] = arg_b;
@@ -862,10 +853,10 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
       p.out[3 * UW + h] = 0; p.out[4 * UW + h] = 0;
       p.trie[h] = -1; p.trie[p.trie_stride + h] = -1; p.trie[(size_t)2 * p.trie_stride + h] = 0;
     }
-  } else if (lead && w == lead_w) {
+  } else if (lead && w == 0) {
     // ---- the utterance as a whole: ended set, end detection, live flags ----------------------
     const bool has_best = ne > 0;
-    const double best = has_best ? s_J[checked(p, s_pick[1], 0, NE - 1, ERR_LIST_ENTRY)] : LOG0D;
+    const double best = has_best ? s_J[checked(p, pick_0, 0, NE - 1, ERR_LIST_ENTRY)] : LOG0D;
     const int j = lane < Wb ? lane : 0;
     const bool mine = lane < Wb && o_live[j];
     const bool fin = wave_ended_set(p, Wb, u, us, l, T, lmax_u, has_best, best, n_new, mine, o_je[j], o_stp[j], o_tau[j],
