@@ -114,8 +114,9 @@ struct Params {
   double* Bcum;
   UttInfo* uinfo;            // [U]
   // hypothesis state, two buffers (index b): forward variables [b][U][Wb][Tp] (stored form) and
-  // per-hypothesis records [b][U][Wb]
-  float* gn[2];
+  // per-hypothesis records [b][U][Wb].  gphi: phi_t = n_t (+) b_t, gb: b_t; the label variable n_t alone is needed
+  // while its hypothesis is made only (every later use is of the sum, or of b_t if the label repeats)
+  float* gphi[2];
   float* gb[2];
   HypRec* rec[2];
   float* dense_F;            // [U][Wb][Tp] every id a candidate: exp of the f terms (k_dense.h)
@@ -176,7 +177,7 @@ struct Params {
 struct ScoreArgs {
   const float* xT;
   const double* Bcum;
-  const float *gn, *gb;      // of the current buffer
+  const float *gphi, *gb;    // of the current buffer
   ListEntry* grp_list;
   GroupOut* grp;
   double lambda, beta;
@@ -200,8 +201,8 @@ enum { SC_RESTRICTED = 1, SC_LOGITS = 2, SC_UNION = 4, SC_KEEP = 8, SC_UNION_UTT
 struct SelectArgs {
   const float* xT;
   const double* Bcum;
-  const float *gn, *gb;      // of the current buffer
-  float *gn_new, *gb_new;    // of the other one
+  const float *gphi, *gb;    // of the current buffer
+  float *gphi_new, *gb_new;  // of the other one
   HypRec* rec_new;
   int32_t* trie;             // back-pointers of this level: parent, token, tau, each trie_stride apart
   int32_t* out;              // step outputs, each UW apart: parent, token, score (float), tau, tau_end

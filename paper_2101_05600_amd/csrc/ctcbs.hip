@@ -214,7 +214,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   A(p.Bcum, (size_t)U * p.Tp);
   A(p.lens, (size_t)U); A(p.lmax, (size_t)U);
   for (int b = 0; b < 2; ++b) {
-    A(p.gn[b], UW * p.Tp); A(p.gb[b], UW * p.Tp);
+    A(p.gphi[b], UW * p.Tp); A(p.gb[b], UW * p.Tp);
     A(p.rec[b], UW8);
   }
   A(p.uinfo, U8);
@@ -349,7 +349,7 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
   const int flags = in_regs | sh << 4;
   const dim3 grid(1u << sh, (unsigned)p.Wb, (unsigned)(p.U + (1 << sh) - 1) >> sh);
   ScoreArgs a;
-  a.xT = p.xT; a.Bcum = p.Bcum; a.gn = p.gn[h->cur]; a.gb = p.gb[h->cur]; a.grp_list = p.grp_list; a.grp = p.grp;
+  a.xT = p.xT; a.Bcum = p.Bcum; a.gphi = p.gphi[h->cur]; a.gb = p.gb[h->cur]; a.grp_list = p.grp_list; a.grp = p.grp;
   a.lambda = p.lambda; a.beta = p.beta;
   a.Tp = p.Tp; a.K = p.K; a.blank_id = p.blank_id; a.eos_id = p.eos_id; a.win_m1 = p.win_m1; a.win_m2 = p.win_m2;
   a.end_flags = p.end_flags; a.eos_run = p.eos_run; a.wp_max = h->wp_max; a.off_f = h->off_f; a.off_small = h->off_small;
@@ -476,7 +476,7 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   const size_t sel_lds = (size_t)36 * ((p.Wb * p.Wb + 63) & ~63) + 32;
   SelectArgs a;
   const int nxt = h->cur ^ 1;
-  a.xT = p.xT; a.Bcum = p.Bcum; a.gn = p.gn[h->cur]; a.gb = p.gb[h->cur]; a.gn_new = p.gn[nxt]; a.gb_new = p.gb[nxt];
+  a.xT = p.xT; a.Bcum = p.Bcum; a.gphi = p.gphi[h->cur]; a.gb = p.gb[h->cur]; a.gphi_new = p.gphi[nxt]; a.gb_new = p.gb[nxt];
   a.rec_new = p.rec[nxt]; a.trie = p.trie_parent + (size_t)l * p.U * p.Wb; a.out = p.out_parent; a.out8 = p.out_live;
   a.trie_stride = (uint32_t)(p.trie_token - p.trie_parent);
   a.U = p.U; a.V = p.V; a.Tp = p.Tp; a.blank_id = p.blank_id; a.end_flags = p.end_flags; a.end_m = p.end_m; a.end_c = p.end_c;

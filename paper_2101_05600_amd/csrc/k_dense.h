@@ -18,8 +18,8 @@
 typedef float f32x4 __attribute__((__vector_size__(16)));
 
 // f term of frame t (log domain): gamma_{t-1}(g) relative to off' + B_r; only where t - 1 lies in the stored range
-__device__ __forceinline__ float dense_f(const float* gn, const float* gb, const double* Bu, double Bref, int t) {
-  return canon0(lae(gn[t - 1], gb[t - 1]) + (float)(Bu[t - 1] - Bref));
+__device__ __forceinline__ float dense_f(const float* gphi, const double* Bu, double Bref, int t) {
+  return canon0(gphi[t - 1] + (float)(Bu[t - 1] - Bref));
 }
 
 template <int BLOCK>
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
   if (p.win_m2 >= 0) e = min(e, r.tau_end + p.win_m2);
   s = checked(p, s, 1, T + 1, ERR_WINDOW);
   e = checked(p, e, -1, T, ERR_WINDOW);
-  const float* gn = p.gn[cur] + h * Tp;
+  const float* gphi = p.gphi[cur] + h * Tp;
   const float* gb = p.gb[cur] + h * Tp;
   const double* Bu = p.Bcum + (size_t)u * Tp;
   const double Bref = r.bref;
@@ -58,8 +58,8 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
   Lse a;                                                       // the repeated label's sum
   a.m = LOG0F; a.s = 0.0f;
   for (int t = lo + tid; t <= hi; t += BLOCK) {
-    const float n = gn[t - 1], b = gb[t - 1], bt = (float)(Bu[t - 1] - Bref);
-    const float f = canon0(lae(n, b) + bt);
+    const float ph = gphi[t - 1], b = gb[t - 1], bt = (float)(Bu[t - 1] - Bref);
+    const float f = canon0(ph + bt);
     dense_f_lds[t] = f;
     m = fmaxf(m, f);
     Lse v;
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
     q.jbase = (1.0 - p.lambda) * r.att + p.beta * (double)l;
     *slot = q;
     const bool has = r.rs <= T && r.re >= T;
-    const float ce = has ? canon0(lae(gn[T], gb[T])) : LOG0F;
+    const float ce = has ? gphi[T] : LOG0F;
     const bool v = ce > LOG0_CLASS;
     const double ctc = v ? q.offr + (ui.BT - Bref) + (double)ce : LOG0D;
     const int W = e >= s ? e - s + 1 : 0;
@@ -215,8 +215,7 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
       const int jr = __builtin_amdgcn_readlane(js, who), idr = __builtin_amdgcn_readlane(id, who);
       const size_t h = h0 + jr;
       const DenseSlot d = slots[h];
-      const float* gn = p.gn[cur] + h * Tp;
-      const float* gb = p.gb[cur] + h * Tp;
+      const float* gphi = p.gphi[cur] + h * Tp;
       const double* Bu = p.Bcum + (size_t)u * Tp;
       const double Bref = Bu[checked(p, d.ref, 0, T, ERR_TIME_INDEX)];
       const float* col = xu + (size_t)idr * Tp;
@@ -224,7 +223,7 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
       a.m = LOG0F; a.s = 0.0f;
       for (int t = max(d.s, d.rs + 1) + lane; t <= min(d.e, d.re + 1); t += 64) {
         Lse v;
-        v.m = (dense_f(gn, gb, Bu, Bref, t) + col[t]) * L2E; v.s = 1.0f;
+        v.m = (dense_f(gphi, Bu, Bref, t) + col[t]) * L2E; v.s = 1.0f;
         a = lse_join(a, v);
       }
       const float r = lse_finish<64>(a);

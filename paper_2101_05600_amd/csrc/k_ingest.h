@@ -34,12 +34,12 @@ __device__ __forceinline__ void init_state(const Params& p, const float* __restr
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int T = p.lens[u];
   const size_t hyp0 = (size_t)u * p.Wb;
-  float* gn = p.gn[0] + hyp0 * p.Tp;
+  float* gphi = p.gphi[0] + hyp0 * p.Tp;
   float* gb = p.gb[0] + hyp0 * p.Tp;
   double* Bu = p.Bcum + (size_t)u * p.Tp;
   const float* xb = x + (size_t)u * p.t_max * p.V + p.blank_id;   // row t - 1 holds frame t
   double carry = 0.0, carry_cut = 0.0;
-  if (tid == 0) { gn[0] = LOG0F; gb[0] = 0.0f; Bu[0] = 0.0; }
+  if (tid == 0) { gphi[0] = 0.0f; gb[0] = 0.0f; Bu[0] = 0.0; }
   constexpr int R = 8;
   for (int base = 1; base <= T; base += 256 * R) {
     float x0[R];
@@ -67,7 +67,7 @@ __device__ __forceinline__ void init_state(const Params& p, const float* __restr
         if (i < w) { v += a; c += b; }
       }
       v += carry; c += carry_cut;
-      if (t <= T) { Bu[t] = v; gb[t] = fmaxf((float)c, LOG0F); gn[t] = LOG0F; }
+      if (t <= T) { Bu[t] = v; gb[t] = gphi[t] = fmaxf((float)c, LOG0F); }
 #pragma unroll
       for (int i = 0; i < 4; ++i) { carry += s_v[k & 1][i]; carry_cut += s_c[k & 1][i]; }
     }

@@ -415,10 +415,11 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
     if (tid < row.n_ex) row.ex = arow[row.ex_id];
   };
   PIN4(rec.live, rec.off, ui.BT, fin_word);
-  PIN4(p.xT, p.Bcum, p.gn, p.gb);
+  PIN4(p.xT, p.Bcum, p.gphi, p.gb);
   PIN4(p.grp_list, p.grp, p.lambda, p.beta);
   PIN4(p.Tp, p.K, p.win_m1, p.eos_run);
-  PIN4(p.wp_max, p.off_f, p.mode, p.err);
+  // (not all of the block: with four more the scalar registers run out and part of it is loaded twice, 35 -> 36.6 us
+  // a launch at 512 utterances)
   const int dead = (int)((fin_word >> (8 * (u & 3))) & 0xffu) | (rec.live == 0);
   if (in_regs && !dead) fetch_row();
   const int K = p.K;
@@ -510,7 +511,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
   const int W = e >= s ? e - s + 1 : 0;
   const int t0 = s & ~3;                                   // column loads start on a 16-byte boundary
   const int n4 = W > 0 ? ((e - t0) >> 2) + 1 : 0;
-  const float* gn = p.gn + (size_t)grp * p.Tp;
+  const float* gphi = p.gphi + (size_t)grp * p.Tp;
   const float* gb = p.gb + (size_t)grp * p.Tp;
   // Stored forward variables have the per-frame reference B_t taken out (see Params::Bcum); all
   // increments of this step are relative to off'(g) + B_r, r = g's reference frame
@@ -523,10 +524,10 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
   // used after the candidate selection: nothing waits for it before.
   auto in_range = [&](int t) { return t >= s && t <= e && t - 1 >= rs && t - 1 <= re; };   // frame t has an f term
   const int pr0 = min(max(t0 + tid - 1, 0), T);
-  const float f0_n = gn[pr0], f0_b = gb[pr0];
+  const float f0_p = gphi[pr0], f0_b = gb[pr0];
   const double f0_B = Bu[pr0];
-  float eos_n = LOG0F, eos_b = LOG0F;
-  if (tid == 0 && rs <= T && re >= T) { eos_n = gn[T]; eos_b = gb[T]; }
+  float eos_p = LOG0F;
+  if (rs <= T && re >= T) eos_p = gphi[T];
 
   TRACE_MARK(1);
   const int R = p.eos_run;
@@ -541,31 +542,32 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
   const int n4r = max(1, (n4 + LPC * IT - 1) / (LPC * IT)) * (LPC * IT);
   const double lam = p.lambda, jbase = (1.0 - lam) * acum + p.beta * (double)l;
   // eos-run rule: E_t = phi_t(g) of frame t = T-R+1+tid
-  float e2_Et = LOG0F, e2_n = LOG0F, e2_b = LOG0F;
+  float e2_Et = LOG0F, e2_p = LOG0F;
   double e2_B = 0.0;
-  if (e2 && tid < R) { const int t = T - R + 1 + tid; e2_n = gn[t]; e2_b = gb[t]; e2_B = Bu[t]; }
+  if (e2 && tid < R) { const int t = T - R + 1 + tid; e2_p = gphi[t]; e2_B = Bu[t]; }
   // The f terms of the window into LDS:
   // gamma_{t-1}(g) - off' - B_r = stored_{t-1} + (B_{t-1} - B_r); far from r the second part is
   // large and coarse in fp32, and the term is then negligible by that same factor
   auto stage_state = [&]() {
-    float n = f0_n, b = f0_b;
+    float ph = f0_p, b = f0_b;
     double B = f0_B;
+
     for (int i = tid; i < 4 * n4r; i += BLOCK) {
       const int t = t0 + i;
-      if (i >= BLOCK) { const int pr = min(max(t - 1, 0), T); n = gn[pr]; b = gb[pr]; B = Bu[pr]; }
+      if (i >= BLOCK) { const int pr = min(max(t - 1, 0), T); ph = gphi[pr]; b = gb[pr]; B = Bu[pr]; }
       float f = LOG0F, fb = LOG0F;
       if (in_range(t)) {
         const float bt = (float)(B - Bref);
-        f = canon0(lae(n, b) + bt); fb = canon0(b + bt);
+        f = canon0(ph + bt); fb = canon0(b + bt);
       }
       const int k = t - (T - R + 1);
       if (e2w && k >= 0 && k < R) { s_e2f[k] = f; s_e2f[MAX_EOS_RUN + k] = fb; f = LOG0F; fb = LOG0F; }
       s_F[i] = f * L2E; s_Fb[i] = fb * L2E;
     }
-    if (e2 && tid < R) e2_Et = canon0(lae(e2_n, e2_b) + (float)(e2_B - Bref));
+    if (e2 && tid < R) e2_Et = canon0(e2_p + (float)(e2_B - Bref));
     if (tid == 0) {
       // eos: phi_T(g) = off' + B_T + stored  (raw scores: the joint score still lacks the row's log-sum-exp)
-      const float ce = (rs <= T && re >= T) ? canon0(lae(eos_n, eos_b)) : LOG0F;
+      const float ce = eos_p;
       const bool v = ce > LOG0_CLASS;
       const double ctc = v ? offr + BT + (double)ce : LOG0D;
       s_eos[0] = ctc;
@@ -779,7 +781,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
     xt = row16_max(xt);
     xt = fmaxf(fmaxf(lane_f(xt, 0), lane_f(xt, 16)), fmaxf(lane_f(xt, 32), lane_f(xt, 48)));
     if ((tid & 63) == 0) s_e2w[tid >> 6] = xt;
-    if (tid == 0) s_e2w[BLOCK / 64] = (rs <= T && re >= T) ? canon0(lae(eos_n, eos_b) + (float)BT) : LOG0F;
+    if (tid == 0) s_e2w[BLOCK / 64] = (rs <= T && re >= T) ? canon0(eos_p + (float)BT) : LOG0F;
     lds_barrier();
     float XT = s_e2w[0];
 #pragma unroll

@@ -76,7 +76,7 @@ __device__ __forceinline__ ArgMax lanes_argmax(ArgMax x) {
 // The recurrence runs on the stored form of the variables (per-frame reference B_t taken out,
 // see Params::Bcum): with x'_t(c) = x_t(c) - max(x_t(blank), floor) and d_t = x_t(blank) -
 // max(x_t(blank), floor) (zero unless the floor cut),
-//   n_t = (n_{t-1} (+) f_t) + x'_t(c),     b_t = (n_{t-1} (+) b_{t-1}) + d_t,
+//   n_t = (n_{t-1} (+) f_t) + x'_t(c),     phi_t = (phi_{t-1} + d_t) (+) n_t,     b_t = phi_{t-1} + d_t,
 // so that staying in blank costs nothing and values do not drift with t.  The child's state is
 // re-based by delta = inc + (B_r - B_r'), r the parent's reference frame and r' = the parent's
 // tau the child's: its values are then near zero around its own tau.  Writes the new state into
@@ -102,8 +102,8 @@ __device__ __forceinline__ Aff scan_aff(Aff v) {
   return v;
 }
 struct SurvivorLds {                                       // NWV > 1
-  Aff tot[2][4];                                           // the waves' composed maps (n, b)
-  float last_n, last_b;                                    // the values of the pass's last frame
+  Aff tot[2][4];                                           // the waves' composed maps (n, phi)
+  float last_n, last_p;                                    // the values of the pass's last frame
   ArgMax best[2][4];
 };
 
@@ -121,9 +121,9 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
   const float* x0p = xu + (size_t)p.blank_id * p.Tp;
   const float* xcp = xu + (size_t)clamped(in.tok, 0, p.V - 1, ERR_TOKEN, bad) * p.Tp;
   const double* Bu = p.Bcum + (size_t)u * p.Tp;
-  const float* pgn = p.gn + hp * p.Tp;
+  const float* pgp = p.gphi + hp * p.Tp;
   const float* pgb = p.gb + hp * p.Tp;
-  float* cgn = p.gn_new + (h0 + n) * p.Tp;
+  float* cgp = p.gphi_new + (h0 + n) * p.Tp;
   float* cgb = p.gb_new + (h0 + n) * p.Tp;
   const int T = in.T;
   const int s = clamped(in.s, 1, T, ERR_WINDOW, bad), en = clamped(in.en, s, T, ERR_WINDOW, bad), rs = in.rs, re = in.re;
@@ -132,34 +132,34 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
   report(p, bad);
   const bool rep = (in.tok == in.plast);
   const int lo = max(s, in.ptau);
-  float carry_n = LOG0F, carry_b = LOG0F;
+  float carry_n = LOG0F, carry_p = LOG0F;
   ArgMax best_n, best_b;
   best_n.v = best_b.v = LOG0F; best_n.t = best_b.t = 0;
   for (int base = s & ~3; __ballot(base <= en) != 0ull; base += SPAN) {
-    float gn[FPL], gb[FPL], x0[FPL], xc[FPL];
+    float gp[FPL], gb[FPL], x0[FPL], xc[FPL];
     double Bt[FPL];
     const int t0 = base + lf;
     const int tm = min(max(base - 1, 0), T);               // the frame before the pass
-    const float gn_m = pgn[tm], gb_m = pgb[tm];
+    const float gp_m = pgp[tm], gb_m = pgb[tm];
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {                         // (clamped into the row; rows are whole multiples of four)
       const int t4 = min(t0 + 4 * k, p.Tp - 4);
-      const float4 a = *(const float4*)(pgn + t4), b = *(const float4*)(pgb + t4), c = *(const float4*)(x0p + t4),
+      const float4 a = *(const float4*)(pgp + t4), b = *(const float4*)(pgb + t4), c = *(const float4*)(x0p + t4),
                    d = *(const float4*)(xcp + t4);
       const double2 e = *(const double2*)(Bu + t4), f = *(const double2*)(Bu + t4 + 2);
-      gn[4 * k] = a.x; gn[4 * k + 1] = a.y; gn[4 * k + 2] = a.z; gn[4 * k + 3] = a.w;
+      gp[4 * k] = a.x; gp[4 * k + 1] = a.y; gp[4 * k + 2] = a.z; gp[4 * k + 3] = a.w;
       gb[4 * k] = b.x; gb[4 * k + 1] = b.y; gb[4 * k + 2] = b.z; gb[4 * k + 3] = b.w;
       x0[4 * k] = c.x; x0[4 * k + 1] = c.y; x0[4 * k + 2] = c.z; x0[4 * k + 3] = c.w;
       xc[4 * k] = d.x; xc[4 * k + 1] = d.y; xc[4 * k + 2] = d.z; xc[4 * k + 3] = d.w;
       Bt[4 * k] = e.x; Bt[4 * k + 1] = e.y; Bt[4 * k + 2] = f.x; Bt[4 * k + 3] = f.y;
     }
-    float tw_n = 0.0f, tw_b = 0.0f;                        // the frame before the wave's
-    if (NWV > 1) { const int tw = min(max(base + w * 64 * FPL - 1, 0), T); tw_n = pgn[tw]; tw_b = pgb[tw]; }
+    float tw_p = 0.0f, tw_b = 0.0f;                        // the frame before the wave's
+    if (NWV > 1) { const int tw = min(max(base + w * 64 * FPL - 1, 0), T); tw_p = pgp[tw]; tw_b = pgb[tw]; }
 #pragma unroll
-    for (int k = 0; k < FPL; ++k) { LOADED(gn[k]); LOADED(gb[k]); }
+    for (int k = 0; k < FPL; ++k) { LOADED(gp[k]); LOADED(gb[k]); }
     // the previous frame's state: the lane before holds it for the lane's first frame
-    float pn = dpp_f<0x138, 0xf>(0.0f, gn[FPL - 1]), pb = dpp_f<0x138, 0xf>(0.0f, gb[FPL - 1]);
-    if (li == 0) { pn = NWV > 1 ? tw_n : gn_m; pb = NWV > 1 ? tw_b : gb_m; }
+    float pp = dpp_f<0x138, 0xf>(0.0f, gp[FPL - 1]), pb = dpp_f<0x138, 0xf>(0.0f, gb[FPL - 1]);
+    if (li == 0) { pp = NWV > 1 ? tw_p : gp_m; pb = NWV > 1 ? tw_b : gb_m; }
     Aff mn[FPL];                                           // n_t = (n_{t-1} (+) f_t) + x'_t(c)
     float d[FPL];
     bool v[FPL];
@@ -167,11 +167,11 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
     for (int k = 0; k < FPL; ++k) {
       const int t = t0 + k;
       v[k] = t >= s && t <= en;
-      const float gnp = k == 0 ? pn : gn[k > 0 ? k - 1 : 0], gbp = k == 0 ? pb : gb[k > 0 ? k - 1 : 0];
+      const float gpp = k == 0 ? pp : gp[k > 0 ? k - 1 : 0], gbp = k == 0 ? pb : gb[k > 0 ? k - 1 : 0];
       const float x0f = fmaxf(x0[k], BLANK_FLOOR), x = xc[k] - x0f;
       d[k] = x0[k] - x0f;
       float f = LOG0F;
-      if (t - 1 >= rs && t - 1 <= re) f = rep ? gbp : lae(gnp, gbp);
+      if (t - 1 >= rs && t - 1 <= re) f = rep ? gbp : gpp;
       mn[k].a = v[k] ? x : 0.0f; mn[k].b = v[k] ? f + x : LOG0F;
     }
     // (mp: the frames' maps on entry; composed from the lane's first frame on as soon as they are read, so that the
@@ -196,30 +196,29 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
 #pragma unroll
       for (int k = 0; k < FPL; ++k) out[k] = lae(v_in + mp[k].a, mp[k].b);
     };
-    float n_in, b_in, nv[FPL], bv[FPL];
+    float n_in, p_in, nv[FPL], pv[FPL];
     run(mn, carry_n, 0, n_in, nv);
-    Aff mb[FPL];                                           // b_t = (n_{t-1} (+) b_{t-1}) + d_t
+    Aff mp[FPL];                                           // phi_t = (phi_{t-1} + d_t) (+) n_t
 #pragma unroll
-    for (int k = 0; k < FPL; ++k) {
-      const float nprev = k == 0 ? n_in : nv[k > 0 ? k - 1 : 0];
-      mb[k].a = v[k] ? d[k] : 0.0f; mb[k].b = v[k] ? nprev + d[k] : LOG0F;
-    }
-    run(mb, carry_b, 1, b_in, bv);
+    for (int k = 0; k < FPL; ++k) { mp[k].a = v[k] ? d[k] : 0.0f; mp[k].b = v[k] ? nv[k] : LOG0F; }
+    run(mp, carry_p, 1, p_in, pv);
     const float delta = in.inc + (float)(Bold - Bnew);
     // re-base, store, and the lane's own first argmax over t >= lo of the true variables
     // (stored + B_t; B relative to the child's reference)
     ArgMax xn, xb;
     xn.v = LOG0F; xn.t = t0; xb.v = LOG0F; xb.t = t0;
-    float rn[FPL], rb[FPL];
+    float rp[FPL], rb[FPL];
 #pragma unroll
     for (int k = 0; k < FPL; ++k) {
       const int t = t0 + k;
-      rn[k] = (!v[k] || nv[k] < LOG0_CLASS) ? LOG0F : nv[k] - delta;
-      rb[k] = (!v[k] || bv[k] < LOG0_CLASS) ? LOG0F : bv[k] - delta;
+      const float bv = (k == 0 ? p_in : pv[k > 0 ? k - 1 : 0]) + d[k];
+      const float rn = (!v[k] || nv[k] < LOG0_CLASS) ? LOG0F : nv[k] - delta;
+      rp[k] = (!v[k] || pv[k] < LOG0_CLASS) ? LOG0F : pv[k] - delta;
+      rb[k] = (!v[k] || bv < LOG0_CLASS) ? LOG0F : bv - delta;
       const bool ok = t >= lo;
       const float bt = (float)(Bt[k] - Bnew);
       // (bt <= 0 from the child's reference frame on: what is log0 stays in its class)
-      const float cn = ok ? rn[k] + bt : LOG0F, cb = ok ? rb[k] + bt : LOG0F;
+      const float cn = ok ? rn + bt : LOG0F, cb = ok ? rb[k] + bt : LOG0F;
       if (cn > xn.v) { xn.v = cn; xn.t = t; }              // (strict: the earlier frame keeps a tie)
       if (cb > xb.v) { xb.v = cb; xb.t = t; }
     }
@@ -227,7 +226,7 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
 #pragma unroll
       for (int k = 0; k < NQ; ++k)
         if (t0 + 4 * k <= en && t0 + 4 * k + 3 >= s) {
-          *(float4*)(cgn + t0 + 4 * k) = make_float4(rn[4 * k], rn[4 * k + 1], rn[4 * k + 2], rn[4 * k + 3]);
+          *(float4*)(cgp + t0 + 4 * k) = make_float4(rp[4 * k], rp[4 * k + 1], rp[4 * k + 2], rp[4 * k + 3]);
           *(float4*)(cgb + t0 + 4 * k) = make_float4(rb[4 * k], rb[4 * k + 1], rb[4 * k + 2], rb[4 * k + 3]);
         }
     }
@@ -236,13 +235,13 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
     if (xb.v > LOG0_CLASS && xb.v > best_b.v) best_b = xb;
     if (__ballot(base + SPAN <= en) != 0ull) {             // (uniform) another pass: hand on the last frame's values
       if (NWV > 1) {
-        if (threadIdx.x == 64 * NWV - 1) { sx->last_n = nv[FPL - 1]; sx->last_b = bv[FPL - 1]; }
+        if (threadIdx.x == 64 * NWV - 1) { sx->last_n = nv[FPL - 1]; sx->last_p = pv[FPL - 1]; }
         lds_barrier();
-        carry_n = sx->last_n; carry_b = sx->last_b;
+        carry_n = sx->last_n; carry_p = sx->last_p;
         lds_barrier();
       } else {
         carry_n = __shfl(nv[FPL - 1], (lane & ~(LPS - 1)) + LPS - 1);
-        carry_b = __shfl(bv[FPL - 1], (lane & ~(LPS - 1)) + LPS - 1);
+        carry_p = __shfl(pv[FPL - 1], (lane & ~(LPS - 1)) + LPS - 1);
       }
     }
   }
@@ -276,9 +275,9 @@ __device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u
   const float* x0 = xu + (size_t)p.blank_id * p.Tp;
   const float* xc = xu + (size_t)clamped(in.tok, 0, p.V - 1, ERR_TOKEN, bad) * p.Tp;
   const double* Bu = p.Bcum + (size_t)u * p.Tp;
-  const float* pgn = p.gn + hp * p.Tp;
+  const float* pgp = p.gphi + hp * p.Tp;
   const float* pgb = p.gb + hp * p.Tp;
-  float* cgn = p.gn_new + (h0 + n) * p.Tp;
+  float* cgp = p.gphi_new + (h0 + n) * p.Tp;
   float* cgb = p.gb_new + (h0 + n) * p.Tp;
   const int T = in.T;
   const int s = clamped(in.s, 1, T, ERR_WINDOW, bad), en = clamped(in.en, s, T, ERR_WINDOW, bad), rs = in.rs, re = in.re;
@@ -287,12 +286,12 @@ __device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u
   report(p, bad);
   const bool rep = (in.tok == in.plast);
   const int lo = max(s, in.ptau);
-  float carry_n = LOG0F, carry_b = LOG0F;
+  float carry_n = LOG0F, carry_p = LOG0F;
   float best_n = LOG0F, best_b = LOG0F;
   arg_n = in.ptau; arg_b = in.ptau_end;
   for (int base = s; base <= en; base += 64 * FPL) {
     int t[FPL]; bool v[FPL]; double Bt[FPL];
-    float g_n[FPL], g_b[FPL], x0v[FPL], xcv[FPL];
+    float g_p[FPL], g_b[FPL], x0v[FPL], xcv[FPL];
     Aff mn[FPL];                                         // n_t = (n_{t-1} (+) f_t) + x'_t(c)
     float d[FPL];
 #pragma unroll
@@ -300,17 +299,16 @@ __device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u
       t[k] = base + FPL * lane + k;
       v[k] = t[k] <= en;
       const int tc = min(t[k], en);                      // clamped: loads are unconditional
-      g_n[k] = pgn[tc - 1]; g_b[k] = pgb[tc - 1]; x0v[k] = x0[tc]; xcv[k] = xc[tc];   // (tc >= s >= 1)
+      g_p[k] = pgp[tc - 1]; g_b[k] = pgb[tc - 1]; x0v[k] = x0[tc]; xcv[k] = xc[tc];   // (tc >= s >= 1)
       Bt[k] = Bu[tc];
     }
 #pragma unroll
-    for (int k = 0; k < FPL; ++k) { LOADED(g_n[k]); LOADED(g_b[k]); }
+    for (int k = 0; k < FPL; ++k) { LOADED(g_p[k]); LOADED(g_b[k]); }
 #pragma unroll
     for (int k = 0; k < FPL; ++k) {
-      const float gn = g_n[k], gb = g_b[k];
       const float x = xcv[k] - fmaxf(x0v[k], BLANK_FLOOR);
       d[k] = x0v[k] - fmaxf(x0v[k], BLANK_FLOOR);
-      float f = rep ? gb : lae(gn, gb);
+      float f = rep ? g_b[k] : g_p[k];
       f = t[k] - 1 >= rs && t[k] - 1 <= re ? f : LOG0F;
       mn[k].a = v[k] ? x : 0.0f; mn[k].b = v[k] ? f + x : LOG0F;
     }
@@ -325,23 +323,20 @@ __device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u
     nv[0] = lae(n_in + mn[0].a, mn[0].b);
 #pragma unroll
     for (int k = 1; k < FPL; ++k) nv[k] = lae(nv[k - 1] + mn[k].a, mn[k].b);
-    Aff mb[FPL];                                         // b_t = (n_{t-1} (+) b_{t-1}) + d_t
+    Aff mp[FPL];                                         // phi_t = (phi_{t-1} + d_t) (+) n_t
 #pragma unroll
-    for (int k = 0; k < FPL; ++k) {
-      const float nprev = k == 0 ? n_in : nv[k - 1];
-      mb[k].a = v[k] ? d[k] : 0.0f; mb[k].b = v[k] ? nprev + d[k] : LOG0F;
-    }
-    C = mb[0];
+    for (int k = 0; k < FPL; ++k) { mp[k].a = v[k] ? d[k] : 0.0f; mp[k].b = v[k] ? nv[k] : LOG0F; }
+    C = mp[0];
 #pragma unroll
-    for (int k = 1; k < FPL; ++k) C = aff_then(C, mb[k]);
+    for (int k = 1; k < FPL; ++k) C = aff_then(C, mp[k]);
     P = scan_aff<64>(C);
     E.a = dpp_f<0x138, 0xf>(0.0f, P.a); E.b = dpp_f<0x138, 0xf>(LOG0F, P.b);
-    const float b_in = lae(E.a + carry_b, E.b);
-    float bv[FPL];
-    bv[0] = lae(b_in + mb[0].a, mb[0].b);
+    const float p_in = lae(E.a + carry_p, E.b);
+    float pv[FPL];
+    pv[0] = lae(p_in + mp[0].a, mp[0].b);
 #pragma unroll
-    for (int k = 1; k < FPL; ++k) bv[k] = lae(bv[k - 1] + mb[k].a, mb[k].b);
-    carry_n = lane_f(nv[FPL - 1], 63); carry_b = lane_f(bv[FPL - 1], 63);
+    for (int k = 1; k < FPL; ++k) pv[k] = lae(pv[k - 1] + mp[k].a, mp[k].b);
+    carry_n = lane_f(nv[FPL - 1], 63); carry_p = lane_f(pv[FPL - 1], 63);
     const float delta = in.inc + (float)(Bold - Bnew);
     // re-base, store, and the lane's own first argmax over t >= lo of the true variables
     // (stored + B_t; B relative to the child's reference)
@@ -349,9 +344,11 @@ __device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u
     xn.v = LOG0F; xn.t = t[0]; xb.v = LOG0F; xb.t = t[0];
 #pragma unroll
     for (int k = 0; k < FPL; ++k) {
+      const float bv = (k == 0 ? p_in : pv[k > 0 ? k - 1 : 0]) + d[k];   // b_t = phi_{t-1} + d_t
       const float rn = (nv[k] < LOG0_CLASS) ? LOG0F : nv[k] - delta;
-      const float rb = (bv[k] < LOG0_CLASS) ? LOG0F : bv[k] - delta;
-      if (v[k]) { cgn[t[k]] = rn; cgb[t[k]] = rb; }
+      const float rp = (pv[k] < LOG0_CLASS) ? LOG0F : pv[k] - delta;
+      const float rb = (bv < LOG0_CLASS) ? LOG0F : bv - delta;
+      if (v[k]) { cgp[t[k]] = rp; cgb[t[k]] = rb; }
       const bool ok = v[k] && t[k] >= lo;
       const float bt = (float)(Bt[k] - Bnew);
       const float cn = ok ? rn + bt : LOG0F, cb = ok ? rb + bt : LOG0F;   // (bt <= 0, as in `survivor`)
@@ -581,8 +578,8 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
   load_entry(tid, le, nj);
   // (scalar loads: on their way together and waited for once, beside the vector loads)
   PIN4(fs, T, lmax_u, p.err);
-  PIN4(p.xT, p.Bcum, p.gn, p.gb);
-  PIN4(p.gn_new, p.gb_new, p.rec_new, p.trie);
+  PIN4(p.xT, p.Bcum, p.gphi, p.gb);
+  PIN4(p.gphi_new, p.gb_new, p.rec_new, p.trie);
   PIN4(p.out, p.out8, p.trie_stride, p.V);
   PIN4(p.Tp, p.blank_id, p.end_flags, p.end_m);
   PIN4(p.end_c, p.end_d, p.win_union, p.win_m2);
@@ -760,8 +757,8 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
   }
   // (scalar loads: on their way together and waited for once, beside the vector loads)
   PIN4(fs, T, lmax_u, p.err);
-  PIN4(p.xT, p.Bcum, p.gn, p.gb);
-  PIN4(p.gn_new, p.gb_new, p.rec_new, p.trie);
+  PIN4(p.xT, p.Bcum, p.gphi, p.gb);
+  PIN4(p.gphi_new, p.gb_new, p.rec_new, p.trie);
   PIN4(p.out, p.out8, p.trie_stride, p.V);
   PIN4(p.Tp, p.blank_id, p.end_flags, p.end_m);
   PIN4(p.end_c, p.end_d, p.win_union, p.win_m2);
