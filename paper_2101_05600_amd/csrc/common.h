@@ -317,6 +317,61 @@ __device__ __forceinline__ float lane_f(float v, int lane) {
 // a value that all lanes of the wave hold alike, into a scalar register: the compiler cannot know it of what comes
 // from LDS or from a wave's number, and without it loops and choices on such values run on vector registers with lane masks
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// n += how many of the values v of lanes I .. I + 3 exceed the lane's own.  A value that one instruction puts into a scalar
+// register can be read by the second next at the earliest; left to itself the compiler waits out that distance after
+// every readlane and every comparison when scalar registers are scarce, 20 cycles a value instead of 13.
+template <int I>
+__device__ __forceinline__ void above4(uint32_t v, int& n) {
+#if defined(__AMDGCN__)
+  __asm__("v_readlane_b32 vcc_lo, %1, %2\n\tv_readlane_b32 s40, %1, %3\n\t"
+          "v_readlane_b32 s42, %1, %4\n\tv_readlane_b32 s44, %1, %5\n\t"
+          "v_cmp_gt_u32_e64 vcc, vcc_lo, %1\n\tv_cmp_gt_u32_e64 s[40:41], s40, %1\n\t"
+          "v_cmp_gt_u32_e64 s[42:43], s42, %1\n\tv_cmp_gt_u32_e64 s[44:45], s44, %1\n\t"
+          "v_addc_co_u32_e64 %0, vcc, 0, %0, vcc\n\tv_addc_co_u32_e64 %0, s[40:41], 0, %0, s[40:41]\n\t"
+          "v_addc_co_u32_e64 %0, s[42:43], 0, %0, s[42:43]\n\tv_addc_co_u32_e64 %0, s[44:45], 0, %0, s[44:45]"
+          : "+v"(n) : "v"(v), "i"(I), "i"(I + 1), "i"(I + 2), "i"(I + 3)
+          : "vcc", "s40", "s41", "s42", "s43", "s44", "s45");
+#else
+  for (int k = 0; k < 4; ++k) n += (uint32_t)__builtin_amdgcn_readlane((int)v, I + k) > v ? 1 : 0;
+#endif
+}
+template <int I>
+__device__ __forceinline__ void above4(unsigned long long v, int& n) {
+#if defined(__AMDGCN__)
+  const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+  __asm__("v_readlane_b32 vcc_lo, %2, %4\n\tv_readlane_b32 vcc_hi, %3, %4\n\t"
+          "v_readlane_b32 s40, %2, %5\n\tv_readlane_b32 s41, %3, %5\n\t"
+          "v_readlane_b32 s42, %2, %6\n\tv_readlane_b32 s43, %3, %6\n\t"
+          "v_readlane_b32 s44, %2, %7\n\tv_readlane_b32 s45, %3, %7\n\t"
+          "v_cmp_gt_u64_e64 vcc, vcc, %1\n\tv_cmp_gt_u64_e64 s[40:41], s[40:41], %1\n\t"
+          "v_cmp_gt_u64_e64 s[42:43], s[42:43], %1\n\tv_cmp_gt_u64_e64 s[44:45], s[44:45], %1\n\t"
+          "v_addc_co_u32_e64 %0, vcc, 0, %0, vcc\n\tv_addc_co_u32_e64 %0, s[40:41], 0, %0, s[40:41]\n\t"
+          "v_addc_co_u32_e64 %0, s[42:43], 0, %0, s[42:43]\n\tv_addc_co_u32_e64 %0, s[44:45], 0, %0, s[44:45]"
+          : "+v"(n) : "v"(v), "v"(lo), "v"(hi), "i"(I), "i"(I + 1), "i"(I + 2), "i"(I + 3)
+          : "vcc", "s40", "s41", "s42", "s43", "s44", "s45");
+#else
+  for (int k = 0; k < 4; ++k) {
+    const unsigned long long o = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), I + k) << 32) |
+                                 (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, I + k);
+    n += o > v ? 1 : 0;
+  }
+#endif
+}
+// the same over the first `count` lanes (uniform, up to STEP - 1 more are counted: they hold values below every other).
+// (A readlane must not follow the instruction that wrote its register at once.)
+template <int STEP, class V>
+__device__ __forceinline__ int lanes_above(V v, int count) {
+  int n = 0;
+#if defined(__AMDGCN__)
+  __asm__ volatile("s_nop 1" : "+v"(v));
+#endif
+#define ABOVE_STEP(I)                                            \
+  if ((I) % STEP == 0 && (I) >= count) return n;                 \
+  above4<(I)>(v, n); above4<(I) + 4>(v, n);
+  ABOVE_STEP(0) ABOVE_STEP(8) ABOVE_STEP(16) ABOVE_STEP(24) ABOVE_STEP(32) ABOVE_STEP(40) ABOVE_STEP(48) ABOVE_STEP(56)
+#undef ABOVE_STEP
+  return n;
+}
 // inclusive prefix sum over the 64 lanes
 __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t x, int /*lane*/) {
   int v = (int)x;

@@ -157,14 +157,7 @@ __device__ __forceinline__ int collect_hits(const RowRegs<NV4>& r, const float (
 __device__ __forceinline__ bool take_k(const unsigned long long* s_ent, const ShortList& sl, int K, int32_t* ids, float* s_av) {
   const int lane = threadIdx.x & 63;
   const unsigned long long me = s_ent[sl.at(min(lane, sl.n - 1))];
-  const int key = lane < sl.n ? (int)((uint32_t)(me >> 32) ^ 0x80000000u) : (int)0x80000000;   // (as a signed number)
-  int rank = 0;
-#pragma unroll
-  for (int e = 0; e < 64; e += 16) {                       // (lanes past the last entry hold the smallest number)
-    if (e >= sl.n) break;                                  // (constant lane numbers: three instructions an entry)
-#pragma unroll
-    for (int k = 0; k < 16; ++k) rank += (int)(__builtin_amdgcn_readlane(key, e + k) > key);
-  }
+  const int rank = lanes_above<16>(lane < sl.n ? (uint32_t)(me >> 32) : 0u, sl.n);   // (constant lane numbers: three instructions an entry)
   const bool take = lane < sl.n && rank < K;
   if (__popcll(__ballot(take)) != K) return false;         // (equal values have equal ranks)
   const int pos = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(__ballot(take) >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)__ballot(take), 0u));
@@ -906,18 +899,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
       const double ctc = valid ? offr + (double)inc : LOG0D;
       const double J = valid ? lam * ctc + (1.0 - lam) * (double)av + jbase : LOG0D;
       const unsigned long long me = has ? joint_key(J, id & 0xFFFF, valid && J == J) : 0ull;
-      const int me_lo = (int)(uint32_t)me, me_hi = (int)(uint32_t)(me >> 32);
-      int rank = 0;
-#pragma unroll
-      for (int c = 0; c < 64; c += 16) {                   // (lanes past the last entry hold zeros)
-        if (c >= K) break;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          const unsigned long long o = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane(me_hi, c + k) << 32) |
-                                       (uint32_t)__builtin_amdgcn_readlane(me_lo, c + k);
-          rank += (int)(o > me);
-        }
-      }
+      const int rank = lanes_above<16>(me, K);             // (lanes past the last entry hold zeros)
       const int nv = __popcll(__ballot(me != 0ull));
       if (!fire && me != 0ull && rank < Wb) p.grp_list[(size_t)grp * Wb + rank] = ListEntry{J, id, inc, av, 0};
       if (tid == 0) group_outputs(fire ? 0 : min(nv, Wb));

@@ -374,11 +374,6 @@ __device__ __forceinline__ unsigned long long entry_key(double J, int i, bool in
 }
 __device__ __forceinline__ int key_entry(unsigned long long key) { return 1023 - (int)(key & 1023ull); }
 
-__device__ __forceinline__ unsigned long long lane_u64(unsigned long long v, int lane) {
-  return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), lane) << 32) |
-         (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
-}
-
 // The Wb largest of the lists' entries in order, by one wave.  The lists are sorted, so few of the Wb * Wb entries can
 // be among them: a lower bound on the Wb-th largest is the Wb-th largest of the first two of every list (compared by the
 // upper halves of their keys; no bound if there are fewer), found with one comparison per list entry on values that
@@ -398,12 +393,7 @@ __device__ __forceinline__ int rank_lists(const unsigned long long* s_key, unsig
   const uint32_t k1 = in2 ? (hi & ~63u) | (uint32_t)(63 - lane) : 0u;
   uint32_t bound = 64u;                                    // (an entry's upper half is above that)
   if (__popcll(__ballot(k1 >= 64u)) >= Wb) {
-    int above = 0;
-#pragma unroll
-    for (int q = 0; q < 64; ++q) {
-      if ((q & 7) == 0 && q >= 2 * Wb) break;              // (uniform)
-      above += (uint32_t)__builtin_amdgcn_readlane((int)k1, q) > k1 ? 1 : 0;
-    }
+    const int above = lanes_above<8>(k1, 2 * Wb);
     const int at = (__ffsll((long long)__ballot(above == Wb - 1)) - 1) & 63;
     bound = (uint32_t)__builtin_amdgcn_readlane((int)k1, at) & ~63u;
   }
@@ -420,12 +410,7 @@ __device__ __forceinline__ int rank_lists(const unsigned long long* s_key, unsig
   __builtin_amdgcn_wave_barrier();
   if (n <= 64) {
     const unsigned long long at = s_ck[lane], me = lane < n ? at : 0ull;
-    int above = 0;
-#pragma unroll
-    for (int q = 0; q < 64; ++q) {
-      if ((q & 7) == 0 && q >= n) break;                   // (uniform)
-      above += lane_u64(me, q) > me ? 1 : 0;
-    }
+    const int above = lanes_above<8>(me, n);
     put(above, key_entry(me), lane < n);
   } else {                                                 // (beams of about 30 and more, scores that agree in 26 bits)
     const int quads = (n + 3) >> 2;
