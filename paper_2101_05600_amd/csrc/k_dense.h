@@ -63,15 +63,12 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
     dense_f_lds[t] = f;
     m = fmaxf(m, f);
     Lse v;
-    v.m = (canon0(b + bt) + xr[t]) * L2E; v.s = 1.0f;
+    v.m = canon0(b + bt) + xr[t]; v.s = 1.0f;
     a = lse_join(a, v);
   }
   m = row16_max(m);
   m = fmaxf(fmaxf(lane_f(m, 0), lane_f(m, 16)), fmaxf(lane_f(m, 32), lane_f(m, 48)));
-  float am = row16_max(a.m);
-  am = fmaxf(fmaxf(lane_f(am, 0), lane_f(am, 16)), fmaxf(lane_f(am, 32), lane_f(am, 48)));
-  float as = row16_sum(a.s * __builtin_amdgcn_exp2f(a.m - am));
-  as = (lane_f(as, 0) + lane_f(as, 16)) + (lane_f(as, 32) + lane_f(as, 48));
+  const float am = chain_max<64>(a.m), as = chain_sum<64>(a.s * __builtin_amdgcn_exp2f((a.m - am) * L2E));
   __shared__ float s_am[BLOCK / 64];
   if ((tid & 63) == 0) { s_red[w] = m; s_am[w] = am; s_rs[w] = as; }
   lds_barrier();
@@ -92,7 +89,7 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
     for (int i = 1; i < BLOCK / 64; ++i) { Lse d; d.m = s_am[i]; d.s = s_rs[i]; c = lse_join(c, d); }
     DenseSlot q;
     q.live = 1; q.last = rep_ok ? r.last : -1; q.s = s; q.e = e;
-    q.mref = M; q.inc_rep = c.m < LOG0_CLASS ? LOG0F : (c.m + __builtin_amdgcn_logf(c.s)) * LN2;
+    q.mref = M; q.inc_rep = c.m < LOG0_CLASS ? LOG0F : c.m + fast_logf(c.s);
     q.rs = r.rs; q.re = r.re; q.ref = r.ref; q.pad = 0;
     q.offr = r.off + Bref;
     q.jbase = (1.0 - p.lambda) * r.att + p.beta * (double)l;
@@ -223,7 +220,7 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
       a.m = LOG0F; a.s = 0.0f;
       for (int t = max(d.s, d.rs + 1) + lane; t <= min(d.e, d.re + 1); t += 64) {
         Lse v;
-        v.m = (dense_f(gphi, Bu, Bref, t) + col[t]) * L2E; v.s = 1.0f;
+        v.m = dense_f(gphi, Bu, Bref, t) + col[t]; v.s = 1.0f;
         a = lse_join(a, v);
       }
       const float r = lse_finish<64>(a);

@@ -12,8 +12,8 @@
 //      f_t + log p^c(z_t = c), f_t = blank variable of g at t-1 if c repeats g's last label,
 //      else phi_{t-1}(g)  (Eq. (3) / Eq. (5)); frames run along lanes (16 or 64 lanes per
 //      candidate, float4 per lane), all of a lane's column loads are issued before the first
-//      is consumed; the terms are formed in units of log 2 by one fused multiply-add each, their
-//      maximum per lane is taken, then one exp2 per term;
+//      is consumed; their sums and the largest over the candidate's lanes are taken, then one fused
+//      multiply-add and one exp2 per term;
 //   4. eos score phi_T(g), joint scores (Eq. (1)), the eos-run test, and the group's
 //      best-first list of at most Wb candidates for the per-utterance selection.
 // The candidate list of a group is in no particular order and no result depends on it; wherever
@@ -258,51 +258,105 @@ __device__ __forceinline__ void select_radix(const float* __restrict__ arow, int
 }
 
 // ---- log-sum-exp pieces -----------------------------------------------------------------------
-// In units of log 2: m the largest term of the lane so far, s the sum of 2^(term - m).
+// Natural units throughout: a term is f + x, rounded once, and the largest term M goes into the result as it is.  (With
+// f and x scaled to units of log 2 a term was rounded twice and M a third time on the way back: 1.3 to 1.4 times the
+// rounding error, for the same number of instructions.)
 #define L2E 1.4426950408889634f
 #define LN2 0.6931471805599453f
-struct Lse { float m, s; };
 
-// N float4 of a column against the (scaled) f terms: one fused multiply-add, one subtraction, one exp2 and one
-// addition per term, and the maximum.
+template <int LPC>
+__device__ __forceinline__ float chain_max(float m) {
+  static_assert(LPC == 16 || LPC == 64, "a candidate's lanes are one DPP row or one wave");
+  m = row16_max(m);
+  if (LPC == 64) m = fmaxf(fmaxf(lane_f(m, 0), lane_f(m, 16)), fmaxf(lane_f(m, 32), lane_f(m, 48)));
+  return m;
+}
+template <int LPC>
+__device__ __forceinline__ float chain_sum(float s) {
+  s = row16_sum(s);
+  if (LPC == 64) s = (lane_f(s, 0) + lane_f(s, 16)) + (lane_f(s, 32) + lane_f(s, 48));
+  return s;
+}
+
+// The sum of a candidate's terms over its LPC lanes: M the largest term so far (of all lanes), s this lane's share of the
+// sum of 2^(term log2 e - c), c = M log2 e as fp32 rounds it (chain_ref).  One addition, one maximum, one fused multiply-add, one exp2
+// and one addition per term.  The fused multiply-add rounds only the distance from M; what c lacks of M log2 e is known
+// exactly and taken out once, in chain_finish.  A reference below -2^28 is not used (c = 0, s = 0): there what c lacks
+// would leave the range of exp2, and neighbouring floats lie 32 apart, so that M is the sum; log0 is of that kind.
+#define LSE_DEEP (-268435456.0f)
+struct ChainSum { float M, s; };
+__device__ __forceinline__ float chain_ref(float M) { return (M < LSE_DEEP ? 0.0f : M) * L2E; }
+
 template <int N>
-__device__ __forceinline__ Lse lse_block(const float4 (&x)[N], const float4 (&f)[N]) {
-  float t[4 * N];
+__device__ __forceinline__ float terms(const float4 (&x)[N], const float4 (&f)[N], float (&v)[4 * N]) {   // their maximum
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    t[4 * i] = fmaf(x[i].x, L2E, f[i].x); t[4 * i + 1] = fmaf(x[i].y, L2E, f[i].y);
-    t[4 * i + 2] = fmaf(x[i].z, L2E, f[i].z); t[4 * i + 3] = fmaf(x[i].w, L2E, f[i].w);
+    v[4 * i] = x[i].x + f[i].x; v[4 * i + 1] = x[i].y + f[i].y;
+    v[4 * i + 2] = x[i].z + f[i].z; v[4 * i + 3] = x[i].w + f[i].w;
   }
-  Lse r;
-  r.m = t[0];
+  float m = v[0];
 #pragma unroll
-  for (int i = 1; i < 4 * N; ++i) r.m = fmaxf(r.m, t[i]);
+  for (int i = 1; i < 4 * N; ++i) m = fmaxf(m, v[i]);
+  return m;
+}
+template <int N>
+__device__ __forceinline__ float exp_sum(const float (&v)[N], float c) {
   float s0 = 0.0f, s1 = 0.0f;
 #pragma unroll
-  for (int i = 0; i < 4 * N; i += 2) {
-    s0 += __builtin_amdgcn_exp2f(t[i] - r.m);
-    s1 += __builtin_amdgcn_exp2f(t[i + 1] - r.m);
+  for (int i = 0; i < N; i += 2) {
+    s0 += __builtin_amdgcn_exp2f(fmaf(v[i], L2E, -c));
+    s1 += __builtin_amdgcn_exp2f(fmaf(v[i + 1], L2E, -c));
   }
-  r.s = s0 + s1;
+  return s0 + s1;
+}
+// N float4 of a column against the f terms
+template <int LPC, int N>
+__device__ __forceinline__ ChainSum chain_first(const float4 (&x)[N], const float4 (&f)[N]) {
+  float v[4 * N];
+  ChainSum a;
+  a.M = chain_max<LPC>(terms<N>(x, f, v));
+  a.s = exp_sum(v, chain_ref(a.M));
+  return a;
+}
+template <int LPC, int N>
+__device__ __forceinline__ void chain_more(ChainSum& a, const float4 (&x)[N], const float4 (&f)[N]) {
+  float v[4 * N];
+  const float c0 = chain_ref(a.M);
+  a.M = fmaxf(a.M, chain_max<LPC>(terms<N>(x, f, v)));
+  const float c = chain_ref(a.M);
+  a.s = a.s * __builtin_amdgcn_exp2f(fminf(c0 - c, 0.0f)) + exp_sum(v, c);   // (c falls only from an unused 0, with s = 0)
+}
+template <int LPC>
+__device__ __forceinline__ float chain_finish(const ChainSum& a) {
+  const float s = chain_sum<LPC>(a.s);
+  float r = a.M + (__builtin_amdgcn_logf(s) - fmaf(a.M, L2E, -chain_ref(a.M))) * LN2;
+  r = a.M < LSE_DEEP ? a.M : r;
+  return (a.M < LOG0_CLASS) ? LOG0F : r;
+}
+
+// The same where lanes go their own ways (sums in two parts, sums redone frame by frame): m the largest term of the lane
+// so far, s the sum of e^(term - m).
+struct Lse { float m, s; };
+__device__ __forceinline__ Lse lse_block(float4 x, float4 f) {
+  const float t0 = x.x + f.x, t1 = x.y + f.y, t2 = x.z + f.z, t3 = x.w + f.w;
+  Lse r;
+  r.m = fmaxf(fmaxf(t0, t1), fmaxf(t2, t3));
+  r.s = (__builtin_amdgcn_exp2f((t0 - r.m) * L2E) + __builtin_amdgcn_exp2f((t1 - r.m) * L2E)) +
+        (__builtin_amdgcn_exp2f((t2 - r.m) * L2E) + __builtin_amdgcn_exp2f((t3 - r.m) * L2E));
   return r;
 }
 __device__ __forceinline__ Lse lse_join(Lse a, Lse b) {
   Lse r;
   r.m = fmaxf(a.m, b.m);
-  r.s = a.s * __builtin_amdgcn_exp2f(a.m - r.m) + b.s * __builtin_amdgcn_exp2f(b.m - r.m);
+  r.s = a.s * __builtin_amdgcn_exp2f((a.m - r.m) * L2E) + b.s * __builtin_amdgcn_exp2f((b.m - r.m) * L2E);
   return r;
 }
-
-// all lanes of a candidate together; natural logarithm
+// all lanes of a candidate together
 template <int LPC>
 __device__ __forceinline__ float lse_finish(Lse a) {
-  static_assert(LPC == 16 || LPC == 64, "a candidate's lanes are one DPP row or one wave");
-  float M = row16_max(a.m);
-  if (LPC == 64) M = fmaxf(fmaxf(lane_f(M, 0), lane_f(M, 16)), fmaxf(lane_f(M, 32), lane_f(M, 48)));
-  float s = row16_sum(a.s * __builtin_amdgcn_exp2f(a.m - M));
-  if (LPC == 64) s = (lane_f(s, 0) + lane_f(s, 16)) + (lane_f(s, 32) + lane_f(s, 48));
-  const float r = (M + __builtin_amdgcn_logf(s)) * LN2;    // (s >= 1: the largest term contributes 1)
-  return (M < LOG0_CLASS) ? LOG0F : r;
+  const float M = chain_max<LPC>(a.m);
+  const float s = chain_sum<LPC>(a.s * __builtin_amdgcn_exp2f((a.m - M) * L2E));
+  return (M < LOG0_CLASS) ? LOG0F : M + fast_logf(s);      // (s >= 1: the largest term contributes 1)
 }
 
 // Block-wide maximum / sum (logits mode: log-sum-exp of a whole attention row).  The per-lane
@@ -373,7 +427,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
   __shared__ int s_nvalid;
   __shared__ __align__(8) float s_red[4 * (BLOCK / 64)];   // per wave: floats (a row's maxima), then doubles (its sums)
   __shared__ float s_lse;                                  // raw scores in: the row's log-sum-exp
-  __shared__ double s_eos[2];                              // eos scores, computed early, written at the end
+  __shared__ double s_eos[4];                              // eos scores, jbase and offr, computed early, needed again at the end
   __shared__ float s_e2f[2 * MAX_EOS_RUN];                 // eos-run rule: f terms of the last R frames (both kinds)
 
   const int tid = threadIdx.x, w = uni(tid >> 6);
@@ -445,7 +499,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
   unsigned long long* s_ent = (unsigned long long*)s_work;
   float4* s_gran = (float4*)(smem + p.off_small);         // (the arrays of that place are only used when these are done with)
   int32_t* s_gid = (int32_t*)(s_gran + 4 * ShortList::GCAP);
-  float* s_F = (float*)(smem + p.off_f);                  // f terms, in units of log 2
+  float* s_F = (float*)(smem + p.off_f);                  // f terms
   float* s_Fb = s_F + p.wp_max;
   // per-candidate arrays of the group (K <= BLOCK): sort key and joint score (8 bytes each), then
   // id, prefix-score increment, attention value, eos-run scratch (4 bytes each)
@@ -555,7 +609,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
       }
       const int k = t - (T - R + 1);
       if (e2w && k >= 0 && k < R) { s_e2f[k] = f; s_e2f[MAX_EOS_RUN + k] = fb; f = LOG0F; fb = LOG0F; }
-      s_F[i] = f * L2E; s_Fb[i] = fb * L2E;
+      s_F[i] = f; s_Fb[i] = fb;
     }
     if (e2 && tid < R) e2_Et = canon0(e2_p + (float)(e2_B - Bref));
     if (tid == 0) {
@@ -565,6 +619,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
       const double ctc = v ? offr + BT + (double)ce : LOG0D;
       s_eos[0] = ctc;
       s_eos[1] = v ? lam * ctc + (1.0 - lam) * (double)x_eos + jbase : LOG0D;
+      s_eos[2] = jbase; s_eos[3] = offr;                   // (held in registers through the sums they cost the forms of 72 a spill)
     }
   };
   TRACE_MARK(2);
@@ -706,14 +761,14 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
         float4 f[IT];
 #pragma unroll
         for (int it = 0; it < IT; ++it) f[it] = f4[q + it * LPC];
-        Lse a = lse_block<IT>(x[b], f);
+        ChainSum a = chain_first<LPC, IT>(x[b], f);
         for (int i0 = LPC * IT; i0 < n4; i0 += LPC * IT) {   // (windows beyond one round of loads)
           float4 y[IT];
 #pragma unroll
           for (int it = 0; it < IT; ++it) { y[it] = col[min(i0 + q + it * LPC, n4 - 1)]; f[it] = f4[i0 + q + it * LPC]; }
-          a = lse_join(a, lse_block<IT>(y, f));
+          chain_more<LPC, IT>(a, y, f);
         }
-        inc = lse_finish<LPC>(a);
+        inc = chain_finish<LPC>(a);
       } else {
         // the sum in two parts: frames up to T - R (needed on its own below) and the last R frames
         Lse a, aq;
@@ -724,15 +779,15 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
           for (int it = 0; it < IT; ++it) {
             const int i = i0 + q + it * LPC;
             const int tb = t0 + 4 * i;
-            float4 xv[1], fv[1];
+            float4 fv;
             const float4 f = f4[i];
-            xv[0] = i0 == 0 ? x[b][it] : col[min(i, n4 - 1)];
-            fv[0].x = tb <= tc ? f.x : LOG0F; fv[0].y = tb + 1 <= tc ? f.y : LOG0F;
-            fv[0].z = tb + 2 <= tc ? f.z : LOG0F; fv[0].w = tb + 3 <= tc ? f.w : LOG0F;
-            a = lse_join(a, lse_block<1>(xv, fv));
-            fv[0].x = tb > tc ? f.x : LOG0F; fv[0].y = tb + 1 > tc ? f.y : LOG0F;
-            fv[0].z = tb + 2 > tc ? f.z : LOG0F; fv[0].w = tb + 3 > tc ? f.w : LOG0F;
-            aq = lse_join(aq, lse_block<1>(xv, fv));
+            const float4 xv = i0 == 0 ? x[b][it] : col[min(i, n4 - 1)];
+            fv.x = tb <= tc ? f.x : LOG0F; fv.y = tb + 1 <= tc ? f.y : LOG0F;
+            fv.z = tb + 2 <= tc ? f.z : LOG0F; fv.w = tb + 3 <= tc ? f.w : LOG0F;
+            a = lse_join(a, lse_block(xv, fv));
+            fv.x = tb > tc ? f.x : LOG0F; fv.y = tb + 1 > tc ? f.y : LOG0F;
+            fv.z = tb + 2 > tc ? f.z : LOG0F; fv.w = tb + 3 > tc ? f.w : LOG0F;
+            aq = lse_join(aq, lse_block(xv, fv));
           }
         }
         pre = lse_finish<LPC>(a);
@@ -802,7 +857,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
 #pragma unroll
         for (int k = 0; k < E2C; ++k) {
           if (k0 + k < R) {
-            acc = lae(acc, fmaf(ff[T - R + 1 + k0 + k - t0], LN2, xv[k]));
+            acc = lae(acc, ff[T - R + 1 + k0 + k - t0] + xv[k]);
             xmax[k] = fmaxf(xmax[k], canon0(acc));
           }
         }
@@ -896,8 +951,8 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
       const float inc = has ? s_inc[tid] : LOG0F;
       const float av = s_av[has ? tid : 0] - row_lse;
       const bool valid = inc > LOG0_CLASS;
-      const double ctc = valid ? offr + (double)inc : LOG0D;
-      const double J = valid ? lam * ctc + (1.0 - lam) * (double)av + jbase : LOG0D;
+      const double ctc = valid ? s_eos[3] + (double)inc : LOG0D;
+      const double J = valid ? lam * ctc + (1.0 - lam) * (double)av + s_eos[2] : LOG0D;
       const unsigned long long me = has ? joint_key(J, id & 0xFFFF, valid && J == J) : 0ull;
       const int rank = lanes_above<16>(me, K);             // (lanes past the last entry hold zeros)
       const int nv = __popcll(__ballot(me != 0ull));

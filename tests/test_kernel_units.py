@@ -1,0 +1,82 @@
+"""Rounding of the kernels' sums, device functions on their own in the CPU build of the kernel sources (tests/cpu_emu), where
+every operation is IEEE fp32 and exp2 / log2 are libm's: against 64-bit sums of the same fp32 inputs."""
+import ctypes
+import os
+import sys
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+sys.path.insert(0, os.path.join(HERE, "cpu_emu"))
+
+import build_emu  # noqa: E402
+
+vp = ctypes.c_void_p
+
+
+@pytest.fixture(scope="module")
+def units(tmp_path_factory):
+    return ctypes.CDLL(build_emu.build(str(tmp_path_factory.mktemp("units")), sanitize=False, units=True))
+
+
+def ptr(a):
+    return a.ctypes.data_as(vp)
+
+
+def chain(units, lpc, it, x, f):
+    out = np.empty(len(x), np.float32)
+    assert x.shape[1] % 4 == 0 and units.unit_chain(lpc, it, ptr(x), ptr(f), len(x), x.shape[1] // 4, ptr(out)) == 0
+    return out.astype(np.float64)
+
+
+def exact(x, f):
+    v = x.astype(np.float64) + f.astype(np.float64)
+    m = v.max(1)
+    return m + np.log(np.exp(v - m[:, None]).sum(1)), v
+
+
+# One rounding per term and one of the result, two of the logarithm of what the terms add up to, at most one per addition on a
+# term's way into that (2 IT per round and log2 LPC between lanes, 2^-23 of the sum each), and nothing else: an error e_t
+# of a term reaches the sum as w_t e_t, w_t the term's share of it; spread evenly over one unit in the last place it is
+# ulp / sqrt(12) rms.  400 sums: the rms itself is known to 4 %, and three times that is allowed.  (Terms
+# scaled to units of log 2 lie 1.3 to 1.4 times higher.)
+@pytest.mark.parametrize("lpc,it,rounds", [(16, 2, 1), (16, 3, 1), (16, 4, 2), (64, 4, 1)])
+@pytest.mark.parametrize("magnitude", [5.0, 40.0, 300.0])
+def test_prefix_sums_round_a_term_once(units, lpc, it, rounds, magnitude):
+    rng = np.random.default_rng(int(magnitude) + lpc + it)
+    n, T = 400, 4 * lpc * it * rounds
+    x = -rng.gamma(2.0, 2.0, (n, T)).astype(np.float32) - np.float32(magnitude * rng.random((n, 1)))
+    f = -rng.gamma(2.0, 1.5, (n, T)).astype(np.float32) - np.float32(magnitude * rng.random((n, 1)))
+    f[rng.random((n, T)) < 0.2] = -1e30
+    want, v = exact(x, f)
+    w = np.exp(v - want[:, None])
+    ulp = lambda a: np.spacing(np.abs(a).astype(np.float32)).astype(np.float64)
+    log2s = (want - v.max(1)) / np.log(2.0)                # (rounded as log2 gives it, and after its correction)
+    expected = ((w * ulp(np.maximum(v, -1e4))) ** 2).sum(1) / 12 + ulp(want) ** 2 / 12 + 2 * (np.log(2.0) * ulp(log2s)) ** 2 / 12
+    expected = expected + (2 * it * rounds + np.log2(lpc)) * 2.0 ** -46 / 12
+    err = chain(units, lpc, it, x, f) - want
+    assert np.sqrt(np.mean(err ** 2)) < 1.12 * np.sqrt(np.mean(expected))
+
+
+# log0, values so low that neighbouring floats lie whole units apart, and sums whose first round of loads is of that kind
+@pytest.mark.parametrize("lpc,it", [(16, 2), (64, 4)])
+def test_prefix_sums_of_values_far_out(units, lpc, it):
+    T = 4 * lpc * it * 3
+    levels = [0.0, -3.0e4, -2.0e6, -1.5e7, -2.0e8, -2.7e8, -4.0e8, -1.0e12, -1.0e25]
+    rows, f_rows = [], []
+    for level in levels:
+        for late in (0, 1, 2):                             # which third holds the values
+            x = np.full(T, -1e30, np.float32)
+            x[late * T // 3:(late + 1) * T // 3] = level + np.linspace(-1, 0, T // 3)
+            rows.append(x); f_rows.append(np.where(np.arange(T) % 5 == 0, -1e30, -0.5).astype(np.float32))
+            rows.append(np.where(x < -1e29, np.float32(1.5 * level - 10.0), x)); f_rows.append(np.zeros(T, np.float32))
+    rows.append(np.full(T, -1e30, np.float32)); f_rows.append(np.full(T, -1e30, np.float32))
+    rows.append(np.full(T, -5.0, np.float32)); f_rows.append(np.full(T, -1e30, np.float32))
+    x, f = np.array(rows, np.float32), np.array(f_rows, np.float32)
+    got = chain(units, lpc, it, x, f)
+    want, _ = exact(x, f)
+    assert (got[-2:] == -1e30).all() or np.allclose(got[-2:], -1e30)
+    # two roundings of half a unit each, and the sum's own
+    tol = 1.5 * np.spacing(np.abs(want[:-2]).astype(np.float32)) + 1e-6
+    assert (np.abs(got[:-2] - want[:-2]) <= tol).all(), (got[:-2] - want[:-2], tol)
