@@ -164,13 +164,15 @@ struct Params {
 // of a line is a trip to memory in a chain of them.  PIN makes a value be in scalar registers from here on, so that
 // loads written above it are issued together and waited for once.  LOADED does the same for vector registers: without it
 // the compiler moves a load into the branch that alone uses it, behind the arrival of the loads before, and a
-// round of loads becomes a chain of them.
+// round of loads becomes a chain of them.  SCHED_FENCE: no instruction is moved across (a prefetch stays ahead of the work).
 #if defined(__AMDGCN__)
 #define PIN4(a, b, c, d) __asm__ volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d))
 #define LOADED(a) __asm__ volatile("" : "+v"(a))
+#define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 #else
 #define PIN4(a, b, c, d) do { } while (0)
 #define LOADED(a) do { } while (0)
+#define SCHED_FENCE() do { } while (0)
 #endif
 
 // arguments of the score kernel behind the preloaded ones

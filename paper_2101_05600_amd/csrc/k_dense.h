@@ -9,6 +9,9 @@
 //   k_list_top     per (utterance, slot): joint scores (Eq. (1)) and the group's best-first list.
 // Range: a product below 2^-126 (87 nats under M) counts as nothing; a sum of such products -- below 1e-30 -- is redone
 // frame by frame in the log domain.
+// Rounding: the exponentials are exact to about an ulp of themselves whatever their argument's size, and sums of 32
+// products are added up with what each addition loses carried on, so that the error does not grow with the number of
+// frames (one chain of additions per wave: 3 times the error of a tree of short sums at 1500 frames, 6 times at 6000).
 // Not handled here (the host then launches k_score): top-K candidates, up to 64 ids, the eos-run rule, raw
 // decoder scores, the batch-wide window.
 #pragma once
@@ -20,6 +23,17 @@ typedef float f32x4 __attribute__((__vector_size__(16)));
 // f term of frame t (log domain): gamma_{t-1}(g) relative to off' + B_r; only where t - 1 lies in the stored range
 __device__ __forceinline__ float dense_f(const float* gphi, const double* Bu, double Bref, int t) {
   return canon0(gphi[t - 1] + (float)(Bu[t - 1] - Bref));
+}
+
+// e^(v + lo), v <= 0, |lo| at most a rounding error of v: what v log2(e) loses by its rounding -- as much of the result as
+// |v| units in the last place -- is put back by one more step of the exponential's series
+__device__ __forceinline__ float exp_exact(float v) {
+  const float h = v * L2E, e = __builtin_amdgcn_exp2f(h);
+  return fmaf(e, fmaf(h, -LN2, v), e);
+}
+__device__ __forceinline__ float exp_exact(float v, float lo) {
+  const float h = v * L2E, e = __builtin_amdgcn_exp2f(h);
+  return fmaf(e, fmaf(h, -LN2, v) + lo, e);
 }
 
 template <int BLOCK>
@@ -79,7 +93,10 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
   float* F = p.dense_F + h * Tp;
   for (int t = tid; t < Tp; t += BLOCK) {
     float v = 0.0f;
-    if (some && t >= lo && t <= hi) v = __builtin_amdgcn_exp2f((dense_f_lds[t] - M) * L2E);
+    if (some && t >= lo && t <= hi) {
+      const float f = dense_f_lds[t], d = f - M, b = d + M;
+      v = exp_exact(d, (f - b) - (M - (b - d)));           // (f - M rounded, and what that lacks)
+    }
     F[t] = v;
   }
   if (tid == 0) {
@@ -146,53 +163,61 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
   for (int k = 0; k < NT; ++k) bp[k] = xu + (size_t)full_v_id(min(c0 + 16 * k + n, K - 1), lo_ex, hi_ex) * Tp + 4 * q;
 #pragma unroll
   for (int k = 0; k < MT; ++k) ap[k] = F + (h0 + min(16 * k + n, Wb - 1)) * Tp + 4 * q;
-  f32x4 acc[MT][NT];
+  f32x4 acc[MT][NT], sum[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int k = 0; k < NT; ++k) acc[i][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  float4 x[2][NT], f[2][MT];
-  auto fetch = [&](int b, float4 (&xx)[2][NT], float4 (&ff)[2][MT]) {
+    for (int k = 0; k < NT; ++k) acc[i][k] = sum[i][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  // half a block (16 frames) is on its way while the half before it is worked on
+  auto fetch = [&](int b, int hf, float4 (&x)[NT], float4 (&f)[MT]) {
 #pragma unroll
-    for (int k = 0; k < NT; ++k) { xx[0][k] = *(const float4*)(bp[k] + 32 * b); xx[1][k] = *(const float4*)(bp[k] + 32 * b + 16); }
+    for (int k = 0; k < NT; ++k) x[k] = *(const float4*)(bp[k] + 32 * b + 16 * hf);
 #pragma unroll
-    for (int k = 0; k < MT; ++k) { ff[0][k] = *(const float4*)(ap[k] + 32 * b); ff[1][k] = *(const float4*)(ap[k] + 32 * b + 16); }
+    for (int k = 0; k < MT; ++k) f[k] = *(const float4*)(ap[k] + 32 * b + 16 * hf);
+    SCHED_FENCE();
   };
-  if (bw < ew) fetch(bw, x, f);
-  for (int b = bw; b < ew; b += 4) {
-    float4 xn[2][NT], fn[2][MT];
-    fetch(min(b + 4, ew - 1), xn, fn);                         // the next block's loads fly during this block's products
+  auto products = [&](const float4 (&x)[NT], const float4 (&f)[MT]) {
+    float ex[NT][4], fa[MT][4];
 #pragma unroll
-    for (int hf = 0; hf < 2; ++hf) {
-      float ex[NT][4], fa[MT][4];
+    for (int k = 0; k < NT; ++k) { ex[k][0] = exp_exact(x[k].x); ex[k][1] = exp_exact(x[k].y); ex[k][2] = exp_exact(x[k].z); ex[k][3] = exp_exact(x[k].w); }
 #pragma unroll
-      for (int k = 0; k < NT; ++k) {
-        ex[k][0] = __builtin_amdgcn_exp2f(x[hf][k].x * L2E); ex[k][1] = __builtin_amdgcn_exp2f(x[hf][k].y * L2E);
-        ex[k][2] = __builtin_amdgcn_exp2f(x[hf][k].z * L2E); ex[k][3] = __builtin_amdgcn_exp2f(x[hf][k].w * L2E);
-      }
+    for (int k = 0; k < MT; ++k) { fa[k][0] = f[k].x; fa[k][1] = f[k].y; fa[k][2] = f[k].z; fa[k][3] = f[k].w; }
 #pragma unroll
-      for (int k = 0; k < MT; ++k) { fa[k][0] = f[hf][k].x; fa[k][1] = f[hf][k].y; fa[k][2] = f[hf][k].z; fa[k][3] = f[hf][k].w; }
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
+      for (int k = 0; k < NT; ++k)
 #pragma unroll
-        for (int k = 0; k < NT; ++k)
+        for (int i = 0; i < MT; ++i) acc[i][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][c], ex[k][c], acc[i][k], 0, 0, 0);
+  };
+  float4 x0[NT], f0[MT], x1[NT], f1[MT];
+  if (bw < ew) {
+    fetch(bw, 0, x0, f0);
+    int b = bw;
+    for (; b + 4 < ew; b += 4) {
+      fetch(b, 1, x1, f1);
+      products(x0, f0);
+      fetch(b + 4, 0, x0, f0);
+      products(x1, f1);
+      // the block's 32 frames join the sum; what that rounds away starts the next block's
 #pragma unroll
-          for (int i = 0; i < MT; ++i) acc[i][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][c], ex[k][c], acc[i][k], 0, 0, 0);
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+          const f32x4 t = sum[i][k] + acc[i][k];
+          acc[i][k] -= t - sum[i][k];
+          sum[i][k] = t;
+        }
     }
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-#pragma unroll
-      for (int k = 0; k < NT; ++k) x[g][k] = xn[g][k];
-#pragma unroll
-      for (int k = 0; k < MT; ++k) f[g][k] = fn[g][k];
-    }
+    fetch(b, 1, x1, f1);                                       // (the wave's last block)
+    products(x0, f0);
+    products(x1, f1);
   }
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int k = 0; k < NT; ++k)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) s_acc[w][16 * i + 4 * q + r][16 * k + n] = acc[i][k][r];
+      for (int r = 0; r < 4; ++r) s_acc[w][16 * i + 4 * q + r][16 * k + n] = sum[i][k][r] + acc[i][k][r];
   lds_barrier();
   // ---- increments: lane = candidate, the slots dealt to 256 / NC groups of lanes ----
   const int cc = tid & (NC - 1), c = c0 + cc;

@@ -27,3 +27,20 @@ extern "C" int unit_chain(int lpc, int it, const float* x, const float* f, int n
 #undef UNIT_CHAIN
   return -1;
 }
+
+// One utterance's increments from the slots' F (mref: their M), every id a candidate: x [V][Tp], F [Wb][Tp], out [Wb][V - 2].
+extern "C" int unit_dense(const float* x, const float* F, const float* mref, int T, int Tp, int V, int Wb, float* out) {
+  Params p;
+  memset(&p, 0, sizeof p);
+  UttInfo ui{T, T, 0.0};
+  uint8_t finished = 0;
+  std::vector<DenseSlot> slots(Wb);
+  for (int j = 0; j < Wb; ++j) { memset(&slots[j], 0, sizeof slots[j]); slots[j].live = 1; slots[j].last = -1; slots[j].s = 1; slots[j].e = T; slots[j].mref = mref[j]; }
+  p.U = 1; p.V = V; p.Wb = Wb; p.K = V - 2; p.Tp = Tp; p.blank_id = 0; p.eos_id = V - 1; p.win_m1 = p.win_m2 = -1;
+  p.finished = &finished; p.uinfo = &ui; p.cand_inc = out;
+  const dim3 grid((unsigned)(p.K + 15) / 16, 1);
+  if (Wb <= 16) hipLaunchKernelGGL((k_dense_scores<1, 1>), grid, dim3(256), 0, nullptr, x, F, slots.data(), Wb, Tp, V, p.K, p, 1, 0);
+  else hipLaunchKernelGGL((k_dense_scores<1, 2>), grid, dim3(256), 0, nullptr, x, F, slots.data(), Wb, Tp, V, p.K, p, 1, 0);
+  return 0;
+}
+extern "C" void unit_exp(const float* v, int n, float* out) { for (int i = 0; i < n; ++i) out[i] = exp_exact(v[i]); }

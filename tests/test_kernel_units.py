@@ -80,3 +80,42 @@ def test_prefix_sums_of_values_far_out(units, lpc, it):
     # two roundings of half a unit each, and the sum's own
     tol = 1.5 * np.spacing(np.abs(want[:-2]).astype(np.float32)) + 1e-6
     assert (np.abs(got[:-2] - want[:-2]) <= tol).all(), (got[:-2] - want[:-2], tol)
+
+
+# Two roundings, of exp2 and of the correction, and as much again for libm's exp2: 2^-24 of the value each; and what fp32's
+# ln 2 lacks, 2.8e-9 of it.  Without the correction 87 times 2^-24 at -87.
+def test_exponential_of_large_arguments(units):
+    v = -np.concatenate([np.linspace(0, 87, 20001), np.geomspace(1e-7, 1, 500)]).astype(np.float32)
+    got = np.empty_like(v)
+    units.unit_exp(ptr(v), len(v), ptr(got))
+    want = np.exp(v.astype(np.float64))
+    assert (np.abs(got / want - 1) < 3 * 2.0 ** -24 + 2.8e-9 * np.abs(v)).all()
+    edge = np.array([-1e30, -1e4, -200.0, 0.0], np.float32)
+    got = np.empty_like(edge)
+    units.unit_exp(ptr(edge), 4, ptr(got))
+    assert (got[:3] == 0).all() and got[3] == 1
+
+
+# Sums of products over thousands of frames: each product is rounded like its factor (exp, below 3 units of 2^-24) in a
+# sum where that averages out; a block's 32 products are added one by one, at most 32 roundings of 2^-24 of the block's
+# share, evenly spread ones 1/sqrt(3) of that; then the waves' last sum and two between the waves, 2^-24 each, and the
+# logarithm's and the increment's own rounding (half a unit in their last places).  A chain over all frames of a wave lies
+# at 1.5 (1500 frames) to 3 times that (6000).
+@pytest.mark.parametrize("T,Wb", [(60, 16), (1500, 16), (3000, 20)])
+def test_long_sums_of_products(units, T, Wb):
+    rng = np.random.default_rng(T)
+    Tp, V = (T + 5 + 31) // 32 * 32, 18
+    x = np.zeros((V, Tp), np.float32)
+    x[:, 1:T + 1] = -rng.gamma(3.0, 2.0, (V, T))
+    F = np.zeros((Wb, Tp), np.float32)
+    F[:, 1:T + 1] = np.exp(-rng.gamma(1.5, 1.0, (Wb, T)))
+    out = np.empty((Wb, V - 2), np.float32)
+    m = np.zeros(Wb, np.float32)
+    units.unit_dense(ptr(x), ptr(F), ptr(m), T, Tp, V, Wb, ptr(out))
+    want = np.log(F.astype(np.float64) @ np.exp(x[1:-1].astype(np.float64)).T)
+    err = out - want
+    u = 2.0 ** -24
+    blocks = T / 32
+    expected = (32 / 3 + 3) * u ** 2 / blocks + 3 * u ** 2 / 3
+    expected += np.mean(np.spacing(np.abs(out)).astype(np.float64) ** 2 + (np.log(2.0) * np.spacing(np.abs(out / np.log(2.0)).astype(np.float32))) ** 2) / 12
+    assert np.sqrt(np.mean(err ** 2)) < 1.12 * np.sqrt(expected)
