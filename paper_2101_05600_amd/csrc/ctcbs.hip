@@ -197,7 +197,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   p.keep_cand = (c.keep_candidates || K > 256) ? 1 : 0;
   // every id a candidate (not: few ids, the eos-run rule, raw decoder scores, the batch-wide window): the kernels of
   // k_dense.h; up to 64 ids k_score ranks the list itself and a step is two launches instead of four
-  h->dense = !restricted && K > 64 && K <= 16384 && !(c.end_flags & CTCBS_END_EOS_RUN) && !c.att_is_logits && !c.win_union;
+  h->dense = !restricted && K > 64 && !(c.end_flags & CTCBS_END_EOS_RUN) && !c.att_is_logits && !c.win_union;
   if (h->dense) p.keep_cand = c.keep_candidates ? 1 : 0;
 
   // capacity for any batch of lengths <= t_max (the step cap grows with the length)
@@ -400,14 +400,18 @@ static hipError_t launch_dense(ctcbs* h, const Params& p, const float* att, int 
   return launch_dense_scores<1>(h, p, l);
 }
 
-// the groups' lists from joint scores in global memory
+// The groups' lists from joint scores in global memory.  Up to 16384 scores stay in registers between the passes; forming
+// them again from increments and attention values costs more (at 15998 ids, beam 8: 14.6 against 17.6 us a launch).
 static hipError_t launch_lists(ctcbs* h, const Params& p, const float* att) {
   const dim3 grid(p.Wb, p.U);
 #define CTCBS_LIST(E, D) hipLaunchKernelGGL((k_list_top<E, D>), grid, dim3(256), 0, h->stream, p, att, h->cur)
-  if (p.K > 8192 && h->dense) CTCBS_LIST(64, true);
-  else if (p.K > 8192) hipLaunchKernelGGL((k_group_top<256>), dim3(p.U * p.Wb), dim3(256), 0, h->stream, p, h->cur);
-  else if (h->dense) { if (p.K <= 1024) CTCBS_LIST(4, true); else if (p.K <= 5120) CTCBS_LIST(20, true); else CTCBS_LIST(32, true); }
-  else { if (p.K <= 1024) CTCBS_LIST(4, false); else if (p.K <= 5120) CTCBS_LIST(20, false); else CTCBS_LIST(32, false); }
+  if (h->dense) {
+    if (p.K <= 1024) CTCBS_LIST(4, true); else if (p.K <= 5120) CTCBS_LIST(20, true);
+    else if (p.K <= 8192) CTCBS_LIST(32, true); else if (p.K <= 16384) CTCBS_LIST(64, true); else CTCBS_LIST(0, true);
+  } else {
+    if (p.K <= 1024) CTCBS_LIST(4, false); else if (p.K <= 5120) CTCBS_LIST(20, false);
+    else if (p.K <= 8192) CTCBS_LIST(32, false); else CTCBS_LIST(0, false);
+  }
 #undef CTCBS_LIST
   return hipGetLastError();
 }

@@ -1001,69 +1001,24 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
   TRACE_FLUSH(p, grp);
 }
 
-// The list for more than 8192 candidates with arrays of their own (see k_list_top for the usual form): Wb rounds of a block-wide argmax
-// over the joint scores in global memory.  One work-group per (utterance, beam slot).
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_group_top(Params p, int cur) {
-  __shared__ double s_v[BLOCK / 64];
-  __shared__ int s_i[BLOCK / 64], s_t[BLOCK / 64];
-  __shared__ int s_pick[MAX_BEAM];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int grp = blockIdx.x, u = grp / p.Wb, K = p.K;
-  if (p.finished[u] || !p.rec[cur][grp].live) return;      // k_score already wrote a count of 0
-  if (p.grp[grp].stopped) { if (tid == 0) p.grp[grp].n = 0; return; }
-  const double* J = p.cand_joint + (size_t)grp * K;
-  const int32_t* ids = p.cand_id + (size_t)grp * K;       // equal scores: smaller token id first
-  int n = 0;
-  for (int r = 0; r < p.Wb; ++r) {
-    double bv = LOG0D; int bi = 0x7fffffff, bt = 0x7fffffff;
-    for (int c = tid; c < K; c += BLOCK) {
-      double v = J[c];
-      if (!(v > (double)LOG0_CLASS)) continue;
-      bool taken = false;
-      for (int k = 0; k < r; ++k) taken |= (s_pick[k] == c);
-      if (taken) continue;
-      const int tk = ids[c];
-      if (v > bv || (v == bv && tk < bt)) { bv = v; bi = c; bt = tk; }
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-      double ov = __shfl_xor(bv, o); int oi = __shfl_xor(bi, o); int ot = __shfl_xor(bt, o);
-      if (ov > bv || (ov == bv && ot < bt)) { bv = ov; bi = oi; bt = ot; }
-    }
-    if (lane == 0) { s_v[w] = bv; s_i[w] = bi; s_t[w] = bt; }
-    __syncthreads();
-    if (tid == 0) {
-      for (int k = 1; k < BLOCK / 64; ++k)
-        if (s_v[k] > bv || (s_v[k] == bv && s_t[k] < bt)) { bv = s_v[k]; bi = s_i[k]; bt = s_t[k]; }
-      s_pick[r] = (bi == 0x7fffffff) ? -1 : bi;
-      if (bi != 0x7fffffff) {
-        const size_t o = (size_t)grp * p.Wb + r;
-        const size_t g = (size_t)grp * K + bi;
-        p.grp_list[o] = ListEntry{bv, p.cand_id[g], p.cand_inc[g], p.cand_att[g], 0};
-      }
-    }
-    __syncthreads();
-    if (s_pick[r] < 0) break;
-    ++n;
-  }
-  if (tid == 0) p.grp[grp].n = n;
-}
-
 // Group list for candidate sets whose joint scores lie in global memory (K > block size, or every id a candidate): one
-// work-group per (utterance, beam slot).  Every lane holds its share of the scores as 64-bit keys (order-preserving
-// image of the score whose 13 lowest mantissa bits (14 beyond 8192 candidates) carry the candidate index, inverted: larger score first, then the smaller
-// index = the smaller token id; scores equal to within 2^-38 relative count as equal).  The upper halves give a pivot that
-// at least Wb of the keys reach (as for the candidates, see find_pivot), the few that do are packed into LDS and ranked.
-// More than CAP of them (scores equal in the upper half, that is to 2^-20 relative): Wb rounds of a block-wide maximum.
-// (68 us at 4998 candidates, beam 20, with the rounds alone: a round costs 2 us.)
+// work-group per (utterance, beam slot).  Order: joint score descending (compared as the fp64 it is), then the candidate's
+// place = token id ascending.  Every lane goes over its share of the scores as order-preserving 64-bit images; the largest
+// upper halves of the lanes give a pivot that at least Wb of the scores reach (as for the candidates, see find_pivot), the
+// few that do are packed into LDS with their places and ranked.  More than CAP of them (scores equal in the upper half, that
+// is to 2^-20 relative): Wb rounds of a block-wide maximum.  (68 us at 4998 candidates, beam 20, with the rounds alone: a
+// round costs 2 us.)
+// EPT: scores per lane, held in registers; 0: as many as there are, read again (from L2) for each pass.
 // DENSE: every id is a candidate (its id follows from its place) and only the increments lie in memory: the joint score
 // is formed here, next to the row of attention values.
+template <int N> struct Int { static constexpr int n = N; };
 template <int EPT, bool DENSE>
 __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restrict__ att, int cur) {
   constexpr int BLOCK = 256, NW = BLOCK / 64, CAP = 512;
-  constexpr unsigned long long IMASK = EPT > 32 ? 0x3FFFull : 0x1FFFull;
   __shared__ unsigned long long s_k[2][NW];
+  __shared__ int s_c[2][NW];
   __shared__ __align__(16) unsigned long long s_ent[CAP + 4];
+  __shared__ __align__(16) int s_at[CAP + 4];
   __shared__ uint32_t s_thr[NW];
   __shared__ int s_n;
   const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6);
@@ -1071,47 +1026,72 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
   if (p.finished[u] || !p.rec[cur][grp].live) return;      // the score kernel already wrote a count of 0
   if (p.grp[grp].stopped) { if (tid == 0) p.grp[grp].n = 0; return; }
   const double* J = p.cand_joint + (size_t)grp * K;         // (not DENSE)
-  unsigned long long key[EPT];
-  uint32_t kmax = 0u;
   const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
   const float* arow = att + (size_t)grp * p.V;
   const float* ginc = p.cand_inc + (size_t)grp * K;
   double offr = 0.0, jbase = 0.0;
+  const double lam = p.lambda;
   if (DENSE) { offr = p.dense_slot[grp].offr; jbase = p.dense_slot[grp].jbase; }
   auto joint = [&](float inc, float a) {
-    return inc > LOG0_CLASS ? p.lambda * (offr + (double)inc) + (1.0 - p.lambda) * (double)a + jbase : LOG0D;
+    return inc > LOG0_CLASS ? lam * (offr + (double)inc) + (1.0 - lam) * (double)a + jbase : LOG0D;
   };
-  constexpr int CH = EPT <= 20 ? EPT : 16;                  // loads in flight
-#pragma unroll
-  for (int k0 = 0; k0 < EPT; k0 += CH) {
-    float iv[CH], av[CH];
-    double jv[CH];
-#pragma unroll
-    for (int k = 0; k < CH; ++k) {
-      const int c = min(tid + (k0 + k) * BLOCK, K - 1);
-      if (DENSE) { iv[k] = ginc[c]; av[k] = arow[full_v_id(c, lo_ex, hi_ex)]; }
-      else jv[k] = J[c];
-    }
-#pragma unroll
-    for (int k = 0; k < CH; ++k) {
-      const int c = tid + (k0 + k) * BLOCK;
-      const double v = DENSE ? joint(iv[k], av[k]) : jv[k];
-      if (DENSE && p.keep_cand && c < K) {
-        const size_t g = (size_t)grp * K + c;
-        p.cand_id[g] = full_v_id(c, lo_ex, hi_ex); p.cand_att[g] = av[k]; p.cand_joint[g] = v;
-        p.cand_ctc[g] = iv[k] > LOG0_CLASS ? offr + (double)iv[k] : LOG0D;
-      }
-      unsigned long long kk = 0ull;                         // not a competitor
-      if (c < K && v > (double)LOG0_CLASS) {                // (false for NaN)
-        const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-        kk = (((b >> 63) ? ~b : (b | 0x8000000000000000ull)) & ~IMASK) | (IMASK - (unsigned long long)c);
-      }
-      key[k0 + k] = kk;
-      kmax = max(kmax, (uint32_t)(kk >> 32));
+  if (DENSE && p.keep_cand) {                               // (for ctcbs_peek; in the pass below it cost every launch 1 us)
+    for (int c = tid; c < K; c += BLOCK) {
+      const size_t g = (size_t)grp * K + c;
+      const int id = full_v_id(c, lo_ex, hi_ex);
+      const float inc = ginc[c], a = arow[id];
+      p.cand_id[g] = id; p.cand_att[g] = a; p.cand_joint[g] = joint(inc, a);
+      p.cand_ctc[g] = inc > LOG0_CLASS ? offr + (double)inc : LOG0D;
     }
   }
-  auto emit = [&](unsigned long long k, int r) {
-    const int c = min((int)(IMASK - (k & IMASK)), K - 1);
+  // f(k, key) over the lane's scores, N loads in flight: candidate me + k * BLOCK (me = tid), key its score's image (0: not
+  // a competitor)
+  auto read_scores = [&](auto n_loads, int me, auto&& f) {
+    constexpr int N = decltype(n_loads)::n;
+    auto some = [&](int k0) {
+      float iv[N], av[N];
+      double jv[N];
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        const int c = min(me + (k0 + k) * BLOCK, K - 1);
+        if (DENSE) { iv[k] = ginc[c]; av[k] = arow[full_v_id(c, lo_ex, hi_ex)]; }
+        else jv[k] = J[c];
+      }
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        const int c = me + (k0 + k) * BLOCK;
+        const double v = DENSE ? joint(iv[k], av[k]) : jv[k];
+        unsigned long long kk = 0ull;
+        if (c < K && v > (double)LOG0_CLASS) {              // (false for NaN)
+          const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+          kk = (b >> 63) ? ~b : (b | 0x8000000000000000ull);
+        }
+        f(k0 + k, kk);
+      }
+    };
+    if (EPT > 0 && N >= (EPT < 16 ? EPT : 16)) {
+#pragma unroll
+      for (int k0 = 0; k0 < EPT; k0 += N) some(k0);
+    } else {
+#pragma unroll 1
+      for (int k0 = 0; k0 * BLOCK < K; k0 += N) some(k0);
+    }
+  };
+  using Loads = Int<(EPT == 0 || EPT > 20) ? 16 : EPT>;
+  unsigned long long key[EPT > 0 ? EPT : 1];
+  uint32_t kmax = 0u;
+  read_scores(Loads(), tid, [&](int k, unsigned long long kk) {
+    if (EPT > 0) key[EPT > 0 ? k : 0] = kk;
+    kmax = max(kmax, (uint32_t)(kk >> 32));
+  });
+  auto each = [&](auto&& f) {
+    if (EPT > 0) {
+#pragma unroll
+      for (int k = 0; k < (EPT > 0 ? EPT : 1); ++k) f(k, key[k]);
+    } else read_scores(Loads(), tid, f);
+  };
+  auto emit = [&](int c, int r) {
+    c = min(c, K - 1);
     const size_t g = (size_t)grp * K + c;
     const float inc = ginc[c];
     int id;
@@ -1133,54 +1113,76 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
   if (tid == 0) s_n = 0;
   lds_barrier();
   const uint32_t L = max(min(min(s_thr[0], s_thr[1]), min(s_thr[2], s_thr[3])), 1u);
-#pragma unroll
-  for (int k = 0; k < EPT; ++k)
-    if ((uint32_t)(key[k] >> 32) >= L) {
+  int me0 = tid;
+  LOADED(me0);                                              // (or the places of all scores stay in registers from the loads on)
+  each([&](int k, unsigned long long kk) {
+    if ((uint32_t)(kk >> 32) >= L) {
       const int pos = atomicAdd(&s_n, 1);
-      if (pos < CAP) s_ent[pos] = key[k];
+      if (pos < CAP) { s_ent[pos] = kk; s_at[pos] = me0 + k * BLOCK; }
     }
+  });
   lds_barrier();
   const int n = uni(s_n);
   if (n <= CAP) {
-    if (tid < 4) s_ent[n + tid] = 0ull;
+    if (tid < 4) { s_ent[n + tid] = 0ull; s_at[n + tid] = 0; }
     lds_barrier();
     const ulonglong2* e2 = (const ulonglong2*)s_ent;
     const int q = (n + 3) >> 2;
     for (int e0 = 0; e0 < n; e0 += BLOCK / 4) {
       const int e = e0 + (tid >> 2);
       const unsigned long long me = e < n ? s_ent[e] : ~0ull;
-      int rank = 0;
+      const int at = e < n ? s_at[e] : 0;
+      int rank = 0, equal = 0;                              // (its own entry among the equal ones)
       for (int i = tid & 3; i < q; i += 4) {
         const ulonglong2 a = e2[2 * i], b = e2[2 * i + 1];
         rank += ((int)(a.x > me) + (int)(a.y > me)) + ((int)(b.x > me) + (int)(b.y > me));
+        equal += ((int)(a.x == me) + (int)(a.y == me)) + ((int)(b.x == me) + (int)(b.y == me));
       }
       rank += dpp_i<0xB1, 0xf>(0, rank);                   // quad_perm [1,0,3,2]
       rank += dpp_i<0x4E, 0xf>(0, rank);                   // quad_perm [2,3,0,1]
-      if ((tid & 3) == 0 && e < n && rank < Wb) emit(me, rank);
+      equal += dpp_i<0xB1, 0xf>(0, equal);
+      equal += dpp_i<0x4E, 0xf>(0, equal);
+      if (__ballot(equal > 1) != 0ull)                      // (uniform, rare: equal scores go by place)
+        for (int i = 0; i < n; ++i) rank += (int)(s_ent[i] == me) & (int)(s_at[i] < at);
+      if ((tid & 3) == 0 && e < n && rank < Wb) emit(at, rank);
     }
     if (tid == 0) p.grp[grp].n = min(n, Wb);
     return;
   }
-  int found = 0;
+  // rounds: the best behind the one taken last
+  LOADED(me0);
+  unsigned long long last = ~0ull;
+  int last_c = 0, found = 0;
   for (int rd = 0; rd < Wb; ++rd) {
-    unsigned long long best = key[0];
-#pragma unroll
-    for (int k = 1; k < EPT; ++k) best = key[k] > best ? key[k] : best;
+    // (a lane's places ascend: the first of equals stays.  Those before the last one taken are taken too, of its equals
+    // those up to its place.  The scores are read again in every form: struck out in registers they cost the usual way
+    // 30 registers more)
+    unsigned long long best = 0ull;
+    int bk = 0;
+    const int k_taken = (last_c - me0) >> 8;                // (rounded down: BLOCK places apart)
+    read_scores(Int<8>(), me0, [&](int k, unsigned long long kk) {
+      const bool left = kk < last || (kk == last && k > k_taken);
+      if (left && kk > best) { best = kk; bk = k; }
+    });
+    int bc = best != 0ull ? me0 + bk * BLOCK : 0x7fffffff;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
       const unsigned long long ob = __shfl_xor(best, o);
-      best = ob > best ? ob : best;
+      const int oc = __shfl_xor(bc, o);
+      if (ob > best || (ob == best && oc < bc)) { best = ob; bc = oc; }
     }
-    if (lane == 0) s_k[rd & 1][w] = best;
+    if (lane == 0) { s_k[rd & 1][w] = best; s_c[rd & 1][w] = bc; }
     lds_barrier();                                          // (two buffers: one barrier per round is enough)
-    best = s_k[rd & 1][0];
+    best = s_k[rd & 1][0]; bc = s_c[rd & 1][0];
 #pragma unroll
-    for (int i = 1; i < NW; ++i) best = s_k[rd & 1][i] > best ? s_k[rd & 1][i] : best;
+    for (int i = 1; i < NW; ++i) {
+      const unsigned long long ob = s_k[rd & 1][i];
+      const int oc = s_c[rd & 1][i];
+      if (ob > best || (ob == best && oc < bc)) { best = ob; bc = oc; }
+    }
     if (best == 0ull) break;                                // uniform: no finite candidate left
-#pragma unroll
-    for (int k = 0; k < EPT; ++k)
-      if (key[k] == best) key[k] = 0ull;                    // only its owner holds this key
-    if (tid == 0) emit(best, rd);
+    if (tid == 0) emit(bc, rd);
+    last = best; last_c = bc;
     ++found;
   }
   if (tid == 0) p.grp[grp].n = found;
