@@ -389,14 +389,13 @@ __device__ __forceinline__ double block_sum_d(float sum, double* s_d /*[BLOCK / 
   return tot;
 }
 
-// Order-preserving 64-bit image of a joint score with the token in its 16 lowest mantissa bits:
-// one integer comparison then orders by (score descending, token ascending); scores equal to
-// within 2^-36 relative count as equal.  0 = not a competitor.  Needs token ids below 65536.
-__device__ __forceinline__ unsigned long long joint_key(double J, int tok, bool valid) {
+// Order-preserving 64-bit image of a joint score whose lowest mantissa bits (`mask`) hold `low` instead: one integer
+// comparison then orders by (score descending, low descending).  0 = not a competitor.
+__device__ __forceinline__ unsigned long long joint_key(double J, unsigned long long mask, int low, bool valid) {
   if (!valid) return 0ull;
   const unsigned long long b = (unsigned long long)__double_as_longlong(J);
   const unsigned long long k = (b >> 63) ? ~b : (b | 0x8000000000000000ull);
-  return (k & ~0xFFFFull) | (unsigned long long)(0xFFFF - tok);
+  return (k & ~mask) | (unsigned long long)low;
 }
 
 // Grid: (1 << sh, Wb, ceil(U / (1 << sh))), sh = bits 4-7 of flags: utterance z * 2^sh + x, beam slot y.  With sh = 3 the
@@ -806,7 +805,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
         // is pending while columns are still being fetched
         if (smallk) {
           s_J[c] = J; s_inc[c] = inc; s_av[c] = av;
-          s_key[c] = joint_key(J, id & 0xFFFF, valid && J == J);
+          s_key[c] = joint_key(J, 0ull, 0, valid && J == J);
           if (e2) s_pre[c] = pre;
         } else {
           g_inc[c] = inc; g_catt[c] = av; g_ctc[c] = ctc; g_joint[c] = J;
@@ -953,7 +952,11 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
       const bool valid = inc > LOG0_CLASS;
       const double ctc = valid ? s_eos[3] + (double)inc : LOG0D;
       const double J = valid ? lam * ctc + (1.0 - lam) * (double)av + s_eos[2] : LOG0D;
-      const unsigned long long me = has ? joint_key(J, id & 0xFFFF, valid && J == J) : 0ull;
+      // equal scores go by token id: the id in 16 bits (below 65536 here; scores equal to within 2^-36 relative count as
+      // equal then), or, every id a candidate, the lane, which ascends with the id (2^-46)
+      const bool by_lane = (p.mode & SC_RESTRICTED) == 0;
+      const unsigned long long me = joint_key(J, by_lane ? 63ull : 0xFFFFull, by_lane ? 63 - (tid & 63) : 0xFFFF - (id & 0xFFFF),
+                                              has && valid && J == J);
       const int rank = lanes_above<16>(me, K);             // (lanes past the last entry hold zeros)
       const int nv = __popcll(__ballot(me != 0ull));
       if (!fire && me != 0ull && rank < Wb) p.grp_list[(size_t)grp * Wb + rank] = ListEntry{J, id, inc, av, 0};
