@@ -165,13 +165,16 @@ int ctcbs_step(ctcbs_t* h, const float* d_att_logp, ctcbs_step_out_t* out);
  * loops, harnesses that forbid hipMalloc.  Same arguments, same kernels, same outputs and return
  * codes as ctcbs_step, bit for bit; the two may be mixed freely on one handle.  The arrays that
  * carry a step's intermediate values from the score kernel to the select kernel (windows, eos
- * scores, the groups' best-first lists, stop flags, work counts) lie in a fixed 4 MiB array inside
+ * scores, the groups' best-first lists, stop flags, work counts) lie in a fixed 5.5 MiB array inside
  * the library's image (one copy per GPU, held until the process ends) instead of the handle's own
  * memory.  The call allocates nothing, on the host or on the device, and enqueues what ctcbs_step does.
  * Limits: the device the handle was created on must be current (else CTCBS_ESTATE); at most 256
- * candidates per hypothesis and not every id a candidate, and
- * 64*U*Wb + 24*U*Wb*Wb bytes (each array rounded up to 256) within the 4 MiB (else CTCBS_EINVAL:
- * e.g. U = 256 at beam 20 fits, U = 2048 at beam 10 does not).
+ * candidates per hypothesis, and 40*U*Wb + 24*U*Wb*Wb bytes (a group's and a list entry's values, in
+ * four arrays of 4 and three of 8 bytes and in four of 4 and one of 8, each rounded up to 256) within
+ * 4 MiB (else CTCBS_EINVAL: e.g. U = 256 at beam 20 fits, U = 2048 at beam 10 does not).  Every id a
+ * candidate -- without the eos-run rule, raw scores or the batch-wide window -- is taken for long
+ * inputs only: P = t_max + 5 rounded up to 32 above 2048, or 4*Wb*P above 150 KiB (else CTCBS_EINVAL);
+ * its per-candidate values lie in the handle's memory.
  * Every call on a GPU uses that GPU's one array, whatever the handle: steps of different handles
  * (or streams) that overlap in time on one GPU race on it.  Callers that keep several batches in
  * flight use ctcbs_step.  ctcbs_peek of windows and eos scores reads the arrays of the handle's

@@ -541,25 +541,29 @@ extern "C" int ctcbs_step(ctcbs_t* h, const float* d_att_logp, ctcbs_step_out_t*
 // to the select kernel (windows, eos scores, the groups' best-first lists, stop flags, work counts) lie
 // in a fixed array in the library's own image instead of memory the handle allocated.  Every GPU holds
 // its own copy of that array at its own address, so its address is asked for once per device.
-#define CTCBS_STATIC_SCRATCH_BYTES (4u << 20)
+#define CTCBS_STATIC_SCRATCH_BYTES ((11u << 19) + 512u)   // (what static_step_takes lets in at most, see there)
 #define CTCBS_MAX_DEVICES 64
 static __device__ __align__(256) unsigned char scratch[CTCBS_STATIC_SCRATCH_BYTES];
 static std::mutex g_scratch_mu;
 static unsigned char* g_scratch_ptr[CTCBS_MAX_DEVICES];     // device address of `scratch` on each device (0: not asked yet)
 
-// bytes of the per-step scratch arrays of a handle, each array on a 256-byte boundary
-static size_t static_scratch_need(const Params& p) {
+// What the call takes: a limit of its interface (include/ctcbs.h), not of the arrays as they are laid out now.
+static bool static_step_takes(const ctcbs* h) {
+  const Params& p = h->p;
+  if (p.K > h->score_block) return false;
+  // every id a candidate: only long inputs
+  if (!p.restricted && !(p.end_flags & CTCBS_END_EOS_RUN) && !p.att_logits && !p.win_union &&
+      p.Tp <= 2048 && (size_t)4 * p.Wb * p.Tp <= 150 * 1024) return false;
+  // 40 bytes per group and 24 per list entry within 4 MiB, in arrays of 4 and 8 bytes an entry, each rounded up to 256.  (A
+  // group's line holds 64 now: at most 24 more for each of at most 65536 groups, a beam of 1.)
   const size_t UW = (size_t)p.U * p.Wb, L = UW * p.Wb;
   auto r = [](size_t n) { return (n + 255) & ~(size_t)255; };
-  return r(UW * sizeof(GroupOut)) + r(L * sizeof(ListEntry));
+  return 4 * r(UW * 4) + 3 * r(UW * 8) + r(L * 8) + 4 * r(L * 4) <= (4u << 20);
 }
 
 extern "C" int ctcbs_step_static(ctcbs_t* h, const float* d_att_logp, ctcbs_step_out_t* out) {
   if (!h || !d_att_logp) return CTCBS_EINVAL;
-  // candidate sets that go through arrays in global memory (more than 256 candidates per hypothesis, or
-  // every id a candidate) would need those arrays here too: not offered
-  if (h->dense || h->p.K > h->score_block) return CTCBS_EINVAL;
-  if (static_scratch_need(h->p) > CTCBS_STATIC_SCRATCH_BYTES) return CTCBS_EINVAL;
+  if (!static_step_takes(h)) return CTCBS_EINVAL;
   int dev = -1;
   HIPCHK(hipGetDevice(&dev));
   if (dev != h->device || dev < 0 || dev >= CTCBS_MAX_DEVICES) return CTCBS_ESTATE;   // the handle's device must be current
@@ -583,6 +587,7 @@ extern "C" int ctcbs_step_static(ctcbs_t* h, const float* d_att_logp, ctcbs_step
   // line, and the select kernel reads no list entry past a line's count)
   p.grp = (GroupOut*)take(UW * sizeof(GroupOut));
   p.grp_list = (ListEntry*)take(L * sizeof(ListEntry));
+  if (off > CTCBS_STATIC_SCRATCH_BYTES) return CTCBS_EINVAL;   // (cannot be, see static_step_takes)
   return step_impl(h, p, d_att_logp, out);
 }
 

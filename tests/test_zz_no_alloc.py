@@ -103,3 +103,58 @@ def test_static_step_rejects_what_does_not_fit():
             assert L.ctcbs_step(h, att.data_ptr(), None) == m.OK     # the handle itself is fine
         finally:
             m.ctcbs_destroy(h)
+
+
+def _one_step(w, t_max, static, reps=2):
+    """A few steps of U utterances of t_max frames on the same random rows -> (return code of the first, outputs of the last)."""
+    import torch
+    import paper_2101_05600_amd as m
+    U, Wb, V = w["n_utt"], w["beam"], w["vocab"]
+    g = torch.Generator(device="cuda").manual_seed(7)
+    ctc = torch.log_softmax(torch.randn((U, t_max, V), generator=g, device="cuda"), -1)
+    att = torch.log_softmax(torch.randn((U, Wb, V), generator=g, device="cuda"), -1)
+    h = m.ctcbs_create(m.make_config(t_max=t_max, keep_candidates=0, **w), ctc, np.full(U, t_max, np.int32))
+    out = m.StepOut()
+    try:
+        import ctypes
+        rcs = [(m.lib().ctcbs_step_static if static else m.lib().ctcbs_step)(h, att.data_ptr(), ctypes.byref(out)) for _ in range(reps)]
+        got = [m.view(p, (U, Wb), dt).cpu().numpy() for p, dt in ((out.d_parent, np.int32), (out.d_token, np.int32), (out.d_score, np.float32))] \
+            if rcs[0] == m.OK else None
+        return rcs[0], got
+    finally:
+        m.ctcbs_destroy(h)
+
+
+def _static_need(U, Wb):
+    r = lambda n: (n + 255) // 256 * 256
+    return 4 * r(4 * U * Wb) + 3 * r(8 * U * Wb) + r(8 * U * Wb * Wb) + 4 * r(4 * U * Wb * Wb)
+
+
+@pytest.mark.parametrize("beam", [1, 4, 10, 32])
+def test_static_step_takes_the_largest_batches_of_its_limit(beam):
+    import paper_2101_05600_amd as m
+    U = 1
+    while _static_need(2 * U, beam) <= 4 << 20:
+        U *= 2
+    for bit in range(U.bit_length() - 2, -1, -1):
+        U += (1 << bit) * (_static_need(U + (1 << bit), beam) <= 4 << 20)
+    w = dict(n_utt=U, vocab=12, beam=beam, cand_k=4, win_m1=3, win_m2=3, max_len_abs=4)
+    rc, got = _one_step(w, 6, static=True)
+    assert rc == m.OK
+    for a, b in zip(got, _one_step(w, 6, static=False)[1]):
+        assert np.array_equal(a, b)
+    assert _one_step(dict(w, n_utt=U + 1), 6, static=True)[0] == m.EINVAL
+
+
+# every id a candidate: long inputs are taken, others are not, as far as 256 candidates; the eos-run rule's own kernel always
+@pytest.mark.parametrize("vocab,beam,t_max,flags,taken", [
+    (100, 2, 2043, 3, False), (100, 2, 2044, 3, True), (258, 2, 2100, 3, True), (259, 2, 2100, 3, False), (60, 3, 2100, 3, True),
+    (60, 3, 100, 3, False), (100, 20, 1883, 3, False), (100, 20, 1916, 3, True), (100, 2, 100, 7, True)])
+def test_static_step_with_every_id_a_candidate(vocab, beam, t_max, flags, taken):
+    import paper_2101_05600_amd as m
+    w = dict(n_utt=2, vocab=vocab, beam=beam, cand_k=0, end_flags=flags, eos_run=3, max_len_abs=5)
+    rc, got = _one_step(w, t_max, static=True, reps=3)
+    assert rc == (m.OK if taken else m.EINVAL)
+    if taken:
+        for a, b in zip(got, _one_step(w, t_max, static=False, reps=3)[1]):
+            assert np.array_equal(a, b)
