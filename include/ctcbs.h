@@ -98,7 +98,8 @@ typedef struct {
   int32_t keep_candidates; /* 1: every step also leaves each hypothesis's candidate ids and their
                            prefix / joint scores in device memory for ctcbs_peek (checking and
                            inspection; costs a few per cent of the step's memory traffic);
-                           0: they stay on chip and ctcbs_peek of them returns CTCBS_ESTATE.
+                           0: up to 256 of more ids stay on chip and ctcbs_peek of them returns
+                           CTCBS_ESTATE (larger sets, and every id, can be peeked at anyway).
                            Step outputs and results are the same either way.               */
   void* stream;         /* hipStream_t; NULL = the null stream                             */
 } ctcbs_config_t;

@@ -93,6 +93,9 @@ struct UttInfo {             // per utterance, constant over a decode
 
 struct DenseSlot;            // (k_dense.h)
 
+// nothing (every id a candidate: what k_dense.h and k_list_top leave); all arrays; joint and prefix score side by side in cand_joint
+enum { KEEP_NONE = 0, KEEP_ARRAYS = 1, KEEP_PAIRS = 2 };
+
 struct Params {
   // sizes and configuration
   int32_t U, V, Wb, K, Tp, t_max, blank_id, eos_id;
@@ -121,7 +124,7 @@ struct Params {
   HypRec* rec[2];
   float* dense_F;            // [U][Wb][Tp] every id a candidate: exp of the f terms (k_dense.h)
   DenseSlot* dense_slot;     // [U][Wb]
-  int32_t keep_cand;         // 1: the per-candidate arrays below are filled every step (ctcbs_peek; large K needs them)
+  int32_t keep_cand;         // KEEP_*: which of the per-candidate arrays below a step fills (ctcbs_peek; large K needs them)
   // per-step scratch between the score and the select kernel
   int32_t* cand_id;          // [U][Wb][K]
   float* cand_inc;           // [U][Wb][K] log psi(g.c) - off(g)
@@ -165,14 +168,17 @@ struct Params {
 // loads written above it are issued together and waited for once.  LOADED does the same for vector registers: without it
 // the compiler moves a load into the branch that alone uses it, behind the arrival of the loads before, and a
 // round of loads becomes a chain of them.  SCHED_FENCE: no instruction is moved across (a prefetch stays ahead of the work).
+// STORE_ASIDE: past the L2, which holds what the kernels read again.
 #if defined(__AMDGCN__)
 #define PIN4(a, b, c, d) __asm__ volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d))
 #define LOADED(a) __asm__ volatile("" : "+v"(a))
 #define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
+#define STORE_ASIDE(v, ptr) __builtin_nontemporal_store(v, ptr)
 #else
 #define PIN4(a, b, c, d) do { } while (0)
 #define LOADED(a) do { } while (0)
 #define SCHED_FENCE() do { } while (0)
+#define STORE_ASIDE(v, ptr) (*(ptr) = (v))
 #endif
 
 // arguments of the score kernel behind the preloaded ones
@@ -197,7 +203,7 @@ struct ScoreArgs {
   double *cand_ctc, *cand_joint;
   unsigned long long* trace;
 };
-enum { SC_RESTRICTED = 1, SC_LOGITS = 2, SC_UNION = 4, SC_KEEP = 8, SC_UNION_UTT = 16 };
+enum { SC_RESTRICTED = 1, SC_LOGITS = 2, SC_UNION = 4, SC_KEEP = 8, SC_UNION_UTT = 16, SC_PAIRS = 32 };
 
 // arguments of the select kernels behind the preloaded ones
 struct SelectArgs {

@@ -194,11 +194,12 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   p.win_union = c.win_union ? 1 : 0;
   p.union_utt = c.win_union && U * Wb <= CTCBS_SPLIT_GROUPS ? 1 : 0;
   // large candidate sets go through the per-candidate arrays in global memory whatever the caller asked for
-  p.keep_cand = (c.keep_candidates || K > 256) ? 1 : 0;
+  p.keep_cand = (c.keep_candidates || K > 256 || (!restricted && K > 64)) ? KEEP_ARRAYS : (!restricted ? KEEP_PAIRS : KEEP_NONE);
   // every id a candidate (not: few ids, the eos-run rule, raw decoder scores, the batch-wide window): the kernels of
-  // k_dense.h; up to 64 ids k_score ranks the list itself and a step is two launches instead of four
+  // k_dense.h; up to 64 ids k_score ranks the list itself and a step is two launches instead of four.  They leave
+  // increments and attention values in memory; the rest follows from those and is written only if asked to (ctcbs_peek)
   h->dense = !restricted && K > 64 && !(c.end_flags & CTCBS_END_EOS_RUN) && !c.att_is_logits && !c.win_union;
-  if (h->dense) p.keep_cand = c.keep_candidates ? 1 : 0;
+  if (h->dense) p.keep_cand = c.keep_candidates ? KEEP_ARRAYS : KEEP_NONE;
 
   // capacity for any batch of lengths <= t_max (the step cap grows with the length)
   h->l_cap_alloc = step_cap(&c, c.t_max);
@@ -219,10 +220,11 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   }
   A(p.uinfo, U8);
   {
-    const size_t nc = p.keep_cand ? UW * K : 1;            // (not kept: never touched)
+    const size_t nc = p.keep_cand == KEEP_ARRAYS ? UW * K : 1;   // (not kept: never touched)
     const size_t nd = h->dense ? UW * K : nc;
-    A(p.cand_id, nc); A(p.cand_inc, nd); A(p.cand_att, nc); A(p.cand_pre, nc);
-    A(p.cand_ctc, nc); A(p.cand_joint, nd);
+    A(p.cand_id, nc); A(p.cand_inc, nd); A(p.cand_att, nd);
+    A(p.cand_pre, !h->dense && (c.end_flags & CTCBS_END_EOS_RUN) ? nc : 1);
+    A(p.cand_ctc, nc); A(p.cand_joint, p.keep_cand == KEEP_PAIRS ? 2 * UW * K : nc);
     A(p.dense_F, h->dense ? UW * p.Tp : 1); A(p.dense_slot, h->dense ? UW : 1);
   }
   A(p.grp, UW); A(p.grp_list, UW * Wb);
@@ -354,7 +356,7 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
   a.Tp = p.Tp; a.K = p.K; a.blank_id = p.blank_id; a.eos_id = p.eos_id; a.win_m1 = p.win_m1; a.win_m2 = p.win_m2;
   a.end_flags = p.end_flags; a.eos_run = p.eos_run; a.wp_max = h->wp_max; a.off_f = h->off_f; a.off_small = h->off_small;
   a.mode = (p.restricted ? SC_RESTRICTED : 0) | (p.att_logits ? SC_LOGITS : 0) | (p.win_union ? SC_UNION : 0) |
-           (p.keep_cand ? SC_KEEP : 0) | (p.union_utt ? SC_UNION_UTT : 0);
+           (p.keep_cand == KEEP_ARRAYS ? SC_KEEP : 0) | (p.keep_cand == KEEP_PAIRS ? SC_PAIRS : 0) | (p.union_utt ? SC_UNION_UTT : 0);
   a.U = p.U; a.pad = 0; a.err = p.err; a.union_win = p.union_win; a.n_finished = p.n_finished; a.host_progress = p.host_progress;
   a.cand_id = p.cand_id; a.cand_inc = p.cand_inc; a.cand_att = p.cand_att; a.cand_pre = p.cand_pre; a.cand_ctc = p.cand_ctc;
   a.cand_joint = p.cand_joint; a.trace = p.trace;
@@ -687,8 +689,8 @@ extern "C" int ctcbs_peek(ctcbs_t* h, int32_t what, void* h_dst, size_t bytes, s
   const size_t UW = (size_t)p.U * p.Wb;
   const void* src = nullptr; size_t sz = 0;
   int32_t k = p.K;
-  if (!p.keep_cand && (what == CTCBS_PEEK_CAND_ID || what == CTCBS_PEEK_CAND_CTC || what == CTCBS_PEEK_CAND_JOINT))
-    return CTCBS_ESTATE;                                   // created without keep_candidates
+  const bool cand = what == CTCBS_PEEK_CAND_ID || what == CTCBS_PEEK_CAND_CTC || what == CTCBS_PEEK_CAND_JOINT;
+  if (cand && p.keep_cand == KEEP_NONE && !h->dense) return CTCBS_ESTATE;   // created without keep_candidates
   switch (what) {
     case CTCBS_PEEK_CAND_ID: src = p.cand_id; sz = UW * p.K * 4; break;
     case CTCBS_PEEK_CAND_CTC: src = p.cand_ctc; sz = UW * p.K * 8; break;
@@ -702,7 +704,41 @@ extern "C" int ctcbs_peek(ctcbs_t* h, int32_t what, void* h_dst, size_t bytes, s
     default: return CTCBS_EINVAL;
   }
   if (need) *need = sz;
-  if (h_dst && bytes && !src) {                            // a field of the groups' lines
+  if (h_dst && bytes && cand && p.keep_cand != KEEP_ARRAYS) {
+    // every id a candidate: ids ascend; scores lie there in pairs, or follow from increments and attention values
+    const int lo_ex = p.blank_id < p.eos_id ? p.blank_id : p.eos_id, hi_ex = p.blank_id < p.eos_id ? p.eos_id : p.blank_id;
+    const size_t w = what == CTCBS_PEEK_CAND_ID ? 4 : 8, K = (size_t)p.K;
+    const bool pairs = p.keep_cand == KEEP_PAIRS;
+    try {
+      std::vector<DenseSlot> slots(pairs ? 0 : UW);
+      std::vector<float> inc(pairs ? 0 : K), att(pairs ? 0 : K);
+      std::vector<double> both(pairs ? 2 * K : 0);
+      if (!pairs) HIPCHK(hipMemcpyAsync(slots.data(), p.dense_slot, UW * sizeof(DenseSlot), hipMemcpyDeviceToHost, h->stream));
+      HIPCHK(hipStreamSynchronize(h->stream));
+      for (size_t g = 0; g < UW && g * K * w < bytes; ++g) {
+        if (pairs) HIPCHK(hipMemcpyAsync(both.data(), p.cand_joint + 2 * g * K, 16 * K, hipMemcpyDeviceToHost, h->stream));
+        else {
+          HIPCHK(hipMemcpyAsync(inc.data(), p.cand_inc + g * K, 4 * K, hipMemcpyDeviceToHost, h->stream));
+          HIPCHK(hipMemcpyAsync(att.data(), p.cand_att + g * K, 4 * K, hipMemcpyDeviceToHost, h->stream));
+        }
+        HIPCHK(hipStreamSynchronize(h->stream));
+        for (size_t c = 0; c < K && (g * K + c + 1) * w <= bytes; ++c) {
+          char* d = (char*)h_dst + (g * K + c) * w;
+          int32_t id = (int32_t)c;
+          if (id >= lo_ex) ++id;
+          if (id >= hi_ex) ++id;
+          double ctc = LOG0D, joint = LOG0D;
+          if (pairs) { joint = both[2 * c]; ctc = both[2 * c + 1]; }
+          else if (inc[c] > LOG0_CLASS) {
+            ctc = slots[g].offr + (double)inc[c];
+            joint = p.lambda * ctc + (1.0 - p.lambda) * (double)att[c] + slots[g].jbase;
+          }
+          if (what == CTCBS_PEEK_CAND_ID) memcpy(d, &id, w);
+          else memcpy(d, what == CTCBS_PEEK_CAND_CTC ? &ctc : &joint, w);
+        }
+      }
+    } catch (const std::bad_alloc&) { return CTCBS_ENOMEM; }
+  } else if (h_dst && bytes && !src) {                            // a field of the groups' lines
     std::vector<GroupOut> g(UW);
     HIPCHK(hipMemcpyAsync(g.data(), p.grp, UW * sizeof(GroupOut), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));

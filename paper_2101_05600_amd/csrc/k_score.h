@@ -961,6 +961,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
       const int nv = __popcll(__ballot(me != 0ull));
       if (!fire && me != 0ull && rank < Wb) p.grp_list[(size_t)grp * Wb + rank] = ListEntry{J, id, inc, av, 0};
       if (tid == 0) group_outputs(fire ? 0 : min(nv, Wb));
+      if ((p.mode & SC_PAIRS) && has) ((double2*)p.cand_joint)[(size_t)grp * K + tid] = double2{J, ctc};
       if ((p.mode & SC_KEEP) && has) {
         g_cid[tid] = id; g_inc[tid] = inc; g_catt[tid] = av; g_ctc[tid] = ctc; g_joint[tid] = J;
       }
@@ -1042,13 +1043,13 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
     for (int c = tid; c < K; c += BLOCK) {
       const size_t g = (size_t)grp * K + c;
       const int id = full_v_id(c, lo_ex, hi_ex);
-      const float inc = ginc[c], a = arow[id];
-      p.cand_id[g] = id; p.cand_att[g] = a; p.cand_joint[g] = joint(inc, a);
+      const float inc = ginc[c];
+      p.cand_id[g] = id; p.cand_joint[g] = joint(inc, arow[id]);
       p.cand_ctc[g] = inc > LOG0_CLASS ? offr + (double)inc : LOG0D;
     }
   }
-  // f(k, key) over the lane's scores, N loads in flight: candidate me + k * BLOCK (me = tid), key its score's image (0: not
-  // a competitor)
+  // f(k, key, a) over the lane's scores, N loads in flight: candidate me + k * BLOCK (me = tid), key its score's image (0: not
+  // a competitor), a its attention value (DENSE)
   auto read_scores = [&](auto n_loads, int me, auto&& f) {
     constexpr int N = decltype(n_loads)::n;
     auto some = [&](int k0) {
@@ -1069,7 +1070,7 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
           const unsigned long long b = (unsigned long long)__double_as_longlong(v);
           kk = (b >> 63) ? ~b : (b | 0x8000000000000000ull);
         }
-        f(k0 + k, kk);
+        f(k0 + k, kk, DENSE ? av[k] : 0.0f);
       }
     };
     if (EPT > 0 && N >= (EPT < 16 ? EPT : 16)) {
@@ -1083,14 +1084,16 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
   using Loads = Int<(EPT == 0 || EPT > 20) ? 16 : EPT>;
   unsigned long long key[EPT > 0 ? EPT : 1];
   uint32_t kmax = 0u;
-  read_scores(Loads(), tid, [&](int k, unsigned long long kk) {
+  float* gatt = p.cand_att + (size_t)grp * K;
+  read_scores(Loads(), tid, [&](int k, unsigned long long kk, float a) {
+    if (DENSE && tid + k * BLOCK < K) STORE_ASIDE(a, gatt + tid + k * BLOCK);   // (for ctcbs_peek: the caller's row may be gone then)
     if (EPT > 0) key[EPT > 0 ? k : 0] = kk;
     kmax = max(kmax, (uint32_t)(kk >> 32));
   });
   auto each = [&](auto&& f) {
     if (EPT > 0) {
 #pragma unroll
-      for (int k = 0; k < (EPT > 0 ? EPT : 1); ++k) f(k, key[k]);
+      for (int k = 0; k < (EPT > 0 ? EPT : 1); ++k) f(k, key[k], 0.0f);
     } else read_scores(Loads(), tid, f);
   };
   auto emit = [&](int c, int r) {
@@ -1118,7 +1121,7 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
   const uint32_t L = max(min(min(s_thr[0], s_thr[1]), min(s_thr[2], s_thr[3])), 1u);
   int me0 = tid;
   LOADED(me0);                                              // (or the places of all scores stay in registers from the loads on)
-  each([&](int k, unsigned long long kk) {
+  each([&](int k, unsigned long long kk, float) {
     if ((uint32_t)(kk >> 32) >= L) {
       const int pos = atomicAdd(&s_n, 1);
       if (pos < CAP) { s_ent[pos] = kk; s_at[pos] = me0 + k * BLOCK; }
@@ -1163,7 +1166,7 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
     unsigned long long best = 0ull;
     int bk = 0;
     const int k_taken = (last_c - me0) >> 8;                // (rounded down: BLOCK places apart)
-    read_scores(Int<8>(), me0, [&](int k, unsigned long long kk) {
+    read_scores(Int<8>(), me0, [&](int k, unsigned long long kk, float) {
       const bool left = kk < last || (kk == last && k > k_taken);
       if (left && kk > best) { best = kk; bk = k; }
     });

@@ -53,3 +53,31 @@ def test_sums_beyond_the_range_of_the_product(value):
     def edit(ctc):
         ctc[:, :, 40:47] = value
     _decode(vocab=90, edit=edit)
+
+
+# candidates can be looked at without keep_candidates: the score kernel's own list, the matrix form, sets through memory
+@pytest.mark.parametrize("vocab,over", [(40, {}), (40, dict(end_flags=7, eos_run=3)), (100, {}), (100, dict(win_union=1)), (700, {}), (9001, {}), (400, dict(cand_k=300))])
+def test_peek_without_keep_candidates(vocab, over):
+    import torch
+    import paper_2101_05600_amd as m
+    U, Wb, T = 2, 3, 40
+    g = torch.Generator(device="cuda").manual_seed(3)
+    ctc = torch.log_softmax(2 * torch.randn((U, T, vocab), generator=g, device="cuda"), -1)
+    ctc[0, :, 11] = float("-inf")
+    att = torch.log_softmax(2 * torch.randn((U, Wb, vocab), generator=g, device="cuda"), -1)
+    got = []
+    for keep in (0, 1):
+        cfg = m.make_config(**dict(dict(n_utt=U, t_max=T, vocab=vocab, beam=Wb, blank_id=3, keep_candidates=keep, win_m1=20, win_m2=20), **over))
+        h = m.ctcbs_create(cfg, ctc, np.array([T, T - 9], np.int32))
+        try:
+            for _ in range(3):
+                assert m.ctcbs_step(h, att, None) == m.OK
+            got.append([m.ctcbs_peek(h, w).copy() for w in (m.PEEK_CAND_ID, m.PEEK_CAND_CTC, m.PEEK_CAND_JOINT)])
+        finally:
+            m.ctcbs_destroy(h)
+    K = vocab - 2 if "cand_k" not in over else over["cand_k"]
+    for a, b in zip(*got):
+        # (joint scores may be put together on the host: three fp64 roundings of values below 1e3)
+        assert a.size == U * Wb * K and np.allclose(a, b, rtol=0, atol=1e3 * 3 * 2.0 ** -53 if a is got[0][2] else 0)
+    if "cand_k" not in over:
+        assert np.array_equal(got[0][0].reshape(U * Wb, K)[0], [i for i in range(vocab) if i not in (3, vocab - 1)])
