@@ -18,7 +18,8 @@
  * positive CTCBS_DONE.  All device work is enqueued on the stream given at creation; the
  * only host synchronisations are inside ctcbs_create (end), ctcbs_finalize,
  * ctcbs_poll/ctcbs_peek/ctcbs_stats/ctcbs_profile_read; with poll_every > 0 ctcbs_step also
- * waits, without draining the stream, until the device is within a few steps of the host.
+ * waits, without draining the stream, until the device is within a few steps of the host (within
+ * two intervals if they are longer than 16 steps).
  * A handle is not thread-safe.
  */
 #ifndef CTCBS_H
@@ -87,8 +88,8 @@ typedef struct {
   int32_t poll_every;   /* > 0: every that many steps ctcbs_step reports, without draining the
                            stream, the count of finished utterances the device has
                            published (it may lag by up to two such intervals), and it keeps the
-                           host from running further ahead than that (or than five steps, if
-                           that is less); 0: never                                         */
+                           host from running further ahead than that (up to intervals of 16:
+                           or than five steps, if that is less); 0: never                  */
   int32_t win_union;    /* 0: every hypothesis has its own window (the two equations for s_ij, e_ij);
                            1: one window for the whole batch, s^l = min_ij s_ij, e^l = max_ij
                            e_ij (last two equations of Sec. 3.2.3), cut at each T_i          */

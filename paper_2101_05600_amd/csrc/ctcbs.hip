@@ -422,10 +422,16 @@ static hipError_t launch_lists(ctcbs* h, const Params& p, const float* att) {
 // from running more than a few steps ahead of the device: far enough that the device always has work queued
 // (a step's launches take the host less time than the device needs to run them), and no further, because every
 // step that is already queued when the last utterance finishes still runs, for nothing (a dead step takes about
-// 6 us; with a look every eight steps and two intervals of lead, up to sixteen of them ended every decode).
+// 6 us; with a look every eight steps and two intervals of lead, up to sixteen of them ended every decode).  A caller who
+// asks for a look at more than CTCBS_POLL_CLOSE steps' distance wants to be let go on: it gets its two intervals.
 #define CTCBS_STEPS_AHEAD 5
+#define CTCBS_POLL_CLOSE 16
+static int steps_ahead(int poll_every) {
+  const int two = 2 * (poll_every < (1 << 20) ? poll_every : 1 << 20);   // (no decode has more steps)
+  return poll_every > CTCBS_POLL_CLOSE || two < CTCBS_STEPS_AHEAD ? two : CTCBS_STEPS_AHEAD;
+}
 static int follow_progress(ctcbs* h, int l) {
-  const int ahead = 2 * h->cfg.poll_every < CTCBS_STEPS_AHEAD ? 2 * h->cfg.poll_every : CTCBS_STEPS_AHEAD;
+  const int ahead = steps_ahead(h->cfg.poll_every);
   unsigned long long v = *(volatile unsigned long long*)h->h_flag;
   if ((int)(v >> 32) + ahead < l) {
     // (the wait ends: the stream's work ends, or hipStreamQuery reports why it does not)

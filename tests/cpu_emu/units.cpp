@@ -44,3 +44,4 @@ extern "C" int unit_dense(const float* x, const float* F, const float* mref, int
   return 0;
 }
 extern "C" void unit_exp(const float* v, int n, float* out) { for (int i = 0; i < n; ++i) out[i] = exp_exact(v[i]); }
+extern "C" int unit_steps_ahead(int poll_every) { return steps_ahead(poll_every); }

@@ -1,4 +1,4 @@
-"""Rounding of the kernels' sums, device functions on their own in the CPU build of the kernel sources (tests/cpu_emu), where
+"""Rounding of the kernels' sums (and a rule of the host): functions on their own in the CPU build of the kernel sources (tests/cpu_emu), where
 every operation is IEEE fp32 and exp2 / log2 are libm's: against 64-bit sums of the same fp32 inputs."""
 import ctypes
 import os
@@ -119,3 +119,9 @@ def test_long_sums_of_products(units, T, Wb):
     expected = (32 / 3 + 3) * u ** 2 / blocks + 3 * u ** 2 / 3
     expected += np.mean(np.spacing(np.abs(out)).astype(np.float64) ** 2 + (np.log(2.0) * np.spacing(np.abs(out / np.log(2.0)).astype(np.float32))) ** 2) / 12
     assert np.sqrt(np.mean(err ** 2)) < 1.12 * np.sqrt(expected)
+
+
+# The host's lead over the device: two intervals, for close looks five steps at most
+@pytest.mark.parametrize("poll_every,steps", [(1, 2), (2, 4), (3, 5), (8, 5), (16, 5), (17, 34), (1000, 2000), (2 ** 31 - 1, 2 ** 21)])
+def test_lead_of_the_host(units, poll_every, steps):
+    assert units.unit_steps_ahead(poll_every) == steps
