@@ -276,7 +276,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   const bool short_whole = !windowed && p.Tp <= 512;
   h->score_lpc = (windowed || short_whole) ? 16 : 64;
   // float4 per lane in flight: windows of up to 128 frames (16 lanes x 2 float4), up to 192, wider ones.  Three fit
-  // in 72 registers, seven waves per SIMD, where four take 80 and spill; one load fewer per lane for the same frames.
+  // in 72 registers, seven waves per SIMD, where four take 80, six waves; one load fewer per lane for the same frames.
   h->score_it = h->score_lpc == 64 || short_whole ? 4 : (c.win_m1 + c.win_m2 + 1 + 3 <= 128 ? 2 : (c.win_m1 + c.win_m2 + 1 + 3 <= 192 ? 3 : 4));
   // LDS of the score kernel: the short list (or the radix histogram), the f terms, the per-candidate arrays
   size_t off = restricted ? (size_t)PIVOT_CAP * 8 : 0;

@@ -426,7 +426,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
   __shared__ int s_nvalid;
   __shared__ __align__(8) float s_red[4 * (BLOCK / 64)];   // per wave: floats (a row's maxima), then doubles (its sums)
   __shared__ float s_lse;                                  // raw scores in: the row's log-sum-exp
-  __shared__ double s_eos[4];                              // eos scores, jbase and offr, computed early, needed again at the end
+  __shared__ double s_eos[5];                              // eos scores, jbase, offr and 1 - lambda, computed early, needed again at the end
   __shared__ float s_e2f[2 * MAX_EOS_RUN];                 // eos-run rule: f terms of the last R frames (both kinds)
 
   const int tid = threadIdx.x, w = uni(tid >> 6);
@@ -618,7 +618,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
       const double ctc = v ? offr + BT + (double)ce : LOG0D;
       s_eos[0] = ctc;
       s_eos[1] = v ? lam * ctc + (1.0 - lam) * (double)x_eos + jbase : LOG0D;
-      s_eos[2] = jbase; s_eos[3] = offr;                   // (held in registers through the sums they cost the forms of 72 a spill)
+      s_eos[2] = jbase; s_eos[3] = offr; s_eos[4] = 1.0 - lam;   // (held in registers through the sums they were spilled)
     }
   };
   TRACE_MARK(2);
@@ -890,7 +890,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
   auto group_outputs = [&](int n) {
     const double je = s_eos[1];
     p.grp[grp] = GroupOut{n, fire, s, e, s_eos[0],
-                          logits && je > (double)LOG0_CLASS ? je - (1.0 - lam) * (double)row_lse : je,
+                          logits && je > (double)LOG0_CLASS ? je - s_eos[4] * (double)row_lse : je,
                           (long long)K * (long long)W, {0, 0, 0, 0, 0, 0}};
   };
   if (!smallk && tid == 0) group_outputs(0);               // (the list builder counts)
@@ -951,7 +951,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
       const float av = s_av[has ? tid : 0] - row_lse;
       const bool valid = inc > LOG0_CLASS;
       const double ctc = valid ? s_eos[3] + (double)inc : LOG0D;
-      const double J = valid ? lam * ctc + (1.0 - lam) * (double)av + s_eos[2] : LOG0D;
+      const double J = valid ? lam * ctc + s_eos[4] * (double)av + s_eos[2] : LOG0D;
       // equal scores go by token id: the id in 16 bits (below 65536 here; scores equal to within 2^-36 relative count as
       // equal then), or, every id a candidate, the lane, which ascends with the id (2^-46)
       const bool by_lane = (p.mode & SC_RESTRICTED) == 0;
