@@ -327,11 +327,13 @@ __device__ __forceinline__ float lane_f(float v, int lane) {
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 // n += how many of the values v of lanes I .. I + 3 exceed the lane's own.  A value that one instruction puts into a scalar
 // register can be read by the second next at the earliest; left to itself the compiler waits out that distance after
-// every readlane and every comparison when scalar registers are scarce, 20 cycles a value instead of 13.
+// every readlane and every comparison when scalar registers are scarce, 20 cycles a value instead of 13.  A readlane must
+// not follow the instruction that wrote its vector register at once: the compiler does not look into the block, and what it
+// puts in front of it may be just that, a copy of v or of one of its halves; hence the s_nop in every block.
 template <int I>
 __device__ __forceinline__ void above4(uint32_t v, int& n) {
 #if defined(__AMDGCN__)
-  __asm__("v_readlane_b32 vcc_lo, %1, %2\n\tv_readlane_b32 s40, %1, %3\n\t"
+  __asm__("s_nop 0\n\tv_readlane_b32 vcc_lo, %1, %2\n\tv_readlane_b32 s40, %1, %3\n\t"
           "v_readlane_b32 s42, %1, %4\n\tv_readlane_b32 s44, %1, %5\n\t"
           "v_cmp_gt_u32_e64 vcc, vcc_lo, %1\n\tv_cmp_gt_u32_e64 s[40:41], s40, %1\n\t"
           "v_cmp_gt_u32_e64 s[42:43], s42, %1\n\tv_cmp_gt_u32_e64 s[44:45], s44, %1\n\t"
@@ -347,7 +349,7 @@ template <int I>
 __device__ __forceinline__ void above4(unsigned long long v, int& n) {
 #if defined(__AMDGCN__)
   const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-  __asm__("v_readlane_b32 vcc_lo, %2, %4\n\tv_readlane_b32 vcc_hi, %3, %4\n\t"
+  __asm__("s_nop 0\n\tv_readlane_b32 vcc_lo, %2, %4\n\tv_readlane_b32 vcc_hi, %3, %4\n\t"
           "v_readlane_b32 s40, %2, %5\n\tv_readlane_b32 s41, %3, %5\n\t"
           "v_readlane_b32 s42, %2, %6\n\tv_readlane_b32 s43, %3, %6\n\t"
           "v_readlane_b32 s44, %2, %7\n\tv_readlane_b32 s45, %3, %7\n\t"
@@ -365,14 +367,10 @@ __device__ __forceinline__ void above4(unsigned long long v, int& n) {
   }
 #endif
 }
-// the same over the first `count` lanes (uniform, up to STEP - 1 more are counted: they hold values below every other).
-// (A readlane must not follow the instruction that wrote its register at once.)
+// the same over the first `count` lanes (uniform, up to STEP - 1 more are counted: they hold values below every other)
 template <int STEP, class V>
 __device__ __forceinline__ int lanes_above(V v, int count) {
   int n = 0;
-#if defined(__AMDGCN__)
-  __asm__ volatile("s_nop 1" : "+v"(v));
-#endif
 #define ABOVE_STEP(I)                                            \
   if ((I) % STEP == 0 && (I) >= count) return n;                 \
   above4<(I)>(v, n); above4<(I) + 4>(v, n);

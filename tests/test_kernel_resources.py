@@ -38,3 +38,24 @@ def test_no_kernel_spills_vector_registers(compiled):
 
 def test_no_packed_fp32_arithmetic(compiled):
     assert not re.search(r"v_pk_(add|mul|fma)_f32", compiled[1])
+
+
+def test_no_readlane_right_behind_the_write_of_its_source(compiled):
+    """gfx950 wants one instruction between a VALU write of a vector register and a v_readlane of it, in inline assembly
+    too, where the compiler does not see to it."""
+    before, bad, seen = "", [], 0
+    for line in compiled[1].splitlines():
+        t = line.split(";")[0].strip()
+        if not t or t.startswith(".") or t.endswith(":"):
+            continue
+        hit = re.match(r"v_readlane_b32\s+\S+,\s*v(\d+)", t)
+        if hit:
+            seen += 1
+            wrote = re.match(r"v_(?!cmp|readlane|readfirstlane)\S+\s+v(?:(\d+)|\[(\d+):(\d+)\])", before)
+            if wrote:
+                lo = int(wrote.group(1) or wrote.group(2))
+                hi = int(wrote.group(1) or wrote.group(3))
+                if lo <= int(hit.group(1)) <= hi:
+                    bad.append((before, t))
+        before = t
+    assert seen > 1000 and bad == []
