@@ -22,7 +22,9 @@
 
 static thread_local int g_last_hip = 0;
 
+#ifndef CTCBS_SPLIT_GROUPS         // (the CPU build of the tests sets 0: small batches through the other kernel)
 #define CTCBS_SPLIT_GROUPS 2048   // (utterance, beam slot) groups up to which the split select kernel runs, see step_impl
+#endif
 
 #define HIPCHK(expr)                                   \
   do {                                                 \

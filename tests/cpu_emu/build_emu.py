@@ -52,8 +52,9 @@ def _patch(text):
     return text
 
 
-def build(out_dir, sanitize=True, plant=None, units=False):
-    """-> path of libctcbs_emu.so.  units: with the entry points of units.cpp (device functions on their own).  sanitize: True = AddressSanitizer + UBSan, "thread" = ThreadSanitizer
+def build(out_dir, sanitize=True, plant=None, units=False, defines=()):
+    """-> path of libctcbs_emu.so.  units: with the entry points of units.cpp (device functions on their own).  defines:
+    macros for the sources.  sanitize: True = AddressSanitizer + UBSan, "thread" = ThreadSanitizer
     (work-items are OS threads and LDS is ordinary memory, so a missing barrier shows as a data race),
     False = plain.  plant: optional (file name, old text, new text) applied to the copied source: a
     deliberate mistake, for the self-test that shows the sanitizer run notices one."""
@@ -77,6 +78,7 @@ def build(out_dir, sanitize=True, plant=None, units=False):
     so = os.path.join(out_dir, "libctcbs_emu.so")
     cmd = ["g++", "-std=c++20", "-O1", "-g", "-fPIC", "-shared", "-pthread", "-fno-strict-aliasing",
            "-I", HERE, "-o", so, os.path.join(src_dir, "units.cpp" if units else "ctcbs.cpp")]
+    cmd[1:1] = [f"-D{d}" for d in defines]
     if sanitize == "thread":
         cmd[1:1] = ["-fsanitize=thread", "-fno-omit-frame-pointer"]
     elif sanitize:

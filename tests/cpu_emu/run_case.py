@@ -23,7 +23,7 @@ CASES = {
     # split select kernel, 16-lane score kernel, eos-run rule, an unused slot
     "windowed": (dict(n_utt=3, vocab=40, beam=3, cand_k=6, win_m1=5, win_m2=5, end_flags=7, eos_run=2,
                       max_len_ratio=0.4), [12, 0, 18]),
-    # per-utterance select kernel (batch-wide window), 64-lane score kernel (no end margin)
+    # batch-wide window, 64-lane score kernel (no end margin)
     "batch_window": (dict(n_utt=2, vocab=36, beam=2, cand_k=5, win_m1=4, win_m2=-1, win_union=1, end_flags=3,
                           max_len_ratio=0.4), [15, 10]),
     # every id a candidate: all-candidates score kernel, list builder from registers

@@ -69,7 +69,7 @@ PLANT = ("k_select.h",
 
 @pytest.fixture(scope="module")
 def runs(tmp_path_factory):
-    """Builds the three instrumented libraries and runs their children, all side by side (a build takes
+    """Builds the instrumented libraries and runs their children, all side by side (a build takes
     most of a minute, a run about a minute, mostly waiting at emulated barriers).
     -> {name: CompletedProcess, or a string saying why it could not run}"""
     from concurrent.futures import ThreadPoolExecutor
@@ -77,25 +77,29 @@ def runs(tmp_path_factory):
     asan, tsan = _runtime("libasan.so"), _runtime("libtsan.so")
     plan = {
         "asan": (asan, ASAN_ENV, dict(sanitize=True),
-                 ["windowed", "batch_window", "all_candidates", "all_candidates_few_ids", "logits_odd_vocab",
-                  "pivot", "pivot_k80", "static_step", "radix_wide_ties", "wide_window_eos_run", "k80_eos_run"]),
+                 ["windowed", "batch_window", "all_candidates", "all_candidates_few_ids", "logits_odd_vocab", "static_step"],
+                 ["pivot", "wide_window_eos_run"], ["pivot_k80", "radix_wide_ties", "k80_eos_run"]),
         # the first steps of a fixed subset of the random configurations that tests/test_gpu_random_configs.py
         # decodes on the GPU (same table, tests/random_cases.py), device memory starting out as garbage
-        "asan_random": (asan, ASAN_ENV, dict(sanitize=True), [f"random:{a}:{b}:{c}" for a, b, c in CPU_SUBSET]),
+        "asan_random": (asan, ASAN_ENV, dict(sanitize=True), *[[f"random:{a}:{b}:{c}"] for a, b, c in CPU_SUBSET]),
+        # the select kernel of large batches
+        "asan_per_utterance": (asan, ASAN_ENV, dict(sanitize=True, defines=["CTCBS_SPLIT_GROUPS=0"]), ["windowed"], ["batch_window"]),
         # executor: the job queue with two host threads on two handles
-        "tsan": (tsan, TSAN_ENV, dict(sanitize="thread"), ["windowed", "batch_window", "executor"]),
+        "tsan": (tsan, TSAN_ENV, dict(sanitize="thread"), ["windowed"], ["batch_window"], ["executor"]),
         "tsan_planted": (tsan, TSAN_ENV, dict(sanitize="thread", plant=PLANT), ["windowed"]),
     }
 
     def one(name):
-        runtime, env, build_kw, cases = plan[name]
+        runtime, env, build_kw, *children = plan[name]     # (each child its list of cases, one after the other)
         if runtime is None:
             return "no such sanitizer runtime in this toolchain"
         if not _preload_works(runtime, env):
             return "a Python child does not start with this sanitizer runtime preloaded here"
         so = build_emu.build(os.path.join(root, name), **build_kw)
-        return _run(so, runtime, env, cases)
-    with ThreadPoolExecutor(max_workers=4) as ex:
+        with ThreadPoolExecutor(max_workers=len(children)) as ex:
+            rs = list(ex.map(lambda cases: _run(so, runtime, env, cases), children))
+        return subprocess.CompletedProcess(rs[0].args, max(abs(r.returncode) for r in rs), "".join(r.stdout for r in rs), "".join(r.stderr for r in rs))
+    with ThreadPoolExecutor(max_workers=5) as ex:
         futs = {k: ex.submit(one, k) for k in plan}
         return {k: f.result() for k, f in futs.items()}
 
@@ -112,6 +116,13 @@ def test_kernels_under_address_and_ub_sanitizers(runs):
     assert r.returncode == 0, out[-4000:]
     assert "ERROR: AddressSanitizer" not in out and "runtime error:" not in out, out[-4000:]
     assert out.count("emu ok") == 11, out[-2000:]
+
+
+def test_select_kernel_of_large_batches_under_address_sanitizer(runs):
+    r, out = _result(runs, "asan_per_utterance")
+    assert r.returncode == 0, out[-4000:]
+    assert "ERROR: AddressSanitizer" not in out and "runtime error:" not in out, out[-4000:]
+    assert out.count("emu ok") == 2, out[-2000:]
 
 
 def test_random_configurations_first_steps_under_address_sanitizer(runs):

@@ -59,3 +59,16 @@ def test_equal_scores_go_by_id(vocab, cand_k):
     # two levels: the better ones are fewer than the beam
     flat[[vocab - 2, 7]] = -1.9
     assert first_step(vocab, cand_k, flat, ctc) == [7, vocab - 2, 1, 2]
+
+
+# whole steps against the oracle where the scores are read again for each pass
+@pytest.mark.parametrize("vocab,cand_k", [(16387, 0), (17003, 0), (9001, 8500)])
+def test_many_candidates_against_the_oracle(vocab, cand_k):
+    import gen
+    from helpers import lockstep_decode
+    w = gen.workload("cfg1")
+    w.update(n_utt=2, t_lo=25, t_hi=40, vocab=vocab, beam=5, cand_k=cand_k, win_m1=-1, win_m2=-1, end_flags=3)
+    w["eos_id"] = vocab - 1
+    lens = gen.workload_lengths(w)
+    rep, _ = lockstep_decode(w, gen.workload_ctc(w, lens), lens, max_steps=4)
+    assert rep["max_ctc_err"] < 1e-4 and rep["max_score_err"] < 1e-4 and rep["utt_steps"] == 8
