@@ -1,8 +1,7 @@
 // Shared device-side definitions of the ctcbs kernels (gfx950, wave64).
 //
-// Numeric form.  Every hypothesis g keeps its two CTC forward variables (paths ending in
-// its last label / ending in blank; their log-sum is the paper's phi_t(g) of Eq. (3)) as
-// fp32 values in a STORED form: gamma_t(g) = stored_t + B_t + off'(g), with B_t the
+// Numeric form.  Every hypothesis g keeps two CTC forward variables per frame (all its paths, the
+// paper's phi_t(g) of Eq. (3), and those of them that end in blank) as fp32 values in a STORED form: gamma_t(g) = stored_t + B_t + off'(g), with B_t the
 // utterance's cumulative blank log-posterior (fp64, Params::Bcum) and off'(g) an fp64 offset
 // per hypothesis (HypRec::off).  Staying in blank leaves the stored value unchanged, so stored
 // values are O(1) near the frames that matter however long the utterance is and however
@@ -325,42 +324,50 @@ __device__ __forceinline__ float lane_f(float v, int lane) {
 // a value that all lanes of the wave hold alike, into a scalar register: the compiler cannot know it of what comes
 // from LDS or from a wave's number, and without it loops and choices on such values run on vector registers with lane masks
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-// n += how many of the values v of lanes I .. I + 3 exceed the lane's own.  A value that one instruction puts into a scalar
+// n += how many of the values v of lanes I .. I + 7 exceed the lane's own.  A value that one instruction puts into a scalar
 // register can be read by the second next at the earliest; left to itself the compiler waits out that distance after
 // every readlane and every comparison when scalar registers are scarce, 20 cycles a value instead of 13.  A readlane must
 // not follow the instruction that wrote its vector register at once: the compiler does not look into the block, and what it
-// puts in front of it may be just that, a copy of v or of one of its halves; hence the s_nop in every block.
-template <int I>
-__device__ __forceinline__ void above4(uint32_t v, int& n) {
+// puts in front of it may be just that, a copy of v or of one of its halves; hence the s_nop in every block (one for every
+// four values: 12.65 -> 13.0 us a launch of the split select kernel at beam 20).
 #if defined(__AMDGCN__)
-  __asm__("s_nop 0\n\tv_readlane_b32 vcc_lo, %1, %2\n\tv_readlane_b32 s40, %1, %3\n\t"
-          "v_readlane_b32 s42, %1, %4\n\tv_readlane_b32 s44, %1, %5\n\t"
-          "v_cmp_gt_u32_e64 vcc, vcc_lo, %1\n\tv_cmp_gt_u32_e64 s[40:41], s40, %1\n\t"
-          "v_cmp_gt_u32_e64 s[42:43], s42, %1\n\tv_cmp_gt_u32_e64 s[44:45], s44, %1\n\t"
-          "v_addc_co_u32_e64 %0, vcc, 0, %0, vcc\n\tv_addc_co_u32_e64 %0, s[40:41], 0, %0, s[40:41]\n\t"
-          "v_addc_co_u32_e64 %0, s[42:43], 0, %0, s[42:43]\n\tv_addc_co_u32_e64 %0, s[44:45], 0, %0, s[44:45]"
-          : "+v"(n) : "v"(v), "i"(I), "i"(I + 1), "i"(I + 2), "i"(I + 3)
+#define ABOVE_ADD                                                                                                  \
+  "v_addc_co_u32_e64 %0, vcc, 0, %0, vcc\n\tv_addc_co_u32_e64 %0, s[40:41], 0, %0, s[40:41]\n\t"                   \
+  "v_addc_co_u32_e64 %0, s[42:43], 0, %0, s[42:43]\n\tv_addc_co_u32_e64 %0, s[44:45], 0, %0, s[44:45]\n\t"
+#define ABOVE_32(A, B, C, D)                                                                                       \
+  "v_readlane_b32 vcc_lo, %1, " A "\n\tv_readlane_b32 s40, %1, " B "\n\t"                                          \
+  "v_readlane_b32 s42, %1, " C "\n\tv_readlane_b32 s44, %1, " D "\n\t"                                             \
+  "v_cmp_gt_u32_e64 vcc, vcc_lo, %1\n\tv_cmp_gt_u32_e64 s[40:41], s40, %1\n\t"                                     \
+  "v_cmp_gt_u32_e64 s[42:43], s42, %1\n\tv_cmp_gt_u32_e64 s[44:45], s44, %1\n\t" ABOVE_ADD
+#define ABOVE_64(A, B, C, D)                                                                                       \
+  "v_readlane_b32 vcc_lo, %2, " A "\n\tv_readlane_b32 vcc_hi, %3, " A "\n\t"                                       \
+  "v_readlane_b32 s40, %2, " B "\n\tv_readlane_b32 s41, %3, " B "\n\t"                                             \
+  "v_readlane_b32 s42, %2, " C "\n\tv_readlane_b32 s43, %3, " C "\n\t"                                             \
+  "v_readlane_b32 s44, %2, " D "\n\tv_readlane_b32 s45, %3, " D "\n\t"                                             \
+  "v_cmp_gt_u64_e64 vcc, vcc, %1\n\tv_cmp_gt_u64_e64 s[40:41], s[40:41], %1\n\t"                                   \
+  "v_cmp_gt_u64_e64 s[42:43], s[42:43], %1\n\tv_cmp_gt_u64_e64 s[44:45], s[44:45], %1\n\t" ABOVE_ADD
+#endif
+template <int I>
+__device__ __forceinline__ void above8(uint32_t v, int& n) {
+#if defined(__AMDGCN__)
+  __asm__("s_nop 0\n\t" ABOVE_32("%2", "%3", "%4", "%5") ABOVE_32("%6", "%7", "%8", "%9")
+          : "+v"(n)
+          : "v"(v), "i"(I), "i"(I + 1), "i"(I + 2), "i"(I + 3), "i"(I + 4), "i"(I + 5), "i"(I + 6), "i"(I + 7)
           : "vcc", "s40", "s41", "s42", "s43", "s44", "s45");
 #else
-  for (int k = 0; k < 4; ++k) n += (uint32_t)__builtin_amdgcn_readlane((int)v, I + k) > v ? 1 : 0;
+  for (int k = 0; k < 8; ++k) n += (uint32_t)__builtin_amdgcn_readlane((int)v, I + k) > v ? 1 : 0;
 #endif
 }
 template <int I>
-__device__ __forceinline__ void above4(unsigned long long v, int& n) {
+__device__ __forceinline__ void above8(unsigned long long v, int& n) {
 #if defined(__AMDGCN__)
   const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-  __asm__("s_nop 0\n\tv_readlane_b32 vcc_lo, %2, %4\n\tv_readlane_b32 vcc_hi, %3, %4\n\t"
-          "v_readlane_b32 s40, %2, %5\n\tv_readlane_b32 s41, %3, %5\n\t"
-          "v_readlane_b32 s42, %2, %6\n\tv_readlane_b32 s43, %3, %6\n\t"
-          "v_readlane_b32 s44, %2, %7\n\tv_readlane_b32 s45, %3, %7\n\t"
-          "v_cmp_gt_u64_e64 vcc, vcc, %1\n\tv_cmp_gt_u64_e64 s[40:41], s[40:41], %1\n\t"
-          "v_cmp_gt_u64_e64 s[42:43], s[42:43], %1\n\tv_cmp_gt_u64_e64 s[44:45], s[44:45], %1\n\t"
-          "v_addc_co_u32_e64 %0, vcc, 0, %0, vcc\n\tv_addc_co_u32_e64 %0, s[40:41], 0, %0, s[40:41]\n\t"
-          "v_addc_co_u32_e64 %0, s[42:43], 0, %0, s[42:43]\n\tv_addc_co_u32_e64 %0, s[44:45], 0, %0, s[44:45]"
-          : "+v"(n) : "v"(v), "v"(lo), "v"(hi), "i"(I), "i"(I + 1), "i"(I + 2), "i"(I + 3)
+  __asm__("s_nop 0\n\t" ABOVE_64("%4", "%5", "%6", "%7") ABOVE_64("%8", "%9", "%10", "%11")
+          : "+v"(n)
+          : "v"(v), "v"(lo), "v"(hi), "i"(I), "i"(I + 1), "i"(I + 2), "i"(I + 3), "i"(I + 4), "i"(I + 5), "i"(I + 6), "i"(I + 7)
           : "vcc", "s40", "s41", "s42", "s43", "s44", "s45");
 #else
-  for (int k = 0; k < 4; ++k) {
+  for (int k = 0; k < 8; ++k) {
     const unsigned long long o = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), I + k) << 32) |
                                  (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, I + k);
     n += o > v ? 1 : 0;
@@ -373,7 +380,7 @@ __device__ __forceinline__ int lanes_above(V v, int count) {
   int n = 0;
 #define ABOVE_STEP(I)                                            \
   if ((I) % STEP == 0 && (I) >= count) return n;                 \
-  above4<(I)>(v, n); above4<(I) + 4>(v, n);
+  above8<(I)>(v, n);
   ABOVE_STEP(0) ABOVE_STEP(8) ABOVE_STEP(16) ABOVE_STEP(24) ABOVE_STEP(32) ABOVE_STEP(40) ABOVE_STEP(48) ABOVE_STEP(56)
 #undef ABOVE_STEP
   return n;
