@@ -349,6 +349,8 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
   hipError_t ea = allow_lds((const void*)k_score<BLOCK, LPC, CB, IT, NV4, BIGK>, h->score_smem_bytes);
   if (ea != hipSuccess) return ea;
   const int in_regs = p.restricted && p.V >= 8 && p.V <= 4 * NV4 * BLOCK ? 1 : 0;
+  // (from eight utterances on no work-group is idle for it.  Below, measured since: 1 to 7 utterances of 437 frames
+  // would gain 0.1 us here and 0.4 in the select kernel, 2 to 4 % of a decode, from the same grouping)
   const int sh = p.U >= 8 ? 3 : 0;
   const int flags = in_regs | sh << 4;
   const dim3 grid(1u << sh, (unsigned)p.Wb, (unsigned)(p.U + (1 << sh) - 1) >> sh);
@@ -484,8 +486,12 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   if (h->dense || p.K > h->score_block) HIPCHK(launch_lists(h, p, d_att_logp));
   // Small batches leave most compute units idle in the one-work-group-per-utterance form: there the
   // split form (one work-group per new beam slot, each ranking the utterance's lists itself) is
-  // faster (measured: U=64 and U=128 at beam 10).  Large batches fill the chip either way and the
-  // Wb-fold repeated ranking only costs (U=256 at beam 20: three times slower).
+  // faster.  Large batches fill the chip either way and the Wb-fold repeated ranking only costs.  Split / per
+  // utterance, us per launch, windows of 101 frames:
+  //   beam 4:  512 groups 7.3 / 8.7, 1024 8.0 / 8.9, 2048 9.5 / 9.7, 4096 11.8 / 10.7
+  //   beam 10: 640 7.6 / 9.0, 1280 8.7 / 9.3, 2560 10.3 / 10.0, 5120 14.1 / 11.7
+  //   beam 20: 1280 10.2 / 10.9, 2560 14.4 / 11.6, 5120 21.3 / 12.1
+  // (windows of 161 frames, beam 20: 1280 14.0 / 12.5, 2560 20.8 / 13.2: there the line would lie lower)
   const bool split = p.U * p.Wb <= CTCBS_SPLIT_GROUPS;
   const size_t sel_lds = (size_t)36 * ((p.Wb * p.Wb + 63) & ~63) + 32;
   SelectArgs a;

@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256) void k_ingest(Params p, const float* __restric
   for (int i = 0; i < N4; ++i) {
     const int q = i * 256 + threadIdx.x;
     const int vl = q >> 3, t4 = (q & 7) * 4;             // eight lanes cover one token's 32 frames
-    // a wave reads 8 tokens x 8 groups of 4 frames; with rows of 260 floats, frames 8 apart would
+    // a wave reads 8 tokens x 8 groups of 4 frames; with rows of 132 floats, frames 8 apart would
     // share banks, so each band of 8 rows keeps its float4 columns in a different order: the lanes
     // of a wave (of a half wave too) fall on distinct banks
     const int vs = vl ^ ((t4 >> 3) << 2);

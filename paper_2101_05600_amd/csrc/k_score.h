@@ -69,8 +69,8 @@ struct ShortList {
 // maximum)) <= d; subtraction is monotone and M - that is exact enough for the maximum to be >= the pivot then.
 // Where the K-th value lies further down, or is not finite: bisection on the float's upper 16 bits.
 // (Pivots of the waves on their own, a quarter of K each, cost less, but the smallest of the four lets 60 values
-// through instead of 47 for K = 40, in every fourth row more than the 64 that one wave ranks: a beam-40 step of
-// one utterance 1259 -> 1249 us per decode, a beam-20 batch of 512 15710 -> 15135 us together with the form below
+// through instead of 47 for K = 40, in every fourth row more than the 64 that one wave ranks: one utterance with 40
+// candidates 1259 -> 1249 us per decode, a batch of 256 at beam 20 15710 -> 15135 us together with the form below
 // that holds three float4 per lane.)
 template <int BLOCK>
 __device__ __forceinline__ float find_pivot(const float* s_mx, int K, float& M) {
