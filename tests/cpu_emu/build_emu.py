@@ -76,7 +76,7 @@ def build(out_dir, sanitize=True, plant=None, units=False, defines=()):
     if units:
         shutil.copy(os.path.join(HERE, "units.cpp"), src_dir)
     so = os.path.join(out_dir, "libctcbs_emu.so")
-    cmd = ["g++", "-std=c++20", "-O1", "-g", "-fPIC", "-shared", "-pthread", "-fno-strict-aliasing",
+    cmd = ["g++", "-std=c++20", "-O0", "-g", "-fPIC", "-shared", "-pthread", "-fno-strict-aliasing",
            "-I", HERE, "-o", so, os.path.join(src_dir, "units.cpp" if units else "ctcbs.cpp")]
     cmd[1:1] = [f"-D{d}" for d in defines]
     if sanitize == "thread":

@@ -26,9 +26,13 @@ CASES = {
     # batch-wide window, 64-lane score kernel (no end margin)
     "batch_window": (dict(n_utt=2, vocab=36, beam=2, cand_k=5, win_m1=4, win_m2=-1, win_union=1, end_flags=3,
                           max_len_ratio=0.4), [15, 10]),
-    # every id a candidate: all-candidates score kernel, list builder from registers
+    # every id a candidate, few ids: the score kernel ranks the list itself
     "all_candidates": (dict(n_utt=1, vocab=12, beam=2, cand_k=0, win_m1=-1, win_m2=-1, end_flags=3,
                             max_len_ratio=0.4), [11]),
+    # every id a candidate, more than one wave ranks: the matrix form of the prefix scores and the list builder, more than
+    # one block of frames per wave
+    "all_candidates_matrix": (dict(n_utt=1, vocab=67, beam=2, cand_k=0, win_m1=-1, win_m2=-1, end_flags=3,
+                                   max_len_ratio=0.0, max_len_abs=2), [131]),
     # fewer ids than beam slots: most slots never hold a hypothesis, their records are never written
     "all_candidates_few_ids": (dict(n_utt=2, vocab=6, beam=6, cand_k=0, win_m1=-1, win_m2=-1, end_flags=3,
                                     max_len_ratio=0.4), [9, 7]),
