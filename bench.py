@@ -415,6 +415,29 @@ def read_profile_summary(path):
     return traffic, prof_us, prof_when
 
 
+def source_hash():
+    """Hash of the library's device sources without comments and blanks: a profile is of this build if it carries the same."""
+    import hashlib
+    import re
+    import paper_2101_05600_amd as m
+    folder = os.path.join(os.path.dirname(os.path.abspath(m.__file__)), "csrc")
+    h = hashlib.sha256()
+    for name in sorted(os.listdir(folder)):
+        if name.endswith((".h", ".hip")) and name != "probe.hip":
+            with open(os.path.join(folder, name)) as f:
+                h.update(re.sub(r"//[^\n]*|\s+", "", f.read()).encode())
+    return h.hexdigest()[:12]
+
+
+def profile_hash(path):
+    """The source hash a committed summary under profiles/ carries, None if there is none."""
+    if os.path.exists(path):
+        for ln in open(path):
+            if ln.startswith("source_hash:"):
+                return ln.split(":")[1].strip()
+    return None
+
+
 def floor(a):
     """Latency floor of one score launch at the headline shape (U=64, beam 10, V=5000, top-40, window
     50/50): the chain of dependent loads alone.  Synthetic buffers of the real sizes; every repetition
@@ -553,14 +576,22 @@ def main():
     K = int(w["cand_k"]) if 0 < w["cand_k"] < w["vocab"] - 2 else w["vocab"] - 2
     restricted = 0 < w["cand_k"] < w["vocab"] - 2
     # algorithmic bytes of the score kernel over the decode: candidate columns 4 B per term,
-    # the parent's two forward variables 8 B per window frame, the attention row 4V per group
-    bytes_score = 4.0 * b.cells + 8.0 * b.cells / K + (4.0 * w["vocab"] * b.groups if restricted else 0.0)
+    # the parent's two forward variables 8 B per window frame, the attention row 4V per group.  Every id a candidate:
+    # a posterior column is read once for the Wb beam slots of its utterance, 4 / Wb bytes per term (every slot live)
+    bytes_score = 4.0 * b.cells + 8.0 * b.cells / K + 4.0 * w["vocab"] * b.groups if restricted else 4.0 * b.cells / w["beam"]
     ach = bytes_score / (score_ms * 1e-3) / 1e9
     # measured HBM bytes per launch of the same kernel (rocprofv3 FETCH_SIZE / WRITE_SIZE, scaled by a
     # plain copy): taken from the committed counter summary, not measurable from inside this process
-    tname = f"k_score_{a.workload}_traffic.txt"
-    traffic, prof_us, prof_when = (read_profile_summary(os.path.join(ROOT, "profiles", tname))
+    tname = f"k_score_{a.workload}_traffic.txt" if restricted else f"k_dense_{a.workload}_traffic.txt"
+    tpath = os.path.join(ROOT, "profiles", tname)
+    traffic, prof_us, prof_when = (read_profile_summary(tpath)
                                    if a.utts == 0 else (None, None, None))   # read at the workload's own size
+    # from the committed rocprofv3 summary (a profiler cannot run inside this process): the kernel's own average duration,
+    # the fraction of the roof it gives, what the HBM counters read, and whether it was taken on the sources of this build
+    rocprof = {"avg_launch_us": prof_us,
+               "frac": (bytes_score / max(n_prof, 1) / (prof_us * 1e-6) / 1e9 / HBM_PEAK_GBS) if prof_us else None,
+               "traffic_bytes_per_launch": traffic, "source": "profiles/" + tname, "measured": prof_when,
+               "same_sources": profile_hash(tpath) == source_hash()}
     if restricted:
         roof = {"bound": "hbm", "kernel": "k_score", "achieved": ach, "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": ach / HBM_PEAK_GBS, "traffic": traffic,
@@ -570,31 +601,15 @@ def main():
                                      "kernel's own duration)",
                 "algorithmic_bytes_per_launch": bytes_score / max(n_prof, 1),
                 "select_kernel_avg_us": select_ms * 1e3 / max(n_prof, 1),
-                # from the committed rocprofv3 summary (a profiler cannot run inside this process): the
-                # kernel's own average duration, the fraction of the roof it gives, and what the HBM counters read
-                "rocprof": {"avg_launch_us": prof_us,
-                            "frac": (bytes_score / max(n_prof, 1) / (prof_us * 1e-6) / 1e9 / HBM_PEAK_GBS) if prof_us else None,
-                            "traffic_bytes_per_launch": traffic, "source": "profiles/" + tname,
-                            "measured": prof_when}}
+                "rocprof": rocprof}
     else:
-        # every id a candidate: the beam slots of an utterance share each posterior column, bytes fall
-        # to 4/Wb per term and the bound is the plain ALUs.  Per term one fused multiply-add, one
-        # exp2, one add = 4 flop; the exp2 issues at quarter rate, so the three instructions take 6
-        # issue slots: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz / 6 = 6.55e12 terms/s = 26.2 TFLOP/s is
-        # the most this instruction mix can reach (the chip's 157.3 TFLOP/s needs an FMA in every slot)
-        tf = 4.0 * b.cells / (score_ms * 1e-3) / 1e12
-        peak = 256 * 4 * 16 * 2.4e9 / 6.0 * 4.0 / 1e12
-        terms_per_s = b.cells / (score_ms * 1e-3)
-        roof = {"bound": "alu", "kernel": "k_score_dense", "achieved": tf, "peak": peak, "unit": "TFLOP/s",
-                "frac": tf / peak, "traffic": None, "avg_launch_us": score_ms * 1e3 / max(n_prof, 1),
-                "flop_per_term": 4, "select_kernel_avg_us": select_ms * 1e3 / max(n_prof, 1),
-                "peak_how": "instruction-mix ceiling derived from the unit counts, not a published chip peak: "
-                            "256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz / 6 issue slots per term x 4 flop",
-                # the same rate against the chip's own figures: one exp2 per term against the transcendental
-                # rate (quarter rate: 256 x 4 x 16 x 2.4e9 / 4 per second), and 4 flop per term against the
-                # published fp32 vector peak
-                "frac_of_transcendental_rate": terms_per_s / (256 * 4 * 16 * 2.4e9 / 4.0),
-                "frac_of_fp32_vector_peak": tf / 157.3}
+        # (each term is one fp32 multiply-add on the matrix cores; the HIP events span k_dense_prep and k_dense_scores)
+        roof = {"bound": "hbm", "kernel": "k_dense_scores", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": ach / HBM_PEAK_GBS, "traffic": traffic, "avg_launch_us": score_ms * 1e3 / max(n_prof, 1),
+                "algorithmic_bytes_per_launch": bytes_score / max(n_prof, 1),
+                "select_kernel_avg_us": select_ms * 1e3 / max(n_prof, 1),
+                "frac_of_fp32_matrix_peak": 2.0 * b.cells / (score_ms * 1e-3) / 157.3e12,
+                "rocprof": rocprof}
     line = {
         "metric": "CTC prefix-score cells/sec (utt·beam·cand·frame) + utterances/sec at B=64",
         "value": b.cells / (dt / a.steps), "unit": "cells/s",

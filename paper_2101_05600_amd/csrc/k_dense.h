@@ -126,7 +126,10 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
 // and their sums meet in LDS at the end.  MFMA 16x16x4: lane (n, q) = (lane & 15, lane >> 4) holds four consecutive
 // frames of candidate n (of slot n): its float4 serves four products whose frame index runs over the four q.
 // Bound: the posteriors, once (4 V T bytes per utterance; 16 utterances of 1500 frames, 5000 ids: 480 MB).  MFMA:
-// 32 cycles for 16 x 16 x 4, two slot tiles beyond 16 slots: half the time the bytes take.
+// 32 cycles for 16 x 16 x 4, two slot tiles beyond 16 slots: half the time the bytes take.  Half a block is fetched ahead:
+// 114 us a launch there, 116.5 with one accumulator per tile and the loads where the compiler put them; with the two
+// accumulators the sums need and the loads left to it a decode of 27.1 ms took 37.5.  159 registers, three waves per
+// SIMD, for four candidate and two slot tiles; held to fewer the form of one slot tile spills (12.4 -> 13.7 ms a decode).
 template <int NT, int MT>
 __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict__ xT, const float* __restrict__ F,
                                                          const DenseSlot* __restrict__ slots,

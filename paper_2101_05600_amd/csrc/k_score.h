@@ -260,7 +260,7 @@ __device__ __forceinline__ void select_radix(const float* __restrict__ arow, int
 // ---- log-sum-exp pieces -----------------------------------------------------------------------
 // Natural units throughout: a term is f + x, rounded once, and the largest term M goes into the result as it is.  (With
 // f and x scaled to units of log 2 a term was rounded twice and M a third time on the way back: 1.3 to 1.4 times the
-// rounding error, for the same number of instructions.)
+// rounding error, for the same number of instructions and the same time: 50.6 / 50.9 us a launch at beam 20, 256 utterances.)
 #define L2E 1.4426950408889634f
 #define LN2 0.6931471805599453f
 
@@ -1012,6 +1012,8 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
 // few that do are packed into LDS with their places and ranked.  More than CAP of them (scores equal in the upper half, that
 // is to 2^-20 relative): Wb rounds of a block-wide maximum.  (68 us at 4998 candidates, beam 20, with the rounds alone: a
 // round costs 2 us.)
+// Per launch at 4998 ids, beam 20, 16 utterances: 10.4 us, 12.1 with the attention values stored for ctcbs_peek (10.2 with the places
+// in the keys' last bits, which put scores closer than 2^-38 in the order of their ids); 300 candidates, beam 10, 64 utterances 6.3.
 // EPT: scores per lane, held in registers; 0: as many as there are, read again (from L2) for each pass.
 // DENSE: every id is a candidate (its id follows from its place) and only the increments lie in memory: the joint score
 // is formed here, next to the row of attention values.

@@ -32,3 +32,15 @@ def test_committed_counter_summaries_are_readable_by_the_bench_line():
         traffic, us, when = bench.read_profile_summary(os.path.join(ROOT, "profiles", f"k_score_{wl}_traffic.txt"))
         assert traffic and traffic > 1e6 and us and 1.0 < us < 1000.0 and when and "MI355X" in when
     assert bench.read_profile_summary(os.path.join(ROOT, "profiles", "no_such_file.txt")) == (None, None, None)
+
+
+def test_profiles_are_told_from_those_of_other_sources():
+    """The bench line says whether the profiler's figures it quotes are of the present sources: by a hash that comments and
+    blanks do not change."""
+    sys.path.insert(0, ROOT)
+    import bench
+    import re
+    for wl in ("cfg2", "cfg4b"):
+        assert re.fullmatch("[0-9a-f]{12}", bench.profile_hash(os.path.join(ROOT, "profiles", f"k_score_{wl}_traffic.txt")))
+    assert re.fullmatch("[0-9a-f]{12}", bench.source_hash())
+    assert bench.profile_hash(os.path.join(ROOT, "profiles", "no_such_file.txt")) is None
