@@ -98,26 +98,26 @@ def test_exponential_of_large_arguments(units):
 
 # Sums of products over thousands of frames: each product is rounded like its factor (exp, below 3 units of 2^-24) in a
 # sum where that averages out; a block's 32 products are added one by one, at most 32 roundings of 2^-24 of the block's
-# share, evenly spread ones 1/sqrt(3) of that; then the waves' last sum and two between the waves, 2^-24 each, and the
-# logarithm's and the increment's own rounding (half a unit in their last places).  A chain over all frames of a wave lies
-# at 1.5 (1500 frames) to 3 times that (6000).
-@pytest.mark.parametrize("T,Wb", [(60, 16), (1500, 16), (3000, 20)])
-def test_long_sums_of_products(units, T, Wb):
+# share, evenly spread ones 1/sqrt(3) of that; then the waves' last sum and two between the waves, 2^-24 each, the
+# mantissa's logarithm (up to 1, one unit of its own and its product with ln 2) and the increment's own rounding.  A chain over
+# all frames of a wave lies at 2 (1500 frames) to 4 times that (6000), a logarithm of the whole sum at 2 for sums around e^-14.
+@pytest.mark.parametrize("T,Wb,low", [(60, 16, 0), (60, 16, 14), (1500, 16, 0), (3000, 20, 20)])
+def test_long_sums_of_products(units, T, Wb, low):
     rng = np.random.default_rng(T)
     Tp, V = (T + 5 + 31) // 32 * 32, 18
     x = np.zeros((V, Tp), np.float32)
-    x[:, 1:T + 1] = -rng.gamma(3.0, 2.0, (V, T))
+    x[:, 1:T + 1] = -rng.gamma(3.0, 2.0, (V, T)) - low
     F = np.zeros((Wb, Tp), np.float32)
     F[:, 1:T + 1] = np.exp(-rng.gamma(1.5, 1.0, (Wb, T)))
     out = np.empty((Wb, V - 2), np.float32)
-    m = np.zeros(Wb, np.float32)
+    m = -rng.random(Wb).astype(np.float32)
     units.unit_dense(ptr(x), ptr(F), ptr(m), T, Tp, V, Wb, ptr(out))
-    want = np.log(F.astype(np.float64) @ np.exp(x[1:-1].astype(np.float64)).T)
+    want = m[:, None].astype(np.float64) + np.log(F.astype(np.float64) @ np.exp(x[1:-1].astype(np.float64)).T)
     err = out - want
     u = 2.0 ** -24
     blocks = T / 32
     expected = (32 / 3 + 3) * u ** 2 / blocks + 3 * u ** 2 / 3
-    expected += np.mean(np.spacing(np.abs(out)).astype(np.float64) ** 2 + (np.log(2.0) * np.spacing(np.abs(out / np.log(2.0)).astype(np.float32))) ** 2) / 12
+    expected += (2 + 1) * u ** 2 / 3 + np.mean(np.spacing(np.abs(out)).astype(np.float64) ** 2) / 12
     assert np.sqrt(np.mean(err ** 2)) < 1.12 * np.sqrt(expected)
 
 
