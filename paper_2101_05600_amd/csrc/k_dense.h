@@ -1,9 +1,9 @@
 // Scoring when every id but blank and eos is a candidate (the paper's Eq. (3) as it stands, no pre-selection).
 // The sum over frames of exp(f_t(g) + x_t(c)) is a product of two matrices -- exp(f_t(g)), beam slots by frames, and
 // exp(x_t(c)) = p^c(z_t = c), frames by candidates -- so that one exp2 per (candidate, frame) serves all beam slots of an
-// utterance and the rest is fp32 MFMA.  What is left is the time it takes to read the posteriors once.
-//   k_dense_prep   per (utterance, slot): window, F_t = exp(f_t - M) over it (M the largest f term; 0 outside), eos
-//                  scores, and the one candidate the product does not fit: the repeat of the slot's last label (blank
+// utterance and the rest is fp32 MFMA.  What is left is the time it takes to read the posteriors.
+//   k_dense_prep   per (utterance, slot): window, F_t = exp(f_t - M) over it (M the largest f term; 0 outside) and the
+//                  frames between its first and its last F that is not 0, eos scores, and the one candidate the product does not fit: the repeat of the slot's last label (blank
 //                  variable only, third alignment rule of Sec. 2.1);
 //   k_dense_scores per (utterance, chunk of candidates): the product, i.e. the prefix-score increments;
 //   k_list_top     per (utterance, slot): joint scores (Eq. (1)) and the group's best-first list.
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
   if (p.finished[u] || !r.live) {
     if (tid == 0) {
       p.grp[h] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
-      slot->live = 0; slot->s = 0x7fffffff; slot->e = -1;
+      slot->live = 0; slot->lo = 0x7fffffff; slot->hi = -1;
     }
     return;
   }
@@ -104,14 +104,24 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
   for (int i = 1; i < BLOCK / 64; ++i) M = fmaxf(M, s_red[i]);
   const bool some = M > LOG0_CLASS;                            // else: no term at all, every increment is log0
   float* F = p.dense_F + h * Tp;
-  for (int t = tid; t < Tp; t += BLOCK) {
+  __shared__ int s_lo[BLOCK / 64], s_hi[BLOCK / 64];
+  int f_lo = 0x7fffffff, f_hi = -1;                            // (scalar: a wave's lanes hold 64 frames in a row)
+  for (int t = tid; t - tid < Tp; t += BLOCK) {
     float v = 0.0f;
     if (some && t >= lo && t <= hi) {
       const float f = dense_f_lds[t], d = f - M, b = d + M;
       v = exp_exact(d, (f - b) - (M - (b - d)));           // (f - M rounded, and what that lacks)
     }
-    F[t] = v;
+    if (t < Tp) F[t] = v;
+    const unsigned long long nz = __ballot(v != 0.0f);
+    if (nz != 0ull) {
+      const int t_w = t - (tid & 63);
+      f_lo = min(f_lo, uni(t_w) + __ffsll((long long)nz) - 1);
+      f_hi = uni(t_w) + 63 - __clzll((long long)nz);
+    }
   }
+  if ((tid & 63) == 0) { s_lo[w] = f_lo; s_hi[w] = f_hi; }
+  lds_barrier();
   if (tid == 0) {
     Lse c;
     c.m = s_am[0]; c.s = s_rs[0];
@@ -121,6 +131,9 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
     q.live = 1; q.last = rep_ok ? r.last : -1; q.s = s; q.e = e;
     q.mref = M; q.inc_rep = c.m < LOG0_CLASS ? LOG0F : c.m + fast_logf(c.s);
     q.rs = r.rs; q.re = r.re; q.ref = r.ref; q.pad = 0;
+    q.lo = s_lo[0]; q.hi = s_hi[0];
+#pragma unroll
+    for (int i = 1; i < BLOCK / 64; ++i) { q.lo = min(q.lo, s_lo[i]); q.hi = max(q.hi, s_hi[i]); }
     q.offr = r.off + Bref;
     q.jbase = (1.0 - p.lambda) * r.att + p.beta * (double)l;
     *slot = q;
@@ -138,9 +151,12 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
 // block of 16 frames (together they walk along the columns) for all the work-group's candidates and slots (no operand is shared between waves, so none goes through LDS),
 // and their sums meet in LDS at the end.  MFMA 16x16x4: lane (n, q) = (lane & 15, lane >> 4) holds four consecutive
 // frames of candidate n (of slot n): its float4 serves four products whose frame index runs over the four q.
-// Bound: the posteriors, once (4 V T bytes per utterance; 16 utterances of 1500 frames, 5000 ids: 480 MB).  MFMA:
+// Only the frames between the first and the last F of any slot that is not 0 are read: where F underflows its products are
+// exactly 0.  Peaked posteriors leave a few hundred frames round the slots' last labels (a label missed costs nats, F is 0
+// from 87 on), 3 to 4 in 16 at 16 utterances of 1500 frames, 5000 ids: 115 -> 33 us a launch; flat ones leave them all.
+// Bound: the posteriors of those frames (4 V T bytes per utterance if all: 480 MB).  MFMA:
 // 32 cycles for 16 x 16 x 4, two slot tiles beyond 16 slots: half the time the bytes take.  Half a block is fetched ahead:
-// 114 us a launch there, 116.5 with one accumulator per tile and the loads where the compiler put them; with the two
+// 114 us a launch with all frames, 116.5 with one accumulator per tile and the loads where the compiler put them; with the two
 // accumulators the sums need and the loads left to it a decode of 27.1 ms took 37.5.  159 registers, three waves per
 // SIMD, for four candidate and two slot tiles; held to fewer the form of one slot tile spills (12.4 -> 13.7 ms a decode).
 template <int NT, int MT>
@@ -156,18 +172,16 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
   const size_t h0 = (size_t)u * Wb;
   if (p.finished[u]) return;
   const int T = p.uinfo[u].T;
-  int smin = l > 1 ? l : 1, emax = T;
+  int smin, emax;                                              // the frames that any slot has an F for
   {
     DenseSlot d;
-    d.live = 0; d.s = 0x7fffffff; d.e = -1;
+    d.live = 0; d.lo = 0x7fffffff; d.hi = -1;
     if (lane < Wb) d = slots[h0 + lane];
     if (tid < Wb) { s_last[tid] = d.last; s_live[tid] = d.live; s_m[tid] = d.mref; s_rep[tid] = d.inc_rep; }
-    if (p.win_m1 >= 0 || p.win_m2 >= 0) {                      // the slots' windows together
-      int a = d.live ? d.s : 0x7fffffff, b = d.live ? d.e : -1;
+    int a = d.live ? d.lo : 0x7fffffff, b = d.live ? d.hi : -1;
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) { a = min(a, __shfl_xor(a, o)); b = max(b, __shfl_xor(b, o)); }
-      smin = uni(min(max(a, 1), T)); emax = uni(min(b, T));
-    }
+    for (int o = 32; o > 0; o >>= 1) { a = min(a, __shfl_xor(a, o)); b = max(b, __shfl_xor(b, o)); }
+    smin = uni(min(max(a, 1), T)); emax = uni(min(b, T));
   }
   const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
   const float* xu = xT + (size_t)u * V * Tp;

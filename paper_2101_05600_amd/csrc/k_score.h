@@ -28,6 +28,7 @@ struct __align__(64) DenseSlot {
   int32_t rs, re, ref;
   int32_t pad;
   double offr, jbase;        // off' + B_r; joint score without this step's terms
+  int32_t lo, hi;            // first and last frame whose F is not 0 (none: lo > hi)
 };
 
 #define PIVOT_CAP 512     // entries of the short list (all waves together)
