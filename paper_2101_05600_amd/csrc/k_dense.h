@@ -65,7 +65,7 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
   if (p.finished[u] || !r.live) {
     if (tid == 0) {
       p.grp[h] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
-      slot->live = 0; slot->lo = 0x7fffffff; slot->hi = -1;
+      slot->live = 0; slot->s = 0x7fffffff; slot->e = -1;
     }
     return;
   }
@@ -128,12 +128,12 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
 #pragma unroll
     for (int i = 1; i < BLOCK / 64; ++i) { Lse d; d.m = s_am[i]; d.s = s_rs[i]; c = lse_join(c, d); }
     DenseSlot q;
-    q.live = 1; q.last = rep_ok ? r.last : -1; q.s = s; q.e = e;
+    q.live = 1; q.last = rep_ok ? r.last : -1; q.win_s = s; q.win_e = e;
     q.mref = M; q.inc_rep = c.m < LOG0_CLASS ? LOG0F : c.m + fast_logf(c.s);
     q.rs = r.rs; q.re = r.re; q.ref = r.ref; q.pad = 0;
-    q.lo = s_lo[0]; q.hi = s_hi[0];
+    q.s = s_lo[0]; q.e = s_hi[0];
 #pragma unroll
-    for (int i = 1; i < BLOCK / 64; ++i) { q.lo = min(q.lo, s_lo[i]); q.hi = max(q.hi, s_hi[i]); }
+    for (int i = 1; i < BLOCK / 64; ++i) { q.s = min(q.s, s_lo[i]); q.e = max(q.e, s_hi[i]); }
     q.offr = r.off + Bref;
     q.jbase = (1.0 - p.lambda) * r.att + p.beta * (double)l;
     *slot = q;
@@ -175,10 +175,10 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
   int smin, emax;                                              // the frames that any slot has an F for
   {
     DenseSlot d;
-    d.live = 0; d.lo = 0x7fffffff; d.hi = -1;
+    d.live = 0; d.s = 0x7fffffff; d.e = -1;
     if (lane < Wb) d = slots[h0 + lane];
     if (tid < Wb) { s_last[tid] = d.last; s_live[tid] = d.live; s_m[tid] = d.mref; s_rep[tid] = d.inc_rep; }
-    int a = d.live ? d.lo : 0x7fffffff, b = d.live ? d.hi : -1;
+    int a = d.live ? d.s : 0x7fffffff, b = d.live ? d.e : -1;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) { a = min(a, __shfl_xor(a, o)); b = max(b, __shfl_xor(b, o)); }
     smin = uni(min(max(a, 1), T)); emax = uni(min(b, T));
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
       const float* col = xu + (size_t)idr * Tp;
       Lse a;
       a.m = LOG0F; a.s = 0.0f;
-      for (int t = max(d.s, d.rs + 1) + lane; t <= min(d.e, d.re + 1); t += 64) {
+      for (int t = max(d.win_s, d.rs + 1) + lane; t <= min(d.win_e, d.re + 1); t += 64) {
         Lse v;
         v.m = dense_f(gphi, Bu, Bref, t) + col[t]; v.s = 1.0f;
         a = lse_join(a, v);

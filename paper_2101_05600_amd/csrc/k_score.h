@@ -23,12 +23,13 @@
 
 // (every id a candidate, see k_dense.h) one beam slot
 struct __align__(64) DenseSlot {
-  int32_t live, last, s, e;  // window
+  int32_t live, last;
+  int32_t s, e;              // first and last frame whose F is not 0 (none: s > e)
   float mref, inc_rep;       // largest f term M; increment of the candidate that repeats the last label
   int32_t rs, re, ref;
   int32_t pad;
   double offr, jbase;        // off' + B_r; joint score without this step's terms
-  int32_t lo, hi;            // first and last frame whose F is not 0 (none: lo > hi)
+  int32_t win_s, win_e;      // window
 };
 
 #define PIVOT_CAP 512     // entries of the short list (all waves together)
