@@ -47,10 +47,10 @@ struct ctcbs {
   int32_t l_cap_alloc; // step cap of an utterance of t_max frames: what the buffers are sized for
   int32_t known_finished;
   size_t score_smem_bytes;
-  int score_block, score_lpc, select_block;
+  int score_block, select_block;
   int select_lps;              // select kernel: lanes per new hypothesis
   bool select_wide;            // windows beyond 128 frames are common
-  int score_it;                // float4 per lane and column in flight
+  int score_form;              // window up to 128 frames, up to 192, wider (k_score)
   bool score_bigk;
   int score_nv4;               // granules of an attention row per lane
   bool dense;                  // every id a candidate: the kernels of k_dense.h
@@ -271,21 +271,16 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   }
   // launch shapes of the per-step kernels
   h->score_block = 256;
-  const bool windowed = c.win_m1 >= 0 && c.win_m2 >= 0 && (c.win_m1 + c.win_m2) <= 448;
-  // whole-utterance windows of utterances of up to ~500 frames are faster in the 16-lane form too (twice
-  // the candidates per round; measured: T <= 250 20.0 -> 15.3 us, T <= 500 21.1 -> 18.8 us, T in 500..800
-  // 25.1 -> 26.9 us, T in 1000..1500 34.2 -> 43.5 us: beyond 512 frames the 64-lane form stays)
-  const bool short_whole = !windowed && p.Tp <= 512;
-  h->score_lpc = (windowed || short_whole) ? 16 : 64;
-  // float4 per lane in flight: windows of up to 128 frames (16 lanes x 2 float4), up to 192, wider ones.  Three fit
-  // in 72 registers, seven waves per SIMD, where four take 80, six waves; one load fewer per lane for the same frames.
-  h->score_it = h->score_lpc == 64 || short_whole ? 4 : (c.win_m1 + c.win_m2 + 1 + 3 <= 128 ? 2 : (c.win_m1 + c.win_m2 + 1 + 3 <= 192 ? 3 : 4));
+  // (a batch-wide window is about as wide as its margins where labels come at about the same rate in all utterances: 21 utterances,
+  // margins of 5 and 60, 1525 us a decode against 1549 with the form for wide windows)
+  const int margins = c.win_m1 >= 0 && c.win_m2 >= 0 ? c.win_m1 + c.win_m2 + 1 + 3 : 1 << 30;
+  h->score_form = margins <= 128 ? 0 : (margins <= 192 ? 1 : 2);
   // LDS of the score kernel: the short list (or the radix histogram), the f terms, the per-candidate arrays
   size_t off = restricted ? (size_t)PIVOT_CAP * 8 : 0;
   h->off_f = (int32_t)off;
-  // the f terms, padded to whole rounds of the column loads (4 * LPC * IT frames)
-  const int round_frames = 4 * h->score_lpc * h->score_it;
-  h->wp_max = (p.Tp + round_frames - 1) / round_frames * round_frames;
+  // the f terms, padded to whole rounds of the column loads, which NEAR starts anywhere in the window
+  const int round_frames = 4 * 16 * (h->score_form == 1 ? 3 : 2);
+  h->wp_max = (p.Tp + round_frames - 1) / round_frames * round_frames + (h->score_form == 2 ? round_frames : 0);
   off += (size_t)2 * h->wp_max * 4;
   h->off_small = (int32_t)off;
   h->score_bigk = K > 64 || V > 65536;
@@ -297,7 +292,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   if (off > 160 * 1024) return CTCBS_EINVAL;
   // Survivors of the select kernels: per-hypothesis windows whose margins keep them within 128 (256) frames, but for a
   // hypothesis whose two time indices lie far apart, go 16 lanes x 8 frames (32 x 8) each, others 64 x 8.
-  const int span = c.win_m1 >= 0 && c.win_m2 >= 0 && !c.win_union ? c.win_m1 + c.win_m2 + 1 + 3 : 1 << 30;
+  const int span = c.win_union ? 1 << 30 : margins;
   h->select_lps = span <= 128 ? 16 : (span <= 256 ? 32 : 64);
   h->select_wide = span > 128;
   // one wave for the ended set and one round of the others for the new hypotheses, as far as a work-group goes
@@ -344,9 +339,9 @@ static hipError_t allow_lds(const void* kernel, size_t bytes) {
   }
 }
 
-template <int BLOCK, int LPC, int CB, int IT, int NV4, bool BIGK>
+template <int BLOCK, int CB, int IT, int NV4, bool NEAR, bool BIGK>
 static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, int l) {
-  hipError_t ea = allow_lds((const void*)k_score<BLOCK, LPC, CB, IT, NV4, BIGK>, h->score_smem_bytes);
+  hipError_t ea = allow_lds((const void*)k_score<BLOCK, CB, IT, NV4, NEAR, BIGK>, h->score_smem_bytes);
   if (ea != hipSuccess) return ea;
   const int in_regs = p.restricted && p.V >= 8 && p.V <= 4 * NV4 * BLOCK ? 1 : 0;
   // (from eight utterances on no work-group is idle for it.  Below, measured since: 1 to 7 utterances of 437 frames
@@ -364,7 +359,7 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
   a.U = p.U; a.pad = 0; a.err = p.err; a.union_win = p.union_win; a.n_finished = p.n_finished; a.host_progress = p.host_progress;
   a.cand_id = p.cand_id; a.cand_inc = p.cand_inc; a.cand_att = p.cand_att; a.cand_pre = p.cand_pre; a.cand_ctc = p.cand_ctc;
   a.cand_joint = p.cand_joint; a.trace = p.trace;
-  hipLaunchKernelGGL((k_score<BLOCK, LPC, CB, IT, NV4, BIGK>), grid, dim3(BLOCK), h->score_smem_bytes,
+  hipLaunchKernelGGL((k_score<BLOCK, CB, IT, NV4, NEAR, BIGK>), grid, dim3(BLOCK), h->score_smem_bytes,
                      h->stream, (const HypRec*)p.rec[h->cur], (const UttInfo*)p.uinfo, (const uint32_t*)p.finished,
                      att, (int)p.Wb, (int)p.V, flags, l, a);
   return hipGetLastError();
@@ -372,17 +367,17 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
 
 // the kernel's form: registers for the row as the vocabulary needs them (up to 3072, 5120, 10240, 16384 ids; larger
 // ones never hold it), and the paths for many candidates only where they can be taken (see k_score)
-template <int BLOCK, int LPC, int CB, int IT>
+template <int BLOCK, int CB, int IT, bool NEAR>
 static hipError_t launch_score(ctcbs* h, const Params& p, const float* att, int l) {
   if (h->score_bigk) {
-    if (h->score_nv4 <= 5) return launch_score_as<BLOCK, LPC, CB, IT, 5, true>(h, p, att, l);
-    return launch_score_as<BLOCK, LPC, CB, IT, 16, true>(h, p, att, l);
+    if (h->score_nv4 <= 5) return launch_score_as<BLOCK, CB, IT, 5, false, true>(h, p, att, l);
+    return launch_score_as<BLOCK, CB, IT, 16, false, true>(h, p, att, l);
   }
   switch (h->score_nv4) {
-    case 3: return launch_score_as<BLOCK, LPC, CB, IT, 3, false>(h, p, att, l);
-    case 5: return launch_score_as<BLOCK, LPC, CB, IT, 5, false>(h, p, att, l);
-    case 10: return launch_score_as<BLOCK, LPC, CB, IT, 10, false>(h, p, att, l);
-    default: return launch_score_as<BLOCK, LPC, CB, IT, 16, false>(h, p, att, l);
+    case 3: return launch_score_as<BLOCK, CB, IT, 3, NEAR, false>(h, p, att, l);
+    case 5: return launch_score_as<BLOCK, CB, IT, 5, NEAR, false>(h, p, att, l);
+    case 10: return launch_score_as<BLOCK, CB, IT, 10, NEAR, false>(h, p, att, l);
+    default: return launch_score_as<BLOCK, CB, IT, 16, NEAR, false>(h, p, att, l);
   }
 }
 
@@ -471,16 +466,12 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
     h->ev_used += 3;
     HIPCHK(hipEventRecord(ev[0], h->stream));
   }
-  // 16 lanes x 2 (3) float4 per candidate cover windows of up to 128 (192) frames without a second trip to
-  // memory, 16 lanes x 4 float4 serve wider windows and whole utterances of up to 512 frames; whole-utterance
-  // windows beyond that use whole waves, 4 float4 (1024 frames) in flight (see create_impl)
   hipError_t e;
   if (h->dense) e = launch_dense(h, p, d_att_logp, l);
   else
-    e = h->score_lpc == 64 ? launch_score<256, 64, 2, 4>(h, p, d_att_logp, l)
-        : h->score_it == 2 ? launch_score<256, 16, 3, 2>(h, p, d_att_logp, l)
-        : h->score_it == 3 ? launch_score<256, 16, 2, 3>(h, p, d_att_logp, l)
-                           : launch_score<256, 16, 2, 4>(h, p, d_att_logp, l);
+    e = h->score_form == 0 ? launch_score<256, 3, 2, false>(h, p, d_att_logp, l)
+        : h->score_form == 1 ? launch_score<256, 2, 3, false>(h, p, d_att_logp, l)
+                             : launch_score<256, 3, 2, true>(h, p, d_att_logp, l);
   HIPCHK(e);
   if (ev) HIPCHK(hipEventRecord(ev[1], h->stream));       // (the list builder below counts as selection)
   if (h->dense || p.K > h->score_block) HIPCHK(launch_lists(h, p, d_att_logp));
@@ -500,7 +491,7 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   a.rec_new = p.rec[nxt]; a.trie = p.trie_parent + (size_t)l * p.U * p.Wb; a.out = p.out_parent; a.out8 = p.out_live;
   a.trie_stride = (uint32_t)(p.trie_token - p.trie_parent);
   a.U = p.U; a.V = p.V; a.Tp = p.Tp; a.blank_id = p.blank_id; a.end_flags = p.end_flags; a.end_m = p.end_m; a.end_c = p.end_c;
-  a.end_d = p.end_d; a.win_union = p.win_union; a.win_m2 = p.win_m2; a.err = p.err; a.finished = p.finished;
+  a.end_d = p.end_d; a.win_union = p.win_union; a.win_m2 = p.win_m2; a.want_near = h->score_form == 2; a.err = p.err; a.finished = p.finished;
   a.n_finished = p.n_finished; a.cells = p.cells; a.groups = p.groups; a.union_win = p.union_win; a.trace = p.trace;
   const int wb_m = (65536 / p.Wb + 1) << 8 | p.Wb;         // (see k_select)
 #define CTCBS_SELECT(K, G, BS, LDS, L)                                                                       \
@@ -509,8 +500,9 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   if (split) {
     const int sh = p.U >= 8 ? 3 : 0;
     const dim3 grid(1u << sh, (unsigned)p.Wb + 1, (unsigned)(p.U + (1 << sh) - 1) >> sh);
-    if (h->select_wide || p.Wb > 12) CTCBS_SELECT((k_select_split<256>), grid, 256, sel_lds, l | sh << 28);
-    else CTCBS_SELECT((k_select_split<64>), grid, 64, sel_lds, l | sh << 28);
+    if (h->score_form == 2) CTCBS_SELECT((k_select_split<256, true>), grid, 256, sel_lds, l | sh << 28);
+    else if (h->select_wide || p.Wb > 12) CTCBS_SELECT((k_select_split<256, false>), grid, 256, sel_lds, l | sh << 28);
+    else CTCBS_SELECT((k_select_split<64, false>), grid, 64, sel_lds, l | sh << 28);
   } else {
     const dim3 grid(p.U);
 #define CTCBS_SELECT_LPS(BS)                                                              \

@@ -6,7 +6,7 @@
 // into device memory, and the batch-wide counters.  set[0..3]: the window words, set[4..]: lengths, then step caps.
 __global__ __launch_bounds__(256) void k_setup(Params p, const int32_t* set, int n_empty) {
   const int u = blockIdx.x * 256 + threadIdx.x;
-  if (u < p.U) { p.lens[u] = set[4 + u]; p.lmax[u] = set[4 + p.U + u]; }
+  if (u < p.U) { p.lens[u] = set[4 + u]; p.lmax[u] = set[4 + p.U + u]; p.uinfo[u].above0 = 0; }
   if (p.union_utt) {                                       // step 1: every hypothesis is empty, tau = tau~ = 0
     if (u < p.U) {
       int32_t* sh = p.union_win + 2 * ((size_t)p.U + u);   // (the first step's parity is 1)
@@ -77,7 +77,7 @@ __device__ __forceinline__ void init_state(const Params& p, const float* __restr
     const size_t h = hyp0 + tid;
     const bool first = tid == 0 && T > 0;
     HypRec r;
-    r.live = first; r.last = -1; r.rs = 0; r.re = T; r.tau = 0; r.tau_end = 0; r.ref = 0; r.pad = 0;
+    r.live = first; r.last = -1; r.rs = 0; r.re = T; r.tau = 0; r.tau_end = 0; r.ref = 0; r.near_frames = near_pack(0, T);
     r.off = 0.0; r.att = 0.0; r.joint = 0.0; r.bref = 0.0;
     p.rec[0][h] = r;
     // the other buffer: dead until the first selection fills it, but never left holding what the
@@ -90,9 +90,8 @@ __device__ __forceinline__ void init_state(const Params& p, const float* __restr
     p.trie_parent[h] = 0; p.trie_token[h] = -1; p.trie_tau[h] = 0;   // level 0: the empty hypothesis
   }
   if (tid == 64) {
-    UttInfo ui;
+    UttInfo& ui = p.uinfo[u];                              // (not above0: the tiles' work-groups set it meanwhile)
     ui.T = T; ui.lmax = p.lmax[u]; ui.BT = carry;          // (B_T: the running sum after the last frame; 0 for T = 0)
-    p.uinfo[u] = ui;
     UttState s;
     s.best_score = LOG0D; s.fb_score = LOG0D;
     for (int i = 0; i < MAX_END_M; ++i) { s.ring_score[i] = LOG0D; s.ring_tag[i] = -1; }
@@ -166,13 +165,16 @@ __global__ __launch_bounds__(256) void k_ingest(Params p, const float* __restric
       }
     }
   }
+  float top = 0.0f;
 #pragma unroll
   for (int i = 0; i < N4; ++i) {
     float4 c;
     c.x = fmaxf(r[i].x, LOG0F); c.y = fmaxf(r[i].y, LOG0F); c.z = fmaxf(r[i].z, LOG0F); c.w = fmaxf(r[i].w, LOG0F);
+    top = fmaxf(fmaxf(fmaxf(top, c.x), fmaxf(c.y, c.z)), c.w);
     const int t = w + (256 / LPF) * i;
     *(float4*)&tile[t][(4 * lane) ^ (((t >> 3) & 3) << 2)] = c;   // (swizzle: see the reads below)
   }
+  if (top > NEAR_X_MAX) atomicOr(&p.uinfo[u].above0, 1);   // (not a log-posterior)
   __syncthreads();
   float* dst = p.xT + (size_t)u * p.V * p.Tp;
 #pragma unroll

@@ -10,8 +10,8 @@
 //   2. window [s, e] from g's time indices (the two equations after Eq. (5));
 //   3. prefix score of every extension g.c: log-sum over t in [s, e] of
 //      f_t + log p^c(z_t = c), f_t = blank variable of g at t-1 if c repeats g's last label,
-//      else phi_{t-1}(g)  (Eq. (3) / Eq. (5)); frames run along lanes (16 or 64 lanes per
-//      candidate, float4 per lane), all of a lane's column loads are issued before the first
+//      else phi_{t-1}(g)  (Eq. (3) / Eq. (5)); frames run along lanes (16 lanes per
+//      candidate, float4 per lane), all of a lane's column loads of a round are issued before the first
 //      is consumed; their sums and the largest over the candidate's lanes are taken, then one fused
 //      multiply-add and one exp2 per term;
 //   4. eos score phi_T(g), joint scores (Eq. (1)), the eos-run test, and the group's
@@ -408,16 +408,24 @@ __device__ __forceinline__ unsigned long long joint_key(double J, unsigned long 
 // of the current buffer = p.rec[cur], p.uinfo, p.finished as words, the attention rows, Wb, p.V): as plain
 // leading arguments they are handed to the wave in registers when it starts (kernel-argument preload),
 // so that the record's load does not have to wait for a load of the argument block first.
+// CB candidates per chain of 16 lanes and round, IT float4 of each in flight.  Windows of up to 128 frames: 3 x 2, up to 192:
+// 2 x 3, both with a loop per candidate for what lies beyond; the same registers, and one more frame round costs what one
+// more candidate round does.  Wider windows, whole utterances: 3 x 2 with NEAR, rounds of all three candidates together, at
+// first over the frames near g's last label only (HypRec::near_frames).  500 frames, 16 utterances, beam 10, 40 candidates, peaked
+// posteriors: 11.5 -> 9.0 us a launch against 2 x 4 over all frames; flat ones: the same to 2 %, and against one candidate per wave
+// (4 float4 per lane) at 1500 frames a decode of 16 utterances 9.4 -> 7.2 ms.  With margins of 80 (long input, beam 20, 60
+// candidates) NEAR costs more than it saves, 51.0 -> 53.1 us: the launch is bound by its instructions, not by the columns.
 // NV4: granules of the row per lane.  BIGK: more candidates per hypothesis than one wave ranks (K > 64, or ids
 // beyond 65535).  Only that form of the
 // kernel carries the paths for it: candidate arrays in global memory when K exceeds the work-group, the exact
 // ranking by the whole work-group, the eos-run rule's work-group-wide path (a second sum beside the first in
 // the column pass, the test across all waves).  They cost registers that the common form does without.
-template <int BLOCK, int LPC, int CB, int IT, int NV4, bool BIGK>
-__global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT <= 6 ? 7 : 6) : 5))) void k_score(const HypRec* __restrict__ rec_now,
+template <int BLOCK, int CB, int IT, int NV4, bool NEAR, bool BIGK>
+__global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 6 : 7) : 5))) void k_score(const HypRec* __restrict__ rec_now,
                                                  const UttInfo* __restrict__ uinfo, const uint32_t* __restrict__ fin_words,
                                                  const float* __restrict__ att, int Wb, int V, int flags, int l,
                                                  ScoreArgs p) {
+  constexpr int LPC = 16;                                  // lanes per candidate: a DPP row
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ __align__(16) float s_mx[BLOCK];              // the lanes' maxima
   __shared__ int s_cnt[BLOCK / 64];                        // short list: entries per wave
@@ -559,6 +567,18 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
   const int W = e >= s ? e - s + 1 : 0;
   const int t0 = s & ~3;                                   // column loads start on a 16-byte boundary
   const int n4 = W > 0 ? ((e - t0) >> 2) + 1 : 0;
+  auto eos_run_armed = [&]() {
+    return (p.end_flags & 4) && p.eos_run > 0 && T >= p.eos_run && W > 0 && e == T && re == T && max(s, rs) <= T - p.eos_run + 1;
+  };
+  // NEAR: the float4 of the window that the sums run over at first, j0 .. j1 - 1, those with frames near g's last label (HypRec),
+  // and the sum from which on the others cannot count (eos-run rule armed: all to the window's end are among the first)
+  int j0 = 0, j1 = n4;
+  float sum_low = -3.0e38f;
+  if (NEAR && n4 > 0) {
+    const int a = max(s, (int)(rec.near_frames & 0xffffu) + 1), b = eos_run_armed() ? e : min(e, (int)(rec.near_frames >> 16) + 1);
+    if (a <= b) { j0 = (a - t0) >> 2; j1 = ((b - t0) >> 2) + 1; }
+    if (j1 - j0 < n4) sum_low = NEAR_MARGIN - NEAR_DEPTH + fast_logf((float)(4 * (n4 - (j1 - j0))));
+  }
   const float* gphi = p.gphi + (size_t)grp * p.Tp;
   const float* gb = p.gb + (size_t)grp * p.Tp;
   // Stored forward variables have the per-frame reference B_t taken out (see Params::Bcum); all
@@ -579,15 +599,14 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
 
   TRACE_MARK(1);
   const int R = p.eos_run;
-  const bool e2 = (p.end_flags & 4) && R > 0 && T >= R && W > 0 && e == T && re == T &&
-                  max(s, rs) <= T - R + 1;
+  const bool e2 = eos_run_armed();
   constexpr bool wave_rank = !BIGK;                        // the group's list is ranked by one wave on 64-bit keys
   // eos-run rule with few candidates: the f terms of the last R frames are kept apart (and left out of the
   // window's arrays), so that the sums below stop at frame T - R; the first wave completes them at the end
   const bool e2w = e2 && wave_rank;
   const bool e2g = BIGK && e2 && !wave_rank;               // the rule by the whole work-group (many candidates)
-  // the arrays hold whole rounds of LPC * IT float4 (log0 past the window's end), so that the sums need no bounds
-  const int n4r = max(1, (n4 + LPC * IT - 1) / (LPC * IT)) * (LPC * IT);
+  // the arrays hold whole rounds of LPC * IT float4 from j0 on (log0 past the window's end), so that the sums need no bounds
+  const int n4r = j0 + max(1, (n4 - j0 + LPC * IT - 1) / (LPC * IT)) * (LPC * IT);   // (not NEAR: j0 = 0)
   const double lam = p.lambda, jbase = (1.0 - lam) * acum + p.beta * (double)l;
   // eos-run rule: E_t = phi_t(g) of frame t = T-R+1+tid
   float e2_Et = LOG0F, e2_p = LOG0F;
@@ -737,10 +756,14 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
   float* g_catt = p.cand_att + (size_t)grp * K;
   double* g_ctc = p.cand_ctc + (size_t)grp * K;
   double* g_joint = p.cand_joint + (size_t)grp * K;
+  // more frames than one round of loads: where that is usual, the candidates' next rounds together
+  constexpr bool TOGETHER = BIGK || NEAR;
+  bool low = false;                                       // a sum that the frames left out may count for
   for (int cb = 0; cb < K; cb += NSG * CB) {              // (uniform: every chain takes part in every round)
     const int c0 = cb + sg;
     float4 x[CB][IT];
     int ids[CB];
+    ChainSum sum[CB];
 #pragma unroll
     for (int b = 0; b < CB; ++b) {
       const int c = c0 + b * NSG;
@@ -748,7 +771,34 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
       const float4* col = (const float4*)(xu + (size_t)(ids[b] < 0 ? 0 : ids[b]) * p.Tp + t0);
 #pragma unroll
       for (int it = 0; it < IT; ++it)                        // unconditional (clamped) loads: all in flight together
-        x[b][it] = col[min(q + it * LPC, max(n4 - 1, 0))];
+        x[b][it] = col[min(j0 + q + it * LPC, max(n4 - 1, 0))];
+    }
+    if (TOGETHER && !e2g) {
+      auto f_terms = [&](int b, int j, float4 (&f)[IT]) {
+        const float4* f4 = (const float4*)(s_F + ((ids[b] == last) ? p.wp_max : 0)) + j;
+#pragma unroll
+        for (int it = 0; it < IT; ++it) f[it] = f4[q + it * LPC];
+      };
+#pragma unroll
+      for (int b = 0; b < CB; ++b) {
+        float4 f[IT];
+        f_terms(b, j0, f);
+        sum[b] = chain_first<LPC, IT>(x[b], f);
+      }
+      for (int j = j0 + LPC * IT; j < j1; j += LPC * IT) {
+#pragma unroll
+        for (int b = 0; b < CB; ++b) {
+          const float4* col = (const float4*)(xu + (size_t)(ids[b] < 0 ? 0 : ids[b]) * p.Tp + t0);
+#pragma unroll
+          for (int it = 0; it < IT; ++it) x[b][it] = col[min(j + q + it * LPC, n4 - 1)];
+        }
+#pragma unroll
+        for (int b = 0; b < CB; ++b) {
+          float4 f[IT];
+          f_terms(b, j, f);
+          chain_more<LPC, IT>(sum[b], x[b], f);
+        }
+      }
     }
 #pragma unroll
     for (int b = 0; b < CB; ++b) {
@@ -759,17 +809,20 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
       const float4* f4 = (const float4*)(s_F + ((id == last) ? p.wp_max : 0));   // Fb follows F
       float inc = LOG0F, pre = LOG0F;
       if (!e2g) {
-        float4 f[IT];
+        if (!TOGETHER) {
+          float4 f[IT];
 #pragma unroll
-        for (int it = 0; it < IT; ++it) f[it] = f4[q + it * LPC];
-        ChainSum a = chain_first<LPC, IT>(x[b], f);
-        for (int i0 = LPC * IT; i0 < n4; i0 += LPC * IT) {   // (windows beyond one round of loads)
-          float4 y[IT];
+          for (int it = 0; it < IT; ++it) f[it] = f4[q + it * LPC];
+          sum[b] = chain_first<LPC, IT>(x[b], f);
+          for (int i0 = LPC * IT; i0 < n4; i0 += LPC * IT) { // (windows beyond one round of loads)
+            float4 y[IT];
 #pragma unroll
-          for (int it = 0; it < IT; ++it) { y[it] = col[min(i0 + q + it * LPC, n4 - 1)]; f[it] = f4[i0 + q + it * LPC]; }
-          chain_more<LPC, IT>(a, y, f);
+            for (int it = 0; it < IT; ++it) { y[it] = col[min(i0 + q + it * LPC, n4 - 1)]; f[it] = f4[i0 + q + it * LPC]; }
+            chain_more<LPC, IT>(sum[b], y, f);
+          }
         }
-        inc = chain_finish<LPC>(a);
+        inc = chain_finish<LPC>(sum[b]);
+        if (NEAR) low |= inc <= sum_low;
       } else {
         // the sum in two parts: frames up to T - R (needed on its own below) and the last R frames
         Lse a, aq;
@@ -814,6 +867,26 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (CB * IT
           if (e2) p.cand_pre[(size_t)grp * K + c] = pre;
         }
       }
+    }
+  }
+  if (NEAR && __ballot(low) != 0ull) {                     // (rare) such sums again, over the whole window
+    wave_lds_fence();
+#pragma unroll 1
+    for (int c = sg; c < K; c += NSG) {
+      if (!(s_inc[c] <= sum_low)) continue;                // uniform over the LPC lanes of a chain
+      const int id = cand_id(c);
+      const float4* col = (const float4*)(xu + (size_t)id * p.Tp + t0);
+      const float4* f4 = (const float4*)(s_F + ((id == last) ? p.wp_max : 0));
+      ChainSum a;
+      a.M = LOG0F; a.s = 0.0f;
+#pragma unroll 1
+      for (int j = 0; j < n4; j += LPC) {
+        const int i = min(j + q, n4 - 1);
+        const float4 y[1] = {col[i]}, f[1] = {j + q < n4 ? f4[i] : make_float4(LOG0F, LOG0F, LOG0F, LOG0F)};
+        chain_more<LPC, 1>(a, y, f);
+      }
+      const float inc = chain_finish<LPC>(a);
+      if (q == 0) s_inc[c] = inc;
     }
   }
 

@@ -72,7 +72,8 @@ __device__ __forceinline__ ArgMax lanes_argmax(ArgMax x) {
 // lane then replays its own frames).
 // LPS lanes share a survivor, 64 / LPS survivors a wave: 16 lanes x 8 frames cost a wave about 1.6 times the instructions
 // of 64 lanes x 2 frames and do four survivors instead of one, which is what counts once there are more survivors than
-// idle SIMDs; NWV = 4: the four waves of a work-group share one survivor (long windows of small batches).
+// idle SIMDs; NWV = 4: the four waves of a work-group share one survivor (long windows of small batches).  NEAR: the frames that
+// matter for the new hypothesis's sums are looked for (HypRec::near_frames).
 // The recurrence runs on the stored form of the variables (per-frame reference B_t taken out,
 // see Params::Bcum): with x'_t(c) = x_t(c) - max(x_t(blank), floor) and d_t = x_t(blank) -
 // max(x_t(blank), floor) (zero unless the floor cut),
@@ -88,6 +89,7 @@ struct SurvivorIn {
   int par, tok, s, en, rs, re, ptau, ptau_end, plast, pref;
   float inc;
   int T;            // frames of the utterance (bounds of every time index)
+  int above0;       // (see UttInfo)
 };
 
 // inclusive scan of affine maps over LPS lanes: lane t ends with map_0 then ... then map_t
@@ -105,11 +107,29 @@ struct SurvivorLds {                                       // NWV > 1
   Aff tot[2][4];                                           // the waves' composed maps (n, phi)
   float last_n, last_p;                                    // the values of the pass's last frame
   ArgMax best[2][4];
+  int near_lo[4], near_hi[4];
 };
+// smallest lo, largest hi over LPS lanes that hold ascending frames (lo > hi: none); result in all of them
+template <int LPS>
+__device__ __forceinline__ void lanes_range(int& lo, int& hi) {
+  if (LPS == 64) {
+    const unsigned long long m = __ballot(lo <= hi);
+    const int a = __builtin_amdgcn_readlane(lo, (__ffsll((long long)m) - 1) & 63), b = __builtin_amdgcn_readlane(hi, 63 - (__clzll((long long)m) & 63));
+    lo = m != 0ull ? a : 0x7fffffff; hi = m != 0ull ? b : -1;
+    return;
+  }
+  lo = row16_min_i(lo); hi = -row16_min_i(-hi);
+  if (LPS == 32) {
+    const bool up = (threadIdx.x & 32) != 0;
+    const int a = min(__builtin_amdgcn_readlane(lo, 0), __builtin_amdgcn_readlane(lo, 16)), b = min(__builtin_amdgcn_readlane(lo, 32), __builtin_amdgcn_readlane(lo, 48));
+    const int c = max(__builtin_amdgcn_readlane(hi, 0), __builtin_amdgcn_readlane(hi, 16)), d = max(__builtin_amdgcn_readlane(hi, 32), __builtin_amdgcn_readlane(hi, 48));
+    lo = up ? b : a; hi = up ? d : c;
+  }
+}
 
-template <int LPS, int FPL, int NWV>
+template <int LPS, int FPL, int NWV, bool NEAR>
 __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int n, bool active, const SurvivorIn& in,
-                                         SurvivorLds* sx, int& arg_n, int& arg_b, float& delta_out, double& bref_out) {
+                                         SurvivorLds* sx, int& arg_n, int& arg_b, uint32_t& near_out, float& delta_out, double& bref_out) {
   static_assert(FPL % 4 == 0 && (NWV == 1 || LPS == 64), "float4 per lane; waves share a survivor as wholes");
   constexpr int NQ = FPL / 4, SPAN = LPS * FPL * NWV;      // frames per pass
   const int lane = threadIdx.x & 63, w = NWV > 1 ? uni(threadIdx.x >> 6) : 0;
@@ -135,6 +155,7 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
   float carry_n = LOG0F, carry_p = LOG0F;
   ArgMax best_n, best_b;
   best_n.v = best_b.v = LOG0F; best_n.t = best_b.t = 0;
+  int near_lo = 0x7fffffff, near_hi = -1;
   for (int base = s & ~3; __ballot(base <= en) != 0ull; base += SPAN) {
     float gp[FPL], gb[FPL], x0[FPL], xc[FPL];
     double Bt[FPL];
@@ -207,7 +228,7 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
     // (stored + B_t; B relative to the child's reference)
     ArgMax xn, xb;
     xn.v = LOG0F; xn.t = t0; xb.v = LOG0F; xb.t = t0;
-    float rp[FPL], rb[FPL];
+    float rp[FPL], rb[FPL], near_v[FPL];
 #pragma unroll
     for (int k = 0; k < FPL; ++k) {
       const int t = t0 + k;
@@ -217,6 +238,7 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
       rb[k] = (!v[k] || bv < LOG0_CLASS) ? LOG0F : bv - delta;
       const bool ok = t >= lo;
       const float bt = (float)(Bt[k] - Bnew);
+      near_v[k] = v[k] ? rp[k] + bt : LOG0F;
       // (bt <= 0 from the child's reference frame on: what is log0 stays in its class)
       const float cn = ok ? rn + bt : LOG0F, cb = ok ? rb[k] + bt : LOG0F;
       if (cn > xn.v) { xn.v = cn; xn.t = t; }              // (strict: the earlier frame keeps a tie)
@@ -231,6 +253,14 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
         }
     }
     xn = lanes_argmax<LPS>(xn); xb = lanes_argmax<LPS>(xb);
+    if (NEAR && (NWV > 1 || p.want_near)) {                // (uniform)
+      int pass_lo = 0x7fffffff, pass_hi = -1;
+#pragma unroll
+      for (int k = FPL - 1; k >= 0; --k)
+        if (near_v[k] >= -NEAR_DEPTH) { pass_lo = t0 + k; pass_hi = max(pass_hi, t0 + k); }
+      lanes_range<LPS>(pass_lo, pass_hi);
+      near_lo = min(near_lo, pass_lo); near_hi = max(near_hi, pass_hi);
+    }
     if (xn.v > LOG0_CLASS && xn.v > best_n.v) best_n = xn;
     if (xb.v > LOG0_CLASS && xb.v > best_b.v) best_b = xb;
     if (__ballot(base + SPAN <= en) != 0ull) {             // (uniform) another pass: hand on the last frame's values
@@ -246,9 +276,11 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
     }
   }
   if (NWV > 1) {
-    if (lane == 0) { sx->best[0][w] = best_n; sx->best[1][w] = best_b; }
+    if (lane == 0) { sx->best[0][w] = best_n; sx->best[1][w] = best_b; sx->near_lo[w] = near_lo; sx->near_hi[w] = near_hi; }
     lds_barrier();
     best_n = sx->best[0][0]; best_b = sx->best[1][0];      // (waves hold ascending frames within a pass, not across passes)
+#pragma unroll
+    for (int i = 0; i < NWV; ++i) { near_lo = min(near_lo, sx->near_lo[i]); near_hi = max(near_hi, sx->near_hi[i]); }
 #pragma unroll
     for (int i = 1; i < NWV; ++i) {
       const ArgMax a = sx->best[0][i], b = sx->best[1][i];
@@ -258,14 +290,16 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
   }
   arg_n = best_n.v > LOG0_CLASS ? best_n.t : in.ptau;
   arg_b = best_b.v > LOG0_CLASS ? best_b.t : in.ptau_end;
+  near_out = in.above0 ? near_pack(0, T) : near_pack(near_lo, near_hi);
   delta_out = in.inc + (float)(Bold - Bnew);
   bref_out = Bnew;
 }
 
 // The form of least latency for windows of up to 128 frames: one wave, two frames per lane (any start; longer windows
 // in several passes).
+template <bool NEAR>
 __device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u, int n, const SurvivorIn& in,
-                                                  int& arg_n, int& arg_b, float& delta_out, double& bref_out) {
+                                                  int& arg_n, int& arg_b, uint32_t& near_out, float& delta_out, double& bref_out) {
   constexpr int FPL = 2;
   const int lane = threadIdx.x & 63;
   const size_t h0 = (size_t)u * Wb;
@@ -288,6 +322,7 @@ __device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u
   const int lo = max(s, in.ptau);
   float carry_n = LOG0F, carry_p = LOG0F;
   float best_n = LOG0F, best_b = LOG0F;
+  int near_lo = 0x7fffffff, near_hi = -1;
   arg_n = in.ptau; arg_b = in.ptau_end;
   for (int base = s; base <= en; base += 64 * FPL) {
     int t[FPL]; bool v[FPL]; double Bt[FPL];
@@ -342,6 +377,7 @@ __device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u
     // (stored + B_t; B relative to the child's reference)
     ArgMax xn, xb;
     xn.v = LOG0F; xn.t = t[0]; xb.v = LOG0F; xb.t = t[0];
+    float near_v[FPL];
 #pragma unroll
     for (int k = 0; k < FPL; ++k) {
       const float bv = (k == 0 ? p_in : pv[k > 0 ? k - 1 : 0]) + d[k];   // b_t = phi_{t-1} + d_t
@@ -351,14 +387,24 @@ __device__ __forceinline__ void wave_survivor(const SelectArgs& p, int Wb, int u
       if (v[k]) { cgp[t[k]] = rp; cgb[t[k]] = rb; }
       const bool ok = v[k] && t[k] >= lo;
       const float bt = (float)(Bt[k] - Bnew);
+      near_v[k] = v[k] ? rp + bt : LOG0F;
       const float cn = ok ? rn + bt : LOG0F, cb = ok ? rb + bt : LOG0F;   // (bt <= 0, as in `survivor`)
       if (cn > xn.v) { xn.v = cn; xn.t = t[k]; }           // (strict: the earlier frame keeps a tie)
       if (cb > xb.v) { xb.v = cb; xb.t = t[k]; }
     }
     xn = lanes_argmax<64>(xn); xb = lanes_argmax<64>(xb);
+    if (NEAR) {
+      int pass_lo = 0x7fffffff, pass_hi = -1;
+#pragma unroll
+      for (int k = FPL - 1; k >= 0; --k)
+        if (near_v[k] >= -NEAR_DEPTH) { pass_lo = t[k]; pass_hi = max(pass_hi, t[k]); }
+      lanes_range<64>(pass_lo, pass_hi);
+      near_lo = min(near_lo, pass_lo); near_hi = max(near_hi, pass_hi);
+    }
     if (xn.v > LOG0_CLASS && xn.v > best_n) { best_n = xn.v; arg_n = xn.t; }
     if (xb.v > LOG0_CLASS && xb.v > best_b) { best_b = xb.v; arg_b = xb.t; }
   }
+  near_out = in.above0 ? near_pack(0, T) : near_pack(near_lo, near_hi);
   delta_out = in.inc + (float)(Bold - Bnew);
   bref_out = Bnew;
 }
@@ -523,6 +569,7 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
   __shared__ double o_je[MAX_BEAM], o_hatt[MAX_BEAM], o_off[MAX_BEAM];
   __shared__ int s_fin;
   __shared__ int s_ntau[MAX_BEAM], s_ntau_end[MAX_BEAM];   // time indices of the new hypotheses
+  __shared__ uint32_t s_near[MAX_BEAM];                    // the frames that matter for their sums (HypRec)
   __shared__ float s_delta[MAX_BEAM];                      // by how much each new hypothesis was re-based
   __shared__ double s_bref[MAX_BEAM];                      // B at each new hypothesis's reference frame
 
@@ -617,7 +664,7 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
     const bool active = n < nu;
     const int e = active ? checked(p, s_sel[n], 0, NE - 1, ERR_LIST_ENTRY) : 0, par = (e * div_m) >> 16;
     SurvivorIn in;
-    in.par = par; in.T = T;
+    in.par = par; in.T = T; in.above0 = ui.above0;
     if (active) {
       in.tok = s_tok[e]; in.inc = s_inc[e];
       in.s = o_ws[par]; in.en = o_we[par]; in.rs = o_rs[par]; in.re = o_re[par];
@@ -626,13 +673,14 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
       in.tok = p.blank_id; in.inc = 0.0f; in.s = in.en = 1; in.rs = in.re = in.ptau = in.ptau_end = in.plast = in.pref = 0;
     }
     int arg_n, arg_b;
+    uint32_t near;
     float delta;
     double bref;
-    survivor<LPS, FPL, 1>(p, Wb, u, active ? n : 0, active, in, nullptr, arg_n, arg_b, delta, bref);
+    survivor<LPS, FPL, 1, (LPS > 16)>(p, Wb, u, active ? n : 0, active, in, nullptr, arg_n, arg_b, near, delta, bref);
     if (active && (lane & (LPS - 1)) == LPS - 1) {
       p.out[3 * UW + h0 + n] = arg_n; p.out[4 * UW + h0 + n] = arg_b;
       p.trie[(size_t)2 * p.trie_stride + h0 + n] = arg_n;
-      s_ntau[n] = arg_n; s_ntau_end[n] = arg_b; s_delta[n] = delta; s_bref[n] = bref;
+      s_ntau[n] = arg_n; s_ntau_end[n] = arg_b; s_near[n] = near; s_delta[n] = delta; s_bref[n] = bref;
     }
   }
   lds_barrier();                       // (the survivors' state stores stay in flight)
@@ -647,7 +695,7 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
       p.trie[h] = par; p.trie[p.trie_stride + h] = tok;
       HypRec r;
       r.live = fin ? 0 : 1; r.last = tok; r.rs = o_ws[par]; r.re = o_we[par];
-      r.tau = s_ntau[n]; r.tau_end = s_ntau_end[n]; r.ref = o_tau[par]; r.pad = 0;
+      r.tau = s_ntau[n]; r.tau_end = s_ntau_end[n]; r.ref = o_tau[par]; r.near_frames = s_near[n];
       r.off = o_off[par] + (double)s_delta[n];
       r.att = o_hatt[par] + (double)s_att[e];
       r.joint = s_J[e];
@@ -684,11 +732,12 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
 // host knows from the window margins), and for beams above 12 (one wave holds 192 list entries), it is four: all of them
 // load, the first one ranks, and all share the recurrence of a window of more than 128 frames.  (Per launch, windows of
 // 101 frames, one wave / four: beam 4, 64 utterances 7.0 / 7.4 us, beam 12, 64 utterances 7.8 / 8.1, 128 9.0 / 10.2.)
+// NEAR: where the score kernel looks at near_frames (one wave: never; found everywhere it cost 1.3 % of a decode at margins of 80).
 // Dynamic LDS: 36 * NP + 32 bytes, NP = Wb * Wb rounded up to whole waves (the list entries and the packed keys).
 // The arguments in front of the block are what the first round of loads needs: plain leading arguments reach the wave
 // in registers when it starts (kernel-argument preload), so that those loads do not wait for a load of the arguments.
 // Grid: (1 << sh, Wb, ceil(U / (1 << sh))), sh = l >> 28: utterance z * 2^sh + x, new slot y (as in k_score).
-template <int BLOCK>
+template <int BLOCK, bool NEAR>
 __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
                                                         const GroupOut* __restrict__ grp, const ListEntry* __restrict__ grp_list,
                                                         const UttInfo* __restrict__ uinfo, int Wb_m, int l_sh, int U, SelectArgs p) {
@@ -803,16 +852,17 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
     if (hyp) {
       const int e = e_n;
       SurvivorIn in;
-      in.par = par; in.tok = uni(s_tok[e]); in.inc = s_inc[e]; in.T = T;
+      in.par = par; in.tok = uni(s_tok[e]); in.inc = s_inc[e]; in.T = T; in.above0 = ui.above0;
       in.s = par_s; in.en = par_e;
       in.rs = __builtin_amdgcn_readlane(pv, 2); in.re = __builtin_amdgcn_readlane(pv, 3);
       in.ptau = __builtin_amdgcn_readlane(pv, 4); in.ptau_end = __builtin_amdgcn_readlane(pv, 5);
       in.plast = __builtin_amdgcn_readlane(pv, 6); in.pref = __builtin_amdgcn_readlane(pv, 7);
       int arg_n, arg_b;
+      uint32_t near;
       float delta;
       double bref;
-      if (WIDE && shared) survivor<64, 4, BLOCK / 64>(p, Wb, u, n, true, in, &s_sx, arg_n, arg_b, delta, bref);
-      else wave_survivor(p, Wb, u, n, in, arg_n, arg_b, delta, bref);
+      if (WIDE && shared) survivor<64, 4, BLOCK / 64, NEAR>(p, Wb, u, n, true, in, &s_sx, arg_n, arg_b, near, delta, bref);
+      else wave_survivor<NEAR>(p, Wb, u, n, in, arg_n, arg_b, near, delta, bref);
       if (tid == 0) {
         p.out[3 * UW + h] = arg_n; p.out[4 * UW + h] = arg_b;
         p.trie[(size_t)2 * p.trie_stride + h] = arg_n;
@@ -821,6 +871,7 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
         // (the record's live flag belongs to the utterance's lead work-group, see below)
         HypRec* r = p.rec_new + h;
         r->last = in.tok; r->rs = in.s; r->re = in.en; r->tau = arg_n; r->tau_end = arg_b; r->ref = in.ptau;
+        if (NEAR) r->near_frames = near;
         r->off = o_off[par] + (double)delta;
         r->att = o_hatt[par] + (double)s_att[e];
         r->joint = s_J[e];

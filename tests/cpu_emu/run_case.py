@@ -17,7 +17,7 @@ import paper_2101_05600_amd as m  # noqa: E402
 m._SO = sys.argv[1]          # the binding loads this instead of the GPU library (tests only)
 
 import gen  # noqa: E402
-from helpers import EmuDecoder, lockstep_decode  # noqa: E402
+from helpers import EmuDecoder, lockstep_decode, peaked_ctc  # noqa: E402
 
 CASES = {
     # split select kernel, 16-lane score kernel, eos-run rule, an unused slot
@@ -55,6 +55,9 @@ CASES = {
     # rule armed (its one-wave walk through the last frames after a two-part sum whose second part is empty)
     "wide_window_eos_run": (dict(n_utt=2, vocab=40, beam=2, cand_k=6, win_m1=70, win_m2=70, end_flags=7, eos_run=3,
                                  max_len_ratio=0.4), [22, 15]),
+    # whole utterances, peaked posteriors: sums over the frames near the last label; ids so unlikely that all frames are summed
+    "near_frames": (dict(n_utt=2, vocab=40, beam=2, cand_k=20, win_m1=-1, win_m2=-1, end_flags=7, eos_run=3,
+                         max_len_ratio=0.0, max_len_abs=4), [150, 61]),
     # logits in, odd vocabulary (radix selection), one candidate per hypothesis
     "logits_odd_vocab": (dict(n_utt=1, vocab=33, beam=2, cand_k=1, win_m1=3, win_m2=8, end_flags=2, att_is_logits=1,
                               max_len_ratio=0.4), [13]),
@@ -148,6 +151,9 @@ def main():
         ctc = gen.workload_ctc(w, np.maximum(lens, 1))
         used = [u for u in range(len(lens)) if lens[u] > 0]
         kw = {}
+        if name == "near_frames":
+            peaked_ctc(ctc, 3, ids=np.arange(20, 38))
+            ctc[:, :, 1:8] = -70.0
         if name == "radix_wide_ties":
             flat = lambda a: np.where(np.isnan(a), a, np.float32(-11.0)).astype(np.float32)
             kw = dict(att_fn=flat, gpu_att_fn=flat)

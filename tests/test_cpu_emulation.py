@@ -83,6 +83,7 @@ def runs(tmp_path_factory):
         # the first steps of a fixed subset of the random configurations that tests/test_gpu_random_configs.py
         # decodes on the GPU (same table, tests/random_cases.py), device memory starting out as garbage
         "asan_random": (asan, ASAN_ENV, dict(sanitize=True), *[[f"random:{a}:{b}:{c}"] for a, b, c in CPU_SUBSET]),
+        "asan_near": (asan, ASAN_ENV, dict(sanitize=True), ["near_frames"]),
         # the select kernel of large batches
         "asan_per_utterance": (asan, ASAN_ENV, dict(sanitize=True, defines=["CTCBS_SPLIT_GROUPS=0"]), ["windowed"], ["batch_window"]),
         # executor: the job queue with two host threads on two handles
@@ -100,7 +101,7 @@ def runs(tmp_path_factory):
         with ThreadPoolExecutor(max_workers=len(children)) as ex:
             rs = list(ex.map(lambda cases: _run(so, runtime, env, cases), children))
         return subprocess.CompletedProcess(rs[0].args, max(abs(r.returncode) for r in rs), "".join(r.stdout for r in rs), "".join(r.stderr for r in rs))
-    with ThreadPoolExecutor(max_workers=5) as ex:
+    with ThreadPoolExecutor(max_workers=6) as ex:
         futs = {k: ex.submit(one, k) for k in plan}
         return {k: f.result() for k, f in futs.items()}
 
@@ -124,6 +125,13 @@ def test_select_kernel_of_large_batches_under_address_sanitizer(runs):
     assert r.returncode == 0, out[-4000:]
     assert "ERROR: AddressSanitizer" not in out and "runtime error:" not in out, out[-4000:]
     assert out.count("emu ok") == 2, out[-2000:]
+
+
+def test_sums_over_near_frames_under_address_sanitizer(runs):
+    r, out = _result(runs, "asan_near")
+    assert r.returncode == 0, out[-4000:]
+    assert "ERROR: AddressSanitizer" not in out and "runtime error:" not in out, out[-4000:]
+    assert out.count("emu ok") == 1, out[-2000:]
 
 
 def test_random_configurations_first_steps_under_address_sanitizer(runs):

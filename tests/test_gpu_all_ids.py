@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import gen
-from helpers import lockstep_decode
+from helpers import lockstep_decode, peaked_ctc
 
 pytestmark = pytest.mark.gpu
 
@@ -59,16 +59,7 @@ def test_sums_beyond_the_range_of_the_product(value):
 # rest underflows against the largest), which moves along the utterance and is read alone; rows end inside a block of frames
 @pytest.mark.parametrize("every,lens,over", [(5, [330, 199], {}), (3, [129, 64], dict(beam=17)), (40, [300, 161], {}), (5, [200, 97], dict(win_m1=60, win_m2=30))])
 def test_short_stretches_of_frames(every, lens, over):
-    def edit(ctc):
-        rng = np.random.RandomState(every)
-        for u in range(ctc.shape[0]):
-            z = rng.randn(*ctc.shape[1:])
-            z[:, 0] += 14.0
-            at = np.arange(2, ctc.shape[1], every)
-            z[at, 0] -= 14.0
-            z[at, rng.randint(1, 98, len(at))] += 14.0
-            ctc[u] = z - np.log(np.exp(z).sum(-1, keepdims=True))
-    _decode(**dict(dict(vocab=100, beam=5, lens=lens, edit=edit, steps=14), **over))
+    _decode(**dict(dict(vocab=100, beam=5, lens=lens, edit=lambda c: peaked_ctc(c, every), steps=14), **over))
 
 
 # candidates can be looked at without keep_candidates: the score kernel's own list, the matrix form, sets through memory
