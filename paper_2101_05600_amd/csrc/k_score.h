@@ -42,8 +42,8 @@ __device__ __forceinline__ float key_to_att(uint32_t k) {
 // ---- candidate selection -----------------------------------------------------------------
 // An attention row in the registers of a work-group: 16-byte granules of it (granule g = ids head + 4 g ..
 // + 3, g = tid + k * BLOCK), and the at most six ids before the first and after the last whole granule of
-// a row that does not start or end on a 16-byte boundary (ex, of id ex_id, in the first lanes).  Ids past the
-// row's end, blank and eos hold -inf.
+// a row that does not start or end on a 16-byte boundary (ex, of id ex_id, in the first lanes; -inf in the others).
+// Granules past the row's end hold the last one again.
 template <int NV4>
 struct RowRegs {
   float4 v[NV4];
@@ -130,20 +130,21 @@ __device__ __forceinline__ int collect_hits(const RowRegs<NV4>& r, const float (
     pack(tid < r.n_ex && r.ex >= L, make_float4(r.ex, ninf, ninf, ninf), r.ex_id);
   }
   wave_lds_fence();
-  const bool linf = (L == -__builtin_huge_valf());         // then excluded ids (held as -inf) are hits too
+  const bool linf = (L == -__builtin_huge_valf());         // then blank and eos are hits too (there may be no K candidates)
   int n = 0;
   const int nv = 4 * min(ngr, ShortList::GCAP);
   for (int i0 = 0; i0 < nv; i0 += 64) {
     const int i = i0 + lane;
     const float val = i < nv ? ((const float*)gran)[i] : 0.0f;
     const int id = i < nv ? gid[i >> 2] + (i & 3) : 0;
-    const bool hit = i < nv && val >= L;
+    const bool none = id == blank_id || id == eos_id;      // not a candidate
+    const bool hit = i < nv && val >= L && (linf || !none);
     const unsigned long long b = __ballot(hit);
     if (hit) {
       const int pos = n + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u));
       const uint32_t u = __float_as_uint(val);
       uint32_t key = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-      if (linf && (id == blank_id || id == eos_id)) key = 0u;   // below a genuine -inf
+      if (none) key = 0u;                                  // below a genuine -inf
       if (pos < ShortList::WCAP) ent[pos] = ((unsigned long long)key << 32) | (uint32_t)~id;
     }
     n += __popcll(b);
@@ -525,9 +526,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
   // the ids is the same, only the values the scores use are shifted by the row's log-sum-exp)
   const bool logits = (p.mode & SC_LOGITS) != 0;
   float row_lse = 0.0f;
-  float x_blank = 0.0f;
   const float x_eos = arow[p.eos_id];
-  if (logits) x_blank = arow[p.blank_id];
   if (logits && !in_regs) {
     float m = -3.0e38f, sum = 0.0f;
     for (int i = tid; i < V; i += BLOCK) m = fmaxf(m, arow[i]);
@@ -650,47 +649,36 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
   if (p.mode & SC_RESTRICTED) {
     bool ok = false;
     if (in_regs) {
-      // ids past the row's end, blank and eos never compete: hold them as -inf
-      const float ninf = -__builtin_huge_valf();
-      const int gb4 = p.blank_id - row.head, ge4 = p.eos_id - row.head;   // (negative: among the first lanes' ids)
-#pragma unroll
-      for (int k = 0; k < NV4; ++k) {
-        if ((k + 1) * BLOCK > ng && tid + k * BLOCK >= ng) row.v[k] = make_float4(ninf, ninf, ninf, ninf);
-        auto drop = [&](int g) {                           // (uniform test first: one register of NV4, one lane)
-          if (g >= 4 * k * BLOCK && g < 4 * (k + 1) * BLOCK && (g >> 2) - k * BLOCK == tid) {
-            if ((g & 3) == 0) row.v[k].x = ninf;
-            if ((g & 3) == 1) row.v[k].y = ninf;
-            if ((g & 3) == 2) row.v[k].z = ninf;
-            if ((g & 3) == 3) row.v[k].w = ninf;
-          }
-        };
-        drop(gb4); drop(ge4);
-      }
-      if (tid < row.n_ex && (row.ex_id == p.blank_id || row.ex_id == p.eos_id)) row.ex = ninf;
-      float m4[NV4], fmx = row.ex;                         // the granules' maxima, the lane's
+      // The granules' maxima, the lane's.  Blank and eos are among them: the pivot is one that two lanes more reach, and the
+      // list leaves them out (taken out here, they cost ten branches: a short launch, one utterance, 8.0 -> 7.6 us).
+      float m4[NV4], fmx = row.ex;
 #pragma unroll
       for (int k = 0; k < NV4; ++k) {
         m4[k] = fmaxf(fmaxf(row.v[k].x, row.v[k].y), fmaxf(row.v[k].z, row.v[k].w));
+        if (tid + k * BLOCK >= ng) m4[k] = __builtin_nanf("");   // (past the row's end: never a hit, whatever the pivot)
         fmx = fmaxf(fmx, m4[k]);
       }
       TRACE_MARK(6);
       s_mx[tid] = fmx;
       lds_barrier();
-      // at least K values are >= L (-inf if there are not K lanes with finite maxima)
+      // at least K values of candidates are >= L (-inf if there are not K + 2 lanes with finite maxima)
       float M;
-      const float L = find_pivot<BLOCK>(s_mx, K, M);
+      const float L = find_pivot<BLOCK>(s_mx, K + 2, M);
       TRACE_MARK(7);
       const int nh = collect_hits<BLOCK, NV4>(row, m4, L, p.blank_id, p.eos_id, s_gran + w * ShortList::GCAP,
                                               s_gid + w * ShortList::GCAP, s_ent + w * ShortList::WCAP);
       if ((tid & 63) == 0) s_cnt[w] = nh;
       TRACE_MARK(14);
       if (logits) {
-        M = fmaxf(fmaxf(M, -3.0e38f), fmaxf(x_blank, x_eos));
+        M = fmaxf(M, -3.0e38f);
         float sum = __expf(row.ex - M);
+        int t = tid;
+        LOADED(t);                                         // (or the lanes within the row are kept from above, in scalar registers)
 #pragma unroll
-        for (int k = 0; k < NV4; ++k)
-          sum += (__expf(row.v[k].x - M) + __expf(row.v[k].y - M)) + (__expf(row.v[k].z - M) + __expf(row.v[k].w - M));
-        if (tid == 0) sum += __expf(x_blank - M) + __expf(x_eos - M);
+        for (int k = 0; k < NV4; ++k) {
+          const float s4 = (__expf(row.v[k].x - M) + __expf(row.v[k].y - M)) + (__expf(row.v[k].z - M) + __expf(row.v[k].w - M));
+          sum += t + k * BLOCK < ng ? s4 : 0.0f;
+        }
         sum = row16_sum(sum);
         const double ws = ((double)lane_f(sum, 0) + (double)lane_f(sum, 16)) +
                           ((double)lane_f(sum, 32) + (double)lane_f(sum, 48));
