@@ -4,8 +4,8 @@
 //      registers.  A pivot that is provably not above the K-th largest value (K of the lanes' maxima
 //      reach it; found by bisection with ballots), then
 //      a short list of the few values that reach it (about 1.2 K), then the K largest of these: up to
-//      64 entries are ranked by every wave for itself, one per lane; more, or equal values at the
-//      K-th place, by the work-group.  Rows that do not fit the registers, or with so many values at the
+//      64 entries are ranked one per lane, the waves sharing the comparisons; more, or equal values at the
+//      K-th place, by quads of lanes.  Rows that do not fit the registers, or with so many values at the
 //      pivot that the short list overflows (heavy ties), take a radix select that re-reads the row.
 //   2. window [s, e] from g's time indices (the two equations after Eq. (5));
 //   3. prefix score of every extension g.c: log-sum over t in [s, e] of
@@ -38,6 +38,11 @@ struct __align__(64) DenseSlot {
 __device__ __forceinline__ float key_to_att(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
+
+// base[i], base the same for all lanes and i < 2^30: the byte offset stays in 32 bits, beside a scalar base (an index that
+// may be negative costs a lane four instructions for its 64-bit address)
+template <class T>
+__device__ __forceinline__ T at32(const T* base, int i) { return *(const T*)((const char*)base + (uint32_t)i * (uint32_t)sizeof(T)); }
 
 // ---- candidate selection -----------------------------------------------------------------
 // An attention row in the registers of a work-group: 16-byte granules of it (granule g = ids head + 4 g ..
@@ -153,20 +158,27 @@ __device__ __forceinline__ int collect_hits(const RowRegs<NV4>& r, const float (
   return ngr > ShortList::GCAP ? ShortList::WCAP + 1 : n;
 }
 
-// The K largest of a short list of at most 64 entries, by every wave for itself and without a barrier: each lane holds
-// an entry, the entries are broadcast one after the other (readlane) and every lane counts those above its own.  (A
-// bisection with ballots until exactly K entries are left takes twice as long.)  ids: this wave's copy of their ids, best
-// first; s_av: their values, by the first wave.  False (in all waves alike) if equal values straddle the K-th place.
-__device__ __forceinline__ bool take_k(const unsigned long long* s_ent, const ShortList& sl, int K, int32_t* ids, float* s_av) {
-  const int lane = threadIdx.x & 63;
+// The K largest of a short list of at most 64 entries.  In every wave each lane holds an entry; a wave broadcasts a quarter of
+// the entries one after the other (readlane), every lane counts those above its own, and the quarters' counts meet in LDS
+// (s_part: a byte per wave and entry).  Each wave for itself over all of them, without the exchange and its barrier, takes a
+// tenth more instructions per work-group: decodes of 64 utterances 2842 -> 2797 us, of 512 8546 -> 8438, of one the same.  (A bisection with ballots until exactly K entries are left takes twice as
+// long.)  ids: this wave's copy of their ids; s_av: their values, by the first wave.  False (in all waves alike) if equal
+// values straddle the K-th place.
+__device__ __forceinline__ bool take_k(int w, const unsigned long long* s_ent, const ShortList& sl, int K, uint32_t* s_part, int32_t* ids, float* s_av) {
+  const int lane = threadIdx.x & 63, turned = (lane + 16 * w) & 63;   // (the wave's quarter: its lanes 0 to 15)
   const unsigned long long me = s_ent[sl.at(min(lane, sl.n - 1))];
-  const int rank = lanes_above<16>(lane < sl.n ? (uint32_t)(me >> 32) : 0u, sl.n);   // (constant lane numbers: three instructions an entry)
+  const uint32_t v = ((const uint32_t*)s_ent)[2 * sl.at(min(turned, sl.n - 1)) + 1];
+  const int above = lanes_above<16>(turned < sl.n ? v : 0u, 16);
+  ((uint8_t*)s_part)[4 * turned + w] = (uint8_t)above;
+  lds_barrier();
+  const int rank = (int)((s_part[lane] * 0x01010101u) >> 24);   // (the bytes' sum, at most 63)
   const bool take = lane < sl.n && rank < K;
-  if (__popcll(__ballot(take)) != K) return false;         // (equal values have equal ranks)
-  const int pos = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(__ballot(take) >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)__ballot(take), 0u));
+  const unsigned long long b = __ballot(take);
+  if (__popcll(b) != K) return false;                      // (equal values have equal ranks)
+  const int pos = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u));
   if (take) {
     ids[pos] = (int)~(uint32_t)me;
-    if (threadIdx.x < 64) s_av[pos] = key_to_att((uint32_t)(me >> 32));
+    if (w == 0) s_av[pos] = key_to_att((uint32_t)(me >> 32));
   }
   return true;
 }
@@ -468,8 +480,8 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
   auto fetch_row = [&]() {
     const float4* a4 = (const float4*)(arow + row.head);
 #pragma unroll
-    for (int k = 0; k < NV4; ++k) row.v[k] = a4[min(tid + k * BLOCK, ng - 1)];
-    if (tid < row.n_ex) row.ex = arow[row.ex_id];
+    for (int k = 0; k < NV4; ++k) row.v[k] = at32(a4, min(tid + k * BLOCK, ng - 1));
+    if (tid < row.n_ex) row.ex = at32(arow, row.ex_id);
   };
   PIN4(rec.live, rec.off, ui.BT, fin_word);
   PIN4(p.xT, p.Bcum, p.gphi, p.gb);
@@ -591,8 +603,8 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
   // used after the candidate selection: nothing waits for it before.
   auto in_range = [&](int t) { return t >= s && t <= e && t - 1 >= rs && t - 1 <= re; };   // frame t has an f term
   const int pr0 = min(max(t0 + tid - 1, 0), T);
-  const float f0_p = gphi[pr0], f0_b = gb[pr0];
-  const double f0_B = Bu[pr0];
+  const float f0_p = at32(gphi, pr0), f0_b = at32(gb, pr0);
+  const double f0_B = at32(Bu, pr0);
   float eos_p = LOG0F;
   if (rs <= T && re >= T) eos_p = gphi[T];
 
@@ -610,7 +622,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
   // eos-run rule: E_t = phi_t(g) of frame t = T-R+1+tid
   float e2_Et = LOG0F, e2_p = LOG0F;
   double e2_B = 0.0;
-  if (e2 && tid < R) { const int t = T - R + 1 + tid; e2_p = gphi[t]; e2_B = Bu[t]; }
+  if (e2 && tid < R) { const int t = T - R + 1 + tid; e2_p = at32(gphi, t); e2_B = at32(Bu, t); }
   // The f terms of the window into LDS:
   // gamma_{t-1}(g) - off' - B_r = stored_{t-1} + (B_{t-1} - B_r); far from r the second part is
   // large and coarse in fp32, and the term is then negligible by that same factor
@@ -620,7 +632,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
 
     for (int i = tid; i < 4 * n4r; i += BLOCK) {
       const int t = t0 + i;
-      if (i >= BLOCK) { const int pr = min(max(t - 1, 0), T); ph = gphi[pr]; b = gb[pr]; B = Bu[pr]; }
+      if (i >= BLOCK) { const int pr = min(max(t - 1, 0), T); ph = at32(gphi, pr); b = at32(gb, pr); B = at32(Bu, pr); }
       float f = LOG0F, fb = LOG0F;
       if (in_range(t)) {
         const float bt = (float)(B - Bref);
@@ -698,7 +710,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
         if (tid == 128) s_lse = row_lse;
       }
       if (!BIGK && ok && sl.n <= 64) {
-        direct = take_k(s_ent, sl, K, s_wid + 64 * w, s_av);
+        direct = take_k(w, s_ent, sl, K, (uint32_t*)s_mx, s_wid + 64 * w, s_av);
         wave_lds_fence();
       }
       if (ok && !direct) {
@@ -740,6 +752,12 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
   constexpr int NSG = BLOCK / LPC;
   const int sg = tid / LPC, q = tid % LPC;
   const float* xu = p.xT + (size_t)u * V * p.Tp;
+  // float4 i of a candidate's column from frame t0 on.  At most 65536 ids of 6176 frames: 32 bits hold the offset
+  auto column = [&](int id, int i) {
+    if (BIGK) return ((const float4*)(xu + (size_t)id * p.Tp + t0))[i];
+    const uint32_t row = (uint32_t)__umul24((unsigned)id, (unsigned)(4 * p.Tp));
+    return *(const float4*)((const char*)xu + (row + 4u * (uint32_t)t0 + 16u * (uint32_t)i));
+  };
   float* g_inc = p.cand_inc + (size_t)grp * K;
   float* g_catt = p.cand_att + (size_t)grp * K;
   double* g_ctc = p.cand_ctc + (size_t)grp * K;
@@ -756,10 +774,9 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
     for (int b = 0; b < CB; ++b) {
       const int c = c0 + b * NSG;
       ids[b] = (c < K) ? cand_id(c) : -1;
-      const float4* col = (const float4*)(xu + (size_t)(ids[b] < 0 ? 0 : ids[b]) * p.Tp + t0);
 #pragma unroll
       for (int it = 0; it < IT; ++it)                        // unconditional (clamped) loads: all in flight together
-        x[b][it] = col[min(j0 + q + it * LPC, max(n4 - 1, 0))];
+        x[b][it] = column(max(ids[b], 0), min(j0 + q + it * LPC, max(n4 - 1, 0)));
     }
     if (TOGETHER && !e2g) {
       auto f_terms = [&](int b, int j, float4 (&f)[IT]) {
@@ -776,9 +793,8 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
       for (int j = j0 + LPC * IT; j < j1; j += LPC * IT) {
 #pragma unroll
         for (int b = 0; b < CB; ++b) {
-          const float4* col = (const float4*)(xu + (size_t)(ids[b] < 0 ? 0 : ids[b]) * p.Tp + t0);
 #pragma unroll
-          for (int it = 0; it < IT; ++it) x[b][it] = col[min(j + q + it * LPC, n4 - 1)];
+          for (int it = 0; it < IT; ++it) x[b][it] = column(max(ids[b], 0), min(j + q + it * LPC, n4 - 1));
         }
 #pragma unroll
         for (int b = 0; b < CB; ++b) {
@@ -793,7 +809,6 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
       const int c = c0 + b * NSG;
       if (ids[b] < 0) continue;                            // uniform over the LPC lanes of a chain
       const int id = ids[b];
-      const float4* col = (const float4*)(xu + (size_t)id * p.Tp + t0);
       const float4* f4 = (const float4*)(s_F + ((id == last) ? p.wp_max : 0));   // Fb follows F
       float inc = LOG0F, pre = LOG0F;
       if (!e2g) {
@@ -805,7 +820,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
           for (int i0 = LPC * IT; i0 < n4; i0 += LPC * IT) { // (windows beyond one round of loads)
             float4 y[IT];
 #pragma unroll
-            for (int it = 0; it < IT; ++it) { y[it] = col[min(i0 + q + it * LPC, n4 - 1)]; f[it] = f4[i0 + q + it * LPC]; }
+            for (int it = 0; it < IT; ++it) { y[it] = column(id, min(i0 + q + it * LPC, n4 - 1)); f[it] = f4[i0 + q + it * LPC]; }
             chain_more<LPC, IT>(sum[b], y, f);
           }
         }
@@ -823,7 +838,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
             const int tb = t0 + 4 * i;
             float4 fv;
             const float4 f = f4[i];
-            const float4 xv = i0 == 0 ? x[b][it] : col[min(i, n4 - 1)];
+            const float4 xv = i0 == 0 ? x[b][it] : column(id, min(i, n4 - 1));
             fv.x = tb <= tc ? f.x : LOG0F; fv.y = tb + 1 <= tc ? f.y : LOG0F;
             fv.z = tb + 2 <= tc ? f.z : LOG0F; fv.w = tb + 3 <= tc ? f.w : LOG0F;
             a = lse_join(a, lse_block(xv, fv));
@@ -863,14 +878,13 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
     for (int c = sg; c < K; c += NSG) {
       if (!(s_inc[c] <= sum_low)) continue;                // uniform over the LPC lanes of a chain
       const int id = cand_id(c);
-      const float4* col = (const float4*)(xu + (size_t)id * p.Tp + t0);
       const float4* f4 = (const float4*)(s_F + ((id == last) ? p.wp_max : 0));
       ChainSum a;
       a.M = LOG0F; a.s = 0.0f;
 #pragma unroll 1
       for (int j = 0; j < n4; j += LPC) {
         const int i = min(j + q, n4 - 1);
-        const float4 y[1] = {col[i]}, f[1] = {j + q < n4 ? f4[i] : make_float4(LOG0F, LOG0F, LOG0F, LOG0F)};
+        const float4 y[1] = {column(id, i)}, f[1] = {j + q < n4 ? f4[i] : make_float4(LOG0F, LOG0F, LOG0F, LOG0F)};
         chain_more<LPC, 1>(a, y, f);
       }
       const float inc = chain_finish<LPC>(a);
