@@ -423,18 +423,18 @@ __device__ __forceinline__ unsigned long long joint_key(double J, unsigned long 
 // so that the record's load does not have to wait for a load of the argument block first.
 // CB candidates per chain of 16 lanes and round, IT float4 of each in flight.  Windows of up to 128 frames: 3 x 2, up to 192:
 // 2 x 3, both with a loop per candidate for what lies beyond; the same registers, and one more frame round costs what one
-// more candidate round does.  Wider windows, whole utterances: 3 x 2 with NEAR, rounds of all three candidates together, at
-// first over the frames near g's last label only (HypRec::near_frames).  500 frames, 16 utterances, beam 10, 40 candidates, peaked
-// posteriors: 11.5 -> 9.0 us a launch against 2 x 4 over all frames; flat ones: the same to 2 %, and against one candidate per wave
-// (4 float4 per lane) at 1500 frames a decode of 16 utterances 9.4 -> 7.2 ms.  With margins of 80 (long input, beam 20, 60
-// candidates) NEAR costs more than it saves, 51.0 -> 53.1 us: the launch is bound by its instructions, not by the columns.
+// more candidate round does.  Wider windows, whole utterances: 3 x 2, rounds of all three candidates together.  NEAR, all but the
+// first: at first over the frames near g's last label only (HypRec::near_frames).  500 frames, 16 utterances, beam 10, 40
+// candidates, peaked posteriors: 11.5 -> 9.0 us a launch against 2 x 4 over all frames; flat ones: the same to 2 %, and against one
+// candidate per wave (4 float4 per lane) at 1500 frames a decode of 16 utterances 9.4 -> 7.2 ms.  Margins of 80 (256 utterances of
+// 1500 frames, beam 20, 60 candidates): a decode 14362 -> 14167 us; with 3 x 2 there 14530.  The first form has nothing to gain.
 // NV4: granules of the row per lane.  BIGK: more candidates per hypothesis than one wave ranks (K > 64, or ids
 // beyond 65535).  Only that form of the
 // kernel carries the paths for it: candidate arrays in global memory when K exceeds the work-group, the exact
 // ranking by the whole work-group, the eos-run rule's work-group-wide path (a second sum beside the first in
 // the column pass, the test across all waves).  They cost registers that the common form does without.
 template <int BLOCK, int CB, int IT, int NV4, bool NEAR, bool BIGK>
-__global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 6 : 7) : 5))) void k_score(const HypRec* __restrict__ rec_now,
+__global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR && IT == 2 ? 6 : 7) : 5))) void k_score(const HypRec* __restrict__ rec_now,
                                                  const UttInfo* __restrict__ uinfo, const uint32_t* __restrict__ fin_words,
                                                  const float* __restrict__ att, int Wb, int V, int flags, int l,
                                                  ScoreArgs p) {
@@ -582,11 +582,11 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
     return (p.end_flags & 4) && p.eos_run > 0 && T >= p.eos_run && W > 0 && e == T && re == T && max(s, rs) <= T - p.eos_run + 1;
   };
   // NEAR: the float4 of the window that the sums run over at first, j0 .. j1 - 1, those with frames near g's last label (HypRec),
-  // and the sum from which on the others cannot count (eos-run rule armed: all to the window's end are among the first)
+  // and the sum from which on the others cannot count (eos-run rule armed: all frames, the sums stop short of the last ones)
   int j0 = 0, j1 = n4;
   float sum_low = -3.0e38f;
-  if (NEAR && n4 > 0) {
-    const int a = max(s, (int)(rec.near_frames & 0xffffu) + 1), b = eos_run_armed() ? e : min(e, (int)(rec.near_frames >> 16) + 1);
+  if (NEAR && n4 > 0 && !eos_run_armed()) {
+    const int a = max(s, (int)(rec.near_frames & 0xffffu) + 1), b = min(e, (int)(rec.near_frames >> 16) + 1);
     if (a <= b) { j0 = (a - t0) >> 2; j1 = ((b - t0) >> 2) + 1; }
     if (j1 - j0 < n4) sum_low = NEAR_MARGIN - NEAR_DEPTH + fast_logf((float)(4 * (n4 - (j1 - j0))));
   }
@@ -763,7 +763,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
   double* g_ctc = p.cand_ctc + (size_t)grp * K;
   double* g_joint = p.cand_joint + (size_t)grp * K;
   // more frames than one round of loads: where that is usual, the candidates' next rounds together
-  constexpr bool TOGETHER = BIGK || NEAR;
+  constexpr bool TOGETHER = BIGK || (NEAR && IT == 2);
   bool low = false;                                       // a sum that the frames left out may count for
   for (int cb = 0; cb < K; cb += NSG * CB) {              // (uniform: every chain takes part in every round)
     const int c0 = cb + sg;
@@ -815,9 +815,9 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR ? 
         if (!TOGETHER) {
           float4 f[IT];
 #pragma unroll
-          for (int it = 0; it < IT; ++it) f[it] = f4[q + it * LPC];
+          for (int it = 0; it < IT; ++it) f[it] = f4[j0 + q + it * LPC];
           sum[b] = chain_first<LPC, IT>(x[b], f);
-          for (int i0 = LPC * IT; i0 < n4; i0 += LPC * IT) { // (windows beyond one round of loads)
+          for (int i0 = j0 + LPC * IT; i0 < j1; i0 += LPC * IT) { // (windows beyond one round of loads)
             float4 y[IT];
 #pragma unroll
             for (int it = 0; it < IT; ++it) { y[it] = column(id, min(i0 + q + it * LPC, n4 - 1)); f[it] = f4[i0 + q + it * LPC]; }
