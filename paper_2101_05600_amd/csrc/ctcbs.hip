@@ -344,9 +344,7 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
   hipError_t ea = allow_lds((const void*)k_score<BLOCK, CB, IT, NV4, NEAR, BIGK>, h->score_smem_bytes);
   if (ea != hipSuccess) return ea;
   const int in_regs = p.restricted && p.V >= 8 && p.V <= 4 * NV4 * BLOCK ? 1 : 0;
-  // (from eight utterances on no work-group is idle for it.  Below, measured since: 1 to 7 utterances of 437 frames
-  // would gain 0.1 us here and 0.4 in the select kernel, 2 to 4 % of a decode, from the same grouping)
-  const int sh = p.U >= 8 ? 3 : 0;
+  const int sh = 3;                              // (also below eight utterances: one of 437 frames 1090 -> 1035 us a decode)
   const int flags = in_regs | sh << 4;
   const dim3 grid(1u << sh, (unsigned)p.Wb, (unsigned)(p.U + (1 << sh) - 1) >> sh);
   ScoreArgs a;
@@ -498,7 +496,7 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   hipLaunchKernelGGL(K, G, dim3(BS), LDS, h->stream, (const HypRec*)p.rec[h->cur], p.utt, (const GroupOut*)p.grp, \
                      (const ListEntry*)p.grp_list, (const UttInfo*)p.uinfo, wb_m, L, (int)p.U, a)
   if (split) {
-    const int sh = p.U >= 8 ? 3 : 0;
+    const int sh = 3;
     const dim3 grid(1u << sh, (unsigned)p.Wb + 1, (unsigned)(p.U + (1 << sh) - 1) >> sh);
     if (h->score_form != 0) CTCBS_SELECT((k_select_split<256, true>), grid, 256, sel_lds, l | sh << 28);
     else if (h->select_wide || p.Wb > 12) CTCBS_SELECT((k_select_split<256, false>), grid, 256, sel_lds, l | sh << 28);
