@@ -22,6 +22,8 @@
 
 static thread_local int g_last_hip = 0;
 
+#define CTCBS_EARLY_GROUPS 256    // groups up to which the score kernel fetches rows before records (k_score: flags)
+
 #ifndef CTCBS_SPLIT_GROUPS         // (the CPU build of the tests sets 0: small batches through the other kernel)
 #define CTCBS_SPLIT_GROUPS 2048   // (utterance, beam slot) groups up to which the split select kernel runs, see step_impl
 #endif
@@ -345,7 +347,7 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
   if (ea != hipSuccess) return ea;
   const int in_regs = p.restricted && p.V >= 8 && p.V <= 4 * NV4 * BLOCK ? 1 : 0;
   const int sh = 3;                              // (also below eight utterances: one of 437 frames 1090 -> 1035 us a decode)
-  const int flags = in_regs | sh << 4;
+  const int flags = in_regs | (p.U * p.Wb <= CTCBS_EARLY_GROUPS ? 2 : 0) | sh << 4;
   const dim3 grid(1u << sh, (unsigned)p.Wb, (unsigned)(p.U + (1 << sh) - 1) >> sh);
   ScoreArgs a;
   a.xT = p.xT; a.Bcum = p.Bcum; a.gphi = p.gphi[h->cur]; a.gb = p.gb[h->cur]; a.grp_list = p.grp_list; a.grp = p.grp;
@@ -359,7 +361,7 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
   a.cand_joint = p.cand_joint; a.trace = p.trace;
   hipLaunchKernelGGL((k_score<BLOCK, CB, IT, NV4, NEAR, BIGK>), grid, dim3(BLOCK), h->score_smem_bytes,
                      h->stream, (const HypRec*)p.rec[h->cur], (const UttInfo*)p.uinfo, (const uint32_t*)p.finished,
-                     att, (int)p.Wb, (int)p.V, flags, l, a);
+                     att, (int)p.Wb, (int)p.V, flags, l, (int)p.U, a);
   return hipGetLastError();
 }
 

@@ -416,7 +416,9 @@ __device__ __forceinline__ unsigned long long joint_key(double J, unsigned long 
 // Grid: (1 << sh, Wb, ceil(U / (1 << sh))), sh = bits 4-7 of flags: utterance z * 2^sh + x, beam slot y.  With sh = 3 the
 // work-groups of an utterance share an XCD (work-groups go round-robin over the eight), and with it the L2 in
 // which a column that several beam slots score is fetched once.
-// flags bit 0: the whole row can be held in registers (NV4 * BLOCK granules).
+// flags bit 0: the whole row can be held in registers (NV4 * BLOCK granules); bit 1: rows are fetched before the record says
+// that there is a hypothesis (up to a work-group per compute unit: the dead slots' rows cost nobody's bandwidth then; one
+// utterance 1021 -> 1011 us a decode, 21 with a batch-wide window 1443 -> 1432, 16 whole utterances within the noise).
 // The arguments in front of the parameter block are what the first loads of a work-group need (the records
 // of the current buffer = p.rec[cur], p.uinfo, p.finished as words, the attention rows, Wb, p.V): as plain
 // leading arguments they are handed to the wave in registers when it starts (kernel-argument preload),
@@ -436,7 +438,7 @@ __device__ __forceinline__ unsigned long long joint_key(double J, unsigned long 
 template <int BLOCK, int CB, int IT, int NV4, bool NEAR, bool BIGK>
 __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR && IT == 2 ? 6 : 7) : 5))) void k_score(const HypRec* __restrict__ rec_now,
                                                  const UttInfo* __restrict__ uinfo, const uint32_t* __restrict__ fin_words,
-                                                 const float* __restrict__ att, int Wb, int V, int flags, int l,
+                                                 const float* __restrict__ att, int Wb, int V, int flags, int l, int U,
                                                  ScoreArgs p) {
   constexpr int LPC = 16;                                  // lanes per candidate: a DPP row
   extern __shared__ __align__(16) unsigned char smem[];
@@ -466,7 +468,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   TRACE_DECL;
   // ---------------- the attention row -----------------------------------------------------------
   // As soon as the record says that the slot holds a hypothesis its row is fetched, all loads in
-  // flight together (a dead slot fetches nothing).  Whole 16-byte granules by the lanes in turn; what a row that
+  // flight together (a dead slot fetches nothing); in small batches without asking the record.  Whole 16-byte granules by the lanes in turn; what a row that
   // is not aligned has before and after them by the first lanes.
   const float* arow = att + (size_t)grp * V;
   const bool in_regs = (flags & 1) != 0;
@@ -483,6 +485,8 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
     for (int k = 0; k < NV4; ++k) row.v[k] = at32(a4, min(tid + k * BLOCK, ng - 1));
     if (tid < row.n_ex) row.ex = at32(arow, row.ex_id);
   };
+  const bool early = (flags & 2) != 0;
+  if (in_regs && early && u < U) fetch_row();
   PIN4(rec.live, rec.off, ui.BT, fin_word);
   PIN4(p.xT, p.Bcum, p.gphi, p.gb);
   PIN4(p.grp_list, p.grp, p.lambda, p.beta);
@@ -490,7 +494,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   // (not all of the block: with four more the scalar registers run out and part of it is loaded twice, 35 -> 36.6 us
   // a launch at 512 utterances)
   const int dead = (int)((fin_word >> (8 * (u & 3))) & 0xffu) | (rec.live == 0);
-  if (in_regs && !dead) fetch_row();
+  if (in_regs && !early && !dead) fetch_row();
   const int K = p.K;
   const bool smallk = !BIGK || (K <= BLOCK);
   const int T = ui.T;
@@ -505,13 +509,13 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
       p.union_win[2 * ((l + 1) & 1) + 1] = -1;
     }
   }
-  if ((p.mode & SC_UNION_UTT) && blockIdx.y == 0 && tid == BLOCK - 1 && u < p.U) {
+  if ((p.mode & SC_UNION_UTT) && blockIdx.y == 0 && tid == BLOCK - 1 && u < U) {
     int32_t* sh_u = p.union_win + 2 * ((size_t)((l + 1) & 1) * p.U + u);
     sh_u[0] = 0x7fffffff; sh_u[1] = -1;
   }
   if (dead) {
     // (the grid is whole eights of utterances; those past the last are dead here too)
-    if (tid == 0 && u < p.U) p.grp[grp] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
+    if (tid == 0 && u < U) p.grp[grp] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
     return;
   }
 
