@@ -10,6 +10,7 @@
 // log0 is the finite sentinel -1e30 (anything below -1e29 is treated as log0).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #define CTCBS_WAVE 64
@@ -198,15 +199,19 @@ struct ScoreArgs {
   const float* xT;
   const double* Bcum;
   const float *gphi, *gb;    // of the current buffer
-  ListEntry* grp_list;
-  GroupOut* grp;
   double lambda, beta;
   int32_t Tp, K, blank_id, eos_id, win_m1, win_m2, end_flags, eos_run;
   int32_t wp_max, off_f, off_small;   // LDS layout: floats per f array, byte offsets
-  int32_t mode, U;           // mode: SC_* bits
-  int32_t pad;
+  int32_t mode;              // SC_* bits
   int32_t* err;
-  // not needed early
+};
+// those that it needs late, or not every time: read where they are used (score_late), not held from the start.  Loaded early with
+// the others they ran the kernel out of scalar registers: 16 to 20 went into lanes of a vector register at once, so that the first
+// thing every wave did was to wait for its arguments, and the record was asked for a trip to memory later (one utterance
+// 1011 -> 1005 us a decode, 512 8380 -> 8338).
+struct ScoreLate {
+  ListEntry* grp_list;
+  GroupOut* grp;
   int32_t* union_win;
   const int32_t* n_finished;
   unsigned long long* host_progress;
@@ -215,6 +220,26 @@ struct ScoreArgs {
   double *cand_ctc, *cand_joint;
   unsigned long long* trace;
 };
+struct ScoreKernarg {        // all of them, as they lie in the kernel's argument segment
+  const HypRec* rec_now;
+  const UttInfo* uinfo;
+  const uint32_t* fin_words;
+  const float* att;
+  int32_t Wb, V, flags, l, U;
+  ScoreArgs p;
+  ScoreLate late;
+};
+#if defined(__AMDGCN__)
+typedef const __attribute__((address_space(4))) ScoreLate* ScoreLatePtr;
+__device__ __forceinline__ ScoreLatePtr score_late(const ScoreLate&) {
+  const __attribute__((address_space(4))) char* k = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
+  __asm__("" : "+s"(k));                                   // (else the compiler loads and holds them with the others)
+  return (ScoreLatePtr)(k + offsetof(ScoreKernarg, late));
+}
+#else
+typedef const ScoreLate* ScoreLatePtr;
+__device__ __forceinline__ ScoreLatePtr score_late(const ScoreLate& q) { return &q; }
+#endif
 enum { SC_RESTRICTED = 1, SC_LOGITS = 2, SC_UNION = 4, SC_KEEP = 8, SC_UNION_UTT = 16, SC_PAIRS = 32 };
 
 // arguments of the select kernels behind the preloaded ones
@@ -290,9 +315,8 @@ __device__ __forceinline__ void report(const P& p, int bad) {
 
 // For the host's non-blocking look: the step that has begun and the count of utterances finished before it, in one
 // 64-bit store to pinned host memory (uncached: it needs no fence to arrive).
-template <class P>
-__device__ __forceinline__ void publish_progress(const P& p, int l) {
-  *(volatile unsigned long long*)p.host_progress = ((unsigned long long)(unsigned)l << 32) | (unsigned)*p.n_finished;
+__device__ __forceinline__ void publish_progress(unsigned long long* host_progress, const int32_t* n_finished, int l) {
+  *(volatile unsigned long long*)host_progress = ((unsigned long long)(unsigned)l << 32) | (unsigned)*n_finished;
 }
 
 __device__ __forceinline__ uint32_t near_pack(int lo, int hi) { return lo <= hi ? (uint32_t)lo | (uint32_t)hi << 16 : 0xffffu; }

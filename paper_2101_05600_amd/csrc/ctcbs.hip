@@ -350,18 +350,20 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
   const int flags = in_regs | (p.U * p.Wb <= CTCBS_EARLY_GROUPS ? 2 : 0) | sh << 4;
   const dim3 grid(1u << sh, (unsigned)p.Wb, (unsigned)(p.U + (1 << sh) - 1) >> sh);
   ScoreArgs a;
-  a.xT = p.xT; a.Bcum = p.Bcum; a.gphi = p.gphi[h->cur]; a.gb = p.gb[h->cur]; a.grp_list = p.grp_list; a.grp = p.grp;
+  a.xT = p.xT; a.Bcum = p.Bcum; a.gphi = p.gphi[h->cur]; a.gb = p.gb[h->cur];
   a.lambda = p.lambda; a.beta = p.beta;
   a.Tp = p.Tp; a.K = p.K; a.blank_id = p.blank_id; a.eos_id = p.eos_id; a.win_m1 = p.win_m1; a.win_m2 = p.win_m2;
   a.end_flags = p.end_flags; a.eos_run = p.eos_run; a.wp_max = h->wp_max; a.off_f = h->off_f; a.off_small = h->off_small;
   a.mode = (p.restricted ? SC_RESTRICTED : 0) | (p.att_logits ? SC_LOGITS : 0) | (p.win_union ? SC_UNION : 0) |
            (p.keep_cand == KEEP_ARRAYS ? SC_KEEP : 0) | (p.keep_cand == KEEP_PAIRS ? SC_PAIRS : 0) | (p.union_utt ? SC_UNION_UTT : 0);
-  a.U = p.U; a.pad = 0; a.err = p.err; a.union_win = p.union_win; a.n_finished = p.n_finished; a.host_progress = p.host_progress;
-  a.cand_id = p.cand_id; a.cand_inc = p.cand_inc; a.cand_att = p.cand_att; a.cand_pre = p.cand_pre; a.cand_ctc = p.cand_ctc;
-  a.cand_joint = p.cand_joint; a.trace = p.trace;
+  a.err = p.err;
+  ScoreLate b;
+  b.grp_list = p.grp_list; b.grp = p.grp; b.union_win = p.union_win; b.n_finished = p.n_finished; b.host_progress = p.host_progress;
+  b.cand_id = p.cand_id; b.cand_inc = p.cand_inc; b.cand_att = p.cand_att; b.cand_pre = p.cand_pre; b.cand_ctc = p.cand_ctc;
+  b.cand_joint = p.cand_joint; b.trace = p.trace;
   hipLaunchKernelGGL((k_score<BLOCK, CB, IT, NV4, NEAR, BIGK>), grid, dim3(BLOCK), h->score_smem_bytes,
                      h->stream, (const HypRec*)p.rec[h->cur], (const UttInfo*)p.uinfo, (const uint32_t*)p.finished,
-                     att, (int)p.Wb, (int)p.V, flags, l, (int)p.U, a);
+                     att, (int)p.Wb, (int)p.V, flags, l, (int)p.U, a, b);
   return hipGetLastError();
 }
 

@@ -439,7 +439,7 @@ template <int BLOCK, int CB, int IT, int NV4, bool NEAR, bool BIGK>
 __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR && IT == 2 ? 6 : 7) : 5))) void k_score(const HypRec* __restrict__ rec_now,
                                                  const UttInfo* __restrict__ uinfo, const uint32_t* __restrict__ fin_words,
                                                  const float* __restrict__ att, int Wb, int V, int flags, int l, int U,
-                                                 ScoreArgs p) {
+                                                 ScoreArgs p, ScoreLate late_args) {
   constexpr int LPC = 16;                                  // lanes per candidate: a DPP row
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ __align__(16) float s_mx[BLOCK];              // the lanes' maxima
@@ -489,7 +489,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   if (in_regs && early && u < U) fetch_row();
   PIN4(rec.live, rec.off, ui.BT, fin_word);
   PIN4(p.xT, p.Bcum, p.gphi, p.gb);
-  PIN4(p.grp_list, p.grp, p.lambda, p.beta);
+  PIN4(p.lambda, p.beta, p.off_f, p.mode);
   PIN4(p.Tp, p.K, p.win_m1, p.eos_run);
   // (not all of the block: with four more the scalar registers run out and part of it is loaded twice, 35 -> 36.6 us
   // a launch at 512 utterances)
@@ -502,20 +502,21 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   const int rs = rec.rs, re = rec.re, last = rec.last;
   const double off = rec.off, acum = rec.att;
   if (grp == 0 && tid == BLOCK - 1) {                      // (not in wave 0, which finishes last)
-    publish_progress(p, l);
+    const ScoreLatePtr q = score_late(late_args);
+    publish_progress(q->host_progress, q->n_finished, l);
     // batch-wide window: clear the slot the select kernel of this step will fill for the next one
     if (!(p.mode & SC_UNION_UTT)) {
-      p.union_win[2 * ((l + 1) & 1)] = 0x7fffffff;
-      p.union_win[2 * ((l + 1) & 1) + 1] = -1;
+      q->union_win[2 * ((l + 1) & 1)] = 0x7fffffff;
+      q->union_win[2 * ((l + 1) & 1) + 1] = -1;
     }
   }
   if ((p.mode & SC_UNION_UTT) && blockIdx.y == 0 && tid == BLOCK - 1 && u < U) {
-    int32_t* sh_u = p.union_win + 2 * ((size_t)((l + 1) & 1) * p.U + u);
+    int32_t* sh_u = score_late(late_args)->union_win + 2 * ((size_t)((l + 1) & 1) * U + u);
     sh_u[0] = 0x7fffffff; sh_u[1] = -1;
   }
   if (dead) {
     // (the grid is whole eights of utterances; those past the last are dead here too)
-    if (tid == 0 && u < U) p.grp[grp] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
+    if (tid == 0 && u < U) score_late(late_args)->grp[grp] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
     return;
   }
 
@@ -536,7 +537,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   float* s_inc = (float*)(s_cid + Ks);
   float* s_av = s_inc + Ks;
   float* s_pre = s_av + Ks;                                // BIGK: prefix score without the last R frames
-  int32_t* g_cid = p.cand_id + (size_t)grp * K;
+  int32_t* g_cid = BIGK ? score_late(late_args)->cand_id + (size_t)grp * K : nullptr;   // (many candidates, like the others below)
 
   // raw scores in: the row holds unnormalised scores; log_softmax is folded in here (the order of
   // the ids is the same, only the values the scores use are shifted by the row's log-sum-exp)
@@ -557,8 +558,8 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   if (p.mode & SC_UNION) {            // s^l = min_ij s_ij, e^l = max_ij e_ij (last two equations of Sec. 3.2.3)
     int lo = 0x7fffffff, hi = -1;
     if (p.mode & SC_UNION_UTT) {                           // the unfinished utterances' shares together
-      const int32_t* shares = p.union_win + 2 * (size_t)(l & 1) * p.U;
-      for (int i = tid; i < p.U; i += BLOCK)
+      const int32_t* shares = score_late(late_args)->union_win + 2 * (size_t)(l & 1) * U;
+      for (int i = tid; i < U; i += BLOCK)
         if (((fin_words[i >> 2] >> (8 * (i & 3))) & 0xffu) == 0u) { lo = min(lo, shares[2 * i]); hi = max(hi, shares[2 * i + 1]); }
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) { lo = min(lo, __shfl_xor(lo, o)); hi = max(hi, __shfl_xor(hi, o)); }
@@ -568,7 +569,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
       for (int i = 0; i < BLOCK / 64; ++i) { lo = min(lo, s_cnt[i]); hi = max(hi, (int)s_scan[i]); }
       lo = uni(lo); hi = uni(hi);
       lds_barrier();                                       // (both arrays serve the selection below)
-    } else { lo = p.union_win[2 * (l & 1)]; hi = p.union_win[2 * (l & 1) + 1]; }
+    } else { const int32_t* share = score_late(late_args)->union_win + 2 * (l & 1); lo = share[0]; hi = share[1]; }
     if (p.win_m1 >= 0) s = max(s, lo - p.win_m1);
     if (p.win_m2 >= 0) e = min(e, hi);
   } else {
@@ -762,10 +763,13 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
     const uint32_t row = (uint32_t)__umul24((unsigned)id, (unsigned)(4 * p.Tp));
     return *(const float4*)((const char*)xu + (row + 4u * (uint32_t)t0 + 16u * (uint32_t)i));
   };
-  float* g_inc = p.cand_inc + (size_t)grp * K;
-  float* g_catt = p.cand_att + (size_t)grp * K;
-  double* g_ctc = p.cand_ctc + (size_t)grp * K;
-  double* g_joint = p.cand_joint + (size_t)grp * K;
+  float *g_inc = nullptr, *g_catt = nullptr, *g_pre = nullptr;
+  double *g_ctc = nullptr, *g_joint = nullptr;
+  if (BIGK) {
+    const ScoreLatePtr a = score_late(late_args);
+    const size_t g = (size_t)grp * K;
+    g_inc = a->cand_inc + g; g_catt = a->cand_att + g; g_ctc = a->cand_ctc + g; g_joint = a->cand_joint + g; g_pre = a->cand_pre + g;
+  }
   // more frames than one round of loads: where that is usual, the candidates' next rounds together
   constexpr bool TOGETHER = BIGK || (NEAR && IT == 2);
   bool low = false;                                       // a sum that the frames left out may count for
@@ -871,7 +875,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
           if (e2) s_pre[c] = pre;
         } else {
           g_inc[c] = inc; g_catt[c] = av; g_ctc[c] = ctc; g_joint[c] = J;
-          if (e2) p.cand_pre[(size_t)grp * K + c] = pre;
+          if (e2) g_pre[c] = pre;
         }
       }
     }
@@ -933,7 +937,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
         float xv[E2C];
 #pragma unroll
         for (int k = 0; k < E2C; ++k) xv[k] = colf[min(T - R + 1 + k0 + k, T)];   // all loads in flight
-        float acc = smallk ? s_pre[c] : p.cand_pre[(size_t)grp * K + c];
+        float acc = smallk ? s_pre[c] : g_pre[c];
 #pragma unroll
         for (int k = 0; k < E2C; ++k) {
           if (k0 + k < R) {
@@ -941,7 +945,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
             xmax[k] = fmaxf(xmax[k], canon0(acc));
           }
         }
-        if (smallk) s_pre[c] = acc; else p.cand_pre[(size_t)grp * K + c] = acc;
+        if (smallk) s_pre[c] = acc; else g_pre[c] = acc;
       }
 #pragma unroll
       for (int k = 0; k < E2C; ++k) {                      // max over the wave, one slot per wave and frame
@@ -970,7 +974,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   }
   auto group_outputs = [&](int n) {
     const double je = s_eos[1];
-    p.grp[grp] = GroupOut{n, fire, s, e, s_eos[0],
+    score_late(late_args)->grp[grp] = GroupOut{n, fire, s, e, s_eos[0],
                           logits && je > (double)LOG0_CLASS ? je - s_eos[4] * (double)row_lse : je,
                           (long long)K * (long long)W, {0, 0, 0, 0, 0, 0}};
   };
@@ -1040,11 +1044,13 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
                                               has && valid && J == J);
       const int rank = lanes_above<16>(me, K);             // (lanes past the last entry hold zeros)
       const int nv = __popcll(__ballot(me != 0ull));
-      if (!fire && me != 0ull && rank < Wb) p.grp_list[(size_t)grp * Wb + rank] = ListEntry{J, id, inc, av, 0};
+      if (!fire && me != 0ull && rank < Wb) score_late(late_args)->grp_list[(size_t)grp * Wb + rank] = ListEntry{J, id, inc, av, 0};
       if (tid == 0) group_outputs(fire ? 0 : min(nv, Wb));
-      if ((p.mode & SC_PAIRS) && has) ((double2*)p.cand_joint)[(size_t)grp * K + tid] = double2{J, ctc};
+      if ((p.mode & SC_PAIRS) && has) ((double2*)score_late(late_args)->cand_joint)[(size_t)grp * K + tid] = double2{J, ctc};
       if ((p.mode & SC_KEEP) && has) {
-        g_cid[tid] = id; g_inc[tid] = inc; g_catt[tid] = av; g_ctc[tid] = ctc; g_joint[tid] = J;
+        const ScoreLatePtr a = score_late(late_args);
+        const size_t g = (size_t)grp * K + tid;
+        a->cand_id[g] = id; a->cand_inc[g] = inc; a->cand_att[g] = av; a->cand_ctc[g] = ctc; a->cand_joint[g] = J;
       }
     } else {
       // rank by (joint desc, token asc), exact comparison: four lanes per candidate
@@ -1065,7 +1071,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
           rank += dpp_i<0xB1, 0xf>(0, rank);               // quad_perm [1,0,3,2]
           rank += dpp_i<0x4E, 0xf>(0, rank);               // quad_perm [2,3,0,1]
           if (part == 0 && mv) {
-            if (rank < Wb) p.grp_list[(size_t)grp * Wb + rank] = ListEntry{me, s_cid[ee], s_inc[ee], s_av[ee], 0};
+            if (rank < Wb) score_late(late_args)->grp_list[(size_t)grp * Wb + rank] = ListEntry{me, s_cid[ee], s_inc[ee], s_av[ee], 0};
             atomicAdd(&s_nvalid, 1);
           }
         }
@@ -1083,7 +1089,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
     }
   }
   TRACE_MARK(5);
-  TRACE_FLUSH(p, grp);
+  TRACE_FLUSH(*score_late(late_args), grp);
 }
 
 // Group list for candidate sets whose joint scores lie in global memory (K > block size, or every id a candidate): one
