@@ -314,9 +314,16 @@ __device__ __forceinline__ void report(const P& p, int bad) {
 }
 
 // For the host's non-blocking look: the step that has begun and the count of utterances finished before it, in one
-// 64-bit store to pinned host memory (uncached: it needs no fence to arrive).
+// 64-bit store to pinned host memory (uncached: it needs no fence to arrive, and nothing here waits for it: as a volatile
+// store, with the count through the vector path, the wave waited for its row, for the count and for the bus).  By one wave.
 __device__ __forceinline__ void publish_progress(unsigned long long* host_progress, const int32_t* n_finished, int l) {
-  *(volatile unsigned long long*)host_progress = ((unsigned long long)(unsigned)l << 32) | (unsigned)*n_finished;
+#if defined(__AMDGCN__)
+  const int n = *(const __attribute__((address_space(4))) int32_t*)(unsigned long long)n_finished;   // (written by earlier kernels only)
+  if ((threadIdx.x & 63) == 0)
+    __hip_atomic_store(host_progress, (unsigned long long)(unsigned)l << 32 | (unsigned)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+#else
+  if ((threadIdx.x & 63) == 0) *(volatile unsigned long long*)host_progress = (unsigned long long)(unsigned)l << 32 | (unsigned)*n_finished;
+#endif
 }
 
 __device__ __forceinline__ uint32_t near_pack(int lo, int hi) { return lo <= hi ? (uint32_t)lo | (uint32_t)hi << 16 : 0xffffu; }

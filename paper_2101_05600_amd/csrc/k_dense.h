@@ -59,7 +59,7 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
   const size_t h = (size_t)u * Wb + j;
   const HypRec r = p.rec[cur][h];
   const UttInfo ui = p.uinfo[u];
-  if (h == 0 && tid == BLOCK - 1) publish_progress(p.host_progress, p.n_finished, l);
+  if (h == 0 && w == BLOCK / 64 - 1) publish_progress(p.host_progress, p.n_finished, l);
   const int T = ui.T;
   DenseSlot* slot = p.dense_slot + h;
   if (p.finished[u] || !r.live) {

@@ -501,11 +501,11 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   const int tau = rec.tau, tau_end = rec.tau_end;
   const int rs = rec.rs, re = rec.re, last = rec.last;
   const double off = rec.off, acum = rec.att;
-  if (grp == 0 && tid == BLOCK - 1) {                      // (not in wave 0, which finishes last)
+  if (grp == 0 && w == BLOCK / 64 - 1) {                   // (not in wave 0, which finishes last)
     const ScoreLatePtr q = score_late(late_args);
     publish_progress(q->host_progress, q->n_finished, l);
     // batch-wide window: clear the slot the select kernel of this step will fill for the next one
-    if (!(p.mode & SC_UNION_UTT)) {
+    if (!(p.mode & SC_UNION_UTT) && tid == BLOCK - 1) {
       q->union_win[2 * ((l + 1) & 1)] = 0x7fffffff;
       q->union_win[2 * ((l + 1) & 1) + 1] = -1;
     }
