@@ -233,8 +233,9 @@ struct ScoreKernarg {        // all of them, as they lie in the kernel's argumen
 typedef const __attribute__((address_space(4))) ScoreLate* ScoreLatePtr;
 __device__ __forceinline__ ScoreLatePtr score_late(const ScoreLate&) {
   const __attribute__((address_space(4))) char* k = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
-  __asm__("" : "+s"(k));                                   // (else the compiler loads and holds them with the others)
-  return (ScoreLatePtr)(k + offsetof(ScoreKernarg, late));
+  uint32_t at;
+  __asm__ volatile("s_movk_i32 %0, %1" : "=s"(at) : "i"(offsetof(ScoreKernarg, late)));   // (a constant it could see, the compiler
+  return (ScoreLatePtr)(k + at);                           // would load from early and hold with the others)
 }
 #else
 typedef const ScoreLate* ScoreLatePtr;

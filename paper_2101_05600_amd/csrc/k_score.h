@@ -1089,7 +1089,10 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
     }
   }
   TRACE_MARK(5);
-  TRACE_FLUSH(*score_late(late_args), grp);
+#ifdef CTCBS_TRACE
+  const struct { unsigned long long* trace; } tr_to = {score_late(late_args)->trace};
+  TRACE_FLUSH(tr_to, grp);
+#endif
 }
 
 // Group list for candidate sets whose joint scores lie in global memory (K > block size, or every id a candidate): one
