@@ -83,8 +83,8 @@ __device__ __forceinline__ ArgMax lanes_argmax(ArgMax x) {
 // tau the child's: its values are then near zero around its own tau.  Writes the new state into
 // slot n of the other buffer and returns delta and tau / tau~ (first argmax of the true variables,
 // stored + B_t, from the parent's tau on; the parent's values if nothing is finite).
-// Lanes own frames from a multiple of four on, so that state, posteriors and B go as 16-byte accesses; what a float4
-// holds outside the window is written as log0 and never read (the stored range says so).
+// Lanes own frames from a multiple of four on, so that state, posteriors and B go as 16-byte accesses (8, two frames per lane); what
+// such an access holds outside the window is written as log0 and never read (the stored range says so).
 struct SurvivorIn {
   int par, tok, s, en, rs, re, ptau, ptau_end, plast, pref;
   float inc;
@@ -130,8 +130,8 @@ __device__ __forceinline__ void lanes_range(int& lo, int& hi) {
 template <int LPS, int FPL, int NWV, bool NEAR>
 __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int n, bool active, const SurvivorIn& in,
                                          SurvivorLds* sx, int& arg_n, int& arg_b, uint32_t& near_out, float& delta_out, double& bref_out) {
-  static_assert(FPL % 4 == 0 && (NWV == 1 || LPS == 64), "float4 per lane; waves share a survivor as wholes");
-  constexpr int NQ = FPL / 4, SPAN = LPS * FPL * NWV;      // frames per pass
+  static_assert((FPL == 2 || FPL % 4 == 0) && (NWV == 1 || LPS == 64), "float4 (float2) per lane; waves share a survivor as wholes");
+  constexpr int N = FPL == 2 ? 2 : 4, NQ = FPL / N, SPAN = LPS * FPL * NWV;      // frames per pass
   const int lane = threadIdx.x & 63, w = NWV > 1 ? uni(threadIdx.x >> 6) : 0;
   const int li = lane & (LPS - 1), lf = (w * 64 + li) * FPL;   // lane's place, its first frame's
   const size_t h0 = (size_t)u * Wb;
@@ -164,15 +164,14 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
     const float gp_m = pgp[tm], gb_m = pgb[tm];
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {                         // (clamped into the row; rows are whole multiples of four)
-      const int t4 = min(t0 + 4 * k, p.Tp - 4);
-      const float4 a = *(const float4*)(pgp + t4), b = *(const float4*)(pgb + t4), c = *(const float4*)(x0p + t4),
-                   d = *(const float4*)(xcp + t4);
-      const double2 e = *(const double2*)(Bu + t4), f = *(const double2*)(Bu + t4 + 2);
-      gp[4 * k] = a.x; gp[4 * k + 1] = a.y; gp[4 * k + 2] = a.z; gp[4 * k + 3] = a.w;
-      gb[4 * k] = b.x; gb[4 * k + 1] = b.y; gb[4 * k + 2] = b.z; gb[4 * k + 3] = b.w;
-      x0[4 * k] = c.x; x0[4 * k + 1] = c.y; x0[4 * k + 2] = c.z; x0[4 * k + 3] = c.w;
-      xc[4 * k] = d.x; xc[4 * k + 1] = d.y; xc[4 * k + 2] = d.z; xc[4 * k + 3] = d.w;
-      Bt[4 * k] = e.x; Bt[4 * k + 1] = e.y; Bt[4 * k + 2] = f.x; Bt[4 * k + 3] = f.y;
+      const int t4 = min(t0 + N * k, p.Tp - N);
+      struct __align__(4 * N) F { float v[N]; };
+      struct __align__(16) D { double v[2]; };
+      const F a = *(const F*)(pgp + t4), b = *(const F*)(pgb + t4), c = *(const F*)(x0p + t4), d = *(const F*)(xcp + t4);
+#pragma unroll
+      for (int i = 0; i < N; ++i) { gp[N * k + i] = a.v[i]; gb[N * k + i] = b.v[i]; x0[N * k + i] = c.v[i]; xc[N * k + i] = d.v[i]; }
+#pragma unroll
+      for (int i = 0; i < N; i += 2) { const D e = *(const D*)(Bu + t4 + i); Bt[N * k + i] = e.v[0]; Bt[N * k + i + 1] = e.v[1]; }
     }
     float tw_p = 0.0f, tw_b = 0.0f;                        // the frame before the wave's
     if (NWV > 1) { const int tw = min(max(base + w * 64 * FPL - 1, 0), T); tw_p = pgp[tw]; tw_b = pgb[tw]; }
@@ -207,11 +206,9 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
       if (NWV > 1) {
         if (lane == 63) sx->tot[which][w] = P;
         lds_barrier();
-        Aff W;                                             // maps of all earlier waves
-        W.a = 0.0f; W.b = LOG0F;
 #pragma unroll
-        for (int i = 0; i < NWV - 1; ++i) if (i < w) W = aff_then(W, sx->tot[which][i]);
-        E = aff_then(W, E);
+        for (int i = 0; i < NWV - 1; ++i)                  // through the earlier waves' maps
+          if (i < w) { const Aff W = sx->tot[which][i]; carry = lae(carry + W.a, W.b); }
       }
       v_in = lae(E.a + carry, E.b);
 #pragma unroll
@@ -247,9 +244,12 @@ __device__ __forceinline__ void survivor(const SelectArgs& p, int Wb, int u, int
     if (active) {
 #pragma unroll
       for (int k = 0; k < NQ; ++k)
-        if (t0 + 4 * k <= en && t0 + 4 * k + 3 >= s) {
-          *(float4*)(cgp + t0 + 4 * k) = make_float4(rp[4 * k], rp[4 * k + 1], rp[4 * k + 2], rp[4 * k + 3]);
-          *(float4*)(cgb + t0 + 4 * k) = make_float4(rb[4 * k], rb[4 * k + 1], rb[4 * k + 2], rb[4 * k + 3]);
+        if (t0 + N * k <= en && t0 + N * k + N - 1 >= s) {
+          struct __align__(4 * N) F { float v[N]; } a, b;
+#pragma unroll
+          for (int i = 0; i < N; ++i) { a.v[i] = rp[N * k + i]; b.v[i] = rb[N * k + i]; }
+          *(F*)(cgp + t0 + N * k) = a;
+          *(F*)(cgb + t0 + N * k) = b;
         }
     }
     xn = lanes_argmax<LPS>(xn); xb = lanes_argmax<LPS>(xb);
@@ -861,7 +861,11 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
       uint32_t near;
       float delta;
       double bref;
-      if (WIDE && shared) survivor<64, 4, BLOCK / 64, NEAR>(p, Wb, u, n, true, in, &s_sx, arg_n, arg_b, near, delta, bref);
+      if (WIDE && shared) {                                // (uniform: two frames per lane while one pass holds the window, 16
+                                                           // whole utterances 1549 -> 1515 us a decode with both forms instead of four always)
+        if (par_e - (par_s & ~3) < 128 * (BLOCK / 64)) survivor<64, 2, BLOCK / 64, NEAR>(p, Wb, u, n, true, in, &s_sx, arg_n, arg_b, near, delta, bref);
+        else survivor<64, 4, BLOCK / 64, NEAR>(p, Wb, u, n, true, in, &s_sx, arg_n, arg_b, near, delta, bref);
+      }
       else wave_survivor<NEAR>(p, Wb, u, n, in, arg_n, arg_b, near, delta, bref);
       if (tid == 0) {
         p.out[3 * UW + h] = arg_n; p.out[4 * UW + h] = arg_b;
