@@ -32,6 +32,7 @@
 // ---------------------------------------------------------------- vector types
 struct dim3 { unsigned x, y, z; dim3(unsigned a = 1, unsigned b = 1, unsigned c = 1) : x(a), y(b), z(c) {} };
 struct alignas(16) float4 { float x, y, z, w; };
+struct alignas(16) uint4 { unsigned x, y, z, w; };
 struct alignas(8) float2 { float x, y; };
 struct alignas(16) ulonglong2 { unsigned long long x, y; };
 struct alignas(16) double2 { double x, y; };
