@@ -178,19 +178,21 @@ struct Params {
 // of a line is a trip to memory in a chain of them.  PIN makes a value be in scalar registers from here on, so that
 // loads written above it are issued together and waited for once.  LOADED does the same for vector registers: without it
 // the compiler moves a load into the branch that alone uses it, behind the arrival of the loads before, and a
-// round of loads becomes a chain of them.  SCHED_FENCE: no instruction is moved across (a prefetch stays ahead of the work).
+// round of loads becomes a chain of them; FETCH is a load that stays where it is written, without a wait.  SCHED_FENCE: no instruction is moved across (a prefetch stays ahead of the work).
 // OPAQUE: what follows from a scalar is worked out again, not kept.  STORE_ASIDE: past the L2, which holds what the kernels read again.
 #if defined(__AMDGCN__)
 #define PIN4(a, b, c, d) __asm__ volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d))
 #define LOADED(a) __asm__ volatile("" : "+v"(a))
 #define OPAQUE(a) __asm__ volatile("" : "+s"(a))
 #define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
+#define FETCH(ptr) __hip_atomic_load(ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT)
 #define STORE_ASIDE(v, ptr) __builtin_nontemporal_store(v, ptr)
 #else
 #define PIN4(a, b, c, d) do { } while (0)
 #define LOADED(a) do { } while (0)
 #define OPAQUE(a) do { } while (0)
 #define SCHED_FENCE() do { } while (0)
+#define FETCH(ptr) (*(ptr))
 #define STORE_ASIDE(v, ptr) (*(ptr) = (v))
 #endif
 

@@ -84,14 +84,27 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
   float m = LOG0F;
   Lse a;                                                       // the repeated label's sum
   a.m = LOG0F; a.s = 0.0f;
-  for (int t = lo + tid; t <= hi; t += BLOCK) {
-    const float ph = gphi[t - 1], b = gb[t - 1], bt = (float)(Bu[t - 1] - Bref);
-    const float f = canon0(ph + bt);
-    dense_f_lds[t] = f;
-    m = fmaxf(m, f);
-    Lse v;
-    v.m = canon0(b + bt) + xr[t]; v.s = 1.0f;
-    a = lse_join(a, v);
+  // frames per lane and round, their loads in flight together (one by one: 7.8 -> 6.9 us a launch at 1500 frames)
+  constexpr int R = 3;
+  for (int t0 = lo; t0 <= hi; t0 += R * BLOCK) {
+    float ph[R], pb[R], x[R];
+    double B[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const int t = min(t0 + k * BLOCK + tid, hi);
+      ph[k] = FETCH(gphi + t - 1); pb[k] = FETCH(gb + t - 1); B[k] = FETCH(Bu + t - 1); x[k] = FETCH(xr + t);
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const int t = t0 + k * BLOCK + tid;
+      if (t > hi) break;
+      const float bt = (float)(B[k] - Bref), f = canon0(ph[k] + bt);
+      dense_f_lds[t] = f;
+      m = fmaxf(m, f);
+      Lse v;
+      v.m = canon0(pb[k] + bt) + x[k]; v.s = 1.0f;
+      a = lse_join(a, v);
+    }
   }
   m = row16_max(m);
   m = fmaxf(fmaxf(lane_f(m, 0), lane_f(m, 16)), fmaxf(lane_f(m, 32), lane_f(m, 48)));

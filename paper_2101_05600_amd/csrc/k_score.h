@@ -1148,15 +1148,18 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
   __shared__ int s_n;
   const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6);
   const int grp = (int)(blockIdx.y * gridDim.x + blockIdx.x), u = blockIdx.y, K = p.K, Wb = p.Wb;
-  if (p.finished[u] || !p.rec[cur][grp].live) return;      // the score kernel already wrote a count of 0
-  if (p.grp[grp].stopped) { if (tid == 0) p.grp[grp].n = 0; return; }
+  // (what decides whether there is anything to do, and the slot, are asked for together)
+  const uint8_t finished = FETCH(p.finished + u);
+  const int live = FETCH(&p.rec[cur][grp].live), stopped = FETCH(&p.grp[grp].stopped);
   const double* J = p.cand_joint + (size_t)grp * K;         // (not DENSE)
   const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
   const float* arow = att + (size_t)grp * p.V;
   const float* ginc = p.cand_inc + (size_t)grp * K;
   double offr = 0.0, jbase = 0.0;
   const double lam = p.lambda;
-  if (DENSE) { offr = p.dense_slot[grp].offr; jbase = p.dense_slot[grp].jbase; }
+  if (DENSE) { offr = FETCH(&p.dense_slot[grp].offr); jbase = FETCH(&p.dense_slot[grp].jbase); }
+  if (finished || !live) return;                            // the score kernel already wrote a count of 0
+  if (stopped) { if (tid == 0) p.grp[grp].n = 0; return; }
   auto joint = [&](float inc, float a) {
     return inc > LOG0_CLASS ? lam * (offr + (double)inc) + (1.0 - lam) * (double)a + jbase : LOG0D;
   };

@@ -862,9 +862,11 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
       float delta;
       double bref;
       if (WIDE && shared) {                                // (uniform: two frames per lane while one pass holds the window, 16
-                                                           // whole utterances 1549 -> 1515 us a decode with both forms instead of four always)
+                                                           // whole utterances 1549 -> 1515 us a decode with both forms instead of four always; eight
+                                                           // where it takes them to need no second pass, 16 x 1500 frames 11889 -> 11659)
         if (par_e - (par_s & ~3) < 128 * (BLOCK / 64)) survivor<64, 2, BLOCK / 64, NEAR>(p, Wb, u, n, true, in, &s_sx, arg_n, arg_b, near, delta, bref);
-        else survivor<64, 4, BLOCK / 64, NEAR>(p, Wb, u, n, true, in, &s_sx, arg_n, arg_b, near, delta, bref);
+        else if (par_e - (par_s & ~3) < 256 * (BLOCK / 64)) survivor<64, 4, BLOCK / 64, NEAR>(p, Wb, u, n, true, in, &s_sx, arg_n, arg_b, near, delta, bref);
+        else survivor<64, 8, BLOCK / 64, NEAR>(p, Wb, u, n, true, in, &s_sx, arg_n, arg_b, near, delta, bref);
       }
       else wave_survivor<NEAR>(p, Wb, u, n, in, arg_n, arg_b, near, delta, bref);
       if (tid == 0) {
