@@ -368,6 +368,13 @@ __device__ __forceinline__ float row16_sum(float v) {
   v += rot_f<0x121>(v);
   return v;
 }
+__device__ __forceinline__ int row16_min_i(int v) {
+  v = min(v, dpp_i<0x128, 0xf>(v, v));
+  v = min(v, dpp_i<0x124, 0xf>(v, v));
+  v = min(v, dpp_i<0x122, 0xf>(v, v));
+  v = min(v, dpp_i<0x121, 0xf>(v, v));
+  return v;
+}
 __device__ __forceinline__ float lane_f(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }

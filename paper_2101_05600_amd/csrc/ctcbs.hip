@@ -383,8 +383,8 @@ static hipError_t launch_score(ctcbs* h, const Params& p, const float* att, int 
   }
 }
 
-// Every id a candidate.  64 candidates per work-group where that gives every compute unit a few work-groups (each reads
-// the slots' F once: a third of what it reads of the posteriors), 16 otherwise.
+// Every id a candidate.  32 candidates per work-group where that gives every compute unit its four work-groups (each reads
+// the slots' F once), 16 otherwise.
 template <int NT>
 static hipError_t launch_dense_scores(ctcbs* h, const Params& p, int l) {
   const dim3 grid((unsigned)(p.K + 16 * NT - 1) / (16 * NT), (unsigned)p.U);
@@ -399,7 +399,7 @@ static hipError_t launch_dense(ctcbs* h, const Params& p, const float* att, int 
   hipLaunchKernelGGL((k_dense_prep<256>), dim3(p.Wb, p.U), dim3(256), (size_t)p.Tp * 4, h->stream, p, att, l, h->cur);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if ((long long)p.U * ((p.K + 63) / 64) >= 512) return launch_dense_scores<4>(h, p, l);
+  if ((long long)p.U * ((p.K + 31) / 32) >= 1024) return launch_dense_scores<2>(h, p, l);
   return launch_dense_scores<1>(h, p, l);
 }
 

@@ -21,6 +21,11 @@
 #include "common.h"
 #include "k_score.h"
 
+// (as for HypRec::near_frames: e^-NEAR_DEPTH; e^NEAR_MARGIN, 2^26 and what a log-posterior of NEAR_X_MAX may add)
+#define NEAR_F 7.8e-20f
+#define NEAR_GAIN 7.3e7f
+#define DENSE_RANGE 1.0e-30f   // a smaller sum may lack products that underflowed
+
 typedef float f32x4 __attribute__((__vector_size__(16)));
 
 // f term of frame t (log domain): gamma_{t-1}(g) relative to off' + B_r; only where t - 1 lies in the stored range
@@ -117,8 +122,11 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
   for (int i = 1; i < BLOCK / 64; ++i) M = fmaxf(M, s_red[i]);
   const bool some = M > LOG0_CLASS;                            // else: no term at all, every increment is log0
   float* F = p.dense_F + h * Tp;
-  __shared__ int s_lo[BLOCK / 64], s_hi[BLOCK / 64];
-  int f_lo = 0x7fffffff, f_hi = -1;                            // (scalar: a wave's lanes hold 64 frames in a row)
+  __shared__ int s_lo[BLOCK / 64], s_hi[BLOCK / 64], s_nlo[BLOCK / 64], s_nhi[BLOCK / 64];
+  __shared__ float s_far[BLOCK / 64];
+  int f_lo = 0x7fffffff, f_hi = -1, n_lo = 0x7fffffff, n_hi = -1;   // (scalar: a wave's lanes hold 64 frames in a row)
+  const bool near_ok = ui.above0 == 0;
+  float far = 0.0f;
   for (int t = tid; t - tid < Tp; t += BLOCK) {
     float v = 0.0f;
     if (some && t >= lo && t <= hi) {
@@ -131,9 +139,17 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
       const int t_w = t - (tid & 63);
       f_lo = min(f_lo, uni(t_w) + __ffsll((long long)nz) - 1);
       f_hi = uni(t_w) + 63 - __clzll((long long)nz);
+      const bool is_near = near_ok ? !(v < NEAR_F) : v != 0.0f;
+      const unsigned long long nr = __ballot(is_near);
+      if (nr != 0ull) {
+        n_lo = min(n_lo, uni(t_w) + __ffsll((long long)nr) - 1);
+        n_hi = uni(t_w) + 63 - __clzll((long long)nr);
+      }
+      if (!is_near) far += v;                                  // (a frame between near ones is read, and counted here too)
     }
   }
-  if ((tid & 63) == 0) { s_lo[w] = f_lo; s_hi[w] = f_hi; }
+  far = chain_sum<64>(far);
+  if ((tid & 63) == 0) { s_lo[w] = f_lo; s_hi[w] = f_hi; s_nlo[w] = n_lo; s_nhi[w] = n_hi; s_far[w] = far; }
   lds_barrier();
   if (tid == 0) {
     Lse c;
@@ -141,12 +157,20 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
 #pragma unroll
     for (int i = 1; i < BLOCK / 64; ++i) { Lse d; d.m = s_am[i]; d.s = s_rs[i]; c = lse_join(c, d); }
     DenseSlot q;
-    q.live = 1; q.last = rep_ok ? r.last : -1; q.win_s = s; q.win_e = e;
+    q.live = 1; q.last = rep_ok ? r.last : -1; q.f_lo = lo; q.f_hi = hi;
     q.mref = M; q.inc_rep = c.m < LOG0_CLASS ? LOG0F : c.m + fast_logf(c.s);
-    q.rs = r.rs; q.re = r.re; q.ref = r.ref; q.pad = 0;
+    q.ref = r.ref;
     q.s = s_lo[0]; q.e = s_hi[0];
+    int ns = s_nlo[0], ne = s_nhi[0];
+    float fs = s_far[0];
 #pragma unroll
-    for (int i = 1; i < BLOCK / 64; ++i) { q.s = min(q.s, s_lo[i]); q.e = max(q.e, s_hi[i]); }
+    for (int i = 1; i < BLOCK / 64; ++i) {
+      q.s = min(q.s, s_lo[i]); q.e = max(q.e, s_hi[i]);
+      ns = min(ns, s_nlo[i]); ne = max(ne, s_nhi[i]);
+      fs += s_far[i];
+    }
+    // (no frame at all: both ranges are empty alike)
+    q.far_s = ns - q.s; q.far_e = q.e - ne; q.low = fs * NEAR_GAIN;
     q.offr = r.off + Bref;
     q.jbase = (1.0 - p.lambda) * r.att + p.beta * (double)l;
     *slot = q;
@@ -160,140 +184,181 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
   }
 }
 
-// Grid: (chunks of 16 * NT candidates, U), four waves that share the frames of the window: each takes every fourth
-// block of 16 frames (together they walk along the columns) for all the work-group's candidates and slots (no operand is shared between waves, so none goes through LDS),
-// and their sums meet in LDS at the end.  MFMA 16x16x4: lane (n, q) = (lane & 15, lane >> 4) holds four consecutive
-// frames of candidate n (of slot n): its float4 serves four products whose frame index runs over the four q.
+// Grid: (chunks of 16 * NT candidates, U), four waves that share the frames of the window for all the work-group's candidates and
+// slots, halves of a block of 32 frames in turn (together they walk along the columns), and their sums meet in LDS at the end.  MFMA
+// 16x16x4: lane (n, q) = (lane & 15, lane >> 4) holds four consecutive frames of candidate n (of slot n), which serve four products
+// whose frame index runs over the four q.  For the loads four neighbouring lanes hold the 64 bytes of a row, and LDS turns
+// them round: loaded as the products want them, the 64 lanes of a load touch 54 cache lines, and the cache serves one a cycle.
 // Only the frames between the first and the last F of any slot that is not 0 are read: where F underflows its products are
 // exactly 0.  Peaked posteriors leave a few hundred frames round the slots' last labels (a label missed costs nats, F is 0
-// from 87 on), 3 to 4 in 16 at 16 utterances of 1500 frames, 5000 ids: 115 -> 33 us a launch; flat ones leave them all.
-// Bound: the posteriors of those frames (4 V T bytes per utterance if all: 480 MB).  MFMA:
-// 32 cycles for 16 x 16 x 4, two slot tiles beyond 16 slots: half the time the bytes take.  Half a block is fetched ahead:
-// 114 us a launch with all frames, 116.5 with one accumulator per tile and the loads where the compiler put them; with the two
-// accumulators the sums need and the loads left to it a decode of 27.1 ms took 37.5.  159 registers, three waves per
-// SIMD, for four candidate and two slot tiles; held to fewer the form of one slot tile spills (12.4 -> 13.7 ms a decode).
+// from 87 on), 10 blocks of 47 at 16 utterances of 1500 frames, 5000 ids, beam 20; flat ones leave them all.  Of those the frames
+// with an F of NEAR_F or more first, 6 blocks, and the others only if some sum does not exceed by 2^26 all that they could add (low:
+// the slot's F left out, as if its posteriors were 1; on these inputs never): a launch 32.7 -> 24.2 us, of which 28.4 with
+// the loads and tiles as they were; posteriors that leave nearly all frames 104 -> 100 us at beam 20, 93 -> 84 at beam 10.
+// Bound there: the posteriors of those frames (480 MB); here: the phases of a work-group, four of which fit a compute unit.  As fast
+// here, slower there (F fetched again for fewer candidates): 16 candidates per work-group, 24.0 and 120 us; a wave for each 16
+// candidates, no sums between waves, 25.4 and 122.  Slower: four halves ahead instead of two (25 registers more, 33 us), work-groups
+// that stay and fetch the next candidates' frames before they finish the last (25.5 and 130).
 template <int NT, int MT>
 __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict__ xT, const float* __restrict__ F,
                                                          const DenseSlot* __restrict__ slots,
                                                          int Wb, int Tp, int V, int K, Params p, int l, int cur) {
-  constexpr int NC = 16 * NT;
+  constexpr int NC = 16 * NT, AHEAD = 2, SLOTS = 256 / NC;   // (slots whose sums are looked at together)
   __shared__ float s_acc[4][16 * MT][NC + 1];
   __shared__ int s_last[MAX_BEAM], s_live[MAX_BEAM];
-  __shared__ float s_m[MAX_BEAM], s_rep[MAX_BEAM];
+  __shared__ float s_m[MAX_BEAM], s_rep[MAX_BEAM], s_low[MAX_BEAM];
+  __shared__ int s_far[4];
+  __shared__ f32x4 s_turn[4][MT + NT][64];
   const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6), n = lane & 15, q = lane >> 4;
   const int u = blockIdx.y, c0 = (int)blockIdx.x * NC;
   const size_t h0 = (size_t)u * Wb;
-  if (p.finished[u]) return;
+  // (all that depends on nothing is asked for together)
+  const uint8_t finished = FETCH(p.finished + u);
   const int T = p.uinfo[u].T;
-  int smin, emax;                                              // the frames that any slot has an F for
+  DenseSlot d = slots[h0 + min(lane, Wb - 1)];
+  LOADED(d.live); LOADED(d.s); LOADED(d.mref);
+  if (finished) return;
+  // the blocks that any slot has an F for, b0 .. e0 - 1, and those read at first, b1 .. e1 - 1
+  int b0, e0, b1, e1;
   {
-    DenseSlot d;
-    d.live = 0; d.s = 0x7fffffff; d.e = -1;
-    if (lane < Wb) d = slots[h0 + lane];
-    if (tid < Wb) { s_last[tid] = d.last; s_live[tid] = d.live; s_m[tid] = d.mref; s_rep[tid] = d.inc_rep; }
-    int a = d.live ? d.s : 0x7fffffff, b = d.live ? d.e : -1;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { a = min(a, __shfl_xor(a, o)); b = max(b, __shfl_xor(b, o)); }
-    smin = uni(min(max(a, 1), T)); emax = uni(min(b, T));
+    if (tid < Wb) { s_last[tid] = d.last; s_live[tid] = d.live; s_m[tid] = d.mref; s_rep[tid] = d.inc_rep; s_low[tid] = fmaxf(d.low, DENSE_RANGE); }
+    const bool live = lane < Wb && d.live;                     // (slots in the first 32 lanes: two rows)
+    auto lowest = [](int v) { v = row16_min_i(v); return min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)); };
+    auto blocks = [&](int s, int e, int& from, int& to) {
+      s = lowest(live ? s : 0x7fffffff); e = -lowest(live ? -e : 1);
+      s = min(max(s, 1), T); e = min(e, T);
+      from = s >> 5; to = e >= s ? (e >> 5) + 1 : from;
+    };
+    blocks(d.s, d.e, b0, e0); blocks(d.s + d.far_s, d.e - d.far_e, b1, e1);
+    b1 = max(b1, b0); e1 = max(min(e1, e0), b1);
   }
   const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
   const float* xu = xT + (size_t)u * V * Tp;
-  const int b0 = smin >> 5, nb = emax >= smin ? (emax >> 5) - b0 + 1 : 0;      // blocks of 32 frames: whole lines of xT
-  const int bw = b0 + w, ew = b0 + nb;
+  // (four lanes in a row hold 64 bytes of a candidate, or slot, for the loads; `turn` brings them to where the products need them)
+  const int row = lane >> 2, piece = lane & 3;
   const float* bp[NT];
   const float* ap[MT];
 #pragma unroll
-  for (int k = 0; k < NT; ++k) bp[k] = xu + (size_t)full_v_id(min(c0 + 16 * k + n, K - 1), lo_ex, hi_ex) * Tp + 4 * q;
+  for (int k = 0; k < NT; ++k) bp[k] = xu + (size_t)full_v_id(min(c0 + 16 * k + row, K - 1), lo_ex, hi_ex) * Tp + 4 * piece;
 #pragma unroll
-  for (int k = 0; k < MT; ++k) ap[k] = F + (h0 + min(16 * k + n, Wb - 1)) * Tp + 4 * q;
+  for (int m = 0; m < MT; ++m) ap[m] = F + (h0 + min(16 * m + row, Wb - 1)) * Tp + 4 * piece;
+  f32x4 (*turn)[64] = s_turn[w];
+  const int put = 16 * piece + ((row + 4 * piece) & 15), get = 16 * q + ((n + 4 * q) & 15);
   f32x4 acc[MT][NT], sum[MT][NT];
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
+  for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int k = 0; k < NT; ++k) acc[i][k] = sum[i][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  // half a block (16 frames) is on its way while the half before it is worked on
-  auto fetch = [&](int b, int hf, float4 (&x)[NT], float4 (&f)[MT]) {
+    for (int k = 0; k < NT; ++k) acc[m][k] = sum[m][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  // all of the loop's control is uniform.  whole: nothing is left out; far: a sum that the frames left out may count for
+  bool whole = b1 == b0 && e1 == e0, far = false;
+  float* inc_u = p.cand_inc + h0 * (size_t)K;
+  const int cc = tid & (NC - 1), c = c0 + cc, id = full_v_id(min(c, K - 1), lo_ex, hi_ex);
+  uint32_t again = 0;                                          // a bit for each of the lane's sums that is to be redone
+  // the frames read at first; where those left out can count, those before and those behind them too
+#pragma unroll 1
+  for (int part = 0; part < 3; ++part) {
+    const int b = part == 0 ? b1 : (part == 1 ? b0 : e1), end = part == 0 ? e1 : (part == 1 ? b1 : e0);
+    const int nh = (2 * (end - b) + 3 - w) >> 2;               // the wave's halves of a block
+    if (nh > 0) {
+      f32x4 x[AHEAD][NT], f[AHEAD][MT];
+      auto fetch = [&](int i, int a) {
+        i = min(i, nh - 1);
+        const int t = 32 * b + 16 * (w + 4 * i);
 #pragma unroll
-    for (int k = 0; k < NT; ++k) x[k] = *(const float4*)(bp[k] + 32 * b + 16 * hf);
+        for (int k = 0; k < NT; ++k) x[a][k] = *(const f32x4*)(bp[k] + t);
 #pragma unroll
-    for (int k = 0; k < MT; ++k) f[k] = *(const float4*)(ap[k] + 32 * b + 16 * hf);
-    SCHED_FENCE();
-  };
-  auto products = [&](const float4 (&x)[NT], const float4 (&f)[MT]) {
-    float ex[NT][4], fa[MT][4];
+        for (int m = 0; m < MT; ++m) f[a][m] = *(const f32x4*)(ap[m] + t);
+        SCHED_FENCE();
+      };
 #pragma unroll
-    for (int k = 0; k < NT; ++k) { ex[k][0] = exp_exact(x[k].x); ex[k][1] = exp_exact(x[k].y); ex[k][2] = exp_exact(x[k].z); ex[k][3] = exp_exact(x[k].w); }
+      for (int a = 0; a < AHEAD; ++a) fetch(a, a);
+#pragma unroll 1
+      for (int i = 0; i < nh; i += AHEAD) {
 #pragma unroll
-    for (int k = 0; k < MT; ++k) { fa[k][0] = f[k].x; fa[k][1] = f[k].y; fa[k][2] = f[k].z; fa[k][3] = f[k].w; }
+        for (int a = 0; a < AHEAD; ++a) {
+          if (a == 0 || i + a < nh) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+            for (int k = 0; k < NT; ++k) turn[MT + k][put] = f32x4{exp_exact(x[a][k][0]), exp_exact(x[a][k][1]), exp_exact(x[a][k][2]), exp_exact(x[a][k][3])};
+#pragma unroll
+            for (int m = 0; m < MT; ++m) turn[m][put] = f[a][m];
+            fetch(i + a + AHEAD, a);
+            wave_lds_fence();
+            f32x4 ex[NT], fv[MT];
+#pragma unroll
+            for (int k = 0; k < NT; ++k) ex[k] = turn[MT + k][get];
+#pragma unroll
+            for (int m = 0; m < MT; ++m) fv[m] = turn[m][get];
+            wave_lds_fence();
+#pragma unroll
+            for (int o = 0; o < 4; ++o)
+#pragma unroll
+              for (int k = 0; k < NT; ++k)
+#pragma unroll
+                for (int m = 0; m < MT; ++m) acc[m][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv[m][o], ex[k][o], acc[m][k], 0, 0, 0);
+            if (a & 1) {                                       // 32 frames join the sum; what that rounds away starts the next ones'
+#pragma unroll
+              for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int k = 0; k < NT; ++k) {
+                  const f32x4 t = sum[m][k] + acc[m][k];
+                  acc[m][k] -= t - sum[m][k];
+                  sum[m][k] = t;
+                }
+            }
+          }
+        }
+      }
+    }
+    if (part == 1) continue;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
 #pragma unroll
       for (int k = 0; k < NT; ++k)
 #pragma unroll
-        for (int i = 0; i < MT; ++i) acc[i][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][c], ex[k][c], acc[i][k], 0, 0, 0);
-  };
-  float4 x0[NT], f0[MT], x1[NT], f1[MT];
-  if (bw < ew) {
-    fetch(bw, 0, x0, f0);
-    int b = bw;
-    for (; b + 4 < ew; b += 4) {
-      fetch(b, 1, x1, f1);
-      products(x0, f0);
-      fetch(b + 4, 0, x0, f0);
-      products(x1, f1);
-      // the block's 32 frames join the sum; what that rounds away starts the next block's
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int k = 0; k < NT; ++k) {
-          const f32x4 t = sum[i][k] + acc[i][k];
-          acc[i][k] -= t - sum[i][k];
-          sum[i][k] = t;
-        }
+        for (int r = 0; r < 4; ++r) s_acc[w][16 * m + 4 * q + r][16 * k + n] = sum[m][k][r] + acc[m][k][r];
+    lds_barrier();
+    // ---- increments: lane = candidate, the slots dealt to the 256 / NC groups of lanes ----
+    whole |= part > 0;
+    far = false; again = 0;
+    for (int j0 = 0; j0 < Wb; j0 += SLOTS) {
+      const int j = j0 + tid / NC, js = min(j, Wb - 1);
+      const float v = (s_acc[0][js][cc] + s_acc[1][js][cc]) + (s_acc[2][js][cc] + s_acc[3][js][cc]);
+      const bool mine = j < Wb && c < K && s_live[js], rep = id == s_last[js];
+      float inc = v < 3.0e38f ? add_log(s_m[js], v) : v;
+      inc = rep ? s_rep[js] : inc;
+      far |= mine && !rep && !(v > s_low[js]);
+      again |= mine && !rep && !(v > DENSE_RANGE) ? 1u << (j0 / SLOTS) : 0u;
+      if (mine) *(float*)((char*)inc_u + 4u * (uint32_t)(js * K + c)) = canon0(inc);
     }
-    fetch(b, 1, x1, f1);                                       // (the wave's last block)
-    products(x0, f0);
-    products(x1, f1);
+    if (whole) break;
+    const bool any = __ballot(far) != 0ull;                    // (rare)
+    if (lane == 0) s_far[w] = any;
+    lds_barrier();                                             // (the sums have been read too)
+    if ((s_far[0] | s_far[1] | s_far[2] | s_far[3]) == 0) return;
   }
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int k = 0; k < NT; ++k)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) s_acc[w][16 * i + 4 * q + r][16 * k + n] = sum[i][k][r] + acc[i][k][r];
-  lds_barrier();
-  // ---- increments: lane = candidate, the slots dealt to 256 / NC groups of lanes ----
-  const int cc = tid & (NC - 1), c = c0 + cc;
-  const int id = full_v_id(min(c, K - 1), lo_ex, hi_ex);
-  for (int j0 = 0; j0 < Wb; j0 += 256 / NC) {
-    const int j = j0 + tid / NC, js = min(j, Wb - 1);
-    const bool mine = j < Wb && c < K && s_live[js];
-    const float sum = (s_acc[0][js][cc] + s_acc[1][js][cc]) + (s_acc[2][js][cc] + s_acc[3][js][cc]);
-    float inc = sum < 3.0e38f ? add_log(s_m[js], sum) : sum;
-    const bool rep = id == s_last[js];
-    if (rep) inc = s_rep[js];
-    const bool redo = mine && !rep && !(sum > 1.0e-30f);
-    unsigned long long todo = __ballot(redo);
-    while (todo != 0ull) {                                     // (uniform) every product far below M, or none finite
-      const int who = __ffsll((long long)todo) - 1;
-      todo &= todo - 1ull;
-      const int jr = __builtin_amdgcn_readlane(js, who), idr = __builtin_amdgcn_readlane(id, who);
-      const size_t h = h0 + jr;
-      const DenseSlot d = slots[h];
+  // a sum below the range of the product, every product far below M or none finite: again, frame by frame
+  unsigned long long todo = __ballot(again != 0u);             // (rare)
+  while (todo != 0ull) {                                       // (uniform)
+    const int who = __ffsll((long long)todo) - 1;
+    todo &= todo - 1ull;
+    const int idw = __builtin_amdgcn_readlane(id, who);
+    for (uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)again, who); bits != 0u; bits &= bits - 1u) {
+      const int j = SLOTS * (__ffs((int)bits) - 1) + (64 * w + who) / NC;
+      const size_t h = h0 + j;
+      const DenseSlot g = slots[h];
       const float* gphi = p.gphi[cur] + h * Tp;
       const double* Bu = p.Bcum + (size_t)u * Tp;
-      const double Bref = Bu[checked(p, d.ref, 0, T, ERR_TIME_INDEX)];
-      const float* col = xu + (size_t)idr * Tp;
+      const double Bref = Bu[checked(p, g.ref, 0, T, ERR_TIME_INDEX)];
+      const float* col = xu + (size_t)idw * Tp;
       Lse a;
       a.m = LOG0F; a.s = 0.0f;
-      for (int t = max(d.win_s, d.rs + 1) + lane; t <= min(d.win_e, d.re + 1); t += 64) {
+      for (int t = g.f_lo + lane; t <= g.f_hi; t += 64) {
         Lse v;
         v.m = dense_f(gphi, Bu, Bref, t) + col[t]; v.s = 1.0f;
         a = lse_join(a, v);
       }
       const float r = lse_finish<64>(a);
-      if (lane == who) inc = r;
+      if (lane == who) *(float*)((char*)inc_u + 4u * (uint32_t)(j * K + c)) = canon0(r);
     }
-    if (mine) p.cand_inc[(h0 + j) * (size_t)K + c] = canon0(inc);
   }
 }

@@ -26,10 +26,11 @@ struct __align__(64) DenseSlot {
   int32_t live, last;
   int32_t s, e;              // first and last frame whose F is not 0 (none: s > e)
   float mref, inc_rep;       // largest f term M; increment of the candidate that repeats the last label
-  int32_t rs, re, ref;
-  int32_t pad;
+  int32_t far_s, far_e;      // frames at either end of s .. e that the product leaves out at first,
+  float low;                 // and the sum from which on they cannot count
+  int32_t ref;               // reference frame (HypRec)
   double offr, jbase;        // off' + B_r; joint score without this step's terms
-  int32_t win_s, win_e;      // window
+  int32_t f_lo, f_hi;        // first and last frame that has an f term
 };
 
 #define PIVOT_CAP 512     // entries of the short list (all waves together)

@@ -31,14 +31,6 @@ __device__ __forceinline__ Aff aff_stage(Aff v) {
 
 struct ArgMax { float v; int t; };
 
-// over a row of 16 lanes, result in all of them
-__device__ __forceinline__ int row16_min_i(int v) {
-  v = min(v, dpp_i<0x128, 0xf>(v, v));
-  v = min(v, dpp_i<0x124, 0xf>(v, v));
-  v = min(v, dpp_i<0x122, 0xf>(v, v));
-  v = min(v, dpp_i<0x121, 0xf>(v, v));
-  return v;
-}
 // largest value, earliest frame among equals, over LPS lanes; result in all of them.  The largest value first, then the
 // smallest frame among the lanes that hold it: each step of either is one instruction, which on pairs took nine (the
 // three maxima of a step together: 1.3 -> 0.6 us at a batch of 512).

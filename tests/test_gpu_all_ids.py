@@ -62,6 +62,26 @@ def test_short_stretches_of_frames(every, lens, over):
     _decode(**dict(dict(vocab=100, beam=5, lens=lens, edit=lambda c: peaked_ctc(c, every), steps=14), **over))
 
 
+# candidates so unlikely that the frames left out at first count, likely at the far end alone, and values that are no
+# log-probabilities; 16 and 32 candidates, one and two tiles of slots per work-group
+@pytest.mark.parametrize("value", [-30.0, -70.0, "far", "above0"])
+@pytest.mark.parametrize("over", [{}, dict(beam=17), dict(beam=17, n_utt=50, vocab=700), dict(n_utt=50, vocab=700)])
+def test_frames_left_out_count(value, over):
+    n = over.get("n_utt", 2)
+
+    def edit(ctc):
+        peaked_ctc(ctc, 5, ids=np.arange(50, 90))
+        if value == "far":
+            ctc[:, :, 1:45] = -60.0
+            ctc[:, -9:, 1:45] = -0.5
+        elif value == "above0":
+            ctc += 3.0
+            ctc[:, -9:, 1:45] = 45.0
+        else:
+            ctc[:, :, 1:45] = value
+    _decode(**dict(dict(vocab=100, beam=4, lens=[300 - 3 * u for u in range(n)], edit=edit, steps=6, check=[0, n - 1]), **over))
+
+
 # candidates can be looked at without keep_candidates: the score kernel's own list, the matrix form, sets through memory
 @pytest.mark.parametrize("vocab,over", [(40, {}), (40, dict(end_flags=7, eos_run=3)), (100, {}), (100, dict(win_union=1)), (700, {}), (9001, {}), (400, dict(cand_k=300))])
 def test_peek_without_keep_candidates(vocab, over):
