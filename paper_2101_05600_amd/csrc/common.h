@@ -53,6 +53,8 @@
 #define TRACE_FLUSH(p, blk) do { } while (0)
 #endif
 
+typedef float f32x4 __attribute__((__vector_size__(16)));
+
 struct UttState {            // per utterance, touched by one thread of the select kernel
   double best_score;         // best joint score in the ended set
   double ring_score[MAX_END_M];  // best ended score per length, lengths l, l-1, ... (ring by l % M)
@@ -179,7 +181,7 @@ struct Params {
 // loads written above it are issued together and waited for once.  LOADED does the same for vector registers: without it
 // the compiler moves a load into the branch that alone uses it, behind the arrival of the loads before, and a
 // round of loads becomes a chain of them; FETCH is a load that stays where it is written, without a wait.  SCHED_FENCE: no instruction is moved across (a prefetch stays ahead of the work).
-// OPAQUE: what follows from a scalar is worked out again, not kept.  STORE_ASIDE: past the L2, which holds what the kernels read again.
+// OPAQUE: what follows from a scalar is worked out again, not kept.  STORE_ASIDE, LOAD_ASIDE: past the L2, which holds what the kernels read again.
 #if defined(__AMDGCN__)
 #define PIN4(a, b, c, d) __asm__ volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d))
 #define LOADED(a) __asm__ volatile("" : "+v"(a))
@@ -187,6 +189,7 @@ struct Params {
 #define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 #define FETCH(ptr) __hip_atomic_load(ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT)
 #define STORE_ASIDE(v, ptr) __builtin_nontemporal_store(v, ptr)
+#define LOAD_ASIDE(ptr) __builtin_nontemporal_load(ptr)
 #else
 #define PIN4(a, b, c, d) do { } while (0)
 #define LOADED(a) do { } while (0)
@@ -194,6 +197,7 @@ struct Params {
 #define SCHED_FENCE() do { } while (0)
 #define FETCH(ptr) (*(ptr))
 #define STORE_ASIDE(v, ptr) (*(ptr) = (v))
+#define LOAD_ASIDE(ptr) (*(ptr))
 #endif
 
 // arguments of the score kernel behind the preloaded ones

@@ -26,8 +26,6 @@
 #define NEAR_GAIN 7.3e7f
 #define DENSE_RANGE 1.0e-30f   // a smaller sum may lack products that underflowed
 
-typedef float f32x4 __attribute__((__vector_size__(16)));
-
 // f term of frame t (log domain): gamma_{t-1}(g) relative to off' + B_r; only where t - 1 lies in the stored range
 __device__ __forceinline__ float dense_f(const float* gphi, const double* Bu, double Bref, int t) {
   return canon0(gphi[t - 1] + (float)(Bu[t - 1] - Bref));

@@ -504,10 +504,15 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   row.n_ex = row.head + tail;
   row.ex_id = tid < row.head ? tid : row.head + 4 * ng + (tid - row.head);
   row.ex = -__builtin_huge_valf();
+  // (each row is read once: past the L2, whose lines the columns and the state need again.  512 utterances 29.2 -> 27.9 us a launch,
+  // 256 of 1500 frames at beam 20 46.6 -> 45.9, 64 utterances the same)
   auto fetch_row = [&]() {
-    const float4* a4 = (const float4*)(arow + row.head);
+    const char* a4 = (const char*)(arow + row.head);
 #pragma unroll
-    for (int k = 0; k < NV4; ++k) row.v[k] = at32(a4, min(tid + k * BLOCK, ng - 1));
+    for (int k = 0; k < NV4; ++k) {
+      const f32x4 v = LOAD_ASIDE((const f32x4*)(a4 + 16u * (uint32_t)min(tid + k * BLOCK, ng - 1)));
+      row.v[k] = make_float4(v[0], v[1], v[2], v[3]);
+    }
     if (tid < row.n_ex) row.ex = at32(arow, row.ex_id);
   };
   const bool early = (flags & 2) != 0;
