@@ -30,6 +30,7 @@
 #define NEAR_DEPTH 44.0f
 #define NEAR_MARGIN 18.1f
 #define NEAR_X_MAX 0.0625f
+#define NEAR_ENOUGH 8
 #define MAX_END_M 8
 #define MAX_EOS_RUN 32
 

@@ -455,6 +455,9 @@ __device__ __forceinline__ unsigned long long joint_key(double J, unsigned long 
 // candidates, peaked posteriors: 11.5 -> 9.0 us a launch against 2 x 4 over all frames; flat ones: the same to 2 %, and against one
 // candidate per wave (4 float4 per lane) at 1500 frames a decode of 16 utterances 9.4 -> 7.2 ms.  Margins of 80 (256 utterances of
 // 1500 frames, beam 20, 60 candidates): a decode 14362 -> 14167 us; with 3 x 2 there 14530.  The first form has nothing to gain.
+// Whole utterances with the eos-run rule are armed at every step; summed over all frames they took up to a quarter longer than
+// with one candidate per wave (498 utterances of 663 to 1007 frames, beam 4: 6.6 -> 8.3 ms; near frames first 6.5; 122 of 590 to
+// 1484, beam 19, 59 candidates: 17.4 -> 18.0 and 11.2).
 // NV4: granules of the row per lane.  BIGK: more candidates per hypothesis than one wave ranks (K > 64, or ids
 // beyond 65535).  Only that form of the
 // kernel carries the paths for it: candidate arrays in global memory when K exceeds the work-group, the exact
@@ -621,12 +624,14 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
     return (p.end_flags & 4) && p.eos_run > 0 && T >= p.eos_run && W > 0 && e == T && re == T && max(s, rs) <= T - p.eos_run + 1;
   };
   // NEAR: the float4 of the window that the sums run over at first, j0 .. j1 - 1, those with frames near g's last label (HypRec),
-  // and the sum from which on the others cannot count (eos-run rule armed: all frames, the sums stop short of the last ones)
+  // and the sum from which on the others cannot count.  With the eos-run rule armed the sums stop short of the last frames: where
+  // less than NEAR_ENOUGH of the frames behind g's last label come before those, most sums would fall below the bound, and all frames
+  // are summed at once
   int j0 = 0, j1 = n4;
   float sum_low = -3.0e38f;
-  if (NEAR && n4 > 0 && !eos_run_armed()) {
+  if (NEAR && n4 > 0) {
     const int a = max(s, (int)(rec.near_frames & 0xffffu) + 1), b = min(e, (int)(rec.near_frames >> 16) + 1);
-    if (a <= b) { j0 = (a - t0) >> 2; j1 = ((b - t0) >> 2) + 1; }
+    if (a <= b && (!eos_run_armed() || tau + NEAR_ENOUGH <= T - p.eos_run)) { j0 = (a - t0) >> 2; j1 = ((b - t0) >> 2) + 1; }
     if (j1 - j0 < n4) sum_low = NEAR_MARGIN - NEAR_DEPTH + fast_logf((float)(4 * (n4 - (j1 - j0))));
   }
   const float* gphi = p.gphi + (size_t)grp * p.Tp;
