@@ -443,7 +443,9 @@ __device__ __forceinline__ unsigned long long joint_key(double J, unsigned long 
 // which a column that several beam slots score is fetched once.
 // flags bit 0: the whole row can be held in registers (NV4 * BLOCK granules); bit 1: rows are fetched before the record says
 // that there is a hypothesis (up to a work-group per compute unit: the dead slots' rows cost nobody's bandwidth then; one
-// utterance 1021 -> 1011 us a decode, 21 with a batch-wide window 1443 -> 1432, 16 whole utterances within the noise).
+// utterance 1021 -> 1011 us a decode, 21 with a batch-wide window 1443 -> 1432, 16 whole utterances within the noise), and the four
+// waves share the ranking of the group's list, with one more barrier (one utterance 965 -> 942, 21 with a batch-wide window 1448 -> 1432,
+// 16 whole utterances 1397 -> 1368; 384 to 1280 groups within half a per cent either way, 5120 slower by that).
 // The arguments in front of the parameter block are what the first loads of a work-group need (the records
 // of the current buffer = p.rec[cur], p.uinfo, p.finished as words, the attention rows, Wb, p.V): as plain
 // leading arguments they are handed to the wave in registers when it starts (kernel-argument preload),
@@ -1032,9 +1034,12 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
         for (int k = 0; k < E2W; ++k) xv0[k] = colf[min(T - R + 1 + k, T)];
       }
       lds_barrier();                                       // prefix scores complete; the other waves are done
-      if (tid >= 64) return;
-      const bool has = tid < K;
-      const int id = cand_id(has ? tid : 0);
+      // (small batches) or they broadcast a quarter of the entries each, turned as in take_k
+      const bool share = early && !e2;
+      if (!share && tid >= 64) return;
+      const int te = ((tid & 63) + 16 * w) & 63;           // (the first wave: tid)
+      const bool has = te < K;
+      const int id = cand_id(has ? te : 0);
       if (logits) row_lse = s_lse;
       if (e2) {
         // eos-run rule by one wave.  The sums so far stop at frame T - R; walking through the last R frames
@@ -1071,18 +1076,24 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
         if (has) s_inc[tid] = canon0(acc);                 // the whole window's sum
         wave_lds_fence();
       }
-      // rank by (joint desc, token asc) on 64-bit keys; joint score (Eq. (1)) and sort key of entry `tid`
-      const float inc = has ? s_inc[tid] : LOG0F;
-      const float av = s_av[has ? tid : 0] - row_lse;
+      // rank by (joint desc, token asc) on 64-bit keys; joint score (Eq. (1)) and sort key of entry `te`
+      const float inc = has ? s_inc[te] : LOG0F;
+      const float av = s_av[has ? te : 0] - row_lse;
       const bool valid = inc > LOG0_CLASS;
       const double ctc = valid ? s_eos[3] + (double)inc : LOG0D;
       const double J = valid ? lam * ctc + s_eos[4] * (double)av + s_eos[2] : LOG0D;
       // equal scores go by token id: the id in 16 bits (below 65536 here; scores equal to within 2^-36 relative count as
       // equal then), or, every id a candidate, the lane, which ascends with the id (2^-46)
       const bool by_lane = (p.mode & SC_RESTRICTED) == 0;
-      const unsigned long long me = joint_key(J, by_lane ? 63ull : 0xFFFFull, by_lane ? 63 - (tid & 63) : 0xFFFF - (id & 0xFFFF),
+      const unsigned long long me = joint_key(J, by_lane ? 63ull : 0xFFFFull, by_lane ? 63 - te : 0xFFFF - (id & 0xFFFF),
                                               has && valid && J == J);
-      const int rank = lanes_above<16>(me, K);             // (lanes past the last entry hold zeros)
+      int rank;                                            // (lanes past the last entry hold zeros)
+      if (share) {
+        ((uint8_t*)s_mx)[4 * te + w] = (uint8_t)lanes_above<16>(me, 16);
+        lds_barrier();
+        if (w != 0) return;
+        rank = (int)((((const uint32_t*)s_mx)[tid] * 0x01010101u) >> 24);
+      } else rank = lanes_above<16>(me, K);
       const int nv = __popcll(__ballot(me != 0ull));
       if (!fire && me != 0ull && rank < Wb) score_late(late_args)->grp_list[(size_t)grp * Wb + rank] = ListEntry{J, id, inc, av, 0};
       if (tid == 0) group_outputs(fire ? 0 : min(nv, Wb));
