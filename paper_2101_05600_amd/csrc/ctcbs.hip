@@ -275,8 +275,10 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   h->score_block = 256;
   // (a batch-wide window is about as wide as its margins where labels come at about the same rate in all utterances: 21 utterances,
   // margins of 5 and 60, 1525 us a decode against 1549 with the form for wide windows)
-  const int margins = c.win_m1 >= 0 && c.win_m2 >= 0 ? c.win_m1 + c.win_m2 + 1 + 3 : 1 << 30;
-  h->score_form = margins <= 128 ? 0 : (margins <= 192 ? 1 : 2);
+  // (no window is wider than the longest utterance, and three frames more where it does not start on a multiple of four)
+  const int longest = c.t_max + 3;
+  const int margins = c.win_m1 >= 0 && c.win_m2 >= 0 && c.win_m1 + c.win_m2 < longest ? c.win_m1 + c.win_m2 + 1 + 3 : longest;
+  h->score_form = margins <= 128 ? 0 : (c.win_m1 >= 0 && c.win_m2 >= 0 && margins <= 192 ? 1 : 2);
   // LDS of the score kernel: the short list (or the radix histogram), the f terms, the per-candidate arrays
   size_t off = restricted ? (size_t)PIVOT_CAP * 8 : 0;
   h->off_f = (int32_t)off;
@@ -294,7 +296,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   if (off > 160 * 1024) return CTCBS_EINVAL;
   // Survivors of the select kernels: per-hypothesis windows whose margins keep them within 128 (256) frames, but for a
   // hypothesis whose two time indices lie far apart, go 16 lanes x 8 frames (32 x 8) each, others 64 x 8.
-  const int span = c.win_union ? 1 << 30 : margins;
+  const int span = c.win_union ? longest : margins;
   h->select_lps = span <= 128 ? 16 : (span <= 256 ? 32 : 64);
   h->select_wide = span > 128;
   // one wave for the ended set and one round of the others for the new hypotheses, as far as a work-group goes

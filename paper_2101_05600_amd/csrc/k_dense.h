@@ -229,6 +229,7 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
     };
     blocks(d.s, d.e, b0, e0); blocks(d.s + d.far_s, d.e - d.far_e, b1, e1);
     b1 = max(b1, b0); e1 = max(min(e1, e0), b1);
+    if (e0 - b0 <= 4) { b1 = b0; e1 = e0; }                    // (two halves a wave at most: nothing to gain)
   }
   const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
   const float* xu = xT + (size_t)u * V * Tp;
