@@ -28,6 +28,14 @@ def test_peaked_posteriors(every, lens, over):
     _decode(lambda c: peaked_ctc(c, every), lens, **over)
 
 
+# utterances about as long as the forms for narrow windows hold (128 frames from a multiple of four on): whole, wide margins, a batch-wide window
+@pytest.mark.parametrize("longest", [124, 125, 126, 129])
+@pytest.mark.parametrize("over", [{}, dict(end_flags=7, eos_run=10), dict(win_m1=200, win_m2=170), dict(win_m1=90, win_m2=60, win_union=1),
+                                  dict(cand_k=0, vocab=60), dict(beam=13)])
+def test_longest_utterance_of_the_narrow_forms(longest, over):
+    _decode(lambda c: peaked_ctc(c, 9), [longest, longest - 1, 30], **over)
+
+
 # the large batches' select kernel, its three widths of a new hypothesis
 @pytest.mark.parametrize("over", [{}, dict(win_m1=100, win_m2=100)])
 def test_large_batch(over):
