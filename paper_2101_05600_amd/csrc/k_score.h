@@ -113,12 +113,15 @@ __device__ __forceinline__ float find_pivot(const float* s_mx, int K, float& M) 
 
 // The same for log-probabilities, whose scale needs no row maximum: sixteenths below zero, counted in LDS by all lanes at once (two
 // counts a word, s_hist zeroed), so that a prefix sum over the 512 counts takes the place of nine dependent rounds, and of the row maximum.
-// Values above zero count as zero; they only cost a longer list.  64 utterances 2760 -> 2699 us a decode, 512 8423 -> 8312, 16 whole
-// utterances 1506 -> 1479; one utterance the same.
+// 64 utterances 2760 -> 2699 us a decode, 512 8423 -> 8312, 16 whole utterances 1506 -> 1479; one utterance the same.
+// Scores on another scale: values above zero count as zero, and three probabilities above 0.94 there are not, so that K values in the
+// first count, or less than K in all of them, send the row to the bisection, which has its scale from the row's maximum (64 utterances
+// whose rows lie 20 higher: 8530 us a decode with a list of all that lies above zero, 2868 with bisection alone, 2843 now).
 __device__ __forceinline__ void pivot_count(uint32_t* s_hist, float mx) {
   const int q = (int)fmaxf(fminf(-16.0f * mx, 511.0f), 0.0f);
   if (q < 511) atomicAdd(&s_hist[q >> 1], (q & 1) ? 0x10000u : 1u);
 }
+template <int BLOCK>
 __device__ __forceinline__ float find_pivot_hist(const uint32_t* s_hist, const float* s_mx, int K) {
   const int lane = threadIdx.x & 63;
   const uint4 h = ((const uint4*)s_hist)[lane];             // counts 8 * lane .. 8 * lane + 7
@@ -126,15 +129,15 @@ __device__ __forceinline__ float find_pivot_hist(const uint32_t* s_hist, const f
   const int all = (int)((s2 & 0xffffu) + (s2 >> 16));
   const int upto = (int)wave_incl_scan_u32((uint32_t)all, lane);
   const unsigned long long reach = __ballot(upto >= K);
-  if (reach == 0ull) return pivot_by_bits(((const float4*)s_mx)[lane], K);
   int n = upto - all, below = 0;                            // (the lane's counts one by one: how many until K are reached)
   auto count = [&](uint32_t w) {
     n += (int)(w & 0xffffu); below += n < K ? 1 : 0;
     n += (int)(w >> 16); below += n < K ? 1 : 0;
   };
   count(h.x); count(h.y); count(h.z); count(h.w);
-  const int first = (__ffsll((long long)reach) - 1) & 63;
-  return (float)(8 * first + __builtin_amdgcn_readlane(below, first) + 1) * -0.0625f;
+  const int first = (__ffsll((long long)reach) - 1) & 63, lim = 8 * first + __builtin_amdgcn_readlane(below, first);
+  float M;
+  return reach != 0ull && lim > 0 ? (float)(lim + 1) * -0.0625f : find_pivot<BLOCK>(s_mx, K, M);   // (uniform)
 }
 
 // This wave's part of the short list.  Its granules whose maximum reaches L are packed into LDS (one ballot per
@@ -722,7 +725,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
       lds_barrier();
       // at least K values of candidates are >= L (-inf if there are not K + 2 lanes with finite maxima)
       float M = 0.0f;
-      const float L = hist ? find_pivot_hist((const uint32_t*)s_wid, s_mx, K + 2) : find_pivot<BLOCK>(s_mx, K + 2, M);
+      const float L = hist ? find_pivot_hist<BLOCK>((const uint32_t*)s_wid, s_mx, K + 2) : find_pivot<BLOCK>(s_mx, K + 2, M);
       TRACE_MARK(7);
       const int nh = collect_hits<BLOCK, NV4>(row, m4, L, p.blank_id, p.eos_id, s_gran + w * ShortList::GCAP,
                                               s_gid + w * ShortList::GCAP, s_ent + w * ShortList::WCAP);

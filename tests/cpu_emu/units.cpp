@@ -43,5 +43,20 @@ extern "C" int unit_dense(const float* x, const float* F, const float* mref, int
   else hipLaunchKernelGGL((k_dense_scores<1, 2>), grid, dim3(256), 0, nullptr, x, F, slots.data(), Wb, Tp, V, p.K, p, 1, 0);
   return 0;
 }
+// The pivot for rows of log-probabilities: s_hist 256 words, mx the lanes' 256 maxima.
+static void unit_pivot_kernel(uint32_t* s_hist, const float* mx, int K, float* out) {
+  s_hist[threadIdx.x] = 0;
+  lds_barrier();
+  pivot_count(s_hist, mx[threadIdx.x]);
+  lds_barrier();
+  const float L = find_pivot_hist<256>(s_hist, mx, K);
+  if ((threadIdx.x & 63) == 0) out[threadIdx.x >> 6] = L;
+}
+extern "C" void unit_pivot(const float* mx, int K, float* out) {
+  alignas(16) uint32_t s_hist[256];
+  alignas(16) float s_mx[256];
+  memcpy(s_mx, mx, sizeof s_mx);
+  hipLaunchKernelGGL(unit_pivot_kernel, dim3(1), dim3(256), 0, nullptr, (uint32_t*)s_hist, (const float*)s_mx, K, out);
+}
 extern "C" void unit_exp(const float* v, int n, float* out) { for (int i = 0; i < n; ++i) out[i] = exp_exact(v[i]); }
 extern "C" int unit_steps_ahead(int poll_every) { return steps_ahead(poll_every); }

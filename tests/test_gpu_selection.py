@@ -49,3 +49,11 @@ def test_values_far_below_the_best():
     def spread(a):
         return np.where(np.isnan(a), a, np.where(a > np.nanmax(a, axis=-1, keepdims=True) - 1e-6, a, a * 8 - 40)).astype(np.float32)
     _decode(vocab=2000, att_fn=spread)
+
+
+# rows on another scale than log-probabilities: above zero, far below it, on both sides of it, and spread so far that the last candidate
+# lies far below the best
+@pytest.mark.parametrize("scale,shift", [(1.0, 40.0), (1.0, -60.0), (1.0, 9.0), (6.0, 50.0)])
+@pytest.mark.parametrize("over", [dict(vocab=2000), dict(vocab=777, cand_k=64)])
+def test_rows_on_another_scale(scale, shift, over):
+    _decode(steps=4, att_fn=lambda a: (a * np.float32(scale) + np.float32(shift)).astype(np.float32), **over)

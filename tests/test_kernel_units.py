@@ -121,6 +121,21 @@ def test_long_sums_of_products(units, T, Wb, low):
     assert np.sqrt(np.mean(err ** 2)) < 1.12 * np.sqrt(expected)
 
 
+# The pivot lets K of the lanes' maxima through, and few more whatever the row's scale: a sixteenth below the K-th largest
+# (or what eight bits of mantissa leave: a 256th of it), and what equals it.  Rows of log-probabilities, of scores above zero, far below
+# it, on both sides of it, and spread so far that the K-th value lies more than 32 below the largest.
+@pytest.mark.parametrize("K", [3, 42, 66])
+@pytest.mark.parametrize("centre,spread", [(-8.0, 2.0), (20.0, 3.0), (3e4, 3.0), (-60.0, 2.0), (-500.0, 3.0), (0.0, 4.0), (-0.5, 0.3), (-20.0, 60.0), (40.0, 90.0)])
+def test_pivot_is_close_to_the_last_candidate(units, K, centre, spread):
+    for seed in range(4):
+        mx = (centre + spread * np.random.default_rng(seed).standard_normal(256)).astype(np.float32)
+        out = np.empty(4, np.float32)
+        units.unit_pivot(ptr(mx), K, ptr(out))
+        kth = np.sort(mx)[-K].astype(np.float64)
+        assert (out == out[0]).all() and (mx >= out[0]).sum() >= K
+        assert out[0] > kth - max(0.125, abs(kth) / 128), (out[0], kth)
+
+
 # The host's lead over the device: two intervals, for close looks five steps at most
 @pytest.mark.parametrize("poll_every,steps", [(1, 2), (2, 4), (3, 5), (8, 5), (16, 5), (17, 34), (1000, 2000), (2 ** 31 - 1, 2 ** 21)])
 def test_lead_of_the_host(units, poll_every, steps):
