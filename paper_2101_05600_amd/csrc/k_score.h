@@ -631,12 +631,16 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   // NEAR: the float4 of the window that the sums run over at first, j0 .. j1 - 1, those with frames near g's last label (HypRec),
   // and the sum from which on the others cannot count.  With the eos-run rule armed the sums stop short of the last frames: where
   // less than NEAR_ENOUGH of the frames behind g's last label come before those, most sums would fall below the bound, and all frames
-  // are summed at once
+  // are summed at once.  Where they fill half of their rounds of loads or less, posteriors are sharp: the rest of the rounds goes to the frames on
+  // both sides, and often no sum is left that the others could count for (margins of 80, three times as sharp: 2260 -> 2020 us a decode;
+  // always, the bytes cost more: long recordings at beam 20 13810 -> 14170)
   int j0 = 0, j1 = n4;
   float sum_low = -3.0e38f;
   if (NEAR && n4 > 0) {
     const int a = max(s, (int)(rec.near_frames & 0xffffu) + 1), b = min(e, (int)(rec.near_frames >> 16) + 1);
     if (a <= b && (!eos_run_armed() || tau + NEAR_ENOUGH <= T - p.eos_run)) { j0 = (a - t0) >> 2; j1 = ((b - t0) >> 2) + 1; }
+    const int m = (j1 - j0 + LPC * IT - 1) / (LPC * IT) * (LPC * IT);
+    if (2 * (j1 - j0) <= m) { j0 = max(0, min(j0 - (m - (j1 - j0)) / 2, n4 - m)); j1 = min(j0 + m, n4); }
     if (j1 - j0 < n4) sum_low = NEAR_MARGIN - NEAR_DEPTH + fast_logf((float)(4 * (n4 - (j1 - j0))));
   }
   const float* gphi = p.gphi + (size_t)grp * p.Tp;
@@ -925,23 +929,45 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
       }
     }
   }
-  if (NEAR && __ballot(low) != 0ull) {                     // (rare) such sums again, over the whole window
+  if (NEAR && __ballot(low) != 0ull) {
+    // Such sums again, over the frames whose f term lies within the margin of the least of them, unless those are among the frames summed.
+    // Sharp posteriors have many such sums (a candidate 30 nats down at the near frames), and f falls as sharply, so that it takes few
+    // frames more (posteriors twice and three times as sharp, against the whole window for each such sum: 16 whole utterances 2155 -> 1518 us
+    // a decode, of 1500 frames 3730 -> 1790, 128 3850 -> 2700, margins of 70 3785 -> 3205; all frames at once 1705, 2230, 3255, 3425).
     wave_lds_fence();
+    float least = 0.0f;                                    // (sum_low lies below -16)
+    for (int c = sg; c < K; c += NSG) { const float v = s_inc[c]; if (v <= sum_low) least = fminf(least, v); }
+    least = fminf(fminf(lane_f(least, 0), lane_f(least, 16)), fminf(lane_f(least, 32), lane_f(least, 48)));
+    const float f_low = fmaxf(least - NEAR_MARGIN - 9.0f, LOG0_CLASS);   // (at most e^9 frames)
+    int ja = j0, jb = j1;
 #pragma unroll 1
-    for (int c = sg; c < K; c += NSG) {
-      if (!(s_inc[c] <= sum_low)) continue;                // uniform over the LPC lanes of a chain
-      const int id = cand_id(c);
-      const float4* f4 = (const float4*)(s_F + ((id == last) ? p.wp_max : 0));
-      ChainSum a;
-      a.M = LOG0F; a.s = 0.0f;
+    for (int i0 = 0; i0 < n4; i0 += 64) {
+      const float4 f = ((const float4*)s_F)[min(i0 + (tid & 63), n4 - 1)];
+      const unsigned long long m = __ballot(fmaxf(fmaxf(f.x, f.y), fmaxf(f.z, f.w)) > f_low);
+      if (m != 0ull) { ja = min(ja, i0 + __ffsll((long long)m) - 1); jb = max(jb, min(i0 + 64 - __clzll((long long)m), n4)); }
+    }
+    if (ja < j0 || jb > j0 + (j1 - j0 + LPC * IT - 1) / (LPC * IT) * (LPC * IT)) {
 #pragma unroll 1
-      for (int j = 0; j < n4; j += LPC) {
-        const int i = min(j + q, n4 - 1);
-        const float4 y[1] = {column(id, i)}, f[1] = {j + q < n4 ? f4[i] : make_float4(LOG0F, LOG0F, LOG0F, LOG0F)};
-        chain_more<LPC, 1>(a, y, f);
+      for (int c = sg; c < K; c += NSG) {
+        if (!(s_inc[c] <= sum_low)) continue;              // uniform over the LPC lanes of a chain
+        const int id = cand_id(c);
+        const float4* f4 = (const float4*)(s_F + ((id == last) ? p.wp_max : 0));
+        ChainSum a;
+        a.M = LOG0F; a.s = 0.0f;
+#pragma unroll 1
+        for (int j = ja; j < jb; j += LPC * IT) {
+          float4 y[IT], f[IT];
+#pragma unroll
+          for (int it = 0; it < IT; ++it) {
+            const int i = min(j + q + it * LPC, n4 - 1);
+            y[it] = column(id, i);
+            f[it] = j + q + it * LPC < n4 ? f4[i] : make_float4(LOG0F, LOG0F, LOG0F, LOG0F);
+          }
+          chain_more<LPC, IT>(a, y, f);
+        }
+        const float inc = chain_finish<LPC>(a);
+        if (q == 0) s_inc[c] = inc;
       }
-      const float inc = chain_finish<LPC>(a);
-      if (q == 0) s_inc[c] = inc;
     }
   }
 

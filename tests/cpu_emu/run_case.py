@@ -2,6 +2,7 @@
 kernels (argv[1] = its shared library), every step compared with the oracle exactly as the GPU
 tests do.  Prints "emu ok <name>" per case; any sanitizer report or mismatch ends it with a non-zero
 status."""
+import ctypes
 import os
 import sys
 
@@ -58,6 +59,8 @@ CASES = {
     # whole utterances, peaked posteriors: sums over the frames near the last label; ids so unlikely that all frames are summed
     "near_frames": (dict(n_utt=2, vocab=40, beam=2, cand_k=20, win_m1=-1, win_m2=-1, end_flags=7, eos_run=3,
                          max_len_ratio=0.0, max_len_abs=4), [150, 61]),
+    # whole utterances, posteriors so sharp that most candidates lie tens of nats down where a label is near
+    "sharp_posteriors": (dict(n_utt=1, vocab=70, beam=1, cand_k=60, win_m1=-1, win_m2=-1, end_flags=3, max_len_ratio=0.0, max_len_abs=3), [900]),
     # logits in, odd vocabulary (radix selection), one candidate per hypothesis
     "logits_odd_vocab": (dict(n_utt=1, vocab=33, beam=2, cand_k=1, win_m1=3, win_m2=8, end_flags=2, att_is_logits=1,
                               max_len_ratio=0.4), [13]),
@@ -154,6 +157,8 @@ def main():
         if name == "near_frames":
             peaked_ctc(ctc, 3, ids=np.arange(20, 38))
             ctc[:, :, 1:8] = -70.0
+        if name == "sharp_posteriors":
+            peaked_ctc(ctc, 9, height=40.0)
         if name == "radix_wide_ties":
             flat = lambda a: np.where(np.isnan(a), a, np.float32(-11.0)).astype(np.float32)
             kw = dict(att_fn=flat, gpu_att_fn=flat)
@@ -172,7 +177,12 @@ def main():
         assert rep["max_score_err"] < tol and rep["max_ctc_err"] < tol, (name, rep)
         if max_steps is None:
             assert res["cells"] == int(res["oracle_cells"]), (name, res["cells"], res["oracle_cells"])
-        print(f"emu ok {name} steps={rep['utt_steps']} score_err={rep['max_score_err']:.2e}", flush=True)
+        loads = getattr(m.lib(), "unit_columns", None)
+        more = ""
+        if loads is not None:
+            loads.restype = ctypes.c_longlong
+            more = f" column_loads_per_term={4 * loads() / max(1, res['cells']):.3f}"
+        print(f"emu ok {name} steps={rep['utt_steps']} score_err={rep['max_score_err']:.2e}{more}", flush=True)
 
 
 if __name__ == "__main__":

@@ -60,3 +60,5 @@ extern "C" void unit_pivot(const float* mx, int K, float* out) {
 }
 extern "C" void unit_exp(const float* v, int n, float* out) { for (int i = 0; i < n; ++i) out[i] = exp_exact(v[i]); }
 extern "C" int unit_steps_ahead(int poll_every) { return steps_ahead(poll_every); }
+// column loads (one float4 of one lane each) of the score kernel so far, where the build counts them
+extern "C" long long unit_columns() { return emu::n_columns; }

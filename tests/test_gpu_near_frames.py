@@ -28,6 +28,16 @@ def test_peaked_posteriors(every, lens, over):
     _decode(lambda c: peaked_ctc(c, every), lens, **over)
 
 
+# so sharp that most candidates lie tens of nats down where a label is near: frames on both sides of the near ones count.  (Height h: the
+# stored variables step by 2 h from frame to frame; a rounding of half a unit in the last place of 120 for each of a few operations of
+# 12 labels stays below 2e-5 root mean square)
+@pytest.mark.parametrize("height,every", [(30.0, 7), (30.0, 60), (60.0, 3), (60.0, 20)])
+@pytest.mark.parametrize("over", [{}, dict(end_flags=7, eos_run=10), dict(win_m1=100, win_m2=70), dict(win_m1=80, win_m2=80, end_flags=7, eos_run=4),
+                                  dict(cand_k=64, beam=13), dict(cand_k=1), dict(cand_k=0, vocab=60), dict(vocab=6000)])
+def test_sharp_posteriors(height, every, over):
+    _decode(lambda c: peaked_ctc(c, every, height), [520, 131], **over)
+
+
 # utterances about as long as the forms for narrow windows hold (128 frames from a multiple of four on): whole, wide margins, a batch-wide window
 @pytest.mark.parametrize("longest", [124, 125, 126, 129])
 @pytest.mark.parametrize("over", [{}, dict(end_flags=7, eos_run=10), dict(win_m1=200, win_m2=170), dict(win_m1=90, win_m2=60, win_union=1),

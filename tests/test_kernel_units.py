@@ -2,6 +2,8 @@
 every operation is IEEE fp32 and exp2 / log2 are libm's: against 64-bit sums of the same fp32 inputs."""
 import ctypes
 import os
+import re
+import subprocess
 import sys
 
 import numpy as np
@@ -134,6 +136,19 @@ def test_pivot_is_close_to_the_last_candidate(units, K, centre, spread):
         kth = np.sort(mx)[-K].astype(np.float64)
         assert (out == out[0]).all() and (mx >= out[0]).sum() >= K
         assert out[0] > kth - max(0.125, abs(kth) / 128), (out[0], kth)
+
+
+# Sums over near frames that the frames left out may count for take in the frames that can, not all of them: in steps
+# whose window is the whole utterance a third of the loads remains (the first of the three steps has no near frames: a
+# term of its third is loaded 1.6 times, and of the others' 0.25 times to begin with).
+def test_sums_of_sharp_posteriors_read_few_frames_more(tmp_path):
+    column = "auto column = [&](int id, int i) {"
+    so = build_emu.build(str(tmp_path), sanitize=False, units=True,
+                         plant=("k_score.h", column, column + " __atomic_fetch_add(&emu::n_columns, 1, __ATOMIC_RELAXED);"))
+    r = subprocess.run([sys.executable, os.path.join(HERE, "cpu_emu", "run_case.py"), so, "sharp_posteriors"],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert float(re.search(r"column_loads_per_term=([\d.]+)", r.stdout).group(1)) < 1.6 / 3 + 2 * 0.5 / 3, r.stdout
 
 
 # The host's lead over the device: two intervals, for close looks five steps at most
