@@ -283,11 +283,11 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   size_t off = restricted ? (size_t)PIVOT_CAP * 8 : 0;
   h->off_f = (int32_t)off;
   // the f terms, padded to whole rounds of the column loads, which NEAR starts anywhere in the window
-  const int round_frames = 4 * 16 * (h->score_form == 1 ? 3 : 2);
-  h->wp_max = (p.Tp + round_frames - 1) / round_frames * round_frames + (h->score_form != 0 ? round_frames : 0);
+  h->score_bigk = K > 64 || V > 65536;
+  const int round_frames = 4 * 16 * (h->score_form == 1 ? 3 : (h->score_form == 2 && h->score_bigk ? 4 : 2));
+  h->wp_max = (p.Tp + round_frames - 1) / round_frames * round_frames + (h->score_form != 0 && !h->score_bigk ? round_frames : 0);
   off += (size_t)2 * h->wp_max * 4;
   h->off_small = (int32_t)off;
-  h->score_bigk = K > 64 || V > 65536;
   const size_t small = (size_t)(h->score_bigk ? (K <= h->score_block ? K : 0) : 64) * 32 + 8;
   const size_t gran = restricted ? (size_t)4 * ShortList::GCAP * 20 : 0;     // (the short list's granules, before those)
   off += small > gran ? small : gran;
@@ -373,9 +373,10 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
 // ones never hold it), and the paths for many candidates only where they can be taken (see k_score)
 template <int BLOCK, int CB, int IT, bool NEAR>
 static hipError_t launch_score(ctcbs* h, const Params& p, const float* att, int l) {
-  if (h->score_bigk) {
-    if (h->score_nv4 <= 5) return launch_score_as<BLOCK, CB, IT, 5, false, true>(h, p, att, l);
-    return launch_score_as<BLOCK, CB, IT, 16, false, true>(h, p, att, l);
+  if (h->score_bigk) {                             // (wide windows: 2 x 4)
+    constexpr int CBK = NEAR && IT == 2 ? 2 : CB, ITK = NEAR && IT == 2 ? 4 : IT;
+    if (h->score_nv4 <= 5) return launch_score_as<BLOCK, CBK, ITK, 5, false, true>(h, p, att, l);
+    return launch_score_as<BLOCK, CBK, ITK, 16, false, true>(h, p, att, l);
   }
   switch (h->score_nv4) {
     case 3: return launch_score_as<BLOCK, CB, IT, 3, NEAR, false>(h, p, att, l);

@@ -463,6 +463,10 @@ __device__ __forceinline__ unsigned long long joint_key(double J, unsigned long 
 // Whole utterances with the eos-run rule are armed at every step; summed over all frames they took up to a quarter longer than
 // with one candidate per wave (498 utterances of 663 to 1007 frames, beam 4: 6.6 -> 8.3 ms; near frames first 6.5; 122 of 590 to
 // 1484, beam 19, 59 candidates: 17.4 -> 18.0 and 11.2).
+// More than 64 candidates: 3 x 2, 2 x 3 as above, wider windows 2 x 4 in rounds of both candidates together, all frames (16 whole utterances
+// of 200 to 500 frames, 256 candidates: 8900 us a decode with 3 x 2, whose last round is two thirds empty, 8470; of 1500 frames, 128
+// candidates 4890 -> 4270, one candidate per wave 5540).  With the eos-run rule armed the two parts of the sums run together too:
+// candidate by candidate, a round's loads after the other's, 1500 frames and 100 candidates take 7260 us a decode, together 4600.
 // NV4: granules of the row per lane.  BIGK: more candidates per hypothesis than one wave ranks (K > 64, or ids
 // beyond 65535).  Only that form of the
 // kernel carries the paths for it: candidate arrays in global memory when K exceeds the work-group, the exact
@@ -729,7 +733,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
       lds_barrier();
       // at least K values of candidates are >= L (-inf if there are not K + 2 lanes with finite maxima)
       float M = 0.0f;
-      const float L = hist ? find_pivot_hist<BLOCK>((const uint32_t*)s_wid, s_mx, K + 2) : find_pivot<BLOCK>(s_mx, K + 2, M);
+      const float L = hist ? find_pivot_hist<BLOCK>((const uint32_t*)s_wid, s_mx, K + 2) : find_pivot<BLOCK>(s_mx, min(K + 2, BLOCK), M);   // (256 candidates: of nearly all lanes)
       TRACE_MARK(7);
       const int nh = collect_hits<BLOCK, NV4>(row, m4, L, p.blank_id, p.eos_id, s_gran + w * ShortList::GCAP,
                                               s_gid + w * ShortList::GCAP, s_ent + w * ShortList::WCAP);
@@ -820,7 +824,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
     g_inc = a->cand_inc + g; g_catt = a->cand_att + g; g_ctc = a->cand_ctc + g; g_joint = a->cand_joint + g; g_pre = a->cand_pre + g;
   }
   // more frames than one round of loads: where that is usual, the candidates' next rounds together
-  constexpr bool TOGETHER = BIGK || (NEAR && IT == 2);
+  constexpr bool TOGETHER = BIGK ? IT == 4 : NEAR && IT == 2;
   bool low = false;                                       // a sum that the frames left out may count for
   for (int cb = 0; cb < K; cb += NSG * CB) {              // (uniform: every chain takes part in every round)
     const int c0 = cb + sg;
@@ -835,6 +839,14 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
       for (int it = 0; it < IT; ++it)                        // unconditional (clamped) loads: all in flight together
         x[b][it] = column(max(ids[b], 0), min(j0 + q + it * LPC, max(n4 - 1, 0)));
     }
+    // the next frames of all candidates of the round
+    auto next_round = [&](int j) {
+#pragma unroll
+      for (int b = 0; b < CB; ++b) {
+#pragma unroll
+        for (int it = 0; it < IT; ++it) x[b][it] = column(max(ids[b], 0), min(j + q + it * LPC, n4 - 1));
+      }
+    };
     if (TOGETHER && !e2g) {
       auto f_terms = [&](int b, int j, float4 (&f)[IT]) {
         const float4* f4 = (const float4*)(s_F + ((ids[b] == last) ? p.wp_max : 0)) + j;
@@ -848,16 +860,38 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
         sum[b] = chain_first<LPC, IT>(x[b], f);
       }
       for (int j = j0 + LPC * IT; j < j1; j += LPC * IT) {
-#pragma unroll
-        for (int b = 0; b < CB; ++b) {
-#pragma unroll
-          for (int it = 0; it < IT; ++it) x[b][it] = column(max(ids[b], 0), min(j + q + it * LPC, n4 - 1));
-        }
+        next_round(j);
 #pragma unroll
         for (int b = 0; b < CB; ++b) {
           float4 f[IT];
           f_terms(b, j, f);
           chain_more<LPC, IT>(sum[b], x[b], f);
+        }
+      }
+    }
+    Lse upto[CB], last_r[CB];
+    if (e2g) {
+      // the sums in two parts: frames up to T - R (needed on their own below) and the last R frames
+      const int tc = T - R;
+#pragma unroll
+      for (int b = 0; b < CB; ++b) { upto[b].m = last_r[b].m = LOG0F; upto[b].s = last_r[b].s = 0.0f; }
+      for (int j = 0; j < n4; j += LPC * IT) {
+        if (j > 0) next_round(j);
+#pragma unroll
+        for (int b = 0; b < CB; ++b) {
+          const float4* f4 = (const float4*)(s_F + ((ids[b] == last) ? p.wp_max : 0));
+#pragma unroll
+          for (int it = 0; it < IT; ++it) {
+            const int i = j + q + it * LPC, tb = t0 + 4 * i;
+            const float4 f = f4[i];
+            float4 fv;
+            fv.x = tb <= tc ? f.x : LOG0F; fv.y = tb + 1 <= tc ? f.y : LOG0F;
+            fv.z = tb + 2 <= tc ? f.z : LOG0F; fv.w = tb + 3 <= tc ? f.w : LOG0F;
+            upto[b] = lse_join(upto[b], lse_block(x[b][it], fv));
+            fv.x = tb > tc ? f.x : LOG0F; fv.y = tb + 1 > tc ? f.y : LOG0F;
+            fv.z = tb + 2 > tc ? f.z : LOG0F; fv.w = tb + 3 > tc ? f.w : LOG0F;
+            last_r[b] = lse_join(last_r[b], lse_block(x[b][it], fv));
+          }
         }
       }
     }
@@ -884,28 +918,8 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
         inc = chain_finish<LPC>(sum[b]);
         if (NEAR) low |= inc <= sum_low;
       } else {
-        // the sum in two parts: frames up to T - R (needed on its own below) and the last R frames
-        Lse a, aq;
-        a.m = aq.m = LOG0F; a.s = aq.s = 0.0f;
-        const int tc = T - R;
-        for (int i0 = 0; i0 < n4; i0 += LPC * IT) {
-#pragma unroll
-          for (int it = 0; it < IT; ++it) {
-            const int i = i0 + q + it * LPC;
-            const int tb = t0 + 4 * i;
-            float4 fv;
-            const float4 f = f4[i];
-            const float4 xv = i0 == 0 ? x[b][it] : column(id, min(i, n4 - 1));
-            fv.x = tb <= tc ? f.x : LOG0F; fv.y = tb + 1 <= tc ? f.y : LOG0F;
-            fv.z = tb + 2 <= tc ? f.z : LOG0F; fv.w = tb + 3 <= tc ? f.w : LOG0F;
-            a = lse_join(a, lse_block(xv, fv));
-            fv.x = tb > tc ? f.x : LOG0F; fv.y = tb + 1 > tc ? f.y : LOG0F;
-            fv.z = tb + 2 > tc ? f.z : LOG0F; fv.w = tb + 3 > tc ? f.w : LOG0F;
-            aq = lse_join(aq, lse_block(xv, fv));
-          }
-        }
-        pre = lse_finish<LPC>(a);
-        inc = lse_finish<LPC>(lse_join(a, aq));
+        pre = lse_finish<LPC>(upto[b]);
+        inc = lse_finish<LPC>(lse_join(upto[b], last_r[b]));
       }
       if (q == 0 && wave_rank) {
         // (joint scores and sort keys: one lane per candidate at the end, not one pass per chain here)
