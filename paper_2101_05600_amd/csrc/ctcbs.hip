@@ -24,6 +24,8 @@ static thread_local int g_last_hip = 0;
 
 #define CTCBS_EARLY_GROUPS 256    // groups up to which the score kernel fetches rows before records (k_score: flags)
 
+#define STATIC_LDS 2560            // bytes: no form of the score kernel declares more LDS of its own
+
 #ifndef CTCBS_SPLIT_GROUPS         // (the CPU build of the tests sets 0: small batches through the other kernel)
 #define CTCBS_SPLIT_GROUPS 2048   // (utterance, beam slot) groups up to which the split select kernel runs, see step_impl
 #endif
@@ -293,7 +295,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   off += small > gran ? small : gran;
   h->score_nv4 = V <= 3072 ? 3 : (V <= 5120 ? 5 : (V <= 10240 ? 10 : 16));
   h->score_smem_bytes = off;
-  if (off > 160 * 1024) return CTCBS_EINVAL;
+  if (off + STATIC_LDS > 160 * 1024) return CTCBS_EINVAL;
   // Survivors of the select kernels: per-hypothesis windows whose margins keep them within 128 (256) frames, but for a
   // hypothesis whose two time indices lie far apart, go 16 lanes x 8 frames (32 x 8) each, others 64 x 8.
   const int span = c.win_union ? longest : margins;
@@ -324,11 +326,11 @@ extern "C" int ctcbs_create(const ctcbs_config_t* cfg, const float* d_ctc_logp, 
   return CTCBS_OK;
 }
 
-// Kernels that want more than 64 KB of dynamic LDS need the attribute raised first.  It belongs to
+// Kernels that want more than 64 KB of LDS (`bytes` dynamic ones beside their own) need the attribute raised first.  It belongs to
 // the kernel, not to a handle: it is only ever raised (handles of different sizes, on different
 // threads, share it), and only when a launch needs more than what is already allowed.
 static hipError_t allow_lds(const void* kernel, size_t bytes) {
-  if (bytes <= 64 * 1024) return hipSuccess;
+  if (bytes + STATIC_LDS <= 64 * 1024) return hipSuccess;
   static std::mutex mu;
   static std::map<const void*, size_t> allowed;
   std::lock_guard<std::mutex> lock(mu);

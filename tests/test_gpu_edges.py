@@ -71,6 +71,15 @@ def test_longest_utterance_windowed():
     run(w, lens=[6140, 6000])
 
 
+@pytest.mark.parametrize("window", [(80, 80), (-1, -1)])
+@pytest.mark.parametrize("k", [64, 256])
+def test_longest_utterance_most_lds(window, k):
+    """The score kernel's largest arrays: f terms of 6140 frames beside those of 64 and 256 candidates."""
+    w = small("cfg1", vocab=270, beam=2, cand_k=k, win_m1=window[0], win_m2=window[1], end_flags=4, eos_run=32,
+              max_len_ratio=0.0, max_len_abs=3)
+    run(w, lens=[6140])
+
+
 def test_longest_end_detection_memory():
     """end_m = 8 (the maximum ring of Eq. (4)) and eos_run = 32 (the maximum run)."""
     w = small("cfg1", n_utt=4, t_lo=50, t_hi=120, vocab=300, beam=5, cand_k=12, win_m1=40, win_m2=40,
