@@ -56,6 +56,7 @@ struct ctcbs {
   bool select_wide;            // windows beyond 128 frames are common
   int score_form;              // window up to 128 frames, up to 192, wider (k_score)
   bool score_bigk;
+  bool want_near;              // the score kernel sums near frames first: the select kernels look for them
   int score_nv4;               // granules of an attention row per lane
   bool dense;                  // every id a candidate: the kernels of k_dense.h
   // Pinned, device-mapped host memory, one allocation: the progress word that the score kernel refreshes every
@@ -288,6 +289,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   h->score_bigk = K > 64 || V > 65536;
   const int round_frames = 4 * 16 * (h->score_form == 1 ? 3 : (h->score_form == 2 && h->score_bigk ? 4 : 2));
   h->wp_max = (p.Tp + round_frames - 1) / round_frames * round_frames + (h->score_form != 0 && !h->score_bigk ? round_frames : 0);
+  h->want_near = h->score_form != 0 && !h->score_bigk && !h->dense;
   off += (size_t)2 * h->wp_max * 4;
   h->off_small = (int32_t)off;
   const size_t small = (size_t)(h->score_bigk ? (K <= h->score_block ? K : 0) : 64) * 32 + 8;
@@ -498,7 +500,7 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   a.rec_new = p.rec[nxt]; a.trie = p.trie_parent + (size_t)l * p.U * p.Wb; a.out = p.out_parent; a.out8 = p.out_live;
   a.trie_stride = (uint32_t)(p.trie_token - p.trie_parent);
   a.U = p.U; a.V = p.V; a.Tp = p.Tp; a.blank_id = p.blank_id; a.end_flags = p.end_flags; a.end_m = p.end_m; a.end_c = p.end_c;
-  a.end_d = p.end_d; a.win_union = p.win_union; a.win_m2 = p.win_m2; a.want_near = h->score_form != 0; a.err = p.err; a.finished = p.finished;
+  a.end_d = p.end_d; a.win_union = p.win_union; a.win_m2 = p.win_m2; a.want_near = h->want_near; a.err = p.err; a.finished = p.finished;
   a.n_finished = p.n_finished; a.cells = p.cells; a.groups = p.groups; a.union_win = p.union_win; a.trace = p.trace;
   const int wb_m = (65536 / p.Wb + 1) << 8 | p.Wb;         // (see k_select)
 #define CTCBS_SELECT(K, G, BS, LDS, L)                                                                       \
@@ -507,7 +509,7 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   if (split) {
     const int sh = 3;
     const dim3 grid(1u << sh, (unsigned)p.Wb + 1, (unsigned)(p.U + (1 << sh) - 1) >> sh);
-    if (h->score_form != 0) CTCBS_SELECT((k_select_split<256, true>), grid, 256, sel_lds, l | sh << 28);
+    if (h->want_near) CTCBS_SELECT((k_select_split<256, true>), grid, 256, sel_lds, l | sh << 28);
     else if (h->select_wide || p.Wb > 12) CTCBS_SELECT((k_select_split<256, false>), grid, 256, sel_lds, l | sh << 28);
     else CTCBS_SELECT((k_select_split<64, false>), grid, 64, sel_lds, l | sh << 28);
   } else {
