@@ -159,8 +159,8 @@ __device__ __forceinline__ int collect_hits(const RowRegs<NV4>& r, const float (
 #pragma unroll
   for (int k = 0; k < NV4; ++k) pack(m4[k] >= L, r.v[k], r.head + 4 * (tid + k * BLOCK));
   if (r.n_ex > 0) {                                        // (uniform)
-    const float ninf = -__builtin_huge_valf();
-    pack(tid < r.n_ex && r.ex >= L, make_float4(r.ex, ninf, ninf, ninf), r.ex_id);
+    const float none = __builtin_nanf("");                 // (never a hit; -inf was one wherever the pivot is -inf)
+    pack(tid < r.n_ex && r.ex >= L, make_float4(r.ex, none, none, none), r.ex_id);
   }
   wave_lds_fence();
   const bool linf = (L == -__builtin_huge_valf());         // then blank and eos are hits too (there may be no K candidates)

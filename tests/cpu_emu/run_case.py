@@ -61,6 +61,9 @@ CASES = {
                          max_len_ratio=0.0, max_len_abs=4), [150, 61]),
     # whole utterances, posteriors so sharp that most candidates lie tens of nats down where a label is near
     "sharp_posteriors": (dict(n_utt=1, vocab=70, beam=1, cand_k=60, win_m1=-1, win_m2=-1, end_flags=3, max_len_ratio=0.0, max_len_abs=3), [900]),
+    # rows that hold fewer numbers than there are candidates, the rest -inf (ids that the decoder masks), and do not start or end
+    # on a 16-byte boundary: the masked ids of the lowest numbers are candidates too, each once
+    "masked_rows": (dict(n_utt=1, vocab=61, beam=3, cand_k=40, win_m1=5, win_m2=5, end_flags=3, max_len_ratio=0.0, max_len_abs=4), [14]),
     # logits in, odd vocabulary (radix selection), one candidate per hypothesis
     "logits_odd_vocab": (dict(n_utt=1, vocab=33, beam=2, cand_k=1, win_m1=3, win_m2=8, end_flags=2, att_is_logits=1,
                               max_len_ratio=0.4), [13]),
@@ -159,6 +162,13 @@ def main():
             ctc[:, :, 1:8] = -70.0
         if name == "sharp_posteriors":
             peaked_ctc(ctc, 9, height=40.0)
+        if name == "masked_rows":
+            def masked(a):
+                a = a.copy()
+                a[..., 3:20] = np.where(np.isnan(a[..., 3:20]), a[..., 3:20], -np.inf)
+                a[..., 24:] = np.where(np.isnan(a[..., 24:]), a[..., 24:], -np.inf)
+                return a
+            kw = dict(att_fn=masked)
         if name == "radix_wide_ties":
             flat = lambda a: np.where(np.isnan(a), a, np.float32(-11.0)).astype(np.float32)
             kw = dict(att_fn=flat, gpu_att_fn=flat)

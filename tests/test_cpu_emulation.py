@@ -77,7 +77,7 @@ def runs(tmp_path_factory):
     asan, tsan = _runtime("libasan.so"), _runtime("libtsan.so")
     plan = {
         "asan": (asan, ASAN_ENV, dict(sanitize=True),
-                 ["windowed", "batch_window", "all_candidates", "all_candidates_few_ids", "logits_odd_vocab", "static_step"],
+                 ["windowed", "batch_window", "all_candidates", "all_candidates_few_ids", "logits_odd_vocab", "static_step", "masked_rows"],
                  ["all_candidates_matrix"],
                  ["pivot", "wide_window_eos_run"], ["pivot_k80", "radix_wide_ties", "k80_eos_run"]),
         # the first steps of a fixed subset of the random configurations that tests/test_gpu_random_configs.py
@@ -117,7 +117,7 @@ def test_kernels_under_address_and_ub_sanitizers(runs):
     r, out = _result(runs, "asan")
     assert r.returncode == 0, out[-4000:]
     assert "ERROR: AddressSanitizer" not in out and "runtime error:" not in out, out[-4000:]
-    assert out.count("emu ok") == 12, out[-2000:]
+    assert out.count("emu ok") == 13, out[-2000:]
 
 
 def test_select_kernel_of_large_batches_under_address_sanitizer(runs):

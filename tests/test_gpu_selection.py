@@ -57,3 +57,14 @@ def test_values_far_below_the_best():
 @pytest.mark.parametrize("over", [dict(vocab=2000), dict(vocab=777, cand_k=64)])
 def test_rows_on_another_scale(scale, shift, over):
     _decode(steps=4, att_fn=lambda a: (a * np.float32(scale) + np.float32(shift)).astype(np.float32), **over)
+
+
+# ids that the decoder masks with -inf: fewer numbers in a row than candidates (masked ids of the lowest numbers fill the list,
+# each once), in rows of every alignment
+@pytest.mark.parametrize("vocab", [45, 61, 270, 1203, 5003])
+@pytest.mark.parametrize("k", [30, 64, 80])
+def test_masked_ids(vocab, k):
+    def masked(a):
+        some = np.arange(vocab) % (vocab // 20) == 1
+        return np.where(np.isnan(a) | some, a, np.float32(-np.inf))
+    _decode(vocab=vocab, cand_k=min(k, vocab - 5), att_fn=masked)
