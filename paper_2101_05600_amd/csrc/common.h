@@ -236,6 +236,17 @@ struct ScoreKernarg {        // all of them, as they lie in the kernel's argumen
   ScoreArgs p;
   ScoreLate late;
 };
+// where a kernel's last argument lies in that segment: each argument at the next multiple of its alignment
+template <class F>
+struct LastArg;
+template <class... A>
+struct LastArg<void (*)(A...)> {
+  static constexpr size_t offset() {
+    size_t at = 0, last = 0;
+    ((last = (at + alignof(A) - 1) / alignof(A) * alignof(A), at = last + sizeof(A)), ...);
+    return last;
+  }
+};
 #if defined(__AMDGCN__)
 typedef const __attribute__((address_space(4))) ScoreLate* ScoreLatePtr;
 __device__ __forceinline__ ScoreLatePtr score_late(const ScoreLate&) {

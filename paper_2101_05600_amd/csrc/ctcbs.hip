@@ -349,6 +349,7 @@ static hipError_t allow_lds(const void* kernel, size_t bytes) {
 
 template <int BLOCK, int CB, int IT, int NV4, bool NEAR, bool BIGK>
 static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, int l) {
+  static_assert(LastArg<decltype(&k_score<BLOCK, CB, IT, NV4, NEAR, BIGK>)>::offset() == offsetof(ScoreKernarg, late), "score_late reads them there");
   hipError_t ea = allow_lds((const void*)k_score<BLOCK, CB, IT, NV4, NEAR, BIGK>, h->score_smem_bytes);
   if (ea != hipSuccess) return ea;
   const int in_regs = p.restricted && p.V >= 8 && p.V <= 4 * NV4 * BLOCK ? 1 : 0;

@@ -495,7 +495,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   const int sh = (flags >> 4) & 15;
   const int u = (int)((blockIdx.z << sh) + blockIdx.x);
   const int grp = u * Wb + (int)blockIdx.y;
-  // first round of loads, g's record and the utterance's constants: one 64-byte line and one 16-byte entry
+  // first round of loads, g's record and the utterance's constants: one 64-byte line and one 32-byte entry
   // through the scalar path (uniform addresses, nothing in this kernel writes them)
   const HypRec rec = rec_now[grp];
   const UttInfo ui = uinfo[u];
