@@ -2,7 +2,7 @@
 //   1. candidate pre-selection: the K ids with the largest attention log-prob, ties to the
 //      smaller id.  The row never goes through LDS: every lane keeps its float4 loads in
 //      registers.  A pivot that is provably not above the K-th largest value (K of the lanes' maxima
-//      reach it; found by bisection with ballots), then
+//      reach it; for log-probabilities from counts of the maxima, else found by bisection with ballots), then
 //      a short list of the few values that reach it (about 1.2 K), then the K largest of these: up to
 //      64 entries are ranked one per lane, the waves sharing the comparisons; more, or equal values at the
 //      K-th place, by quads of lanes.  Rows that do not fit the registers, or with so many values at the
@@ -13,7 +13,8 @@
 //      else phi_{t-1}(g)  (Eq. (3) / Eq. (5)); frames run along lanes (16 lanes per
 //      candidate, float4 per lane), all of a lane's column loads of a round are issued before the first
 //      is consumed; their sums and the largest over the candidate's lanes are taken, then one fused
-//      multiply-add and one exp2 per term;
+//      multiply-add and one exp2 per term.  In wide windows over the frames near g's last label first, and over others
+//      only where a sum does not outweigh what they could add;
 //   4. eos score phi_T(g), joint scores (Eq. (1)), the eos-run test, and the group's
 //      best-first list of at most Wb candidates for the per-utterance selection.
 // The candidate list of a group is in no particular order and no result depends on it; wherever
@@ -1069,9 +1070,8 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
     if (wave_rank) {
       // one lane of the first wave per entry from here on
       constexpr int E2W = 16;                              // eos-run rule: frames per round of loads
-      constexpr bool E2_EARLY = (CB * IT <= 6);            // (the forms with more column loads in flight have no registers to spare)
-      float xv0[E2_EARLY ? E2W : 1];
-      if (E2_EARLY && e2 && tid < 64) {                    // the candidate's posteriors of the last R frames: on
+      float xv0[E2W];
+      if (e2 && tid < 64) {                    // the candidate's posteriors of the last R frames: on
         const float* colf = xu + (size_t)cand_id(tid < K ? tid : 0) * p.Tp;   // their way while the other waves finish
 #pragma unroll
         for (int k = 0; k < E2W; ++k) xv0[k] = colf[min(T - R + 1 + k, T)];
@@ -1098,9 +1098,9 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
         fire = 1;
         for (int k0 = 0; k0 < R; k0 += E2W) {
           float xv[E2W];
-          if (E2_EARLY && k0 == 0) {
+          if (k0 == 0) {
 #pragma unroll
-            for (int k = 0; k < E2W; ++k) xv[k] = xv0[E2_EARLY ? k : 0];
+            for (int k = 0; k < E2W; ++k) xv[k] = xv0[k];
           } else {
 #pragma unroll
             for (int k = 0; k < E2W; ++k) xv[k] = colf[min(T - R + 1 + k0 + k, T)];   // all loads in flight
