@@ -21,12 +21,13 @@ import gen  # noqa: E402
 from helpers import EmuDecoder, lockstep_decode, peaked_ctc  # noqa: E402
 
 CASES = {
-    # split select kernel, 16-lane score kernel, eos-run rule, an unused slot
+    # split select kernel, narrow windows, eos-run rule, an unused slot
     "windowed": (dict(n_utt=3, vocab=40, beam=3, cand_k=6, win_m1=5, win_m2=5, end_flags=7, eos_run=2,
                       max_len_ratio=0.4), [12, 0, 18]),
-    # batch-wide window, 64-lane score kernel (no end margin)
+    # batch-wide window without an end margin: the score kernel's form for wide windows, and a new hypothesis by a whole wave in the
+    # select kernel of large batches
     "batch_window": (dict(n_utt=2, vocab=36, beam=2, cand_k=5, win_m1=4, win_m2=-1, win_union=1, end_flags=3,
-                          max_len_ratio=0.4), [15, 10]),
+                          max_len_ratio=0.0, max_len_abs=4), [262, 30]),
     # every id a candidate, few ids: the score kernel ranks the list itself
     "all_candidates": (dict(n_utt=1, vocab=12, beam=2, cand_k=0, win_m1=-1, win_m2=-1, end_flags=3,
                             max_len_ratio=0.4), [11]),
@@ -52,10 +53,13 @@ CASES = {
     # than 16 bits count, and the K smallest ids must come out
     "radix_wide_ties": (dict(n_utt=1, vocab=66000, beam=1, cand_k=3, win_m1=-1, win_m2=-1, end_flags=3,
                              max_len_abs=3, max_len_ratio=0.0), [5]),
-    # window margins beyond 128 frames: the score kernel's form with four float4 per lane in flight, eos-run
-    # rule armed (its one-wave walk through the last frames after a two-part sum whose second part is empty)
-    "wide_window_eos_run": (dict(n_utt=2, vocab=40, beam=2, cand_k=6, win_m1=70, win_m2=70, end_flags=7, eos_run=3,
-                                 max_len_ratio=0.4), [22, 15]),
+    # window margins beyond 128 frames: the score kernel's form with three float4 per lane in flight, eos-run
+    # rule armed (its one-wave walk through the last frames)
+    "wide_window_eos_run": (dict(n_utt=2, vocab=40, beam=2, cand_k=6, win_m1=50, win_m2=120, end_flags=7, eos_run=3,
+                                 max_len_ratio=0.0, max_len_abs=5), [175, 110]),
+    # the same rule and more than 64 candidates on whole utterances: both parts of the sums in several rounds of 2 x 4
+    "k80_whole_eos_run": (dict(n_utt=2, vocab=1024, beam=2, cand_k=80, win_m1=-1, win_m2=-1, end_flags=7, eos_run=3,
+                               max_len_ratio=0.0, max_len_abs=3), [270, 129]),
     # whole utterances, peaked posteriors: sums over the frames near the last label; ids so unlikely that all frames are summed
     "near_frames": (dict(n_utt=2, vocab=40, beam=2, cand_k=20, win_m1=-1, win_m2=-1, end_flags=7, eos_run=3,
                          max_len_ratio=0.0, max_len_abs=4), [150, 61]),
@@ -68,6 +72,22 @@ CASES = {
     "logits_odd_vocab": (dict(n_utt=1, vocab=33, beam=2, cand_k=1, win_m1=3, win_m2=8, end_flags=2, att_is_logits=1,
                               max_len_ratio=0.4), [13]),
 }
+
+
+# the forms that a case is there for (units.cpp: unit_forms): the score kernel's by the window, lanes per new hypothesis in the select
+# kernel of large batches, whether near frames are looked for
+FORMS = {"windowed": (0, 16, False), "batch_window": (2, 64, True), "wide_window_eos_run": (1, 32, True), "near_frames": (2, 32, True),
+         "sharp_posteriors": (2, 64, True), "k80_eos_run": (0, 16, False), "k80_whole_eos_run": (2, 64, False), "pivot": (0, 16, False)}
+
+
+def decoder_of(forms):
+    class Decoder(EmuDecoder):
+        def __init__(self, *a, **k):
+            super().__init__(*a, **k)
+            if forms is not None:
+                f = m.lib().unit_forms(ctypes.c_void_p(self.h))
+                assert (f & 3, f >> 8, bool(f & 16)) == forms, hex(f)
+    return Decoder
 
 
 def executor_case():
@@ -182,17 +202,15 @@ def main():
                 mx = np.nanmax(z, axis=-1, keepdims=True)
                 return (z - (mx + np.log(np.nansum(np.exp(z - mx), axis=-1, keepdims=True)))).astype(np.float32)
             kw = dict(att_fn=normalised, gpu_att_fn=to_logits)
-        rep, res = lockstep_decode(w, ctc, lens, check_utts=used, decoder_cls=EmuDecoder, max_steps=max_steps, **kw)
+        rep, res = lockstep_decode(w, ctc, lens, check_utts=used, decoder_cls=decoder_of(FORMS.get(name)), max_steps=max_steps, **kw)
         tol = 2e-4 if w.get("att_is_logits") else 1e-4
         assert rep["max_score_err"] < tol and rep["max_ctc_err"] < tol, (name, rep)
         if max_steps is None:
             assert res["cells"] == int(res["oracle_cells"]), (name, res["cells"], res["oracle_cells"])
-        loads = getattr(m.lib(), "unit_columns", None)
-        more = ""
-        if loads is not None:
-            loads.restype = ctypes.c_longlong
-            more = f" column_loads_per_term={4 * loads() / max(1, res['cells']):.3f}"
-        print(f"emu ok {name} steps={rep['utt_steps']} score_err={rep['max_score_err']:.2e}{more}", flush=True)
+        loads = m.lib().unit_columns
+        loads.restype = ctypes.c_longlong
+        print(f"emu ok {name} steps={rep['utt_steps']} score_err={rep['max_score_err']:.2e} "
+              f"column_loads_per_term={4 * loads() / max(1, res['cells']):.3f}", flush=True)
 
 
 if __name__ == "__main__":

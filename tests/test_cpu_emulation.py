@@ -79,13 +79,14 @@ def runs(tmp_path_factory):
         "asan": (asan, ASAN_ENV, dict(sanitize=True),
                  ["windowed", "batch_window", "all_candidates", "all_candidates_few_ids", "logits_odd_vocab", "static_step", "masked_rows"],
                  ["all_candidates_matrix"],
-                 ["pivot", "wide_window_eos_run"], ["pivot_k80", "radix_wide_ties", "k80_eos_run"]),
+                 ["pivot", "wide_window_eos_run"], ["pivot_k80", "radix_wide_ties", "k80_eos_run", "k80_whole_eos_run"]),
         # the first steps of a fixed subset of the random configurations that tests/test_gpu_random_configs.py
         # decodes on the GPU (same table, tests/random_cases.py), device memory starting out as garbage
         "asan_random": (asan, ASAN_ENV, dict(sanitize=True), *[[f"random:{a}:{b}:{c}"] for a, b, c in CPU_SUBSET]),
-        "asan_near": (asan, ASAN_ENV, dict(sanitize=True), ["near_frames"]),
-        # the select kernel of large batches
-        "asan_per_utterance": (asan, ASAN_ENV, dict(sanitize=True, defines=["CTCBS_SPLIT_GROUPS=0"]), ["windowed"], ["batch_window"]),
+        "asan_near": (asan, ASAN_ENV, dict(sanitize=True), ["near_frames"], ["sharp_posteriors"]),
+        # the select kernel of large batches, 16, 64 and 32 lanes per new hypothesis
+        "asan_per_utterance": (asan, ASAN_ENV, dict(sanitize=True, defines=["CTCBS_SPLIT_GROUPS=0"]), ["windowed"], ["batch_window"],
+                               ["near_frames"]),
         # executor: the job queue with two host threads on two handles
         "tsan": (tsan, TSAN_ENV, dict(sanitize="thread"), ["windowed"], ["batch_window"], ["executor"]),
         "tsan_planted": (tsan, TSAN_ENV, dict(sanitize="thread", plant=PLANT), ["windowed"]),
@@ -97,7 +98,7 @@ def runs(tmp_path_factory):
             return "no such sanitizer runtime in this toolchain"
         if not _preload_works(runtime, env):
             return "a Python child does not start with this sanitizer runtime preloaded here"
-        so = build_emu.build(os.path.join(root, name), **build_kw)
+        so = build_emu.build(os.path.join(root, name), units=True, **build_kw)
         with ThreadPoolExecutor(max_workers=len(children)) as ex:
             rs = list(ex.map(lambda cases: _run(so, runtime, env, cases), children))
         return subprocess.CompletedProcess(rs[0].args, max(abs(r.returncode) for r in rs), "".join(r.stdout for r in rs), "".join(r.stderr for r in rs))
@@ -117,21 +118,21 @@ def test_kernels_under_address_and_ub_sanitizers(runs):
     r, out = _result(runs, "asan")
     assert r.returncode == 0, out[-4000:]
     assert "ERROR: AddressSanitizer" not in out and "runtime error:" not in out, out[-4000:]
-    assert out.count("emu ok") == 13, out[-2000:]
+    assert out.count("emu ok") == 14, out[-2000:]
 
 
 def test_select_kernel_of_large_batches_under_address_sanitizer(runs):
     r, out = _result(runs, "asan_per_utterance")
     assert r.returncode == 0, out[-4000:]
     assert "ERROR: AddressSanitizer" not in out and "runtime error:" not in out, out[-4000:]
-    assert out.count("emu ok") == 2, out[-2000:]
+    assert out.count("emu ok") == 3, out[-2000:]
 
 
 def test_sums_over_near_frames_under_address_sanitizer(runs):
     r, out = _result(runs, "asan_near")
     assert r.returncode == 0, out[-4000:]
     assert "ERROR: AddressSanitizer" not in out and "runtime error:" not in out, out[-4000:]
-    assert out.count("emu ok") == 1, out[-2000:]
+    assert out.count("emu ok") == 2, out[-2000:]
 
 
 def test_random_configurations_first_steps_under_address_sanitizer(runs):

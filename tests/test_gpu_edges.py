@@ -54,8 +54,8 @@ def test_widest_beam():
 
 
 def test_longest_utterance_unrestricted_window():
-    """t_max at the limit of the ABI (6140 frames), whole-utterance windows (one wave per candidate,
-    many passes), few steps.
+    """t_max at the limit of the ABI (6140 frames), whole-utterance windows (many rounds of loads),
+    few steps.
     The eos score of a hypothesis of a handful of labels on 6140 frames (the probability that the WHOLE
     utterance is those labels) lies some 2000 nats below its prefix score: it only keeps the 1e-4 bar
     because the per-frame reference B_t is carried in fp64 outside the fp32 state."""

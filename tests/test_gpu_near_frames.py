@@ -46,13 +46,14 @@ def test_longest_utterance_of_the_narrow_forms(longest, over):
     _decode(lambda c: peaked_ctc(c, 9), [longest, longest - 1, 30], **over)
 
 
-# the large batches' select kernel, its three widths of a new hypothesis
-@pytest.mark.parametrize("over", [{}, dict(win_m1=100, win_m2=100)])
+# the large batches' select kernel, its three widths of a new hypothesis: a wave (windows beyond 256 frames), 32 lanes, 16 (up to 128 frames,
+# where no near frames are looked for)
+@pytest.mark.parametrize("over", [{}, dict(win_m1=100, win_m2=100), dict(win_m1=50, win_m2=60)])
 def test_large_batch(over):
     w = gen.workload("cfg1")
     w.update(dict(n_utt=300, vocab=120, beam=8, cand_k=20, win_m1=-1, win_m2=-1, end_flags=3), **over)
     w["eos_id"] = w["vocab"] - 1
-    lens = np.asarray([230 + u % 11 for u in range(300)], np.int32)
+    lens = np.asarray([250 + u % 11 for u in range(300)], np.int32)
     ctc = gen.workload_ctc(w, lens)
     peaked_ctc(ctc, 6)
     rep, _ = lockstep_decode(w, ctc, lens, max_steps=8, check_utts=[0, 10, 299])
