@@ -518,12 +518,15 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   row.ex_id = tid < row.head ? tid : row.head + 4 * ng + (tid - row.head);
   row.ex = -__builtin_huge_valf();
   // (each row is read once: past the L2, whose lines the columns and the state need again.  512 utterances 29.2 -> 27.9 us a launch,
-  // 256 of 1500 frames at beam 20 46.6 -> 45.9, 64 utterances the same)
+  // 256 of 1500 frames at beam 20 46.6 -> 45.9, 64 utterances the same.  Not long rows with many candidates, which mostly end in the
+  // radix selection that reads them again: 26 utterances, 11520 ids, 141 candidates 23050 -> 21130 us a decode; up to 5120 ids 2 % more
+  // for 200 candidates, 2 % less for 100)
   auto fetch_row = [&]() {
     const char* a4 = (const char*)(arow + row.head);
 #pragma unroll
     for (int k = 0; k < NV4; ++k) {
-      const f32x4 v = LOAD_ASIDE((const f32x4*)(a4 + 16u * (uint32_t)min(tid + k * BLOCK, ng - 1)));
+      const f32x4* at = (const f32x4*)(a4 + 16u * (uint32_t)min(tid + k * BLOCK, ng - 1));
+      const f32x4 v = BIGK && NV4 > 5 ? *at : LOAD_ASIDE(at);
       row.v[k] = make_float4(v[0], v[1], v[2], v[3]);
     }
     if (tid < row.n_ex) row.ex = at32(arow, row.ex_id);
