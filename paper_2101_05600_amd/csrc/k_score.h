@@ -83,6 +83,8 @@ struct ShortList {
 // that holds three float4 per lane.)
 __device__ __forceinline__ float pivot_by_bits(float4 m, int K) {
   const float ninf = -__builtin_huge_valf();
+  const int some = (__popcll(__ballot(m.x > ninf)) + __popcll(__ballot(m.y > ninf))) + (__popcll(__ballot(m.z > ninf)) + __popcll(__ballot(m.w > ninf)));
+  if (some < K) return ninf;                               // (few ids)
   const uint32_t k0 = att_key(m.x, -1, -2, -2), k1 = att_key(m.y, -1, -2, -2), k2 = att_key(m.z, -1, -2, -2), k3 = att_key(m.w, -1, -2, -2);
   uint32_t thr = 0;
 #pragma unroll 1
@@ -138,7 +140,8 @@ __device__ __forceinline__ float find_pivot_hist(const uint32_t* s_hist, const f
   count(h.x); count(h.y); count(h.z); count(h.w);
   const int first = (__ffsll((long long)reach) - 1) & 63, lim = 8 * first + __builtin_amdgcn_readlane(below, first);
   float M;
-  return reach != 0ull && lim > 0 ? (float)(lim + 1) * -0.0625f : find_pivot<BLOCK>(s_mx, K, M);   // (uniform)
+  if (reach != 0ull && lim > 0) return (float)(lim + 1) * -0.0625f;   // (uniform)
+  return find_pivot<BLOCK>(s_mx, K, M);
 }
 
 // This wave's part of the short list.  Its granules whose maximum reaches L are packed into LDS (one ballot per

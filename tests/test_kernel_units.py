@@ -178,3 +178,14 @@ def test_forms_by_the_configuration(units, over, form, lps, near):
     f = units.unit_forms(h)
     units.ctcbs_destroy(h)
     assert (f & 3, f >> 8, bool(f & 16)) == (form, lps, near)
+
+
+# fewer lanes with a value than the pivot is to let through: all values
+def test_pivot_of_few_values(units):
+    mx = np.full(256, -np.inf, np.float32)
+    mx[:40] = np.linspace(-9, -3, 40)
+    out = np.empty(4, np.float32)
+    units.unit_pivot(ptr(mx), 42, ptr(out))
+    assert (out == -np.inf).all()
+    units.unit_pivot(ptr(mx), 40, ptr(out))
+    assert (mx >= out[0]).sum() == 40 and out[0] > -9.2
