@@ -54,7 +54,7 @@ struct ctcbs {
   int score_block, select_block;
   int select_lps;              // select kernel: lanes per new hypothesis
   bool select_wide;            // windows beyond 128 frames are common
-  int score_form;              // window up to 128 frames, up to 192, wider (k_score)
+  int score_form;              // score kernel: windows up to 128 frames; 192 frames a round; wider ones, 33 to 48 candidates (see create_impl)
   bool score_bigk;
   bool want_near;              // the score kernel sums near frames first: the select kernels look for them
   int score_nv4;               // granules of an attention row per lane
@@ -282,6 +282,11 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   const int longest = c.t_max + 3;
   const int margins = c.win_m1 >= 0 && c.win_m2 >= 0 && c.win_m1 + c.win_m2 < longest ? c.win_m1 + c.win_m2 + 1 + 3 : longest;
   h->score_form = margins <= 128 ? 0 : (c.win_m1 >= 0 && c.win_m2 >= 0 && margins <= 192 ? 1 : 2);
+  // Wider windows: three candidates per chain and 128 frames a round where the last round has few empty places (33 to 48 candidates),
+  // else two and 192: an empty place costs what a candidate does.  74 utterances of 359 to 983 frames, whole, beam 2, us a
+  // decode, three / two: 16 candidates 2848 / 2601, 24 2886 / 2786, 32 2885 / 2794, 40 2840 / 2946, 50 3373 / 3167, 64 3516 / 3293; 16
+  // utterances, beam 10: 16 candidates 2391 / 2216, 64 2961 / 2747; 16 of 200 to 500 frames, 40 candidates 1405 / 1430.
+  if (h->score_form == 2 && K <= 64 && (K <= 32 || K > 48)) h->score_form = 1;
   // LDS of the score kernel: the short list (or the radix histogram), the f terms, the per-candidate arrays
   size_t off = restricted ? (size_t)PIVOT_CAP * 8 : 0;
   h->off_f = (int32_t)off;

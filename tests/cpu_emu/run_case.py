@@ -26,7 +26,7 @@ CASES = {
                       max_len_ratio=0.4), [12, 0, 18]),
     # batch-wide window without an end margin: the score kernel's form for wide windows, and a new hypothesis by a whole wave in the
     # select kernel of large batches
-    "batch_window": (dict(n_utt=2, vocab=36, beam=2, cand_k=5, win_m1=4, win_m2=-1, win_union=1, end_flags=3,
+    "batch_window": (dict(n_utt=2, vocab=36, beam=2, cand_k=33, win_m1=4, win_m2=-1, win_union=1, end_flags=3,
                           max_len_ratio=0.0, max_len_abs=4), [262, 30]),
     # every id a candidate, few ids: the score kernel ranks the list itself
     "all_candidates": (dict(n_utt=1, vocab=12, beam=2, cand_k=0, win_m1=-1, win_m2=-1, end_flags=3,
@@ -61,10 +61,12 @@ CASES = {
     "k80_whole_eos_run": (dict(n_utt=2, vocab=1024, beam=2, cand_k=80, win_m1=-1, win_m2=-1, end_flags=7, eos_run=3,
                                max_len_ratio=0.0, max_len_abs=3), [270, 129]),
     # whole utterances, peaked posteriors: sums over the frames near the last label; ids so unlikely that all frames are summed
-    "near_frames": (dict(n_utt=2, vocab=40, beam=2, cand_k=20, win_m1=-1, win_m2=-1, end_flags=7, eos_run=3,
+    "near_frames": (dict(n_utt=2, vocab=40, beam=2, cand_k=36, win_m1=-1, win_m2=-1, end_flags=7, eos_run=3,
                          max_len_ratio=0.0, max_len_abs=4), [150, 61]),
     # whole utterances, posteriors so sharp that most candidates lie tens of nats down where a label is near
-    "sharp_posteriors": (dict(n_utt=1, vocab=70, beam=1, cand_k=60, win_m1=-1, win_m2=-1, end_flags=3, max_len_ratio=0.0, max_len_abs=3), [900]),
+    "sharp_posteriors": (dict(n_utt=1, vocab=70, beam=1, cand_k=48, win_m1=-1, win_m2=-1, end_flags=3, max_len_ratio=0.0, max_len_abs=3), [900]),
+    # the same of few candidates: rounds of 192 frames of one candidate per chain
+    "few_candidates": (dict(n_utt=1, vocab=40, beam=2, cand_k=9, win_m1=-1, win_m2=-1, end_flags=3, max_len_ratio=0.0, max_len_abs=3), [420]),
     # rows that hold fewer numbers than there are candidates, the rest -inf (ids that the decoder masks), and do not start or end
     # on a 16-byte boundary: the masked ids of the lowest numbers are candidates too, each once
     "masked_rows": (dict(n_utt=1, vocab=61, beam=3, cand_k=40, win_m1=5, win_m2=5, end_flags=3, max_len_ratio=0.0, max_len_abs=4), [14]),
@@ -77,7 +79,7 @@ CASES = {
 # the forms that a case is there for (units.cpp: unit_forms): the score kernel's by the window, lanes per new hypothesis in the select
 # kernel of large batches, whether near frames are looked for
 FORMS = {"windowed": (0, 16, False), "batch_window": (2, 64, True), "wide_window_eos_run": (1, 32, True), "near_frames": (2, 32, True),
-         "sharp_posteriors": (2, 64, True), "k80_eos_run": (0, 16, False), "k80_whole_eos_run": (2, 64, False), "pivot": (0, 16, False)}
+         "sharp_posteriors": (2, 64, True), "few_candidates": (1, 64, True), "k80_eos_run": (0, 16, False), "k80_whole_eos_run": (2, 64, False), "pivot": (0, 16, False)}
 
 
 def decoder_of(forms):
@@ -180,7 +182,7 @@ def main():
         if name == "near_frames":
             peaked_ctc(ctc, 3, ids=np.arange(20, 38))
             ctc[:, :, 1:8] = -70.0
-        if name == "sharp_posteriors":
+        if name in ("sharp_posteriors", "few_candidates"):
             peaked_ctc(ctc, 9, height=40.0)
         if name == "masked_rows":
             def masked(a):

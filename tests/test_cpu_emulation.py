@@ -83,7 +83,7 @@ def runs(tmp_path_factory):
         # the first steps of a fixed subset of the random configurations that tests/test_gpu_random_configs.py
         # decodes on the GPU (same table, tests/random_cases.py), device memory starting out as garbage
         "asan_random": (asan, ASAN_ENV, dict(sanitize=True), *[[f"random:{a}:{b}:{c}"] for a, b, c in CPU_SUBSET]),
-        "asan_near": (asan, ASAN_ENV, dict(sanitize=True), ["near_frames"], ["sharp_posteriors"]),
+        "asan_near": (asan, ASAN_ENV, dict(sanitize=True), ["near_frames"], ["sharp_posteriors", "few_candidates"]),
         # the select kernel of large batches, 16, 64 and 32 lanes per new hypothesis
         "asan_per_utterance": (asan, ASAN_ENV, dict(sanitize=True, defines=["CTCBS_SPLIT_GROUPS=0"]), ["windowed"], ["batch_window"],
                                ["near_frames"]),
@@ -132,7 +132,7 @@ def test_sums_over_near_frames_under_address_sanitizer(runs):
     r, out = _result(runs, "asan_near")
     assert r.returncode == 0, out[-4000:]
     assert "ERROR: AddressSanitizer" not in out and "runtime error:" not in out, out[-4000:]
-    assert out.count("emu ok") == 2, out[-2000:]
+    assert out.count("emu ok") == 3, out[-2000:]
 
 
 def test_random_configurations_first_steps_under_address_sanitizer(runs):

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 def _decode(edit, lens, steps=12, **over):
     w = gen.workload("cfg1")
-    w.update(dict(n_utt=len(lens), vocab=300, beam=4, cand_k=30, win_m1=-1, win_m2=-1, end_flags=3), **over)
+    w.update(dict(n_utt=len(lens), vocab=300, beam=4, cand_k=40, win_m1=-1, win_m2=-1, end_flags=3), **over)
     w["eos_id"] = w["vocab"] - 1
     lens = np.asarray(lens, np.int32)
     ctc = gen.workload_ctc(w, np.maximum(lens, 1))
@@ -23,7 +23,7 @@ def _decode(edit, lens, steps=12, **over):
 # every: frames between labels, so that few frames, about one round of loads (128 frames) or several are near
 @pytest.mark.parametrize("every,lens", [(4, [300, 129]), (33, [500, 131]), (90, [700, 0, 257]), (5, [1500])])
 @pytest.mark.parametrize("over", [{}, dict(end_flags=7, eos_run=10), dict(win_m1=200, win_m2=170), dict(win_m1=30, win_m2=60, win_union=1),
-                                  dict(cand_k=64, beam=13), dict(cand_k=1)])
+                                  dict(cand_k=64, beam=13), dict(cand_k=1), dict(cand_k=30), dict(cand_k=49)])
 def test_peaked_posteriors(every, lens, over):
     _decode(lambda c: peaked_ctc(c, every), lens, **over)
 

@@ -157,18 +157,21 @@ def test_lead_of_the_host(units, poll_every, steps):
     assert units.unit_steps_ahead(poll_every) == steps
 
 
-# The kernels' forms by the configuration: the score kernel's by the window, near frames looked for where that kernel sums them first
+# The kernels' forms by the configuration: the score kernel's by the window and, in wide ones, by the places that its rounds leave empty, near frames looked for where that kernel sums them first
 # (more than 64 candidates, and the kernels for every id, sum all frames), lanes per new hypothesis by the widest window.
 @pytest.mark.parametrize("over,form,lps,near", [
     (dict(win_m1=50, win_m2=50), 0, 16, False), (dict(win_m1=62, win_m2=62), 0, 16, False), (dict(win_m1=62, win_m2=63), 1, 32, True),
     (dict(win_m1=80, win_m2=80), 1, 32, True), (dict(win_m1=94, win_m2=95), 2, 32, True), (dict(win_m1=126, win_m2=127), 2, 64, True),
     (dict(), 2, 64, True), (dict(t_max=125), 0, 16, False), (dict(t_max=126), 2, 32, True), (dict(t_max=253), 2, 32, True), (dict(t_max=254), 2, 64, True),
     (dict(cand_k=65), 2, 64, False), (dict(cand_k=65, win_m1=80, win_m2=80), 1, 32, False), (dict(cand_k=0), 2, 64, False),
-    (dict(cand_k=0, end_flags=7, eos_run=3), 2, 64, False), (dict(cand_k=0, vocab=60), 2, 64, True),
+    (dict(cand_k=0, end_flags=7, eos_run=3), 2, 64, False), (dict(cand_k=0, vocab=60), 1, 64, True), (dict(cand_k=0, vocab=42), 2, 64, True),
+    (dict(cand_k=10), 1, 64, True), (dict(cand_k=32), 1, 64, True), (dict(cand_k=33), 2, 64, True), (dict(cand_k=48), 2, 64, True),
+    (dict(cand_k=49), 1, 64, True), (dict(cand_k=64), 1, 64, True), (dict(cand_k=10, t_max=125), 0, 16, False),
+    (dict(cand_k=10, win_m1=50, win_m2=90, win_union=1), 1, 64, True),
     (dict(win_m1=50, win_m2=50, win_union=1), 0, 64, False), (dict(win_m1=50, win_m2=50, win_union=1, t_max=125), 0, 16, False)])
 def test_forms_by_the_configuration(units, over, form, lps, near):
     import paper_2101_05600_amd as m
-    c = dict(n_utt=1, t_max=300, vocab=100, beam=2, blank_id=0, cand_k=20, win_m1=-1, win_m2=-1, end_flags=3)
+    c = dict(n_utt=1, t_max=300, vocab=100, beam=2, blank_id=0, cand_k=40, win_m1=-1, win_m2=-1, end_flags=3)
     c.update(over)
     cfg = m.make_config(**c)
     ctc = np.full((c["t_max"], c["vocab"]), -4.6, np.float32)
