@@ -415,6 +415,18 @@ def read_profile_summary(path):
     return traffic, prof_us, prof_when
 
 
+def dense_roofline(score_ms, n_launches, terms, beam, traffic):
+    """The roofline object of the kernel for every id a candidate.  It reads and multiplies only the frames in which some beam slot has a
+    share of its sum, so its rate is that of the bytes the counters read (None without a summary for this size), not
+    of the posteriors of all frames: those stand beside it, with the terms they make up, as what the decode is worth."""
+    us = score_ms * 1e3 / max(n_launches, 1)
+    ach = traffic / us * 1e-3 if traffic else None
+    return {"bound": "hbm", "kernel": "k_dense_scores", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": ach / HBM_PEAK_GBS if ach else None, "achieved_how": "measured bytes over the time of the HIP events, which span k_dense_prep too",
+            "traffic": traffic, "avg_launch_us": us, "bytes_of_all_frames_per_launch": 4.0 * terms / beam / max(n_launches, 1),
+            "effective_terms_per_sec": terms / (score_ms * 1e-3)}
+
+
 def source_hash():
     """Hash of the library's device sources without comments and blanks: a profile is of this build if it carries the same."""
     import hashlib
@@ -575,24 +587,24 @@ def main():
     score_ms, select_ms, n_prof = prof
     K = int(w["cand_k"]) if 0 < w["cand_k"] < w["vocab"] - 2 else w["vocab"] - 2
     restricted = 0 < w["cand_k"] < w["vocab"] - 2
+    matrix = not restricted and K > 64                       # (none of the workloads with every id has the eos-run rule, raw scores or one window)
     # algorithmic bytes of the score kernel over the decode: candidate columns 4 B per term,
-    # the parent's two forward variables 8 B per window frame, the attention row 4V per group.  Every id a candidate:
-    # a posterior column is read once for the Wb beam slots of its utterance, 4 / Wb bytes per term (every slot live)
-    bytes_score = 4.0 * b.cells + 8.0 * b.cells / K + 4.0 * w["vocab"] * b.groups if restricted else 4.0 * b.cells / w["beam"]
+    # the parent's two forward variables 8 B per window frame, the attention row 4V per group
+    bytes_score = 4.0 * b.cells + 8.0 * b.cells / K + 4.0 * w["vocab"] * b.groups
     ach = bytes_score / (score_ms * 1e-3) / 1e9
     # measured HBM bytes per launch of the same kernel (rocprofv3 FETCH_SIZE / WRITE_SIZE, scaled by a
     # plain copy): taken from the committed counter summary, not measurable from inside this process
-    tname = f"k_score_{a.workload}_traffic.txt" if restricted else f"k_dense_{a.workload}_traffic.txt"
+    size = f"_u{a.utts}" if a.utts else ""                                      # (at the size that was counted alone)
+    tname = f"k_{'dense' if matrix else 'score'}_{a.workload}{size}_traffic.txt"
     tpath = os.path.join(ROOT, "profiles", tname)
-    traffic, prof_us, prof_when = (read_profile_summary(tpath)
-                                   if a.utts == 0 else (None, None, None))   # read at the workload's own size
+    traffic, prof_us, prof_when = read_profile_summary(tpath)
     # from the committed rocprofv3 summary (a profiler cannot run inside this process): the kernel's own average duration,
     # the fraction of the roof it gives, what the HBM counters read, and whether it was taken on the sources of this build
     rocprof = {"avg_launch_us": prof_us,
-               "frac": (bytes_score / max(n_prof, 1) / (prof_us * 1e-6) / 1e9 / HBM_PEAK_GBS) if prof_us else None,
+               "frac": ((traffic if matrix else bytes_score / max(n_prof, 1)) / (prof_us * 1e-6) / 1e9 / HBM_PEAK_GBS) if prof_us and traffic else None,
                "traffic_bytes_per_launch": traffic, "source": "profiles/" + tname, "measured": prof_when,
                "same_sources": profile_hash(tpath) == source_hash()}
-    if restricted:
+    if not matrix:
         roof = {"bound": "hbm", "kernel": "k_score", "achieved": ach, "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": ach / HBM_PEAK_GBS, "traffic": traffic,
                 "avg_launch_us": score_ms * 1e3 / max(n_prof, 1),
@@ -603,13 +615,8 @@ def main():
                 "select_kernel_avg_us": select_ms * 1e3 / max(n_prof, 1),
                 "rocprof": rocprof}
     else:
-        # (each term is one fp32 multiply-add on the matrix cores; the HIP events span k_dense_prep and k_dense_scores)
-        roof = {"bound": "hbm", "kernel": "k_dense_scores", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": ach / HBM_PEAK_GBS, "traffic": traffic, "avg_launch_us": score_ms * 1e3 / max(n_prof, 1),
-                "algorithmic_bytes_per_launch": bytes_score / max(n_prof, 1),
-                "select_kernel_avg_us": select_ms * 1e3 / max(n_prof, 1),
-                "frac_of_fp32_matrix_peak": 2.0 * b.cells / (score_ms * 1e-3) / 157.3e12,
-                "rocprof": rocprof}
+        roof = dense_roofline(score_ms, n_prof, b.cells, w["beam"], traffic)
+        roof.update(select_kernel_avg_us=select_ms * 1e3 / max(n_prof, 1), rocprof=rocprof)
     line = {
         "metric": "CTC prefix-score cells/sec (utt·beam·cand·frame) + utterances/sec at B=64",
         "value": b.cells / (dt / a.steps), "unit": "cells/s",

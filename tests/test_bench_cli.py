@@ -44,3 +44,15 @@ def test_profiles_are_told_from_those_of_other_sources():
         assert re.fullmatch("[0-9a-f]{12}", bench.profile_hash(os.path.join(ROOT, "profiles", f"k_score_{wl}_traffic.txt")))
     assert re.fullmatch("[0-9a-f]{12}", bench.source_hash())
     assert bench.profile_hash(os.path.join(ROOT, "profiles", "no_such_file.txt")) is None
+
+
+def test_rate_of_the_matrix_form_is_that_of_the_bytes_it_reads():
+    """Every id a candidate: frames without a share are skipped, so the rate comes from the counters' bytes; without them there is none."""
+    sys.path.insert(0, ROOT)
+    import bench
+    traffic, us, _ = bench.read_profile_summary(os.path.join(ROOT, "profiles", "k_dense_cfg4a_u32_traffic.txt"))
+    r = bench.dense_roofline(1e-3 * us * 10, 10, 4e11, 20, traffic)
+    assert abs(r["achieved"] - traffic / us * 1e-3) < 1e-6 * r["achieved"] and 0.0 < r["frac"] < 0.8
+    assert r["bytes_of_all_frames_per_launch"] == 4e11 * 4 / 20 / 10 and "frac_of_fp32_matrix_peak" not in r
+    r = bench.dense_roofline(1.0, 10, 4e11, 20, None)
+    assert r["achieved"] is None and r["frac"] is None
