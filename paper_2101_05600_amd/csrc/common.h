@@ -182,7 +182,8 @@ struct Params {
 // loads written above it are issued together and waited for once.  LOADED does the same for vector registers: without it
 // the compiler moves a load into the branch that alone uses it, behind the arrival of the loads before, and a
 // round of loads becomes a chain of them; FETCH is a load that stays where it is written, without a wait.  SCHED_FENCE: no instruction is moved across (a prefetch stays ahead of the work).
-// OPAQUE: what follows from a scalar is worked out again, not kept.  STORE_ASIDE, LOAD_ASIDE: past the L2, which holds what the kernels read again.
+// OPAQUE: what follows from a scalar is worked out again, not kept.  STORE_ASIDE, LOAD_ASIDE: past the L2, which holds what the kernels read again.  STORE_FLAG: several
+// may store it, all the same value, for later kernels.
 #if defined(__AMDGCN__)
 #define PIN4(a, b, c, d) __asm__ volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d))
 #define LOADED(a) __asm__ volatile("" : "+v"(a))
@@ -190,6 +191,7 @@ struct Params {
 #define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 #define FETCH(ptr) __hip_atomic_load(ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT)
 #define STORE_ASIDE(v, ptr) __builtin_nontemporal_store(v, ptr)
+#define STORE_FLAG(v, ptr) __hip_atomic_store(ptr, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT)
 #define LOAD_ASIDE(ptr) __builtin_nontemporal_load(ptr)
 #else
 #define PIN4(a, b, c, d) do { } while (0)
@@ -198,6 +200,7 @@ struct Params {
 #define SCHED_FENCE() do { } while (0)
 #define FETCH(ptr) (*(ptr))
 #define STORE_ASIDE(v, ptr) (*(ptr) = (v))
+#define STORE_FLAG(v, ptr) __atomic_store_n(ptr, v, __ATOMIC_RELAXED)
 #define LOAD_ASIDE(ptr) (*(ptr))
 #endif
 

@@ -233,6 +233,7 @@ inline void launch(dim3 grid, dim3 block, size_t smem, const std::function<void(
   dog.join();
 }
 inline long long n_columns = 0;          // (test_kernel_units.py plants its counting)
+inline long long n_atomic_or = 0;
 }  // namespace emu
 
 #define threadIdx (emu::self().tid)
@@ -355,7 +356,7 @@ inline float __builtin_amdgcn_logf(float x) { return log2f(x); }            // (
 inline int atomicAdd(int* p, int v) { return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST); }
 inline unsigned atomicAdd(unsigned* p, unsigned v) { return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST); }
 inline unsigned long long atomicAdd(unsigned long long* p, unsigned long long v) { return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST); }
-inline int atomicOr(int* p, int v) { return __atomic_fetch_or(p, v, __ATOMIC_SEQ_CST); }
+inline int atomicOr(int* p, int v) { __atomic_fetch_add(&emu::n_atomic_or, 1, __ATOMIC_RELAXED); return __atomic_fetch_or(p, v, __ATOMIC_SEQ_CST); }
 template <class T> inline T emu_atomic_minmax(T* p, T v, bool is_min) {
   T cur = __atomic_load_n(p, __ATOMIC_SEQ_CST);
   while ((is_min ? v < cur : v > cur) &&

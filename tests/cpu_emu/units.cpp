@@ -62,6 +62,10 @@ extern "C" void unit_exp(const float* v, int n, float* out) { for (int i = 0; i 
 extern "C" int unit_steps_ahead(int poll_every) { return steps_ahead(poll_every); }
 // column loads (one float4 of one lane each) of the score kernel so far, where the build counts them
 extern "C" long long unit_columns() { return emu::n_columns; }
+// atomicOr calls so far
+extern "C" long long unit_atomic_ors() { return emu::n_atomic_or; }
+// whether an utterance's posteriors were found to be no log-posteriors
+extern "C" int unit_above0(const ctcbs* h, int u) { return h->p.uinfo[u].above0; }
 // which forms of the kernels a handle runs: bits 0-1 score kernel's window form, 2 more than 64 candidates, 3 every id's own kernels, 4 near
 // frames are looked for, 8-15 lanes per new hypothesis (select kernel of large batches)
 extern "C" int unit_forms(const ctcbs* h) {

@@ -183,6 +183,23 @@ def test_forms_by_the_configuration(units, over, form, lps, near):
     assert (f & 3, f >> 8, bool(f & 16)) == (form, lps, near)
 
 
+# Posteriors that are no log-posteriors set the utterance's flag, without an atomic per tile (all XCDs meet at its address); ones rounded
+# a little above zero do not.
+@pytest.mark.parametrize("vocab,T,value,above", [(130, 40, 2.0, 1), (130, 40, 0.05, 0), (131, 20, np.inf, 1)])
+def test_values_above_zero_set_a_flag_without_atomics(units, vocab, T, value, above):
+    import paper_2101_05600_amd as m
+    units.unit_atomic_ors.restype = ctypes.c_longlong
+    cfg = m.make_config(n_utt=2, t_max=T, vocab=vocab, beam=2, blank_id=0, cand_k=20, win_m1=-1, win_m2=-1, end_flags=3)
+    ctc = np.full((2, T, vocab), -3.0, np.float32)
+    ctc[1, T - 2, vocab - 1] = value
+    lens = np.array([T, T - 1], np.int32)
+    h, before = vp(), units.unit_atomic_ors()
+    assert units.ctcbs_create(ctypes.byref(cfg), ptr(ctc), ptr(lens), ctypes.byref(h)) == 0
+    found = [units.unit_above0(h, u) for u in (0, 1)]
+    units.ctcbs_destroy(h)
+    assert found == [0, above] and units.unit_atomic_ors() == before
+
+
 # fewer lanes with a value than the pivot is to let through: all values
 def test_pivot_of_few_values(units):
     mx = np.full(256, -np.inf, np.float32)
