@@ -52,6 +52,8 @@ __device__ __forceinline__ float add_log(float M, float sum) {
   return h + (((M - (h - d)) + (k - d)) + fmaf(e, 1.42860682e-6f, t));
 }
 
+template <int N> struct Const { static constexpr int value = N; };
+
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __restrict__ att, int l, int cur) {
   extern __shared__ __align__(16) unsigned char dense_smem[];
@@ -87,28 +89,33 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
   float m = LOG0F;
   Lse a;                                                       // the repeated label's sum
   a.m = LOG0F; a.s = 0.0f;
-  // frames per lane and round, their loads in flight together (one by one: 7.8 -> 6.9 us a launch at 1500 frames)
-  constexpr int R = 3;
-  for (int t0 = lo; t0 <= hi; t0 += R * BLOCK) {
-    float ph[R], pb[R], x[R];
-    double B[R];
+  // R frames per lane and round, their loads in flight together: three (one by one: 7.8 -> 6.9 us a launch at 1500 frames), one where that
+  // is the whole window, whose frames would be asked for three times over (70 utterances of 1100 frames, beam 24, windows of 60: 6.2
+  // us a launch one by one, 7.8 with three always, 7.1 now; at 1500 frames, whole, 7.0 -> 6.7: the last steps' windows are short)
+  auto take = [&](auto rounds) {
+    constexpr int R = decltype(rounds)::value;
+    for (int t0 = lo; t0 <= hi; t0 += R * BLOCK) {
+      float ph[R], pb[R], x[R];
+      double B[R];
 #pragma unroll
-    for (int k = 0; k < R; ++k) {
-      const int t = min(t0 + k * BLOCK + tid, hi);
-      ph[k] = FETCH(gphi + t - 1); pb[k] = FETCH(gb + t - 1); B[k] = FETCH(Bu + t - 1); x[k] = FETCH(xr + t);
-    }
+      for (int k = 0; k < R; ++k) {
+        const int t = min(t0 + k * BLOCK + tid, hi);
+        ph[k] = FETCH(gphi + t - 1); pb[k] = FETCH(gb + t - 1); B[k] = FETCH(Bu + t - 1); x[k] = FETCH(xr + t);
+      }
 #pragma unroll
-    for (int k = 0; k < R; ++k) {
-      const int t = t0 + k * BLOCK + tid;
-      if (t > hi) break;
-      const float bt = (float)(B[k] - Bref), f = canon0(ph[k] + bt);
-      dense_f_lds[t] = f;
-      m = fmaxf(m, f);
-      Lse v;
-      v.m = canon0(pb[k] + bt) + x[k]; v.s = 1.0f;
-      a = lse_join(a, v);
+      for (int k = 0; k < R; ++k) {
+        const int t = t0 + k * BLOCK + tid;
+        if (t > hi) break;
+        const float bt = (float)(B[k] - Bref), f = canon0(ph[k] + bt);
+        dense_f_lds[t] = f;
+        m = fmaxf(m, f);
+        Lse v;
+        v.m = canon0(pb[k] + bt) + x[k]; v.s = 1.0f;
+        a = lse_join(a, v);
+      }
     }
-  }
+  };
+  if (hi - lo < BLOCK) take(Const<1>()); else take(Const<3>());
   m = row16_max(m);
   m = fmaxf(fmaxf(lane_f(m, 0), lane_f(m, 16)), fmaxf(lane_f(m, 32), lane_f(m, 48)));
   const float am = chain_max<64>(a.m), as = chain_sum<64>(a.s * __builtin_amdgcn_exp2f((a.m - am) * L2E));

@@ -33,7 +33,7 @@ def test_slot_tiles(beam):
     _decode(vocab=130, beam=beam)
 
 
-@pytest.mark.parametrize("frames", [1, 2, 15, 16, 17, 31, 33, 257, 1600])
+@pytest.mark.parametrize("frames", [1, 2, 15, 16, 17, 31, 33, 256, 257, 258, 1600])
 def test_frame_blocks(frames):
     _decode(vocab=100, lens=[frames, max(1, frames - 1)], steps=min(4, frames))
 
