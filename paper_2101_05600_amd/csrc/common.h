@@ -24,8 +24,8 @@
 // A prefix score is a sum over frames of exp(f + x), x <= 0, and most of it comes from the frames round the hypothesis's last
 // label: away from them f falls by nats with every label that is missed.  A record says which frames have f above
 // -NEAR_DEPTH; the score kernel sums those, and others only for candidates whose sum does not exceed by 2^26 (NEAR_MARGIN)
-// all that they could add, their number times exp(-NEAR_DEPTH) (those among them that can count).  (Increments of 40 candidates lie 9 to 16 nats below the largest f
-// on posteriors of 5000 ids, whose bound is -20 for 300 frames left out.)  Where a "log-posterior" above NEAR_X_MAX was given,
+// all that they could add, their number times exp(-NEAR_DEPTH) (those among them that can count).  (Increments of 40 candidates lie 9
+// to 16 nats below the largest f on posteriors of 5000 ids, whose bound is -20 for 300 frames left out.)  Where a "log-posterior" above NEAR_X_MAX was given,
 // that bound does not hold and all frames are summed.
 #define NEAR_DEPTH 44.0f
 #define NEAR_MARGIN 18.1f

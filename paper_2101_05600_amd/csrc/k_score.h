@@ -459,8 +459,8 @@ __device__ __forceinline__ unsigned long long joint_key(double J, unsigned long 
 // so that the record's load does not have to wait for a load of the argument block first.
 // CB candidates per chain of 16 lanes and round, IT float4 of each in flight.  Windows of up to 128 frames: 3 x 2, up to 192:
 // 2 x 3, both with a loop per candidate for what lies beyond; the same registers, and one more frame round costs what one
-// more candidate round does.  Wider windows, whole utterances: 3 x 2, rounds of all three candidates together.  NEAR, all but the
-// first: at first over the frames near g's last label only (HypRec::near_frames).  500 frames, 16 utterances, beam 10, 40
+// more candidate round does.  Wider windows, whole utterances: 3 x 2 for 33 to 48 candidates, rounds of all three together, 2 x 3 for other
+// numbers, which would leave places of three empty (create_impl).  NEAR, all but the first: at first over the frames near g's last label only (HypRec::near_frames).  500 frames, 16 utterances, beam 10, 40
 // candidates, peaked posteriors: 11.5 -> 9.0 us a launch against 2 x 4 over all frames; flat ones: the same to 2 %, and against one
 // candidate per wave (4 float4 per lane) at 1500 frames a decode of 16 utterances 9.4 -> 7.2 ms.  Margins of 80 (256 utterances of
 // 1500 frames, beam 20, 60 candidates): a decode 14362 -> 14167 us; with 3 x 2 there 14530.  The first form has nothing to gain.
