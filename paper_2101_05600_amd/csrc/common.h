@@ -450,6 +450,32 @@ __device__ __forceinline__ void above8(unsigned long long v, int& n) {
   }
 #endif
 }
+// na, nb += how many of the values v of lanes I .. I + 7 exceed the lane's own a, b.
+#if defined(__AMDGCN__)
+#define ABOVE_2(A, B, C, D)                                                                                        \
+  "v_readlane_b32 s46, %2, " A "\n\tv_readlane_b32 s47, %2, " B "\n\t"                                             \
+  "v_readlane_b32 s48, %2, " C "\n\tv_readlane_b32 s49, %2, " D "\n\t"                                             \
+  "v_cmp_gt_u32_e64 vcc, s46, %3\n\tv_cmp_gt_u32_e64 s[40:41], s47, %3\n\t"                                        \
+  "v_cmp_gt_u32_e64 s[42:43], s48, %3\n\tv_cmp_gt_u32_e64 s[44:45], s49, %3\n\t" ABOVE_ADD                         \
+  "v_cmp_gt_u32_e64 vcc, s46, %4\n\tv_cmp_gt_u32_e64 s[40:41], s47, %4\n\t"                                        \
+  "v_cmp_gt_u32_e64 s[42:43], s48, %4\n\tv_cmp_gt_u32_e64 s[44:45], s49, %4\n\t"                                   \
+  "v_addc_co_u32_e64 %1, vcc, 0, %1, vcc\n\tv_addc_co_u32_e64 %1, s[40:41], 0, %1, s[40:41]\n\t"                   \
+  "v_addc_co_u32_e64 %1, s[42:43], 0, %1, s[42:43]\n\tv_addc_co_u32_e64 %1, s[44:45], 0, %1, s[44:45]\n\t"
+#endif
+template <int I>
+__device__ __forceinline__ void above8(uint32_t v, uint32_t a, uint32_t b, int& na, int& nb) {
+#if defined(__AMDGCN__)
+  __asm__("s_nop 0\n\t" ABOVE_2("%5", "%6", "%7", "%8") ABOVE_2("%9", "%10", "%11", "%12")
+          : "+v"(na), "+v"(nb)
+          : "v"(v), "v"(a), "v"(b), "i"(I), "i"(I + 1), "i"(I + 2), "i"(I + 3), "i"(I + 4), "i"(I + 5), "i"(I + 6), "i"(I + 7)
+          : "vcc", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49");
+#else
+  for (int k = 0; k < 8; ++k) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)v, I + k);
+    na += o > a ? 1 : 0; nb += o > b ? 1 : 0;
+  }
+#endif
+}
 // the same over the first `count` lanes (uniform, up to STEP - 1 more are counted: they hold values below every other)
 template <int STEP, class V>
 __device__ __forceinline__ int lanes_above(V v, int count) {

@@ -4,8 +4,8 @@
 //      registers.  A pivot that is provably not above the K-th largest value (K of the lanes' maxima
 //      reach it; for log-probabilities from counts of the maxima, else found by bisection with ballots), then
 //      a short list of the few values that reach it (about 1.2 K), then the K largest of these: up to
-//      64 entries are ranked one per lane, the waves sharing the comparisons; more, or equal values at the
-//      K-th place, by quads of lanes.  Rows that do not fit the registers, or with so many values at the
+//      64 entries are ranked one per lane, up to 128 two per lane, the waves sharing the comparisons; more, or equal
+//      values at the K-th place, by quads of lanes.  Rows that do not fit the registers, or with so many values at the
 //      pivot that the short list overflows (heavy ties), take a radix select that re-reads the row.
 //   2. window [s, e] from g's time indices (the two equations after Eq. (5));
 //   3. prefix score of every extension g.c: log-sum over t in [s, e] of
@@ -212,6 +212,38 @@ __device__ __forceinline__ bool take_k(int w, const unsigned long long* s_ent, c
     ids[pos] = (int)~(uint32_t)me;
     if (w == 0) s_av[pos] = key_to_att((uint32_t)(me >> 32));
   }
+  return true;
+}
+
+// The same of 65 to 128 entries, two per lane (60 candidates: about 73 entries), whose ranking by quads of lanes, each reading the whole
+// list from LDS, took 2.1 of a work-group's 10.4 us (256 utterances, beam 20, 60 candidates: a decode 13840 -> 13570 us).  Rows of
+// 50 candidates have that many now and then.
+__device__ __forceinline__ bool take_k_of_128(int w, const unsigned long long* s_ent, const ShortList& sl, int K, uint32_t* s_part, int32_t* ids, float* s_av) {
+  const int lane = threadIdx.x & 63, turned = (lane + 16 * w) & 63;
+  const uint32_t* hi = (const uint32_t*)s_ent + 1;
+  const uint32_t a = hi[2 * sl.at(turned)], b1 = hi[2 * sl.at(min(64 + turned, sl.n - 1))], b = 64 + turned < sl.n ? b1 : 0u;
+  int na = 0, nb = 0;
+  above8<0>(a, a, b, na, nb); above8<8>(a, a, b, na, nb);
+  if (64 + 16 * w < sl.n) {                                // (uniform)
+    above8<0>(b, a, b, na, nb);
+    if (72 + 16 * w < sl.n) above8<8>(b, a, b, na, nb);
+  }
+  ((uint8_t*)s_part)[4 * turned + w] = (uint8_t)na;
+  ((uint8_t*)s_part)[256 + 4 * turned + w] = (uint8_t)nb;
+  lds_barrier();
+  auto rank = [&](int e) { return (int)((s_part[e] * 0x01010101u) >> 24); };   // (at most 127)
+  const bool ta = rank(lane) < K, tb = 64 + lane < sl.n && rank(64 + lane) < K;
+  const unsigned long long ba = __ballot(ta), bb = __ballot(tb);
+  if (__popcll(ba) + __popcll(bb) != K) return false;      // (equal values have equal ranks)
+  auto put = [&](int pos, int e) {
+    const unsigned long long me = s_ent[sl.at(e)];
+    ids[pos] = (int)~(uint32_t)me;
+    if (w == 0) s_av[pos] = key_to_att((uint32_t)(me >> 32));
+  };
+  auto before = [&](unsigned long long m) { return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u)); };
+  const int pa = before(ba), pb = __popcll(ba) + before(bb);
+  if (ta) put(pa, lane);
+  if (tb) put(pb, 64 + lane);
   return true;
 }
 
@@ -776,6 +808,10 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
       }
       if (!BIGK && ok && sl.n <= 64) {
         direct = take_k(w, s_ent, sl, K, (uint32_t*)s_mx, s_wid + 64 * w, s_av);
+        wave_lds_fence();
+      }
+      if (!BIGK && ok && sl.n > 64 && sl.n <= 128) {
+        direct = take_k_of_128(w, s_ent, sl, K, (uint32_t*)s_mx, s_wid + 64 * w, s_av);
         wave_lds_fence();
       }
       if (ok && !direct) {
