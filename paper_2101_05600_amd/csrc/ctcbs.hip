@@ -22,7 +22,7 @@
 
 static thread_local int g_last_hip = 0;
 
-#define CTCBS_EARLY_GROUPS 256    // groups up to which the score kernel fetches rows before records (k_score: flags)
+#define CTCBS_EARLY_GROUPS 256    // groups up to which the score kernel fetches rows before it knows of any utterance (k_score: flags)
 
 #define STATIC_LDS 2560            // bytes: no form of the score kernel declares more LDS of its own
 

@@ -480,8 +480,8 @@ __device__ __forceinline__ unsigned long long joint_key(double J, unsigned long 
 // Grid: (1 << sh, Wb, ceil(U / (1 << sh))), sh = bits 4-7 of flags: utterance z * 2^sh + x, beam slot y.  With sh = 3 the
 // work-groups of an utterance share an XCD (work-groups go round-robin over the eight), and with it the L2 in
 // which a column that several beam slots score is fetched once.
-// flags bit 0: the whole row can be held in registers (NV4 * BLOCK granules); bit 1: rows are fetched before the record says
-// that there is a hypothesis (up to a work-group per compute unit: the dead slots' rows cost nobody's bandwidth then; one
+// flags bit 0: the whole row can be held in registers (NV4 * BLOCK granules); bit 1: rows are fetched before it is known whether the
+// utterance has finished (up to a work-group per compute unit: the dead slots' rows cost nobody's bandwidth then; one
 // utterance 1021 -> 1011 us a decode, 21 with a batch-wide window 1443 -> 1432, 16 whole utterances within the noise), and the four
 // waves share the ranking of the group's list, with one more barrier (one utterance 965 -> 942, 21 with a batch-wide window 1448 -> 1432,
 // 16 whole utterances 1397 -> 1368; 384 to 1280 groups within half a per cent either way, 5120 slower by that).
@@ -531,18 +531,16 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   const int sh = (flags >> 4) & 15;
   const int u = (int)((blockIdx.z << sh) + blockIdx.x);
   const int grp = u * Wb + (int)blockIdx.y;
-  // first round of loads, g's record and the utterance's constants: one 64-byte line and one 32-byte entry
-  // through the scalar path (uniform addresses, nothing in this kernel writes them)
-  const HypRec rec = rec_now[grp];
-  const UttInfo ui = uinfo[u];
   // (the utterance's finished byte is fetched as part of its aligned word: a uniform word load
   // can take the scalar path, a byte load cannot)
-  const uint32_t fin_word = fin_words[u >> 2];
+  uint32_t fin_word = fin_words[u >> 2];
   TRACE_DECL;
   // ---------------- the attention row -----------------------------------------------------------
-  // As soon as the record says that the slot holds a hypothesis its row is fetched, all loads in
-  // flight together (a dead slot fetches nothing); in small batches without asking the record.  Whole 16-byte granules by the lanes in turn; what a row that
-  // is not aligned has before and after them by the first lanes.
+  // A running utterance's rows are fetched before the records are there, all loads in flight together: nearly all of its slots hold
+  // hypotheses, and a work-group's time is 2 us until its record is there and 1.8 until its row is (256 utterances, beam 20, 13570 ->
+  // 13449 us a decode, eight instead of seven work-groups on a compute unit among them; 48 utterances of 10000 ids 2395 -> 2335; 128 of 2300
+  // ids, all of whose work-groups start at once, 1965 -> 1976).  In small batches without asking for the flag either.  Whole
+  // 16-byte granules by the lanes in turn; what a row that is not aligned has before and after them by the first lanes.
   const float* arow = att + (size_t)grp * V;
   const bool in_regs = (flags & 1) != 0;
   RowRegs<NV4> row;
@@ -567,7 +565,15 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
     if (tid < row.n_ex) row.ex = at32(arow, row.ex_id);
   };
   const bool early = (flags & 2) != 0;
-  if (in_regs && early && u < U) fetch_row();
+  int rec_at = grp, ui_at = u;                             // (OPAQUE: loads that are not waited for together with the flag)
+  int go = in_regs && u < U;
+  if (!early) { OPAQUE(fin_word); go &= ((fin_word >> (8 * (u & 3))) & 0xffu) == 0u; }
+  if (go) fetch_row();
+  OPAQUE(rec_at); OPAQUE(ui_at);
+  // g's record and the utterance's constants: one 64-byte line and one 32-byte entry
+  // through the scalar path (uniform addresses, nothing in this kernel writes them)
+  const HypRec rec = rec_now[rec_at];
+  const UttInfo ui = uinfo[ui_at];
   PIN4(rec.live, rec.off, ui.BT, fin_word);
   PIN4(p.xT, p.Bcum, p.gphi, p.gb);
   PIN4(p.lambda, p.beta, p.off_f, p.mode);
@@ -575,7 +581,6 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   // (not all of the block: with four more the scalar registers run out and part of it is loaded twice, 35 -> 36.6 us
   // a launch at 512 utterances)
   const int dead = (int)((fin_word >> (8 * (u & 3))) & 0xffu) | (rec.live == 0);
-  if (in_regs && !early && !dead) fetch_row();
   const int K = p.K;
   const bool smallk = !BIGK || (K <= BLOCK);
   const int T = ui.T;
