@@ -138,6 +138,8 @@ struct Params {
   HypRec* rec[2];
   float* dense_F;            // [U][Wb][Tp] every id a candidate: exp of the f terms (k_dense.h)
   DenseSlot* dense_slot;     // [U][Wb]
+  unsigned long long* dense_best;   // [U][Wb][chunks] the best joint score of each work-group's candidates (joint_image; 0: none)
+  const float* dense_att;    // this step's attention rows (null: increments alone)
   int32_t keep_cand;         // KEEP_*: which of the per-candidate arrays below a step fills (ctcbs_peek; large K needs them)
   // per-step scratch between the score and the select kernel
   int32_t* cand_id;          // [U][Wb][K]
@@ -285,7 +287,22 @@ struct SelectArgs {
   unsigned long long *cells, *groups;
   int32_t* union_win;
   unsigned long long* trace;
+  // every id a candidate (dense_top)
+  double lambda;
+  const DenseSlot* slots;
+  const unsigned long long* best;
+  const float *inc, *att;    // [U][Wb][K]
+  int32_t K, n_chunks, chunk_bits, eos_id;
 };
+
+// Order-preserving 64-bit image of a joint score; 0: not a competitor (log0, NaN).  And back.
+__device__ __forceinline__ unsigned long long joint_image(double J) {
+  const long long b = __double_as_longlong(J);
+  return (unsigned long long)(b ^ ((b >> 63) | (long long)0x8000000000000000ull)) & (J > (double)LOG0_CLASS ? ~0ull : 0ull);
+}
+__device__ __forceinline__ double image_joint(unsigned long long k) {
+  return __longlong_as_double((long long)((k >> 63) ? (k & 0x7fffffffffffffffull) : ~k));
+}
 
 // natural logarithm of a normal positive number: the hardware's log2 times ln 2 (about 1.5 ulp; the
 // library's logf spends a dozen instructions more on denormal arguments and the last half ulp)

@@ -233,6 +233,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
     A(p.cand_pre, !h->dense && (c.end_flags & CTCBS_END_EOS_RUN) ? nc : 1);
     A(p.cand_ctc, nc); A(p.cand_joint, p.keep_cand == KEEP_PAIRS ? 2 * UW * K : nc);
     A(p.dense_F, h->dense ? UW * p.Tp : 1); A(p.dense_slot, h->dense ? UW : 1);
+    A(p.dense_best, h->dense ? UW * ((K + 15) / 16) : 1);
   }
   A(p.grp, UW); A(p.grp_list, UW * Wb);
   A(p.utt, (size_t)U); A(p.finished, U8);   /* read as whole words by the score kernel */ A(p.cells, (size_t)U); A(p.groups, (size_t)U);
@@ -408,26 +409,21 @@ static hipError_t launch_dense_scores(ctcbs* h, const Params& p, int l) {
 #undef CTCBS_DENSE
   return hipGetLastError();
 }
+static int dense_chunk_bits(const Params& p) { return (long long)p.U * ((p.K + 31) / 32) >= 1024 ? 5 : 4; }
 static hipError_t launch_dense(ctcbs* h, const Params& p, const float* att, int l) {
   hipLaunchKernelGGL((k_dense_prep<256>), dim3(p.Wb, p.U), dim3(256), (size_t)p.Tp * 4, h->stream, p, att, l, h->cur);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if ((long long)p.U * ((p.K + 31) / 32) >= 1024) return launch_dense_scores<2>(h, p, l);
-  return launch_dense_scores<1>(h, p, l);
+  Params q = p;
+  q.dense_att = att;
+  return dense_chunk_bits(p) == 5 ? launch_dense_scores<2>(h, q, l) : launch_dense_scores<1>(h, q, l);
 }
 
-// The groups' lists from joint scores in global memory.  Up to 16384 scores stay in registers between the passes; forming
-// them again from increments and attention values costs more (at 15998 ids, beam 8: 14.6 against 17.6 us a launch).
-static hipError_t launch_lists(ctcbs* h, const Params& p, const float* att) {
+// The groups' lists from joint scores in global memory.  Up to 8192 scores stay in registers between the passes.
+static hipError_t launch_lists(ctcbs* h, const Params& p) {
   const dim3 grid(p.Wb, p.U);
-#define CTCBS_LIST(E, D) hipLaunchKernelGGL((k_list_top<E, D>), grid, dim3(256), 0, h->stream, p, att, h->cur)
-  if (h->dense) {
-    if (p.K <= 1024) CTCBS_LIST(4, true); else if (p.K <= 5120) CTCBS_LIST(20, true);
-    else if (p.K <= 8192) CTCBS_LIST(32, true); else if (p.K <= 16384) CTCBS_LIST(64, true); else CTCBS_LIST(0, true);
-  } else {
-    if (p.K <= 1024) CTCBS_LIST(4, false); else if (p.K <= 5120) CTCBS_LIST(20, false);
-    else if (p.K <= 8192) CTCBS_LIST(32, false); else CTCBS_LIST(0, false);
-  }
+#define CTCBS_LIST(E) hipLaunchKernelGGL((k_list_top<E>), grid, dim3(256), 0, h->stream, p, h->cur)
+  if (p.K <= 1024) CTCBS_LIST(4); else if (p.K <= 5120) CTCBS_LIST(20); else if (p.K <= 8192) CTCBS_LIST(32); else CTCBS_LIST(0);
 #undef CTCBS_LIST
   return hipGetLastError();
 }
@@ -488,8 +484,8 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
         : h->score_form == 1 ? launch_score<256, 2, 3, true>(h, p, d_att_logp, l)
                              : launch_score<256, 3, 2, true>(h, p, d_att_logp, l);
   HIPCHK(e);
-  if (ev) HIPCHK(hipEventRecord(ev[1], h->stream));       // (the list builder below counts as selection)
-  if (h->dense || p.K > h->score_block) HIPCHK(launch_lists(h, p, d_att_logp));
+  if (ev) HIPCHK(hipEventRecord(ev[1], h->stream));       // (a list builder below counts as selection)
+  if (!h->dense && p.K > h->score_block) HIPCHK(launch_lists(h, p));
   // Small batches leave most compute units idle in the one-work-group-per-utterance form: there the
   // split form (one work-group per new beam slot, each ranking the utterance's lists itself) is
   // faster.  Large batches fill the chip either way and the Wb-fold repeated ranking only costs.  Split / per
@@ -508,6 +504,8 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   a.U = p.U; a.V = p.V; a.Tp = p.Tp; a.blank_id = p.blank_id; a.end_flags = p.end_flags; a.end_m = p.end_m; a.end_c = p.end_c;
   a.end_d = p.end_d; a.win_union = p.win_union; a.win_m2 = p.win_m2; a.want_near = h->want_near; a.err = p.err; a.finished = p.finished;
   a.n_finished = p.n_finished; a.cells = p.cells; a.groups = p.groups; a.union_win = p.union_win; a.trace = p.trace;
+  a.lambda = p.lambda; a.slots = p.dense_slot; a.best = p.dense_best; a.inc = p.cand_inc; a.att = p.cand_att; a.K = p.K; a.eos_id = p.eos_id;
+  a.chunk_bits = dense_chunk_bits(p); a.n_chunks = (p.K + (1 << a.chunk_bits) - 1) >> a.chunk_bits;
   const int wb_m = (65536 / p.Wb + 1) << 8 | p.Wb;         // (see k_select)
 #define CTCBS_SELECT(K, G, BS, LDS, L)                                                                       \
   hipLaunchKernelGGL(K, G, dim3(BS), LDS, h->stream, (const HypRec*)p.rec[h->cur], p.utt, (const GroupOut*)p.grp, \
@@ -515,21 +513,22 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   if (split) {
     const int sh = 3;
     const dim3 grid(1u << sh, (unsigned)p.Wb + 1, (unsigned)(p.U + (1 << sh) - 1) >> sh);
-    if (h->want_near) CTCBS_SELECT((k_select_split<256, true>), grid, 256, sel_lds, l | sh << 28);
-    else if (h->select_wide || p.Wb > 12) CTCBS_SELECT((k_select_split<256, false>), grid, 256, sel_lds, l | sh << 28);
-    else CTCBS_SELECT((k_select_split<64, false>), grid, 64, sel_lds, l | sh << 28);
+    if (h->dense) CTCBS_SELECT((k_select_split<256, false, true>), grid, 256, sel_lds, l | sh << 28);
+    else if (h->want_near) CTCBS_SELECT((k_select_split<256, true, false>), grid, 256, sel_lds, l | sh << 28);
+    else if (h->select_wide || p.Wb > 12) CTCBS_SELECT((k_select_split<256, false, false>), grid, 256, sel_lds, l | sh << 28);
+    else CTCBS_SELECT((k_select_split<64, false, false>), grid, 64, sel_lds, l | sh << 28);
   } else {
     const dim3 grid(p.U);
-#define CTCBS_SELECT_LPS(BS)                                                              \
-  do {                                                                                    \
-    if (h->select_lps == 16) CTCBS_SELECT((k_select<BS, 16, 8>), grid, BS, sel_lds, l);   \
-    else if (h->select_lps == 32) CTCBS_SELECT((k_select<BS, 32, 8>), grid, BS, sel_lds, l); \
-    else CTCBS_SELECT((k_select<BS, 64, 8>), grid, BS, sel_lds, l);                       \
+#define CTCBS_SELECT_LPS(BS, D)                                                              \
+  do {                                                                                       \
+    if (h->select_lps == 16) CTCBS_SELECT((k_select<BS, 16, 8, D>), grid, BS, sel_lds, l);   \
+    else if (h->select_lps == 32) CTCBS_SELECT((k_select<BS, 32, 8, D>), grid, BS, sel_lds, l); \
+    else CTCBS_SELECT((k_select<BS, 64, 8, D>), grid, BS, sel_lds, l);                       \
   } while (0)
     switch (h->select_block) {
-      case 256: CTCBS_SELECT_LPS(256); break;
-      case 512: CTCBS_SELECT_LPS(512); break;
-      default: CTCBS_SELECT_LPS(1024); break;
+      case 256: if (h->dense) CTCBS_SELECT_LPS(256, true); else CTCBS_SELECT_LPS(256, false); break;
+      case 512: if (h->dense) CTCBS_SELECT_LPS(512, true); else CTCBS_SELECT_LPS(512, false); break;
+      default: if (h->dense) CTCBS_SELECT_LPS(1024, true); else CTCBS_SELECT_LPS(1024, false); break;
     }
 #undef CTCBS_SELECT_LPS
   }

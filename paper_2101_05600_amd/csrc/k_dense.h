@@ -5,8 +5,9 @@
 //   k_dense_prep   per (utterance, slot): window, F_t = exp(f_t - M) over it (M the largest f term; 0 outside) and the
 //                  frames between its first and its last F that is not 0, eos scores, and the one candidate the product does not fit: the repeat of the slot's last label (blank
 //                  variable only, third alignment rule of Sec. 2.1);
-//   k_dense_scores per (utterance, chunk of candidates): the product, i.e. the prefix-score increments;
-//   k_list_top     per (utterance, slot): joint scores (Eq. (1)) and the group's best-first list.
+//   k_dense_scores per (utterance, chunk of candidates): the product, i.e. the prefix-score increments, and the best joint score
+//                  (Eq. (1)) that each slot has there;
+//   the select kernels find the best of all (slot, candidate) pairs from those (dense_top).
 // Range: a product below 2^-126 (87 nats under M) counts as nothing; a sum of such products -- below 1e-30 -- is redone
 // frame by frame in the log domain.
 // Rounding: the exponentials are exact to about an ulp of themselves whatever their argument's size, and sums of 32
@@ -50,6 +51,22 @@ __device__ __forceinline__ float add_log(float M, float sum) {
   const float k = e * 0.693145751953125f;                      // (ln 2 in 15 bits: exact)
   const float h = M + k, d = h - M;
   return h + (((M - (h - d)) + (k - d)) + fmaf(e, 1.42860682e-6f, t));
+}
+
+// the largest value of each half of the wave (N = 32) or row of 16 lanes, in all of its lanes
+template <int N>
+__device__ __forceinline__ uint32_t lanes_max_u32(uint32_t v) {
+  auto turn = [&](uint32_t o) { return max(v, o); };
+  v = turn((uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true));
+  v = turn((uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xf, 0xf, true));
+  v = turn((uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x122, 0xf, 0xf, true));
+  v = turn((uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x121, 0xf, 0xf, true));
+  if (N == 32) {
+    const uint32_t a = max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16));
+    const uint32_t b = max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48));
+    v = (threadIdx.x & 32) != 0 ? b : a;
+  }
+  return v;
 }
 
 template <int N> struct Const { static constexpr int value = N; };
@@ -204,6 +221,10 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
 // here, slower there (F fetched again for fewer candidates): 16 candidates per work-group, 24.0 and 120 us; a wave for each 16
 // candidates, no sums between waves, 25.4 and 122.  Slower: four halves ahead instead of two (25 registers more, 33 us), work-groups
 // that stay and fetch the next candidates' frames before they finish the last (25.5 and 130).
+// The joint scores and each slot's best of them take 5.4 us more a launch (24.7 -> 30.1 at 16 utterances of 1500 frames, 5000 ids,
+// beam 20: 2 of it arithmetic, 1.4 the attention values' way to memory), the select kernel 2.8 more (10.9 -> 13.7); the launch that
+// made lists of all scores took 10.7.  A decode there 9978 -> 9620 us, of one utterance of 800 frames, beam 10, 2455 -> 2098, of 24 of 250 to 500,
+// 3000 ids, beam 3, windows of 50 2326 -> 2143, of 32 of 1500 frames at beam 20 the same.
 template <int NT, int MT>
 __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict__ xT, const float* __restrict__ F,
                                                          const DenseSlot* __restrict__ slots,
@@ -214,6 +235,9 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
   __shared__ float s_m[MAX_BEAM], s_rep[MAX_BEAM], s_low[MAX_BEAM];
   __shared__ int s_far[4];
   __shared__ f32x4 s_turn[4][MT + NT][64];
+  __shared__ double s_jb[MAX_BEAM];
+  constexpr int NS = 16 * MT / SLOTS;
+  __shared__ float s_att[NS][256];                             // the lanes' attention values
   const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6), n = lane & 15, q = lane >> 4;
   const int u = blockIdx.y, c0 = (int)blockIdx.x * NC;
   const size_t h0 = (size_t)u * Wb;
@@ -221,12 +245,24 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
   const uint8_t finished = FETCH(p.finished + u);
   const int T = p.uinfo[u].T;
   DenseSlot d = slots[h0 + min(lane, Wb - 1)];
+  const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
+  const int cc = tid & (NC - 1), c = c0 + cc, id = full_v_id(min(c, K - 1), lo_ex, hi_ex);
+  const bool joint = p.dense_att != nullptr;                   // (uniform)
+  float att[NS];
+#pragma unroll
+  for (int i = 0; i < NS; ++i) att[i] = joint ? FETCH(p.dense_att + (h0 + min(i * SLOTS + tid / NC, Wb - 1)) * (size_t)V + id) : 0.0f;
   LOADED(d.live); LOADED(d.s); LOADED(d.mref);
   if (finished) return;
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    const int j = i * SLOTS + tid / NC;
+    s_att[i][tid] = att[i];
+    if (joint && j < Wb && c < K) STORE_ASIDE(att[i], p.cand_att + h0 * (size_t)K + (uint32_t)(j * K + c));
+  }
   // the blocks that any slot has an F for, b0 .. e0 - 1, and those read at first, b1 .. e1 - 1
   int b0, e0, b1, e1;
   {
-    if (tid < Wb) { s_last[tid] = d.last; s_live[tid] = d.live; s_m[tid] = d.mref; s_rep[tid] = d.inc_rep; s_low[tid] = fmaxf(d.low, DENSE_RANGE); }
+    if (tid < Wb) { s_last[tid] = d.last; s_live[tid] = d.live; s_m[tid] = d.mref; s_rep[tid] = d.inc_rep; s_low[tid] = fmaxf(d.low, DENSE_RANGE); s_jb[tid] = dense_base(p.lambda, d); }
     const bool live = lane < Wb && d.live;                     // (slots in the first 32 lanes: two rows)
     auto lowest = [](int v) { v = row16_min_i(v); return min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)); };
     auto blocks = [&](int s, int e, int& from, int& to) {
@@ -238,7 +274,6 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
     b1 = max(b1, b0); e1 = max(min(e1, e0), b1);
     if (e0 - b0 <= 4) { b1 = b0; e1 = e0; }                    // (two halves a wave at most: nothing to gain)
   }
-  const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
   const float* xu = xT + (size_t)u * V * Tp;
   // (four lanes in a row hold 64 bytes of a candidate, or slot, for the loads; `turn` brings them to where the products need them)
   const int row = lane >> 2, piece = lane & 3;
@@ -255,10 +290,35 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
   for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int k = 0; k < NT; ++k) acc[m][k] = sum[m][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  // Joint scores (Eq. (1)): the best of each slot's candidates here, from which the select kernel finds the utterance's best; the
+  // attention values beside the increments (the caller's rows may be gone when someone looks)
+  const int n_chunks = (K + NC - 1) / NC;                      // (the grid's width)
+  unsigned long long* best_u = p.dense_best + h0 * n_chunks + blockIdx.x;
+  auto scored = [&](int j0, bool mine, int js, float inc) {
+    const float a = s_att[j0 / SLOTS][tid];
+    const double J = dense_joint(p.lambda, s_jb[js], inc, a);
+    const unsigned long long img = mine ? joint_image(J) : 0ull;
+    const uint32_t hi = (uint32_t)(img >> 32), best_hi = lanes_max_u32<NC>(hi);
+    // (the lane that has it stores it; scores equal in the upper half, or none at all: the first lane, the largest lower half)
+    unsigned long long best = img;
+    bool write = hi == best_hi;
+    if (__popcll(__ballot(write)) != 64 / NC) {                // (uniform)
+      best = (unsigned long long)best_hi << 32 | lanes_max_u32<NC>(write ? (uint32_t)img : 0u);
+      write = cc == 0;
+    }
+    if (write && j0 + tid / NC < Wb) best_u[js * n_chunks] = best;
+    if (mine) {
+      const uint32_t g = (uint32_t)js * (uint32_t)K + (uint32_t)c;
+      if (p.keep_cand) {                                       // (uniform: for ctcbs_peek)
+        const size_t gk = h0 * (size_t)K + g;
+        p.cand_id[gk] = id; p.cand_joint[gk] = J;
+        p.cand_ctc[gk] = inc > LOG0_CLASS ? slots[h0 + js].offr + (double)inc : LOG0D;
+      }
+    }
+  };
   // all of the loop's control is uniform.  whole: nothing is left out; far: a sum that the frames left out may count for
   bool whole = b1 == b0 && e1 == e0, far = false;
   float* inc_u = p.cand_inc + h0 * (size_t)K;
-  const int cc = tid & (NC - 1), c = c0 + cc, id = full_v_id(min(c, K - 1), lo_ex, hi_ex);
   uint32_t again = 0;                                          // a bit for each of the lane's sums that is to be redone
   // the frames read at first; where those left out can count, those before and those behind them too
 #pragma unroll 1
@@ -326,6 +386,7 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
     // ---- increments: lane = candidate, the slots dealt to the 256 / NC groups of lanes ----
     whole |= part > 0;
     far = false; again = 0;
+#pragma unroll 1
     for (int j0 = 0; j0 < Wb; j0 += SLOTS) {
       const int j = j0 + tid / NC, js = min(j, Wb - 1);
       const float v = (s_acc[0][js][cc] + s_acc[1][js][cc]) + (s_acc[2][js][cc] + s_acc[3][js][cc]);
@@ -335,15 +396,17 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
       far |= mine && !rep && !(v > s_low[js]);
       again |= mine && !rep && !(v > DENSE_RANGE) ? 1u << (j0 / SLOTS) : 0u;
       if (mine) *(float*)((char*)inc_u + 4u * (uint32_t)(js * K + c)) = canon0(inc);
+      if (joint) scored(j0, mine, js, canon0(inc));
     }
     if (whole) break;
     const bool any = __ballot(far) != 0ull;                    // (rare)
     if (lane == 0) s_far[w] = any;
     lds_barrier();                                             // (the sums have been read too)
-    if ((s_far[0] | s_far[1] | s_far[2] | s_far[3]) == 0) return;
+    if ((s_far[0] | s_far[1] | s_far[2] | s_far[3]) == 0) break;   // (then no sum is below the product's range either, see s_low)
   }
   // a sum below the range of the product, every product far below M or none finite: again, frame by frame
   unsigned long long todo = __ballot(again != 0u);             // (rare)
+  const unsigned long long redone = todo;
   while (todo != 0ull) {                                       // (uniform)
     const int who = __ffsll((long long)todo) - 1;
     todo &= todo - 1ull;
@@ -367,4 +430,11 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
       if (lane == who) *(float*)((char*)inc_u + 4u * (uint32_t)(j * K + c)) = canon0(r);
     }
   }
+  if (joint && redone != 0ull)                                 // (uniform: the wave holds whole chunks)
+#pragma unroll 1
+    for (int j0 = 0; j0 < Wb; j0 += SLOTS) {
+      const int j = j0 + tid / NC, js = min(j, Wb - 1);
+      const bool mine = j < Wb && c < K && s_live[js];
+      scored(j0, mine, js, mine ? FETCH(inc_u + (size_t)js * K + c) : LOG0F);
+    }
 }

@@ -34,6 +34,12 @@ struct __align__(64) DenseSlot {
   int32_t f_lo, f_hi;        // first and last frame that has an f term
 };
 
+// Joint score (Eq. (1)) of a candidate from its increment and its attention value: the same to the last bit wherever it is formed
+__device__ __forceinline__ double dense_base(double lambda, const DenseSlot& d) { return fma(lambda, d.offr, d.jbase); }
+__device__ __forceinline__ double dense_joint(double lambda, double base, float inc, float att) {
+  return inc > LOG0_CLASS ? fma(lambda, (double)inc, fma(1.0 - lambda, (double)att, base)) : LOG0D;
+}
+
 #define PIVOT_CAP 512     // entries of the short list (all waves together)
 #define RADIX_BITS 10
 
@@ -1236,21 +1242,18 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
 #endif
 }
 
-// Group list for candidate sets whose joint scores lie in global memory (K > block size, or every id a candidate): one
+// Group list for candidate sets whose joint scores lie in global memory (K > block size; not the matrix form, see dense_top): one
 // work-group per (utterance, beam slot).  Order: joint score descending (compared as the fp64 it is), then the candidate's
 // place = token id ascending.  Every lane goes over its share of the scores as order-preserving 64-bit images; the largest
 // upper halves of the lanes give a pivot that at least Wb of the scores reach (as for the candidates, see find_pivot), the
 // few that do are packed into LDS with their places and ranked.  More than CAP of them (scores equal in the upper half, that
 // is to 2^-20 relative): Wb rounds of a block-wide maximum.  (68 us at 4998 candidates, beam 20, with the rounds alone: a
 // round costs 2 us.)
-// Per launch at 4998 ids, beam 20, 16 utterances: 10.4 us, 12.1 with the attention values stored for ctcbs_peek (10.2 with the places
-// in the keys' last bits, which put scores closer than 2^-38 in the order of their ids); 300 candidates, beam 10, 64 utterances 6.3.
+// Per launch at 300 candidates, beam 10, 64 utterances 6.3 us.
 // EPT: scores per lane, held in registers; 0: as many as there are, read again (from L2) for each pass.
-// DENSE: every id is a candidate (its id follows from its place) and only the increments lie in memory: the joint score
-// is formed here, next to the row of attention values.
 template <int N> struct Int { static constexpr int n = N; };
-template <int EPT, bool DENSE>
-__global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restrict__ att, int cur) {
+template <int EPT>
+__global__ __launch_bounds__(256) void k_list_top(Params p, int cur) {
   constexpr int BLOCK = 256, NW = BLOCK / 64, CAP = 512;
   __shared__ unsigned long long s_k[2][NW];
   __shared__ int s_c[2][NW];
@@ -1263,50 +1266,24 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
   // (what decides whether there is anything to do, and the slot, are asked for together)
   const uint8_t finished = FETCH(p.finished + u);
   const int live = FETCH(&p.rec[cur][grp].live), stopped = FETCH(&p.grp[grp].stopped);
-  const double* J = p.cand_joint + (size_t)grp * K;         // (not DENSE)
-  const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
-  const float* arow = att + (size_t)grp * p.V;
+  const double* J = p.cand_joint + (size_t)grp * K;
   const float* ginc = p.cand_inc + (size_t)grp * K;
-  double offr = 0.0, jbase = 0.0;
-  const double lam = p.lambda;
-  if (DENSE) { offr = FETCH(&p.dense_slot[grp].offr); jbase = FETCH(&p.dense_slot[grp].jbase); }
   if (finished || !live) return;                            // the score kernel already wrote a count of 0
   if (stopped) { if (tid == 0) p.grp[grp].n = 0; return; }
-  auto joint = [&](float inc, float a) {
-    return inc > LOG0_CLASS ? lam * (offr + (double)inc) + (1.0 - lam) * (double)a + jbase : LOG0D;
-  };
-  if (DENSE && p.keep_cand) {                               // (for ctcbs_peek; in the pass below it cost every launch 1 us)
-    for (int c = tid; c < K; c += BLOCK) {
-      const size_t g = (size_t)grp * K + c;
-      const int id = full_v_id(c, lo_ex, hi_ex);
-      const float inc = ginc[c];
-      p.cand_id[g] = id; p.cand_joint[g] = joint(inc, arow[id]);
-      p.cand_ctc[g] = inc > LOG0_CLASS ? offr + (double)inc : LOG0D;
-    }
-  }
-  // f(k, key, a) over the lane's scores, N loads in flight: candidate me + k * BLOCK (me = tid), key its score's image (0: not
-  // a competitor), a its attention value (DENSE)
+  // f(k, key) over the lane's scores, N loads in flight: candidate me + k * BLOCK (me = tid), key its score's image (0: not
+  // a competitor)
   auto read_scores = [&](auto n_loads, int me, auto&& f) {
     constexpr int N = decltype(n_loads)::n;
     auto some = [&](int k0) {
-      float iv[N], av[N];
       double jv[N];
 #pragma unroll
       for (int k = 0; k < N; ++k) {
-        const int c = min(me + (k0 + k) * BLOCK, K - 1);
-        if (DENSE) { iv[k] = ginc[c]; av[k] = arow[full_v_id(c, lo_ex, hi_ex)]; }
-        else jv[k] = J[c];
+        jv[k] = J[min(me + (k0 + k) * BLOCK, K - 1)];
       }
 #pragma unroll
       for (int k = 0; k < N; ++k) {
         const int c = me + (k0 + k) * BLOCK;
-        const double v = DENSE ? joint(iv[k], av[k]) : jv[k];
-        unsigned long long kk = 0ull;
-        if (c < K && v > (double)LOG0_CLASS) {              // (false for NaN)
-          const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-          kk = (b >> 63) ? ~b : (b | 0x8000000000000000ull);
-        }
-        f(k0 + k, kk, DENSE ? av[k] : 0.0f);
+        f(k0 + k, c < K ? joint_image(jv[k]) : 0ull);
       }
     };
     if (EPT > 0 && N >= (EPT < 16 ? EPT : 16)) {
@@ -1320,27 +1297,21 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
   using Loads = Int<(EPT == 0 || EPT > 20) ? 16 : EPT>;
   unsigned long long key[EPT > 0 ? EPT : 1];
   uint32_t kmax = 0u;
-  float* gatt = p.cand_att + (size_t)grp * K;
-  read_scores(Loads(), tid, [&](int k, unsigned long long kk, float a) {
-    if (DENSE && tid + k * BLOCK < K) STORE_ASIDE(a, gatt + tid + k * BLOCK);   // (for ctcbs_peek: the caller's row may be gone then)
+  read_scores(Loads(), tid, [&](int k, unsigned long long kk) {
     if (EPT > 0) key[EPT > 0 ? k : 0] = kk;
     kmax = max(kmax, (uint32_t)(kk >> 32));
   });
   auto each = [&](auto&& f) {
     if (EPT > 0) {
 #pragma unroll
-      for (int k = 0; k < (EPT > 0 ? EPT : 1); ++k) f(k, key[k], 0.0f);
+      for (int k = 0; k < (EPT > 0 ? EPT : 1); ++k) f(k, key[k]);
     } else read_scores(Loads(), tid, f);
   };
   auto emit = [&](int c, int r) {
     c = min(c, K - 1);
     const size_t g = (size_t)grp * K + c;
-    const float inc = ginc[c];
-    int id;
-    float a;
-    if (DENSE) { id = full_v_id(c, lo_ex, hi_ex); a = arow[id]; }
-    else { id = checked(p, p.cand_id[g], 0, p.V - 1, ERR_CAND_ID); a = p.cand_att[g]; }
-    p.grp_list[(size_t)grp * Wb + r] = ListEntry{DENSE ? joint(inc, a) : J[c], id, inc, a, 0};
+    const int id = checked(p, p.cand_id[g], 0, p.V - 1, ERR_CAND_ID);
+    p.grp_list[(size_t)grp * Wb + r] = ListEntry{J[c], id, ginc[c], p.cand_att[g], 0};
   };
   // pivot on the upper halves: every wave's share of Wb
   const int have = min(max(K - 64 * w, 0), 64), all = K < BLOCK ? K : BLOCK;
@@ -1357,7 +1328,7 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
   const uint32_t L = max(min(min(s_thr[0], s_thr[1]), min(s_thr[2], s_thr[3])), 1u);
   int me0 = tid;
   LOADED(me0);                                              // (or the places of all scores stay in registers from the loads on)
-  each([&](int k, unsigned long long kk, float) {
+  each([&](int k, unsigned long long kk) {
     if ((uint32_t)(kk >> 32) >= L) {
       const int pos = atomicAdd(&s_n, 1);
       if (pos < CAP) { s_ent[pos] = kk; s_at[pos] = me0 + k * BLOCK; }
@@ -1402,7 +1373,7 @@ __global__ __launch_bounds__(256) void k_list_top(Params p, const float* __restr
     unsigned long long best = 0ull;
     int bk = 0;
     const int k_taken = (last_c - me0) >> 8;                // (rounded down: BLOCK places apart)
-    read_scores(Int<8>(), me0, [&](int k, unsigned long long kk, float) {
+    read_scores(Int<8>(), me0, [&](int k, unsigned long long kk) {
       const bool left = kk < last || (kk == last && k > k_taken);
       if (left && kk > best) { best = kk; bk = k; }
     });

@@ -14,6 +14,7 @@
 // survivors' state and posterior columns.
 #pragma once
 #include "common.h"
+#include "k_score.h"
 
 struct Aff { float a, b; };   // v -> (v + a) (+) b   in the log semiring
 
@@ -469,6 +470,166 @@ __device__ __forceinline__ int rank_lists(const unsigned long long* s_key, unsig
   return n;
 }
 
+// Every id a candidate: the Wb best of all (slot, candidate) pairs of an utterance, joint score descending (compared as the fp64 it is),
+// then slot, then place = token id ascending.  The scores are not in memory: k_dense_scores leaves increments and attention
+// values, and of each slot's chunks of 16 or 32 candidates the best score.  A pivot that at least Wb of those reach (from 64
+// maxima), the chunks that reach it, about 1.2 Wb, their candidates' scores, those that reach it, ranked by quads of lanes.  Scores so alike that too many do (equal to 2^-20 relative): the Wb best chunks exactly, in Wb rounds of a
+// block-wide maximum, whose candidates are all that can be among the best.  (Figures: k_dense_scores.)
+struct DenseTopLds {
+  static constexpr int CAP = 32 * MAX_BEAM, CHUNKS = 128;
+  unsigned long long key[CAP];
+  uint32_t at[CAP];                                        // slot in the upper 5 bits, place
+  float inc[CAP], att[CAP];
+  uint32_t chunk[CHUNKS];                                  // (likewise, the chunk's first place)
+  double base[MAX_BEAM];
+  unsigned long long r_key[2][16];
+  int r_at[2][16];
+  uint32_t kmax[1024];
+  int n_chunks, n;
+};
+template <bool DENSE> struct DenseLds { int none; };
+template <> struct DenseLds<true> { DenseTopLds top; };
+constexpr int DENSE_KEYS = 16;                             // best scores of chunks that a lane holds
+
+template <int BLOCK>
+__device__ __forceinline__ void dense_fetch(const SelectArgs& p, size_t h0, int Wb, unsigned long long (&key)[DENSE_KEYS]) {
+  const unsigned long long* best = p.best + h0 * p.n_chunks;
+  const int total = Wb * p.n_chunks;
+#pragma unroll
+  for (int k = 0; k < DENSE_KEYS; ++k) {
+    key[k] = 0ull;
+    if (k * BLOCK < total) key[k] = FETCH(best + min((int)threadIdx.x + k * BLOCK, total - 1));   // (uniform)
+  }
+}
+// put(rank, image, slot, place, inc, att) by one lane for each of the best.  Returns how many there are (Wb or more: all).
+template <int BLOCK, class F>
+__device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, size_t h0, int Wb, const unsigned long long (&key)[DENSE_KEYS], F&& put) {
+  constexpr int NW = BLOCK / 64;
+  int tid = threadIdx.x;
+  const int lane = tid & 63, w = uni(tid >> 6);
+  const unsigned long long* best = p.best + h0 * p.n_chunks;
+  const int total = Wb * p.n_chunks, bits = p.chunk_bits;
+  auto each = [&](auto&& f) {                              // f(place in the utterance's chunks, its best)
+#pragma unroll
+    for (int k = 0; k < DENSE_KEYS; ++k)
+      if (tid + k * BLOCK < total) f(tid + k * BLOCK, key[k]);
+#pragma unroll 1
+    for (int i = tid + DENSE_KEYS * BLOCK; i < total; i += BLOCK) f(i, best[i]);
+  };
+  uint32_t kmax = 0u;
+  each([&](int, unsigned long long k) { kmax = max(kmax, (uint32_t)(k >> 32)); });
+  t.kmax[tid] = kmax;
+  if (tid == 0) { t.n_chunks = 0; t.n = 0; }
+  lds_barrier();
+  // 64 maxima, each of every 64th lane's, of which Wb reach the pivot (every wave for itself)
+#pragma unroll
+  for (int i = 0; i < NW; ++i) kmax = max(kmax, t.kmax[64 * i + lane]);
+  uint32_t L = 0u;
+#pragma unroll
+  for (int bit = 31; bit >= 10; --bit) {
+    const uint32_t c = L | (1u << bit);
+    if (__popcll(__ballot(kmax >= c)) >= Wb) L = c;
+  }
+  L = max(L, 1u);
+  auto chunk_at = [&](int i) { const int slot = i / p.n_chunks; return (uint32_t)slot << 27 | (uint32_t)(i - slot * p.n_chunks) << bits; };
+  LOADED(tid);                                             // (or the places stay in registers from the first pass on)
+  each([&](int i, unsigned long long k) {
+    if ((uint32_t)(k >> 32) >= L) {
+      const int pos = atomicAdd(&t.n_chunks, 1);
+      if (pos < DenseTopLds::CHUNKS) t.chunk[pos] = chunk_at(i);
+    }
+  });
+  lds_barrier();
+  // the candidates of n chunks that reach `low`
+  auto candidates = [&](int n, unsigned long long low) {
+    constexpr int R = 4;                                   // loads in flight
+#pragma unroll 1
+    for (int e0 = 0; e0 < n << bits; e0 += R * BLOCK) {
+      float inc[R], att[R];
+      uint32_t at[R];
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const int e = e0 + k * BLOCK + tid;
+        at[k] = t.chunk[min(e >> bits, n - 1)] + (uint32_t)(e & ((1 << bits) - 1));
+        const size_t g = (h0 + (at[k] >> 27)) * (size_t)p.K + min((int)(at[k] & 0x7ffffffu), p.K - 1);
+        inc[k] = FETCH(p.inc + g); att[k] = FETCH(p.att + g);
+      }
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const int e = e0 + k * BLOCK + tid, slot = (int)(at[k] >> 27);
+        const double J = dense_joint(p.lambda, t.base[slot], inc[k], att[k]);
+        const unsigned long long m = joint_image(J);
+        if (e < n << bits && (int)(at[k] & 0x7ffffffu) < p.K && m != 0ull && m >= low) {
+          const int pos = atomicAdd(&t.n, 1);
+          if (pos < DenseTopLds::CAP) { t.key[pos] = m; t.at[pos] = at[k]; t.inc[pos] = inc[k]; t.att[pos] = att[k]; }
+        }
+      }
+    }
+  };
+  int nc = uni(t.n_chunks);
+  if (nc <= DenseTopLds::CHUNKS) candidates(nc, (unsigned long long)L << 32);
+  lds_barrier();
+  if (nc > DenseTopLds::CHUNKS || uni(t.n) > DenseTopLds::CAP) {   // (uniform, rare)
+    unsigned long long last = ~0ull;
+    int last_at = -1;
+    nc = 0;
+#pragma unroll 1
+    for (int rd = 0; rd < Wb; ++rd) {                      // the best behind the one taken last
+      unsigned long long m = 0ull;
+      int at = 0x7fffffff;
+#pragma unroll 1
+      for (int i = tid; i < total; i += BLOCK) {           // (ascending: the first of equals stays)
+        const unsigned long long k = best[i];
+        const bool left = k < last || (k == last && i > last_at);
+        if (left && k > m) { m = k; at = i; }
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long om = __shfl_xor(m, o);
+        const int oa = __shfl_xor(at, o);
+        if (om > m || (om == m && oa < at)) { m = om; at = oa; }
+      }
+      if (lane == 0) { t.r_key[rd & 1][w] = m; t.r_at[rd & 1][w] = at; }
+      lds_barrier();                                       // (two buffers: one barrier per round is enough)
+      m = t.r_key[rd & 1][0]; at = t.r_at[rd & 1][0];
+#pragma unroll
+      for (int i = 1; i < NW; ++i) {
+        const unsigned long long om = t.r_key[rd & 1][i];
+        const int oa = t.r_at[rd & 1][i];
+        if (om > m || (om == m && oa < at)) { m = om; at = oa; }
+      }
+      if (m == 0ull) break;                                // (uniform)
+      if (tid == 0) { t.chunk[rd] = chunk_at(at); t.n = 0; }
+      last = m; last_at = at; ++nc;
+    }
+    lds_barrier();
+    candidates(nc, last);
+    lds_barrier();
+  }
+  const int n = min(uni(t.n), (int)DenseTopLds::CAP);
+#pragma unroll 1
+  for (int e0 = 0; e0 < n; e0 += BLOCK / 4) {
+    const int e = e0 + (tid >> 2);
+    const unsigned long long me = e < n ? t.key[e] : ~0ull;
+    const uint32_t at = e < n ? t.at[e] : 0u;
+    int rank = 0, equal = 0;                               // (its own entry among the equal ones)
+#pragma unroll 2
+    for (int i = tid & 3; i < n; i += 4) {
+      const unsigned long long o = t.key[i];
+      rank += o > me ? 1 : 0; equal += o == me ? 1 : 0;
+    }
+    rank += dpp_i<0xB1, 0xf>(0, rank);                     // quad_perm [1,0,3,2]
+    rank += dpp_i<0x4E, 0xf>(0, rank);                     // quad_perm [2,3,0,1]
+    equal += dpp_i<0xB1, 0xf>(0, equal);
+    equal += dpp_i<0x4E, 0xf>(0, equal);
+    if (__ballot(equal > 1) != 0ull)                       // (uniform, rare: equal scores go by slot and place)
+#pragma unroll 1
+      for (int i = 0; i < n; ++i) rank += (int)(t.key[i] == me) & (int)(t.at[i] < at);
+    if ((tid & 3) == 0 && e < n && rank < Wb) put(rank, me, (int)(at >> 27), (int)(at & 0x7ffffffu), t.inc[e], t.att[e]);
+  }
+  return n;
+}
+
 // Ended set and ENDDETECT of one utterance, by one wave (lane j = old slot j).  `mine`: slot j
 // held a live hypothesis; je / stp / tau_j / cells_j: its eos joint score, eos-run stop, tau and
 // prefix-score terms of this step.  st_* / ring_*: the utterance's state as loaded by lane 0
@@ -537,8 +698,8 @@ __device__ __forceinline__ bool wave_ended_set(const SelectArgs& p, int Wb, int 
 // Wave 0 ranks the lists and takes the ended set, the others 64 / LPS new hypotheses each at a time.
 // Wb_m: the beam, in the bits from 8 on 65536 / Wb + 1 (a position i < 1024 is of list (i * that) >> 16).
 // Dynamic LDS: 36 * NP + 32 bytes, NP = Wb * Wb rounded up to whole waves (the list entries and the packed keys).
-template <int BLOCK, int LPS, int FPL>
-__global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
+template <int BLOCK, int LPS, int FPL, bool DENSE>
+__global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
                                                   const GroupOut* __restrict__ grp, const ListEntry* __restrict__ grp_list,
                                                   const UttInfo* __restrict__ uinfo, int Wb_m, int l, int U, SelectArgs p) {
   constexpr int NW = BLOCK / 64;
@@ -552,6 +713,7 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
   int* s_tok = (int*)(s_J + NP);                                      // [NP] each
   float* s_inc = (float*)(s_tok + NP);
   float* s_att = s_inc + NP;
+  __shared__ DenseLds<DENSE> s_top;
   __shared__ int s_sel[MAX_BEAM];          // entry index of the new beam's slot n
   __shared__ int s_n;                      // entries ranked
   // old slots' records
@@ -599,7 +761,10 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
   };
   ListEntry le;
   int nj;
-  load_entry(tid, le, nj);
+  unsigned long long best[DENSE_KEYS];
+  double d_base = 0.0;
+  if constexpr (DENSE) { d_base = dense_base(p.lambda, p.slots[h0 + hj]); dense_fetch<BLOCK>(p, h0, Wb, best); }
+  else load_entry(tid, le, nj);
   // (scalar loads: on their way together and waited for once, beside the vector loads)
   PIN4(fs, T, lmax_u, p.err);
   PIN4(p.xT, p.Bcum, p.gphi, p.gb);
@@ -609,8 +774,11 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
   PIN4(p.end_c, p.end_d, p.win_union, p.win_m2);
   PIN4(p.finished, p.n_finished, p.cells, p.groups);
   if (fs != 0 && fs < l) return;           // outputs of a finished utterance were settled when it finished
-  if (64 * w < NP) keep_entry(tid, le, nj);                // (whole waves)
-  for (int i = tid + BLOCK; i < NP; i += BLOCK) { load_entry(i, le, nj); keep_entry(i, le, nj); }
+  if constexpr (DENSE) { if (tid < Wb) s_top.top.base[tid] = d_base; }
+  else {
+    if (64 * w < NP) keep_entry(tid, le, nj);              // (whole waves)
+    for (int i = tid + BLOCK; i < NP; i += BLOCK) { load_entry(i, le, nj); keep_entry(i, le, nj); }
+  }
   if (tid < Wb) {
     o_live[tid] = r.live; o_stp[tid] = g.stopped;
     o_tau[tid] = r.tau; o_tau_end[tid] = r.tau_end;
@@ -622,7 +790,14 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
   if (tid < MAX_BEAM) s_sel[tid] = -1;
   lds_barrier();
   TRACE_POINT(p, (size_t)u * Wb, 9);
-  if (w == 0) {
+  if constexpr (DENSE) {
+    const int n = dense_top<BLOCK>(p, s_top.top, h0, Wb, best, [&](int rank, unsigned long long image, int slot, int place, float inc, float att) {
+      const int e = slot * Wb + rank;                      // (an entry of that slot's list, see div_m)
+      s_sel[rank] = e; s_J[e] = image_joint(image); s_inc[e] = inc; s_att[e] = att;
+      s_tok[e] = full_v_id(place, min(p.blank_id, p.eos_id), max(p.blank_id, p.eos_id));
+    });
+    if (tid == 0) s_n = n;
+  } else if (w == 0) {
     const int n = rank_lists(s_key, s_ck, NP, Wb, [&](int rank, int e, bool valid) { if (valid && rank < Wb) s_sel[rank] = e; });
     if (lane == 0) s_n = n;
   }
@@ -729,8 +904,8 @@ __global__ __launch_bounds__(BLOCK) void k_select(const HypRec* __restrict__ rec
 // The arguments in front of the block are what the first round of loads needs: plain leading arguments reach the wave
 // in registers when it starts (kernel-argument preload), so that those loads do not wait for a load of the arguments.
 // Grid: (1 << sh, Wb, ceil(U / (1 << sh))), sh = l >> 28: utterance z * 2^sh + x, new slot y (as in k_score).
-template <int BLOCK, bool NEAR>
-__global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
+template <int BLOCK, bool NEAR, bool DENSE>
+__global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select_split(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
                                                         const GroupOut* __restrict__ grp, const ListEntry* __restrict__ grp_list,
                                                         const UttInfo* __restrict__ uinfo, int Wb_m, int l_sh, int U, SelectArgs p) {
   constexpr bool WIDE = BLOCK > 64;
@@ -744,6 +919,8 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
   int* s_tok = (int*)(s_J + NP);                                      // [NP] each
   float* s_inc = (float*)(s_tok + NP);
   float* s_att = s_inc + NP;
+  __shared__ DenseLds<DENSE> s_top;
+  __shared__ int s_sel[DENSE ? MAX_BEAM : 1];
   __shared__ SurvivorLds s_sx;
   __shared__ int o_live[MAX_BEAM], o_stp[MAX_BEAM], o_tau[MAX_BEAM];
   __shared__ int o_par[MAX_BEAM][8];       // what a survivor needs of its parent: window, range, tau, tau~, last label, reference frame
@@ -769,8 +946,11 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
   constexpr int CH = BLOCK == 64 ? 3 : 1024 / BLOCK;       // (NE <= 144 for one wave)
   ListEntry le[CH];
   int nj[CH];
+  unsigned long long best[DENSE_KEYS];
+  double d_base = 0.0;
+  if constexpr (DENSE) { d_base = dense_base(p.lambda, p.slots[h0 + hj]); dense_fetch<BLOCK>(p, h0, Wb, best); }
 #pragma unroll
-  for (int k = 0; k < CH; ++k) {
+  for (int k = 0; !DENSE && k < CH; ++k) {
     const int i = min(tid + k * BLOCK, NE - 1);
     if (BLOCK == 64 || k == 0 || k * BLOCK < NE) { le[k] = grp_list[h0 * Wb + i]; nj[k] = grp[h0 + ((i * div_m) >> 16)].n; }
   }
@@ -790,8 +970,9 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
   PIN4(p.Tp, p.blank_id, p.end_flags, p.end_m);
   PIN4(p.end_c, p.end_d, p.win_union, p.win_m2);
   PIN4(p.finished, p.n_finished, p.cells, p.groups);
+  if constexpr (DENSE) { if (tid < Wb) s_top.top.base[tid] = d_base; }
 #pragma unroll
-  for (int k = 0; k < CH; ++k) {
+  for (int k = 0; !DENSE && k < CH; ++k) {
     const int i = tid + k * BLOCK;
     if (k * BLOCK + 64 * w < NP) {         // (whole waves)
       s_tok[i] = le[k].tok; s_inc[i] = le[k].inc; s_att[i] = le[k].att;
@@ -812,7 +993,13 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
   if (lead) TRACE_POINT(p, (size_t)u * Wb, 9);
 
   int pick_n = -1, pick_0 = -1, ne = 0;                    // entry ranked n, entry ranked 0 (all scalar)
-  if (w == 0) {
+  if constexpr (DENSE) {
+    ne = dense_top<BLOCK>(p, s_top.top, h0, Wb, best, [&](int rank, unsigned long long image, int slot, int place, float inc, float att) {
+      const int e = slot * Wb + rank;                      // (an entry of that slot's list, see div_m)
+      s_sel[rank] = e; s_J[e] = image_joint(image); s_inc[e] = inc; s_att[e] = att;
+      s_tok[e] = full_v_id(place, min(p.blank_id, p.eos_id), max(p.blank_id, p.eos_id));
+    });
+  } else if (w == 0) {
     ne = rank_lists(s_key, s_ck, NP, Wb, [&](int rank, int e, bool) {   // (ranks below ne are of entries)
       const unsigned long long mn = __ballot(rank == n), m0 = __ballot(rank == 0);
       const int en = __builtin_amdgcn_readlane(e, (__ffsll((long long)mn) - 1) & 63), e0 = __builtin_amdgcn_readlane(e, (__ffsll((long long)m0) - 1) & 63);
@@ -821,7 +1008,10 @@ __global__ __launch_bounds__(BLOCK) void k_select_split(const HypRec* __restrict
     });
     if (WIDE && lane == 0) { s_pick[0] = pick_n; s_pick[1] = pick_0; s_pick[2] = ne; }
   }
-  if (WIDE) {
+  if constexpr (DENSE) {
+    lds_barrier();
+    pick_n = n < min(ne, Wb) ? uni(s_sel[n]) : -1; pick_0 = ne > 0 ? uni(s_sel[0]) : -1;
+  } else if (WIDE) {
     lds_barrier();
     pick_n = uni(s_pick[0]); pick_0 = uni(s_pick[1]); ne = uni(s_pick[2]);
   }
