@@ -544,8 +544,9 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   // ---------------- the attention row -----------------------------------------------------------
   // A running utterance's rows are fetched before the records are there, all loads in flight together: nearly all of its slots hold
   // hypotheses, and a work-group's time is 2 us until its record is there and 1.8 until its row is (256 utterances, beam 20, 13570 ->
-  // 13449 us a decode, eight instead of seven work-groups on a compute unit among them; 48 utterances of 10000 ids 2395 -> 2335; 128 of 2300
-  // ids, all of whose work-groups start at once, 1965 -> 1976).  In small batches without asking for the flag either.  Whole
+  // 13449 us a decode, eight instead of seven work-groups on a compute unit among them; 48 utterances of 10000 ids 2395 -> 2335).  In
+  // small batches without asking for the flag either.  Not rows of up to 3072 ids, which are soon there: a live slot's row once its record
+  // is (2300 ids: 128 utterances 1997 -> 1980 us a decode, 512 4593 -> 4561, 256 at beam 20 4176 -> 4139, 64 the same).  Whole
   // 16-byte granules by the lanes in turn; what a row that is not aligned has before and after them by the first lanes.
   const float* arow = att + (size_t)grp * V;
   const bool in_regs = (flags & 1) != 0;
@@ -572,8 +573,9 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   };
   const bool early = (flags & 2) != 0;
   int rec_at = grp, ui_at = u;                             // (OPAQUE: loads that are not waited for together with the flag)
-  int go = in_regs && u < U;
-  if (!early) { OPAQUE(fin_word); go &= ((fin_word >> (8 * (u & 3))) & 0xffu) == 0u; }
+  constexpr bool LONG_ROW = NV4 > 3;
+  int go = in_regs && u < U && (early || LONG_ROW);
+  if (!early && LONG_ROW) { OPAQUE(fin_word); go &= ((fin_word >> (8 * (u & 3))) & 0xffu) == 0u; }
   if (go) fetch_row();
   OPAQUE(rec_at); OPAQUE(ui_at);
   // g's record and the utterance's constants: one 64-byte line and one 32-byte entry
@@ -611,6 +613,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
     if (tid == 0 && u < U) score_late(late_args)->grp[grp] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
     return;
   }
+  if (in_regs && !early && !LONG_ROW) fetch_row();
 
   TRACE_MARK(0);
   uint32_t* s_work = (uint32_t*)(smem);
