@@ -217,24 +217,28 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
 // with an F of NEAR_F or more first, 6 blocks, and the others only if some sum does not exceed by 2^26 all that they could add (low:
 // the slot's F left out, as if its posteriors were 1; on these inputs never): a launch 32.7 -> 24.2 us, of which 28.4 with
 // the loads and tiles as they were; posteriors that leave nearly all frames 104 -> 100 us at beam 20, 93 -> 84 at beam 10.
-// Bound there: the posteriors of those frames (480 MB); here: the phases of a work-group, four of which fit a compute unit.  As fast
-// here, slower there (F fetched again for fewer candidates): 16 candidates per work-group, 24.0 and 120 us; a wave for each 16
-// candidates, no sums between waves, 25.4 and 122.  Slower: four halves ahead instead of two (25 registers more, 33 us), work-groups
+// Bound there: the posteriors of those frames (480 MB); here: the phases of a work-group, so that what counts is how many fit a compute
+// unit.  Five with two tiles of slots, seven otherwise: one half ahead, and a wave's sums in the place of its tiles.  Two halves ahead
+// and sums beside the tiles (112 registers and 38 KB, four; 78 registers, six): 16 utterances of 1500 frames, 5000 ids, beam 20, a decode
+// 9613 -> 9161 us, beam 10 7283 -> 7099, 8 utterances 7075 -> 6485, 32 14789 -> 14010, 64 of 200 to 400 frames, beam 17, 5478 -> 5131.
+// Tried before that, slower with four: 16 candidates per work-group (120 us there), a wave for each 16
+// candidates, no sums between waves, 25.4 and 122, four halves ahead (33 us), work-groups
 // that stay and fetch the next candidates' frames before they finish the last (25.5 and 130).
 // The joint scores and each slot's best of them take 5.4 us more a launch (24.7 -> 30.1 at 16 utterances of 1500 frames, 5000 ids,
 // beam 20: 2 of it arithmetic, 1.4 the attention values' way to memory), the select kernel 2.8 more (10.9 -> 13.7); the launch that
 // made lists of all scores took 10.7.  A decode there 9978 -> 9620 us, of one utterance of 800 frames, beam 10, 2455 -> 2098, of 24 of 250 to 500,
 // 3000 ids, beam 3, windows of 50 2326 -> 2143, of 32 of 1500 frames at beam 20 the same.
 template <int NT, int MT>
-__global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict__ xT, const float* __restrict__ F,
+__global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(const float* __restrict__ xT, const float* __restrict__ F,
                                                          const DenseSlot* __restrict__ slots,
                                                          int Wb, int Tp, int V, int K, Params p, int l, int cur) {
-  constexpr int NC = 16 * NT, AHEAD = 2, SLOTS = 256 / NC;   // (slots whose sums are looked at together)
-  __shared__ float s_acc[4][16 * MT][NC + 1];
+  constexpr int NC = 16 * NT, AHEAD = MT * NT > 1 ? 1 : 2, SLOTS = 256 / NC;   // (slots whose sums are looked at together)
+  // (a wave's tiles while it multiplies, its sums when it is done)
+  constexpr int TURN = (MT + NT) * 64 * 4, SUMS = 16 * MT * (NC + 1), WAVE_LDS = ((TURN > SUMS ? TURN : SUMS) + 3) & ~3;
+  __shared__ __align__(16) float s_wave[4][WAVE_LDS];
   __shared__ int s_last[MAX_BEAM], s_live[MAX_BEAM];
   __shared__ float s_m[MAX_BEAM], s_rep[MAX_BEAM], s_low[MAX_BEAM];
   __shared__ int s_far[4];
-  __shared__ f32x4 s_turn[4][MT + NT][64];
   __shared__ double s_jb[MAX_BEAM];
   constexpr int NS = 16 * MT / SLOTS;
   __shared__ float s_att[NS][256];                             // the lanes' attention values
@@ -283,7 +287,7 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
   for (int k = 0; k < NT; ++k) bp[k] = xu + (size_t)full_v_id(min(c0 + 16 * k + row, K - 1), lo_ex, hi_ex) * Tp + 4 * piece;
 #pragma unroll
   for (int m = 0; m < MT; ++m) ap[m] = F + (h0 + min(16 * m + row, Wb - 1)) * Tp + 4 * piece;
-  f32x4 (*turn)[64] = s_turn[w];
+  f32x4 (*turn)[64] = (f32x4 (*)[64])s_wave[w];
   const int put = 16 * piece + ((row + 4 * piece) & 15), get = 16 * q + ((n + 4 * q) & 15);
   f32x4 acc[MT][NT], sum[MT][NT];
 #pragma unroll
@@ -361,7 +365,7 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
               for (int k = 0; k < NT; ++k)
 #pragma unroll
                 for (int m = 0; m < MT; ++m) acc[m][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(fv[m][o], ex[k][o], acc[m][k], 0, 0, 0);
-            if (a & 1) {                                       // 32 frames join the sum; what that rounds away starts the next ones'
+            if ((AHEAD == 1 ? i : a) & 1) {                    // 32 frames join the sum; what that rounds away starts the next ones'
 #pragma unroll
               for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -376,12 +380,13 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
       }
     }
     if (part == 1) continue;
+    wave_lds_fence();                                          // (the tiles have been read)
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
       for (int k = 0; k < NT; ++k)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) s_acc[w][16 * m + 4 * q + r][16 * k + n] = sum[m][k][r] + acc[m][k][r];
+        for (int r = 0; r < 4; ++r) s_wave[w][(16 * m + 4 * q + r) * (NC + 1) + 16 * k + n] = sum[m][k][r] + acc[m][k][r];
     lds_barrier();
     // ---- increments: lane = candidate, the slots dealt to the 256 / NC groups of lanes ----
     whole |= part > 0;
@@ -389,7 +394,8 @@ __global__ __launch_bounds__(256, 3) void k_dense_scores(const float* __restrict
 #pragma unroll 1
     for (int j0 = 0; j0 < Wb; j0 += SLOTS) {
       const int j = j0 + tid / NC, js = min(j, Wb - 1);
-      const float v = (s_acc[0][js][cc] + s_acc[1][js][cc]) + (s_acc[2][js][cc] + s_acc[3][js][cc]);
+      const int at = js * (NC + 1) + cc;
+      const float v = (s_wave[0][at] + s_wave[1][at]) + (s_wave[2][at] + s_wave[3][at]);
       const bool mine = j < Wb && c < K && s_live[js], rep = id == s_last[js];
       float inc = v < 3.0e38f ? add_log(s_m[js], v) : v;
       inc = rep ? s_rep[js] : inc;
