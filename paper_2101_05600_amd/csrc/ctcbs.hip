@@ -398,7 +398,9 @@ static hipError_t launch_score(ctcbs* h, const Params& p, const float* att, int 
 }
 
 // Every id a candidate.  32 candidates per work-group where that gives every compute unit its four work-groups (each reads
-// the slots' F once), 16 otherwise.
+// the slots' F once), and where chunks of 16 leave the select kernel more of them than its lanes hold (4096; us a decode with 16 / 32
+// candidates, beam 20, 1500 frames, 5000 ids: one utterance 5105 / 4702, three 5708 / 5164, six 6945 / 5949; 9000 ids, beam 10, one 4621 / 4437);
+// 16 otherwise (20 utterances of 400 to 900 frames, 1000 ids, 640 work-groups of 32: 2968 / 3196).
 template <int NT>
 static hipError_t launch_dense_scores(ctcbs* h, const Params& p, int l) {
   const dim3 grid((unsigned)(p.K + 16 * NT - 1) / (16 * NT), (unsigned)p.U);
@@ -409,7 +411,9 @@ static hipError_t launch_dense_scores(ctcbs* h, const Params& p, int l) {
 #undef CTCBS_DENSE
   return hipGetLastError();
 }
-static int dense_chunk_bits(const Params& p) { return (long long)p.U * ((p.K + 31) / 32) >= 1024 ? 5 : 4; }
+static int dense_chunk_bits(const Params& p) {
+  return (long long)p.U * ((p.K + 31) / 32) >= 1024 || (long long)p.Wb * ((p.K + 15) / 16) > 256 * DENSE_KEYS ? 5 : 4;
+}
 static hipError_t launch_dense(ctcbs* h, const Params& p, const float* att, int l) {
   hipLaunchKernelGGL((k_dense_prep<256>), dim3(p.Wb, p.U), dim3(256), (size_t)p.Tp * 4, h->stream, p, att, l, h->cur);
   const hipError_t e = hipGetLastError();

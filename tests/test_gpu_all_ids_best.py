@@ -1,6 +1,6 @@
 """Every id a candidate: the best of all (slot, candidate) pairs from the best of each chunk of 16 or 32 candidates.  Fewer chunks than
-beam slots, more chunks than the lanes hold, posteriors and attention rows that are the same for most ids (more chunks reach the pivot
-than fit, equal scores go by slot and id), one work-group per slot and one per utterance.  Against the oracle, step by step (tolerances
+beam slots, more chunks than the lanes hold (2050 ids: 4096 chunks of 16; 2051 ids: one per slot more, so chunks of 32), posteriors
+and attention rows that are the same for most ids (more chunks reach the pivot than fit, equal scores go by slot and id), one work-group per slot and one per utterance.  Against the oracle, step by step (tolerances
 as in test_gpu_parity.py)."""
 import numpy as np
 import pytest
@@ -11,7 +11,7 @@ from helpers import lockstep_decode
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("vocab,beam,utts", [(70, 32, 2), (530, 32, 2), (1300, 3, 2), (2100, 20, 2), (9001, 32, 2), (1300, 3, 690), (90, 32, 70)])
+@pytest.mark.parametrize("vocab,beam,utts", [(70, 32, 2), (530, 32, 2), (1300, 3, 2), (2100, 20, 2), (9001, 32, 2), (2050, 32, 2), (2051, 32, 2), (1300, 3, 690), (90, 32, 70)])
 @pytest.mark.parametrize("same", [0, 3])                     # ids that differ from the others (0: all do)
 def test_best_of_all_pairs(vocab, beam, utts, same):
     w = gen.workload("cfg1")
