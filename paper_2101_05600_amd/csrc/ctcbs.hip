@@ -296,11 +296,10 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   const int round_frames = 4 * 16 * (h->score_form == 1 ? 3 : (h->score_form == 2 && h->score_bigk ? 4 : 2));
   h->wp_max = (p.Tp + round_frames - 1) / round_frames * round_frames + (h->score_form != 0 && !h->score_bigk ? round_frames : 0);
   h->want_near = h->score_form != 0 && !h->score_bigk && !h->dense;
-  off += (size_t)2 * h->wp_max * 4;
+  const size_t terms = (size_t)2 * h->wp_max * 4, gran = restricted ? (size_t)4 * ShortList::GCAP * 20 : 0;   // (the short list's granules lie there before)
+  off += terms > gran ? terms : gran;
   h->off_small = (int32_t)off;
-  const size_t small = (size_t)(h->score_bigk ? (K <= h->score_block ? K : 0) : 64) * 32 + 8;
-  const size_t gran = restricted ? (size_t)4 * ShortList::GCAP * 20 : 0;     // (the short list's granules, before those)
-  off += small > gran ? small : gran;
+  off += (size_t)(h->score_bigk ? (K <= h->score_block ? K : 0) : 64) * 32 + 8;
   h->score_nv4 = V <= 3072 ? 3 : (V <= 5120 ? 5 : (V <= 10240 ? 10 : 16));
   h->score_smem_bytes = off;
   if (off + STATIC_LDS > 160 * 1024) return CTCBS_EINVAL;
