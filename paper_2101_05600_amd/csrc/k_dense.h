@@ -132,7 +132,7 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
       }
     }
   };
-  if (hi - lo < BLOCK) take(Const<1>()); else take(Const<3>());
+  if (hi - lo < BLOCK) take(Const<1>()); else if (hi - lo < 3 * BLOCK) take(Const<3>()); else take(Const<6>());
   m = row16_max(m);
   m = fmaxf(fmaxf(lane_f(m, 0), lane_f(m, 16)), fmaxf(lane_f(m, 32), lane_f(m, 48)));
   const float am = chain_max<64>(a.m), as = chain_sum<64>(a.s * __builtin_amdgcn_exp2f((a.m - am) * L2E));
