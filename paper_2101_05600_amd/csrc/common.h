@@ -105,7 +105,8 @@ struct __align__(32) UttInfo {   // per utterance, constant over a decode
   int32_t pad[3];
 };
 
-struct DenseSlot;            // (k_dense.h)
+struct DenseSlot;            // (k_score.h)
+struct DenseEos;
 
 // nothing (every id a candidate: what k_dense.h and k_list_top leave); all arrays; joint and prefix score side by side in cand_joint
 enum { KEEP_NONE = 0, KEEP_ARRAYS = 1, KEEP_PAIRS = 2 };
@@ -137,7 +138,8 @@ struct Params {
   float* gb[2];
   HypRec* rec[2];
   float* dense_F;            // [U][Wb][Tp] every id a candidate: exp of the f terms (k_dense.h)
-  DenseSlot* dense_slot;     // [U][Wb]
+  DenseSlot* dense_slot;     // [2][U][Wb], by the record's buffer (a step's: its own)
+  DenseEos* dense_eos;       // [2][U][Wb] (likewise)
   unsigned long long* dense_best;   // [U][Wb][chunks] the best joint score of each work-group's candidates (joint_image; 0: none)
   const float* dense_att;    // this step's attention rows (null: increments alone)
   int32_t keep_cand;         // KEEP_*: which of the per-candidate arrays below a step fills (ctcbs_peek; large K needs them)
@@ -290,6 +292,11 @@ struct SelectArgs {
   // every id a candidate (dense_top)
   double lambda;
   const DenseSlot* slots;
+  DenseSlot* slots_next;     // for the next step (dense_terms)
+  DenseEos* eos_next;
+  float* dense_F;
+  double beta;
+  int32_t win_m1;
   const unsigned long long* best;
   const float *inc, *att;    // [U][Wb][K]
   int32_t K, n_chunks, chunk_bits, eos_id;

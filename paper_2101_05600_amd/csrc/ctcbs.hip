@@ -232,7 +232,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
     A(p.cand_id, nc); A(p.cand_inc, nd); A(p.cand_att, nd);
     A(p.cand_pre, !h->dense && (c.end_flags & CTCBS_END_EOS_RUN) ? nc : 1);
     A(p.cand_ctc, nc); A(p.cand_joint, p.keep_cand == KEEP_PAIRS ? 2 * UW * K : nc);
-    A(p.dense_F, h->dense ? UW * p.Tp : 1); A(p.dense_slot, h->dense ? UW : 1);
+    A(p.dense_F, h->dense ? UW * p.Tp : 1); A(p.dense_slot, h->dense ? 2 * UW : 1); A(p.dense_eos, h->dense ? 2 * UW : 1);
     A(p.dense_best, h->dense ? UW * ((K + 15) / 16) : 1);
   }
   A(p.grp, UW); A(p.grp_list, UW * Wb);
@@ -413,10 +413,13 @@ static hipError_t launch_dense_scores(ctcbs* h, const Params& p, int l) {
 static int dense_chunk_bits(const Params& p) {
   return (long long)p.U * ((p.K + 31) / 32) >= 1024 || (long long)p.Wb * ((p.K + 15) / 16) > 256 * DENSE_KEYS ? 5 : 4;
 }
+static bool split_select(const Params& p) { return p.U * p.Wb <= CTCBS_SPLIT_GROUPS; }
 static hipError_t launch_dense(ctcbs* h, const Params& p, const float* att, int l) {
-  hipLaunchKernelGGL((k_dense_prep<256>), dim3(p.Wb, p.U), dim3(256), (size_t)p.Tp * 4, h->stream, p, att, l, h->cur);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (l == 1 || !split_select(p)) {                        // (else the select kernel of the step before has done it)
+    hipLaunchKernelGGL((k_dense_prep<256>), dim3(p.Wb, p.U), dim3(256), (size_t)p.Tp * 4, h->stream, p, l, h->cur);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   Params q = p;
   q.dense_att = att;
   return dense_chunk_bits(p) == 5 ? launch_dense_scores<2>(h, q, l) : launch_dense_scores<1>(h, q, l);
@@ -470,10 +473,12 @@ static int follow_progress(ctcbs* h, int l) {
 
 // One step with the kernels working on `p`: the handle's own parameter block, or a copy of it whose
 // per-step scratch arrays lie elsewhere (ctcbs_step_static).
-static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs_step_out_t* out) {
+static int step_impl(ctcbs_t* h, const Params& with, const float* d_att_logp, ctcbs_step_out_t* out) {
   if (!h || !d_att_logp) return CTCBS_EINVAL;
-  if (h->known_finished >= p.U || h->step >= h->l_cap) return CTCBS_DONE;
+  if (h->known_finished >= with.U || h->step >= h->l_cap) return CTCBS_DONE;
   const int l = h->step + 1;
+  Params p = with;
+  if (h->dense) { p.dense_slot += (size_t)h->cur * p.U * p.Wb; p.dense_eos += (size_t)h->cur * p.U * p.Wb; }
   hipEvent_t* ev = nullptr;
   if (h->profiling && h->ev_used + 3 <= h->events.size()) {
     ev = &h->events[h->ev_used];
@@ -497,8 +502,12 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   //   beam 10: 640 7.6 / 9.0, 1280 8.7 / 9.3, 2560 10.3 / 10.0, 5120 14.1 / 11.7
   //   beam 20: 1280 10.2 / 10.9, 2560 14.4 / 11.6, 5120 21.3 / 12.1
   // (windows of 161 frames, beam 20: 1280 14.0 / 12.5, 2560 20.8 / 13.2: there the line would lie lower)
-  const bool split = p.U * p.Wb <= CTCBS_SPLIT_GROUPS;
-  const size_t sel_lds = (size_t)36 * ((p.Wb * p.Wb + 63) & ~63) + 32;
+  const bool split = split_select(p);
+  size_t sel_lds = (size_t)36 * ((p.Wb * p.Wb + 63) & ~63) + 32;
+  if (h->dense && split) {                                 // (no keys; then dense_terms)
+    sel_lds = (size_t)20 * ((p.Wb * p.Wb + 63) & ~63);
+    if (sel_lds < (size_t)p.Tp * 4) sel_lds = (size_t)p.Tp * 4;
+  }
   SelectArgs a;
   const int nxt = h->cur ^ 1;
   a.xT = p.xT; a.Bcum = p.Bcum; a.gphi = p.gphi[h->cur]; a.gb = p.gb[h->cur]; a.gphi_new = p.gphi[nxt]; a.gb_new = p.gb[nxt];
@@ -507,7 +516,8 @@ static int step_impl(ctcbs_t* h, const Params& p, const float* d_att_logp, ctcbs
   a.U = p.U; a.V = p.V; a.Tp = p.Tp; a.blank_id = p.blank_id; a.end_flags = p.end_flags; a.end_m = p.end_m; a.end_c = p.end_c;
   a.end_d = p.end_d; a.win_union = p.win_union; a.win_m2 = p.win_m2; a.want_near = h->want_near; a.err = p.err; a.finished = p.finished;
   a.n_finished = p.n_finished; a.cells = p.cells; a.groups = p.groups; a.union_win = p.union_win; a.trace = p.trace;
-  a.lambda = p.lambda; a.slots = p.dense_slot; a.best = p.dense_best; a.inc = p.cand_inc; a.att = p.cand_att; a.K = p.K; a.eos_id = p.eos_id;
+  a.lambda = p.lambda; a.slots = p.dense_slot; a.beta = p.beta; a.win_m1 = p.win_m1; a.dense_F = p.dense_F;
+  a.slots_next = h->p.dense_slot + (size_t)nxt * p.U * p.Wb; a.eos_next = h->p.dense_eos + (size_t)nxt * p.U * p.Wb; a.best = p.dense_best; a.inc = p.cand_inc; a.att = p.cand_att; a.K = p.K; a.eos_id = p.eos_id;
   a.chunk_bits = dense_chunk_bits(p); a.n_chunks = (p.K + (1 << a.chunk_bits) - 1) >> a.chunk_bits;
   const int wb_m = (65536 / p.Wb + 1) << 8 | p.Wb;         // (see k_select)
 #define CTCBS_SELECT(K, G, BS, LDS, L)                                                                       \

@@ -2,9 +2,10 @@
 // The sum over frames of exp(f_t(g) + x_t(c)) is a product of two matrices -- exp(f_t(g)), beam slots by frames, and
 // exp(x_t(c)) = p^c(z_t = c), frames by candidates -- so that one exp2 per (candidate, frame) serves all beam slots of an
 // utterance and the rest is fp32 MFMA.  What is left is the time it takes to read the posteriors.
-//   k_dense_prep   per (utterance, slot): window, F_t = exp(f_t - M) over it (M the largest f term; 0 outside) and the
-//                  frames between its first and its last F that is not 0, eos scores, and the one candidate the product does not fit: the repeat of the slot's last label (blank
-//                  variable only, third alignment rule of Sec. 2.1);
+//   dense_terms    per (utterance, slot): window, F_t = exp(f_t - M) over it (M the largest f term; 0 outside) and the
+//                  frames between its first and its last F that is not 0, ctc part of the eos score, and the one candidate the product does not fit: the repeat of the slot's last label (blank
+//                  variable only, third alignment rule of Sec. 2.1).  By k_select_split where it has made the hypothesis, else (first
+//                  step, large batches) by a launch of k_dense_prep;
 //   k_dense_scores per (utterance, chunk of candidates): the product, i.e. the prefix-score increments, and the best joint score
 //                  (Eq. (1)) that each slot has there;
 //   the select kernels find the best of all (slot, candidate) pairs from those (dense_top).
@@ -71,35 +72,25 @@ __device__ __forceinline__ uint32_t lanes_max_u32(uint32_t v) {
 
 template <int N> struct Const { static constexpr int value = N; };
 
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __restrict__ att, int l, int cur) {
-  extern __shared__ __align__(16) unsigned char dense_smem[];
-  float* dense_f_lds = (float*)dense_smem;                     // [Tp]
+__device__ __forceinline__ void dense_no_slot(DenseSlot* slot) { slot->live = 0; slot->s = 0x7fffffff; slot->e = -1; }
+
+// What the product needs of a slot of utterance u at step l, by a whole work-group: its hypothesis r (live flag apart) with its forward
+// variables gphi, gb.  dense_f_lds: Tp floats.  Behind the select kernel's part, in the same work-group, it takes 3 us a step less than
+// as a launch (7 us: the launch, the records, then the variables from memory): 16 utterances of 1500 frames, 5000 ids, beam 20, a decode
+// 9173 -> 8602 us, one 4626 -> 4158, one of 500 to 700, 1000 ids, beam 10 1284 -> 1086, 32 of 60 to 120, 3000 ids, beam 5 546 -> 487.
+// Not in the form of one work-group per utterance, which would take its slots one after the other.
+template <int BLOCK, class P>
+__device__ __forceinline__ void dense_terms(const P& p, float* dense_f_lds, int u, const UttInfo& ui, int l, const HypRec& r, const float* gphi, const float* gb,
+                                            float* F, DenseSlot* slot, DenseEos* eos) {
   __shared__ float s_red[BLOCK / 64], s_rs[BLOCK / 64];
-  const int tid = threadIdx.x, w = uni(tid >> 6);
-  const int Wb = p.Wb, Tp = p.Tp, u = blockIdx.y, j = blockIdx.x;
-  const size_t h = (size_t)u * Wb + j;
-  const HypRec r = p.rec[cur][h];
-  const UttInfo ui = p.uinfo[u];
-  if (h == 0 && w == BLOCK / 64 - 1) publish_progress(p.host_progress, p.n_finished, l);
-  const int T = ui.T;
-  DenseSlot* slot = p.dense_slot + h;
-  if (p.finished[u] || !r.live) {
-    if (tid == 0) {
-      p.grp[h] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
-      slot->live = 0; slot->s = 0x7fffffff; slot->e = -1;
-    }
-    return;
-  }
+  const int tid = threadIdx.x, w = uni(tid >> 6), Tp = p.Tp, T = ui.T;
+  const double* Bu = p.Bcum + (size_t)u * Tp;
+  const double Bref = r.bref;
   int s = l > 1 ? l : 1, e = T;
   if (p.win_m1 >= 0) s = max(s, r.tau - p.win_m1);
   if (p.win_m2 >= 0) e = min(e, r.tau_end + p.win_m2);
   s = checked(p, s, 1, T + 1, ERR_WINDOW);
   e = checked(p, e, -1, T, ERR_WINDOW);
-  const float* gphi = p.gphi[cur] + h * Tp;
-  const float* gb = p.gb[cur] + h * Tp;
-  const double* Bu = p.Bcum + (size_t)u * Tp;
-  const double Bref = r.bref;
   const int lo = max(s, r.rs + 1), hi = min(e, r.re + 1);      // frames that have an f term
   const bool rep_ok = r.last >= 0 && r.last != p.blank_id && r.last != p.eos_id && r.last < p.V;
   const float* xr = p.xT + ((size_t)u * p.V + (rep_ok ? r.last : 0)) * Tp;
@@ -143,7 +134,6 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
 #pragma unroll
   for (int i = 1; i < BLOCK / 64; ++i) M = fmaxf(M, s_red[i]);
   const bool some = M > LOG0_CLASS;                            // else: no term at all, every increment is log0
-  float* F = p.dense_F + h * Tp;
   __shared__ int s_lo[BLOCK / 64], s_hi[BLOCK / 64], s_nlo[BLOCK / 64], s_nhi[BLOCK / 64];
   __shared__ float s_far[BLOCK / 64];
   int f_lo = 0x7fffffff, f_hi = -1, n_lo = 0x7fffffff, n_hi = -1;   // (scalar: a wave's lanes hold 64 frames in a row)
@@ -200,10 +190,23 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, const float* __r
     const float ce = has ? gphi[T] : LOG0F;
     const bool v = ce > LOG0_CLASS;
     const double ctc = v ? q.offr + (ui.BT - Bref) + (double)ce : LOG0D;
-    const int W = e >= s ? e - s + 1 : 0;
-    p.grp[h] = GroupOut{0, 0, s, e, ctc, v ? p.lambda * ctc + (1.0 - p.lambda) * (double)att[h * p.V + p.eos_id] + q.jbase : LOG0D,
-                        (long long)p.K * (long long)W, {0, 0, 0, 0, 0, 0}};
+    *eos = DenseEos{ctc, s, e};
   }
+}
+
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, int l, int cur) {
+  extern __shared__ __align__(16) unsigned char dense_smem[];
+  const int u = blockIdx.y;
+  const size_t h = (size_t)u * p.Wb + blockIdx.x;
+  const HypRec r = p.rec[cur][h];
+  const UttInfo ui = p.uinfo[u];
+  DenseSlot* slot = p.dense_slot + h;
+  if (p.finished[u] || !r.live) {
+    if (threadIdx.x == 0) dense_no_slot(slot);
+    return;
+  }
+  dense_terms<BLOCK>(p, (float*)dense_smem, u, ui, l, r, p.gphi[cur] + h * p.Tp, p.gb[cur] + h * p.Tp, p.dense_F + h * p.Tp, slot, p.dense_eos + h);
 }
 
 // Grid: (chunks of 16 * NT candidates, U), four waves that share the frames of the window for all the work-group's candidates and
@@ -245,17 +248,32 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
   const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6), n = lane & 15, q = lane >> 4;
   const int u = blockIdx.y, c0 = (int)blockIdx.x * NC;
   const size_t h0 = (size_t)u * Wb;
+  const bool joint = p.dense_att != nullptr;                   // (uniform)
+  if (joint && blockIdx.x == 0 && u == 0 && w == 3) publish_progress(p.host_progress, p.n_finished, l);
   // (all that depends on nothing is asked for together)
   const uint8_t finished = FETCH(p.finished + u);
   const int T = p.uinfo[u].T;
   DenseSlot d = slots[h0 + min(lane, Wb - 1)];
   const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
   const int cc = tid & (NC - 1), c = c0 + cc, id = full_v_id(min(c, K - 1), lo_ex, hi_ex);
-  const bool joint = p.dense_att != nullptr;                   // (uniform)
   float att[NS];
 #pragma unroll
   for (int i = 0; i < NS; ++i) att[i] = joint ? FETCH(p.dense_att + (h0 + min(i * SLOTS + tid / NC, Wb - 1)) * (size_t)V + id) : 0.0f;
   LOADED(d.live); LOADED(d.s); LOADED(d.mref);
+  if (joint && blockIdx.x == 0 && tid < Wb) {                  // the slot's own results: window, eos scores, work
+    GroupOut g = {0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
+    if (finished) {                                            // (ctcbs_peek: what its last step left)
+      DenseSlot before = p.dense_slot[h0 + tid + (cur ? -1 : 1) * (ptrdiff_t)p.U * Wb];
+      before.live = 0; before.s = 0x7fffffff; before.e = -1;
+      p.dense_slot[h0 + tid] = before;
+    } else if (d.live) {
+      const DenseEos o = p.dense_eos[h0 + tid];
+      const int W = o.e >= o.s ? o.e - o.s + 1 : 0;
+      g.win_s = o.s; g.win_e = o.e; g.ctc_eos = o.ctc; g.cells = (long long)K * (long long)W;
+      if (o.ctc > (double)LOG0_CLASS) g.joint_eos = p.lambda * o.ctc + (1.0 - p.lambda) * (double)p.dense_att[(h0 + tid) * V + p.eos_id] + d.jbase;
+    }
+    p.grp[h0 + tid] = g;
+  }
   if (finished) return;
 #pragma unroll
   for (int i = 0; i < NS; ++i) {

@@ -34,6 +34,9 @@ struct __align__(64) DenseSlot {
   int32_t f_lo, f_hi;        // first and last frame that has an f term
 };
 
+// and what its eos extension and its window are
+struct DenseEos { double ctc; int32_t s, e; };
+
 // Joint score (Eq. (1)) of a candidate from its increment and its attention value: the same to the last bit wherever it is formed
 __device__ __forceinline__ double dense_base(double lambda, const DenseSlot& d) { return fma(lambda, d.offr, d.jbase); }
 __device__ __forceinline__ double dense_joint(double lambda, double base, float inc, float att) {

@@ -489,6 +489,8 @@ struct DenseTopLds {
 };
 template <bool DENSE> struct DenseLds { int none; };
 template <> struct DenseLds<true> { DenseTopLds top; };
+template <bool DENSE> struct DenseNext { int none; };
+template <> struct DenseNext<true> : HypRec {};             // the new hypothesis
 constexpr int DENSE_KEYS = 16;                             // best scores of chunks that a lane holds
 
 template <int BLOCK>
@@ -900,7 +902,8 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select(const HypRec* _
 // load, the first one ranks, and all share the recurrence of a window of more than 128 frames.  (Per launch, windows of
 // 101 frames, one wave / four: beam 4, 64 utterances 7.0 / 7.4 us, beam 12, 64 utterances 7.8 / 8.1, 128 9.0 / 10.2.)
 // NEAR: where the score kernel looks at near_frames (one wave: never; found everywhere it cost 1.3 % of a decode at margins of 80).
-// Dynamic LDS: 36 * NP + 32 bytes, NP = Wb * Wb rounded up to whole waves (the list entries and the packed keys).
+// Dynamic LDS: 36 * NP + 32 bytes, NP = Wb * Wb rounded up to whole waves (the list entries and the packed keys); every id a candidate:
+// 20 * NP, and 4 * Tp at least (dense_terms).
 // The arguments in front of the block are what the first round of loads needs: plain leading arguments reach the wave
 // in registers when it starts (kernel-argument preload), so that those loads do not wait for a load of the arguments.
 // Grid: (1 << sh, Wb, ceil(U / (1 << sh))), sh = l >> 28: utterance z * 2^sh + x, new slot y (as in k_score).
@@ -915,11 +918,12 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select_split(const Hyp
   const int NP = (NE + 63) & ~63;
   unsigned long long* s_key = (unsigned long long*)split_smem;        // [NP]
   unsigned long long* s_ck = s_key + NP;                              // [NP + 4]
-  double* s_J = (double*)(s_ck + NP + 4);                             // [NP]
+  double* s_J = DENSE ? (double*)split_smem : (double*)(s_ck + NP + 4);   // [NP]
   int* s_tok = (int*)(s_J + NP);                                      // [NP] each
   float* s_inc = (float*)(s_tok + NP);
   float* s_att = s_inc + NP;
   __shared__ DenseLds<DENSE> s_top;
+  __shared__ DenseNext<DENSE> s_next;
   __shared__ int s_sel[DENSE ? MAX_BEAM : 1];
   __shared__ SurvivorLds s_sx;
   __shared__ int o_live[MAX_BEAM], o_stp[MAX_BEAM], o_tau[MAX_BEAM];
@@ -1064,6 +1068,10 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select_split(const Hyp
         r->att = o_hatt[par] + (double)s_att[e];
         r->joint = s_J[e];
         r->bref = bref;
+        if constexpr (DENSE) {
+          s_next.last = in.tok; s_next.rs = in.s; s_next.re = in.en; s_next.tau = arg_n; s_next.tau_end = arg_b; s_next.ref = in.ptau;
+          s_next.off = o_off[par] + (double)delta; s_next.att = o_hatt[par] + (double)s_att[e]; s_next.bref = bref;
+        }
         if (p.win_union) {                       // the utterance's share of the next step's window (ignored if it finishes)
           int32_t* sh = p.union_win + 2 * ((size_t)((l + 1) & 1) * p.U + u);
           atomicMin(&sh[0], arg_n);
@@ -1090,4 +1098,13 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select_split(const Hyp
     }
   }
   if (lead) TRACE_POINT(p, (size_t)u * Wb, 13);
+  if constexpr (DENSE) {
+    // ---- what the product of the next step needs of the new hypothesis (should the utterance have finished, that step looks at
+    // nothing of it)
+    if (n < Wb && hyp) {                                   // (uniform)
+      __syncthreads();                                     // (the forward variables are written, the arrays read)
+      dense_terms<BLOCK>(p, (float*)split_smem, u, ui, l + 1, s_next, p.gphi_new + (h0 + n) * p.Tp, p.gb_new + (h0 + n) * p.Tp,
+                         p.dense_F + (h0 + n) * p.Tp, p.slots_next + h0 + n, p.eos_next + h0 + n);
+    } else if (n < Wb && tid == 0) dense_no_slot(p.slots_next + h0 + n);
+  }
 }

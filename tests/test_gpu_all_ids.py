@@ -108,3 +108,30 @@ def test_peek_without_keep_candidates(vocab, over):
         assert a.size == U * Wb * K and np.allclose(a, b, rtol=0, atol=1e3 * 3 * 2.0 ** -53 if a is got[0][2] else 0)
     if "cand_k" not in over:
         assert np.array_equal(got[0][0].reshape(U * Wb, K)[0], [i for i in range(vocab) if i not in (3, vocab - 1)])
+
+
+# slots are prepared for the next step where the select kernel makes them (2048 groups at most): of an utterance that finishes, of one
+# that goes on beside it, and, with more groups, by a launch
+@pytest.mark.parametrize("utts", [2, 690])
+def test_a_finished_utterance_beside_others(utts):
+    import torch
+    import paper_2101_05600_amd as m
+    Wb, T, V = 3, 24, 100
+    lens = np.full(utts, T, np.int32)
+    lens[0] = 2
+    g = torch.Generator(device="cuda").manual_seed(5)
+    ctc = torch.log_softmax(2 * torch.randn((1, T, V), generator=g, device="cuda"), -1).expand(utts, T, V).contiguous()
+    att = torch.log_softmax(2 * torch.randn((utts, Wb, V), generator=g, device="cuda"), -1)
+    h = m.ctcbs_create(m.make_config(n_utt=utts, t_max=T, vocab=V, beam=Wb, blank_id=0, win_m1=9, win_m2=9, max_len_ratio=1.0, end_flags=0, keep_candidates=0), ctc, lens)
+    try:
+        seen = []
+        for _ in range(5):
+            assert m.ctcbs_step(h, att, None) == m.OK
+            seen.append([m.ctcbs_peek(h, w).reshape(utts, -1).copy() for w in (m.PEEK_WIN_S, m.PEEK_WIN_E, m.PEEK_CAND_CTC, m.PEEK_CAND_JOINT)])
+    finally:
+        m.ctcbs_destroy(h)
+    s, e, ctc5, joint5 = seen[4]
+    assert (s[0] == 0).all() and (e[0] == -1).all()
+    for _, _, a, b in seen[2:]:                              # (what its last step, the second, left)
+        assert np.array_equal(a[0], seen[1][2][0]) and np.array_equal(b[0], seen[1][3][0])
+    assert (s[1:] >= 5).all() and (e[1:] <= T).all() and (e[1:] >= s[1:]).all() and (ctc5[1:] > -1e3).all() and (joint5[1:] > -1e3).all()
