@@ -108,7 +108,7 @@ struct __align__(32) UttInfo {   // per utterance, constant over a decode
 struct DenseSlot;            // (k_score.h)
 struct DenseEos;
 
-// nothing (every id a candidate: what k_dense.h and k_list_top leave); all arrays; joint and prefix score side by side in cand_joint
+// nothing (every id a candidate: what k_dense.h leaves); all arrays; joint and prefix score side by side in cand_joint
 enum { KEEP_NONE = 0, KEEP_ARRAYS = 1, KEEP_PAIRS = 2 };
 
 struct Params {

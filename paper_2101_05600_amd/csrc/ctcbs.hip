@@ -203,7 +203,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   // large candidate sets go through the per-candidate arrays in global memory whatever the caller asked for
   p.keep_cand = (c.keep_candidates || K > 256 || (!restricted && K > 64)) ? KEEP_ARRAYS : (!restricted ? KEEP_PAIRS : KEEP_NONE);
   // every id a candidate (not: few ids, the eos-run rule, raw decoder scores, the batch-wide window): the kernels of
-  // k_dense.h; up to 64 ids k_score ranks the list itself and a step is two launches instead of four.  They leave
+  // k_dense.h; up to 64 ids k_score ranks the list itself.  They leave
   // increments and attention values in memory; the rest follows from those and is written only if asked to (ctcbs_peek)
   h->dense = !restricted && K > 64 && !(c.end_flags & CTCBS_END_EOS_RUN) && !c.att_is_logits && !c.win_union;
   if (h->dense) p.keep_cand = c.keep_candidates ? KEEP_ARRAYS : KEEP_NONE;
@@ -504,9 +504,9 @@ static int step_impl(ctcbs_t* h, const Params& with, const float* d_att_logp, ct
   // (windows of 161 frames, beam 20: 1280 14.0 / 12.5, 2560 20.8 / 13.2: there the line would lie lower)
   const bool split = split_select(p);
   size_t sel_lds = (size_t)36 * ((p.Wb * p.Wb + 63) & ~63) + 32;
-  if (h->dense && split) {                                 // (no keys; then dense_terms)
+  if (h->dense) {                                          // (no keys; split: then dense_terms)
     sel_lds = (size_t)20 * ((p.Wb * p.Wb + 63) & ~63);
-    if (sel_lds < (size_t)p.Tp * 4) sel_lds = (size_t)p.Tp * 4;
+    if (split && sel_lds < (size_t)p.Tp * 4) sel_lds = (size_t)p.Tp * 4;
   }
   SelectArgs a;
   const int nxt = h->cur ^ 1;

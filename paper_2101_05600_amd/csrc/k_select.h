@@ -699,7 +699,8 @@ __device__ __forceinline__ bool wave_ended_set(const SelectArgs& p, int Wb, int 
 
 // Wave 0 ranks the lists and takes the ended set, the others 64 / LPS new hypotheses each at a time.
 // Wb_m: the beam, in the bits from 8 on 65536 / Wb + 1 (a position i < 1024 is of list (i * that) >> 16).
-// Dynamic LDS: 36 * NP + 32 bytes, NP = Wb * Wb rounded up to whole waves (the list entries and the packed keys).
+// Dynamic LDS: 36 * NP + 32 bytes, NP = Wb * Wb rounded up to whole waves (the list entries and the packed keys); every id a candidate:
+// 20 * NP (no keys: with them a beam of 32 would take more than 64 KB).
 template <int BLOCK, int LPS, int FPL, bool DENSE>
 __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
                                                   const GroupOut* __restrict__ grp, const ListEntry* __restrict__ grp_list,
@@ -711,7 +712,7 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select(const HypRec* _
   const int NP = (NE + 63) & ~63;
   unsigned long long* s_key = (unsigned long long*)sel_smem;          // [NP]
   unsigned long long* s_ck = s_key + NP;                              // [NP + 4] keys of the entries that can reach the new beam
-  double* s_J = (double*)(s_ck + NP + 4);                             // [NP]
+  double* s_J = DENSE ? (double*)sel_smem : (double*)(s_ck + NP + 4); // [NP]
   int* s_tok = (int*)(s_J + NP);                                      // [NP] each
   float* s_inc = (float*)(s_tok + NP);
   float* s_att = s_inc + NP;

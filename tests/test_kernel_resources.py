@@ -44,6 +44,15 @@ def test_score_kernels_own_lds_is_what_the_host_counts(compiled):
     assert len(sizes) >= 16 and max(sizes) <= counted
 
 
+def test_select_kernels_fit_64_kb(compiled):
+    """Own LDS and what the host asks for: beam 32, 1024 list entries; every id a candidate: no keys, the longest input's f terms."""
+    report, _ = compiled
+    sizes = {k: v["LDS Size"] for k, v in report.items() if "k_select" in k}
+    dense = [v for k, v in sizes.items() if re.search(r"k_select(_splitILi256ELb0E|ILi\d+ELi\d+ELi8E)Lb1E", k)]
+    assert len(dense) == 10 and max(dense) + max(20 * 1024, 4 * 6176) <= 65536
+    assert max(v for v in sizes.values() if v < 16384) + 36 * 1024 + 32 <= 65536
+
+
 def test_no_packed_fp32_arithmetic(compiled):
     assert not re.search(r"v_pk_(add|mul|fma)_f32", compiled[1])
 
