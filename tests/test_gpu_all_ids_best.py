@@ -25,3 +25,13 @@ def test_best_of_all_pairs(vocab, beam, utts, same):
         kw = dict(att_fn=lambda a: np.where(np.isnan(a), a, np.where(np.arange(vocab) < 1 + same, a, np.float32(-9.0))).astype(np.float32))
     rep, _ = lockstep_decode(w, ctc, lens, max_steps=4, check_utts=[0, 1, utts - 1] if utts > 2 else None, **kw)
     assert rep["max_ctc_err"] < 1e-4 and rep["max_score_err"] < 1e-4
+
+
+# scores far below zero, whose upper halves lie close together (a pivot short of some of their bits lets too many chunks through)
+def test_scores_far_below_zero():
+    w = gen.workload("cfg1")
+    w.update(n_utt=2, vocab=3001, beam=20, cand_k=0, win_m1=-1, win_m2=-1, end_flags=3, max_len_ratio=0.0, max_len_abs=6)
+    w["eos_id"] = w["vocab"] - 1
+    lens = np.array([24, 19], np.int32)
+    rep, _ = lockstep_decode(w, gen.workload_ctc(w, lens), lens, max_steps=4, att_fn=lambda a: (a - np.float32(128.0)).astype(np.float32))
+    assert rep["max_ctc_err"] < 1e-4 and rep["max_score_err"] < 1e-4
