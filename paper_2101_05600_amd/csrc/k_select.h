@@ -526,25 +526,31 @@ __device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, si
   // 64 maxima, each of every 64th lane's, of which Wb reach the pivot (every wave for itself)
 #pragma unroll
   for (int i = 0; i < NW; ++i) kmax = max(kmax, t.kmax[64 * i + lane]);
-  // (to the last bit, from the first in which they differ on: scores of -1000 to -2000 that agree in the upper 22 bits lie a nat apart,
-  // and with those alone too many reached the pivot; the cfg4a recipe at
-  // 32 utterances, a decode 52.1 -> 43.5 ms)
-  const uint32_t some = (uint32_t)__builtin_amdgcn_readlane((int)kmax, 0);
-  uint32_t x = kmax ^ some;
-  x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xf, 0xf, true);
-  x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x124, 0xf, 0xf, true);
-  x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x122, 0xf, 0xf, true);
-  x |= (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x121, 0xf, 0xf, true);
-  x = (uint32_t)(__builtin_amdgcn_readlane((int)x, 0) | __builtin_amdgcn_readlane((int)x, 16) | __builtin_amdgcn_readlane((int)x, 32) |
-                 __builtin_amdgcn_readlane((int)x, 48) | 1);
-  const int top = 31 - __builtin_clz(x);
-  uint32_t L = some & ~((2u << top) - 1u);
-#pragma unroll 1
-  for (int bit = top; bit >= 0; --bit) {
-    const uint32_t c = L | (1u << bit);
-    if (__popcll(__ballot(kmax >= c)) >= Wb) L = c;
+  // (14 bits of where they lie between the least and the largest maximum: with 22 bits of the scores themselves, a nat at scores of -1000 to
+  // -2000, too many reached the pivot; the cfg4a recipe at 32 utterances, a decode 52.1 -> 43.3 ms; 16 of 1500 frames, beam 20,
+  // 8599 -> 8736 us)
+  auto turned = [](uint32_t v, auto&& f) {
+    v = f(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true));
+    v = f(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xf, 0xf, true));
+    v = f(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x122, 0xf, 0xf, true));
+    v = f(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x121, 0xf, 0xf, true));
+    return f(f((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
+             f((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
+  };
+  uint32_t L = 1u;
+  if (__popcll(__ballot(kmax != 0u)) >= Wb) {              // (uniform)
+    const uint32_t least = turned(kmax - 1u, [](uint32_t a, uint32_t b) { return min(a, b); }) + 1u;   // (of those that are not 0)
+    const uint32_t most = turned(kmax, [](uint32_t a, uint32_t b) { return max(a, b); });
+    const int up = __builtin_clz((most - least) | 1u);
+    const uint32_t y = kmax != 0u ? (kmax - least) << up : 0u;
+    uint32_t c = 0u;
+#pragma unroll
+    for (int bit = 31; bit >= 18; --bit) {
+      const uint32_t d = c | (1u << bit);
+      if (__popcll(__ballot(y >= d)) >= Wb) c = d;
+    }
+    L = least + (c >> up);
   }
-  L = max(L, 1u);
   auto chunk_at = [&](int i) { const int slot = i / p.n_chunks; return (uint32_t)slot << 27 | (uint32_t)(i - slot * p.n_chunks) << bits; };
   LOADED(tid);                                             // (or the places stay in registers from the first pass on)
   each([&](int i, unsigned long long k) {
