@@ -107,6 +107,7 @@ struct __align__(32) UttInfo {   // per utterance, constant over a decode
 
 struct DenseSlot;            // (k_score.h)
 struct DenseEos;
+struct DenseLeft;
 
 // nothing (every id a candidate: what k_dense.h leaves); all arrays; joint and prefix score side by side in cand_joint
 enum { KEEP_NONE = 0, KEEP_ARRAYS = 1, KEEP_PAIRS = 2 };
@@ -140,6 +141,7 @@ struct Params {
   float* dense_F;            // [U][Wb][Tp] every id a candidate: exp of the f terms (k_dense.h)
   DenseSlot* dense_slot;     // [2][U][Wb], by the record's buffer (a step's: its own)
   DenseEos* dense_eos;       // [2][U][Wb] (likewise)
+  DenseLeft* dense_left;     // [U][Wb] what ctcbs_peek needs of the last step in which a slot held a hypothesis
   unsigned long long* dense_best;   // [U][Wb][chunks] the best joint score of each work-group's candidates (joint_image; 0: none)
   const float* dense_att;    // this step's attention rows (null: increments alone)
   int32_t keep_cand;         // KEEP_*: which of the per-candidate arrays below a step fills (ctcbs_peek; large K needs them)

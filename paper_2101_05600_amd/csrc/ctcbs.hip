@@ -233,6 +233,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
     A(p.cand_pre, !h->dense && (c.end_flags & CTCBS_END_EOS_RUN) ? nc : 1);
     A(p.cand_ctc, nc); A(p.cand_joint, p.keep_cand == KEEP_PAIRS ? 2 * UW * K : nc);
     A(p.dense_F, h->dense ? UW * p.Tp : 1); A(p.dense_slot, h->dense ? 2 * UW : 1); A(p.dense_eos, h->dense ? 2 * UW : 1);
+    A(p.dense_left, h->dense ? UW : 1);
     A(p.dense_best, h->dense ? UW * ((K + 15) / 16) : 1);
   }
   A(p.grp, UW); A(p.grp_list, UW * Wb);
@@ -743,10 +744,10 @@ extern "C" int ctcbs_peek(ctcbs_t* h, int32_t what, void* h_dst, size_t bytes, s
     const size_t w = what == CTCBS_PEEK_CAND_ID ? 4 : 8, K = (size_t)p.K;
     const bool pairs = p.keep_cand == KEEP_PAIRS;
     try {
-      std::vector<DenseSlot> slots(pairs ? 0 : UW);
+      std::vector<DenseLeft> slots(pairs ? 0 : UW);
       std::vector<float> inc(pairs ? 0 : K), att(pairs ? 0 : K);
       std::vector<double> both(pairs ? 2 * K : 0);
-      if (!pairs) HIPCHK(hipMemcpyAsync(slots.data(), p.dense_slot, UW * sizeof(DenseSlot), hipMemcpyDeviceToHost, h->stream));
+      if (!pairs) HIPCHK(hipMemcpyAsync(slots.data(), p.dense_left, UW * sizeof(DenseLeft), hipMemcpyDeviceToHost, h->stream));
       HIPCHK(hipStreamSynchronize(h->stream));
       for (size_t g = 0; g < UW && g * K * w < bytes; ++g) {
         if (pairs) HIPCHK(hipMemcpyAsync(both.data(), p.cand_joint + 2 * g * K, 16 * K, hipMemcpyDeviceToHost, h->stream));
@@ -764,7 +765,7 @@ extern "C" int ctcbs_peek(ctcbs_t* h, int32_t what, void* h_dst, size_t bytes, s
           if (pairs) { joint = both[2 * c]; ctc = both[2 * c + 1]; }
           else if (inc[c] > LOG0_CLASS) {
             ctc = slots[g].offr + (double)inc[c];
-            joint = p.lambda * ctc + (1.0 - p.lambda) * (double)att[c] + slots[g].jbase;
+            joint = dense_joint(p.lambda, dense_base(p.lambda, slots[g]), inc[c], att[c]);
           }
           if (what == CTCBS_PEEK_CAND_ID) memcpy(d, &id, w);
           else memcpy(d, what == CTCBS_PEEK_CAND_CTC ? &ctc : &joint, w);

@@ -262,24 +262,22 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
   LOADED(d.live); LOADED(d.s); LOADED(d.mref);
   if (joint && blockIdx.x == 0 && tid < Wb) {                  // the slot's own results: window, eos scores, work
     GroupOut g = {0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
-    if (finished) {                                            // (ctcbs_peek: what its last step left)
-      DenseSlot before = p.dense_slot[h0 + tid + (cur ? -1 : 1) * (ptrdiff_t)p.U * Wb];
-      before.live = 0; before.s = 0x7fffffff; before.e = -1;
-      p.dense_slot[h0 + tid] = before;
-    } else if (d.live) {
+    if (!finished && d.live) {
       const DenseEos o = p.dense_eos[h0 + tid];
       const int W = o.e >= o.s ? o.e - o.s + 1 : 0;
       g.win_s = o.s; g.win_e = o.e; g.ctc_eos = o.ctc; g.cells = (long long)K * (long long)W;
       if (o.ctc > (double)LOG0_CLASS) g.joint_eos = p.lambda * o.ctc + (1.0 - p.lambda) * (double)p.dense_att[(h0 + tid) * V + p.eos_id] + d.jbase;
+      p.dense_left[h0 + tid] = DenseLeft{d.offr, d.jbase};
     }
     p.grp[h0 + tid] = g;
   }
   if (finished) return;
+  const uint32_t live_slots = (uint32_t)__ballot(lane < Wb && d.live);
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
     const int j = i * SLOTS + tid / NC;
     s_att[i][tid] = att[i];
-    if (joint && j < Wb && c < K) STORE_ASIDE(att[i], p.cand_att + h0 * (size_t)K + (uint32_t)(j * K + c));
+    if (joint && (live_slots >> j & 1u) != 0u && c < K) STORE_ASIDE(att[i], p.cand_att + h0 * (size_t)K + (uint32_t)(j * K + c));
   }
   // the blocks that any slot has an F for, b0 .. e0 - 1, and those read at first, b1 .. e1 - 1
   int b0, e0, b1, e1;

@@ -37,9 +37,13 @@ struct __align__(64) DenseSlot {
 // and what its eos extension and its window are
 struct DenseEos { double ctc; int32_t s, e; };
 
+// and what its candidates' scores are formed from, beside increments and attention values
+struct DenseLeft { double offr, jbase; };
+
 // Joint score (Eq. (1)) of a candidate from its increment and its attention value: the same to the last bit wherever it is formed
-__device__ __forceinline__ double dense_base(double lambda, const DenseSlot& d) { return fma(lambda, d.offr, d.jbase); }
-__device__ __forceinline__ double dense_joint(double lambda, double base, float inc, float att) {
+template <class S>
+__host__ __device__ __forceinline__ double dense_base(double lambda, const S& d) { return fma(lambda, d.offr, d.jbase); }
+__host__ __device__ __forceinline__ double dense_joint(double lambda, double base, float inc, float att) {
   return inc > LOG0_CLASS ? fma(lambda, (double)inc, fma(1.0 - lambda, (double)att, base)) : LOG0D;
 }
 

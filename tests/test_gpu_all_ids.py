@@ -135,3 +135,49 @@ def test_a_finished_utterance_beside_others(utts):
     for _, _, a, b in seen[2:]:                              # (what its last step, the second, left)
         assert np.array_equal(a[0], seen[1][2][0]) and np.array_equal(b[0], seen[1][3][0])
     assert (s[1:] >= 5).all() and (e[1:] <= T).all() and (e[1:] >= s[1:]).all() and (ctc5[1:] > -1e3).all() and (joint5[1:] > -1e3).all()
+
+
+# A slot that holds no hypothesis any more, in an utterance that goes on, and a slot of an utterance that a later batch does not use: what their
+# last step left, with and without keep_candidates (the same arithmetic on the host and on the GPU: to the last bit).
+@pytest.mark.parametrize("utts", [2, 690])
+def test_peek_at_slots_without_a_hypothesis(utts):
+    import torch
+    import paper_2101_05600_amd as m
+    Wb, T, V = 3, 24, 100
+    g = torch.Generator(device="cuda").manual_seed(8)
+    ctc = torch.log_softmax(2 * torch.randn((1, T, V), generator=g, device="cuda"), -1).expand(utts, T, V).contiguous()
+    rows = [torch.log_softmax(2 * torch.randn((utts, Wb, V), generator=g, device="cuda"), -1) for _ in range(5)]
+    for k in (2, 3):                                         # from the third step on a single extension has a score
+        rows[k] = torch.where(torch.arange(V, device="cuda") == 5, rows[k], float("-inf"))
+        rows[k][:, 1:] = float("-inf")
+    lens = np.full(utts, T, np.int32)
+    last = utts - 1
+    got = []
+    for keep in (0, 1):
+        h = m.ctcbs_create(m.make_config(n_utt=utts, t_max=T, vocab=V, beam=Wb, blank_id=0, max_len_ratio=1.0, end_flags=0, keep_candidates=keep), ctc, lens)
+        try:
+            seen = []
+            peek = lambda: seen.append([m.ctcbs_peek(h, w).reshape(utts, Wb, V - 2).copy() for w in (m.PEEK_CAND_CTC, m.PEEK_CAND_JOINT)])
+            for r in rows:
+                assert m.ctcbs_step(h, r, None) == m.OK
+                peek()
+            used = lens.copy()
+            used[last] = 0
+            m.ctcbs_reset(h, ctc, used)
+            for r in rows[:2]:
+                assert m.ctcbs_step(h, r, None) == m.OK
+                peek()
+            got.append(seen)
+        finally:
+            m.ctcbs_destroy(h)
+    for step, (a, b) in enumerate(zip(*got)):
+        for x, y in zip(a, b):
+            if step >= 1:                                    # (all slots have held a hypothesis)
+                assert np.array_equal(x, y), step
+    for seen in got:
+        for k in (3, 4):
+            for x, y in zip(seen[k], seen[2]):
+                assert np.array_equal(x[:, 1:], y[:, 1:])    # dead from the fourth step on
+        for k in (5, 6):
+            for x, y in zip(seen[k], seen[4]):
+                assert np.array_equal(x[last], y[last])
