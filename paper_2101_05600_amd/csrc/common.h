@@ -142,8 +142,8 @@ struct Params {
   DenseSlot* dense_slot;     // [2][U][Wb], by the record's buffer (a step's: its own)
   DenseEos* dense_eos;       // [2][U][Wb] (likewise)
   DenseLeft* dense_left;     // [U][Wb] what ctcbs_peek needs of the last step in which a slot held a hypothesis
-  unsigned long long* dense_best;   // [U][Wb][chunks] the best joint score of each work-group's candidates (joint_image; 0: none)
-  const float* dense_att;    // this step's attention rows (null: increments alone)
+  double* dense_best;        // [U][chunks][dense_pitch] the best joint score that each slot has in each work-group's candidates (log0: none)
+  const float* dense_att;    // this step's attention rows
   int32_t keep_cand;         // KEEP_*: which of the per-candidate arrays below a step fills (ctcbs_peek; large K needs them)
   // per-step scratch between the score and the select kernel
   int32_t* cand_id;          // [U][Wb][K]
@@ -299,10 +299,15 @@ struct SelectArgs {
   float* dense_F;
   double beta;
   int32_t win_m1;
-  const unsigned long long* best;
+  const double* best;        // (Params::dense_best)
   const float *inc, *att;    // [U][Wb][K]
   int32_t K, n_chunks, chunk_bits, eos_id;
+  int32_t pitch;             // (dense_pitch)
 };
+
+// entries per chunk of Params::dense_best: odd, so that a chunk's slots and the slots' same chunks lie in places that differ modulo 64
+// (dense_top); the spare entry is never written after ctcbs_create
+__host__ __device__ __forceinline__ int dense_pitch(int Wb) { return Wb | 1; }
 
 // Order-preserving 64-bit image of a joint score; 0: not a competitor (log0, NaN).  And back.
 __device__ __forceinline__ unsigned long long joint_image(double J) {

@@ -234,7 +234,9 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
     A(p.cand_ctc, nc); A(p.cand_joint, p.keep_cand == KEEP_PAIRS ? 2 * UW * K : nc);
     A(p.dense_F, h->dense ? UW * p.Tp : 1); A(p.dense_slot, h->dense ? 2 * UW : 1); A(p.dense_eos, h->dense ? 2 * UW : 1);
     A(p.dense_left, h->dense ? UW : 1);
-    A(p.dense_best, h->dense ? UW * ((K + 15) / 16) : 1);
+    const size_t n_best = h->dense ? (size_t)U * ((K + 15) / 16) * dense_pitch(Wb) : 1;
+    A(p.dense_best, n_best);
+    HIPCHK(hipMemsetAsync(p.dense_best, 0xff, n_best * sizeof(double), h->stream));   // (NaN: no score)
   }
   A(p.grp, UW); A(p.grp_list, UW * Wb);
   A(p.utt, (size_t)U); A(p.finished, U8);   /* read as whole words by the score kernel */ A(p.cells, (size_t)U); A(p.groups, (size_t)U);
@@ -412,7 +414,7 @@ static hipError_t launch_dense_scores(ctcbs* h, const Params& p, int l) {
   return hipGetLastError();
 }
 static int dense_chunk_bits(const Params& p) {
-  return (long long)p.U * ((p.K + 31) / 32) >= 1024 || (long long)p.Wb * ((p.K + 15) / 16) > 256 * DENSE_KEYS ? 5 : 4;
+  return (long long)p.U * ((p.K + 31) / 32) >= 1024 || (long long)dense_pitch(p.Wb) * ((p.K + 15) / 16) > 256 * DENSE_KEYS ? 5 : 4;
 }
 static bool split_select(const Params& p) { return p.U * p.Wb <= CTCBS_SPLIT_GROUPS; }
 static hipError_t launch_dense(ctcbs* h, const Params& p, const float* att, int l) {
@@ -518,8 +520,9 @@ static int step_impl(ctcbs_t* h, const Params& with, const float* d_att_logp, ct
   a.end_d = p.end_d; a.win_union = p.win_union; a.win_m2 = p.win_m2; a.want_near = h->want_near; a.err = p.err; a.finished = p.finished;
   a.n_finished = p.n_finished; a.cells = p.cells; a.groups = p.groups; a.union_win = p.union_win; a.trace = p.trace;
   a.lambda = p.lambda; a.slots = p.dense_slot; a.beta = p.beta; a.win_m1 = p.win_m1; a.dense_F = p.dense_F;
-  a.slots_next = h->p.dense_slot + (size_t)nxt * p.U * p.Wb; a.eos_next = h->p.dense_eos + (size_t)nxt * p.U * p.Wb; a.best = p.dense_best; a.inc = p.cand_inc; a.att = p.cand_att; a.K = p.K; a.eos_id = p.eos_id;
-  a.chunk_bits = dense_chunk_bits(p); a.n_chunks = (p.K + (1 << a.chunk_bits) - 1) >> a.chunk_bits;
+  a.slots_next = h->p.dense_slot + (size_t)nxt * p.U * p.Wb; a.eos_next = h->p.dense_eos + (size_t)nxt * p.U * p.Wb;
+  a.best = p.dense_best; a.inc = p.cand_inc; a.att = p.cand_att; a.K = p.K; a.eos_id = p.eos_id;
+  a.chunk_bits = dense_chunk_bits(p); a.n_chunks = (p.K + (1 << a.chunk_bits) - 1) >> a.chunk_bits; a.pitch = dense_pitch(p.Wb);
   const int wb_m = (65536 / p.Wb + 1) << 8 | p.Wb;         // (see k_select)
 #define CTCBS_SELECT(K, G, BS, LDS, L)                                                                       \
   hipLaunchKernelGGL(K, G, dim3(BS), LDS, h->stream, (const HypRec*)p.rec[h->cur], p.utt, (const GroupOut*)p.grp, \

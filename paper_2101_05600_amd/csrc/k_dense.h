@@ -313,7 +313,7 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
   // Joint scores (Eq. (1)): the best of each slot's candidates here, from which the select kernel finds the utterance's best; the
   // attention values beside the increments (the caller's rows may be gone when someone looks)
   const int n_chunks = (K + NC - 1) / NC;                      // (the grid's width)
-  unsigned long long* best_u = p.dense_best + h0 * n_chunks + blockIdx.x;
+  double* best_c = p.dense_best + ((size_t)u * n_chunks + blockIdx.x) * dense_pitch(Wb);
   auto scored = [&](int j0, bool mine, int js, float inc) {
     const float a = s_att[j0 / SLOTS][tid];
     const double J = dense_joint(p.lambda, s_jb[js], inc, a);
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
       best = (unsigned long long)best_hi << 32 | lanes_max_u32<NC>(write ? (uint32_t)img : 0u);
       write = cc == 0;
     }
-    if (write && j0 + tid / NC < Wb) best_u[js * n_chunks] = best;
+    if (write && j0 + tid / NC < Wb) best_c[js] = best != 0ull ? image_joint(best) : LOG0D;
     if (mine) {
       const uint32_t g = (uint32_t)js * (uint32_t)K + (uint32_t)c;
       if (p.keep_cand) {                                       // (uniform: for ctcbs_peek)

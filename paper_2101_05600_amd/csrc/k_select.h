@@ -472,18 +472,26 @@ __device__ __forceinline__ int rank_lists(const unsigned long long* s_key, unsig
 
 // Every id a candidate: the Wb best of all (slot, candidate) pairs of an utterance, joint score descending (compared as the fp64 it is),
 // then slot, then place = token id ascending.  The scores are not in memory: k_dense_scores leaves increments and attention
-// values, and of each slot's chunks of 16 or 32 candidates the best score.  A pivot that at least Wb of those reach (from 64
-// maxima), the chunks that reach it, about 1.2 Wb, their candidates' scores, those that reach it, ranked by quads of lanes.  Scores so alike that too many do (equal to 2^-20 relative): the Wb best chunks exactly, in Wb rounds of a
-// block-wide maximum, whose candidates are all that can be among the best.  (Figures: k_dense_scores.)
+// values, and the best score that each slot has in each chunk of 16 or 32 candidates, chunk by chunk (SelectArgs::pitch entries each).
+// The Wb-th largest of 64 maxima over those is a pivot that at least Wb scores reach; then the chunks that reach it, their candidates'
+// scores, those that reach it, ranked by quads of lanes.  How many chunks reach it depends on how the best ones share
+// the 64 maxima (an entry's is its place modulo 64): the slots of a beam have their best candidates in the same few chunks, which an odd
+// pitch puts into maxima of their own.  Measured (decodes of 130 to 9001 ids, peaked and flat rows, beams 3 to 32): 1.0 to 1.2 Wb chunks on
+// average, at most 2 Wb.  With the slots one after the other and a pivot known to 14 bits of the maxima's range: 1.5 Wb and 9 Wb
+// at beam 32, and where a slot's number of chunks was a multiple of 64 the rounds below in many steps: a decode of 4 utterances of 700 frames,
+// 4096 ids, beam 32, 9450 -> 3180 us, 16 at beam 20 7570 -> 4760, 16 of 500, 1024 ids, beam 32, 4240 -> 2260; 16 of 1500, 5000 ids, beam 20,
+// 8740 -> 8480; maxima past those that the lanes hold eight at a time: one utterance of 300, 20000 ids, beam 32, 2760 -> 1840.
+// More than CHUNKS chunks or CAP scores at the pivot (scores equal in their upper halves, to 2^-20 relative): the Wb best chunks exactly, in
+// Wb rounds of a block-wide maximum, whose candidates are all that can be among the best.  (Figures: k_dense_scores.)
 struct DenseTopLds {
   static constexpr int CAP = 32 * MAX_BEAM, CHUNKS = 128;
-  unsigned long long key[CAP];
+  double key[CAP];
   uint32_t at[CAP];                                        // slot in the upper 5 bits, place
   float inc[CAP], att[CAP];
   uint32_t chunk[CHUNKS];                                  // (likewise, the chunk's first place)
   double base[MAX_BEAM];
-  unsigned long long r_key[2][16];
-  int r_at[2][16];
+  double r_key[2][16];
+  uint32_t r_at[2][16];
   uint32_t kmax[1024];
   int n_chunks, n;
 };
@@ -494,74 +502,67 @@ template <> struct DenseNext<true> : HypRec {};             // the new hypothesi
 constexpr int DENSE_KEYS = 16;                             // best scores of chunks that a lane holds
 
 template <int BLOCK>
-__device__ __forceinline__ void dense_fetch(const SelectArgs& p, size_t h0, int Wb, unsigned long long (&key)[DENSE_KEYS]) {
-  const unsigned long long* best = p.best + h0 * p.n_chunks;
-  const int total = Wb * p.n_chunks;
+__device__ __forceinline__ void dense_fetch(const SelectArgs& p, int u, double (&key)[DENSE_KEYS]) {
+  const int total = p.n_chunks * p.pitch;
+  const double* best = p.best + (size_t)u * total;
 #pragma unroll
   for (int k = 0; k < DENSE_KEYS; ++k) {
-    key[k] = 0ull;
+    key[k] = LOG0D;
     if (k * BLOCK < total) key[k] = FETCH(best + min((int)threadIdx.x + k * BLOCK, total - 1));   // (uniform)
   }
 }
-// put(rank, image, slot, place, inc, att) by one lane for each of the best.  Returns how many there are (Wb or more: all).
+// put(rank, score, slot, place, inc, att) by one lane for each of the best.  Returns how many there are (Wb or more: all).
 template <int BLOCK, class F>
-__device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, size_t h0, int Wb, const unsigned long long (&key)[DENSE_KEYS], F&& put) {
+__device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, int u, int Wb, const double (&key)[DENSE_KEYS], F&& put) {
   constexpr int NW = BLOCK / 64;
   int tid = threadIdx.x;
   const int lane = tid & 63, w = uni(tid >> 6);
-  const unsigned long long* best = p.best + h0 * p.n_chunks;
-  const int total = Wb * p.n_chunks, bits = p.chunk_bits;
-  auto each = [&](auto&& f) {                              // f(place in the utterance's chunks, its best)
+  const size_t h0 = (size_t)u * Wb;
+  const int total = p.n_chunks * p.pitch, bits = p.chunk_bits;
+  const double* best = p.best + (size_t)u * total;
+  auto each = [&](auto&& f) {                              // f(place among the utterance's best, its score)
 #pragma unroll
     for (int k = 0; k < DENSE_KEYS; ++k)
       if (tid + k * BLOCK < total) f(tid + k * BLOCK, key[k]);
+    constexpr int R = 8;                                   // loads in flight
 #pragma unroll 1
-    for (int i = tid + DENSE_KEYS * BLOCK; i < total; i += BLOCK) f(i, best[i]);
+    for (int i0 = DENSE_KEYS * BLOCK; i0 < total; i0 += R * BLOCK) {
+      double more[R];
+#pragma unroll
+      for (int k = 0; k < R; ++k) more[k] = FETCH(best + min(i0 + k * BLOCK + tid, total - 1));
+#pragma unroll
+      for (int k = 0; k < R; ++k)
+        if (i0 + k * BLOCK + tid < total) f(i0 + k * BLOCK + tid, more[k]);
+    }
   };
-  uint32_t kmax = 0u;
-  each([&](int, unsigned long long k) { kmax = max(kmax, (uint32_t)(k >> 32)); });
+  double most = LOG0D;
+  each([&](int, double k) { most = fmax(most, k); });      // (the pitch's spare entries are NaN)
+  uint32_t kmax = (uint32_t)(joint_image(most) >> 32);
   t.kmax[tid] = kmax;
   if (tid == 0) { t.n_chunks = 0; t.n = 0; }
   lds_barrier();
   // 64 maxima, each of every 64th lane's, of which Wb reach the pivot (every wave for itself)
 #pragma unroll
   for (int i = 0; i < NW; ++i) kmax = max(kmax, t.kmax[64 * i + lane]);
-  // (14 bits of where they lie between the least and the largest maximum: with 22 bits of the scores themselves, a nat at scores of -1000 to
-  // -2000, too many reached the pivot; the cfg4a recipe at 32 utterances, a decode 52.1 -> 43.3 ms; 16 of 1500 frames, beam 20,
-  // 8599 -> 8736 us)
-  auto turned = [](uint32_t v, auto&& f) {
-    v = f(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true));
-    v = f(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xf, 0xf, true));
-    v = f(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x122, 0xf, 0xf, true));
-    v = f(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x121, 0xf, 0xf, true));
-    return f(f((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
-             f((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
-  };
-  uint32_t L = 1u;
-  if (__popcll(__ballot(kmax != 0u)) >= Wb) {              // (uniform)
-    const uint32_t least = turned(kmax - 1u, [](uint32_t a, uint32_t b) { return min(a, b); }) + 1u;   // (of those that are not 0)
-    const uint32_t most = turned(kmax, [](uint32_t a, uint32_t b) { return max(a, b); });
-    const int up = __builtin_clz((most - least) | 1u);
-    const uint32_t y = kmax != 0u ? (kmax - least) << up : 0u;
-    uint32_t c = 0u;
-#pragma unroll
-    for (int bit = 31; bit >= 18; --bit) {
-      const uint32_t d = c | (1u << bit);
-      if (__popcll(__ballot(y >= d)) >= Wb) c = d;
-    }
-    L = least + (c >> up);
+  const int above = lanes_above<8>(kmax, 64);
+  uint32_t L = 0u;
+#pragma unroll 1
+  for (int r = Wb - 1; r >= 0; --r) {                      // (equal maxima: the rank before)
+    const unsigned long long m = __ballot(above == r);
+    if (m != 0ull) { L = (uint32_t)__builtin_amdgcn_readlane((int)kmax, __ffsll((long long)m) - 1); break; }
   }
-  auto chunk_at = [&](int i) { const int slot = i / p.n_chunks; return (uint32_t)slot << 27 | (uint32_t)(i - slot * p.n_chunks) << bits; };
+  const double low = L != 0u ? image_joint((unsigned long long)L << 32) : (double)LOG0_CLASS;   // (the least score with that upper half; fewer maxima than Wb: all scores)
+  auto chunk_at = [&](int i) { const int c = i / p.pitch; return (uint32_t)(i - c * p.pitch) << 27 | (uint32_t)c << bits; };
   LOADED(tid);                                             // (or the places stay in registers from the first pass on)
-  each([&](int i, unsigned long long k) {
-    if ((uint32_t)(k >> 32) >= L) {
+  each([&](int i, double k) {
+    if (k >= low) {
       const int pos = atomicAdd(&t.n_chunks, 1);
       if (pos < DenseTopLds::CHUNKS) t.chunk[pos] = chunk_at(i);
     }
   });
   lds_barrier();
-  // the candidates of n chunks that reach `low`
-  auto candidates = [&](int n, unsigned long long low) {
+  // the candidates of n chunks that reach `least`
+  auto candidates = [&](int n, double least) {
     constexpr int R = 4;                                   // loads in flight
 #pragma unroll 1
     for (int e0 = 0; e0 < n << bits; e0 += R * BLOCK) {
@@ -578,35 +579,36 @@ __device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, si
       for (int k = 0; k < R; ++k) {
         const int e = e0 + k * BLOCK + tid, slot = (int)(at[k] >> 27);
         const double J = dense_joint(p.lambda, t.base[slot], inc[k], att[k]);
-        const unsigned long long m = joint_image(J);
-        if (e < n << bits && (int)(at[k] & 0x7ffffffu) < p.K && m != 0ull && m >= low) {
+        if (e < n << bits && (int)(at[k] & 0x7ffffffu) < p.K && J > (double)LOG0_CLASS && J >= least) {   // (false for NaN)
           const int pos = atomicAdd(&t.n, 1);
-          if (pos < DenseTopLds::CAP) { t.key[pos] = m; t.at[pos] = at[k]; t.inc[pos] = inc[k]; t.att[pos] = att[k]; }
+          if (pos < DenseTopLds::CAP) { t.key[pos] = J; t.at[pos] = at[k]; t.inc[pos] = inc[k]; t.att[pos] = att[k]; }
         }
       }
     }
   };
   int nc = uni(t.n_chunks);
-  if (nc <= DenseTopLds::CHUNKS) candidates(nc, (unsigned long long)L << 32);
+  if (nc <= DenseTopLds::CHUNKS) candidates(nc, low);
   lds_barrier();
   if (nc > DenseTopLds::CHUNKS || uni(t.n) > DenseTopLds::CAP) {   // (uniform, rare)
-    unsigned long long last = ~0ull;
-    int last_at = -1;
+    double last = 0.0;
+    uint32_t last_at = 0u;
     nc = 0;
 #pragma unroll 1
-    for (int rd = 0; rd < Wb; ++rd) {                      // the best behind the one taken last
-      unsigned long long m = 0ull;
-      int at = 0x7fffffff;
+    for (int rd = 0; rd < Wb; ++rd) {                      // the best behind the one taken last: by score, slot, place
+      double m = LOG0D;
+      uint32_t at = ~0u;
 #pragma unroll 1
-      for (int i = tid; i < total; i += BLOCK) {           // (ascending: the first of equals stays)
-        const unsigned long long k = best[i];
-        const bool left = k < last || (k == last && i > last_at);
-        if (left && k > m) { m = k; at = i; }
+      for (int i = tid; i < total; i += BLOCK) {
+        const double k = best[i];
+        if (k > (double)LOG0_CLASS && k >= m && (rd == 0 || k <= last)) {
+          const uint32_t a = chunk_at(i);
+          if ((rd == 0 || k < last || a > last_at) && (k > m || a < at)) { m = k; at = a; }
+        }
       }
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long om = __shfl_xor(m, o);
-        const int oa = __shfl_xor(at, o);
+        const double om = __shfl_xor(m, o);
+        const uint32_t oa = __shfl_xor(at, o);
         if (om > m || (om == m && oa < at)) { m = om; at = oa; }
       }
       if (lane == 0) { t.r_key[rd & 1][w] = m; t.r_at[rd & 1][w] = at; }
@@ -614,12 +616,12 @@ __device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, si
       m = t.r_key[rd & 1][0]; at = t.r_at[rd & 1][0];
 #pragma unroll
       for (int i = 1; i < NW; ++i) {
-        const unsigned long long om = t.r_key[rd & 1][i];
-        const int oa = t.r_at[rd & 1][i];
+        const double om = t.r_key[rd & 1][i];
+        const uint32_t oa = t.r_at[rd & 1][i];
         if (om > m || (om == m && oa < at)) { m = om; at = oa; }
       }
-      if (m == 0ull) break;                                // (uniform)
-      if (tid == 0) { t.chunk[rd] = chunk_at(at); t.n = 0; }
+      if (!(m > (double)LOG0_CLASS)) break;                // (uniform)
+      if (tid == 0) { t.chunk[rd] = at; t.n = 0; }
       last = m; last_at = at; ++nc;
     }
     lds_barrier();
@@ -630,19 +632,19 @@ __device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, si
 #pragma unroll 1
   for (int e0 = 0; e0 < n; e0 += BLOCK / 4) {
     const int e = e0 + (tid >> 2);
-    const unsigned long long me = e < n ? t.key[e] : ~0ull;
+    const double me = e < n ? t.key[e] : 0.0;
     const uint32_t at = e < n ? t.at[e] : 0u;
     int rank = 0, equal = 0;                               // (its own entry among the equal ones)
 #pragma unroll 2
     for (int i = tid & 3; i < n; i += 4) {
-      const unsigned long long o = t.key[i];
+      const double o = t.key[i];
       rank += o > me ? 1 : 0; equal += o == me ? 1 : 0;
     }
     rank += dpp_i<0xB1, 0xf>(0, rank);                     // quad_perm [1,0,3,2]
     rank += dpp_i<0x4E, 0xf>(0, rank);                     // quad_perm [2,3,0,1]
     equal += dpp_i<0xB1, 0xf>(0, equal);
     equal += dpp_i<0x4E, 0xf>(0, equal);
-    if (__ballot(equal > 1) != 0ull)                       // (uniform, rare: equal scores go by slot and place)
+    if (__ballot(e < n && equal > 1) != 0ull)              // (uniform, rare: equal scores go by slot and place)
 #pragma unroll 1
       for (int i = 0; i < n; ++i) rank += (int)(t.key[i] == me) & (int)(t.at[i] < at);
     if ((tid & 3) == 0 && e < n && rank < Wb) put(rank, me, (int)(at >> 27), (int)(at & 0x7ffffffu), t.inc[e], t.att[e]);
@@ -782,9 +784,9 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select(const HypRec* _
   };
   ListEntry le;
   int nj;
-  unsigned long long best[DENSE_KEYS];
+  double best[DENSE_KEYS];
   double d_base = 0.0;
-  if constexpr (DENSE) { d_base = dense_base(p.lambda, p.slots[h0 + hj]); dense_fetch<BLOCK>(p, h0, Wb, best); }
+  if constexpr (DENSE) { d_base = dense_base(p.lambda, p.slots[h0 + hj]); dense_fetch<BLOCK>(p, u, best); }
   else load_entry(tid, le, nj);
   // (scalar loads: on their way together and waited for once, beside the vector loads)
   PIN4(fs, T, lmax_u, p.err);
@@ -812,9 +814,9 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select(const HypRec* _
   lds_barrier();
   TRACE_POINT(p, (size_t)u * Wb, 9);
   if constexpr (DENSE) {
-    const int n = dense_top<BLOCK>(p, s_top.top, h0, Wb, best, [&](int rank, unsigned long long image, int slot, int place, float inc, float att) {
+    const int n = dense_top<BLOCK>(p, s_top.top, u, Wb, best, [&](int rank, double J, int slot, int place, float inc, float att) {
       const int e = slot * Wb + rank;                      // (an entry of that slot's list, see div_m)
-      s_sel[rank] = e; s_J[e] = image_joint(image); s_inc[e] = inc; s_att[e] = att;
+      s_sel[rank] = e; s_J[e] = J; s_inc[e] = inc; s_att[e] = att;
       s_tok[e] = full_v_id(place, min(p.blank_id, p.eos_id), max(p.blank_id, p.eos_id));
     });
     if (tid == 0) s_n = n;
@@ -969,9 +971,9 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select_split(const Hyp
   constexpr int CH = BLOCK == 64 ? 3 : 1024 / BLOCK;       // (NE <= 144 for one wave)
   ListEntry le[CH];
   int nj[CH];
-  unsigned long long best[DENSE_KEYS];
+  double best[DENSE_KEYS];
   double d_base = 0.0;
-  if constexpr (DENSE) { d_base = dense_base(p.lambda, p.slots[h0 + hj]); dense_fetch<BLOCK>(p, h0, Wb, best); }
+  if constexpr (DENSE) { d_base = dense_base(p.lambda, p.slots[h0 + hj]); dense_fetch<BLOCK>(p, u, best); }
 #pragma unroll
   for (int k = 0; !DENSE && k < CH; ++k) {
     const int i = min(tid + k * BLOCK, NE - 1);
@@ -1017,9 +1019,9 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select_split(const Hyp
 
   int pick_n = -1, pick_0 = -1, ne = 0;                    // entry ranked n, entry ranked 0 (all scalar)
   if constexpr (DENSE) {
-    ne = dense_top<BLOCK>(p, s_top.top, h0, Wb, best, [&](int rank, unsigned long long image, int slot, int place, float inc, float att) {
+    ne = dense_top<BLOCK>(p, s_top.top, u, Wb, best, [&](int rank, double J, int slot, int place, float inc, float att) {
       const int e = slot * Wb + rank;                      // (an entry of that slot's list, see div_m)
-      s_sel[rank] = e; s_J[e] = image_joint(image); s_inc[e] = inc; s_att[e] = att;
+      s_sel[rank] = e; s_J[e] = J; s_inc[e] = inc; s_att[e] = att;
       s_tok[e] = full_v_id(place, min(p.blank_id, p.eos_id), max(p.blank_id, p.eos_id));
     });
   } else if (w == 0) {

@@ -43,6 +43,35 @@ extern "C" int unit_dense(const float* x, const float* F, const float* mref, int
   else hipLaunchKernelGGL((k_dense_scores<1, 2>), grid, dim3(256), 0, nullptr, x, F, slots.data(), Wb, Tp, V, p.K, p, 1, 0);
   return 0;
 }
+// The best Wb of all (slot, candidate) pairs: increments and attention values inc, att [Wb][K], the slots' base, in chunks of 1 << bits.  Out, per
+// rank: score, slot, place; returns how many reached the pivot (or, after rounds, the last best chunk's score), n_chunks how many chunks.
+template <int BLOCK>
+static void unit_top_kernel(SelectArgs p, DenseTopLds* t, const double* base, int Wb, double* J, int* slot, int* place, int* counts) {
+  double key[DENSE_KEYS];
+  dense_fetch<BLOCK>(p, 0, key);
+  if ((int)threadIdx.x < Wb) t->base[threadIdx.x] = base[threadIdx.x];
+  lds_barrier();
+  const int n = dense_top<BLOCK>(p, *t, 0, Wb, key, [&](int rank, double score, int s, int c, float, float) { J[rank] = score; slot[rank] = s; place[rank] = c; });
+  if (threadIdx.x == 0) { counts[0] = n; counts[1] = t->n_chunks; }
+}
+extern "C" void unit_top(int block, double lambda, const float* inc, const float* att, const double* base, int Wb, int K, int bits, double* J, int* slot, int* place, int* counts) {
+  SelectArgs p;
+  memset(&p, 0, sizeof p);
+  p.lambda = lambda; p.inc = inc; p.att = att; p.K = K; p.chunk_bits = bits; p.n_chunks = (K + (1 << bits) - 1) >> bits; p.pitch = dense_pitch(Wb);
+  std::vector<double> best((size_t)p.n_chunks * p.pitch, __builtin_nan(""));
+  for (int c = 0; c < p.n_chunks; ++c)
+    for (int j = 0; j < Wb; ++j) {
+      double& b = best[(size_t)c * p.pitch + j];
+      b = LOG0D;
+      for (int k = c << bits; k < min(K, (c + 1) << bits); ++k) b = fmax(b, dense_joint(lambda, base[j], inc[(size_t)j * K + k], att[(size_t)j * K + k]));
+    }
+  p.best = best.data();
+  DenseTopLds* t = (DenseTopLds*)malloc(sizeof(DenseTopLds));
+  memset(t, 0xa5, sizeof *t);
+  if (block == 1024) hipLaunchKernelGGL(unit_top_kernel<1024>, dim3(1), dim3(1024), 0, nullptr, p, t, base, Wb, J, slot, place, counts);
+  else hipLaunchKernelGGL(unit_top_kernel<256>, dim3(1), dim3(256), 0, nullptr, p, t, base, Wb, J, slot, place, counts);
+  free(t);
+}
 // The pivot for rows of log-probabilities: s_hist 256 words, mx the lanes' 256 maxima.
 static void unit_pivot_kernel(uint32_t* s_hist, const float* mx, int K, float* out) {
   s_hist[threadIdx.x] = 0;

@@ -1,5 +1,6 @@
 """Every id a candidate: the best of all (slot, candidate) pairs from the best of each chunk of 16 or 32 candidates.  Fewer chunks than
-beam slots, more chunks than the lanes hold (2050 ids: 4096 chunks of 16; 2051 ids: one per slot more, so chunks of 32), posteriors
+beam slots, about as many chunks as the lanes hold (4096 entries of a beam's slots and one more, or none, per chunk; 1986 ids, beam 32: 124 chunks of 16; 1987 ids: one more,
+so chunks of 32), more of them, numbers of ids that are powers of two, posteriors
 and attention rows that are the same for most ids (more chunks reach the pivot than fit, equal scores go by slot and id), one work-group per slot and one per utterance.  Against the oracle, step by step (tolerances
 as in test_gpu_parity.py)."""
 import numpy as np
@@ -11,7 +12,7 @@ from helpers import lockstep_decode
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("vocab,beam,utts", [(70, 32, 2), (530, 32, 2), (1300, 3, 2), (2100, 20, 2), (9001, 32, 2), (2050, 32, 2), (2051, 32, 2), (1300, 3, 690), (90, 32, 70)])
+@pytest.mark.parametrize("vocab,beam,utts", [(70, 32, 2), (530, 32, 2), (1300, 3, 2), (2100, 20, 2), (9001, 32, 2), (2050, 32, 2), (2051, 32, 2), (1986, 32, 2), (1987, 32, 2), (1024, 20, 2), (4096, 20, 2), (4096, 32, 2), (1300, 3, 690), (90, 32, 70)])
 @pytest.mark.parametrize("same", [0, 3])                     # ids that differ from the others (0: all do)
 def test_best_of_all_pairs(vocab, beam, utts, same):
     w = gen.workload("cfg1")

@@ -138,6 +138,68 @@ def test_pivot_is_close_to_the_last_candidate(units, K, centre, spread):
         assert out[0] > kth - max(0.125, abs(kth) / 128), (out[0], kth)
 
 
+def top_pairs(units, inc, att, base, bits, lam=1.0, block=256):
+    Wb, K = inc.shape
+    J, slot, place, counts = np.full(Wb, np.nan), np.full(Wb, -1, np.int32), np.full(Wb, -1, np.int32), np.zeros(2, np.int32)
+    base = np.ascontiguousarray(base, np.float64)
+    units.unit_top(block, ctypes.c_double(lam), ptr(inc), ptr(att), ptr(base), Wb, K, bits, ptr(J), ptr(slot), ptr(place), ptr(counts))
+    return J, slot, place, counts
+
+
+def check_top(inc, base, got):
+    # (lambda = 1: the joint score is base + increment, rounded once)
+    Wb, K = inc.shape
+    want = np.where(inc > -1e29, base[:, None] + inc.astype(np.float64), -np.inf).ravel()
+    order = np.lexsort((np.arange(Wb * K), -want))[:Wb]
+    order = order[want[order] > -1e29]
+    J, slot, place, counts = got
+    n = len(order)
+    assert np.array_equal(J[:n], want[order]) and np.array_equal(slot[:n], order // K) and np.array_equal(place[:n], order % K)
+    assert (slot[n:] == -1).all() and counts[0] >= n
+
+
+# The best pairs of a beam, slots that share their best candidates as the hypotheses of a beam do; numbers of candidates whose chunks per
+# slot are a power of two among them, more chunks than the lanes hold.  How many chunks reach the pivot: the Wb-th largest of 64 maxima
+# lets those through that share a maximum with a better one, up to 2 Wb measured in decodes; bound 3 Wb and a few.  (Slots one after the other
+# in the maxima: 4 to 9 Wb at numbers of chunks that are multiples of 64; a pivot of 14 bits of the range, scores on both sides of
+# zero: up to 10 Wb.)
+@pytest.mark.parametrize("Wb,K,bits", [(1, 65, 4), (3, 998, 5), (8, 2048, 4), (16, 1022, 4), (20, 1022, 4), (20, 4094, 5), (20, 4998, 5), (32, 66, 4), (32, 510, 4), (32, 2048, 5), (32, 4094, 5), (10, 65533, 5)])
+@pytest.mark.parametrize("level,spread", [(-40.0, 4.0), (-1500.0, 4.0), (0.0, 3.0)])
+def test_best_pairs_from_few_chunks(units, Wb, K, bits, level, spread):
+    for zipf in (0, 1):
+        rng = np.random.default_rng(100 * Wb + zipf)
+        shared = spread * rng.standard_normal(K) - spread * 0.6 * np.log1p(np.arange(K)) * zipf
+        inc = (shared[None] + 0.5 * rng.standard_normal((Wb, K))).astype(np.float32)
+        base = level - 0.7 * spread * rng.random(Wb)
+        got = top_pairs(units, inc, np.zeros((Wb, K), np.float32), base, bits)
+        check_top(inc, base, got)
+        assert got[3][1] <= 3 * Wb + 6, got[3]
+
+
+# More chunks or more scores at the pivot than fit: all scores equal, two levels, equal in their upper halves; and hardly any score at all.
+# Equal scores go by slot and place.
+@pytest.mark.parametrize("Wb,K,bits,block", [(32, 2048, 4, 256), (32, 4094, 5, 1024), (20, 1022, 4, 256), (2, 9001, 4, 256), (3, 70, 4, 256), (32, 600, 5, 256)])
+def test_best_pairs_of_scores_that_agree(units, Wb, K, bits, block):
+    rng = np.random.default_rng(K)
+    att = rng.standard_normal((Wb, K)).astype(np.float32)
+    flat = np.full((Wb, K), -2.0, np.float32)
+    base = np.full(Wb, -7.0)
+    check_top(flat, base, top_pairs(units, flat, att, base, bits, block=block))
+    two = flat.copy()
+    two[-1, [K - 1, 5]] = -1.0
+    check_top(two, base, top_pairs(units, two, att, base, bits, block=block))
+    near = (flat + rng.permutation(Wb * K).reshape(Wb, K).astype(np.float32) * np.float32(2.0 ** -22)).astype(np.float32)
+    check_top(near, base + 4000.0, top_pairs(units, near, att, base + 4000.0, bits, block=block))
+    signs = np.where(rng.random((Wb, K)) < 0.5, 7.0, np.float32(7.0 - 2.0 ** -21)).astype(np.float32)      # (scores of zero, and a little below)
+    check_top(signs, base, top_pairs(units, signs, att, base, bits, block=block))
+    few = np.full((Wb, K), -1e30, np.float32)
+    few[Wb // 2, 3] = -5.0
+    few[0, K - 1] = -5.0
+    check_top(few, base, top_pairs(units, few, att, base, bits, block=block))
+    few[:] = -1e30
+    check_top(few, base, top_pairs(units, few, att, base, bits, block=block))
+
+
 # Sums over near frames that the frames left out may count for take in the frames that can, not all of them: in steps
 # whose window is the whole utterance a third of the loads remains (the first of the three steps has no near frames: a
 # term of its third is loaded 1.6 times, and of the others' 0.25 times to begin with).
