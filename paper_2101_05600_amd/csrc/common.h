@@ -142,7 +142,7 @@ struct Params {
   DenseSlot* dense_slot;     // [2][U][Wb], by the record's buffer (a step's: its own)
   DenseEos* dense_eos;       // [2][U][Wb] (likewise)
   DenseLeft* dense_left;     // [U][Wb] what ctcbs_peek needs of the last step in which a slot held a hypothesis
-  double* dense_best;        // [U][chunks][dense_pitch] the best joint score that each slot has in each work-group's candidates (log0: none)
+  double* dense_best;        // [U][chunks][dense_pitch] the best joint score that each slot has in each work-group's candidates (NaN: none)
   const float* dense_att;    // this step's attention rows
   int32_t keep_cand;         // KEEP_*: which of the per-candidate arrays below a step fills (ctcbs_peek; large K needs them)
   // per-step scratch between the score and the select kernel

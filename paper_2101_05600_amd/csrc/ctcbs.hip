@@ -508,7 +508,7 @@ static int step_impl(ctcbs_t* h, const Params& with, const float* d_att_logp, ct
   const bool split = split_select(p);
   size_t sel_lds = (size_t)36 * ((p.Wb * p.Wb + 63) & ~63) + 32;
   if (h->dense) {                                          // (no keys; split: then dense_terms)
-    sel_lds = (size_t)20 * ((p.Wb * p.Wb + 63) & ~63);
+    sel_lds = (size_t)20 * ((p.Wb * p.Wb + 63) & ~63) + (size_t)DenseTopList::BYTES * p.Wb;
     if (split && sel_lds < (size_t)p.Tp * 4) sel_lds = (size_t)p.Tp * 4;
   }
   SelectArgs a;

@@ -56,16 +56,20 @@ __device__ __forceinline__ float add_log(float M, float sum) {
 
 // the largest value of each half of the wave (N = 32) or row of 16 lanes, in all of its lanes
 template <int N>
-__device__ __forceinline__ uint32_t lanes_max_u32(uint32_t v) {
-  auto turn = [&](uint32_t o) { return max(v, o); };
-  v = turn((uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, true));
-  v = turn((uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xf, 0xf, true));
-  v = turn((uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x122, 0xf, 0xf, true));
-  v = turn((uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x121, 0xf, 0xf, true));
+__device__ __forceinline__ int lanes_max_i(int v) {
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, true));
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x124, 0xf, 0xf, true));
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x122, 0xf, 0xf, true));
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x121, 0xf, 0xf, true));
   if (N == 32) {
-    const uint32_t a = max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16));
-    const uint32_t b = max((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48));
+#if defined(__AMDGCN__)
+    const auto rows = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);   // (each row beside its neighbour)
+    v = max((int)rows[0], (int)rows[1]);
+#else
+    const int a = max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16));
+    const int b = max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48));
     v = (threadIdx.x & 32) != 0 ? b : a;
+#endif
   }
   return v;
 }
@@ -227,10 +231,12 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, int l, int cur) 
 // Tried before that, slower with four: 16 candidates per work-group (120 us there), a wave for each 16
 // candidates, no sums between waves, 25.4 and 122, four halves ahead (33 us), work-groups
 // that stay and fetch the next candidates' frames before they finish the last (25.5 and 130).
-// The joint scores and each slot's best of them take 5.4 us more a launch (24.7 -> 30.1 at 16 utterances of 1500 frames, 5000 ids,
-// beam 20: 2 of it arithmetic, 1.4 the attention values' way to memory), the select kernel 2.8 more (10.9 -> 13.7); the launch that
-// made lists of all scores took 10.7.  A decode there 9978 -> 9620 us, of one utterance of 800 frames, beam 10, 2455 -> 2098, of 24 of 250 to 500,
-// 3000 ids, beam 3, windows of 50 2326 -> 2143, of 32 of 1500 frames at beam 20 the same.
+// The joint scores and each slot's best of them took 5.4 us more a launch (24.7 -> 30.1 at 16 utterances of 1500 frames, 5000 ids,
+// beam 20), the select kernel 2.8 more; the launch that made lists of all scores took 10.7.  A decode there 9978 -> 9620 us, of one utterance of
+// 800 frames, beam 10, 2455 -> 2098.  In large batches of short inputs that was more than it saved, until the attention values no longer waited for
+// the finished flag, waves without a slot did nothing and a slot's best took two thirds of the instructions; us a decode with lists, then, now:
+// 128 utterances of 300 to 400 frames, 5000 ids, beam 20 14060 / 14340 / 12945, 690 of 100 to 200, 1000 ids, beam 3 4210 / 4410 / 4245,
+// 2100 of 60 to 120, beam 1 6250 / 7290 / 6910 (there the lists are still better), 16 of 1500, beam 20 9980 / 8480 / 8285.
 template <int NT, int MT>
 __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(const float* __restrict__ xT, const float* __restrict__ F,
                                                          const DenseSlot* __restrict__ slots,
@@ -248,19 +254,26 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
   const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6), n = lane & 15, q = lane >> 4;
   const int u = blockIdx.y, c0 = (int)blockIdx.x * NC;
   const size_t h0 = (size_t)u * Wb;
-  const bool joint = p.dense_att != nullptr;                   // (uniform)
-  if (joint && blockIdx.x == 0 && u == 0 && w == 3) publish_progress(p.host_progress, p.n_finished, l);
-  // (all that depends on nothing is asked for together)
-  const uint8_t finished = FETCH(p.finished + u);
-  const int T = p.uinfo[u].T;
+  PIN4(p.finished, p.uinfo, p.dense_att, p.blank_id);
+  // (all that depends on nothing is asked for together; LOADED: what a uniform address gives is wanted in scalar registers, for which
+  // the compiler waits as soon as it can)
+  int finished = FETCH(p.finished + u), T = FETCH(&p.uinfo[u].T);
   DenseSlot d = slots[h0 + min(lane, Wb - 1)];
   const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
-  const int cc = tid & (NC - 1), c = c0 + cc, id = full_v_id(min(c, K - 1), lo_ex, hi_ex);
+  int me = tid;
+  auto candidate = [&](int& cc, int& c, int& id) { cc = me & (NC - 1); c = c0 + cc; id = full_v_id(min(c, K - 1), lo_ex, hi_ex); };
+  int cc, c, id;
+  candidate(cc, c, id);
+  const float* att_u = p.dense_att + h0 * (size_t)V;
+  const int first = 64 / NC * w;                               // of the wave's slots among SLOTS (waves beyond the beam have nothing to do)
   float att[NS];
 #pragma unroll
-  for (int i = 0; i < NS; ++i) att[i] = joint ? FETCH(p.dense_att + (h0 + min(i * SLOTS + tid / NC, Wb - 1)) * (size_t)V + id) : 0.0f;
-  LOADED(d.live); LOADED(d.s); LOADED(d.mref);
-  if (joint && blockIdx.x == 0 && tid < Wb) {                  // the slot's own results: window, eos scores, work
+  for (int i = 0; i < NS; ++i)
+    if (i * SLOTS + first < Wb) att[i] = FETCH((const float*)((const char*)att_u + 4u * ((uint32_t)min(i * SLOTS + tid / NC, Wb - 1) * (uint32_t)V + (uint32_t)id)));
+  LOADED(finished); LOADED(T); LOADED(d.live); LOADED(d.s); LOADED(d.mref);
+  finished = uni(finished); T = uni(T);
+  if (blockIdx.x == 0 && u == 0 && w == 3) publish_progress(p.host_progress, p.n_finished, l);
+  if (blockIdx.x == 0 && tid < Wb) {                  // the slot's own results: window, eos scores, work
     GroupOut g = {0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
     if (!finished && d.live) {
       const DenseEos o = p.dense_eos[h0 + tid];
@@ -273,12 +286,6 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
   }
   if (finished) return;
   const uint32_t live_slots = (uint32_t)__ballot(lane < Wb && d.live);
-#pragma unroll
-  for (int i = 0; i < NS; ++i) {
-    const int j = i * SLOTS + tid / NC;
-    s_att[i][tid] = att[i];
-    if (joint && (live_slots >> j & 1u) != 0u && c < K) STORE_ASIDE(att[i], p.cand_att + h0 * (size_t)K + (uint32_t)(j * K + c));
-  }
   // the blocks that any slot has an F for, b0 .. e0 - 1, and those read at first, b1 .. e1 - 1
   int b0, e0, b1, e1;
   {
@@ -298,11 +305,12 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
   // (four lanes in a row hold 64 bytes of a candidate, or slot, for the loads; `turn` brings them to where the products need them)
   const int row = lane >> 2, piece = lane & 3;
   const float* bp[NT];
-  const float* ap[MT];
+  uint32_t ap[MT];                                             // (bytes from the utterance's F on)
 #pragma unroll
   for (int k = 0; k < NT; ++k) bp[k] = xu + (size_t)full_v_id(min(c0 + 16 * k + row, K - 1), lo_ex, hi_ex) * Tp + 4 * piece;
 #pragma unroll
-  for (int m = 0; m < MT; ++m) ap[m] = F + (h0 + min(16 * m + row, Wb - 1)) * Tp + 4 * piece;
+  for (int m = 0; m < MT; ++m) ap[m] = 4u * (uint32_t)(min(16 * m + row, Wb - 1) * Tp + 4 * piece);
+  const char* F_u = (const char*)(F + h0 * Tp);
   f32x4 (*turn)[64] = (f32x4 (*)[64])s_wave[w];
   const int put = 16 * piece + ((row + 4 * piece) & 15), get = 16 * q + ((n + 4 * q) & 15);
   f32x4 acc[MT][NT], sum[MT][NT];
@@ -314,26 +322,23 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
   // attention values beside the increments (the caller's rows may be gone when someone looks)
   const int n_chunks = (K + NC - 1) / NC;                      // (the grid's width)
   double* best_c = p.dense_best + ((size_t)u * n_chunks + blockIdx.x) * dense_pitch(Wb);
-  auto scored = [&](int j0, bool mine, int js, float inc) {
-    const float a = s_att[j0 / SLOTS][tid];
-    const double J = dense_joint(p.lambda, s_jb[js], inc, a);
-    const unsigned long long img = mine ? joint_image(J) : 0ull;
-    const uint32_t hi = (uint32_t)(img >> 32), best_hi = lanes_max_u32<NC>(hi);
-    // (the lane that has it stores it; scores equal in the upper half, or none at all: the first lane, the largest lower half)
-    unsigned long long best = img;
-    bool write = hi == best_hi;
-    if (__popcll(__ballot(write)) != 64 / NC) {                // (uniform)
-      best = (unsigned long long)best_hi << 32 | lanes_max_u32<NC>(write ? (uint32_t)img : 0u);
-      write = cc == 0;
+  auto scored = [&](int j0, bool mine, int js, float inc, int cc, int c, int id) {
+    const double J = dense_sum(p.lambda, s_jb[js], inc, s_att[j0 / SLOTS][tid]);
+    // (the upper half of the score as an integer of its order; the lane with the largest stores its score.  No score: NaN, the least there)
+    const long long b = __double_as_longlong(J);
+    const bool some = mine & (inc > LOG0_CLASS) & (J > (double)LOG0_CLASS);
+    const int hi = some ? (int)(b >> 32) : -1, sign = hi >> 31, ord = hi ^ (sign & 0x7fffffff);
+    bool write = ord == lanes_max_i<NC>(ord);
+    if (__popcll(__ballot(write)) != 64 / NC) {                // (uniform) scores equal in the upper half, or none at all
+      const int lo = (int)b ^ (int)0x80000000 ^ sign, best_lo = lanes_max_i<NC>(write ? lo : (int)0x80000000);
+      const unsigned long long same = __ballot(write & (lo == best_lo)) >> (lane & ~(NC - 1));   // (equal scores: the first lane)
+      write = cc == __ffs((int)((uint32_t)same & (NC == 32 ? ~0u : 0xffffu))) - 1;
     }
-    if (write && j0 + tid / NC < Wb) best_c[js] = best != 0ull ? image_joint(best) : LOG0D;
-    if (mine) {
-      const uint32_t g = (uint32_t)js * (uint32_t)K + (uint32_t)c;
-      if (p.keep_cand) {                                       // (uniform: for ctcbs_peek)
-        const size_t gk = h0 * (size_t)K + g;
-        p.cand_id[gk] = id; p.cand_joint[gk] = J;
-        p.cand_ctc[gk] = inc > LOG0_CLASS ? slots[h0 + js].offr + (double)inc : LOG0D;
-      }
+    if (write && j0 + tid / NC < Wb) best_c[js] = __longlong_as_double((long long)((unsigned long long)(uint32_t)hi << 32 | (uint32_t)b));
+    if (mine && p.keep_cand) {                                 // (for ctcbs_peek)
+      const size_t gk = h0 * (size_t)K + ((uint32_t)js * (uint32_t)K + (uint32_t)c);
+      p.cand_id[gk] = id; p.cand_joint[gk] = inc > LOG0_CLASS ? J : LOG0D;
+      p.cand_ctc[gk] = inc > LOG0_CLASS ? slots[h0 + js].offr + (double)inc : LOG0D;
     }
   };
   // all of the loop's control is uniform.  whole: nothing is left out; far: a sum that the frames left out may count for
@@ -341,23 +346,41 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
   float* inc_u = p.cand_inc + h0 * (size_t)K;
   uint32_t again = 0;                                          // a bit for each of the lane's sums that is to be redone
   // the frames read at first; where those left out can count, those before and those behind them too
-#pragma unroll 1
-  for (int part = 0; part < 3; ++part) {
-    const int b = part == 0 ? b1 : (part == 1 ? b0 : e1), end = part == 0 ? e1 : (part == 1 ? b1 : e0);
-    const int nh = (2 * (end - b) + 3 - w) >> 2;               // the wave's halves of a block
+  f32x4 x[AHEAD][NT], f[AHEAD][MT];
+  int b = b1, end = e1, nh;
+  auto fetch = [&](int i, int a) {
+    i = min(i, nh - 1);
+    const int t = 32 * b + 16 * (w + 4 * i);
+#pragma unroll
+    for (int k = 0; k < NT; ++k) x[a][k] = *(const f32x4*)(bp[k] + t);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) f[a][m] = *(const f32x4*)(F_u + 4 * (size_t)t + ap[m]);
+    SCHED_FENCE();
+  };
+  auto start = [&]() {
+    nh = (2 * (end - b) + 3 - w) >> 2;                         // the wave's halves of a block
     if (nh > 0) {
-      f32x4 x[AHEAD][NT], f[AHEAD][MT];
-      auto fetch = [&](int i, int a) {
-        i = min(i, nh - 1);
-        const int t = 32 * b + 16 * (w + 4 * i);
-#pragma unroll
-        for (int k = 0; k < NT; ++k) x[a][k] = *(const f32x4*)(bp[k] + t);
-#pragma unroll
-        for (int m = 0; m < MT; ++m) f[a][m] = *(const f32x4*)(ap[m] + t);
-        SCHED_FENCE();
-      };
 #pragma unroll
       for (int a = 0; a < AHEAD; ++a) fetch(a, a);
+    }
+  };
+  // (the attention values when the first frames are on their way, so that nothing waits for both in turn; not where that spills:
+  // 128 utterances of 300 to 400 frames, 5000 ids, beam 20, 13590 -> 14030 us a decode, 2100 of 60 to 120, 1000 ids, beam 1, 6970 -> 6920)
+  constexpr bool FRAMES_FIRST = MT * NT < 4;
+  if (FRAMES_FIRST) start();
+  float* att_kept = p.cand_att + h0 * (size_t)K;
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    const int j = i * SLOTS + tid / NC;
+    if (i * SLOTS + first >= Wb) break;                        // (uniform)
+    s_att[i][tid] = att[i];
+    if ((live_slots >> j & 1u) != 0u && c < K) STORE_ASIDE(att[i], (float*)((char*)att_kept + 4u * (uint32_t)(j * K + c)));
+  }
+#pragma unroll 1
+  for (int part = 0; part < 3; ++part) {
+    if (part > 0) { b = part == 1 ? b0 : e1; end = part == 1 ? b1 : e0; }
+    if (part > 0 || !FRAMES_FIRST) start();
+    if (nh > 0) {
 #pragma unroll 1
       for (int i = 0; i < nh; i += AHEAD) {
 #pragma unroll
@@ -407,8 +430,10 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
     // ---- increments: lane = candidate, the slots dealt to the 256 / NC groups of lanes ----
     whole |= part > 0;
     far = false; again = 0;
+    LOADED(me);                                                // (or the lane's candidate is kept in registers through the products)
+    candidate(cc, c, id);
 #pragma unroll 1
-    for (int j0 = 0; j0 < Wb; j0 += SLOTS) {
+    for (int j0 = 0; j0 + first < Wb; j0 += SLOTS) {
       const int j = j0 + tid / NC, js = min(j, Wb - 1);
       const int at = js * (NC + 1) + cc;
       const float v = (s_wave[0][at] + s_wave[1][at]) + (s_wave[2][at] + s_wave[3][at]);
@@ -418,7 +443,7 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
       far |= mine && !rep && !(v > s_low[js]);
       again |= mine && !rep && !(v > DENSE_RANGE) ? 1u << (j0 / SLOTS) : 0u;
       if (mine) *(float*)((char*)inc_u + 4u * (uint32_t)(js * K + c)) = canon0(inc);
-      if (joint) scored(j0, mine, js, canon0(inc));
+      scored(j0, mine, js, canon0(inc), cc, c, id);
     }
     if (whole) break;
     const bool any = __ballot(far) != 0ull;                    // (rare)
@@ -452,11 +477,11 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
       if (lane == who) *(float*)((char*)inc_u + 4u * (uint32_t)(j * K + c)) = canon0(r);
     }
   }
-  if (joint && redone != 0ull)                                 // (uniform: the wave holds whole chunks)
+  if (redone != 0ull)                                          // (uniform: the wave holds whole chunks)
 #pragma unroll 1
-    for (int j0 = 0; j0 < Wb; j0 += SLOTS) {
+    for (int j0 = 0; j0 + first < Wb; j0 += SLOTS) {
       const int j = j0 + tid / NC, js = min(j, Wb - 1);
       const bool mine = j < Wb && c < K && s_live[js];
-      scored(j0, mine, js, mine ? FETCH(inc_u + (size_t)js * K + c) : LOG0F);
+      scored(j0, mine, js, mine ? FETCH(inc_u + (size_t)js * K + c) : LOG0F, cc, c, id);
     }
 }

@@ -43,8 +43,9 @@ struct DenseLeft { double offr, jbase; };
 // Joint score (Eq. (1)) of a candidate from its increment and its attention value: the same to the last bit wherever it is formed
 template <class S>
 __host__ __device__ __forceinline__ double dense_base(double lambda, const S& d) { return fma(lambda, d.offr, d.jbase); }
+__host__ __device__ __forceinline__ double dense_sum(double lambda, double base, float inc, float att) { return fma(lambda, (double)inc, fma(1.0 - lambda, (double)att, base)); }
 __host__ __device__ __forceinline__ double dense_joint(double lambda, double base, float inc, float att) {
-  return inc > LOG0_CLASS ? fma(lambda, (double)inc, fma(1.0 - lambda, (double)att, base)) : LOG0D;
+  return inc > LOG0_CLASS ? dense_sum(lambda, base, inc, att) : LOG0D;
 }
 
 #define PIVOT_CAP 512     // entries of the short list (all waves together)

@@ -481,22 +481,33 @@ __device__ __forceinline__ int rank_lists(const unsigned long long* s_key, unsig
 // at beam 32, and where a slot's number of chunks was a multiple of 64 the rounds below in many steps: a decode of 4 utterances of 700 frames,
 // 4096 ids, beam 32, 9450 -> 3180 us, 16 at beam 20 7570 -> 4760, 16 of 500, 1024 ids, beam 32, 4240 -> 2260; 16 of 1500, 5000 ids, beam 20,
 // 8740 -> 8480; maxima past those that the lanes hold eight at a time: one utterance of 300, 20000 ids, beam 32, 2760 -> 1840.
-// More than CHUNKS chunks or CAP scores at the pivot (scores equal in their upper halves, to 2^-20 relative): the Wb best chunks exactly, in
+// More than CHUNKS chunks or 32 Wb scores at the pivot (scores equal in their upper halves, to 2^-20 relative): the Wb best chunks exactly, in
 // Wb rounds of a block-wide maximum, whose candidates are all that can be among the best.  (Figures: k_dense_scores.)
+template <int BLOCK>
 struct DenseTopLds {
-  static constexpr int CAP = 32 * MAX_BEAM, CHUNKS = 128;
-  double key[CAP];
-  uint32_t at[CAP];                                        // slot in the upper 5 bits, place
-  float inc[CAP], att[CAP];
-  uint32_t chunk[CHUNKS];                                  // (likewise, the chunk's first place)
+  static constexpr int CHUNKS = 128;
+  uint32_t chunk[CHUNKS];                                  // slot in the upper 5 bits, the chunk's first place
   double base[MAX_BEAM];
   double r_key[2][16];
   uint32_t r_at[2][16];
-  uint32_t kmax[1024];
+  uint32_t all_max[BLOCK];
+  uint32_t kmax[64], rank[64];
   int n_chunks, n;
 };
-template <bool DENSE> struct DenseLds { int none; };
-template <> struct DenseLds<true> { DenseTopLds top; };
+// The scores that reach the pivot, 32 for each new hypothesis (as many as Wb chunks hold), in dynamic LDS behind the 20 * NP bytes of the
+// select kernels' entries: 20 bytes each.
+struct DenseTopList {
+  double* key;
+  uint32_t* at;                                            // slot in the upper 5 bits, place
+  float *inc, *att;
+  int cap;
+  static constexpr int BYTES = 20 * 32;
+  __device__ __forceinline__ DenseTopList(unsigned char* lds, int Wb) : key((double*)lds), cap(32 * Wb) {
+    at = (uint32_t*)(key + cap); inc = (float*)(at + cap); att = inc + cap;
+  }
+};
+template <bool DENSE, int BLOCK> struct DenseLds { int none; };
+template <int BLOCK> struct DenseLds<true, BLOCK> { DenseTopLds<BLOCK> top; };
 template <bool DENSE> struct DenseNext { int none; };
 template <> struct DenseNext<true> : HypRec {};             // the new hypothesis
 constexpr int DENSE_KEYS = 16;                             // best scores of chunks that a lane holds
@@ -513,7 +524,7 @@ __device__ __forceinline__ void dense_fetch(const SelectArgs& p, int u, double (
 }
 // put(rank, score, slot, place, inc, att) by one lane for each of the best.  Returns how many there are (Wb or more: all).
 template <int BLOCK, class F>
-__device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, int u, int Wb, const double (&key)[DENSE_KEYS], F&& put) {
+__device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds<BLOCK>& t, const DenseTopList& list, int u, int Wb, const double (&key)[DENSE_KEYS], F&& put) {
   constexpr int NW = BLOCK / 64;
   int tid = threadIdx.x;
   const int lane = tid & 63, w = uni(tid >> 6);
@@ -537,14 +548,25 @@ __device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, in
   };
   double most = LOG0D;
   each([&](int, double k) { most = fmax(most, k); });      // (the pitch's spare entries are NaN)
-  uint32_t kmax = (uint32_t)(joint_image(most) >> 32);
-  t.kmax[tid] = kmax;
+  // The 64 maxima, and the rank of each: a quarter of the comparisons by each of four waves (lanes turned by a quarter, see take_k; all by
+  // every wave, 13 cycles a value: 100 utterances of 60 to 200 frames, 800 ids, beam 20, 1727 -> 1617 us a decode, 256 of 400 to 700, 1000 ids 13490 -> 13290; bit by bit with ballots, until just Wb are left: 128 utterances, 100 ids,
+  // beam 20, 2785 -> 2850).
+  t.all_max[tid] = (uint32_t)(joint_image(most) >> 32);
   if (tid == 0) { t.n_chunks = 0; t.n = 0; }
   lds_barrier();
-  // 64 maxima, each of every 64th lane's, of which Wb reach the pivot (every wave for itself)
+  if (w < 4) {
+    const int turned = (lane + 16 * w) & 63;
+    uint32_t v = t.all_max[turned];
 #pragma unroll
-  for (int i = 0; i < NW; ++i) kmax = max(kmax, t.kmax[64 * i + lane]);
-  const int above = lanes_above<8>(kmax, 64);
+    for (int i = 1; i < NW; ++i) v = max(v, t.all_max[64 * i + turned]);
+    int n = 0;
+    above8<0>(v, n); above8<8>(v, n);
+    ((uint8_t*)t.rank)[4 * turned + w] = (uint8_t)n;
+    if (w == 0) t.kmax[lane] = v;
+  }
+  lds_barrier();
+  const uint32_t kmax = t.kmax[lane];
+  const int above = (int)((t.rank[lane] * 0x01010101u) >> 24);
   uint32_t L = 0u;
 #pragma unroll 1
   for (int r = Wb - 1; r >= 0; --r) {                      // (equal maxima: the rank before)
@@ -557,7 +579,7 @@ __device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, in
   each([&](int i, double k) {
     if (k >= low) {
       const int pos = atomicAdd(&t.n_chunks, 1);
-      if (pos < DenseTopLds::CHUNKS) t.chunk[pos] = chunk_at(i);
+      if (pos < DenseTopLds<BLOCK>::CHUNKS) t.chunk[pos] = chunk_at(i);
     }
   });
   lds_barrier();
@@ -581,15 +603,15 @@ __device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, in
         const double J = dense_joint(p.lambda, t.base[slot], inc[k], att[k]);
         if (e < n << bits && (int)(at[k] & 0x7ffffffu) < p.K && J > (double)LOG0_CLASS && J >= least) {   // (false for NaN)
           const int pos = atomicAdd(&t.n, 1);
-          if (pos < DenseTopLds::CAP) { t.key[pos] = J; t.at[pos] = at[k]; t.inc[pos] = inc[k]; t.att[pos] = att[k]; }
+          if (pos < list.cap) { list.key[pos] = J; list.at[pos] = at[k]; list.inc[pos] = inc[k]; list.att[pos] = att[k]; }
         }
       }
     }
   };
   int nc = uni(t.n_chunks);
-  if (nc <= DenseTopLds::CHUNKS) candidates(nc, low);
+  if (nc <= DenseTopLds<BLOCK>::CHUNKS) candidates(nc, low);
   lds_barrier();
-  if (nc > DenseTopLds::CHUNKS || uni(t.n) > DenseTopLds::CAP) {   // (uniform, rare)
+  if (nc > DenseTopLds<BLOCK>::CHUNKS || uni(t.n) > list.cap) {   // (uniform, rare)
     double last = 0.0;
     uint32_t last_at = 0u;
     nc = 0;
@@ -628,16 +650,16 @@ __device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, in
     candidates(nc, last);
     lds_barrier();
   }
-  const int n = min(uni(t.n), (int)DenseTopLds::CAP);
+  const int n = min(uni(t.n), list.cap);
 #pragma unroll 1
   for (int e0 = 0; e0 < n; e0 += BLOCK / 4) {
     const int e = e0 + (tid >> 2);
-    const double me = e < n ? t.key[e] : 0.0;
-    const uint32_t at = e < n ? t.at[e] : 0u;
+    const double me = e < n ? list.key[e] : 0.0;
+    const uint32_t at = e < n ? list.at[e] : 0u;
     int rank = 0, equal = 0;                               // (its own entry among the equal ones)
 #pragma unroll 2
     for (int i = tid & 3; i < n; i += 4) {
-      const double o = t.key[i];
+      const double o = list.key[i];
       rank += o > me ? 1 : 0; equal += o == me ? 1 : 0;
     }
     rank += dpp_i<0xB1, 0xf>(0, rank);                     // quad_perm [1,0,3,2]
@@ -646,8 +668,8 @@ __device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds& t, in
     equal += dpp_i<0x4E, 0xf>(0, equal);
     if (__ballot(e < n && equal > 1) != 0ull)              // (uniform, rare: equal scores go by slot and place)
 #pragma unroll 1
-      for (int i = 0; i < n; ++i) rank += (int)(t.key[i] == me) & (int)(t.at[i] < at);
-    if ((tid & 3) == 0 && e < n && rank < Wb) put(rank, me, (int)(at >> 27), (int)(at & 0x7ffffffu), t.inc[e], t.att[e]);
+      for (int i = 0; i < n; ++i) rank += (int)(list.key[i] == me) & (int)(list.at[i] < at);
+    if ((tid & 3) == 0 && e < n && rank < Wb) put(rank, me, (int)(at >> 27), (int)(at & 0x7ffffffu), list.inc[e], list.att[e]);
   }
   return n;
 }
@@ -720,7 +742,7 @@ __device__ __forceinline__ bool wave_ended_set(const SelectArgs& p, int Wb, int 
 // Wave 0 ranks the lists and takes the ended set, the others 64 / LPS new hypotheses each at a time.
 // Wb_m: the beam, in the bits from 8 on 65536 / Wb + 1 (a position i < 1024 is of list (i * that) >> 16).
 // Dynamic LDS: 36 * NP + 32 bytes, NP = Wb * Wb rounded up to whole waves (the list entries and the packed keys); every id a candidate:
-// 20 * NP (no keys: with them a beam of 32 would take more than 64 KB).
+// 20 * NP (no keys: with them a beam of 32 would take more than 64 KB) and DenseTopList::BYTES * Wb.
 template <int BLOCK, int LPS, int FPL, bool DENSE>
 __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select(const HypRec* __restrict__ rec_now, UttState* __restrict__ utt,
                                                   const GroupOut* __restrict__ grp, const ListEntry* __restrict__ grp_list,
@@ -736,7 +758,8 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select(const HypRec* _
   int* s_tok = (int*)(s_J + NP);                                      // [NP] each
   float* s_inc = (float*)(s_tok + NP);
   float* s_att = s_inc + NP;
-  __shared__ DenseLds<DENSE> s_top;
+  using TopLds = DenseLds<DENSE, BLOCK>;
+  __shared__ TopLds s_top;
   __shared__ int s_sel[MAX_BEAM];          // entry index of the new beam's slot n
   __shared__ int s_n;                      // entries ranked
   // old slots' records
@@ -814,7 +837,7 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select(const HypRec* _
   lds_barrier();
   TRACE_POINT(p, (size_t)u * Wb, 9);
   if constexpr (DENSE) {
-    const int n = dense_top<BLOCK>(p, s_top.top, u, Wb, best, [&](int rank, double J, int slot, int place, float inc, float att) {
+    const int n = dense_top<BLOCK>(p, s_top.top, DenseTopList((unsigned char*)s_J + 20 * NP, Wb), u, Wb, best, [&](int rank, double J, int slot, int place, float inc, float att) {
       const int e = slot * Wb + rank;                      // (an entry of that slot's list, see div_m)
       s_sel[rank] = e; s_J[e] = J; s_inc[e] = inc; s_att[e] = att;
       s_tok[e] = full_v_id(place, min(p.blank_id, p.eos_id), max(p.blank_id, p.eos_id));
@@ -924,7 +947,7 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select(const HypRec* _
 // 101 frames, one wave / four: beam 4, 64 utterances 7.0 / 7.4 us, beam 12, 64 utterances 7.8 / 8.1, 128 9.0 / 10.2.)
 // NEAR: where the score kernel looks at near_frames (one wave: never; found everywhere it cost 1.3 % of a decode at margins of 80).
 // Dynamic LDS: 36 * NP + 32 bytes, NP = Wb * Wb rounded up to whole waves (the list entries and the packed keys); every id a candidate:
-// 20 * NP, and 4 * Tp at least (dense_terms).
+// 20 * NP + DenseTopList::BYTES * Wb, and 4 * Tp at least (dense_terms).
 // The arguments in front of the block are what the first round of loads needs: plain leading arguments reach the wave
 // in registers when it starts (kernel-argument preload), so that those loads do not wait for a load of the arguments.
 // Grid: (1 << sh, Wb, ceil(U / (1 << sh))), sh = l >> 28: utterance z * 2^sh + x, new slot y (as in k_score).
@@ -943,7 +966,8 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select_split(const Hyp
   int* s_tok = (int*)(s_J + NP);                                      // [NP] each
   float* s_inc = (float*)(s_tok + NP);
   float* s_att = s_inc + NP;
-  __shared__ DenseLds<DENSE> s_top;
+  using TopLds = DenseLds<DENSE, BLOCK>;
+  __shared__ TopLds s_top;
   __shared__ DenseNext<DENSE> s_next;
   __shared__ int s_sel[DENSE ? MAX_BEAM : 1];
   __shared__ SurvivorLds s_sx;
@@ -1019,7 +1043,7 @@ __global__ __launch_bounds__(BLOCK, DENSE ? 4 : 1) void k_select_split(const Hyp
 
   int pick_n = -1, pick_0 = -1, ne = 0;                    // entry ranked n, entry ranked 0 (all scalar)
   if constexpr (DENSE) {
-    ne = dense_top<BLOCK>(p, s_top.top, u, Wb, best, [&](int rank, double J, int slot, int place, float inc, float att) {
+    ne = dense_top<BLOCK>(p, s_top.top, DenseTopList((unsigned char*)s_J + 20 * NP, Wb), u, Wb, best, [&](int rank, double J, int slot, int place, float inc, float att) {
       const int e = slot * Wb + rank;                      // (an entry of that slot's list, see div_m)
       s_sel[rank] = e; s_J[e] = J; s_inc[e] = inc; s_att[e] = att;
       s_tok[e] = full_v_id(place, min(p.blank_id, p.eos_id), max(p.blank_id, p.eos_id));

@@ -38,6 +38,15 @@ extern "C" int unit_dense(const float* x, const float* F, const float* mref, int
   for (int j = 0; j < Wb; ++j) { memset(&slots[j], 0, sizeof slots[j]); slots[j].live = 1; slots[j].last = -1; slots[j].s = 1; slots[j].e = T; slots[j].mref = mref[j]; }
   p.U = 1; p.V = V; p.Wb = Wb; p.K = V - 2; p.Tp = Tp; p.blank_id = 0; p.eos_id = V - 1; p.win_m1 = p.win_m2 = -1;
   p.finished = &finished; p.uinfo = &ui; p.cand_inc = out;
+  std::vector<float> att((size_t)Wb * V), kept((size_t)Wb * p.K);
+  std::vector<double> best((size_t)((p.K + 15) / 16) * dense_pitch(Wb));
+  std::vector<DenseEos> eos(Wb);
+  std::vector<DenseLeft> left(Wb);
+  std::vector<GroupOut> grp(Wb);
+  unsigned long long progress = 0;
+  int32_t n_finished = 0;
+  p.dense_att = att.data(); p.cand_att = kept.data(); p.dense_best = best.data(); p.dense_eos = eos.data(); p.dense_left = left.data();
+  p.grp = grp.data(); p.host_progress = &progress; p.n_finished = &n_finished;
   const dim3 grid((unsigned)(p.K + 15) / 16, 1);
   if (Wb <= 16) hipLaunchKernelGGL((k_dense_scores<1, 1>), grid, dim3(256), 0, nullptr, x, F, slots.data(), Wb, Tp, V, p.K, p, 1, 0);
   else hipLaunchKernelGGL((k_dense_scores<1, 2>), grid, dim3(256), 0, nullptr, x, F, slots.data(), Wb, Tp, V, p.K, p, 1, 0);
@@ -46,12 +55,12 @@ extern "C" int unit_dense(const float* x, const float* F, const float* mref, int
 // The best Wb of all (slot, candidate) pairs: increments and attention values inc, att [Wb][K], the slots' base, in chunks of 1 << bits.  Out, per
 // rank: score, slot, place; returns how many reached the pivot (or, after rounds, the last best chunk's score), n_chunks how many chunks.
 template <int BLOCK>
-static void unit_top_kernel(SelectArgs p, DenseTopLds* t, const double* base, int Wb, double* J, int* slot, int* place, int* counts) {
+static void unit_top_kernel(SelectArgs p, DenseTopLds<BLOCK>* t, unsigned char* lds, const double* base, int Wb, double* J, int* slot, int* place, int* counts) {
   double key[DENSE_KEYS];
   dense_fetch<BLOCK>(p, 0, key);
   if ((int)threadIdx.x < Wb) t->base[threadIdx.x] = base[threadIdx.x];
   lds_barrier();
-  const int n = dense_top<BLOCK>(p, *t, 0, Wb, key, [&](int rank, double score, int s, int c, float, float) { J[rank] = score; slot[rank] = s; place[rank] = c; });
+  const int n = dense_top<BLOCK>(p, *t, DenseTopList(lds, Wb), 0, Wb, key, [&](int rank, double score, int s, int c, float, float) { J[rank] = score; slot[rank] = s; place[rank] = c; });
   if (threadIdx.x == 0) { counts[0] = n; counts[1] = t->n_chunks; }
 }
 extern "C" void unit_top(int block, double lambda, const float* inc, const float* att, const double* base, int Wb, int K, int bits, double* J, int* slot, int* place, int* counts) {
@@ -66,11 +75,17 @@ extern "C" void unit_top(int block, double lambda, const float* inc, const float
       for (int k = c << bits; k < min(K, (c + 1) << bits); ++k) b = fmax(b, dense_joint(lambda, base[j], inc[(size_t)j * K + k], att[(size_t)j * K + k]));
     }
   p.best = best.data();
-  DenseTopLds* t = (DenseTopLds*)malloc(sizeof(DenseTopLds));
-  memset(t, 0xa5, sizeof *t);
-  if (block == 1024) hipLaunchKernelGGL(unit_top_kernel<1024>, dim3(1), dim3(1024), 0, nullptr, p, t, base, Wb, J, slot, place, counts);
-  else hipLaunchKernelGGL(unit_top_kernel<256>, dim3(1), dim3(256), 0, nullptr, p, t, base, Wb, J, slot, place, counts);
-  free(t);
+  unsigned char* lds = (unsigned char*)malloc((size_t)DenseTopList::BYTES * Wb);
+  memset(lds, 0xa5, (size_t)DenseTopList::BYTES * Wb);
+  auto run = [&](auto block_size) {
+    constexpr int BLOCK = decltype(block_size)::value;
+    DenseTopLds<BLOCK>* t = (DenseTopLds<BLOCK>*)malloc(sizeof(DenseTopLds<BLOCK>));
+    memset((void*)t, 0xa5, sizeof *t);
+    hipLaunchKernelGGL(unit_top_kernel<BLOCK>, dim3(1), dim3(BLOCK), 0, nullptr, p, t, lds, base, Wb, J, slot, place, counts);
+    free(t);
+  };
+  if (block == 1024) run(Const<1024>()); else run(Const<256>());
+  free(lds);
 }
 // The pivot for rows of log-probabilities: s_hist 256 words, mx the lanes' 256 maxima.
 static void unit_pivot_kernel(uint32_t* s_hist, const float* mx, int K, float* out) {
