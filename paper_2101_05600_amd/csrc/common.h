@@ -147,8 +147,8 @@ struct Params {
   int32_t keep_cand;         // KEEP_*: which of the per-candidate arrays below a step fills (ctcbs_peek; large K needs them)
   // per-step scratch between the score and the select kernel
   int32_t* cand_id;          // [U][Wb][K]
-  float* cand_inc;           // [U][Wb][K] log psi(g.c) - off(g)
-  float* cand_att;           // [U][Wb][K] this step's attention log-prob of c
+  float* cand_inc;           // [U][Wb][K] log psi(g.c) - off(g) (every id a candidate: rows of dense_row(K))
+  float* cand_att;           // [U][Wb][K] this step's attention log-prob of c (likewise)
   float* cand_pre;           // [U][Wb][K] scratch of the eos-run rule
   double* cand_ctc;          // [U][Wb][K] log psi(g.c)
   double* cand_joint;        // [U][Wb][K]
@@ -196,6 +196,7 @@ struct Params {
 #define OPAQUE(a) __asm__ volatile("" : "+s"(a))
 #define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 #define FETCH(ptr) __hip_atomic_load(ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT)
+#define FETCH_SCALAR(ptr) (*(const __attribute__((address_space(4))) int32_t*)(unsigned long long)(ptr))   // (uniform address, written by earlier kernels only)
 #define STORE_ASIDE(v, ptr) __builtin_nontemporal_store(v, ptr)
 #define STORE_FLAG(v, ptr) __hip_atomic_store(ptr, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT)
 #define LOAD_ASIDE(ptr) __builtin_nontemporal_load(ptr)
@@ -205,6 +206,7 @@ struct Params {
 #define OPAQUE(a) do { } while (0)
 #define SCHED_FENCE() do { } while (0)
 #define FETCH(ptr) (*(ptr))
+#define FETCH_SCALAR(ptr) (*(const int32_t*)(ptr))
 #define STORE_ASIDE(v, ptr) (*(ptr) = (v))
 #define STORE_FLAG(v, ptr) __atomic_store_n(ptr, v, __ATOMIC_RELAXED)
 #define LOAD_ASIDE(ptr) (*(ptr))
@@ -300,7 +302,7 @@ struct SelectArgs {
   double beta;
   int32_t win_m1;
   const double* best;        // (Params::dense_best)
-  const float *inc, *att;    // [U][Wb][K]
+  const float *inc, *att;    // [U][Wb][dense_row(K)]
   int32_t K, n_chunks, chunk_bits, eos_id;
   int32_t pitch;             // (dense_pitch)
 };
@@ -308,6 +310,10 @@ struct SelectArgs {
 // entries per chunk of Params::dense_best: odd, so that a chunk's slots and the slots' same chunks lie in places that differ modulo 64
 // (dense_top); the spare entry is never written after ctcbs_create
 __host__ __device__ __forceinline__ int dense_pitch(int Wb) { return Wb | 1; }
+
+// floats in a row of increments, or attention values, where every id is a candidate: whole 128-byte lines, so that a work-group's share of a
+// row is lines of its own (the work-groups of an utterance are on different XCDs, and each writes its part of a shared line to memory by itself)
+__host__ __device__ __forceinline__ int dense_row(int K) { return (K + 31) & ~31; }
 
 // Order-preserving 64-bit image of a joint score; 0: not a competitor (log0, NaN).  And back.
 __device__ __forceinline__ unsigned long long joint_image(double J) {
@@ -371,7 +377,7 @@ __device__ __forceinline__ void report(const P& p, int bad) {
 // store, with the count through the vector path, the wave waited for its row, for the count and for the bus).  By one wave.
 __device__ __forceinline__ void publish_progress(unsigned long long* host_progress, const int32_t* n_finished, int l) {
 #if defined(__AMDGCN__)
-  const int n = *(const __attribute__((address_space(4))) int32_t*)(unsigned long long)n_finished;   // (written by earlier kernels only)
+  const int n = FETCH_SCALAR(n_finished);
   if ((threadIdx.x & 63) == 0)
     __hip_atomic_store(host_progress, (unsigned long long)(unsigned)l << 32 | (unsigned)n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 #else

@@ -228,7 +228,7 @@ static int create_impl(ctcbs* h, const float* d_ctc_logp, const int32_t* h_lens)
   A(p.uinfo, U8);
   {
     const size_t nc = p.keep_cand == KEEP_ARRAYS ? UW * K : 1;   // (not kept: never touched)
-    const size_t nd = h->dense ? UW * K : nc;
+    const size_t nd = h->dense ? UW * dense_row(K) : nc;
     A(p.cand_id, nc); A(p.cand_inc, nd); A(p.cand_att, nd);
     A(p.cand_pre, !h->dense && (c.end_flags & CTCBS_END_EOS_RUN) ? nc : 1);
     A(p.cand_ctc, nc); A(p.cand_joint, p.keep_cand == KEEP_PAIRS ? 2 * UW * K : nc);
@@ -755,8 +755,8 @@ extern "C" int ctcbs_peek(ctcbs_t* h, int32_t what, void* h_dst, size_t bytes, s
       for (size_t g = 0; g < UW && g * K * w < bytes; ++g) {
         if (pairs) HIPCHK(hipMemcpyAsync(both.data(), p.cand_joint + 2 * g * K, 16 * K, hipMemcpyDeviceToHost, h->stream));
         else {
-          HIPCHK(hipMemcpyAsync(inc.data(), p.cand_inc + g * K, 4 * K, hipMemcpyDeviceToHost, h->stream));
-          HIPCHK(hipMemcpyAsync(att.data(), p.cand_att + g * K, 4 * K, hipMemcpyDeviceToHost, h->stream));
+          HIPCHK(hipMemcpyAsync(inc.data(), p.cand_inc + g * dense_row(p.K), 4 * K, hipMemcpyDeviceToHost, h->stream));
+          HIPCHK(hipMemcpyAsync(att.data(), p.cand_att + g * dense_row(p.K), 4 * K, hipMemcpyDeviceToHost, h->stream));
         }
         HIPCHK(hipStreamSynchronize(h->stream));
         for (size_t c = 0; c < K && (g * K + c + 1) * w <= bytes; ++c) {

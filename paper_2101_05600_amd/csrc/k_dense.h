@@ -76,7 +76,7 @@ __device__ __forceinline__ int lanes_max_i(int v) {
 
 template <int N> struct Const { static constexpr int value = N; };
 
-__device__ __forceinline__ void dense_no_slot(DenseSlot* slot) { slot->live = 0; slot->s = 0x7fffffff; slot->e = -1; }
+__device__ __forceinline__ void dense_no_slot(DenseSlot* slot) { slot->s = 0x7fffffff; slot->e = -1; slot->far_s = -1; slot->far_e = 0; }
 
 // What the product needs of a slot of utterance u at step l, by a whole work-group: its hypothesis r (live flag apart) with its forward
 // variables gphi, gb.  dense_f_lds: Tp floats.  Behind the select kernel's part, in the same work-group, it takes 3 us a step less than
@@ -173,7 +173,7 @@ __device__ __forceinline__ void dense_terms(const P& p, float* dense_f_lds, int 
 #pragma unroll
     for (int i = 1; i < BLOCK / 64; ++i) { Lse d; d.m = s_am[i]; d.s = s_rs[i]; c = lse_join(c, d); }
     DenseSlot q;
-    q.live = 1; q.last = rep_ok ? r.last : -1; q.f_lo = lo; q.f_hi = hi;
+    q.last = rep_ok ? r.last : -1; q.f_lo = lo; q.f_hi = hi;
     q.mref = M; q.inc_rep = c.m < LOG0_CLASS ? LOG0F : c.m + fast_logf(c.s);
     q.ref = r.ref;
     q.s = s_lo[0]; q.e = s_hi[0];
@@ -234,9 +234,11 @@ __global__ __launch_bounds__(BLOCK) void k_dense_prep(Params p, int l, int cur) 
 // The joint scores and each slot's best of them took 5.4 us more a launch (24.7 -> 30.1 at 16 utterances of 1500 frames, 5000 ids,
 // beam 20), the select kernel 2.8 more; the launch that made lists of all scores took 10.7.  A decode there 9978 -> 9620 us, of one utterance of
 // 800 frames, beam 10, 2455 -> 2098.  In large batches of short inputs that was more than it saved, until the attention values no longer waited for
-// the finished flag, waves without a slot did nothing and a slot's best took two thirds of the instructions; us a decode with lists, then, now:
-// 128 utterances of 300 to 400 frames, 5000 ids, beam 20 14060 / 14340 / 12945, 690 of 100 to 200, 1000 ids, beam 3 4210 / 4410 / 4245,
-// 2100 of 60 to 120, beam 1 6250 / 7290 / 6910 (there the lists are still better), 16 of 1500, beam 20 9980 / 8480 / 8285.
+// the finished flag, waves without a slot did nothing, a slot's best took two thirds of the instructions, the first loads were fewer, and increments and
+// attention values lay in rows of whole lines (dense_row: 128 utterances of 300 to 400 frames, 5000 ids, beam 20, 12945 -> 12110, the same as
+// with no attention values stored; 16 of 1500 8285 -> 8035); us a decode with lists, then, now: those 128 14060 / 14340 / 12050, 690 of 100 to
+// 200, 1000 ids, beam 3 4210 / 4410 / 3975, 2100 of 60 to 120, beam 1 6240 / 7290 / 6440 (there the lists were better by the selection's 7 us a launch),
+// 16 of 1500, beam 20 9980 / 8480 / 8050.
 template <int NT, int MT>
 __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(const float* __restrict__ xT, const float* __restrict__ F,
                                                          const DenseSlot* __restrict__ slots,
@@ -252,13 +254,17 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
   constexpr int NS = 16 * MT / SLOTS;
   __shared__ float s_att[NS][256];                             // the lanes' attention values
   const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6), n = lane & 15, q = lane >> 4;
-  const int u = blockIdx.y, c0 = (int)blockIdx.x * NC;
+  const int u = blockIdx.y, c0 = (int)blockIdx.x * NC, Kr = dense_row(K);
   const size_t h0 = (size_t)u * Wb;
   PIN4(p.finished, p.uinfo, p.dense_att, p.blank_id);
-  // (all that depends on nothing is asked for together; LOADED: what a uniform address gives is wanted in scalar registers, for which
-  // the compiler waits as soon as it can)
-  int finished = FETCH(p.finished + u), T = FETCH(&p.uinfo[u].T);
-  DenseSlot d = slots[h0 + min(lane, Wb - 1)];
+  PIN4(p.eos_id, p.lambda, p.cand_att, p.cand_inc);
+  // (all that depends on nothing is asked for together.  A load of four words a lane takes the address unit 16 cycles, and with some hundred
+  // short-lived work-groups a compute unit that adds up: every wave asks for the slots' frames alone, the first one for the rest; the flag and the
+  // length go the scalar way.  A launch of 67000 work-groups, 250 -> 234 us, 16 x 1500 frames, 1024 ids, beam 20, a decode 2860 -> 2825)
+  int fin_word = FETCH_SCALAR((const int32_t*)p.finished + (u >> 2)), T = FETCH_SCALAR(&p.uinfo[u].T);
+  DenseRange rg = slots[h0 + min(lane, Wb - 1)];
+  DenseSlot d;
+  if (w == 0) d = slots[h0 + min(lane, Wb - 1)];
   const int lo_ex = min(p.blank_id, p.eos_id), hi_ex = max(p.blank_id, p.eos_id);
   int me = tid;
   auto candidate = [&](int& cc, int& c, int& id) { cc = me & (NC - 1); c = c0 + cc; id = full_v_id(min(c, K - 1), lo_ex, hi_ex); };
@@ -270,12 +276,12 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
 #pragma unroll
   for (int i = 0; i < NS; ++i)
     if (i * SLOTS + first < Wb) att[i] = FETCH((const float*)((const char*)att_u + 4u * ((uint32_t)min(i * SLOTS + tid / NC, Wb - 1) * (uint32_t)V + (uint32_t)id)));
-  LOADED(finished); LOADED(T); LOADED(d.live); LOADED(d.s); LOADED(d.mref);
-  finished = uni(finished); T = uni(T);
+  LOADED(rg.s); LOADED(rg.e); LOADED(rg.far_s); LOADED(rg.far_e);
+  const bool finished = (fin_word >> (8 * (u & 3)) & 0xff) != 0;
   if (blockIdx.x == 0 && u == 0 && w == 3) publish_progress(p.host_progress, p.n_finished, l);
   if (blockIdx.x == 0 && tid < Wb) {                  // the slot's own results: window, eos scores, work
     GroupOut g = {0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
-    if (!finished && d.live) {
+    if (!finished && rg.live()) {
       const DenseEos o = p.dense_eos[h0 + tid];
       const int W = o.e >= o.s ? o.e - o.s + 1 : 0;
       g.win_s = o.s; g.win_e = o.e; g.ctc_eos = o.ctc; g.cells = (long long)K * (long long)W;
@@ -285,19 +291,20 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
     p.grp[h0 + tid] = g;
   }
   if (finished) return;
-  const uint32_t live_slots = (uint32_t)__ballot(lane < Wb && d.live);
+  LOADED(d.low);                                               // (or it is waited for where it is asked for)
+  const uint32_t live_slots = (uint32_t)__ballot(lane < Wb && rg.live());
   // the blocks that any slot has an F for, b0 .. e0 - 1, and those read at first, b1 .. e1 - 1
   int b0, e0, b1, e1;
   {
-    if (tid < Wb) { s_last[tid] = d.last; s_live[tid] = d.live; s_m[tid] = d.mref; s_rep[tid] = d.inc_rep; s_low[tid] = fmaxf(d.low, DENSE_RANGE); s_jb[tid] = dense_base(p.lambda, d); }
-    const bool live = lane < Wb && d.live;                     // (slots in the first 32 lanes: two rows)
+    if (tid < Wb) { s_last[tid] = d.last; s_live[tid] = rg.live(); s_m[tid] = d.mref; s_rep[tid] = d.inc_rep; s_low[tid] = fmaxf(d.low, DENSE_RANGE); s_jb[tid] = dense_base(p.lambda, d); }
+    const bool live = lane < Wb && rg.live();                   // (slots in the first 32 lanes: two rows)
     auto lowest = [](int v) { v = row16_min_i(v); return min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)); };
     auto blocks = [&](int s, int e, int& from, int& to) {
       s = lowest(live ? s : 0x7fffffff); e = -lowest(live ? -e : 1);
       s = min(max(s, 1), T); e = min(e, T);
       from = s >> 5; to = e >= s ? (e >> 5) + 1 : from;
     };
-    blocks(d.s, d.e, b0, e0); blocks(d.s + d.far_s, d.e - d.far_e, b1, e1);
+    blocks(rg.s, rg.e, b0, e0); blocks(rg.s + rg.far_s, rg.e - rg.far_e, b1, e1);
     b1 = max(b1, b0); e1 = max(min(e1, e0), b1);
     if (e0 - b0 <= 4) { b1 = b0; e1 = e0; }                    // (two halves a wave at most: nothing to gain)
   }
@@ -343,7 +350,7 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
   };
   // all of the loop's control is uniform.  whole: nothing is left out; far: a sum that the frames left out may count for
   bool whole = b1 == b0 && e1 == e0, far = false;
-  float* inc_u = p.cand_inc + h0 * (size_t)K;
+  float* inc_u = p.cand_inc + h0 * (size_t)Kr;
   uint32_t again = 0;                                          // a bit for each of the lane's sums that is to be redone
   // the frames read at first; where those left out can count, those before and those behind them too
   f32x4 x[AHEAD][NT], f[AHEAD][MT];
@@ -365,16 +372,16 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
     }
   };
   // (the attention values when the first frames are on their way, so that nothing waits for both in turn; not where that spills:
-  // 128 utterances of 300 to 400 frames, 5000 ids, beam 20, 13590 -> 14030 us a decode, 2100 of 60 to 120, 1000 ids, beam 1, 6970 -> 6920)
+  // 128 utterances of 300 to 400 frames, 5000 ids, beam 20, 13590 -> 14030 us a decode; 2100 of 60 to 120, 1000 ids, beam 1, 6970 -> 6920)
   constexpr bool FRAMES_FIRST = MT * NT < 4;
   if (FRAMES_FIRST) start();
-  float* att_kept = p.cand_att + h0 * (size_t)K;
+  float* att_kept = p.cand_att + h0 * (size_t)Kr;
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
     const int j = i * SLOTS + tid / NC;
     if (i * SLOTS + first >= Wb) break;                        // (uniform)
     s_att[i][tid] = att[i];
-    if ((live_slots >> j & 1u) != 0u && c < K) STORE_ASIDE(att[i], (float*)((char*)att_kept + 4u * (uint32_t)(j * K + c)));
+    if ((live_slots >> j & 1u) != 0u && c < K) STORE_ASIDE(att[i], (float*)((char*)att_kept + 4u * (uint32_t)(j * Kr + c)));
   }
 #pragma unroll 1
   for (int part = 0; part < 3; ++part) {
@@ -442,7 +449,7 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
       inc = rep ? s_rep[js] : inc;
       far |= mine && !rep && !(v > s_low[js]);
       again |= mine && !rep && !(v > DENSE_RANGE) ? 1u << (j0 / SLOTS) : 0u;
-      if (mine) *(float*)((char*)inc_u + 4u * (uint32_t)(js * K + c)) = canon0(inc);
+      if (mine) *(float*)((char*)inc_u + 4u * (uint32_t)(js * Kr + c)) = canon0(inc);
       scored(j0, mine, js, canon0(inc), cc, c, id);
     }
     if (whole) break;
@@ -474,7 +481,7 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
         a = lse_join(a, v);
       }
       const float r = lse_finish<64>(a);
-      if (lane == who) *(float*)((char*)inc_u + 4u * (uint32_t)(j * K + c)) = canon0(r);
+      if (lane == who) *(float*)((char*)inc_u + 4u * (uint32_t)(j * Kr + c)) = canon0(r);
     }
   }
   if (redone != 0ull)                                          // (uniform: the wave holds whole chunks)
@@ -482,6 +489,6 @@ __global__ __launch_bounds__(256, MT * NT == 4 ? 5 : 7) void k_dense_scores(cons
     for (int j0 = 0; j0 + first < Wb; j0 += SLOTS) {
       const int j = j0 + tid / NC, js = min(j, Wb - 1);
       const bool mine = j < Wb && c < K && s_live[js];
-      scored(j0, mine, js, mine ? FETCH(inc_u + (size_t)js * K + c) : LOG0F, cc, c, id);
+      scored(j0, mine, js, mine ? FETCH(inc_u + (size_t)js * Kr + c) : LOG0F, cc, c, id);
     }
 }

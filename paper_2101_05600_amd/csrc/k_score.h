@@ -22,15 +22,18 @@
 #pragma once
 #include "common.h"
 
-// (every id a candidate, see k_dense.h) one beam slot
-struct __align__(64) DenseSlot {
-  int32_t live, last;
+// (every id a candidate, see k_dense.h) one beam slot: its frames,
+struct DenseRange {
   int32_t s, e;              // first and last frame whose F is not 0 (none: s > e)
+  int32_t far_s, far_e;      // frames at either end of s .. e that the product leaves out at first (far_s -1: no hypothesis)
+  __device__ __forceinline__ bool live() const { return far_s >= 0; }
+};
+struct __align__(64) DenseSlot : DenseRange {
+  float low;                 // the sum from which on they cannot count
+  int32_t last;
   float mref, inc_rep;       // largest f term M; increment of the candidate that repeats the last label
-  int32_t far_s, far_e;      // frames at either end of s .. e that the product leaves out at first,
-  float low;                 // and the sum from which on they cannot count
-  int32_t ref;               // reference frame (HypRec)
   double offr, jbase;        // off' + B_r; joint score without this step's terms
+  int32_t ref;               // reference frame (HypRec)
   int32_t f_lo, f_hi;        // first and last frame that has an f term
 };
 

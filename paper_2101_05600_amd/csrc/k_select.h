@@ -594,7 +594,7 @@ __device__ __forceinline__ int dense_top(const SelectArgs& p, DenseTopLds<BLOCK>
       for (int k = 0; k < R; ++k) {
         const int e = e0 + k * BLOCK + tid;
         at[k] = t.chunk[min(e >> bits, n - 1)] + (uint32_t)(e & ((1 << bits) - 1));
-        const size_t g = (h0 + (at[k] >> 27)) * (size_t)p.K + min((int)(at[k] & 0x7ffffffu), p.K - 1);
+        const size_t g = (h0 + (at[k] >> 27)) * (size_t)dense_row(p.K) + min((int)(at[k] & 0x7ffffffu), p.K - 1);
         inc[k] = FETCH(p.inc + g); att[k] = FETCH(p.att + g);
       }
 #pragma unroll

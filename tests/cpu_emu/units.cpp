@@ -33,12 +33,13 @@ extern "C" int unit_dense(const float* x, const float* F, const float* mref, int
   Params p;
   memset(&p, 0, sizeof p);
   UttInfo ui{T, T, 0.0};
-  uint8_t finished = 0;
+  alignas(4) uint8_t finished[4] = {0, 0, 0, 0};
   std::vector<DenseSlot> slots(Wb);
-  for (int j = 0; j < Wb; ++j) { memset(&slots[j], 0, sizeof slots[j]); slots[j].live = 1; slots[j].last = -1; slots[j].s = 1; slots[j].e = T; slots[j].mref = mref[j]; }
+  for (int j = 0; j < Wb; ++j) { memset(&slots[j], 0, sizeof slots[j]); slots[j].last = -1; slots[j].s = 1; slots[j].e = T; slots[j].mref = mref[j]; }
   p.U = 1; p.V = V; p.Wb = Wb; p.K = V - 2; p.Tp = Tp; p.blank_id = 0; p.eos_id = V - 1; p.win_m1 = p.win_m2 = -1;
-  p.finished = &finished; p.uinfo = &ui; p.cand_inc = out;
-  std::vector<float> att((size_t)Wb * V), kept((size_t)Wb * p.K);
+  p.finished = finished; p.uinfo = &ui;
+  std::vector<float> att((size_t)Wb * V), kept((size_t)Wb * dense_row(p.K)), inc(kept.size());
+  p.cand_inc = inc.data();
   std::vector<double> best((size_t)((p.K + 15) / 16) * dense_pitch(Wb));
   std::vector<DenseEos> eos(Wb);
   std::vector<DenseLeft> left(Wb);
@@ -50,6 +51,7 @@ extern "C" int unit_dense(const float* x, const float* F, const float* mref, int
   const dim3 grid((unsigned)(p.K + 15) / 16, 1);
   if (Wb <= 16) hipLaunchKernelGGL((k_dense_scores<1, 1>), grid, dim3(256), 0, nullptr, x, F, slots.data(), Wb, Tp, V, p.K, p, 1, 0);
   else hipLaunchKernelGGL((k_dense_scores<1, 2>), grid, dim3(256), 0, nullptr, x, F, slots.data(), Wb, Tp, V, p.K, p, 1, 0);
+  for (int j = 0; j < Wb; ++j) memcpy(out + (size_t)j * p.K, &inc[(size_t)j * dense_row(p.K)], (size_t)p.K * 4);
   return 0;
 }
 // The best Wb of all (slot, candidate) pairs: increments and attention values inc, att [Wb][K], the slots' base, in chunks of 1 << bits.  Out, per
@@ -66,7 +68,13 @@ static void unit_top_kernel(SelectArgs p, DenseTopLds<BLOCK>* t, unsigned char* 
 extern "C" void unit_top(int block, double lambda, const float* inc, const float* att, const double* base, int Wb, int K, int bits, double* J, int* slot, int* place, int* counts) {
   SelectArgs p;
   memset(&p, 0, sizeof p);
-  p.lambda = lambda; p.inc = inc; p.att = att; p.K = K; p.chunk_bits = bits; p.n_chunks = (K + (1 << bits) - 1) >> bits; p.pitch = dense_pitch(Wb);
+  const int Kr = dense_row(K);
+  std::vector<float> inc_rows((size_t)Wb * Kr), att_rows((size_t)Wb * Kr);
+  for (int j = 0; j < Wb; ++j) {
+    memcpy(&inc_rows[(size_t)j * Kr], inc + (size_t)j * K, (size_t)K * 4);
+    memcpy(&att_rows[(size_t)j * Kr], att + (size_t)j * K, (size_t)K * 4);
+  }
+  p.lambda = lambda; p.inc = inc_rows.data(); p.att = att_rows.data(); p.K = K; p.chunk_bits = bits; p.n_chunks = (K + (1 << bits) - 1) >> bits; p.pitch = dense_pitch(Wb);
   std::vector<double> best((size_t)p.n_chunks * p.pitch, __builtin_nan(""));
   for (int c = 0; c < p.n_chunks; ++c)
     for (int j = 0; j < Wb; ++j) {
