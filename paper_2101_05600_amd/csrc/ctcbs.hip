@@ -22,7 +22,9 @@
 
 static thread_local int g_last_hip = 0;
 
+#ifndef CTCBS_EARLY_GROUPS         // (the CPU build of a test sets 0)
 #define CTCBS_EARLY_GROUPS 256    // groups up to which the score kernel fetches rows before it knows of any utterance (k_score: flags)
+#endif
 
 #define STATIC_LDS 2560            // bytes: no form of the score kernel declares more LDS of its own
 
@@ -362,7 +364,7 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
   if (ea != hipSuccess) return ea;
   const int in_regs = p.restricted && p.V >= 8 && p.V <= 4 * NV4 * BLOCK ? 1 : 0;
   const int sh = 3;                              // (also below eight utterances: one of 437 frames 1090 -> 1035 us a decode)
-  const int flags = in_regs | (p.U * p.Wb <= CTCBS_EARLY_GROUPS ? 2 : 0) | sh << 4;
+  const int flags = in_regs | (p.U * p.Wb <= CTCBS_EARLY_GROUPS ? 2 : 0) | (p.K == 1 ? 4 : 0) | sh << 4;
   const dim3 grid(1u << sh, (unsigned)p.Wb, (unsigned)(p.U + (1 << sh) - 1) >> sh);
   ScoreArgs a;
   a.xT = p.xT; a.Bcum = p.Bcum; a.gphi = p.gphi[h->cur]; a.gb = p.gb[h->cur];

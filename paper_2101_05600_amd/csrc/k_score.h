@@ -556,8 +556,11 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   // A running utterance's rows are fetched before the records are there, all loads in flight together: nearly all of its slots hold
   // hypotheses, and a work-group's time is 2 us until its record is there and 1.8 until its row is (256 utterances, beam 20, 13570 ->
   // 13449 us a decode, eight instead of seven work-groups on a compute unit among them; 48 utterances of 10000 ids 2395 -> 2335).  In
-  // small batches without asking for the flag either.  Not rows of up to 3072 ids, which are soon there: a live slot's row once its record
-  // is (2300 ids: 128 utterances 1997 -> 1980 us a decode, 512 4593 -> 4561, 256 at beam 20 4176 -> 4139, 64 the same).  Whole
+  // small batches without asking for the flag either.  Not rows of up to 3072 ids, which are soon there: the record first, a live slot's row once it
+  // is there (2300 ids: 128 utterances 1997 -> 1980 us a decode, 512 4593 -> 4561, 256 at beam 20 4176 -> 4139, 64 the same); nor, with more than 64
+  // candidates, rows of up to 5120 (100 of 2300 ids, 128 utterances 4310 -> 4250, 200 of 3000 11530 -> 11440, 100 of 5000 4940 -> 4900; longer rows
+  // 5575 -> 5535 the other way).  With one candidate per hypothesis the first slot alone holds one (flags bit 2: 256 utterances, beam 20, 5000 ids
+  // 3080 -> 2490); a row that no registers hold is not waited for (48 of 20000 ids 18460 -> 18210).  Whole
   // 16-byte granules by the lanes in turn; what a row that is not aligned has before and after them by the first lanes.
   const float* arow = att + (size_t)grp * V;
   const bool in_regs = (flags & 1) != 0;
@@ -583,16 +586,22 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
     if (tid < row.n_ex) row.ex = at32(arow, row.ex_id);
   };
   const bool early = (flags & 2) != 0;
+  constexpr bool AHEAD = NV4 > (BIGK ? 5 : 3);
   int rec_at = grp, ui_at = u;                             // (OPAQUE: loads that are not waited for together with the flag)
-  constexpr bool LONG_ROW = NV4 > 3;
-  int go = in_regs && u < U && (early || LONG_ROW);
-  if (!early && LONG_ROW) { OPAQUE(fin_word); go &= ((fin_word >> (8 * (u & 3))) & 0xffu) == 0u; }
-  if (go) fetch_row();
-  OPAQUE(rec_at); OPAQUE(ui_at);
+  if (AHEAD) {
+    int go = in_regs && u < U;
+    if (!early && in_regs) {
+      OPAQUE(fin_word);
+      go &= (int)(((fin_word >> (8 * (u & 3))) & 0xffu) == 0u) & (int)((flags & 4) == 0 || blockIdx.y == 0u);
+    }
+    if (go) fetch_row();
+    OPAQUE(rec_at); OPAQUE(ui_at);
+  }
   // g's record and the utterance's constants: one 64-byte line and one 32-byte entry
   // through the scalar path (uniform addresses, nothing in this kernel writes them)
   const HypRec rec = rec_now[rec_at];
   const UttInfo ui = uinfo[ui_at];
+  if (!AHEAD && in_regs && early && u < U) fetch_row();
   PIN4(rec.live, rec.off, ui.BT, fin_word);
   PIN4(p.xT, p.Bcum, p.gphi, p.gb);
   PIN4(p.lambda, p.beta, p.off_f, p.mode);
@@ -624,7 +633,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
     if (tid == 0 && u < U) score_late(late_args)->grp[grp] = GroupOut{0, 0, 0, -1, LOG0D, LOG0D, 0, {0, 0, 0, 0, 0, 0}};
     return;
   }
-  if (in_regs && !early && !LONG_ROW) fetch_row();
+  if (!AHEAD && in_regs && !early) fetch_row();
 
   TRACE_MARK(0);
   uint32_t* s_work = (uint32_t*)(smem);

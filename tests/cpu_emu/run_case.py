@@ -70,6 +70,8 @@ CASES = {
     # rows that hold fewer numbers than there are candidates, the rest -inf (ids that the decoder masks), and do not start or end
     # on a 16-byte boundary: the masked ids of the lowest numbers are candidates too, each once
     "masked_rows": (dict(n_utt=1, vocab=61, beam=3, cand_k=40, win_m1=5, win_m2=5, end_flags=3, max_len_ratio=0.0, max_len_abs=4), [14]),
+    # one candidate per hypothesis of a row that is fetched ahead of the records: the beam never holds more than one
+    "one_candidate": (dict(n_utt=2, vocab=3100, beam=3, cand_k=1, win_m1=5, win_m2=5, end_flags=3, max_len_ratio=0.0, max_len_abs=4), [14, 9]),
     # logits in, odd vocabulary (radix selection), one candidate per hypothesis
     "logits_odd_vocab": (dict(n_utt=1, vocab=33, beam=2, cand_k=1, win_m1=3, win_m2=8, end_flags=2, att_is_logits=1,
                               max_len_ratio=0.4), [13]),
@@ -212,7 +214,7 @@ def main():
         loads = m.lib().unit_columns
         loads.restype = ctypes.c_longlong
         print(f"emu ok {name} steps={rep['utt_steps']} score_err={rep['max_score_err']:.2e} "
-              f"column_loads_per_term={4 * loads() / max(1, res['cells']):.3f}", flush=True)
+              f"column_loads_per_term={4 * loads() / max(1, res['cells']):.3f} counted={loads()} groups={res['groups']}", flush=True)
 
 
 if __name__ == "__main__":
