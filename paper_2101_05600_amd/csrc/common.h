@@ -443,6 +443,7 @@ __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlan
 // not follow the instruction that wrote its vector register at once: the compiler does not look into the block, and what it
 // puts in front of it may be just that, a copy of v or of one of its halves; hence the s_nop in every block (one for every
 // four values: 12.65 -> 13.0 us a launch of the split select kernel at beam 20).
+// (& in the constraints: the counts are written while the values are still read)
 #if defined(__AMDGCN__)
 #define ABOVE_ADD                                                                                                  \
   "v_addc_co_u32_e64 %0, vcc, 0, %0, vcc\n\tv_addc_co_u32_e64 %0, s[40:41], 0, %0, s[40:41]\n\t"                   \
@@ -464,7 +465,7 @@ template <int I>
 __device__ __forceinline__ void above8(uint32_t v, int& n) {
 #if defined(__AMDGCN__)
   __asm__("s_nop 0\n\t" ABOVE_32("%2", "%3", "%4", "%5") ABOVE_32("%6", "%7", "%8", "%9")
-          : "+v"(n)
+          : "+&v"(n)
           : "v"(v), "i"(I), "i"(I + 1), "i"(I + 2), "i"(I + 3), "i"(I + 4), "i"(I + 5), "i"(I + 6), "i"(I + 7)
           : "vcc", "s40", "s41", "s42", "s43", "s44", "s45");
 #else
@@ -476,7 +477,7 @@ __device__ __forceinline__ void above8(unsigned long long v, int& n) {
 #if defined(__AMDGCN__)
   const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
   __asm__("s_nop 0\n\t" ABOVE_64("%4", "%5", "%6", "%7") ABOVE_64("%8", "%9", "%10", "%11")
-          : "+v"(n)
+          : "+&v"(n)
           : "v"(v), "v"(lo), "v"(hi), "i"(I), "i"(I + 1), "i"(I + 2), "i"(I + 3), "i"(I + 4), "i"(I + 5), "i"(I + 6), "i"(I + 7)
           : "vcc", "s40", "s41", "s42", "s43", "s44", "s45");
 #else
@@ -503,7 +504,7 @@ template <int I>
 __device__ __forceinline__ void above8(uint32_t v, uint32_t a, uint32_t b, int& na, int& nb) {
 #if defined(__AMDGCN__)
   __asm__("s_nop 0\n\t" ABOVE_2("%5", "%6", "%7", "%8") ABOVE_2("%9", "%10", "%11", "%12")
-          : "+v"(na), "+v"(nb)
+          : "+&v"(na), "+&v"(nb)
           : "v"(v), "v"(a), "v"(b), "i"(I), "i"(I + 1), "i"(I + 2), "i"(I + 3), "i"(I + 4), "i"(I + 5), "i"(I + 6), "i"(I + 7)
           : "vcc", "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49");
 #else
