@@ -364,7 +364,7 @@ static hipError_t launch_score_as(ctcbs* h, const Params& p, const float* att, i
   if (ea != hipSuccess) return ea;
   const int in_regs = p.restricted && p.V >= 8 && p.V <= 4 * NV4 * BLOCK ? 1 : 0;
   const int sh = 3;                              // (also below eight utterances: one of 437 frames 1090 -> 1035 us a decode)
-  const int flags = in_regs | (p.U * p.Wb <= CTCBS_EARLY_GROUPS ? 2 : 0) | (p.K == 1 ? 4 : 0) | sh << 4;
+  const int flags = in_regs | (p.U * p.Wb <= CTCBS_EARLY_GROUPS ? 2 : 0) | sh << 4 | (p.K == 1 ? 0 : p.Wb - 1) << 8;
   const dim3 grid(1u << sh, (unsigned)p.Wb, (unsigned)(p.U + (1 << sh) - 1) >> sh);
   ScoreArgs a;
   a.xT = p.xT; a.Bcum = p.Bcum; a.gphi = p.gphi[h->cur]; a.gb = p.gb[h->cur];
@@ -415,8 +415,11 @@ static hipError_t launch_dense_scores(ctcbs* h, const Params& p, int l) {
 #undef CTCBS_DENSE
   return hipGetLastError();
 }
+#ifndef CTCBS_WIDE_CHUNKS          // (a CPU build of the tests sets 1)
+#define CTCBS_WIDE_CHUNKS 1024     // work-groups of 32 candidates from which on there are no smaller ones
+#endif
 static int dense_chunk_bits(const Params& p) {
-  return (long long)p.U * ((p.K + 31) / 32) >= 1024 || (long long)dense_pitch(p.Wb) * ((p.K + 15) / 16) > 256 * DENSE_KEYS ? 5 : 4;
+  return (long long)p.U * ((p.K + 31) / 32) >= CTCBS_WIDE_CHUNKS || (long long)dense_pitch(p.Wb) * ((p.K + 15) / 16) > 256 * DENSE_KEYS ? 5 : 4;
 }
 static bool split_select(const Params& p) { return p.U * p.Wb <= CTCBS_SPLIT_GROUPS; }
 static hipError_t launch_dense(ctcbs* h, const Params& p, const float* att, int l) {

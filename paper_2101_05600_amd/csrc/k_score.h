@@ -559,8 +559,8 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   // small batches without asking for the flag either.  Not rows of up to 3072 ids, which are soon there: the record first, a live slot's row once it
   // is there (2300 ids: 128 utterances 1997 -> 1980 us a decode, 512 4593 -> 4561, 256 at beam 20 4176 -> 4139, 64 the same); nor, with more than 64
   // candidates, rows of up to 5120 (100 of 2300 ids, 128 utterances 4310 -> 4250, 200 of 3000 11530 -> 11440, 100 of 5000 4940 -> 4900; longer rows
-  // 5575 -> 5535 the other way).  With one candidate per hypothesis the first slot alone holds one (flags bit 2: 256 utterances, beam 20, 5000 ids
-  // 3080 -> 2490); a row that no registers hold is not waited for (48 of 20000 ids 18460 -> 18210).  Whole
+  // 5575 -> 5535 the other way).  With one candidate per hypothesis the first slot alone ever holds one (the last slot that can is in flags from bit 8 on: 256 utterances, beam 20, 5000 ids,
+  // 3080 -> 2480); a row that no registers hold is not waited for (48 of 20000 ids 18460 -> 18210).  Whole
   // 16-byte granules by the lanes in turn; what a row that is not aligned has before and after them by the first lanes.
   const float* arow = att + (size_t)grp * V;
   const bool in_regs = (flags & 1) != 0;
@@ -589,11 +589,8 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   constexpr bool AHEAD = NV4 > (BIGK ? 5 : 3);
   int rec_at = grp, ui_at = u;                             // (OPAQUE: loads that are not waited for together with the flag)
   if (AHEAD) {
-    int go = in_regs && u < U;
-    if (!early && in_regs) {
-      OPAQUE(fin_word);
-      go &= (int)(((fin_word >> (8 * (u & 3))) & 0xffu) == 0u) & (int)((flags & 4) == 0 || blockIdx.y == 0u);
-    }
+    int go = in_regs && u < U && (int)blockIdx.y <= flags >> 8;
+    if (!early && (NV4 < 16 || in_regs)) { OPAQUE(fin_word); go &= ((fin_word >> (8 * (u & 3))) & 0xffu) == 0u; }   // (up to 10240 ids: always there)
     if (go) fetch_row();
     OPAQUE(rec_at); OPAQUE(ui_at);
   }
