@@ -422,7 +422,7 @@ def dense_roofline(score_ms, n_launches, terms, beam, traffic):
     us = score_ms * 1e3 / max(n_launches, 1)
     ach = traffic / us * 1e-3 if traffic else None
     return {"bound": "hbm", "kernel": "k_dense_scores", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": ach / HBM_PEAK_GBS if ach else None, "achieved_how": "measured bytes over the time of the HIP events, which span k_dense_prep too",
+            "frac": ach / HBM_PEAK_GBS if ach else None, "achieved_how": "measured bytes over the time of the HIP events, which span k_dense_prep too where it is launched (the first step, more than 2048 groups)",
             "traffic": traffic, "avg_launch_us": us, "bytes_of_all_frames_per_launch": 4.0 * terms / beam / max(n_launches, 1),
             "effective_terms_per_sec": terms / (score_ms * 1e-3)}
 

@@ -31,10 +31,17 @@ CASES = {
     # every id a candidate, few ids: the score kernel ranks the list itself
     "all_candidates": (dict(n_utt=1, vocab=12, beam=2, cand_k=0, win_m1=-1, win_m2=-1, end_flags=3,
                             max_len_ratio=0.4), [11]),
-    # every id a candidate, more than one wave ranks: the matrix form of the prefix scores and the list builder, more than
+    # every id a candidate, more than one wave ranks: the matrix form of the prefix scores and the best of all pairs, more than
     # one block of frames per wave
     "all_candidates_matrix": (dict(n_utt=1, vocab=67, beam=2, cand_k=0, win_m1=-1, win_m2=-1, end_flags=3,
                                    max_len_ratio=0.0, max_len_abs=2), [131]),
+    # the same with ids that are all alike and two tiles of slots: from the second step on more chunks reach the pivot than the select
+    # kernel's list of them holds, and it goes round by round
+    "matrix_ties": (dict(n_utt=1, vocab=130, beam=17, cand_k=0, win_m1=-1, win_m2=-1, end_flags=3,
+                         max_len_ratio=0.0, max_len_abs=2), [9]),
+    # more than 64 entries in the short list: ranked two per lane
+    "short_list_of_two_per_lane": (dict(n_utt=1, vocab=1027, beam=2, cand_k=60, win_m1=5, win_m2=5, end_flags=3,
+                                        max_len_ratio=0.0, max_len_abs=2), [12]),
     # fewer ids than beam slots: most slots never hold a hypothesis, their records are never written
     "all_candidates_few_ids": (dict(n_utt=2, vocab=6, beam=6, cand_k=0, win_m1=-1, win_m2=-1, end_flags=3,
                                     max_len_ratio=0.4), [9, 7]),
@@ -186,6 +193,10 @@ def main():
             ctc[:, :, 1:8] = -70.0
         if name in ("sharp_posteriors", "few_candidates"):
             peaked_ctc(ctc, 9, height=40.0)
+        if name == "matrix_ties":
+            ctc[:, :, 1:] = ctc[:, :, 1:2]
+            alike = lambda a: np.where(np.isnan(a), a, np.float32(-4.0)).astype(np.float32)
+            kw = dict(att_fn=alike)
         if name == "masked_rows":
             def masked(a):
                 a = a.copy()

@@ -78,17 +78,17 @@ def runs(tmp_path_factory):
     plan = {
         "asan": (asan, ASAN_ENV, dict(sanitize=True),
                  ["windowed", "batch_window", "all_candidates", "all_candidates_few_ids", "logits_odd_vocab", "static_step", "masked_rows"],
-                 ["all_candidates_matrix"],
-                 ["pivot", "wide_window_eos_run"], ["pivot_k80", "radix_wide_ties", "k80_eos_run", "k80_whole_eos_run"]),
+                 ["all_candidates_matrix", "short_list_of_two_per_lane"], ["matrix_ties"],
+                 ["pivot", "wide_window_eos_run", "one_candidate"], ["pivot_k80", "radix_wide_ties", "k80_eos_run", "k80_whole_eos_run"]),
         # the first steps of a fixed subset of the random configurations that tests/test_gpu_random_configs.py
         # decodes on the GPU (same table, tests/random_cases.py), device memory starting out as garbage
         "asan_random": (asan, ASAN_ENV, dict(sanitize=True), *[[f"random:{a}:{b}:{c}"] for a, b, c in CPU_SUBSET]),
         "asan_near": (asan, ASAN_ENV, dict(sanitize=True), ["near_frames"], ["sharp_posteriors", "few_candidates"]),
-        # the select kernel of large batches, 16, 64 and 32 lanes per new hypothesis
-        "asan_per_utterance": (asan, ASAN_ENV, dict(sanitize=True, defines=["CTCBS_SPLIT_GROUPS=0"]), ["windowed"], ["batch_window"],
-                               ["near_frames"]),
+        # the select kernel of large batches, 16, 64 and 32 lanes per new hypothesis, and its matrix form with 32 candidates per work-group
+        "asan_per_utterance": (asan, ASAN_ENV, dict(sanitize=True, defines=["CTCBS_SPLIT_GROUPS=0", "CTCBS_WIDE_CHUNKS=1"]), ["windowed"], ["batch_window"],
+                               ["near_frames"], ["all_candidates_matrix", "matrix_ties"]),
         # executor: the job queue with two host threads on two handles
-        "tsan": (tsan, TSAN_ENV, dict(sanitize="thread"), ["windowed"], ["batch_window"], ["executor"]),
+        "tsan": (tsan, TSAN_ENV, dict(sanitize="thread"), ["windowed"], ["batch_window"], ["executor"], ["all_candidates_matrix"], ["matrix_ties"]),
         "tsan_planted": (tsan, TSAN_ENV, dict(sanitize="thread", plant=PLANT), ["windowed"]),
     }
 
@@ -118,14 +118,14 @@ def test_kernels_under_address_and_ub_sanitizers(runs):
     r, out = _result(runs, "asan")
     assert r.returncode == 0, out[-4000:]
     assert "ERROR: AddressSanitizer" not in out and "runtime error:" not in out, out[-4000:]
-    assert out.count("emu ok") == 14, out[-2000:]
+    assert out.count("emu ok") == 17, out[-2000:]
 
 
 def test_select_kernel_of_large_batches_under_address_sanitizer(runs):
     r, out = _result(runs, "asan_per_utterance")
     assert r.returncode == 0, out[-4000:]
     assert "ERROR: AddressSanitizer" not in out and "runtime error:" not in out, out[-4000:]
-    assert out.count("emu ok") == 3, out[-2000:]
+    assert out.count("emu ok") == 5, out[-2000:]
 
 
 def test_sums_over_near_frames_under_address_sanitizer(runs):
@@ -148,7 +148,7 @@ def test_kernels_under_thread_sanitizer(runs):
     r, out = _result(runs, "tsan")
     assert r.returncode == 0, out[-4000:]
     assert "WARNING: ThreadSanitizer" not in out, out[-6000:]
-    assert out.count("emu ok") == 3, out[-2000:]
+    assert out.count("emu ok") == 5, out[-2000:]
 
 
 def test_thread_sanitizer_run_notices_a_missing_barrier(runs):

@@ -1,5 +1,5 @@
-"""Every id a candidate: the matrix form of the prefix scores and the list builder, at the edges of their tiles (16
-candidates, 16 slots, 16-frame blocks, chunks of 64 candidates for large batches) and where a sum leaves the range of
+"""Every id a candidate: the matrix form of the prefix scores, at the edges of its tiles (16
+candidates, 16 slots, 16-frame blocks, chunks of 32 candidates for large batches) and where a sum leaves the range of
 the product.  Against the oracle, step by step (tolerances as in test_gpu_parity.py)."""
 import numpy as np
 import pytest
@@ -42,7 +42,7 @@ def test_windows_of_the_slots_together():
     _decode(vocab=150, beam=6, t_lo=120, t_hi=300, win_m1=9, win_m2=14, steps=20)
 
 
-# 64 candidates per work-group (chunks x utterances >= 512), an unused slot among them
+# 32 candidates per work-group (chunks x utterances >= 1024), an unused slot among them
 def test_large_batch():
     _decode(vocab=700, n_utt=50, beam=4, lens=[40 + u % 7 if u != 5 else 0 for u in range(50)], check=[0, 6, 49], steps=3)
 

@@ -28,7 +28,7 @@ def test_best_of_all_pairs(vocab, beam, utts, same):
     assert rep["max_ctc_err"] < 1e-4 and rep["max_score_err"] < 1e-4
 
 
-# scores far below zero, whose upper halves lie close together (a pivot short of some of their bits lets too many chunks through)
+# scores far below zero, whose upper halves lie close together (how many chunks reach the pivot there: tests/test_kernel_units.py)
 def test_scores_far_below_zero():
     w = gen.workload("cfg1")
     w.update(n_utt=2, vocab=3001, beam=20, cand_k=0, win_m1=-1, win_m2=-1, end_flags=3, max_len_ratio=0.0, max_len_abs=6)

@@ -111,7 +111,7 @@ def test_degenerate_posteriors():
 
 
 def test_very_large_unrestricted_vocabulary():
-    """Every id a candidate on a vocabulary of more than 8192: the list builder's widest form in registers."""
+    """Every id a candidate on a vocabulary of more than 8192."""
     w = small("cfg1", n_utt=2, t_lo=25, t_hi=40, vocab=9001, beam=3, cand_k=0, win_m1=-1, win_m2=-1,
               end_flags=3, max_len_abs=7)
     rep, res = run(w)

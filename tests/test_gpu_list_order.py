@@ -5,9 +5,9 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-# (vocab, candidates): every id (the score kernel's own list up to 66 ids, then 4, 20, 32 and 64 scores per lane, then
-# scores read for each pass), restricted sets of more than one wave's and more than one work-group's, and those beyond 8192
-FORMS = [(40, 0), (66, 0), (67, 0), (1000, 0), (4000, 0), (8194, 0), (8195, 0), (16386, 0), (16387, 0), (20001, 0), (200, 100), (400, 300), (5000, 4000), (9001, 8500)]
+# (vocab, candidates): every id (the score kernel's own list up to 66 ids, then the matrix form: the best of all pairs, no lists), restricted
+# sets of more than one wave's and more than one work-group's: 4, 20 and 32 scores per lane, and those beyond 8192, read for each pass
+FORMS = [(40, 0), (66, 0), (67, 0), (1000, 0), (4000, 0), (8194, 0), (8195, 0), (16386, 0), (16387, 0), (20001, 0), (200, 100), (400, 300), (5000, 4000), (9001, 7000), (9001, 8500)]
 
 
 def first_step(vocab, cand_k, att, ctc, beam=4):
@@ -62,7 +62,7 @@ def test_equal_scores_go_by_id(vocab, cand_k):
 
 
 # whole steps against the oracle where the scores are read again for each pass
-@pytest.mark.parametrize("vocab,cand_k", [(16387, 0), (17003, 0), (9001, 8500)])
+@pytest.mark.parametrize("vocab,cand_k", [(16387, 0), (17003, 0), (9001, 7000), (9001, 8500)])
 def test_many_candidates_against_the_oracle(vocab, cand_k):
     import gen
     from helpers import lockstep_decode

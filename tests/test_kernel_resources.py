@@ -45,12 +45,15 @@ def test_score_kernels_own_lds_is_what_the_host_counts(compiled):
 
 
 def test_select_kernels_fit_64_kb(compiled):
-    """Own LDS and what the host asks for: beam 32, 1024 list entries; every id a candidate: no keys, the longest input's f terms."""
+    """Own LDS and what the host asks for: beam 32, 1024 list entries; every id a candidate (the last template argument): no keys,
+    640 bytes a beam slot, or the longest input's f terms."""
     report, _ = compiled
     sizes = {k: v["LDS Size"] for k, v in report.items() if "k_select" in k}
-    dense = [v for k, v in sizes.items() if re.search(r"k_select(_splitILi256ELb0E|ILi\d+ELi\d+ELi8E)Lb1E", k)]
-    assert len(dense) == 10 and max(dense) + max(20 * 1024, 4 * 6176) <= 65536
-    assert max(v for v in sizes.values() if v < 16384) + 36 * 1024 + 32 <= 65536
+    dense = [v for k, v in sizes.items() if re.search(r"k_select(_split)?I[^v]*Lb1EEv", k) and not re.search(r"_splitILi\d+ELb1ELb0E", k)]
+    lists = [v for k, v in sizes.items() if re.search(r"k_select(_split)?I[^v]*Lb0EEv", k)]
+    assert len(dense) == 10 and len(lists) == 12 and len(sizes) == 22
+    assert max(dense) + max(20 * 1024 + 640 * 32, 4 * 6176) <= 65536
+    assert max(lists) + 36 * 1024 + 32 <= 65536
 
 
 def test_no_packed_fp32_arithmetic(compiled):

@@ -164,7 +164,7 @@ def check_top(inc, base, got):
 # in the maxima: 4 to 9 Wb at numbers of chunks that are multiples of 64; a pivot of 14 bits of the range, scores on both sides of
 # zero: up to 10 Wb.)
 @pytest.mark.parametrize("Wb,K,bits", [(1, 65, 4), (3, 998, 5), (8, 2048, 4), (16, 1022, 4), (20, 1022, 4), (20, 4094, 5), (20, 4998, 5), (32, 66, 4), (32, 510, 4), (32, 2048, 5), (32, 4094, 5), (10, 65533, 5)])
-@pytest.mark.parametrize("level,spread", [(-40.0, 4.0), (-1500.0, 4.0), (0.0, 3.0)])
+@pytest.mark.parametrize("level,spread", [(-1500.0, 4.0), (0.0, 3.0)])
 def test_best_pairs_from_few_chunks(units, Wb, K, bits, level, spread):
     for zipf in (0, 1):
         rng = np.random.default_rng(100 * Wb + zipf)
