@@ -560,7 +560,7 @@ __global__ __launch_bounds__(BLOCK, (BIGK || NV4 > 10 ? 4 : (NV4 <= 5 ? (NEAR &&
   // is there (2300 ids: 128 utterances 1997 -> 1980 us a decode, 512 4593 -> 4561, 256 at beam 20 4176 -> 4139, 64 the same); nor, with more than 64
   // candidates, rows of up to 5120 (100 of 2300 ids, 128 utterances 4310 -> 4250, 200 of 3000 11530 -> 11440, 100 of 5000 4940 -> 4900; longer rows
   // 5575 -> 5535 the other way).  With one candidate per hypothesis the first slot alone ever holds one (the last slot that can is in flags from bit 8 on: 256 utterances, beam 20, 5000 ids,
-  // 3080 -> 2480); a row that no registers hold is not waited for (48 of 20000 ids 18460 -> 18210).  Whole
+  // 3080 -> 2480); a row that no registers hold is not waited for (48 of 20000 ids 18460 -> 18210 to 18410, by the build).  Whole
   // 16-byte granules by the lanes in turn; what a row that is not aligned has before and after them by the first lanes.
   const float* arow = att + (size_t)grp * V;
   const bool in_regs = (flags & 1) != 0;
