@@ -163,7 +163,7 @@ def check_top(inc, base, got):
 # lets those through that share a maximum with a better one, up to 2 Wb measured in decodes; bound 3 Wb and a few.  (Slots one after the other
 # in the maxima: 4 to 9 Wb at numbers of chunks that are multiples of 64; a pivot of 14 bits of the range, scores on both sides of
 # zero: up to 10 Wb.)
-@pytest.mark.parametrize("Wb,K,bits", [(1, 65, 4), (3, 998, 5), (8, 2048, 4), (16, 1022, 4), (20, 1022, 4), (20, 4094, 5), (20, 4998, 5), (32, 66, 4), (32, 510, 4), (32, 2048, 5), (32, 4094, 5), (10, 65533, 5)])
+@pytest.mark.parametrize("Wb,K,bits", [(1, 65, 4), (3, 998, 5), (16, 1022, 4), (20, 4998, 5), (32, 510, 4), (32, 2048, 5), (32, 4094, 5)])
 @pytest.mark.parametrize("level,spread", [(-1500.0, 4.0), (0.0, 3.0)])
 def test_best_pairs_from_few_chunks(units, Wb, K, bits, level, spread):
     for zipf in (0, 1):
@@ -178,7 +178,7 @@ def test_best_pairs_from_few_chunks(units, Wb, K, bits, level, spread):
 
 # More chunks or more scores at the pivot than fit: all scores equal, two levels, equal in their upper halves; and hardly any score at all.
 # Equal scores go by slot and place.
-@pytest.mark.parametrize("Wb,K,bits,block", [(32, 2048, 4, 256), (32, 4094, 5, 1024), (20, 1022, 4, 256), (2, 9001, 4, 256), (3, 70, 4, 256), (32, 600, 5, 256)])
+@pytest.mark.parametrize("Wb,K,bits,block", [(32, 2048, 4, 256), (20, 1022, 4, 1024), (3, 70, 4, 256)])
 def test_best_pairs_of_scores_that_agree(units, Wb, K, bits, block):
     rng = np.random.default_rng(K)
     att = rng.standard_normal((Wb, K)).astype(np.float32)
@@ -216,15 +216,15 @@ def test_sums_of_sharp_posteriors_read_few_frames_more(tmp_path):
 # Whose attention rows are fetched in batches that do not fetch them blindly: live slots' alone where that is known in time, from the record (short rows, many
 # candidates) or because the beam cannot hold more than one hypothesis (one candidate each; 256 utterances, beam 20, 5000 ids: a
 # decode took 3080 us with the dead slots' rows, 2490 without).
-@pytest.mark.parametrize("case", ["one_candidate", "pivot_k80", "pivot"])
-def test_no_rows_of_dead_slots(tmp_path, case):
+def test_no_rows_of_dead_slots(tmp_path):
     fetch = "auto fetch_row = [&]() {"
     so = build_emu.build(str(tmp_path), sanitize=False, units=True, defines=["CTCBS_EARLY_GROUPS=0"],
                          plant=("k_score.h", fetch, fetch + " if (threadIdx.x == 0) __atomic_fetch_add(&emu::n_columns, 1, __ATOMIC_RELAXED);"))
-    r = subprocess.run([sys.executable, os.path.join(HERE, "cpu_emu", "run_case.py"), so, case], capture_output=True, text=True, timeout=300)
-    assert r.returncode == 0, r.stdout + r.stderr
-    rows, groups = re.search(r"counted=(\d+) groups=(\d+)", r.stdout).groups()
-    assert 0 < int(rows) == int(groups), r.stdout
+    for case in ("one_candidate", "pivot_k80", "pivot"):     # (each a process: the count is of all that it decodes)
+        r = subprocess.run([sys.executable, os.path.join(HERE, "cpu_emu", "run_case.py"), so, case], capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stdout + r.stderr
+        rows, groups = re.search(r"counted=(\d+) groups=(\d+)", r.stdout).groups()
+        assert 0 < int(rows) == int(groups), r.stdout
 
 
 # The host's lead over the device: two intervals, for close looks five steps at most
